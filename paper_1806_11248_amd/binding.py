@@ -177,13 +177,43 @@ def new_tree_leaves(max_leaves: int) -> dict:
     return t
 
 
+def _address(a) -> int:
+    try:
+        return C.addressof(C.c_char.from_buffer(a))   # a third of the time of a.ctypes.data
+    except (TypeError, ValueError, BufferError):      # read-only, empty or strided
+        return a.ctypes.data
+
+
+_TREE_NAMES = [nm for nm, _ in _TREE_FIELDS]
+
+
 def _tree_struct(t: dict) -> Tree:
-    s = Tree()
-    s.capacity = int(t["capacity"])
-    s.n_nodes = int(t["n_nodes"])
-    for nm, _ in _TREE_FIELDS:
-        setattr(s, nm, t[nm].ctypes.data)
-    return s
+    return Tree(int(t["capacity"]), int(t["n_nodes"]), *[_address(t[nm]) for nm in _TREE_NAMES])
+
+
+# what prediction reads of a tree, in gbt_tree's order; the other addresses stay NULL
+_WALK_NAMES = ["feature", "bin", "default_left", "left", "right", "threshold", "weight"]
+_WORDS = C.sizeof(Tree) // 8
+
+
+def _tree_table(trees):
+    """An array of gbt_tree for prediction, filled as 64-bit words: a model has hundreds of trees and seven addresses each,
+    and field by field that took longer than the walk itself (100 trees: 0.7 ms)."""
+    arr = (Tree * len(trees))()
+    if not trees:
+        return arr
+    words = np.zeros((len(trees), _WORDS), np.int64)
+    counts = words.view(np.int32)                 # the two counts share the first word
+    counts[:, 0] = [t["capacity"] for t in trees]
+    counts[:, 1] = [t["n_nodes"] for t in trees]
+    view, at = C.c_char.from_buffer, C.addressof
+    try:
+        flat = [at(view(t[nm])) for t in trees for nm in _WALK_NAMES]
+    except (TypeError, ValueError, BufferError):
+        flat = [_address(t[nm]) for t in trees for nm in _WALK_NAMES]
+    words[:, 1:1 + len(_WALK_NAMES)] = np.array(flat, np.int64).reshape(len(trees), -1)
+    C.memmove(arr, words.ctypes.data, words.nbytes)
+    return arr
 
 
 def _ptr(t):
@@ -529,7 +559,7 @@ class Context:
 
     # -- Sec. 2.4 ------------------------------------------------------------
     def predict_sparse(self, trees, margin, eta: float, rowptr, ent, n, F, max_bins):
-        arr = (Tree * len(trees))(*[_tree_struct(t) for t in trees])
+        arr = _tree_table(trees)
         ws_bytes = self.lib.gbt_predict_workspace_bytes(arr, len(trees))
         ws = self.workspace("predict", ws_bytes)
         self._check(self.lib.gbt_predict_sparse(self.h, arr, len(trees), _ptr(rowptr), _ptr(ent), n, F, max_bins, eta,
@@ -537,7 +567,7 @@ class Context:
         return margin
 
     def predict(self, trees, margin, eta: float, *, packed=None, bits=0, missing_sym=0, X=None, n=None, F=None):
-        arr = (Tree * len(trees))(*[_tree_struct(t) for t in trees])
+        arr = _tree_table(trees)
         if X is not None:
             n, F = X.shape
         ws_bytes = self.lib.gbt_predict_workspace_bytes(arr, len(trees))

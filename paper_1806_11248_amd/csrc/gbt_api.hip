@@ -147,7 +147,8 @@ int32_t sync(gbt_ctx *ctx) {
     return GBT_OK;
 }
 
-int32_t stage(gbt_ctx *ctx, const void *host, size_t bytes, char **slot) {
+// A slot of `bytes` bytes for the caller to fill.
+int32_t reserve(gbt_ctx *ctx, size_t bytes, char **slot) {
     GBT_REQUIRE(ctx, bytes <= kUploadBytes, GBT_EUNSUPPORTED, "job table of %zu bytes exceeds staging", bytes);
     const size_t need = gbt_align(bytes ? bytes : 1);
     if (ctx->up_off + need > kUploadBytes) {
@@ -155,8 +156,14 @@ int32_t stage(gbt_ctx *ctx, const void *host, size_t bytes, char **slot) {
         if (st != GBT_OK) return st;
     }
     *slot = up(ctx) + ctx->up_off;
-    memcpy(*slot, host, bytes);
     ctx->up_off += need;
+    return GBT_OK;
+}
+
+int32_t stage(gbt_ctx *ctx, const void *host, size_t bytes, char **slot) {
+    int32_t st = reserve(ctx, bytes, slot);
+    if (st != GBT_OK) return st;
+    memcpy(*slot, host, bytes);
     return GBT_OK;
 }
 
@@ -1942,7 +1949,7 @@ size_t predict_plain_bytes(const gbt_tree *trees, int32_t n_trees) {
     for (int t = 0; t < n_trees; ++t) o += tree_bytes(trees[t].n_nodes);
     return o + 256;
 }
-// ... and behind it the form of the many-trees kernel: 8-byte nodes, weights, three small tables
+// ... or the form of the many-trees kernel: 8-byte nodes, weights, three small tables
 struct BatchLayout {
     size_t nodes, wts, tree_off, tree_depth, group_end, total;
 };
@@ -1957,6 +1964,15 @@ BatchLayout batch_layout(size_t base, int64_t total_nodes, int32_t n_trees) {
     L.total = o;
     return L;
 }
+// A threshold in the order of the many-trees kernel's integer values (gbt_batch_node): value + a >= thr sends a row right.
+int32_t batch_threshold(float thr, uint32_t a) {
+    if (thr != thr) return INT32_MIN + (int32_t)a;   // no value lies below: every one goes right, a missing one by default
+    const float z = thr + 0.0f;                      // -0 and +0 compare equal as floats
+    int32_t b;
+    memcpy(&b, &z, 4);
+    const int32_t key = b ^ ((b >> 31) & 0x7fffffff);
+    return key + (int32_t)a;
+}
 int64_t total_nodes_of(const gbt_tree *trees, int32_t n_trees) {
     int64_t s = 0;
     for (int t = 0; t < n_trees; ++t) s += std::max(trees[t].n_nodes, 0);
@@ -1966,7 +1982,7 @@ int64_t total_nodes_of(const gbt_tree *trees, int32_t n_trees) {
 
 extern "C" size_t gbt_predict_workspace_bytes(const gbt_tree *trees, int32_t n_trees) {
     if (!trees || n_trees < 0) return 0;
-    return batch_layout(predict_plain_bytes(trees, n_trees), total_nodes_of(trees, n_trees), n_trees).total;
+    return std::max(predict_plain_bytes(trees, n_trees), batch_layout(0, total_nodes_of(trees, n_trees), n_trees).total);
 }
 
 // Stages the trees in `workspace` and walks them: margin += eta * leaf weight per tree, or (leaf_out,
@@ -1994,15 +2010,16 @@ static int32_t predict_impl(gbt_ctx *ctx, const gbt_tree *trees, int32_t n_trees
                                                    : predict_plain_bytes(trees, n_trees)),
                 GBT_ENOMEM, "workspace too small");
     bool compact_ok = true;   // the 8-byte node form of the register-window kernel applies
-    // stage the trees: table of offsets, then each tree's arrays
-    std::vector<char> host(predict_plain_bytes(trees, n_trees), 0);
-    std::vector<int> depths((size_t)n_trees, 0);
     bool ordered = true;      // every child comes after its parent, in every tree
-    DevTree *tab = (DevTree *)host.data();
-    size_t o = gbt_align((size_t)n_trees * sizeof(DevTree));
+    std::vector<int> depths((size_t)n_trees, 0), depth_of;
+    int max_nodes = 1;
     for (int t = 0; t < n_trees; ++t) {
         const gbt_tree &T = trees[t];
         GBT_REQUIRE(ctx, T.n_nodes >= 1 && T.n_nodes <= T.capacity, GBT_EINVAL, "tree %d: bad n_nodes", t);
+        max_nodes = std::max(max_nodes, T.n_nodes);
+        depth_of.assign((size_t)T.n_nodes, 0);   // the tree's depth (steps of its longest walk), if every child comes after its parent
+        int tree_depth = 0;
+        bool in_order = true;
         for (int i = 0; i < T.n_nodes; ++i) {
             if (T.feature[i] < 0) continue;
             if (T.right[i] != T.left[i] + 1 || T.feature[i] >= (1 << 20) || T.bin[i] < 0 || T.bin[i] >= 4096)
@@ -2010,103 +2027,111 @@ static int32_t predict_impl(gbt_ctx *ctx, const gbt_tree *trees, int32_t n_trees
             GBT_REQUIRE(ctx, T.feature[i] < F && T.left[i] >= 0 && T.left[i] < T.n_nodes && T.right[i] >= 0 &&
                                  T.right[i] < T.n_nodes,
                         GBT_EINVAL, "tree %d node %d: bad feature or child id", t, i);
-        }
-        // the tree's depth (steps of its longest walk), if every child comes after its parent
-        std::vector<int> depth_of((size_t)T.n_nodes, 0);
-        int tree_depth = 0;
-        for (int i = 0; i < T.n_nodes; ++i) {
-            if (T.feature[i] < 0) continue;
-            if (T.left[i] <= i || T.right[i] <= i) {
-                compact_ok = false;
-                ordered = false;
-                break;
+            in_order = in_order && T.left[i] > i && T.right[i] > i;
+            if (in_order) {
+                depth_of[T.left[i]] = depth_of[T.right[i]] = depth_of[i] + 1;
+                tree_depth = std::max(tree_depth, depth_of[i] + 1);
             }
-            depth_of[T.left[i]] = depth_of[T.right[i]] = depth_of[i] + 1;
-            tree_depth = std::max(tree_depth, depth_of[i] + 1);
         }
-        const size_t a4 = gbt_align((size_t)T.n_nodes * 4);
-        tab[t].n_nodes = T.n_nodes;
-        tab[t].pad = tree_depth;
+        if (!in_order) compact_ok = ordered = false;
         depths[(size_t)t] = tree_depth;
-        const void *src4[6] = {T.feature, T.bin, T.default_left, T.left, T.right, T.threshold};
-        uint64_t *dst4[6] = {&tab[t].feature, &tab[t].bin, &tab[t].default_left, &tab[t].left, &tab[t].right,
-                             &tab[t].threshold};
-        for (int k = 0; k < 6; ++k) {
-            memcpy(host.data() + o, src4[k], (size_t)T.n_nodes * 4);
-            *dst4[k] = o;
-            o += a4;
-        }
-        memcpy(host.data() + o, T.weight, (size_t)T.n_nodes * 8);
-        tab[t].weight = o;
-        o += gbt_align((size_t)T.n_nodes * 8);
     }
-    GBT_HIP(ctx, hipMemcpyAsync(workspace, host.data(), o, hipMemcpyHostToDevice, ctx->stream));
-    int max_nodes = 1;
-    for (int t = 0; t < n_trees; ++t) max_nodes = std::max(max_nodes, trees[t].n_nodes);
     // Several trees on raw floats: one pass over the rows with the trees taken through LDS in groups
     // (needs right == left + 1 and children after parents, which grown trees have).
-    if (may_batch && compact_ok && ordered && F <= gbt_predict_batch_max_features() && max_nodes <= 32767) {
-        const size_t tile = (((size_t)256 * (size_t)(F | 1) * 4) + 15) & ~(size_t)15;
-        int cap_nodes = std::max(2048, max_nodes);
-        if (tile + (size_t)cap_nodes * 16 > ctx->lds_per_block) cap_nodes = max_nodes;
-        if (tile + (size_t)cap_nodes * 16 <= ctx->lds_per_block) {
+    if (may_batch && compact_ok && ordered && F < 65536 && max_nodes <= 32767) {
+        // (1536 nodes beside the rows leave a compute unit three workgroups of a 28-feature tile: 0.267 ms for 1M rows and
+        // 100 trees; 700 nodes 0.33, 1024 0.28, 2560 0.28)
+        const size_t tile = gbt_predict_batch_tile_bytes(F);
+        const int cap_nodes = std::max(tile + (size_t)1536 * 8 <= ctx->lds_per_block ? 1536 : 1, max_nodes);
+        if (tile + (size_t)cap_nodes * 8 <= ctx->lds_per_block) {
             const int64_t total_nodes = total_nodes_of(trees, n_trees);
-            const BatchLayout BL = batch_layout(predict_plain_bytes(trees, n_trees), total_nodes, n_trees);
-            std::vector<gbt_batch_node> bn((size_t)total_nodes);
-            std::vector<double> bw((size_t)total_nodes);
-            std::vector<int32_t> off((size_t)n_trees + 1), grp;
+            const BatchLayout BL = batch_layout(0, total_nodes, n_trees);
+            // built where the copy reads it: the pinned staging if it fits there
+            std::vector<char> big;
+            char *img = nullptr;
+            if (BL.total <= kUploadBytes) {
+                int32_t st = reserve(ctx, BL.total, &img);
+                if (st != GBT_OK) return st;
+            } else {
+                big.resize(BL.total);
+                img = big.data();
+            }
+            gbt_batch_node *bn = (gbt_batch_node *)(img + BL.nodes);
+            double *bw = (double *)(img + BL.wts);
+            int32_t *off = (int32_t *)(img + BL.tree_off), *grp = (int32_t *)(img + BL.group_end);
             int64_t run = 0;
-            int in_group = 0;
+            int in_group = 0, n_groups = 0;
             for (int t = 0; t < n_trees; ++t) {
                 const gbt_tree &T = trees[t];
                 if (in_group + T.n_nodes > cap_nodes) {   // the group is full: it ends before this tree
-                    grp.push_back(t);
+                    grp[n_groups++] = t;
                     in_group = 0;
                 }
                 in_group += T.n_nodes;
-                off[(size_t)t] = (int32_t)run;
+                off[t] = (int32_t)run;
                 for (int i = 0; i < T.n_nodes; ++i) {
                     gbt_batch_node q;
                     if (T.feature[i] < 0) {
-                        q.thr = INFINITY;
+                        q.thr = INT32_MAX;
                         q.meta = (uint32_t)i | (1u << 15);
                     } else {
-                        q.thr = T.threshold[i];
-                        q.meta = (uint32_t)T.left[i] | ((T.default_left[i] ? 1u : 0u) << 15) | (1u << 16) |
-                                 ((uint32_t)T.feature[i] << 17);
+                        const uint32_t a = T.default_left[i] ? 1u : 0u;
+                        q.thr = batch_threshold(T.threshold[i], a);
+                        q.meta = (uint32_t)T.left[i] | (a << 15) | ((uint32_t)T.feature[i] << 16);
                     }
-                    bn[(size_t)(run + i)] = q;
-                    bw[(size_t)(run + i)] = T.weight[i];
+                    bn[run + i] = q;
+                    bw[run + i] = eta * T.weight[i];
                 }
                 run += T.n_nodes;
             }
-            off[(size_t)n_trees] = (int32_t)run;
-            grp.push_back(n_trees);
+            off[n_trees] = (int32_t)run;
+            grp[n_groups++] = n_trees;
+            memcpy(img + BL.tree_depth, depths.data(), depths.size() * 4);
             char *wsb = (char *)workspace;
-            const size_t per_upload = kUploadBytes;
-            auto put = [&](const void *src, size_t bytes, size_t at) -> int32_t {
-                for (size_t o2 = 0; o2 < bytes; o2 += per_upload) {
-                    int32_t st2 = upload(ctx, (const char *)src + o2, std::min(per_upload, bytes - o2), wsb + at + o2);
-                    if (st2 != GBT_OK) return st2;
-                }
-                return GBT_OK;
-            };
-            int32_t st = put(bn.data(), bn.size() * 8, BL.nodes);
-            if (st == GBT_OK) st = put(bw.data(), bw.size() * 8, BL.wts);
-            if (st == GBT_OK) st = put(off.data(), off.size() * 4, BL.tree_off);
-            if (st == GBT_OK) st = put(depths.data(), depths.size() * 4, BL.tree_depth);
-            if (st == GBT_OK) st = put(grp.data(), grp.size() * 4, BL.group_end);
-            if (st != GBT_OK) return st;
+            GBT_HIP(ctx, hipMemcpyAsync(wsb, img, BL.total, hipMemcpyHostToDevice, ctx->stream));
+            if (!big.empty()) GBT_SYNC(ctx);   // (the copy may still read `big`)
             if (own_span) gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * ((double)F * 4.0 + 8.0));
             GBT_HIP(ctx, gbt_launch_predict_raw_batched(ctx->stream, (const gbt_batch_node *)(wsb + BL.nodes),
                                                         (const double *)(wsb + BL.wts), (const int32_t *)(wsb + BL.tree_off),
                                                         (const int32_t *)(wsb + BL.tree_depth),
-                                                        (const int32_t *)(wsb + BL.group_end), (int)grp.size(), cap_nodes,
-                                                        X, n, F, eta, margin));
+                                                        (const int32_t *)(wsb + BL.group_end), n_groups, cap_nodes, X, n, F,
+                                                        margin));
             if (own_span) gbt_prof_end(ctx);
             return GBT_OK;
         }
     }
+    // stage the trees: table of offsets, then each tree's arrays
+    const size_t plain = predict_plain_bytes(trees, n_trees);
+    std::vector<char> big;
+    char *img = nullptr;
+    if (plain <= kUploadBytes) {
+        int32_t st = reserve(ctx, plain, &img);
+        if (st != GBT_OK) return st;
+    } else {
+        big.resize(plain);
+        img = big.data();
+    }
+    DevTree *tab = (DevTree *)img;
+    size_t o = gbt_align((size_t)n_trees * sizeof(DevTree));
+    for (int t = 0; t < n_trees; ++t) {
+        const gbt_tree &T = trees[t];
+        tab[t].n_nodes = T.n_nodes;
+        tab[t].pad = depths[(size_t)t];
+        const size_t a4 = gbt_align((size_t)T.n_nodes * 4);
+        const void *src4[6] = {T.feature, T.bin, T.default_left, T.left, T.right, T.threshold};
+        uint64_t *dst4[6] = {&tab[t].feature, &tab[t].bin, &tab[t].default_left, &tab[t].left, &tab[t].right,
+                             &tab[t].threshold};
+        for (int k = 0; k < 6; ++k) {
+            memcpy(img + o, src4[k], (size_t)T.n_nodes * 4);
+            *dst4[k] = o;
+            o += a4;
+        }
+        memcpy(img + o, T.weight, (size_t)T.n_nodes * 8);
+        tab[t].weight = o;
+        o += gbt_align((size_t)T.n_nodes * 8);
+    }
+    GBT_HIP(ctx, hipMemcpyAsync(workspace, img, o, hipMemcpyHostToDevice, ctx->stream));
+    if (!big.empty()) GBT_SYNC(ctx);
     if (sparse) {
         if (own_span) gbt_prof_begin(ctx, GBT_PROF_OTHER, 0.0);
         GBT_HIP(ctx, gbt_launch_sparse_walk(ctx->stream, (const char *)workspace, (const DevTree *)workspace, n_trees,

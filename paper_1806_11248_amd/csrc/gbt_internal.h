@@ -429,20 +429,21 @@ constexpr int kNodeRowsStride = 32;   // words between two nodes' row counters (
 bool gbt_predict_counts_ok(bool packed, int bits, int F, int max_nodes, bool compact_ok);
 // compact_ok: every split node has right == left + 1, feature < 2^20 and bin < 4096
 
-// Many trees on raw floats in one pass over the rows (kernels_misc.hip).  A node is 8 bytes:
-// meta = left child's id inside its tree (15 bits) | default_left << 15 | step << 16 | feature << 17,
-// next = left + (go left ? 0 : step); a leaf has step 0 and left = its own id.  tree_off[t] = first
-// node of tree t in nodes / wts (tree_off[n_trees] = total); group_end[g] = one past the last tree of
-// group g; no group has more than cap_nodes nodes.
+// Many trees on raw floats in one pass over the rows (kernels_misc.hip).  A node is 8 bytes: values are compared as
+// integers in the floats' order (NaN the largest), "right" iff value + a >= thr with a = the node's default_left, and
+// meta = left child's id inside its tree (15 bits) | a << 15 | feature << 16; a leaf leads to itself (thr = the
+// largest integer, a = 1, left = its own id).  wts: eta * weight of every node.  tree_off[t] = first node of
+// tree t in nodes / wts (tree_off[n_trees] = total); group_end[g] = one past the last tree of group g; no group has
+// more than cap_nodes nodes; gbt_predict_batch_tile_bytes(F) + 8 * cap_nodes bytes of LDS per workgroup.
 struct gbt_batch_node {
-    float thr;
+    int32_t thr;
     uint32_t meta;
 };
-int gbt_predict_batch_max_features();
+size_t gbt_predict_batch_tile_bytes(int F);
 hipError_t gbt_launch_predict_raw_batched(hipStream_t s, const gbt_batch_node *nodes, const double *wts,
                                           const int32_t *tree_off, const int32_t *tree_depth,
                                           const int32_t *group_end, int n_groups, int cap_nodes, const float *X,
-                                          int64_t n, int F, double eta, float *margin);
+                                          int64_t n, int F, float *margin);
 
 // Four consecutive words with ONE load instruction at 4-byte alignment (rows of packed symbols start at any byte).
 typedef uint32_t gbt_u32x4 __attribute__((ext_vector_type(4), aligned(4)));

@@ -81,3 +81,23 @@ def test_many_trees_on_raw_floats(ctx, oracle, n, F, B, rounds, depth, miss):
     for t in trees:
         ctx.predict([t], step, 0.3, X=dev(Z))
     assert np.array_equal(step.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("F", [1, 4, 64, 65, 128, 129, 300])   # the widths at which the rows per tile change, and four-feature chunks with and without a remainder
+@pytest.mark.parametrize("n", [1, 255, 1_027])
+def test_row_tiles_of_every_width(ctx, oracle, n, F):
+    rng = np.random.default_rng(17 * n + F)
+    X = rng.standard_normal((3_000, F)).astype(np.float32)
+    X[rng.random(X.shape) < 0.1] = np.nan
+    X[:, -1] = np.where(rng.random(3_000) < 0.5, -0.0, np.round(rng.standard_normal(3_000)))   # a threshold of zero, either sign
+    y = (np.nan_to_num(X[:, 0]) + X[:, -1] > 0).astype(np.float32)
+    print(f"row tiles n={n} F={F}", flush=True)
+    trees, _ = _boost(ctx, X, y, 32, 5, 6)
+    Z = X[rng.permutation(3_000)[:n]].copy()
+    Z[rng.random(Z.shape) < 0.05] = 0.0
+    start = rng.standard_normal(n).astype(np.float32)
+    ref = start.copy()
+    for t in trees:
+        ref = oracle.predict_raw(t, Z, 0.3, ref)
+    got = ctx.predict(trees, dev(start), 0.3, X=dev(Z)).cpu().numpy()
+    assert np.array_equal(got, ref)
