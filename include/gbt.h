@@ -130,6 +130,7 @@ typedef struct gbt_tree {
  *   GBT_TUNE_HIST_MERGE_RATIO   [96] 1..100000: LDS additions a bin should receive per value a job merges into HBM (longer row pieces)
  *   GBT_TUNE_LOSSGUIDE_BATCH    [16] 1..64: open leaves expanded per round of loss-guided growth
  *   GBT_TUNE_SPARSE_JOBS        [1] 1..64: sparse-row histogram workgroups per compute unit
+ *   GBT_TUNE_QUANTISE_SORT      [0] 1: order statistics from sorted columns also where they would be found by selection
  *   GBT_TUNE_SPARSE_TILED       [0] 1: sparse-row histogram in id-range tiles even where all ids fit one workgroup's LDS */
 GBT_API int32_t gbt_create(gbt_ctx **ctx_out, int32_t device, void *stream);
 GBT_API int32_t gbt_destroy(gbt_ctx *ctx);

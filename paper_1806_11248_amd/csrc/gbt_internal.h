@@ -46,6 +46,7 @@ struct gbt_ctx {
     int hist8;              // 1: the root histogram of 8-bit symbols with at most 16 features takes kernels_hist8.hip
     int hist8_stagger;      // its workgroups on one compute unit get unequal shares of rows: spread in 1/256ths
     int sparse_jobs_per_cu; // row pieces per compute unit and launch of the sparse-row histogram kernel
+    int quantise_sort;      // 1: cuts from sorted columns also where selection applies
     int sparse_tiled;       // 1: keep the sparse-row LDS histogram under hist_lds_kb even where all ids would fit
     char *part_static;      // this device's copy of the static partition scratch (gbt_partition_static), or NULL
     size_t up_off;          // next free byte of the upload ring (first half of `pinned`)
@@ -466,6 +467,22 @@ constexpr int kHShift = 30;                        // width of the h field
 constexpr uint32_t kHMask = (1u << kHShift) - 1u;
 
 
+// order statistics by selection (kernels_select.hip): keys, segments and tiles as kernels_quantise.hip lays them out,
+// `collected` a second buffer of n_values words; cuts, nb and present (values that are not missing) per feature
+struct SelArrays;
+bool gbt_select_ok(int B);
+size_t gbt_select_layout(int F, int64_t n_values, int B, char *base, SelArrays *A);   // bytes; base, A may be NULL
+hipError_t gbt_launch_select(gbt_ctx *ctx, const uint32_t *keys, uint32_t *collected, const uint64_t *seg_off,
+                             const uint32_t *blk_off, int F, int64_t n_values, int B, const SelArrays &A, float *cuts,
+                             int32_t *nb, uint32_t *present);
+// ... and, for a dense matrix, the bit stream from the key columns: gbt_launch_bin_table once the cuts are there, then
+// gbt_launch_bin_columns (cols: gbt_bin_columns_bytes scratch bytes)
+size_t gbt_bin_columns_bytes(int64_t n, int F);
+bool gbt_bin_columns_ok(int64_t n, int F, int bits);
+hipError_t gbt_launch_bin_table(gbt_ctx *ctx, int F, int B, const SelArrays &A, const float *cuts, const int32_t *nb);
+hipError_t gbt_launch_bin_columns(gbt_ctx *ctx, const uint32_t *keys, void *cols, const uint64_t *seg_off, const uint32_t *blk_off,
+                                  int64_t n, int F, int B, const SelArrays &A, const float *cuts, const int32_t *nb,
+                                  uint32_t missing, int bits, uint32_t *packed, int64_t n_words);
 // quantise
 hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr, const int32_t *indices,
                             const float *values, int64_t n, int F, int64_t n_values, int B, float *cuts,

@@ -1,40 +1,26 @@
-// Feature quantile generation (Sec. 2.1) on the GPU: exact per-feature order
-// statistics by a segmented LSD radix sort of the order-preserving integer
-// image of the fp32 values, then cuts, then binning.
+// Feature quantile generation (Sec. 2.1) on the GPU: exact per-feature order statistics, then cuts, then binning.
 //
-//   1. keys: every feature's values become one contiguous segment of uint32
-//      keys (dense input: an LDS-tiled transpose, a missing value becomes the
-//      largest key; CSR input: counted, offset and scattered by column);
-//   2. sort: four 8-bit passes; per pass a per-tile digit histogram, one
-//      workgroup per segment turning the tile histograms into offsets, and a
-//      stable scatter (ranks from wave ballots, tiles and waves in order);
-//   3. cuts: one thread per feature walks the sorted segment (distinct values
-//      by upper-bound jumps, else the order statistics v[floor(k*m/B)]);
-//   4. bin: symbol = number of cuts <= x by bisection over the feature's cuts.
+//   1. keys: every feature's values become one contiguous segment of uint32 keys in the floats' order (dense input: an
+//      LDS-tiled transpose, a missing value becomes the largest key; CSR input: counted, offset and scattered by
+//      column);
+//   2. order statistics and cuts by selection (kernels_select.hip), for up to 1024 bins.  With more bins, and for
+//      matrices whose values lie too close together for it, by a segmented LSD radix sort (here): four 8-bit passes,
+//      each a per-tile digit histogram, offsets from the tile histograms and a stable scatter (ranks from wave ballots,
+//      tiles and waves in order), then one wave per feature walks the sorted segment;
+//   3. bin: symbol = number of cuts <= x by bisection over the feature's cuts.
 #include "gbt_internal.h"
+#include "quantise_common.h"
 
 #include <string.h>
 
+#include <initializer_list>
 #include <vector>
 
 namespace {
 
 constexpr int kSortBlock = 256;
-constexpr int kSortTile = 4096;                       // keys per workgroup and pass
 constexpr int kKeysPerWave = kSortTile / (kSortBlock / 64);   // 1024
 constexpr int kRounds = kKeysPerWave / 64;            // 16
-constexpr uint32_t kMissingKey = 0xffffffffu;
-
-__device__ inline uint32_t float_key(float x) {
-    if (x != x) return kMissingKey;
-    x = x + 0.0f;   // -0.0 -> +0.0: the two compare equal and must share a key
-    uint32_t u = __float_as_uint(x);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-__device__ inline float key_float(uint32_t k) {
-    uint32_t u = (k & 0x80000000u) ? (k & 0x7fffffffu) : ~k;
-    return __uint_as_float(u);
-}
 
 // ---- 1a. dense input: transpose into per-feature key segments -------------
 constexpr int kTrRows = 64, kTrCols = 64;
@@ -77,103 +63,216 @@ __global__ __launch_bounds__(256) void dense_keys_narrow_kernel(const float *__r
 }
 
 // ---- 1b. CSR input: count, offset, scatter by column -----------------------
-// Workgroups take chunks of kCsrChunk stored values and count columns in LDS first, so that
-// HBM sees one atomic per (chunk, column) instead of one per value.  Columns beyond
-// kCsrLdsCols use the direct form.
-constexpr int kCsrChunk = 8192;
+// A fixed number of workgroups take equal runs of whole chunks of the stored values, the same run in both kernels, so the
+// first leaves a table of counts per (column, workgroup) whose prefix sums are where the second writes: no atomics on HBM
+// (one per chunk and column took turns on each column's address, some 12 ns each).  10M x 50 rows of 10 entries: count
+// 0.26 -> 0.09 ms, scatter 1.09 -> 0.43 ms (that one also by writing whole runs, see there).
+// More than kCsrLdsCols columns: an atomic per value.
+constexpr int kCsrChunk = 4096;   // (24 KB staged: six workgroups of 256 per compute unit, one's barriers under another's loads)
 constexpr int kCsrLdsCols = 4096;
+constexpr int kCsrBlock = 256;
+constexpr int kCsrPer = kCsrChunk / kCsrBlock;
 
-__global__ __launch_bounds__(256) void csr_count_kernel(const int32_t *__restrict__ indices, int64_t nnz, int F,
-                                                        uint32_t *__restrict__ counts) {
-    __shared__ uint32_t lc[kCsrLdsCols];
-    const bool use_lds = F <= kCsrLdsCols;
-    if (use_lds) {
-        for (int i = threadIdx.x; i < F; i += 256) lc[i] = 0;
-        __syncthreads();
+// chunks [*c0, *c1) of workgroup blockIdx.x
+__device__ inline void csr_run(int64_t nnz, int64_t *c0, int64_t *c1) {
+    const int64_t chunks = (nnz + kCsrChunk - 1) / kCsrChunk;
+    *c0 = chunks * blockIdx.x / gridDim.x;
+    *c1 = chunks * (blockIdx.x + 1) / gridDim.x;
+}
+
+__global__ __launch_bounds__(kCsrBlock) void csr_count_kernel(const int32_t *__restrict__ indices, int64_t nnz, int F,
+                                                              uint32_t *__restrict__ table) {
+    extern __shared__ uint32_t lc[];   // F
+    for (int i = threadIdx.x; i < F; i += kCsrBlock) lc[i] = 0;
+    __syncthreads();
+    int64_t c0, c1;
+    csr_run(nnz, &c0, &c1);
+    for (int64_t c = c0; c < c1; ++c) {
+        const int64_t i0 = c * kCsrChunk + threadIdx.x;
+        int f[kCsrPer];
+#pragma unroll
+        for (int k = 0; k < kCsrPer; ++k) f[k] = i0 + k * kCsrBlock < nnz ? indices[i0 + k * kCsrBlock] : -1;
+#pragma unroll
+        for (int k = 0; k < kCsrPer; ++k)
+            if (f[k] >= 0 && f[k] < F) atomicAdd(&lc[f[k]], 1u);
     }
+    __syncthreads();
+    for (int i = threadIdx.x; i < F; i += kCsrBlock) table[(int64_t)i * gridDim.x + blockIdx.x] = lc[i];
+}
+
+// table[f][w] becomes the first slot of workgroup w in column f; counts[f] the column's length.  A wave per column.
+__global__ __launch_bounds__(64) void csr_offsets_kernel(uint32_t *__restrict__ table, int W, uint32_t *__restrict__ counts) {
+    uint32_t *t = table + (int64_t)blockIdx.x * W;
+    const int lane = threadIdx.x;
+    uint32_t run = 0;
+    for (int w0 = 0; w0 < W; w0 += 64) {
+        const uint32_t v = w0 + lane < W ? t[w0 + lane] : 0u;
+        uint32_t x = v;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)x, o);
+            if (lane >= o) x += y;
+        }
+        if (w0 + lane < W) t[w0 + lane] = run + x - v;
+        run += (uint32_t)__shfl((int)x, 63);
+    }
+    if (lane == 0) counts[blockIdx.x] = run;
+}
+
+// The direct form's count.
+__global__ __launch_bounds__(256) void csr_count_direct_kernel(const int32_t *__restrict__ indices, int64_t nnz, int F,
+                                                               uint32_t *__restrict__ counts) {
+    const int64_t i0 = (int64_t)blockIdx.x * kCsrChunk;
+    const int64_t i1 = i0 + kCsrChunk < nnz ? i0 + kCsrChunk : nnz;
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
+        const int f = indices[i];
+        if (f >= 0 && f < F) atomicAdd(&counts[f], 1u);
+    }
+}
+
+// Scatter.  A chunk's keys are put in column order inside LDS and copied out from there: consecutive threads hold
+// consecutive keys of a column's run, so a run goes to HBM as whole lines.
+inline size_t csr_scatter_lds(int F) { return (size_t)kCsrChunk * 6 + (size_t)F * 12; }
+__global__ __launch_bounds__(kCsrBlock) void csr_scatter_kernel(const int32_t *__restrict__ indices,
+                                                                const float *__restrict__ values, int64_t nnz, int F,
+                                                                const uint64_t *__restrict__ seg_off,
+                                                                const uint32_t *__restrict__ table,
+                                                                uint32_t *__restrict__ keys) {
+    extern __shared__ uint32_t stage[];                        // kCsrChunk keys in column order
+    uint32_t *lc = stage + kCsrChunk;                          // F: keys of a column in this chunk
+    uint32_t *start = lc + F;                                  // F: the run's first place in `stage`
+    uint32_t *cur = start + F;                                 // F: the column's next slot in its segment
+    uint16_t *col = (uint16_t *)(cur + F);                     // kCsrChunk: column of a staged key
+    __shared__ uint32_t wsum[kCsrBlock / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < F; i += kCsrBlock) {
+        cur[i] = table[(int64_t)i * gridDim.x + blockIdx.x];
+        lc[i] = 0;
+    }
+    int64_t c0, c1;
+    csr_run(nnz, &c0, &c1);
+    const int per = (F + kCsrBlock - 1) / kCsrBlock, f0 = tid * per, f1 = f0 + per < F ? f0 + per : F;
+    for (int64_t c = c0; c < c1; ++c) {
+        const int64_t i0 = c * kCsrChunk + tid;
+        int f[kCsrPer];
+        uint32_t key[kCsrPer], rank[kCsrPer];
+#pragma unroll
+        for (int k = 0; k < kCsrPer; ++k) {
+            const int64_t i = i0 + k * kCsrBlock;
+            f[k] = i < nnz ? indices[i] : -1;
+            key[k] = i < nnz ? float_key(values[i]) : 0u;
+            if (f[k] >= F) f[k] = -1;
+        }
+        __syncthreads();   // the chunk before has been copied out, its counts cleared
+#pragma unroll
+        for (int k = 0; k < kCsrPer; ++k) rank[k] = f[k] >= 0 ? atomicAdd(&lc[f[k]], 1u) : 0u;
+        __syncthreads();
+        // exclusive prefix of the counts: a piece of columns per thread, a scan over the pieces
+        uint32_t sum = 0;
+        for (int j = f0; j < f1; ++j) sum += lc[j];
+        uint32_t x = sum;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)x, o);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) wsum[wave] = x;
+        __syncthreads();
+        uint32_t at = x - sum, total = 0;
+        for (int w = 0; w < kCsrBlock / 64; ++w) {
+            at += w < wave ? wsum[w] : 0u;
+            total += wsum[w];
+        }
+        for (int j = f0; j < f1; ++j) {
+            start[j] = at;
+            at += lc[j];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kCsrPer; ++k)
+            if (f[k] >= 0) {
+                const uint32_t d = start[f[k]] + rank[k];
+                stage[d] = key[k];
+                col[d] = (uint16_t)f[k];
+            }
+        __syncthreads();
+        for (uint32_t i = tid; i < total; i += kCsrBlock) {
+            const uint32_t j = col[i];
+            keys[seg_off[j] + cur[j] + (i - start[j])] = stage[i];
+        }
+        __syncthreads();
+        for (int j = f0; j < f1; ++j) {
+            cur[j] += lc[j];
+            lc[j] = 0;
+        }
+    }
+}
+
+// More columns than the counters in LDS: a global slot per value.
+__global__ __launch_bounds__(256) void csr_scatter_direct_kernel(const int32_t *__restrict__ indices,
+                                                                 const float *__restrict__ values, int64_t nnz, int F,
+                                                                 const uint64_t *__restrict__ seg_off,
+                                                                 uint32_t *__restrict__ cursor,
+                                                                 uint32_t *__restrict__ keys) {
     const int64_t i0 = (int64_t)blockIdx.x * kCsrChunk;
     const int64_t i1 = i0 + kCsrChunk < nnz ? i0 + kCsrChunk : nnz;
     for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
         const int f = indices[i];
         if (f < 0 || f >= F) continue;
-        if (use_lds) atomicAdd(&lc[f], 1u); else atomicAdd(&counts[f], 1u);
-    }
-    if (use_lds) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < F; i += 256)
-            if (lc[i]) atomicAdd(&counts[i], lc[i]);
+        const uint32_t slot = atomicAdd(&cursor[f], 1u);
+        keys[seg_off[f] + slot] = float_key(values[i]);
     }
 }
 
-__global__ __launch_bounds__(256) void csr_scatter_kernel(const int32_t *__restrict__ indices,
-                                                          const float *__restrict__ values, int64_t nnz, int F,
-                                                          const uint64_t *__restrict__ seg_off,
-                                                          uint32_t *__restrict__ cursor,
-                                                          uint32_t *__restrict__ keys) {
-    __shared__ uint32_t lc[kCsrLdsCols];     // count, then the chunk's first slot, per column
-    const bool use_lds = F <= kCsrLdsCols;
-    const int64_t i0 = (int64_t)blockIdx.x * kCsrChunk;
-    const int64_t i1 = i0 + kCsrChunk < nnz ? i0 + kCsrChunk : nnz;
-    if (!use_lds) {
-        for (int64_t i = i0 + threadIdx.x; i < i1; i += 256) {
-            const int f = indices[i];
-            if (f < 0 || f >= F) continue;
-            const uint32_t slot = atomicAdd(&cursor[f], 1u);   // order inside a segment is irrelevant before the sort
-            keys[seg_off[f] + slot] = float_key(values[i]);
-        }
-        return;
-    }
-    for (int i = threadIdx.x; i < F; i += 256) lc[i] = 0;
-    __syncthreads();
-    // rank of every value among the chunk's values of its column (kCsrChunk / 256 = 32 per thread)
-    uint32_t rank[kCsrChunk / 256];
-#pragma unroll
-    for (int k = 0; k < kCsrChunk / 256; ++k) {
-        const int64_t i = i0 + (int64_t)k * 256 + threadIdx.x;
-        rank[k] = 0;
-        if (i < i1) {
-            const int f = indices[i];
-            if (f >= 0 && f < F) rank[k] = atomicAdd(&lc[f], 1u);
-        }
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < F; i += 256) {
-        const uint32_t c = lc[i];
-        lc[i] = c ? atomicAdd(&cursor[i], c) : 0u;   // the chunk's slots in column i start here
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kCsrChunk / 256; ++k) {
-        const int64_t i = i0 + (int64_t)k * 256 + threadIdx.x;
-        if (i < i1) {
-            const int f = indices[i];
-            if (f >= 0 && f < F) keys[seg_off[f] + lc[f] + rank[k]] = float_key(values[i]);
-        }
-    }
-}
-
-// chk_off[f] = exclusive prefix of the segments' scan chunks (kScanChunk tiles each)
-__global__ void offsets_kernel(const uint32_t *counts, int F, int64_t fixed_len, uint64_t *seg_off,
-                               uint32_t *blk_off, uint32_t *chk_off, int scan_chunk) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+// seg_off / blk_off / chk_off [f] = exclusive prefix of the segments' lengths, tiles and scan chunks (kScanChunk tiles
+// each), by one workgroup: a piece of features per thread, then a scan over the pieces.
+__global__ __launch_bounds__(1024) void offsets_kernel(const uint32_t *counts, int F, int64_t fixed_len, uint64_t *seg_off,
+                                                       uint32_t *blk_off, uint32_t *chk_off, int scan_chunk) {
+    __shared__ uint64_t so[1024];
+    __shared__ uint32_t bo[1024], co[1024];
+    const int tid = threadIdx.x, per = (F + 1023) / 1024, f0 = tid * per, f1 = f0 + per < F ? f0 + per : F;
+    auto tiles_of = [&](uint64_t len) { return (uint32_t)((len + kSortTile - 1) / kSortTile); };
     uint64_t o = 0;
     uint32_t b = 0, c = 0;
-    for (int f = 0; f < F; ++f) {
-        seg_off[f] = o;
-        blk_off[f] = b;
-        chk_off[f] = c;
+    for (int f = f0; f < f1; ++f) {
         const uint64_t len = counts ? (uint64_t)counts[f] : (uint64_t)fixed_len;
-        const uint32_t tiles = (uint32_t)((len + kSortTile - 1) / kSortTile);
+        const uint32_t tiles = tiles_of(len);
         o += len;
         b += tiles;
         c += (tiles + (uint32_t)scan_chunk - 1) / (uint32_t)scan_chunk;
     }
-    seg_off[F] = o;
-    blk_off[F] = b;
-    chk_off[F] = c;
+    so[tid] = o;
+    bo[tid] = b;
+    co[tid] = c;
+    __syncthreads();
+    for (int d = 1; d < 1024; d <<= 1) {
+        const uint64_t po = tid >= d ? so[tid - d] : 0;
+        const uint32_t pb = tid >= d ? bo[tid - d] : 0, pc = tid >= d ? co[tid - d] : 0;
+        __syncthreads();
+        so[tid] += po;
+        bo[tid] += pb;
+        co[tid] += pc;
+        __syncthreads();
+    }
+    o = so[tid] - o;
+    b = bo[tid] - b;
+    c = co[tid] - c;
+    for (int f = f0; f < f1; ++f) {
+        seg_off[f] = o;
+        blk_off[f] = b;
+        chk_off[f] = c;
+        const uint64_t len = counts ? (uint64_t)counts[f] : (uint64_t)fixed_len;
+        const uint32_t tiles = tiles_of(len);
+        o += len;
+        b += tiles;
+        c += (tiles + (uint32_t)scan_chunk - 1) / (uint32_t)scan_chunk;
+    }
+    if (tid == 1023) {
+        seg_off[F] = so[1023];
+        blk_off[F] = bo[1023];
+        chk_off[F] = co[1023];
+    }
 }
 
-// ---- 2. segmented radix sort ----------------------------------------------
+// ---- 2a. segmented radix sort ----------------------------------------------
 // One count per key into a 256-bin LDS histogram.  Sorted or low-cardinality data gives a whole wave
 // the same digit, which as 64 atomics on one address would take 64 turns: that case is one add.
 __device__ inline void count_digit(uint32_t *h, uint32_t d, bool live) {
@@ -185,15 +284,6 @@ __device__ inline void count_digit(uint32_t *h, uint32_t d, bool live) {
     } else if (live) {
         atomicAdd(&h[d], 1u);
     }
-}
-
-__device__ inline int find_segment(const uint32_t *blk_off, int F, uint32_t blk) {
-    int lo = 0, hi = F;   // last f with blk_off[f] <= blk and a non-empty tile range
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (blk_off[mid] <= blk) lo = mid; else hi = mid;
-    }
-    return lo;
 }
 
 // A segment's keys sit in one of the two key buffers (bit 0 of its flag word: 0 = keys_a); a pass in which all keys
@@ -400,7 +490,7 @@ __global__ void flip_kernel(uint32_t *seg_flags, int F) {
     seg_flags[f] = (fl & kSegSkip) ? (fl & kSegInB) : ((fl & kSegInB) ^ kSegInB);
 }
 
-// ---- 3. cuts ----------------------------------------------------------------
+// ---- 2b. cuts of a sorted segment ----------------------------------------------------------------
 // First index in [lo, hi) with a[i] > v (hi if there is none), found by a whole wave: 64 probes per step cut the
 // range by 65, so 1.15e8 keys take five dependent rounds of loads instead of 27.  Every lane passes the same
 // arguments and gets the same result.
@@ -480,7 +570,7 @@ __global__ __launch_bounds__(64) void cuts_kernel(const uint32_t *__restrict__ k
     if (lane == 0) nb[f] = nc + 1;
 }
 
-// ---- 4. binning -------------------------------------------------------------
+// ---- 3. binning -------------------------------------------------------------
 __device__ inline uint32_t bin_of(const float *c, int ncut, float x) {
     int lo = 0, hi = ncut;   // number of cuts <= x
     while (lo < hi) {
@@ -564,7 +654,7 @@ __global__ void bin_csr_kernel(const int64_t *__restrict__ indptr, const int32_t
     if ((threadIdx.x & 63) == 0) atomicMax(max_out, mx);
 }
 
-// ---- 4b. binning and packing in one pass (Sec. 2.1 -> Sec. 2.2) ------------------
+// ---- 3b. binning and packing in one pass (Sec. 2.1 -> Sec. 2.2) ------------------
 // The symbols of a tile of elements are binned into LDS and leave as words of the bit stream: the uint16 symbol
 // matrix never exists.  A tile holds a multiple of 32 elements, so it starts on a word boundary whatever the width;
 // one thread assembles one word from the LDS symbols that overlap it.
@@ -627,42 +717,117 @@ __global__ __launch_bounds__(256) void bin_pack_dense_kernel(const float *__rest
     if (blockIdx.x == 0 && threadIdx.x == 0) packed[n_words - 1] = 0;   // the pad word (Sec. 2.2 layout)
 }
 
-// CSR input: a tile of rows (a multiple of 32) is laid out in LDS as missing symbols, the stored values of those
-// rows (one contiguous piece of the CSR arrays) are binned into their places, and the tile is packed.
-__global__ __launch_bounds__(256) void bin_pack_csr_kernel(const int64_t *__restrict__ indptr,
-                                                           const int32_t *__restrict__ indices,
-                                                           const float *__restrict__ values, int64_t n, int64_t nnz,
-                                                           int F, int B, const float *__restrict__ cuts,
-                                                           const int32_t *__restrict__ nb, uint32_t missing, int bits,
-                                                           int tile_rows, uint32_t *__restrict__ packed,
-                                                           int64_t n_words) {
-    extern __shared__ uint16_t lrow[];                       // tile_rows * F symbols
-    int64_t *lptr = (int64_t *)(lrow + (((size_t)tile_rows * F + 3) & ~(size_t)3));   // tile_rows + 1 row pointers
+// CSR input: a tile of rows (a multiple of 32) is laid out in LDS as missing symbols, the stored values of those rows
+// are binned into their places, and the tile is packed.  A row is taken by 2^log_lanes neighbouring lanes (about as many
+// as a row has entries), so no lane has to search for the row of its entry and a wave's loads are one piece of the CSR
+// arrays.  The cuts are searched in two levels: every 2^cut_log-th one in LDS (all of them where they fit: 51 KB for
+// 50 x 255), then the few between two of those.
+// 10M x 50 rows of 10 entries: 0.84 ms; 1.99 ms with a bisection for the row, one through global memory for the cut and
+// a word of the stream at a time.  Instruction issue is what remains (90 MB of words written, 0.9 GB read).
+constexpr int kCsrPackBlock = 1024;
+template <int BITS>
+__global__ __launch_bounds__(kCsrPackBlock) __attribute__((amdgpu_waves_per_eu(8))) void bin_pack_csr_kernel(
+    const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices, const float *__restrict__ values, int64_t n,
+    int64_t nnz, int F, int B, const float *__restrict__ cuts, const int32_t *__restrict__ nb, uint32_t missing, int tile_rows,
+    int log_lanes, int cut_log, int step0, uint32_t *__restrict__ packed, int64_t n_words) {
+    extern __shared__ uint32_t dyn[];
+    uint16_t *lrow = (uint16_t *)dyn;                        // tile_rows * F symbols (a multiple of 32)
+    float *tops = (float *)(dyn + ((size_t)tile_rows * F) / 2);   // F x n_top, padded with +inf
+    const int n_top = 2 * step0 - 1;
+    int32_t *lcut = (int32_t *)(tops + (size_t)F * n_top);   // F: cuts of a feature
+    int32_t *lptr = lcut + F;                                // tile_rows + 1 row pointers, relative to the tile's first
+    for (int i = threadIdx.x; i < F * n_top; i += kCsrPackBlock) {
+        const int f = i / n_top, at = ((i - f * n_top + 1) << cut_log) - 1;
+        tops[i] = at < B - 1 ? cuts[(int64_t)f * (B - 1) + at] : __uint_as_float(0x7f800000u);
+    }
+    for (int i = threadIdx.x; i < F; i += kCsrPackBlock) lcut[i] = nb[i] - 1;
     const int64_t n_tiles = (n + tile_rows - 1) / tile_rows;
+    const int lanes = 1 << log_lanes, sub = threadIdx.x & (lanes - 1), groups = kCsrPackBlock >> log_lanes;
+    const uint32_t two = missing | (missing << 16);
     for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
         const int64_t r0 = t * tile_rows;
         const int rows = n - r0 < tile_rows ? (int)(n - r0) : tile_rows;
-        for (int i = threadIdx.x; i < rows * F; i += 256) lrow[i] = (uint16_t)missing;
-        for (int i = threadIdx.x; i <= rows; i += 256) {
+        const int elems = rows * F;
+        int64_t a0 = indptr[r0];
+        a0 = a0 < 0 ? 0 : a0 > nnz ? nnz : a0;
+        for (int i = threadIdx.x; i < (elems + 1) / 2; i += kCsrPackBlock) dyn[i] = two;
+        for (int i = threadIdx.x; i <= rows; i += kCsrPackBlock) {
             int64_t p = indptr[r0 + i];
-            p = p < 0 ? 0 : p;
-            lptr[i] = p > nnz ? nnz : p;
+            p = p < a0 ? a0 : p > nnz ? nnz : p;
+            lptr[i] = p - a0 < INT32_MAX ? (int)(p - a0) : INT32_MAX;
         }
         __syncthreads();
-        const int64_t a0 = lptr[0], b0 = lptr[rows];
-        for (int64_t i = a0 + threadIdx.x; i < b0; i += 256) {
-            int lo = 0, hi = rows;   // last row whose first entry is at or before i
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (lptr[mid] <= i) lo = mid; else hi = mid;
+        const int32_t *ip = indices + a0;
+        const float *vp = values + a0;
+        // rows side by side: their loads and searches overlap
+        constexpr int U = 4;
+        for (int rb = threadIdx.x >> log_lanes; rb < rows; rb += U * groups) {
+            int at[U], end[U];
+            bool more = false;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int r = rb + u * groups;
+                at[u] = r < rows ? lptr[r] + sub : 0;
+                end[u] = r < rows ? lptr[r + 1] : 0;
+                more |= at[u] < end[u];
             }
-            const int f = indices[i];
-            if (f < 0 || f >= F) continue;
-            const float x = values[i];
-            lrow[lo * F + f] = (uint16_t)((x != x) ? missing : bin_of(cuts + (int64_t)f * (B - 1), nb[f] - 1, x));
+            while (more) {
+                int f[U], base[U], pos[U];
+                float x[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    f[u] = at[u] < end[u] ? ip[at[u]] : -1;
+                    x[u] = at[u] < end[u] ? vp[at[u]] : 0.0f;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    f[u] = (unsigned)f[u] < (unsigned)F ? f[u] : -1;
+                    base[u] = pos[u] = (f[u] < 0 ? 0 : f[u]) * n_top;
+                }
+                for (int step = step0; step > 0; step >>= 1) {   // pos - base: tops at or below x
+#pragma unroll
+                    for (int u = 0; u < U; ++u) pos[u] += tops[pos[u] + step - 1] <= x[u] ? step : 0;
+                }
+                more = false;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (f[u] >= 0) {
+                        const int ncut = lcut[f[u]];
+                        int lo = (pos[u] - base[u]) << cut_log;
+                        if (cut_log) {
+                            const float *c = cuts + (int64_t)f[u] * (B - 1);
+                            int hi = lo + (1 << cut_log) - 1;
+                            hi = hi < B - 1 ? hi : B - 1;
+                            while (lo < hi) {
+                                const int mid = (lo + hi) >> 1;
+                                if (c[mid] <= x[u]) lo = mid + 1; else hi = mid;
+                            }
+                        }
+                        lo = lo < ncut ? lo : ncut;   // (x = +inf lies at or above the padding)
+                        lrow[(rb + u * groups) * F + f[u]] = (uint16_t)(x[u] == x[u] ? (uint32_t)lo : missing);
+                    }
+                    at[u] += lanes;
+                    more |= at[u] < end[u];
+                }
+            }
         }
         __syncthreads();
-        pack_tile(lrow, rows * F, bits, packed + (r0 * F) / 32 * bits);   // r0 * F is a multiple of 32
+        uint32_t *out = packed + ((r0 * F) >> 5) * BITS;   // r0 * F is a multiple of 32
+        const int nw = (int)(((int64_t)elems * BITS + 31) >> 5);
+        for (int g = threadIdx.x; g < (elems + 31) >> 5; g += kCsrPackBlock) {
+            const uint4 *src = (const uint4 *)(dyn + 16 * g);
+            const uint4 q[4] = {src[0], src[1], src[2], src[3]};
+            const uint32_t s[16] = {q[0].x, q[0].y, q[0].z, q[0].w, q[1].x, q[1].y, q[1].z, q[1].w,
+                                    q[2].x, q[2].y, q[2].z, q[2].w, q[3].x, q[3].y, q[3].z, q[3].w};
+            uint32_t w[BITS];
+            pack_group<BITS>(w, [&](int j) -> uint32_t {
+                const uint32_t v = (j & 1) ? s[j >> 1] >> 16 : s[j >> 1] & 0xffffu;
+                return 32 * g + j < elems ? v : 0u;
+            });
+#pragma unroll
+            for (int i = 0; i < BITS; ++i)
+                if (g * BITS + i < nw) out[(int64_t)g * BITS + i] = w[i];
+        }
         __syncthreads();
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) packed[n_words - 1] = 0;
@@ -686,17 +851,26 @@ __global__ void csr_any_missing_kernel(const int64_t *__restrict__ indptr, const
     if (__ballot(any) != 0 && (threadIdx.x & 63) == 0) atomicOr(flag, 1u);
 }
 
+// workgroups of the CSR count and scatter: six per compute unit, at least a chunk each
+constexpr int kCsrWorkgroups = 1536;
+int csr_workgroups(int num_cu, int64_t nnz) {
+    const int64_t chunks = (nnz + kCsrChunk - 1) / kCsrChunk;
+    const int most = 6 * num_cu < kCsrWorkgroups ? 6 * num_cu : kCsrWorkgroups;
+    return (int)(chunks < 1 ? 1 : chunks < most ? chunks : most);
+}
+
 struct QLayout {
-    size_t keys_a, keys_b, tile_hist, chunk_tot, seg_off, blk_off, chk_off, counts, cursor, seg_flags, present, misc, total;
+    size_t keys_a, keys_b, tile_hist, chunk_tot, seg_off, blk_off, chk_off, counts, cursor, seg_flags, present, misc, select, csr_table, total;
     int64_t max_tiles, max_chunks;
 };
-QLayout q_layout(int64_t n, int F, int64_t n_values) {
-    (void)n;
+QLayout q_layout(int64_t n, int F, int64_t n_values, int B) {
     QLayout L;
     L.max_tiles = n_values / kSortTile + F + 1;
     size_t o = 0;
     L.keys_a = o;    o += gbt_align((size_t)n_values * 4 + 4);
-    L.keys_b = o;    o += gbt_align((size_t)n_values * 4 + 4);
+    // (behind the selection, a dense matrix's columns of symbols)
+    const size_t cols = n_values == n * (int64_t)F ? gbt_bin_columns_bytes(n, F) : 0;
+    L.keys_b = o;    o += gbt_align(cols > (size_t)n_values * 4 + 4 ? cols : (size_t)n_values * 4 + 4);
     L.tile_hist = o; o += gbt_align((size_t)L.max_tiles * 256 * 4);
     L.max_chunks = L.max_tiles / 128 + F + 1;
     L.chunk_tot = o; o += gbt_align((size_t)L.max_chunks * 256 * 4);
@@ -708,6 +882,8 @@ QLayout q_layout(int64_t n, int F, int64_t n_values) {
     L.seg_flags = o; o += gbt_align((size_t)F * 4);
     L.present = o;   o += gbt_align((size_t)F * 4);
     L.misc = o;      o += 256;
+    L.select = o;    o += gbt_select_ok(B) ? gbt_select_layout(F, n_values, B, nullptr, nullptr) : 0;
+    L.csr_table = o; o += F > kCsrLdsCols ? 0 : gbt_align((size_t)F * kCsrWorkgroups * 4);
     L.total = o;
     return L;
 }
@@ -722,8 +898,7 @@ inline int grid_for(int64_t count, int per_block, int cap) {
 }  // namespace
 
 size_t gbt_quantise_ws(int64_t n, int F, int64_t n_values, int B) {
-    (void)B;
-    return q_layout(n, F, n_values).total;
+    return q_layout(n, F, n_values, B).total;
 }
 
 #define Q_HIP(call)                        \
@@ -731,6 +906,33 @@ size_t gbt_quantise_ws(int64_t n, int F, int64_t n_values, int B) {
         hipError_t e_ = (call);            \
         if (e_ != hipSuccess) return e_;   \
     } while (0)
+
+// Small results to the host with one wait: through the pinned staging as far as they fit there.
+struct ReadBack {
+    void *to;
+    const void *from;
+    size_t bytes;
+};
+static hipError_t read_back(gbt_ctx *ctx, std::initializer_list<ReadBack> what) {
+    const size_t room = GBT_STAGING_BYTES / 2;
+    char *pin = ctx->pinned + room;
+    size_t at = 0;
+    for (const ReadBack &r : what) {
+        const bool fits = at + r.bytes <= room;
+        hipError_t e = hipMemcpyAsync(fits ? (void *)(pin + at) : r.to, r.from, r.bytes, hipMemcpyDeviceToHost, ctx->stream);
+        if (e != hipSuccess) return e;
+        if (fits) at += gbt_align(r.bytes, 16);
+    }
+    hipError_t e = hipStreamSynchronize(ctx->stream);
+    if (e != hipSuccess) return e;
+    at = 0;
+    for (const ReadBack &r : what)
+        if (at + r.bytes <= room) {
+            memcpy(r.to, pin + at, r.bytes);
+            at += gbt_align(r.bytes, 16);
+        }
+    return hipSuccess;
+}
 
 hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr, const int32_t *indices,
                             const float *values, int64_t n, int F, int64_t n_values, int B, float *cuts,
@@ -740,7 +942,7 @@ hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr,
     (void)ws_bytes;
     *status = GBT_OK;
     hipStream_t s = ctx->stream;
-    const QLayout L = q_layout(n, F, n_values);
+    const QLayout L = q_layout(n, F, n_values, B);
     uint32_t *keys_a = (uint32_t *)(ws + L.keys_a), *keys_b = (uint32_t *)(ws + L.keys_b);
     uint32_t *tile_hist = (uint32_t *)(ws + L.tile_hist);
     uint64_t *seg_off = (uint64_t *)(ws + L.seg_off);
@@ -755,7 +957,7 @@ hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr,
 
     // 1. key segments
     if (dense) {
-        offsets_kernel<<<1, 1, 0, s>>>(nullptr, F, n, seg_off, blk_off, chk_off, kScanChunk);
+        offsets_kernel<<<1, 1024, 0, s>>>(nullptr, F, n, seg_off, blk_off, chk_off, kScanChunk);
         if (n > 0 && F <= 64) {
             const size_t lds = (size_t)kTrNarrowRows * (F | 1) * 4;   // at most 65 KB
             GbtLdsGuard lds_guard(lds);
@@ -770,47 +972,65 @@ hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr,
             dense_keys_kernel<<<grid, 256, 0, s>>>(X, n, F, keys_a);
         }
     } else {
-        Q_HIP(gbt_launch_fill_u64(s, (uint64_t *)counts, 0, (int64_t)(gbt_align((size_t)F * 4) / 8)));
-        Q_HIP(gbt_launch_fill_u64(s, (uint64_t *)cursor, 0, (int64_t)(gbt_align((size_t)F * 4) / 8)));
-        const int csr_grid = (int)((n_values + kCsrChunk - 1) / kCsrChunk);
-        if (n_values > 0) csr_count_kernel<<<csr_grid, 256, 0, s>>>(indices, n_values, F, counts);
-        offsets_kernel<<<1, 1, 0, s>>>(counts, F, 0, seg_off, blk_off, chk_off, kScanChunk);
-        if (n_values > 0)
-            csr_scatter_kernel<<<csr_grid, 256, 0, s>>>(indices, values, n_values, F, seg_off, cursor, keys_a);
+        if (F <= kCsrLdsCols) {
+            const int W = csr_workgroups(ctx->num_cu, n_values);
+            uint32_t *table = (uint32_t *)(ws + L.csr_table);
+            const size_t lds = csr_scatter_lds(F);
+            GbtLdsGuard lds_guard(lds);
+            if (lds_guard.needed)
+                Q_HIP(hipFuncSetAttribute((const void *)csr_scatter_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            csr_count_kernel<<<W, kCsrBlock, (size_t)F * 4, s>>>(indices, n_values, F, table);
+            csr_offsets_kernel<<<F, 64, 0, s>>>(table, W, counts);
+            offsets_kernel<<<1, 1024, 0, s>>>(counts, F, 0, seg_off, blk_off, chk_off, kScanChunk);
+            csr_scatter_kernel<<<W, kCsrBlock, lds, s>>>(indices, values, n_values, F, seg_off, table, keys_a);
+        } else {
+            Q_HIP(gbt_launch_fill_u64(s, (uint64_t *)counts, 0, (int64_t)(gbt_align((size_t)F * 4) / 8)));
+            Q_HIP(gbt_launch_fill_u64(s, (uint64_t *)cursor, 0, (int64_t)(gbt_align((size_t)F * 4) / 8)));
+            const int csr_grid = (int)((n_values + kCsrChunk - 1) / kCsrChunk);
+            if (n_values > 0) csr_count_direct_kernel<<<csr_grid, 256, 0, s>>>(indices, n_values, F, counts);
+            offsets_kernel<<<1, 1024, 0, s>>>(counts, F, 0, seg_off, blk_off, chk_off, kScanChunk);
+            if (n_values > 0)
+                csr_scatter_direct_kernel<<<csr_grid, 256, 0, s>>>(indices, values, n_values, F, seg_off, cursor, keys_a);
+        }
     }
     Q_HIP(hipGetLastError());
-    // number of sort tiles
-    Q_HIP(hipMemcpyAsync(ctx->pinned + GBT_STAGING_BYTES / 2, blk_off + F, 4, hipMemcpyDeviceToHost, s));
-    Q_HIP(hipMemcpyAsync(ctx->pinned + GBT_STAGING_BYTES / 2 + 4, chk_off + F, 4, hipMemcpyDeviceToHost, s));
-    Q_HIP(hipStreamSynchronize(s));
-    uint32_t n_tiles, n_chunks;
-    memcpy(&n_tiles, ctx->pinned + GBT_STAGING_BYTES / 2, 4);
-    memcpy(&n_chunks, ctx->pinned + GBT_STAGING_BYTES / 2 + 4, 4);
-    if ((int64_t)n_tiles > L.max_tiles || (int64_t)n_chunks > L.max_chunks) {
-        *status = gbt_fail(ctx, GBT_EINVAL, "gbt_quantise: inconsistent input (tile count)");
-        return hipSuccess;
-    }
-
-    // 2. four stable 8-bit passes between the two key buffers; a segment skips the passes whose digit is the same
-    //    for all its keys (small integers stored as floats: the low mantissa bytes) and stays where it is
-    Q_HIP(gbt_launch_fill_u64(s, (uint64_t *)seg_flags, 0, (int64_t)(gbt_align((size_t)F * 4) / 8)));
-    for (int pass = 0; pass < 4 && n_tiles > 0; ++pass) {
-        const int shift = pass * 8;
-        sort_hist_kernel<<<n_tiles, kSortBlock, 0, s>>>(keys_a, keys_b, seg_flags, seg_off, blk_off, F, shift, tile_hist);
-        scan_partial_kernel<<<n_chunks, 256, 0, s>>>(blk_off, chk_off, F, tile_hist, chunk_tot);
-        scan_chunks_kernel<<<F, 256, 0, s>>>(chk_off, seg_off, seg_flags, chunk_tot);
-        scan_apply_kernel<<<n_chunks, 256, 0, s>>>(blk_off, chk_off, F, tile_hist, chunk_tot);
-        sort_scatter_kernel<<<n_tiles, kSortBlock, 0, s>>>(keys_a, keys_b, seg_flags, seg_off, blk_off, F, shift, tile_hist);
-        flip_kernel<<<(F + 255) / 256, 256, 0, s>>>(seg_flags, F);
-    }
-    Q_HIP(hipGetLastError());
-
-    // 3. cuts
-    cuts_kernel<<<F, 64, 0, s>>>(keys_a, keys_b, seg_flags, seg_off, F, B, cuts, nb, present);
-    Q_HIP(hipGetLastError());
+    // 2. + 3. the cuts: by selection where that applies, else (or where it says it cannot) from the sorted segments
     std::vector<int32_t> hnb((size_t)F);
-    Q_HIP(hipMemcpyAsync(hnb.data(), nb, (size_t)F * 4, hipMemcpyDeviceToHost, s));
-    Q_HIP(hipStreamSynchronize(s));
+    std::vector<uint32_t> hp((size_t)F);   // values that are not missing
+    bool done = false;
+    SelArrays A{};
+    if (gbt_select_ok(B) && !ctx->quantise_sort) {
+        gbt_select_layout(F, n_values, B, ws + L.select, &A);
+        Q_HIP(gbt_launch_select(ctx, keys_a, keys_b, seg_off, blk_off, F, n_values, B, A, cuts, nb, present));
+        if (dense && packed) Q_HIP(gbt_launch_bin_table(ctx, F, B, A, cuts, nb));
+        uint32_t failed = 0;
+        Q_HIP(read_back(ctx, {{&failed, A.flag, 4}, {hnb.data(), nb, (size_t)F * 4}, {hp.data(), present, (size_t)F * 4}}));
+        done = failed == 0;
+    }
+    if (!done) {
+        uint32_t n_tiles = 0, n_chunks = 0;
+        Q_HIP(read_back(ctx, {{&n_tiles, blk_off + F, 4}, {&n_chunks, chk_off + F, 4}}));
+        if ((int64_t)n_tiles > L.max_tiles || (int64_t)n_chunks > L.max_chunks) {
+            *status = gbt_fail(ctx, GBT_EINVAL, "gbt_quantise: inconsistent input (tile count)");
+            return hipSuccess;
+        }
+        // four stable 8-bit passes between the two key buffers; a segment skips the passes whose digit is the same
+        // for all its keys (small integers stored as floats: the low mantissa bytes) and stays where it is
+        Q_HIP(gbt_launch_fill_u64(s, (uint64_t *)seg_flags, 0, (int64_t)(gbt_align((size_t)F * 4) / 8)));
+        for (int pass = 0; pass < 4 && n_tiles > 0; ++pass) {
+            const int shift = pass * 8;
+            sort_hist_kernel<<<n_tiles, kSortBlock, 0, s>>>(keys_a, keys_b, seg_flags, seg_off, blk_off, F, shift, tile_hist);
+            scan_partial_kernel<<<n_chunks, 256, 0, s>>>(blk_off, chk_off, F, tile_hist, chunk_tot);
+            scan_chunks_kernel<<<F, 256, 0, s>>>(chk_off, seg_off, seg_flags, chunk_tot);
+            scan_apply_kernel<<<n_chunks, 256, 0, s>>>(blk_off, chk_off, F, tile_hist, chunk_tot);
+            sort_scatter_kernel<<<n_tiles, kSortBlock, 0, s>>>(keys_a, keys_b, seg_flags, seg_off, blk_off, F, shift, tile_hist);
+            flip_kernel<<<(F + 255) / 256, 256, 0, s>>>(seg_flags, F);
+        }
+        Q_HIP(hipGetLastError());
+        cuts_kernel<<<F, 64, 0, s>>>(keys_a, keys_b, seg_flags, seg_off, F, B, cuts, nb, present);
+        Q_HIP(hipGetLastError());
+        Q_HIP(read_back(ctx, {{hnb.data(), nb, (size_t)F * 4}, {hp.data(), present, (size_t)F * 4}}));
+    }
     int32_t miss = 1;
     for (int f = 0; f < F; ++f) miss = hnb[f] > miss ? hnb[f] : miss;
     if (miss > 65535) {
@@ -819,27 +1039,19 @@ hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr,
     }
 
     if (packed) {
-        // 4b. symbols straight into the bit stream.  Its width follows from the largest symbol, which is known
+        // 3b. symbols straight into the bit stream.  Its width follows from the largest symbol, which is known
         //     without binning: the largest present value of a feature falls into its last bin, and the missing
         //     symbol (max_f nb[f]) occurs iff some element has no value.
-        bool any_missing;
-        if (dense) {
-            std::vector<uint32_t> hp((size_t)F);
-            Q_HIP(hipMemcpyAsync(hp.data(), present, (size_t)F * 4, hipMemcpyDeviceToHost, s));
-            Q_HIP(hipStreamSynchronize(s));
-            uint64_t tot = 0;
-            for (int f = 0; f < F; ++f) tot += hp[f];
-            any_missing = tot < (uint64_t)n * (uint64_t)F;
-        } else {
+        uint64_t tot = 0;
+        for (int f = 0; f < F; ++f) tot += hp[f];
+        bool any_missing = tot < (uint64_t)n * (uint64_t)F;
+        if (!dense && !any_missing && n > 0) {   // as many values as elements; a row may still have fewer than F (and another more)
             Q_HIP(gbt_launch_fill_u64(s, (uint64_t *)misc, 0, 1));
-            if (n > 0)
-                csr_any_missing_kernel<<<grid_for(n > n_values ? n : n_values, 256 * 8, 4096), 256, 0, s>>>(
-                    indptr, values, n, n_values, F, misc);
+            csr_any_missing_kernel<<<grid_for(n > n_values ? n : n_values, 256 * 8, 4096), 256, 0, s>>>(
+                indptr, values, n, n_values, F, misc);
             Q_HIP(hipGetLastError());
-            Q_HIP(hipMemcpyAsync(ctx->pinned + GBT_STAGING_BYTES / 2, misc, 4, hipMemcpyDeviceToHost, s));
-            Q_HIP(hipStreamSynchronize(s));
-            uint32_t fl;
-            memcpy(&fl, ctx->pinned + GBT_STAGING_BYTES / 2, 4);
+            uint32_t fl = 0;
+            Q_HIP(read_back(ctx, {{&fl, misc, 4}}));
             any_missing = fl != 0;
         }
         const int32_t mx = n == 0 ? 0 : (any_missing ? miss : miss - 1);
@@ -855,7 +1067,10 @@ hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr,
             return hipSuccess;
         }
         const int64_t n_elems = n * (int64_t)F;
-        if (dense) {
+        if (dense && done && gbt_bin_columns_ok(n, F, bits)) {
+            Q_HIP(gbt_launch_bin_columns(ctx, keys_a, keys_b, seg_off, blk_off, n, F, B, A, cuts, nb, (uint32_t)miss, bits,
+                                         packed, n_words));
+        } else if (dense) {
             const size_t cut_bytes = ((size_t)F * (B - 1) + (size_t)F) * 4;
             const int grid = grid_for(n_elems, kPackTile, 8192);
             if (cut_bytes <= 48u * 1024u)
@@ -872,10 +1087,33 @@ hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr,
                                    "packing tile; use gbt_quantise and gbt_compress", F);
                 return hipSuccess;
             }
-            const size_t lds = (((size_t)tile_rows * F + 3) & ~(size_t)3) * 2 + ((size_t)tile_rows + 1) * 8;
-            bin_pack_csr_kernel<<<grid_for(n, tile_rows, 8192), 256, lds, s>>>(indptr, indices, values, n, n_values, F, B,
-                                                                             cuts, nb, (uint32_t)miss, bits, tile_rows,
-                                                                             packed, n_words);
+            // the cuts kept in LDS, a power of two less one per feature: at most 56 KB of them
+            int cut_log = 0, step0 = 1;
+            auto steps_of = [&](int cl) {
+                int st = 1;
+                while (2 * st - 1 < (B - 1) >> cl) st *= 2;
+                return st;
+            };
+            for (;; ++cut_log) {
+                step0 = steps_of(cut_log);
+                if (step0 == 1 || (size_t)F * (2 * step0 - 1) * 4 <= 56u * 1024u) break;
+            }
+            int log_lanes = 0;   // lanes per row: at least a row's average number of entries, where that is below 64
+            while (log_lanes < 6 && ((int64_t)n << log_lanes) < n_values) ++log_lanes;
+            const size_t lds = (size_t)tile_rows * F * 2 + (size_t)F * (2 * step0 - 1) * 4 + (size_t)F * 4 + ((size_t)tile_rows + 1) * 4;
+            Q_HIP(with_bits(bits, [&](auto bc) {
+                constexpr int BITS = decltype(bc)::value;
+                GbtLdsGuard lds_guard(lds);
+                if (lds_guard.needed) {
+                    hipError_t e = hipFuncSetAttribute((const void *)bin_pack_csr_kernel<BITS>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                    if (e != hipSuccess) return e;
+                }
+                bin_pack_csr_kernel<BITS><<<grid_for(n, tile_rows, 2 * ctx->num_cu), kCsrPackBlock, lds, s>>>(
+                    indptr, indices, values, n, n_values, F, B, cuts, nb, (uint32_t)miss, tile_rows, log_lanes, cut_log, step0,
+                    packed, n_words);
+                return hipGetLastError();
+            }));
         }
         Q_HIP(hipGetLastError());
         Q_HIP(hipStreamSynchronize(s));
@@ -885,7 +1123,7 @@ hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr,
         return hipSuccess;
     }
 
-    // 4. symbols
+    // 3. symbols
     Q_HIP(gbt_launch_fill_u64(s, (uint64_t *)misc, 0, 1));
     if (n > 0) {
         if (dense) {

@@ -1,0 +1,102 @@
+"""Quantile cuts by selection (Sec. 2.1): columns whose values test the cells, slots and ranks of the selection, against the
+oracle's cuts and against the library's own sort (-m gpu).  Everything is compared bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctxs():
+    import os
+    import paper_1806_11248_amd as g
+    sel = g.Context(0)
+    os.environ["GBT_TUNE_QUANTISE_SORT"] = "1"
+    try:
+        srt = g.Context(0)
+    finally:
+        del os.environ["GBT_TUNE_QUANTISE_SORT"]
+    yield sel, srt
+    sel.close()
+    srt.close()
+
+
+def _columns(n, B, rng):
+    u = rng.random(n)
+    cols = {
+        "normal": rng.standard_normal(n),
+        "lognormal": rng.lognormal(0, 4, n),
+        "constant": np.full(n, 3.5),
+        "two values": np.where(u < 0.999, 1.0, 2.0),
+        "B values": np.floor(u * B),
+        "B + 1 values": np.floor(u * (B + 1)),
+        "rare categories": np.floor(300 * u ** 6),
+        # more than B values in fewer than B cells: neighbours of one float
+        "close together": 1.0 + np.floor(u * 4 * B) * 2.0 ** -23,
+        "fewer close together": 1.0 + np.floor(u * (B // 2 + 1)) * 2.0 ** -23,
+        "one value and a crowd beside it": np.where(u < 0.6, 40.0, 40.0 + rng.standard_normal(n) * 1e-3),
+        "zeros of both signs": np.where(u < 0.3, -0.0, np.where(u < 0.6, 0.0, rng.standard_normal(n) * 1e-30)),
+        "infinities": np.where(u < 0.1, -np.inf, np.where(u < 0.2, np.inf, rng.standard_normal(n))),
+        "mostly missing": np.where(u < 0.97, np.nan, rng.standard_normal(n)),
+        "missing": np.full(n, np.nan),
+        "sorted": np.sort(rng.standard_normal(n)),
+        "far outliers": np.where(u < 2e-4, rng.standard_normal(n) * 1e30, 100 + rng.random(n)),
+    }
+    return cols
+
+
+@pytest.mark.parametrize("n,B", [(1, 2), (3, 4), (63, 16), (4095, 16), (4096, 256), (4097, 255), (16_385, 64),
+                                 (70_001, 1024), (400_003, 256)])
+def test_cuts_by_selection(ctxs, oracle, n, B):
+    sel, srt = ctxs
+    rng = np.random.default_rng(n * 1000 + B)
+    cols = _columns(n, B, rng)
+    X = np.stack([c.astype(np.float32) for c in cols.values()], 1)
+    print(f"selection n={n} B={B}", flush=True)
+    cuts, nb, packed, bits, mv, ms = sel.quantise_packed(dev(X), max_bins=B)
+    o_cuts, o_nb = oracle.cuts(X, B)
+    for f, name in enumerate(cols):
+        assert int(nb[f]) == o_nb[f], name
+        assert np.array_equal(cuts[f].cpu().numpy(), o_cuts[f]), name
+    c2, nb2, p2, bits2, mv2, ms2 = srt.quantise_packed(dev(X), max_bins=B)
+    assert torch.equal(cuts, c2) and torch.equal(nb, nb2) and torch.equal(packed, p2) and (bits, mv, ms) == (bits2, mv2, ms2)
+
+
+@pytest.mark.parametrize("n,F", [(3_000_000, 3), (900, 700)])
+def test_long_and_many_columns(ctxs, oracle, n, F):
+    """Slots with more collected keys than a wave ranks; more columns than workgroups of a launch share out evenly."""
+    sel, srt = ctxs
+    rng = np.random.default_rng(n + F)
+    X = rng.standard_normal((n, F)).astype(np.float32)
+    X[:, 1] = np.exp(3 * X[:, 1])
+    X[:, 2] = np.where(rng.random(n) < 0.5, 1e-20, X[:, 2])
+    print(f"selection n={n} F={F}", flush=True)
+    a = sel.quantise_packed(dev(X), max_bins=256)
+    b = srt.quantise_packed(dev(X), max_bins=256)
+    assert all(torch.equal(x, y) if isinstance(x, torch.Tensor) else x == y for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("n,F", [(40, 4096), (40, 4097), (5_001, 3), (100_003, 17)])
+def test_csr_columns(ctxs, oracle, n, F):
+    """The counted and the direct scatter by column (4096 columns is where the counters leave LDS), a part-filled last chunk,
+    empty rows."""
+    sel, _ = ctxs
+    rng = np.random.default_rng(n + F)
+    X = np.where(rng.random((n, F)) < 0.3, rng.standard_normal((n, F)), np.nan).astype(np.float32)
+    X[n // 3: n // 2] = np.nan
+    ok = ~np.isnan(X)
+    indptr = np.concatenate([[0], np.cumsum(ok.sum(1))]).astype(np.int64)
+    csr = tuple(dev(a) for a in (indptr, np.nonzero(ok)[1].astype(np.int32), X[ok]))
+    print(f"csr columns n={n} F={F}", flush=True)
+    cuts, nb, sym, mv, ms = sel.quantise(csr=csr, max_bins=64, n=n, F=F)
+    o_cuts, o_nb = oracle.cuts(X, 64)
+    assert np.array_equal(nb.cpu().numpy(), o_nb) and np.array_equal(cuts.cpu().numpy(), o_cuts)
+    o_sym, o_missing, o_mx = oracle.bin_matrix(X, o_cuts, o_nb)
+    assert (mv, ms) == (o_mx, o_missing) and np.array_equal(sym.cpu().numpy(), o_sym)
+    if F <= 700:
+        c2, nb2, packed, bits, mv2, ms2 = sel.quantise_packed(csr=csr, max_bins=64, n=n, F=F)
+        assert torch.equal(c2, cuts) and (mv2, ms2) == (mv, ms)
+        assert np.array_equal(packed.cpu().numpy().view(np.uint32), oracle.pack(o_sym, bits))
