@@ -100,3 +100,20 @@ def test_csr_columns(ctxs, oracle, n, F):
         c2, nb2, packed, bits, mv2, ms2 = sel.quantise_packed(csr=csr, max_bins=64, n=n, F=F)
         assert torch.equal(c2, cuts) and (mv2, ms2) == (mv, ms)
         assert np.array_equal(packed.cpu().numpy().view(np.uint32), oracle.pack(o_sym, bits))
+
+
+@pytest.mark.parametrize("n,F", [(1, 1), (1, 64), (1, 65), (255, 1), (256, 13), (257, 63), (513, 64), (63, 65), (64, 128),
+                                 (65, 129), (1_000, 255)])
+def test_dense_keys(ctxs, oracle, n, F):
+    """Keys by column from both transposes (64 columns is where they meet): part-filled last tiles of rows and columns, and
+    column counts that do and do not divide a workgroup's stride of 256 elements."""
+    sel, _ = ctxs
+    rng = np.random.default_rng(n * 1000 + F)
+    X = np.where(rng.random((n, F)) < 0.9, rng.standard_normal((n, F)), np.nan).astype(np.float32)
+    print(f"dense keys n={n} F={F}", flush=True)
+    cuts, nb, packed, bits, mv, ms = sel.quantise_packed(dev(X), max_bins=32)
+    o_cuts, o_nb = oracle.cuts(X, 32)
+    assert np.array_equal(nb.cpu().numpy(), o_nb) and np.array_equal(cuts.cpu().numpy(), o_cuts)
+    o_sym, o_missing, o_mx = oracle.bin_matrix(X, o_cuts, o_nb)
+    assert (mv, ms) == (o_mx, o_missing)
+    assert np.array_equal(packed.cpu().numpy().view(np.uint32), oracle.pack(o_sym, bits))
