@@ -47,6 +47,7 @@ struct gbt_ctx {
     int hist8_stagger;      // its workgroups on one compute unit get unequal shares of rows: spread in 1/256ths
     int sparse_jobs_per_cu; // row pieces per compute unit and launch of the sparse-row histogram kernel
     int quantise_sort;      // 1: cuts from sorted columns also where selection applies
+    int quantise_work;      // key reads one workgroup of the selection may spend on a column (0: its own rule)
     int sparse_tiled;       // 1: keep the sparse-row LDS histogram under hist_lds_kb even where all ids would fit
     char *part_static;      // this device's copy of the static partition scratch (gbt_partition_static), or NULL
     size_t up_off;          // next free byte of the upload ring (first half of `pinned`)

@@ -37,7 +37,7 @@ constexpr int kSmallSlot = 256;        // collected keys up to which a wave rank
 constexpr int kMidSlot = 8192;         // ... and up to which a workgroup of 256 threads takes one
 constexpr int kMidBits = 12, kBigBits = 14;   // counters of those workgroups (16 and 64 KB of LDS)
 constexpr int kMarkBits = 19;          // bits of the mark table (64 KB of LDS)
-constexpr uint64_t kSlotWorkMax = 1ull << 26;   // key reads one workgroup may spend on one slot or feature
+constexpr uint64_t kSlotWorkMax = 1ull << 26;   // key reads one workgroup may spend on one slot or feature (GBT_TUNE_QUANTISE_WORK)
 enum : uint32_t { kSelOrder = 0, kSelDistinct = 1 };
 constexpr uint16_t kNoSlot = 0xffff;
 
@@ -468,7 +468,8 @@ static_assert(kCollectPer * kSelBlock <= 65536, "a rank inside a step has 16 bit
 // has a slot, so nothing is missing for the order statistics).
 __global__ __launch_bounds__(kSelBlock) void sel_distinct_kernel(const uint64_t *__restrict__ seg_off, int B, SelArrays A,
                                                                  const uint32_t *__restrict__ collected,
-                                                                 float *__restrict__ cuts, int32_t *__restrict__ nb) {
+                                                                 float *__restrict__ cuts, int32_t *__restrict__ nb,
+                                                                 uint64_t work_max) {
     extern __shared__ uint32_t dyn[];
     uint32_t *mark = dyn;                               // 2^kMarkBits bits
     uint32_t *ext = dyn + (1 << kMarkBits) / 32;        // B + 1 distinct keys of the slots with collected keys, in order
@@ -499,8 +500,12 @@ __global__ __launch_bounds__(kSelBlock) void sel_distinct_kernel(const uint64_t 
         const uint32_t *k = collected + seg_off[f] + sl.off;
         const uint32_t span = 1u << sl.shift, win = span < (1u << kMarkBits) ? span : (1u << kMarkBits);
         work += (uint64_t)L * (span / win);
-        if (work > kSlotWorkMax) {
-            if (tid == 0) A.flag[0] = 1;
+        if (work > work_max) {   // (cuts and nb are written all the same: kernels behind this one may read them)
+            for (int i = tid; i < B - 1; i += kSelBlock) c[i] = __uint_as_float(0x7f800000u);
+            if (tid == 0) {
+                nb[f] = 1;
+                A.flag[0] = 1;
+            }
             return;
         }
         const uint32_t words = (win + 31) / 32;
@@ -642,7 +647,8 @@ __global__ __launch_bounds__(256) void sel_order_small_kernel(const uint64_t *__
 template <int BLOCK, int BITS>
 __global__ __launch_bounds__(BLOCK) void sel_order_kernel(const uint64_t *__restrict__ seg_off, int F, int B, SelArrays A,
                                                           const uint32_t *__restrict__ present,
-                                                          const uint32_t *__restrict__ collected, int cls) {
+                                                          const uint32_t *__restrict__ collected, int cls,
+                                                          uint64_t work_max) {
     static_assert(2 * BITS >= kSegShift + 1, "two levels reach the last bit");
     extern __shared__ uint32_t dyn[];
     uint32_t *cnt = dyn;                     // 2^BITS
@@ -712,7 +718,7 @@ __global__ __launch_bounds__(BLOCK) void sel_order_kernel(const uint64_t *__rest
         take(sl.key_lo, nb1, rest, sl.start);
         if (rest > 0) {
             const uint32_t nbk = n_buckets;   // (at most the slot's ranks, so at most B)
-            if ((uint64_t)nbk * L > kSlotWorkMax) {
+            if ((uint64_t)nbk * L > work_max) {
                 if (tid == 0) A.flag[0] = 1;
             } else {
                 for (uint32_t b = 0; b < nbk; ++b) {
@@ -752,6 +758,7 @@ __global__ __launch_bounds__(kSelBlock) void sel_bins_kernel(int B, SelArrays A,
                                                              const int32_t *__restrict__ nb) {
     __shared__ uint32_t seg[kSegs];
     __shared__ uint32_t ck[kSelBinsMax];
+    if (A.flag[0]) return;   // some feature was given up: the cuts are not final, and the table is not used
     const int f = blockIdx.x;
     const uint32_t nc = A.n_cells[f];
     const int ncut = nb[f] - 1;
@@ -954,6 +961,7 @@ hipError_t gbt_launch_select(gbt_ctx *ctx, const uint32_t *keys, uint32_t *colle
     const size_t lds_collect = (size_t)B * 12 + (size_t)A.cap * 2;
     const size_t lds_distinct = (size_t)(1 << kMarkBits) / 8 + (size_t)(3 * B + 1) * 4;
     const size_t lds_big = (size_t)(1 << kBigBits) * 4 + (size_t)B * 8, lds_mid = (size_t)(1 << kMidBits) * 4 + (size_t)B * 8;
+    const uint64_t work_max = ctx->quantise_work > 0 ? (uint64_t)ctx->quantise_work : kSlotWorkMax;
     GbtLdsGuard guard(lds_distinct);
     hipError_t e = hipSuccess;
     auto raise = [&](const void *fn, size_t lds) {
@@ -970,13 +978,13 @@ hipError_t gbt_launch_select(gbt_ctx *ctx, const uint32_t *keys, uint32_t *colle
     sel_count_kernel<<<grid, kSelBlock, lds_count, s>>>(keys, seg_off, blk_off, F, A);
     sel_pick_kernel<<<F, kSelBlock, 0, s>>>(A, B, present);
     sel_collect_kernel<<<grid, kSelBlock, lds_collect, s>>>(keys, seg_off, blk_off, F, B, A, collected);
-    sel_distinct_kernel<<<F, kSelBlock, lds_distinct, s>>>(seg_off, B, A, collected, cuts, nb);
+    sel_distinct_kernel<<<F, kSelBlock, lds_distinct, s>>>(seg_off, B, A, collected, cuts, nb, work_max);
     const uint64_t all = (uint64_t)F * B;
     auto at_most = [&](uint64_t n, int per_cu) { return (unsigned)(n < (uint64_t)per_cu * ctx->num_cu ? n : (uint64_t)per_cu * ctx->num_cu); };
     sel_list_kernel<<<(unsigned)((all + kSelBlock - 1) / kSelBlock), kSelBlock, 0, s>>>(F, B, A);
     sel_order_small_kernel<<<at_most((all + 3) / 4, 8), 256, 0, s>>>(seg_off, B, A, present, collected);
-    sel_order_kernel<256, kMidBits><<<at_most(all, 8), 256, lds_mid, s>>>(seg_off, F, B, A, present, collected, 1);
-    sel_order_kernel<1024, kBigBits><<<at_most(all, 2), 1024, lds_big, s>>>(seg_off, F, B, A, present, collected, 2);
+    sel_order_kernel<256, kMidBits><<<at_most(all, 8), 256, lds_mid, s>>>(seg_off, F, B, A, present, collected, 1, work_max);
+    sel_order_kernel<1024, kBigBits><<<at_most(all, 2), 1024, lds_big, s>>>(seg_off, F, B, A, present, collected, 2, work_max);
     sel_cuts_kernel<<<F, 256, 0, s>>>(B, A, cuts, nb);
     return hipGetLastError();
 }

@@ -117,3 +117,45 @@ def test_dense_keys(ctxs, oracle, n, F):
     o_sym, o_missing, o_mx = oracle.bin_matrix(X, o_cuts, o_nb)
     assert (mv, ms) == (o_mx, o_missing)
     assert np.array_equal(packed.cpu().numpy().view(np.uint32), oracle.pack(o_sym, bits))
+
+
+def _context(**env):
+    import os
+    import paper_1806_11248_amd as g
+    os.environ.update(env)
+    try:
+        return g.Context(0)
+    finally:
+        for k in env:
+            del os.environ[k]
+
+
+def _check_all_forms(ctx, oracle, X, B, names):
+    """Dense and CSR, packed and as symbols, against the oracle."""
+    n, F = X.shape
+    o_cuts, o_nb = oracle.cuts(X, B)
+    o_sym, o_missing, o_mx = oracle.bin_matrix(X, o_cuts, o_nb)
+    ok = ~np.isnan(X)
+    csr = tuple(dev(a) for a in (np.concatenate([[0], np.cumsum(ok.sum(1))]).astype(np.int64), np.nonzero(ok)[1].astype(np.int32), X[ok]))
+    for arg in (dict(X=dev(X)), dict(csr=csr, n=n, F=F)):
+        form = next(iter(arg))
+        cuts, nb, packed, bits, mv, ms = ctx.quantise_packed(**arg, max_bins=B)
+        c2, nb2, sym, mv2, ms2 = ctx.quantise(**arg, max_bins=B)
+        for f, name in enumerate(names):
+            assert int(nb[f]) == o_nb[f] and np.array_equal(cuts[f].cpu().numpy(), o_cuts[f]), (form, name)
+        assert torch.equal(cuts, c2) and torch.equal(nb, nb2) and (mv, ms) == (mv2, ms2) == (o_mx, o_missing), form
+        assert np.array_equal(packed.cpu().numpy().view(np.uint32), oracle.pack(o_sym, bits)), form
+        assert np.array_equal(sym.cpu().numpy(), o_sym), form
+
+
+@pytest.mark.parametrize("n,B", [(3, 4), (4097, 255), (50_021, 64)])
+@pytest.mark.parametrize("work", [1, 300, 20_000])
+def test_columns_given_up(oracle, n, B, work):
+    """Columns that would cost a workgroup more than `work` key reads are sorted after all: given up while their distinct
+    values are counted (1: whatever was collected), and where a slot's buckets are looked into."""
+    ctx = _context(GBT_TUNE_QUANTISE_WORK=str(work))
+    rng = np.random.default_rng(n * 1000 + B + work)
+    cols = _columns(n, B, rng)
+    print(f"given up n={n} B={B} work={work}", flush=True)
+    _check_all_forms(ctx, oracle, np.stack([c.astype(np.float32) for c in cols.values()], 1), B, list(cols))
+    ctx.close()
