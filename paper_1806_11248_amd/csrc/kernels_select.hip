@@ -753,7 +753,9 @@ __global__ __launch_bounds__(256) void sel_cuts_kernel(int B, SelArrays A, float
 
 // ---- symbols of whole columns -------------------------------------------------------------------------------------
 // The symbol of a key is the number of cuts at or below it.  Most cells hold no cut: their keys' symbol is one table
-// read behind the cell; in the others (bit 15) the cuts from there on are compared.  slot_of is free by now.
+// read behind the cell; in the others (bit 15) the cuts up to the next cell's are bisected: one or two of them as a rule,
+// most of a column's where its values are neighbours as floats (100,000 x 200 ids of 200 values above 10^7, the whole call:
+// 1.69 ms one cut after the other, 0.45 bisected).  slot_of is free by now.
 __global__ __launch_bounds__(kSelBlock) void sel_bins_kernel(int B, SelArrays A, const float *__restrict__ cuts,
                                                              const int32_t *__restrict__ nb) {
     __shared__ uint32_t seg[kSegs];
@@ -791,7 +793,7 @@ __global__ __launch_bounds__(kSelBlock) void col_bins_kernel(const uint32_t *__r
     extern __shared__ uint32_t dyn[];
     __shared__ uint32_t seg[kSegs];
     uint32_t *ck = dyn;                             // B
-    uint16_t *first = (uint16_t *)(dyn + B);        // cap
+    uint16_t *first = (uint16_t *)(dyn + B);        // cap + 1
     TileRun run(blk_off, F);
     uint64_t k0, k1;
     while (run.next(blk_off, seg_off, &k0, &k1)) {
@@ -801,16 +803,21 @@ __global__ __launch_bounds__(kSelBlock) void col_bins_kernel(const uint32_t *__r
         __syncthreads();
         for (int i = threadIdx.x; i < kSegs; i += kSelBlock) seg[i] = A.seg[(uint64_t)f * kSegs + i];
         for (uint32_t i = threadIdx.x; i < nc; i += kSelBlock) first[i] = A.slot_of[(uint64_t)f * A.cap + i];
+        if (threadIdx.x == 0) first[nc] = (uint16_t)ncut;
         for (uint32_t i = threadIdx.x; i < ncut; i += kSelBlock) ck[i] = float_key(cuts[(int64_t)f * (B - 1) + i]);
         __syncthreads();
         const uint32_t *p = keys + seg_off[f];
         T *o = sym + (int64_t)f * stride;
         auto symbol = [&](uint32_t k) -> uint32_t {
             if (k == kMissingKey) return missing;
-            uint32_t b = first[cell_of(seg, k)];
+            const uint32_t c = cell_of(seg, k);
+            uint32_t b = first[c];
             if (b & 0x8000u) {
                 b &= 0x7fffu;
-                while (b < ncut && ck[b] <= k) ++b;
+                for (uint32_t e = first[c + 1] & 0x7fffu; b < e;) {
+                    const uint32_t mid = (b + e) >> 1;
+                    if (ck[mid] <= k) b = mid + 1; else e = mid;
+                }
             }
             return b;
         };
@@ -1010,7 +1017,7 @@ hipError_t bin_pack_columns(gbt_ctx *ctx, const uint32_t *keys, void *cols, cons
     const int grid = (int)(tiles < 2 * ctx->num_cu ? tiles : 2 * ctx->num_cu);
     const int lr = pack_log_rows(F, sizeof(T));
     const size_t lds = (size_t)F * (((size_t)sizeof(T) << lr) + 4);
-    col_bins_kernel<T><<<grid, kSelBlock, (size_t)B * 4 + (size_t)A.cap * 2, s>>>(keys, seg_off, blk_off, F, B, A, cuts, nb, missing,
+    col_bins_kernel<T><<<grid, kSelBlock, (size_t)B * 4 + (size_t)(A.cap + 1) * 2, s>>>(keys, seg_off, blk_off, F, B, A, cuts, nb, missing,
                                                                                  (T *)cols, stride);
     return with_bits(bits, [&](auto bc) {
         constexpr int BITS = decltype(bc)::value;
