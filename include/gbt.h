@@ -131,7 +131,8 @@ typedef struct gbt_tree {
  *   GBT_TUNE_LOSSGUIDE_BATCH    [16] 1..64: open leaves expanded per round of loss-guided growth
  *   GBT_TUNE_SPARSE_JOBS        [1] 1..64: sparse-row histogram workgroups per compute unit
  *   GBT_TUNE_QUANTISE_SORT      [0] 1: order statistics from sorted columns also where they would be found by selection
- *   GBT_TUNE_QUANTISE_WORK      [2^26] 1..2^31-1: key reads one workgroup of the selection may spend on a column before the sort is taken
+ *   GBT_TUNE_QUANTISE_WORK      [0: by lengths] 1..2^31-1: key reads one workgroup of the selection may spend on a column before it is sorted
+ *   GBT_TUNE_QUANTISE_LATE      [0] 1: columns are sorted only once their selection has reached that, not by the look of a sample
  *   GBT_TUNE_SPARSE_TILED       [0] 1: sparse-row histogram in id-range tiles even where all ids fit one workgroup's LDS */
 GBT_API int32_t gbt_create(gbt_ctx **ctx_out, int32_t device, void *stream);
 GBT_API int32_t gbt_destroy(gbt_ctx *ctx);

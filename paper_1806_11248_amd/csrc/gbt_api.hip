@@ -247,6 +247,7 @@ extern "C" int32_t gbt_create(gbt_ctx **ctx_out, int32_t device, void *stream) {
         if (const char *e12 = getenv("GBT_TUNE_SPARSE_JOBS")) { int v = atoi(e12); if (v >= 1 && v <= 64) c->sparse_jobs_per_cu = v; }
         if (const char *e21 = getenv("GBT_TUNE_QUANTISE_SORT")) c->quantise_sort = atoi(e21) != 0;
         if (const char *e22 = getenv("GBT_TUNE_QUANTISE_WORK")) { int v = atoi(e22); if (v >= 1) c->quantise_work = v; }
+        if (const char *e23 = getenv("GBT_TUNE_QUANTISE_LATE")) c->quantise_late = atoi(e23) != 0;
         if (const char *e13 = getenv("GBT_TUNE_SPARSE_TILED")) c->sparse_tiled = atoi(e13) != 0;
         c->lossguide_batch = 16;
         if (const char *e16 = getenv("GBT_TUNE_LOSSGUIDE_BATCH")) { int v = atoi(e16); if (v >= 1 && v <= 64) c->lossguide_batch = v; }

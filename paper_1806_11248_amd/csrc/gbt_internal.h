@@ -47,7 +47,8 @@ struct gbt_ctx {
     int hist8_stagger;      // its workgroups on one compute unit get unequal shares of rows: spread in 1/256ths
     int sparse_jobs_per_cu; // row pieces per compute unit and launch of the sparse-row histogram kernel
     int quantise_sort;      // 1: cuts from sorted columns also where selection applies
-    int quantise_work;      // key reads one workgroup of the selection may spend on a column (0: its own rule)
+    int quantise_work;      // key reads one workgroup of the selection may spend on a column (0: by the column's length)
+    int quantise_late;      // 1: columns go to the sort only where their selection has reached that, not by their sample
     int sparse_tiled;       // 1: keep the sparse-row LDS histogram under hist_lds_kb even where all ids would fit
     char *part_static;      // this device's copy of the static partition scratch (gbt_partition_static), or NULL
     size_t up_off;          // next free byte of the upload ring (first half of `pinned`)
@@ -469,7 +470,8 @@ constexpr uint32_t kHMask = (1u << kHShift) - 1u;
 
 
 // order statistics by selection (kernels_select.hip): keys, segments and tiles as kernels_quantise.hip lays them out,
-// `collected` a second buffer of n_values words; cuts, nb and present (values that are not missing) per feature
+// `collected` a second buffer of n_values words; cuts, nb and present (values that are not missing) per feature, but for
+// those whose mode is kSelSorted (some is iff *A.flag is not zero): theirs are still to be found
 struct SelArrays;
 bool gbt_select_ok(int B);
 size_t gbt_select_layout(int F, int64_t n_values, int B, char *base, SelArrays *A);   // bytes; base, A may be NULL

@@ -3,8 +3,8 @@
 //   1. keys: every feature's values become one contiguous segment of uint32 keys in the floats' order (dense input: an
 //      LDS-tiled transpose, a missing value becomes the largest key; CSR input: counted, offset and scattered by
 //      column);
-//   2. order statistics and cuts by selection (kernels_select.hip), for up to 1024 bins.  With more bins, and for
-//      matrices whose values lie too close together for it, by a segmented LSD radix sort (here): four 8-bit passes,
+//   2. order statistics and cuts by selection (kernels_select.hip), for up to 1024 bins.  With more bins, and for the
+//      columns whose values lie too close together for it, by a segmented LSD radix sort (here): four 8-bit passes,
 //      each a per-tile digit histogram, offsets from the tile histograms and a stable scatter (ranks from wave ballots,
 //      tiles and waves in order), then one wave per feature walks the sorted segment;
 //   3. bin: symbol = number of cuts <= x by bisection over the feature's cuts.
@@ -248,18 +248,23 @@ __global__ __launch_bounds__(256) void csr_scatter_direct_kernel(const int32_t *
 }
 
 // seg_off / blk_off / chk_off [f] = exclusive prefix of the segments' lengths, tiles and scan chunks (kScanChunk tiles
-// each), by one workgroup: a piece of features per thread, then a scan over the pieces.
-__global__ __launch_bounds__(1024) void offsets_kernel(const uint32_t *counts, int F, int64_t fixed_len, uint64_t *seg_off,
-                                                       uint32_t *blk_off, uint32_t *chk_off, int scan_chunk) {
+// each), by one workgroup: a piece of features per thread, then a scan over the pieces.  With `mode` only the features to
+// be sorted (kSelSorted) have tiles.  *dear (may be NULL) is cleared for the selection.
+__global__ __launch_bounds__(1024) void offsets_kernel(const uint32_t *counts, int F, int64_t fixed_len,
+                                                       const uint32_t *__restrict__ mode, uint64_t *seg_off,
+                                                       uint32_t *blk_off, uint32_t *chk_off, int scan_chunk,
+                                                       unsigned long long *dear) {
     __shared__ uint64_t so[1024];
     __shared__ uint32_t bo[1024], co[1024];
     const int tid = threadIdx.x, per = (F + 1023) / 1024, f0 = tid * per, f1 = f0 + per < F ? f0 + per : F;
-    auto tiles_of = [&](uint64_t len) { return (uint32_t)((len + kSortTile - 1) / kSortTile); };
+    auto tiles_of = [&](int f, uint64_t len) {
+        return mode && mode[f] != kSelSorted ? 0u : (uint32_t)((len + kSortTile - 1) / kSortTile);
+    };
     uint64_t o = 0;
     uint32_t b = 0, c = 0;
     for (int f = f0; f < f1; ++f) {
         const uint64_t len = counts ? (uint64_t)counts[f] : (uint64_t)fixed_len;
-        const uint32_t tiles = tiles_of(len);
+        const uint32_t tiles = tiles_of(f, len);
         o += len;
         b += tiles;
         c += (tiles + (uint32_t)scan_chunk - 1) / (uint32_t)scan_chunk;
@@ -285,7 +290,7 @@ __global__ __launch_bounds__(1024) void offsets_kernel(const uint32_t *counts, i
         blk_off[f] = b;
         chk_off[f] = c;
         const uint64_t len = counts ? (uint64_t)counts[f] : (uint64_t)fixed_len;
-        const uint32_t tiles = tiles_of(len);
+        const uint32_t tiles = tiles_of(f, len);
         o += len;
         b += tiles;
         c += (tiles + (uint32_t)scan_chunk - 1) / (uint32_t)scan_chunk;
@@ -294,6 +299,7 @@ __global__ __launch_bounds__(1024) void offsets_kernel(const uint32_t *counts, i
         seg_off[F] = so[1023];
         blk_off[F] = bo[1023];
         chk_off[F] = co[1023];
+        if (dear) *dear = 0;
     }
 }
 
@@ -538,14 +544,14 @@ __device__ inline uint64_t upper_bound_wave(const uint32_t *a, uint64_t lo, uint
     return m ? lo + (uint64_t)__builtin_ctzll(m) : hi;
 }
 
-// One wave per feature.  Wave-uniform control flow throughout; lane 0 writes.
+// One wave per feature (with `mode`: of those that were sorted).  Wave-uniform control flow throughout; lane 0 writes.
 __global__ __launch_bounds__(64) void cuts_kernel(const uint32_t *__restrict__ keys_a, const uint32_t *__restrict__ keys_b,
                                                   const uint32_t *__restrict__ seg_flags,
-                                                  const uint64_t *__restrict__ seg_off, int F, int B,
-                                                  float *__restrict__ cuts, int32_t *__restrict__ nb,
+                                                  const uint64_t *__restrict__ seg_off, const uint32_t *__restrict__ mode,
+                                                  int F, int B, float *__restrict__ cuts, int32_t *__restrict__ nb,
                                                   uint32_t *__restrict__ present) {
     const int f = blockIdx.x, lane = threadIdx.x;
-    if (f >= F) return;
+    if (f >= F || (mode && mode[f] != kSelSorted)) return;
     const uint32_t *v = ((seg_flags[f] & kSegInB) ? keys_b : keys_a) + seg_off[f];
     const uint64_t len = seg_off[f + 1] - seg_off[f];
     float *c = cuts + (int64_t)f * (B - 1);
@@ -980,9 +986,13 @@ hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr,
     uint32_t *present = (uint32_t *)(ws + L.present);
     const bool dense = X != nullptr;
 
+    const bool select = gbt_select_ok(B) && !ctx->quantise_sort;
+    SelArrays A{};
+    if (select) gbt_select_layout(F, n_values, B, ws + L.select, &A);
+
     // 1. key segments
     if (dense) {
-        offsets_kernel<<<1, 1024, 0, s>>>(nullptr, F, n, seg_off, blk_off, chk_off, kScanChunk);
+        offsets_kernel<<<1, 1024, 0, s>>>(nullptr, F, n, nullptr, seg_off, blk_off, chk_off, kScanChunk, A.dear);
         if (n > 0 && F <= 64) {
             const size_t lds = (size_t)kTrNarrowRows * (F | 1) * 4;   // at most 65 KB
             GbtLdsGuard lds_guard(lds);
@@ -1006,31 +1016,34 @@ hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr,
                 Q_HIP(hipFuncSetAttribute((const void *)csr_scatter_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
             csr_count_kernel<<<W, kCsrBlock, (size_t)F * 4, s>>>(indices, n_values, F, table);
             csr_offsets_kernel<<<F, 64, 0, s>>>(table, W, counts);
-            offsets_kernel<<<1, 1024, 0, s>>>(counts, F, 0, seg_off, blk_off, chk_off, kScanChunk);
+            offsets_kernel<<<1, 1024, 0, s>>>(counts, F, 0, nullptr, seg_off, blk_off, chk_off, kScanChunk, A.dear);
             csr_scatter_kernel<<<W, kCsrBlock, lds, s>>>(indices, values, n_values, F, seg_off, table, keys_a);
         } else {
             Q_HIP(gbt_launch_fill_u64(s, (uint64_t *)counts, 0, (int64_t)(gbt_align((size_t)F * 4) / 8)));
             Q_HIP(gbt_launch_fill_u64(s, (uint64_t *)cursor, 0, (int64_t)(gbt_align((size_t)F * 4) / 8)));
             const int csr_grid = (int)((n_values + kCsrChunk - 1) / kCsrChunk);
             if (n_values > 0) csr_count_direct_kernel<<<csr_grid, 256, 0, s>>>(indices, n_values, F, counts);
-            offsets_kernel<<<1, 1024, 0, s>>>(counts, F, 0, seg_off, blk_off, chk_off, kScanChunk);
+            offsets_kernel<<<1, 1024, 0, s>>>(counts, F, 0, nullptr, seg_off, blk_off, chk_off, kScanChunk, A.dear);
             if (n_values > 0)
                 csr_scatter_direct_kernel<<<csr_grid, 256, 0, s>>>(indices, values, n_values, F, seg_off, cursor, keys_a);
         }
     }
     Q_HIP(hipGetLastError());
-    // 2. + 3. the cuts: by selection where that applies, else (or where it says it cannot) from the sorted segments
+    // 2. the cuts: by selection where that applies, else (all of them, or the features it leaves) from the sorted segments
     std::vector<int32_t> hnb((size_t)F);
     std::vector<uint32_t> hp((size_t)F);   // values that are not missing
-    bool done = false;
-    SelArrays A{};
-    if (gbt_select_ok(B) && !ctx->quantise_sort) {
-        gbt_select_layout(F, n_values, B, ws + L.select, &A);
+    bool done = false;                     // by selection, every feature: keys_a is as it was made
+    const uint32_t *to_sort = nullptr;     // the modes of the features, or all are to be sorted
+    if (select) {
         Q_HIP(gbt_launch_select(ctx, keys_a, keys_b, seg_off, blk_off, F, n_values, B, A, cuts, nb, present));
         if (dense && packed) Q_HIP(gbt_launch_bin_table(ctx, F, B, A, cuts, nb));
         uint32_t failed = 0;
         Q_HIP(read_back(ctx, {{&failed, A.flag, 4}, {hnb.data(), nb, (size_t)F * 4}, {hp.data(), present, (size_t)F * 4}}));
         done = failed == 0;
+        if (!done) {
+            to_sort = A.mode;
+            offsets_kernel<<<1, 1024, 0, s>>>(dense ? nullptr : counts, F, dense ? n : 0, to_sort, seg_off, blk_off, chk_off, kScanChunk, nullptr);
+        }
     }
     if (!done) {
         uint32_t n_tiles = 0, n_chunks = 0;
@@ -1052,7 +1065,7 @@ hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr,
             flip_kernel<<<(F + 255) / 256, 256, 0, s>>>(seg_flags, F);
         }
         Q_HIP(hipGetLastError());
-        cuts_kernel<<<F, 64, 0, s>>>(keys_a, keys_b, seg_flags, seg_off, F, B, cuts, nb, present);
+        cuts_kernel<<<F, 64, 0, s>>>(keys_a, keys_b, seg_flags, seg_off, to_sort, F, B, cuts, nb, present);
         Q_HIP(hipGetLastError());
         Q_HIP(read_back(ctx, {{hnb.data(), nb, (size_t)F * 4}, {hp.data(), present, (size_t)F * 4}}));
     }

@@ -15,6 +15,9 @@
 //   distinct, order  the slots' keys sorted, counted or marked in LDS, and the statistics read off;
 //   cuts     statistics thinned to strictly increasing cuts.
 //
+// A column whose values lie so close together that one workgroup would have to read much of it is left to the sort (mode
+// kSelSorted): by its sample as a rule, else as soon as distinct or order meets such a cell.
+//
 // Bound: the two readings (HBM) where columns are long, LDS atomics beside them where a column is a few categories.
 // The sort it replaces (four 8-bit digits) reads and writes every key up to four times.  115M x 13 columns, of which 8
 // categories: sort and cuts 24.6 ms, selection 3.2 ms (count 1.7, collect 1.15); 10M x 50 rows of 10 entries: 2.6 and
@@ -37,8 +40,7 @@ constexpr int kSmallSlot = 256;        // collected keys up to which a wave rank
 constexpr int kMidSlot = 8192;         // ... and up to which a workgroup of 256 threads takes one
 constexpr int kMidBits = 12, kBigBits = 14;   // counters of those workgroups (16 and 64 KB of LDS)
 constexpr int kMarkBits = 19;          // bits of the mark table (64 KB of LDS)
-constexpr uint64_t kSlotWorkMax = 1ull << 26;   // key reads one workgroup may spend on one slot or feature (GBT_TUNE_QUANTISE_WORK)
-enum : uint32_t { kSelOrder = 0, kSelDistinct = 1 };
+constexpr uint32_t kKindDiscrete = 1, kKindNoCollect = 2;   // bits of SelArrays::kind
 constexpr uint16_t kNoSlot = 0xffff;
 
 // Exclusive prefix sum over the workgroup's threads; *total receives the sum.  tmp: one word per wave.
@@ -73,17 +75,54 @@ __device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Key reads that one workgroup may spend on a feature's distinct values or on one slot; beyond it the feature is sorted.  A
+// workgroup reads 2 to 3 keys per ns where they are few distinct ones, which meet on few LDS words (9M collected keys of 108
+// values: 3.1 ms), or come from HBM; 4 to 6 where the whole matrix's keys fit the 256 MB cache (kCachedKeys).  The sort takes
+// about 0.5 ms of launches and 16 ns per 1000 keys, of all features that go there together; the workgroups work side by
+// side.  So the limit follows from `dear`, the keys of all features that would be sorted for their own sake: 8 columns of
+// 10M dates in 64 bins, 1.3 ms, sorted 2.1; 30 columns of 3M narrow normals in 16 bins, 1.6 and 2.3.
+constexpr uint64_t kCachedKeys = 1ull << 25;
+__device__ inline uint64_t work_limit(uint64_t tuned, const uint64_t *seg_off, int F, int f, uint64_t dear, bool discrete) {
+    const uint64_t len = seg_off[f + 1] - seg_off[f], reads = (1ull << 20) + (len > dear ? len : dear) / 32;
+    return tuned ? tuned : discrete || seg_off[F] > kCachedKeys ? reads : reads * 5 / 2;
+}
+constexpr uint32_t kSlotReads = 12u << 10;   // what a slot costs sel_distinct_kernel beside its keys (100 slots: 0.45 ms)
+
+// Bits of the first count of sel_order_kernel<*, most> over a slot of L collected keys: counters for twice the keys, and no
+// more bits left than a second count takes.
+__device__ inline int order_bits(uint32_t L, int shift, int most) {
+    int nb = 33 - __builtin_clz(L | 1u);
+    nb = nb < kSegShift - most ? kSegShift - most : nb > most ? most : nb;
+    return nb > shift ? shift : nb;
+}
+
 // The first k with floor(k m / B) >= rank.
 __device__ inline uint64_t first_k(uint64_t rank, uint64_t m, uint32_t B) { return (rank * B + m - 1) / m; }
 
 // ---- sample ---------------------------------------------------------------------------------------------------
 // One workgroup per feature: 4096 keys at jittered even steps, sorted (bitonic), then the cells.  Also clears the cell
-// counts.
-__global__ __launch_bounds__(kSelBlock) void sel_sample_kernel(const uint32_t *__restrict__ keys,
-                                                               const uint64_t *__restrict__ seg_off, SelArrays A) {
+// counts, and says which features are to be sorted: where values lie so close together that many share a cell (months as
+// 201501.0, dates, ids above 10^7: a cell is never less than 128 neighbouring floats, and 2048 in a discrete feature), one
+// workgroup would read most of the column in sel_distinct_kernel or sel_order_kernel.
+// One column of 10M such months, the whole call: 0.78 ms sorted, 3.34 by selection, 0.85 with this.  The look at the sample
+// takes 3 us of the kernel's 47.
+template <typename Less>
+__device__ inline int sample_bound(const uint32_t *v, int lo, int hi, Less &&less) {   // first j in [lo, hi) without less(v[j])
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (less(v[mid])) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+// (With 80 scalar registers or fewer two workgroups fit a compute unit: 512 columns of 30,000 in 72 us, with 88 in 96.)
+__global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) void sel_sample_kernel(
+    const uint32_t *__restrict__ keys, const uint64_t *__restrict__ seg_off, int B, SelArrays A, uint64_t work_tuned) {
     __shared__ uint32_t v[kSampleMax];
-    __shared__ uint32_t per_seg[kSegs];
+    __shared__ uint32_t per_seg[kSegs];   // sampled keys of an interval, then its first cell and shift
     __shared__ uint32_t tmp[kSelBlock / 64];
+    __shared__ uint32_t n_mixed, sum_other;     // cells of several values, and their sampled keys besides the frequent one
+    __shared__ uint32_t max_other, max_order;   // the dearest cell: such keys, and key reads of sel_order_kernel
     const int f = blockIdx.x, tid = threadIdx.x;
     const uint64_t len = seg_off[f + 1] - seg_off[f];
     const uint32_t *p = keys + seg_off[f];
@@ -121,7 +160,6 @@ __global__ __launch_bounds__(kSelBlock) void sel_sample_kernel(const uint32_t *_
     uint32_t mine = 0, fresh = 0;
     for (int j = tid; j < A.sample_cap; j += kSelBlock) {
         const uint32_t k = j < P ? v[j] : kMissingKey;
-        A.sample[(uint64_t)f * A.sample_cap + j] = k;
         if (k != kMissingKey) {
             atomicAdd(&per_seg[k >> kSegShift], 1u);
             ++mine;
@@ -157,26 +195,74 @@ __global__ __launch_bounds__(kSelBlock) void sel_sample_kernel(const uint32_t *_
     }
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        A.seg[(uint64_t)f * kSegs + tid * PER + i] = first | ((uint32_t)(kSegShift - bits[i]) << 24);
+        per_seg[tid * PER + i] = first | ((uint32_t)(kSegShift - bits[i]) << 24);
         first += 1u << bits[i];
     }
-    if (tid == 0) {
-        A.n_cells[f] = total;
-        A.kind[f] = discrete ? 1u : 0u;
-    }
-    for (uint32_t c = tid; c < total; c += kSelBlock) A.counts[(uint64_t)f * A.cap + c] = 0;
-    if (discrete) {
-        uint32_t *rep = A.rep + (uint64_t)f * A.cap;
-        for (uint32_t c = tid; c < total; c += kSelBlock) {
-            rep[c] = kMissingKey;
-            A.mixed[(uint64_t)f * A.cap + c] = 0;
+    if (tid == 0) n_mixed = sum_other = max_other = max_order = 0;
+    __syncthreads();
+    uint32_t *rep = A.rep + (uint64_t)f * A.cap;
+    if (discrete)
+        for (uint32_t c = tid; c < total; c += kSelBlock) rep[c] = kMissingKey;
+    // The cells of the sampled keys, which are neighbours in v.  (Cells are aligned: keys of one share their top bits.)
+    auto first_of_cell = [&](int j, uint32_t *shift) {
+        *shift = per_seg[v[j] >> kSegShift] >> 24;
+        return v[j] != kMissingKey && (j == 0 || v[j - 1] >> *shift != v[j] >> *shift);
+    };
+    uint32_t shift, heads = 0, used;
+    for (int j = tid; j < P; j += kSelBlock) heads += first_of_cell(j, &shift) ? 1u : 0u;
+    block_scan(heads, tmp, &used);   // (with barriers: `rep` is clear)
+    // What the feature would cost.  In no more cells than bins the distinct values are counted by one workgroup; otherwise a
+    // workgroup takes a cell, and only one with a share of the feature that shows in S / 128 sampled keys can be dear.
+    const int least_keys = used > (uint32_t)B ? S / 128 : 2;
+    const float per_key = (float)len / (float)(S > 0 ? S : 1), per_rank = (float)B / (float)(present > 0 ? present : 1);
+    for (int j = tid; j < P; j += kSelBlock) {
+        if (!first_of_cell(j, &shift)) continue;
+        const uint32_t k = v[j], same = k >> shift;
+        uint32_t mid = k;
+        const int quick = j + (least_keys > 2 ? least_keys : 2) - 1;
+        if (quick < P && v[quick] >> shift == same) {
+            const int end = sample_bound(v, quick + 1, P, [&](uint32_t x) { return x >> shift == same; });
+            mid = v[(j + end) >> 1];   // the frequent key, if there is one: not collected
+            const int m0 = sample_bound(v, j, end, [&](uint32_t x) { return x < mid; });
+            const int m1 = sample_bound(v, m0, end, [&](uint32_t x) { return x <= mid; });
+            const uint32_t other = (uint32_t)(end - j - (m1 - m0));
+            if (other) {
+                const uint32_t reads = shift > (uint32_t)kMarkBits ? other << (shift - kMarkBits) : other;
+                atomicAdd(&n_mixed, 1u);
+                atomicAdd(&sum_other, reads);
+                atomicMax(&max_other, reads);
+                const float L = per_key * (float)other;
+                const int rest = (int)shift - order_bits(L < 2e9f ? (uint32_t)L : 2000000000u, (int)shift, kBigBits);
+                const float cost = rest > 0 ? L * (2.0f + (float)(end - j) * per_rank) : L;
+                atomicMax(&max_order, cost < 4e9f ? (uint32_t)cost : 4000000000u);
+            }
         }
-        __syncthreads();   // (and the table of intervals is written)
-        const uint32_t *seg = A.seg + (uint64_t)f * kSegs;
-        for (int j = tid; j < P; j += kSelBlock)
-            if (v[j] != kMissingKey && (j == 0 || v[j - 1] != v[j])) rep[cell_of(seg, v[j])] = v[j];   // any one of a cell's
+        if (discrete) rep[cell_of(per_seg, k)] = mid;
     }
-    if (f == 0 && tid == 0) {
+    __syncthreads();
+    if (tid == 0) {
+        float cost = (float)max_order;
+        if (used <= (uint32_t)B) {
+            const float all = per_key * (float)sum_other + (float)n_mixed * (float)kSlotReads;
+            if (distinct > (uint32_t)B) {   // it stops behind the slot that brings the one value too many
+                const float part = all * (float)B / (float)distinct + per_key * (float)max_other;
+                cost += part < all ? part : all;
+            } else {
+                cost = all;
+            }
+        }
+        A.kind[f] = discrete ? kKindDiscrete : 0u;
+        A.cost[f] = cost < 4e9f ? (uint32_t)cost : 4000000000u;
+        if (A.cost[f] > work_limit(work_tuned, seg_off, gridDim.x, f, 0, discrete)) atomicAdd(A.dear, (unsigned long long)len);
+        A.n_cells[f] = total;
+    }
+    // what the next kernels read (behind the last barrier: none waits for these stores)
+    for (int j = tid; j < A.sample_cap; j += kSelBlock) A.sample[(uint64_t)f * A.sample_cap + j] = j < P ? v[j] : kMissingKey;
+    for (int i = tid; i < kSegs; i += kSelBlock) A.seg[(uint64_t)f * kSegs + i] = per_seg[i];
+    for (uint32_t c = tid; c < total; c += kSelBlock) A.counts[(uint64_t)f * A.cap + c] = 0;
+    if (discrete)
+        for (uint32_t c = tid; c < total; c += kSelBlock) A.mixed[(uint64_t)f * A.cap + c] = 0;
+    if (f == 0 && tid == 0) {   // (*A.dear is cleared with the offsets: this kernel adds to it)
         A.n_work[0] = A.n_work[1] = A.n_work[2] = 0;
         A.flag[0] = 0;
     }
@@ -230,7 +316,8 @@ __device__ inline void for_each_key(const uint32_t *p, uint64_t k0, uint64_t k1,
 
 __global__ __launch_bounds__(kSelBlock) void sel_count_kernel(const uint32_t *__restrict__ keys,
                                                               const uint64_t *__restrict__ seg_off,
-                                                              const uint32_t *__restrict__ blk_off, int F, SelArrays A) {
+                                                              const uint32_t *__restrict__ blk_off, int F, SelArrays A,
+                                                              uint64_t work_tuned) {
     extern __shared__ uint32_t cnt[];   // cap words: the counters, as many copies as fit (a lane adds to one of them);
                                         // a discrete feature's keys and marks in front of them
     __shared__ uint32_t seg[kSegs];
@@ -239,7 +326,8 @@ __global__ __launch_bounds__(kSelBlock) void sel_count_kernel(const uint32_t *__
     while (run.next(blk_off, seg_off, &k0, &k1)) {
         const int f = run.f;
         const uint32_t nc = A.n_cells[f];
-        const bool discrete = A.kind[f] & 1u;
+        const bool discrete = A.kind[f] & kKindDiscrete;
+        if (A.cost[f] > work_limit(work_tuned, seg_off, F, f, *A.dear, discrete)) continue;
         uint32_t *rep = cnt, *counters = discrete ? cnt + nc : cnt;   // rep: key of a cell
         uint32_t copies = ((uint32_t)A.cap - (discrete ? nc : 0u)) / nc;
         copies = copies < 1 ? 1 : copies > 8 ? 8 : copies;
@@ -283,11 +371,20 @@ __global__ __launch_bounds__(kSelBlock) void sel_count_kernel(const uint32_t *__
 }
 
 // ---- pick -------------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kSelBlock) void sel_pick_kernel(SelArrays A, int B, uint32_t *__restrict__ present) {
+__global__ __launch_bounds__(kSelBlock) void sel_pick_kernel(const uint64_t *__restrict__ seg_off, SelArrays A, int B,
+                                                             uint32_t *__restrict__ present, uint64_t work_tuned) {
     __shared__ uint32_t seg[kSegs];
     __shared__ uint32_t cell[kSelBinsMax];   // of a slot
     __shared__ uint32_t tmp[kSelBlock / 64];
     const int f = blockIdx.x, tid = threadIdx.x;
+    if (A.cost[f] > work_limit(work_tuned, seg_off, gridDim.x, f, *A.dear, A.kind[f] & kKindDiscrete)) {
+        if (tid == 0) {
+            A.n_slots[f] = 0;
+            A.mode[f] = kSelSorted;
+            A.flag[0] = 1;
+        }
+        return;
+    }
     const uint32_t nc = A.n_cells[f];
     constexpr int PER = kCellsMax / kSelBlock;
     for (int i = tid; i < kSegs; i += kSelBlock) seg[i] = A.seg[(uint64_t)f * kSegs + i];
@@ -303,7 +400,7 @@ __global__ __launch_bounds__(kSelBlock) void sel_pick_kernel(SelArrays A, int B,
     uint32_t m, n_used;
     const uint32_t start0 = block_scan(sum, tmp, &m);
     block_scan(ne, tmp, &n_used);
-    const bool order = n_used > (uint32_t)B, discrete = A.kind[f] & 1u;
+    const bool order = n_used > (uint32_t)B, discrete = A.kind[f] & kKindDiscrete;
     bool collect = !discrete;
     // which cells: those with a wanted rank, or all that hold anything
     uint32_t sel = 0, n_sel = 0, sel_keys = 0, start = start0;
@@ -386,7 +483,7 @@ __global__ __launch_bounds__(kSelBlock) void sel_pick_kernel(SelArrays A, int B,
     }
     collect = __syncthreads_or(collect ? 1 : 0) != 0;
     if (tid == 0) {
-        A.kind[f] = (discrete ? 1u : 0u) | (collect ? 0u : 2u);
+        A.kind[f] = (discrete ? kKindDiscrete : 0u) | (collect ? 0u : kKindNoCollect);
         A.n_slots[f] = n_slots;
         A.mode[f] = order ? kSelOrder : kSelDistinct;
         present[f] = m;
@@ -408,7 +505,7 @@ __global__ __launch_bounds__(kSelBlock) void sel_collect_kernel(const uint32_t *
     while (run.next(blk_off, seg_off, &k0, &k1)) {
         const int f = run.f;
         const uint32_t nc = A.n_cells[f], ns = A.n_slots[f];
-        if (ns == 0 || (A.kind[f] & 2u)) continue;   // every key is missing, or every cell has one key only
+        if (ns == 0 || (A.kind[f] & kKindNoCollect)) continue;   // nothing to look for, or every cell has one key only
         __syncthreads();
         for (int i = threadIdx.x; i < kSegs; i += kSelBlock) seg[i] = A.seg[(uint64_t)f * kSegs + i];
         for (uint32_t i = threadIdx.x; i < nc; i += kSelBlock) slot_of[i] = A.slot_of[(uint64_t)f * A.cap + i];
@@ -469,7 +566,7 @@ static_assert(kCollectPer * kSelBlock <= 65536, "a rank inside a step has 16 bit
 __global__ __launch_bounds__(kSelBlock) void sel_distinct_kernel(const uint64_t *__restrict__ seg_off, int B, SelArrays A,
                                                                  const uint32_t *__restrict__ collected,
                                                                  float *__restrict__ cuts, int32_t *__restrict__ nb,
-                                                                 uint64_t work_max) {
+                                                                 uint64_t work_tuned) {
     extern __shared__ uint32_t dyn[];
     uint32_t *mark = dyn;                               // 2^kMarkBits bits
     uint32_t *ext = dyn + (1 << kMarkBits) / 32;        // B + 1 distinct keys of the slots with collected keys, in order
@@ -491,6 +588,7 @@ __global__ __launch_bounds__(kSelBlock) void sel_distinct_kernel(const uint64_t 
     const uint32_t *cur = A.cursor + (uint64_t)f * B;
     for (uint32_t s = tid; s < ns; s += kSelBlock) dcnt[s] = cur[s] ? 0u : 1u;
     __syncthreads();
+    const uint64_t work_max = work_limit(work_tuned, seg_off, gridDim.x, f, *A.dear, A.kind[f] & kKindDiscrete);
     uint64_t work = 0;
     bool many = false;
     for (uint32_t s = 0; s < ns && !many; ++s) {
@@ -500,10 +598,9 @@ __global__ __launch_bounds__(kSelBlock) void sel_distinct_kernel(const uint64_t 
         const uint32_t *k = collected + seg_off[f] + sl.off;
         const uint32_t span = 1u << sl.shift, win = span < (1u << kMarkBits) ? span : (1u << kMarkBits);
         work += (uint64_t)L * (span / win);
-        if (work > work_max) {   // (cuts and nb are written all the same: kernels behind this one may read them)
-            for (int i = tid; i < B - 1; i += kSelBlock) c[i] = __uint_as_float(0x7f800000u);
+        if (work > work_max) {
             if (tid == 0) {
-                nb[f] = 1;
+                A.mode[f] = kSelSorted;
                 A.flag[0] = 1;
             }
             return;
@@ -648,7 +745,7 @@ template <int BLOCK, int BITS>
 __global__ __launch_bounds__(BLOCK) void sel_order_kernel(const uint64_t *__restrict__ seg_off, int F, int B, SelArrays A,
                                                           const uint32_t *__restrict__ present,
                                                           const uint32_t *__restrict__ collected, int cls,
-                                                          uint64_t work_max) {
+                                                          uint64_t work_tuned) {
     static_assert(2 * BITS >= kSegShift + 1, "two levels reach the last bit");
     extern __shared__ uint32_t dyn[];
     uint32_t *cnt = dyn;                     // 2^BITS
@@ -667,9 +764,7 @@ __global__ __launch_bounds__(BLOCK) void sel_order_kernel(const uint64_t *__rest
         const uint32_t *k = collected + seg_off[f] + sl.off;
         const uint64_t m = present[f];
         uint32_t *pick = A.pick + (uint64_t)f * B;
-        int nb1 = 33 - __builtin_clz(L | 1u);   // counters for twice the keys
-        nb1 = nb1 < kSegShift - BITS ? kSegShift - BITS : nb1 > BITS ? BITS : nb1;
-        nb1 = nb1 > (int)sl.shift ? (int)sl.shift : nb1;
+        const int nb1 = order_bits(L, (int)sl.shift, BITS);
         const int rest = (int)sl.shift - nb1;
         auto count = [&](uint32_t lo, int bits, int drop, uint32_t len) {   // keys in [lo, lo + len) by (key - lo) >> drop
             for (uint32_t i = tid; i < (1u << bits); i += BLOCK) cnt[i] = 0;
@@ -712,6 +807,14 @@ __global__ __launch_bounds__(BLOCK) void sel_order_kernel(const uint64_t *__rest
             }
             __syncthreads();
         };
+        const uint64_t work_max = work_limit(work_tuned, seg_off, F, f, *A.dear, A.kind[f] & kKindDiscrete);
+        if (L > work_max) {   // (the sample did not show this many)
+            if (tid == 0) {
+                A.mode[f] = kSelSorted;
+                A.flag[0] = 1;
+            }
+            continue;
+        }
         if (tid == 0) n_buckets = 0;
         __syncthreads();
         count(sl.key_lo, nb1, rest, 1u << sl.shift);
@@ -719,7 +822,10 @@ __global__ __launch_bounds__(BLOCK) void sel_order_kernel(const uint64_t *__rest
         if (rest > 0) {
             const uint32_t nbk = n_buckets;   // (at most the slot's ranks, so at most B)
             if ((uint64_t)nbk * L > work_max) {
-                if (tid == 0) A.flag[0] = 1;
+                if (tid == 0) {
+                    A.mode[f] = kSelSorted;
+                    A.flag[0] = 1;
+                }
             } else {
                 for (uint32_t b = 0; b < nbk; ++b) {
                     const uint32_t lo = sl.key_lo + (bucket[b] << rest), r0 = bstart[b];
@@ -736,7 +842,7 @@ __global__ __launch_bounds__(BLOCK) void sel_order_kernel(const uint64_t *__rest
 __global__ __launch_bounds__(256) void sel_cuts_kernel(int B, SelArrays A, float *__restrict__ cuts, int32_t *__restrict__ nb) {
     __shared__ uint32_t tmp[4];
     const int f = blockIdx.x, tid = threadIdx.x;
-    if (A.mode[f] != kSelOrder) return;   // written by sel_distinct_kernel
+    if (A.mode[f] != kSelOrder) return;   // written by sel_distinct_kernel, or left to the sort
     const uint32_t *pick = A.pick + (uint64_t)f * B;
     float *c = cuts + (int64_t)f * (B - 1);
     const uint32_t vmin = pick[0];
@@ -760,7 +866,7 @@ __global__ __launch_bounds__(kSelBlock) void sel_bins_kernel(int B, SelArrays A,
                                                              const int32_t *__restrict__ nb) {
     __shared__ uint32_t seg[kSegs];
     __shared__ uint32_t ck[kSelBinsMax];
-    if (A.flag[0]) return;   // some feature was given up: the cuts are not final, and the table is not used
+    if (A.flag[0]) return;   // some feature is to be sorted: its cuts are not there, and the table is not used
     const int f = blockIdx.x;
     const uint32_t nc = A.n_cells[f];
     const int ncut = nb[f] - 1;
@@ -956,6 +1062,8 @@ size_t gbt_select_layout(int F, int64_t n_values, int B, char *base, SelArrays *
     a.work = (uint32_t *)take((size_t)F * B * 12);
     a.n_work = (uint32_t *)take(12);
     a.flag = (uint32_t *)take(4);
+    a.cost = (uint32_t *)take((size_t)F * 4);
+    a.dear = (unsigned long long *)take(8);
     if (A) *A = a;
     return o;
 }
@@ -968,7 +1076,7 @@ hipError_t gbt_launch_select(gbt_ctx *ctx, const uint32_t *keys, uint32_t *colle
     const size_t lds_collect = (size_t)B * 12 + (size_t)A.cap * 2;
     const size_t lds_distinct = (size_t)(1 << kMarkBits) / 8 + (size_t)(3 * B + 1) * 4;
     const size_t lds_big = (size_t)(1 << kBigBits) * 4 + (size_t)B * 8, lds_mid = (size_t)(1 << kMidBits) * 4 + (size_t)B * 8;
-    const uint64_t work_max = ctx->quantise_work > 0 ? (uint64_t)ctx->quantise_work : kSlotWorkMax;
+    const uint64_t work = (uint64_t)ctx->quantise_work, by_sample = ctx->quantise_late ? ~0ull : work;   // 0: by lengths
     GbtLdsGuard guard(lds_distinct);
     hipError_t e = hipSuccess;
     auto raise = [&](const void *fn, size_t lds) {
@@ -981,17 +1089,17 @@ hipError_t gbt_launch_select(gbt_ctx *ctx, const uint32_t *keys, uint32_t *colle
     // two workgroups of 1024 threads per compute unit, and no more than there are tiles to share out
     const int64_t tiles = n_values / kSortTile + F;
     const int grid = (int)(tiles < 2 * ctx->num_cu ? (tiles > 0 ? tiles : 1) : 2 * ctx->num_cu);
-    sel_sample_kernel<<<F, kSelBlock, 0, s>>>(keys, seg_off, A);
-    sel_count_kernel<<<grid, kSelBlock, lds_count, s>>>(keys, seg_off, blk_off, F, A);
-    sel_pick_kernel<<<F, kSelBlock, 0, s>>>(A, B, present);
+    sel_sample_kernel<<<F, kSelBlock, 0, s>>>(keys, seg_off, B, A, by_sample);
+    sel_count_kernel<<<grid, kSelBlock, lds_count, s>>>(keys, seg_off, blk_off, F, A, by_sample);
+    sel_pick_kernel<<<F, kSelBlock, 0, s>>>(seg_off, A, B, present, by_sample);
     sel_collect_kernel<<<grid, kSelBlock, lds_collect, s>>>(keys, seg_off, blk_off, F, B, A, collected);
-    sel_distinct_kernel<<<F, kSelBlock, lds_distinct, s>>>(seg_off, B, A, collected, cuts, nb, work_max);
+    sel_distinct_kernel<<<F, kSelBlock, lds_distinct, s>>>(seg_off, B, A, collected, cuts, nb, work);
     const uint64_t all = (uint64_t)F * B;
     auto at_most = [&](uint64_t n, int per_cu) { return (unsigned)(n < (uint64_t)per_cu * ctx->num_cu ? n : (uint64_t)per_cu * ctx->num_cu); };
     sel_list_kernel<<<(unsigned)((all + kSelBlock - 1) / kSelBlock), kSelBlock, 0, s>>>(F, B, A);
     sel_order_small_kernel<<<at_most((all + 3) / 4, 8), 256, 0, s>>>(seg_off, B, A, present, collected);
-    sel_order_kernel<256, kMidBits><<<at_most(all, 8), 256, lds_mid, s>>>(seg_off, F, B, A, present, collected, 1, work_max);
-    sel_order_kernel<1024, kBigBits><<<at_most(all, 2), 1024, lds_big, s>>>(seg_off, F, B, A, present, collected, 2, work_max);
+    sel_order_kernel<256, kMidBits><<<at_most(all, 8), 256, lds_mid, s>>>(seg_off, F, B, A, present, collected, 1, work);
+    sel_order_kernel<1024, kBigBits><<<at_most(all, 2), 1024, lds_big, s>>>(seg_off, F, B, A, present, collected, 2, work);
     sel_cuts_kernel<<<F, 256, 0, s>>>(B, A, cuts, nb);
     return hipGetLastError();
 }

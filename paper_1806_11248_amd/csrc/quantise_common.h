@@ -64,6 +64,11 @@ inline hipError_t with_bits(int bits, Fn &&fn) {
 
 }  // namespace
 
+enum : uint32_t {
+    kSelOrder = 0,      // more than B distinct values: order statistics
+    kSelDistinct = 1,   // at most B, perhaps
+    kSelSorted = 2      // the feature's values lie too close together for selection: its cuts come from the sort
+};
 // Selection (kernels_select.hip).  Device arrays, all inside the quantise workspace.
 struct SelSlot {
     uint32_t start;    // rank of the cell's smallest key
@@ -86,10 +91,12 @@ struct SelArrays {
     uint32_t *n_slots;   // [F]
     uint32_t *cursor;    // [F][B] keys collected per slot
     uint32_t *pick;      // [F][B] the order statistics floor(k m / B), k = 0..B-1
-    uint32_t *mode;      // [F] kSelOrder / kSelDistinct
+    uint32_t *mode;      // [F] kSelOrder / kSelDistinct / kSelSorted
     uint32_t *work;      // [3][F * B] slots by the number of collected keys ...
     uint32_t *n_work;    // [3] ... and how many
-    uint32_t *flag;      // [1] not zero: some feature's values lie too close together for this form
+    uint32_t *flag;      // [1] not zero: some feature's mode is kSelSorted
+    uint32_t *cost;      // [F] key reads of the workgroup that would spend most on the feature, by its sample
+    unsigned long long *dear;   // [1] keys of the features whose cost is more than sorting them alone
     int cap, sample_cap;
 };
 #endif
