@@ -473,7 +473,7 @@ constexpr uint32_t kHMask = (1u << kHShift) - 1u;
 // `collected` a second buffer of n_values words; cuts, nb and present (values that are not missing) per feature, but for
 // those whose mode is kSelSorted (some is iff *A.flag is not zero): theirs are still to be found
 struct SelArrays;
-bool gbt_select_ok(int B);
+bool gbt_select_ok(int F, int64_t n_values, int B);
 size_t gbt_select_layout(int F, int64_t n_values, int B, char *base, SelArrays *A);   // bytes; base, A may be NULL
 hipError_t gbt_launch_select(gbt_ctx *ctx, const uint32_t *keys, uint32_t *collected, const uint64_t *seg_off,
                              const uint32_t *blk_off, int F, int64_t n_values, int B, const SelArrays &A, float *cuts,

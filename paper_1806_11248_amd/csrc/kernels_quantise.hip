@@ -3,8 +3,8 @@
 //   1. keys: every feature's values become one contiguous segment of uint32 keys in the floats' order (dense input: an
 //      LDS-tiled transpose, a missing value becomes the largest key; CSR input: counted, offset and scattered by
 //      column);
-//   2. order statistics and cuts by selection (kernels_select.hip), for up to 1024 bins.  With more bins, and for the
-//      columns whose values lie too close together for it, by a segmented LSD radix sort (here): four 8-bit passes,
+//   2. order statistics and cuts by selection (kernels_select.hip).  With more than 1024 bins, for many short columns
+//      (gbt_select_ok) and for columns whose values lie too close together, by a segmented LSD radix sort (here): four 8-bit passes,
 //      each a per-tile digit histogram, offsets from the tile histograms and a stable scatter (ranks from wave ballots,
 //      tiles and waves in order), then one wave per feature walks the sorted segment;
 //   3. bin: symbol = number of cuts <= x by bisection over the feature's cuts.
@@ -900,7 +900,8 @@ QLayout q_layout(int64_t n, int F, int64_t n_values, int B) {
     size_t o = 0;
     L.keys_a = o;    o += gbt_align((size_t)n_values * 4 + 4);
     // (behind the selection, a dense matrix's columns of symbols)
-    const size_t cols = n_values == n * (int64_t)F ? gbt_bin_columns_bytes(n, F) : 0;
+    const bool select = gbt_select_ok(F, n_values, B);
+    const size_t cols = select && n_values >= n * (int64_t)F ? gbt_bin_columns_bytes(n, F) : 0;
     L.keys_b = o;    o += gbt_align(cols > (size_t)n_values * 4 + 4 ? cols : (size_t)n_values * 4 + 4);
     L.tile_hist = o; o += gbt_align((size_t)L.max_tiles * 256 * 4);
     L.max_chunks = L.max_tiles / 128 + F + 1;
@@ -913,7 +914,7 @@ QLayout q_layout(int64_t n, int F, int64_t n_values, int B) {
     L.seg_flags = o; o += gbt_align((size_t)F * 4);
     L.present = o;   o += gbt_align((size_t)F * 4);
     L.misc = o;      o += 256;
-    L.select = o;    o += gbt_select_ok(B) ? gbt_select_layout(F, n_values, B, nullptr, nullptr) : 0;
+    L.select = o;    o += select ? gbt_select_layout(F, n_values, B, nullptr, nullptr) : 0;
     L.csr_table = o; o += F > kCsrLdsCols ? 0 : gbt_align((size_t)F * kCsrWorkgroups * 4);
     L.total = o;
     return L;
@@ -986,7 +987,7 @@ hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr,
     uint32_t *present = (uint32_t *)(ws + L.present);
     const bool dense = X != nullptr;
 
-    const bool select = gbt_select_ok(B) && !ctx->quantise_sort;
+    const bool select = gbt_select_ok(F, n_values, B) && !ctx->quantise_sort;
     SelArrays A{};
     if (select) gbt_select_layout(F, n_values, B, ws + L.select, &A);
 

@@ -29,6 +29,8 @@
 #include "gbt_internal.h"
 #include "quantise_common.h"
 
+#include <algorithm>
+
 namespace {
 
 constexpr int kSelBlock = 1024;
@@ -200,7 +202,7 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) voi
     }
     if (tid == 0) n_mixed = sum_other = max_other = max_order = 0;
     __syncthreads();
-    uint32_t *rep = A.rep + (uint64_t)f * A.cap;
+    uint32_t *rep = A.rep + (uint64_t)f * kDiscreteCells;
     if (discrete)
         for (uint32_t c = tid; c < total; c += kSelBlock) rep[c] = kMissingKey;
     // The cells of the sampled keys, which are neighbours in v.  (Cells are aligned: keys of one share their top bits.)
@@ -261,7 +263,7 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) voi
     for (int i = tid; i < kSegs; i += kSelBlock) A.seg[(uint64_t)f * kSegs + i] = per_seg[i];
     for (uint32_t c = tid; c < total; c += kSelBlock) A.counts[(uint64_t)f * A.cap + c] = 0;
     if (discrete)
-        for (uint32_t c = tid; c < total; c += kSelBlock) A.mixed[(uint64_t)f * A.cap + c] = 0;
+        for (uint32_t c = tid; c < total; c += kSelBlock) A.mixed[(uint64_t)f * kDiscreteCells + c] = 0;
     if (f == 0 && tid == 0) {   // (*A.dear is cleared with the offsets: this kernel adds to it)
         A.n_work[0] = A.n_work[1] = A.n_work[2] = 0;
         A.flag[0] = 0;
@@ -335,12 +337,12 @@ __global__ __launch_bounds__(kSelBlock) void sel_count_kernel(const uint32_t *__
         for (int i = threadIdx.x; i < kSegs; i += kSelBlock) seg[i] = A.seg[(uint64_t)f * kSegs + i];
         for (uint32_t i = threadIdx.x; i < nc * copies; i += kSelBlock) counters[i] = 0;
         if (discrete)
-            for (uint32_t i = threadIdx.x; i < nc; i += kSelBlock) rep[i] = A.rep[(uint64_t)f * A.cap + i];
+            for (uint32_t i = threadIdx.x; i < nc; i += kSelBlock) rep[i] = A.rep[(uint64_t)f * kDiscreteCells + i];
         __syncthreads();
         const uint32_t *p = keys + seg_off[f];
         uint32_t *mine = counters + (threadIdx.x % copies) * nc;
         if (discrete) {
-            uint8_t *mixed = A.mixed + (uint64_t)f * A.cap;
+            uint8_t *mixed = A.mixed + (uint64_t)f * kDiscreteCells;
             for_each_key(p, k0, k1, [&](uint32_t k) {
                 if (k == kMissingKey) return;
                 const uint32_t c = cell_of(seg, k);
@@ -363,8 +365,8 @@ __global__ __launch_bounds__(kSelBlock) void sel_count_kernel(const uint32_t *__
             if (!sum) continue;
             atomicAdd(&A.counts[(uint64_t)f * A.cap + c], sum);
             if (discrete) {   // the workgroups' keys of a cell have to agree
-                const uint32_t r = atomicCAS(&A.rep[(uint64_t)f * A.cap + c], kMissingKey, rep[c]);
-                if (r != kMissingKey && r != rep[c]) A.mixed[(uint64_t)f * A.cap + c] = 1;
+                const uint32_t r = atomicCAS(&A.rep[(uint64_t)f * kDiscreteCells + c], kMissingKey, rep[c]);
+                if (r != kMissingKey && r != rep[c]) A.mixed[(uint64_t)f * kDiscreteCells + c] = 1;
             }
         }
     }
@@ -458,8 +460,8 @@ __global__ __launch_bounds__(kSelBlock) void sel_pick_kernel(const uint64_t *__r
         const uint32_t shift = seg[lo] >> 24, key_lo = ((uint32_t)lo << kSegShift) + ((ci - (seg[lo] & 0xffffffu)) << shift);
         uint32_t heavy = kMissingKey;
         if (discrete) {
-            heavy = A.rep[(uint64_t)f * A.cap + ci];
-            collect = collect || A.mixed[(uint64_t)f * A.cap + ci];
+            heavy = A.rep[(uint64_t)f * kDiscreteCells + ci];
+            collect = collect || A.mixed[(uint64_t)f * kDiscreteCells + ci];
         } else {
             // the middle one of the sample's keys in the cell: the frequent key, if there is one
             const uint32_t last = key_lo + ((1u << shift) - 1u);
@@ -1031,9 +1033,33 @@ int sample_cap(int F, int64_t n_values) {
 
 }  // namespace
 
-// Up to this many bins: a wanted rank per cell is rare then (1024 of some 6000 cells that hold anything); with more the
-// sort is the shorter way.
-bool gbt_select_ok(int B) { return B <= kSelBinsMax; }
+// Where selection is the shorter way.  Up to 1024 bins: a wanted rank per cell is rare then (1024 of some 6000 cells that
+// hold anything).  A column costs it some 0.3 us besides its values (cells, counters and slots, however few they are) and
+// about a hundred KB of workspace, the sort some 0.1 us and 2 KB; but a few columns spend their time on launches, of which
+// the sort has twice as many.  Dense matrices of normal values, the whole call in us by selection and by sort:
+//   rows x columns        16 bins        64           256          1024
+//     1000 x  256      173   197     183   234     206   333     617   617
+//     1000 x 1000      341   232      -     -      458   398    1940   688
+//     4000 x  700      358   267     377   328     452   466     731   949
+//     5000 x 1900       -     -      790   749     990  1101      -     -
+//     8000 x 1000      475   428     504   593     609   870    1043  1739
+//     8000 x 4000     1583  1123    2169  1708    2925  2500    6850  6650
+//    12000 x 3500     1461  1391    1582  2138    1995  3022    7252  7476
+//    16000 x 1000      507   611     547   896     674  1249    1181  2228
+//    16000 x 10000    4770  5185    7465  7941   15095 15562   31594 31913
+// (with more than 3640 columns, 1920 of more than 255 bins, the symbols are bisected either way).  And the workspace: beyond
+// 8 GB the selection's arrays may take a sixteenth of what the keys take.
+bool gbt_select_ok(int F, int64_t n_values, int B) {
+    if (B > kSelBinsMax) return false;
+    // (the most a column can take, so that a larger matrix of as many columns never needs less)
+    const int64_t column = (int64_t)(kSampleMax + kSegs + kCellsMax + kDiscreteCells) * 4 + kDiscreteCells + kCellsMax * 2 +
+                           (int64_t)B * (int64_t)(sizeof(SelSlot) + 20);
+    if (F * column > std::max((int64_t)8 << 30, n_values / 2)) return false;
+    const int64_t len = n_values / F;   // of a column, on average
+    if (len >= 14000) return true;
+    if (len >= 3584 + (1 << 17) / B) return F <= 3640;   // (the widest matrix of 8-bit symbols that is packed from columns)
+    return F <= 256 + (len > B ? 2 * std::min(B, 512) : 0);
+}
 
 size_t gbt_select_layout(int F, int64_t n_values, int B, char *base, SelArrays *A) {
     const int cap = cells_cap(F, n_values), sc = sample_cap(F, n_values);
@@ -1050,8 +1076,8 @@ size_t gbt_select_layout(int F, int64_t n_values, int B, char *base, SelArrays *
     a.seg = (uint32_t *)take((size_t)F * kSegs * 4);
     a.n_cells = (uint32_t *)take((size_t)F * 4);
     a.counts = (uint32_t *)take((size_t)F * cap * 4);
-    a.rep = (uint32_t *)take((size_t)F * cap * 4);
-    a.mixed = (uint8_t *)take((size_t)F * cap);
+    a.rep = (uint32_t *)take((size_t)F * kDiscreteCells * 4);
+    a.mixed = (uint8_t *)take((size_t)F * kDiscreteCells);
     a.kind = (uint32_t *)take((size_t)F * 4);
     a.slot_of = (uint16_t *)take((size_t)F * cap * 2);
     a.slots = (SelSlot *)take((size_t)F * B * sizeof(SelSlot));

@@ -83,8 +83,8 @@ struct SelArrays {
     uint32_t *seg;       // [F][2048] first cell of a key's top 11 bits | (shift << 24)
     uint32_t *n_cells;   // [F]
     uint32_t *counts;    // [F][cap] keys per cell
-    uint32_t *rep;       // [F][cap] a discrete feature's cells: a key of the cell (kMissingKey: none seen yet) ...
-    uint8_t *mixed;      // [F][cap] ... and whether the cell holds another one as well
+    uint32_t *rep;       // [F][kDiscreteCells] a discrete feature's cells: a key of the cell (kMissingKey: none seen yet) ...
+    uint8_t *mixed;      // [F][kDiscreteCells] ... and whether the cell holds another one as well
     uint32_t *kind;      // [F] bit 0: discrete (few distinct keys in the sample), bit 1: nothing of it has to be collected
     uint16_t *slot_of;   // [F][cap] the slot of a cell that is looked into, 0xffff: none
     SelSlot *slots;      // [F][B]

@@ -78,3 +78,21 @@ def test_every_environment_switch_is_documented_in_the_header():
     header = open(os.path.join(root, "include", "gbt.h")).read()
     missing = sorted(v for v in read if not re.search(r"\b%s\b\s+\[" % v, header))
     assert not missing, f"undocumented environment switches: {missing}"
+
+
+def test_quantise_workspace_of_many_short_columns(lib):
+    """Columns of few values need the two key buffers and the sort's tables (some 2.3 KB a column), not the tables of the
+    selection (some 100 KB a column); and more values never need less."""
+    ws = lib.gbt_quantise_workspace_bytes
+    for n, F in ((16, 1 << 20), (40, 100_000), (300, 30_000), (2_000, 10_000), (8_191, 300_000)):
+        assert 8 * n * F <= ws(n, F, n * F, 256) <= 9 * n * F + 4096 * F, (n, F)
+        assert ws(n, F, n * F // 10, 256) <= 9 * (n * F // 10) + 4096 * F, (n, F)     # the same in CSR, a tenth present
+    # where selection applies to a large matrix its tables stay below a sixteenth of the keys, or 8 GB
+    for n, F in ((20_000, 1 << 20), (100_000, 200_000), (500_000, 2_000), (115_000_000, 13)):
+        assert ws(n, F, n * F, 256) <= 8.3 * n * F + max(n * F // 2, 8 << 30) + 4096 * F + (64 << 20), (n, F)
+    for F, B in ((1, 2), (256, 16), (289, 16), (2_048, 256), (60_000, 1_024), (1 << 20, 256)):
+        last = 0
+        for per_column in (0, 1, 15, 255, 1_025, 8_191, 8_192, 16_383, 16_384, 32_767, 32_768, 65_536, 200_000, 400_000):
+            now = ws(1 << 19, F, per_column * F, B)
+            assert now >= last, (F, B, per_column)
+            last = now

@@ -233,3 +233,30 @@ def test_many_cuts_in_one_cell(ctxs, oracle):
     o_cuts, o_nb = oracle.cuts(X[:, :3], 256)
     assert np.array_equal(a[0][:3].cpu().numpy(), o_cuts) and np.array_equal(a[1][:3].cpu().numpy(), o_nb)
     assert t_sel < 1.15 * t_sort, (t_sel, t_sort)
+
+
+@pytest.mark.parametrize("n,F,B", [(300, 288, 16), (300, 289, 16), (1_000, 256, 1024), (1_000, 257, 1024), (4_095, 769, 256),
+                                   (4_096, 769, 256), (5_632, 3_640, 64), (5_632, 3_641, 64), (13_999, 3_641, 255),
+                                   (14_000, 3_641, 255), (2_000, 10_000, 64)])
+def test_many_short_columns(ctxs, n, F, B):
+    """Both sides of where selection takes over from the sort, by columns, their length and bins."""
+    gen = torch.Generator(device="cuda").manual_seed(n + F)
+    X = torch.randn((n, F), device="cuda", generator=gen)
+    X[:, ::3] = (4 * X[:, ::3]).round()
+    X[torch.rand((n, F), device="cuda", generator=gen) < 0.02] = float("nan")
+    print(f"short columns n={n} F={F} B={B}", flush=True)
+    assert _same(*(ctx.quantise_packed(X, max_bins=B) for ctx in ctxs))
+
+
+@pytest.mark.parametrize("n,F", [(50, 20_000), (2_000, 300)])
+def test_many_short_csr_columns(ctxs, oracle, n, F):
+    rng = np.random.default_rng(n + F)
+    X = np.where(rng.random((n, F)) < 0.1, np.round(4 * rng.standard_normal((n, F))), np.nan).astype(np.float32)
+    ok = ~np.isnan(X)
+    csr = tuple(dev(a) for a in (np.concatenate([[0], np.cumsum(ok.sum(1))]).astype(np.int64), np.nonzero(ok)[1].astype(np.int32), X[ok]))
+    print(f"short csr columns n={n} F={F}", flush=True)
+    cuts, nb, sym, mv, ms = ctxs[0].quantise(csr=csr, max_bins=64, n=n, F=F)
+    o_cuts, o_nb = oracle.cuts(X, 64)
+    o_sym, o_missing, o_mx = oracle.bin_matrix(X, o_cuts, o_nb)
+    assert np.array_equal(nb.cpu().numpy(), o_nb) and np.array_equal(cuts.cpu().numpy(), o_cuts)
+    assert (mv, ms) == (o_mx, o_missing) and np.array_equal(sym.cpu().numpy(), o_sym)
