@@ -1967,6 +1967,23 @@ BatchLayout batch_layout(size_t base, int64_t total_nodes, int32_t n_trees) {
     L.total = o;
     return L;
 }
+// Many trees on wide rows: one pass that stages whole rows (the many-trees kernel, `lds` bytes a workgroup, `steps` = depth + 1
+// over all trees), or a kernel per tree that gathers the few values a walk asks for.  Up to 95 features the one pass is never
+// the longer way.  Beyond, few waves of it fit a compute unit and every one reads all F values of its rows: in us, per round
+// of resident rows, some 0.1 F for the rows and 0.09 per step (0.35 where a group holds a single tree); a kernel per tree
+// takes its launch and 3 to 12 per step, up to 1M rows by its latency and beyond by its gathers.  1M rows x 300, in us by
+// one pass and by tree: 2 trees of depth 3 1633 and 99, 60 of them 2361 and 2575; 10,000 rows x 300: 46 and 59, 119 and 1158;
+// 1M x 129: 2 trees 371 and 87, 16 trees 442 and 626.  The constants are a fit to 1600 such pairs (96 to 500 features, 200 to
+// 3M rows, 2 to 60 trees of depth 3 to 9): what the rule takes is at most 1.24 times the better one, 1.003 on average.
+bool batch_pays(const gbt_ctx *ctx, int64_t n, int F, int n_trees, int64_t steps, size_t lds, bool one_tree_groups) {
+    if (F < 96) return true;
+    const int rows = gbt_predict_batch_rows(F);
+    const int waves = std::max(1, std::min(32, (int)(ctx->lds_max / lds) * (rows / 64)));   // of a compute unit
+    const double rounds = std::ceil((double)n / ((double)ctx->num_cu * waves * 64.0)), m = (double)n * 1e-6;
+    const double one_pass = rounds * ((0.1 + 0.012 * waves) * F + (one_tree_groups ? 0.35 : 0.09) * (double)steps);
+    const double step = std::max(5.0 * std::min(1.0, (double)n / 5e3) + 3.0 * std::min(1.0, (double)n / 1e5) + 4.5 * m, 11.0 * m);
+    return one_pass < 2.0 * n_trees + step * (double)steps;
+}
 // A threshold in the order of the many-trees kernel's integer values (gbt_batch_node): value + a >= thr sends a row right.
 int32_t batch_threshold(float thr, uint32_t a) {
     if (thr != thr) return INT32_MIN + (int32_t)a;   // no value lies below: every one goes right, a missing one by default
@@ -2046,7 +2063,10 @@ static int32_t predict_impl(gbt_ctx *ctx, const gbt_tree *trees, int32_t n_trees
         // 100 trees; 700 nodes 0.33, 1024 0.28, 2560 0.28)
         const size_t tile = gbt_predict_batch_tile_bytes(F);
         const int cap_nodes = std::max(tile + (size_t)1536 * 8 <= ctx->lds_per_block ? 1536 : 1, max_nodes);
-        if (tile + (size_t)cap_nodes * 8 <= ctx->lds_per_block) {
+        const size_t lds = tile + (size_t)cap_nodes * 8;
+        int64_t steps = n_trees;
+        for (int t = 0; t < n_trees; ++t) steps += depths[(size_t)t];
+        if (lds <= ctx->lds_per_block && batch_pays(ctx, n, F, n_trees, steps, lds, cap_nodes < 2 * max_nodes)) {
             const int64_t total_nodes = total_nodes_of(trees, n_trees);
             const BatchLayout BL = batch_layout(0, total_nodes, n_trees);
             // built where the copy reads it: the pinned staging if it fits there

@@ -442,6 +442,7 @@ struct gbt_batch_node {
     int32_t thr;
     uint32_t meta;
 };
+int gbt_predict_batch_rows(int F);
 size_t gbt_predict_batch_tile_bytes(int F);
 hipError_t gbt_launch_predict_raw_batched(hipStream_t s, const gbt_batch_node *nodes, const double *wts,
                                           const int32_t *tree_off, const int32_t *tree_depth,

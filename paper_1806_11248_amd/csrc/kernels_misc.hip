@@ -992,6 +992,7 @@ hipError_t launch_batched(hipStream_t s, const gbt_batch_node *nodes, const doub
 }
 }  // namespace
 
+int gbt_predict_batch_rows(int F) { return batch_rows(F); }
 size_t gbt_predict_batch_tile_bytes(int F) { return (size_t)batch_rows(F) * F * 4; }
 
 hipError_t gbt_launch_predict_raw_batched(hipStream_t s, const gbt_batch_node *nodes, const double *wts,

@@ -101,3 +101,44 @@ def test_row_tiles_of_every_width(ctx, oracle, n, F):
         ref = oracle.predict_raw(t, Z, 0.3, ref)
     got = ctx.predict(trees, dev(start), 0.3, X=dev(Z)).cpu().numpy()
     assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("n,F,rounds", [(30_001, 300, 2), (30_001, 300, 12), (5_000, 300, 2), (9_000, 500, 3), (300, 129, 9)])
+def test_few_trees_on_wide_rows(ctx, oracle, n, F, rounds):
+    """Wide rows take one pass over the rows or a kernel per tree, by rows, columns and trees: the same margins."""
+    rng = np.random.default_rng(n + F + rounds)
+    X = rng.standard_normal((3_000, F)).astype(np.float32)
+    y = (X[:, 0] + X[:, -1] * X[:, F // 2] > 0).astype(np.float32)
+    print(f"wide rows n={n} F={F} trees={rounds}", flush=True)
+    trees, _ = _boost(ctx, X, y, 32, rounds, 4)
+    Z = rng.standard_normal((n, F)).astype(np.float32)
+    Z[rng.random(Z.shape) < 0.05] = np.nan
+    start = rng.standard_normal(n).astype(np.float32)
+    ref = start.copy()
+    for t in trees:
+        ref = oracle.predict_raw(t, Z, 0.3, ref)
+    assert np.array_equal(ctx.predict(trees, dev(start), 0.3, X=dev(Z)).cpu().numpy(), ref)
+
+
+def test_few_trees_on_wide_rows_cost_no_more_than_one_by_one(ctx):
+    """Two shallow trees on 1M x 300: a pass that stages whole rows took 12 times what the two walks take."""
+    import time
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    X = torch.randn((1_000_000, 300), device="cuda", generator=gen)
+    head = X[:3_000].cpu().numpy()
+    trees, _ = _boost(ctx, head, (head[:, 0] + head[:, 299] * head[:, 150] > 0).astype(np.float32), 32, 2, 3)
+    margin = torch.zeros(1_000_000, device="cuda")
+
+    def fastest(groups):
+        best = 1e9
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            for g in groups:
+                ctx.predict(g, margin, 0.3, X=X)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t)
+        return best
+    print("wide rows, two trees", flush=True)
+    together, single = fastest([trees]), fastest([[t] for t in trees])
+    assert together < 2 * single, (together, single)
