@@ -766,7 +766,7 @@ __global__ __launch_bounds__(kCsrPackBlock) __attribute__((amdgpu_waves_per_eu(8
     float *tops = (float *)(dyn + ((size_t)tile_rows * F) / 2);   // F x n_top, padded with +inf
     const int n_top = 2 * step0 - 1;
     int32_t *lcut = (int32_t *)(tops + (size_t)F * n_top);   // F: cuts of a feature
-    int32_t *lptr = lcut + F;                                // tile_rows + 1 row pointers, relative to the tile's first
+    uint32_t *lptr = (uint32_t *)(lcut + F);                 // tile_rows + 1 row pointers, relative to the tile's first
     for (int i = threadIdx.x; i < F * n_top; i += kCsrPackBlock) {
         const int f = i / n_top, at = ((i - f * n_top + 1) << cut_log) - 1;
         tops[i] = at < B - 1 ? cuts[(int64_t)f * (B - 1) + at] : __uint_as_float(0x7f800000u);
@@ -775,6 +775,9 @@ __global__ __launch_bounds__(kCsrPackBlock) __attribute__((amdgpu_waves_per_eu(8
     const int64_t n_tiles = (n + tile_rows - 1) / tile_rows;
     const int lanes = 1 << log_lanes, sub = threadIdx.x & (lanes - 1), groups = kCsrPackBlock >> log_lanes;
     const uint32_t two = missing | (missing << 16);
+    // Entries of a tile (rows may repeat a column).  A lane whose row has ended moves on with the others of its turn: twice
+    // this and a lane count more has to fit 32 bits.
+    constexpr uint32_t kMost = (1u << 31) - 128u;
     for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
         const int64_t r0 = t * tile_rows;
         const int rows = n - r0 < tile_rows ? (int)(n - r0) : tile_rows;
@@ -785,7 +788,7 @@ __global__ __launch_bounds__(kCsrPackBlock) __attribute__((amdgpu_waves_per_eu(8
         for (int i = threadIdx.x; i <= rows; i += kCsrPackBlock) {
             int64_t p = indptr[r0 + i];
             p = p < a0 ? a0 : p > nnz ? nnz : p;
-            lptr[i] = p - a0 < INT32_MAX ? (int)(p - a0) : INT32_MAX;
+            lptr[i] = p - a0 < (int64_t)kMost ? (uint32_t)(p - a0) : kMost;
         }
         __syncthreads();
         const int32_t *ip = indices + a0;
@@ -793,7 +796,7 @@ __global__ __launch_bounds__(kCsrPackBlock) __attribute__((amdgpu_waves_per_eu(8
         // rows side by side: their loads and searches overlap
         constexpr int U = 4;
         for (int rb = threadIdx.x >> log_lanes; rb < rows; rb += U * groups) {
-            int at[U], end[U];
+            uint32_t at[U], end[U];
             bool more = false;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
