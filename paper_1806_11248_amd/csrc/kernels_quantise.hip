@@ -753,10 +753,15 @@ __global__ __launch_bounds__(256) void bin_pack_dense_kernel(const float *__rest
 // as a row has entries), so no lane has to search for the row of its entry and a wave's loads are one piece of the CSR
 // arrays.  The cuts are searched in two levels: every 2^cut_log-th one in LDS (all of them where they fit: 51 KB for
 // 50 x 255), then the few between two of those.
+// UNEVEN (rows can have more entries than four turns of their lanes): a tile with such a row gives every row more lanes, up to
+// what takes all rows in one turn; otherwise its longest row holds up the whole workgroup.  5M x 50, one row in a hundred full,
+// the others with one entry: the call 1.87 ms without this, 0.84 with it.  The look costs 0.3 us a tile, so where no row can be
+// that long it is left out.
 // 10M x 50 rows of 10 entries: 0.84 ms; 1.99 ms with a bisection for the row, one through global memory for the cut and
 // a word of the stream at a time.  Instruction issue is what remains (90 MB of words written, 0.9 GB read).
 constexpr int kCsrPackBlock = 1024;
-template <int BITS>
+constexpr int kCsrPackRows = 4;   // rows side by side: their loads and searches overlap
+template <int BITS, bool UNEVEN>
 __global__ __launch_bounds__(kCsrPackBlock) __attribute__((amdgpu_waves_per_eu(8))) void bin_pack_csr_kernel(
     const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices, const float *__restrict__ values, int64_t n,
     int64_t nnz, int F, int B, const float *__restrict__ cuts, const int32_t *__restrict__ nb, uint32_t missing, int tile_rows,
@@ -773,7 +778,11 @@ __global__ __launch_bounds__(kCsrPackBlock) __attribute__((amdgpu_waves_per_eu(8
     }
     for (int i = threadIdx.x; i < F; i += kCsrPackBlock) lcut[i] = nb[i] - 1;
     const int64_t n_tiles = (n + tile_rows - 1) / tile_rows;
-    const int lanes = 1 << log_lanes, sub = threadIdx.x & (lanes - 1), groups = kCsrPackBlock >> log_lanes;
+    __shared__ uint32_t longest;   // row of the tile, if it takes more than four turns
+    if (UNEVEN) {
+        if (threadIdx.x == 0) longest = 0;
+        __syncthreads();
+    }
     const uint32_t two = missing | (missing << 16);
     // Entries of a tile (rows may repeat a column).  A lane whose row has ended moves on with the others of its turn: twice
     // this and a lane count more has to fit 32 bits.
@@ -789,13 +798,22 @@ __global__ __launch_bounds__(kCsrPackBlock) __attribute__((amdgpu_waves_per_eu(8
             int64_t p = indptr[r0 + i];
             p = p < a0 ? a0 : p > nnz ? nnz : p;
             lptr[i] = p - a0 < (int64_t)kMost ? (uint32_t)(p - a0) : kMost;
+            if (UNEVEN && i < rows) {
+                const int64_t len = indptr[r0 + i + 1] - p;
+                if (len > (4 << log_lanes)) atomicMax(&longest, len < (int64_t)kMost ? (uint32_t)len : kMost);
+            }
         }
         __syncthreads();
+        int ll = log_lanes;   // (in scalar registers, as what follows from it)
+        if (UNEVEN) {
+            const uint32_t most = (uint32_t)__builtin_amdgcn_readfirstlane((int)longest);
+            while (ll < 6 && most > (4u << ll) && (rows << (ll + 1)) <= kCsrPackRows * kCsrPackBlock) ++ll;
+        }
+        const int lanes = 1 << ll, sub = threadIdx.x & (lanes - 1), groups = kCsrPackBlock >> ll;
         const int32_t *ip = indices + a0;
         const float *vp = values + a0;
-        // rows side by side: their loads and searches overlap
-        constexpr int U = 4;
-        for (int rb = threadIdx.x >> log_lanes; rb < rows; rb += U * groups) {
+        constexpr int U = kCsrPackRows;
+        for (int rb = threadIdx.x >> ll; rb < rows; rb += U * groups) {
             uint32_t at[U], end[U];
             bool more = false;
 #pragma unroll
@@ -846,6 +864,7 @@ __global__ __launch_bounds__(kCsrPackBlock) __attribute__((amdgpu_waves_per_eu(8
             }
         }
         __syncthreads();
+        if (UNEVEN && threadIdx.x == 0) longest = 0;
         uint32_t *out = packed + ((r0 * F) >> 5) * BITS;   // r0 * F is a multiple of 32
         const int nw = (int)(((int64_t)elems * BITS + 31) >> 5);
         for (int g = threadIdx.x; g < (elems + 31) >> 5; g += kCsrPackBlock) {
@@ -1145,13 +1164,13 @@ hipError_t gbt_quantise_run(gbt_ctx *ctx, const float *X, const int64_t *indptr,
             const size_t lds = (size_t)tile_rows * F * 2 + (size_t)F * (2 * step0 - 1) * 4 + (size_t)F * 4 + ((size_t)tile_rows + 1) * 4;
             Q_HIP(with_bits(bits, [&](auto bc) {
                 constexpr int BITS = decltype(bc)::value;
+                const auto fn = F > (4 << log_lanes) ? bin_pack_csr_kernel<BITS, true> : bin_pack_csr_kernel<BITS, false>;
                 GbtLdsGuard lds_guard(lds);
                 if (lds_guard.needed) {
-                    hipError_t e = hipFuncSetAttribute((const void *)bin_pack_csr_kernel<BITS>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                    hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
                     if (e != hipSuccess) return e;
                 }
-                bin_pack_csr_kernel<BITS><<<grid_for(n, tile_rows, 2 * ctx->num_cu), kCsrPackBlock, lds, s>>>(
+                fn<<<grid_for(n, tile_rows, 2 * ctx->num_cu), kCsrPackBlock, lds, s>>>(
                     indptr, indices, values, n, n_values, F, B, cuts, nb, (uint32_t)miss, tile_rows, log_lanes, cut_log, step0,
                     packed, n_words);
                 return hipGetLastError();
