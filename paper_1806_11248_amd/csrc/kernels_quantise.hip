@@ -4,10 +4,12 @@
 //      LDS-tiled transpose, a missing value becomes the largest key; CSR input: counted, offset and scattered by
 //      column);
 //   2. order statistics and cuts by selection (kernels_select.hip).  With more than 1024 bins, for many short columns
-//      (gbt_select_ok) and for columns whose values lie too close together, by a segmented LSD radix sort (here): four 8-bit passes,
-//      each a per-tile digit histogram, offsets from the tile histograms and a stable scatter (ranks from wave ballots,
-//      tiles and waves in order), then one wave per feature walks the sorted segment;
-//   3. bin: symbol = number of cuts <= x by bisection over the feature's cuts.
+//      (gbt_select_ok) and for columns whose values lie too close together, by a segmented LSD radix sort (here): four
+//      8-bit passes, each a per-tile digit histogram, offsets from the tile histograms and a stable scatter (ranks from
+//      wave ballots, tiles and waves in order), then one wave per feature walks the sorted segment;
+//   3. bin: symbol = number of cuts <= x.  Packed and dense, all columns by selection: column by column with the selection's
+//      cells, then packed from the columns (kernels_select.hip).  Otherwise from the values: by bisection over the feature's
+//      cuts, or for packed CSR rows in two levels with the upper one in LDS.
 #include "gbt_internal.h"
 #include "quantise_common.h"
 
