@@ -973,7 +973,10 @@ __global__ __launch_bounds__(R) void predict_raw_batched_kernel(
     if (live) margin[r0 + threadIdx.x] = m;
 }
 
-// Rows of a tile: 256 while two workgroups of a compute unit find room for it beside their nodes, then fewer.
+// Rows of a tile: 256 while two workgroups of a compute unit find room for it beside their nodes, then fewer.  1M rows and 100
+// trees of depth 6, the call in us with 64, 128 and 256 rows: 28 columns 612, 472, 403; 64 columns 848, 688, 570; 95 columns
+// 1092, 1011, 958; 128 columns 1434, 1148, does not fit; 200 columns 2214, 1975, does not fit (the lines at 64 and 128 columns
+// are not the best ones: at 65 columns 128 rows take 730 and 256 take 588).
 inline int batch_rows(int F) { return F <= 64 ? 256 : F <= 128 ? 128 : 64; }
 
 template <int R>
