@@ -123,6 +123,7 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) voi
     const uint32_t *__restrict__ keys, const uint64_t *__restrict__ seg_off, int B, SelArrays A, uint64_t work_tuned) {
     __shared__ uint32_t v[kSampleMax];
     __shared__ uint32_t per_seg[kSegs];   // sampled keys of an interval, then its first cell and shift
+    __shared__ uint64_t heads[kSampleMax / 64];   // bits: a cell's first sampled key
     __shared__ uint32_t tmp[kSelBlock / 64];
     __shared__ uint32_t n_mixed, sum_other;     // cells of several values, and their sampled keys besides the frequent one
     __shared__ uint32_t max_other, max_order;   // the dearest cell: such keys, and key reads of sel_order_kernel
@@ -207,29 +208,37 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) voi
     if (discrete)
         for (uint32_t c = tid; c < total; c += kSelBlock) rep[c] = kMissingKey;
     // The cells of the sampled keys, which are neighbours in v.  (Cells are aligned: keys of one share their top bits.)
-    auto first_of_cell = [&](int j, uint32_t *shift) {
-        *shift = per_seg[v[j] >> kSegShift] >> 24;
-        return v[j] != kMissingKey && (j == 0 || v[j - 1] >> *shift != v[j] >> *shift);
-    };
-    uint32_t shift, heads = 0, used;
-    for (int j = tid; j < P; j += kSelBlock) heads += first_of_cell(j, &shift) ? 1u : 0u;
-    block_scan(heads, tmp, &used);   // (with barriers: `rep` is clear)
+    for (int j = tid; j < P; j += kSelBlock) {   // (P is a multiple of 64: a wave takes a whole word)
+        const uint32_t k = v[j], shift = per_seg[k >> kSegShift] >> 24;
+        const uint64_t m = __ballot(k != kMissingKey && (j == 0 || v[j - 1] >> shift != k >> shift));
+        if ((tid & 63) == 0) heads[j >> 6] = m;
+    }
+    __syncthreads();   // (and `rep` is clear)
+    uint32_t used = (tid & 63) < P / 64 ? (uint32_t)__popcll(heads[tid & 63]) : 0u;   // every wave adds them up
+    for (int o = 32; o > 0; o >>= 1) used += (uint32_t)__shfl_xor((int)used, o);
     // What the feature would cost.  In no more cells than bins the distinct values are counted by one workgroup; otherwise a
     // workgroup takes a cell, and only one with a share of the feature that shows in S / 128 sampled keys can be dear.
     const int least_keys = used > (uint32_t)B ? S / 128 : 2;
     const float per_key = (float)len / (float)(S > 0 ? S : 1), per_rank = (float)B / (float)(present > 0 ? present : 1);
     for (int j = tid; j < P; j += kSelBlock) {
-        if (!first_of_cell(j, &shift)) continue;
-        const uint32_t k = v[j], same = k >> shift;
+        if (!((heads[j >> 6] >> (j & 63)) & 1u)) continue;
+        const uint32_t k = v[j], shift = per_seg[k >> kSegShift] >> 24, same = k >> shift;
         uint32_t mid = k;
         const int quick = j + (least_keys > 2 ? least_keys : 2) - 1;
         if (quick < P && v[quick] >> shift == same) {
-            const int end = sample_bound(v, quick + 1, P, [&](uint32_t x) { return x >> shift == same; });
-            mid = v[(j + end) >> 1];   // the frequent key, if there is one: not collected
-            const int m0 = sample_bound(v, j, end, [&](uint32_t x) { return x < mid; });
-            const int m1 = sample_bound(v, m0, end, [&](uint32_t x) { return x <= mid; });
-            const uint32_t other = (uint32_t)(end - j - (m1 - m0));
-            if (other) {
+            int w = j >> 6, end = (int)present;   // the next cell's first key, in this word or one of the next three, or bisected
+            uint64_t m = heads[w] & (~1ull << (j & 63));
+            for (int i = 0; i < 3 && !m && w + 1 < P / 64; ++i) m = heads[++w];
+            if (m) {
+                end = 64 * w + (int)__builtin_ctzll(m);
+            } else if (64 * (w + 1) < (int)present) {
+                end = sample_bound(v, 64 * (w + 1), (int)present, [&](uint32_t x) { return x >> shift == same; });
+            }
+            if (v[end - 1] != k) {
+                mid = v[(j + end) >> 1];   // the frequent key, if there is one: not collected
+                const int m0 = sample_bound(v, j, end, [&](uint32_t x) { return x < mid; });
+                const int m1 = sample_bound(v, m0, end, [&](uint32_t x) { return x <= mid; });
+                const uint32_t other = (uint32_t)(end - j - (m1 - m0));
                 const uint32_t reads = shift > (uint32_t)kMarkBits ? other << (shift - kMarkBits) : other;
                 atomicAdd(&n_mixed, 1u);
                 atomicAdd(&sum_other, reads);
