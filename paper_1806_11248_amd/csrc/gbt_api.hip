@@ -116,6 +116,7 @@ void add_hist_jobs(std::vector<HistJob> &jobs, uint64_t hist_off, uint32_t begin
 // bin, and the chip retires only ~1e11 of those per second, some forty times fewer than LDS atomics: a row piece
 // is therefore long enough that a bin receives hist_merge_ratio LDS additions on average per value merged
 // (rows >= ratio * 2 * B), unless that would leave fewer than about one workgroup per compute unit.
+constexpr int64_t kMinRowsPerJob = 4096;
 uint32_t pick_rows_per_job(const gbt_ctx *ctx, int64_t total_rows, int64_t max_rows = 1 << 21, int n_tiles = 1,
                            int B = 0) {
     int64_t pieces = std::max<int64_t>(1, (int64_t)ctx->num_cu * ctx->hist_jobs_per_cu / std::max(1, n_tiles));
@@ -125,7 +126,7 @@ uint32_t pick_rows_per_job(const gbt_ctx *ctx, int64_t total_rows, int64_t max_r
         pieces = std::min(pieces, std::max<int64_t>(1, by_merge));
     }
     int64_t rpj = (total_rows + pieces - 1) / pieces;
-    if (rpj < 4096) rpj = 4096;
+    if (rpj < kMinRowsPerJob) rpj = kMinRowsPerJob;
     if (rpj > max_rows) rpj = max_rows;
     return (uint32_t)rpj;
 }
@@ -251,6 +252,8 @@ extern "C" int32_t gbt_create(gbt_ctx **ctx_out, int32_t device, void *stream) {
         if (const char *e13 = getenv("GBT_TUNE_SPARSE_TILED")) c->sparse_tiled = atoi(e13) != 0;
         c->lossguide_batch = 16;
         if (const char *e16 = getenv("GBT_TUNE_LOSSGUIDE_BATCH")) { int v = atoi(e16); if (v >= 1 && v <= 64) c->lossguide_batch = v; }
+        c->plan = 1;
+        if (const char *e24 = getenv("GBT_TUNE_PLAN")) c->plan = atoi(e24) != 0;
         c->part_nomove = 2;
         if (const char *e15 = getenv("GBT_TUNE_PART_NOMOVE")) { int v = atoi(e15); if (v >= 0 && v <= 2) c->part_nomove = v; }
         c->part_cycle = 1;
@@ -339,6 +342,12 @@ void gbt_prof_patch(gbt_ctx *ctx, int span, double alg_bytes, double row_feature
     if (!ctx->profiling || span < 0 || span >= (int)ctx->spans->size()) return;
     (*ctx->spans)[(size_t)span].alg_bytes = alg_bytes;
     (*ctx->spans)[(size_t)span].row_features = row_features;
+}
+
+static void prof_patch_bytes(gbt_ctx *ctx, int span, double bytes, double alg_bytes, double row_features) {
+    if (!ctx->profiling || span < 0 || span >= (int)ctx->spans->size()) return;
+    (*ctx->spans)[(size_t)span].bytes = bytes;
+    gbt_prof_patch(ctx, span, alg_bytes, row_features);
 }
 
 void gbt_prof_end(gbt_ctx *ctx) {
@@ -792,8 +801,32 @@ static int32_t hist_uniform(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, 
 // -------------------------------------------------------------------- grow --
 namespace {
 
+// The tables of growth planned on the device (kernels_plan.hip), one block of a workspace.
+struct PlanLayout {
+    size_t levels, nodes, win, pjobs, pinfo, enodes, recs, rank_count, total;
+};
+constexpr int kPlanEvalRecords = 8192;   // gbt_eval_chunks keeps a level's records below this plus one per node
+PlanLayout plan_layout(int64_t cap_nodes, int64_t level_nodes) {
+    PlanLayout P;
+    size_t o = 0;
+    P.levels = o;     o += gbt_align((kMaxDepth + 2) * sizeof(PlanLevel));
+    P.nodes = o;      o += gbt_align((size_t)cap_nodes * sizeof(PlanNode));
+    P.win = o;        o += gbt_align((size_t)level_nodes * 4);
+    P.pjobs = o;      o += gbt_align((size_t)level_nodes * sizeof(PartJob));
+    P.pinfo = o;      o += gbt_align((size_t)level_nodes * sizeof(PlanJob));
+    P.enodes = o;     o += gbt_align((size_t)level_nodes * 2 * sizeof(EvalNode));
+    P.recs = o;       o += gbt_align((size_t)(kPlanEvalRecords + level_nodes) * sizeof(gbt_split));
+    P.rank_count = o; o += gbt_align((size_t)cap_nodes * 4);
+    P.total = o;
+    return P;
+}
+// What the host reads back of a planned growth, in the read-back half of the staging
+constexpr size_t kPlanHintOff = 2048, kPlanNodesOff = 4096;
+constexpr int64_t kPlanNodesMax = (int64_t)((GBT_STAGING_BYTES - kReadbackOff - kPlanNodesOff) / sizeof(PlanNode));
+static_assert((kMaxDepth + 2) * sizeof(PlanLevel) <= kPlanHintOff && kPlanHintOff + (kMaxDepth + 2) * 4 <= kPlanNodesOff, "");
+
 struct GrowLayout {
-    size_t tree_stage, tree_stage_bytes, gq, wsym[2], wgq[2], wid[2], masks, tile_left, n_left, state, pool, eval_nodes, jobs, scratch, order, rank_tbl, node_rows, total;
+    size_t tree_stage, tree_stage_bytes, gq, wsym[2], wgq[2], wid[2], masks, tile_left, n_left, state, pool, eval_nodes, jobs, scratch, order, rank_tbl, node_rows, plan, total;
     int64_t hist_nodes, level_nodes, tiles, w_words;
     int sw;   // 32-bit words per row of the working copies
 };
@@ -838,6 +871,7 @@ GrowLayout grow_layout_nodes(int64_t n, int F, int bits, int B, int64_t hist_nod
     L.rank_tbl = o;   o += gbt_align(cap_nodes * 4);
     // one row counter per node, a 128-byte line each, for the walk that also counts (trees small enough for it)
     L.node_rows = o;  o += gbt_align(std::min<size_t>(cap_nodes, 8192) * kNodeRowsStride * 4);
+    L.plan = o;       o += plan_layout((int64_t)cap_nodes, level_nodes).total;
     L.total = o;
     return L;
 }
@@ -923,6 +957,156 @@ static int32_t predict_impl(gbt_ctx *ctx, const gbt_tree *trees, int32_t n_trees
                             const SparseRowsArg *sparse = nullptr, bool own_span = false, uint32_t *node_rows = nullptr,
                             const float *margin_src = nullptr);
 
+// ---- depth-wise growth planned on the device (kernels_plan.hip) ----------------
+namespace {
+struct PlannedGrowth {
+    PlanView v;
+    PlanHistRule rule;
+    int max_depth, F, B;
+    int64_t n, cap_nodes;
+    // the partition of the last level [1] (whose children are leaves) and of the others [0]: rows of a tile, and where it
+    // leaves the left rows of split k: n_left[k * n_left_stride]
+    uint32_t tile_rows[2];
+    const uint32_t *n_left[2];
+    int n_left_stride[2];
+    bool defer_last;                 // the row counts of the last level's children come from a walk of the tree
+    const int32_t *nb;
+    double min_child_weight;
+};
+// the rule by which pick_rows_per_job cuts a level's rows into jobs
+PlanHistRule plan_hist_rule(const gbt_ctx *ctx, const HistPlan &pl, int F, int B, int64_t max_rows) {
+    PlanHistRule r;
+    r.pieces_max = std::max<int64_t>(1, (int64_t)ctx->num_cu * ctx->hist_jobs_per_cu / std::max(1, pl.n_ftiles));
+    r.merge_div = (int64_t)ctx->hist_merge_ratio * 2 * B;
+    r.cu_per_tile = ((int64_t)ctx->num_cu + pl.n_ftiles - 1) / pl.n_ftiles;
+    r.min_rows = kMinRowsPerJob;
+    r.max_rows = max_rows;
+    r.tiles = (F + pl.ft - 1) / pl.ft;
+    r.ft = pl.ft;
+    r.width = F;
+    r.exclusive_ok = 1;
+    return r;
+}
+// the most jobs `splits` built children of a matrix of n rows can be cut into
+int64_t plan_hist_jobs_max(const PlanHistRule &r, int64_t n, int64_t splits) {
+    const int64_t built = n / 2 + 1;
+    int64_t pieces = r.pieces_max;
+    if (r.merge_div) pieces = std::min(pieces, std::max<int64_t>({1, built / r.merge_div, r.cu_per_tile}));
+    pieces = std::max(pieces, (built + r.max_rows - 1) / r.max_rows);
+    return (pieces + splits) * r.tiles;
+}
+constexpr int kPlanExactDepth = 9;   // from this depth on the host waits for a level's number of splits: see planned_levels
+constexpr int kPlanWalkDepth = 10;   // a tree of at most this depth is walked from LDS at its largest size (41 KB)
+
+// Enqueues the levels.  partition(depth, most splits, most tiles, last level): the launches that partition depth's splits;
+// hist(depth, most jobs): builds the histograms of the children made at `depth`.  On return *levels says how many levels
+// have been enqueued (the depths of the nodes that exist are 0..levels).
+// The grids are made for 2^depth nodes.  A tree often has far fewer deep nodes than that, and a wide launch of
+// workgroups that leave at once costs microseconds per thousand: from kPlanExactDepth on the host waits for each level's
+// number of splits.  Above it the host only looks whether a level without splits is already known (a tree that ends
+// early), without waiting.
+template <typename Partition, typename Hist>
+int32_t planned_levels(gbt_ctx *ctx, const PlannedGrowth &g, Partition partition, Hist hist, std::vector<std::pair<int, int>> *eval_spans,
+                       int *levels) {
+    hipStream_t s = ctx->stream;
+    volatile uint32_t *hint = (volatile uint32_t *)g.v.hint;
+    int64_t nodes = 1;
+    *levels = 0;
+    for (int d = 0; d < g.max_depth; ++d) {
+        bool ended = false;
+        for (int e = 0; e < d; ++e) ended = ended || hint[e] == 0u;
+        if (ended) break;
+        if (d >= kPlanExactDepth) {
+            GBT_SYNC(ctx);
+            nodes = 2 * (int64_t)hint[d - 1];
+            if (nodes == 0) break;
+        }
+        const bool last = d + 1 == g.max_depth;
+        const int chunks = gbt_eval_chunks(g.F, (int)nodes, (size_t)-1);
+        EvalTail tail{nullptr, nullptr, 0, 0, -1, 0};
+        tail.skip_store = last ? 1 : 0;   // (the children are leaves: nothing will subtract from these histograms)
+        const int span = gbt_prof_begin(ctx, GBT_PROF_EVAL, 0.0);
+        if (span >= 0) eval_spans->push_back({span, d});
+        GBT_HIP(ctx, gbt_launch_eval(s, g.v.pool, g.v.enodes, (int)nodes, g.nb, g.F, g.B, chunks, g.v.inv_sg, g.v.inv_sh,
+                                     g.v.lambda, g.min_child_weight, (gbt_split *)g.v.recs, tail, &g.v.levels[d].n_nodes));
+        gbt_prof_end(ctx);
+        GBT_HIP(ctx, gbt_launch_plan_split(s, g.v, d, chunks, g.tile_rows[last]));
+        const bool deferred = last && g.defer_last;
+        if (!deferred) {
+            const int32_t st = partition(d, nodes, g.n / g.tile_rows[last] + nodes, last);
+            if (st != GBT_OK) return st;
+        }
+        GBT_HIP(ctx, gbt_launch_plan_children(s, g.v, d, nodes, deferred ? nullptr : g.n_left[last],
+                                              g.n_left_stride[last], !last, g.rule));
+        if (!last) {
+            const int32_t st = hist(d, plan_hist_jobs_max(g.rule, g.n, nodes));
+            if (st != GBT_OK) return st;
+        }
+        *levels = d + 1;
+        nodes *= 2;
+    }
+    return GBT_OK;
+}
+
+// The caller's tree from the nodes a planned growth left in the read-back buffer (the stream has been waited for).
+int32_t read_planned_tree(gbt_ctx *ctx, const PlannedGrowth &g, int n_levels, gbt_tree *tree) {
+    const PlanLevel *lv = (const PlanLevel *)rb(ctx);
+    const PlanNode *nd = (const PlanNode *)(rb(ctx) + kPlanNodesOff);
+    int64_t n_nodes = 1;
+    for (int d = 0; d <= n_levels; ++d) {
+        n_nodes = std::max<int64_t>(n_nodes, (int64_t)lv[d].first_node + lv[d].n_nodes);
+        GBT_REQUIRE(ctx, !lv[d].bad, GBT_EHIP, "internal: a node of depth %d has fewer rows than went left", d - 1);
+    }
+    GBT_REQUIRE(ctx, n_nodes <= g.cap_nodes && n_nodes <= tree->capacity, GBT_EHIP, "internal: %lld nodes", (long long)n_nodes);
+    for (int64_t i = 0; i < n_nodes; ++i) {
+        const PlanNode &q = nd[i];
+        const double G = (double)q.Gq * g.v.inv_sg, H = (double)q.Hq * g.v.inv_sh;
+        const bool leaf = q.feature < 0;
+        tree->feature[i] = q.feature;
+        tree->bin[i] = leaf ? 0 : q.bin;
+        tree->default_left[i] = leaf ? 0 : q.default_left;
+        tree->left[i] = leaf ? -1 : q.left;
+        tree->right[i] = leaf ? -1 : q.left + 1;
+        tree->threshold[i] = leaf ? INFINITY : q.threshold;
+        tree->gain[i] = leaf ? 0.0 : q.gain;
+        tree->sumG[i] = G;
+        tree->sumH[i] = H;
+        tree->weight[i] = H + g.v.lambda > 0.0 ? -G / (H + g.v.lambda) : 0.0;   // no curvature, no step
+        tree->n_rows[i] = q.len;
+    }
+    tree->n_nodes = (int32_t)n_nodes;
+    return GBT_OK;
+}
+// offsets of a tree's arrays behind its DevTree, as predict_impl lays one tree out
+DevTree plan_tree_arrays(int64_t cap_nodes) {
+    DevTree t{};
+    size_t o = gbt_align(sizeof(DevTree));
+    uint64_t *at[6] = {&t.feature, &t.bin, &t.default_left, &t.left, &t.right, &t.threshold};
+    for (uint64_t *p : at) {
+        *p = o;
+        o += gbt_align((size_t)cap_nodes * 4);
+    }
+    t.weight = o;
+    return t;
+}
+// the view's members that do not depend on the storage form
+PlanView plan_view(gbt_ctx *ctx, char *plan, const PlanLayout &P, char *tree_stage, int64_t cap_nodes) {
+    PlanView v{};
+    v.levels = (PlanLevel *)(plan + P.levels);
+    v.nodes = (PlanNode *)(plan + P.nodes);
+    v.recs = (const gbt_split *)(plan + P.recs);
+    v.win = (uint32_t *)(plan + P.win);
+    v.pjobs = (PartJob *)(plan + P.pjobs);
+    v.pinfo = (PlanJob *)(plan + P.pinfo);
+    v.enodes = (EvalNode *)(plan + P.enodes);
+    v.tree = tree_stage;
+    v.arrays = plan_tree_arrays(cap_nodes);
+    v.hint = (uint32_t *)(rb(ctx) + kPlanHintOff);
+    for (int d = 0; d < kMaxDepth + 2; ++d) v.hint[d] = 0xffffffffu;
+    return v;
+}
+}  // namespace
+
 // Alg. 1 under either policy of Sec. 2.3.  Growth proceeds in rounds: the nodes created by the round
 // before are evaluated; depth-wise then splits every one of them that may split, loss-guided only
 // the open leaf with the largest gain (smaller id on equal gains), however long ago it was created.
@@ -1001,27 +1185,36 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
     matrix.gq_rw = nullptr;
     matrix.id_rw = nullptr;
 
+    const bool root_may_split = max_depth > 0 && (!lossguide || max_leaves > 1);
+    const bool fix_in_hist = ctx->hist_fix && root_may_split && gbt_hist_fix_ok(bits, row_bits, pl.ft, pl.n_ftiles);
+    // Paths 1 and 3, depth-wise: the levels are planned on the device and enqueued without a wait.  (Path 2 and the
+    // loss-guided policy plan on the host; so does a tree too deep for the tables: its job table would not fit the
+    // workspace's, or its nodes the read-back buffer.)
+    bool planned = ctx->plan && !lossguide && root_may_split && (path == 1 || path == 3) && !fix_in_hist && cap <= kPlanNodesMax;
+    PlanHistRule plan_rule{};
+    if (planned) {
+        plan_rule = plan_hist_rule(ctx, pl, F, B, gbt_histw_max_rows(true));   // (the limit that makes the most jobs)
+        planned = plan_hist_jobs_max(plan_rule, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
+    }
     // thresholds come from the cut table: it travels through the part of the pinned read-back buffer that
     // the split records use later, and is picked up behind the first wait below (a copy into pageable
     // memory would be a wait of its own); a table too large for that is copied directly
-    std::vector<float> hcuts((size_t)F * (B - 1));
+    std::vector<float> hcuts(planned ? 0 : (size_t)F * (B - 1));
     constexpr size_t kCutsRb = 512u << 10;   // (= where the split records go, see kSplitRb)
     const bool cuts_via_pinned = hcuts.size() * sizeof(float) <= GBT_STAGING_BYTES - kReadbackOff - kCutsRb;
-    GBT_HIP(ctx, hipMemcpyAsync(cuts_via_pinned ? (void *)(rb(ctx) + kCutsRb) : (void *)hcuts.data(), cuts,
+    if (!planned) GBT_HIP(ctx, hipMemcpyAsync(cuts_via_pinned ? (void *)(rb(ctx) + kCutsRb) : (void *)hcuts.data(), cuts,
                                 hcuts.size() * sizeof(float), hipMemcpyDeviceToHost, s));
 
     // Fixed-point gradient pairs and the root's totals: the scales need one pass over the pairs;
     // the conversion is a pass of its own, or part of the root histogram kernel where that can do it.
     double scale[2];
     int64_t *sums_dev = (int64_t *)(ws + L.scratch + 256);
-    const bool root_may_split = max_depth > 0 && (!lossguide || max_leaves > 1);
     // With a margin to update the finished tree is walked over all rows anyway; that walk can count the rows of
     // every node, so the children of the last level (leaves, of which only the row counts are wanted) need no
     // counting pass of their own.
-    const bool defer_counts = margin_update && !tracked && !leaf_of_row_out && !lossguide && (path == 1 || path == 2) &&
+    const bool defer_counts = margin_update && !tracked && !leaf_of_row_out && !lossguide && path != 0 &&
                               cap <= 8192 && gbt_predict_counts_ok(true, bits, F, (int)cap, true);
     std::vector<int32_t> deferred_children;
-    const bool fix_in_hist = ctx->hist_fix && root_may_split && gbt_hist_fix_ok(bits, row_bits, pl.ft, pl.n_ftiles);
     int uniform_h = 0;
     float h_value = 0.0f;
     gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * (fix_in_hist ? 8.0 : 24.0));
@@ -1051,9 +1244,248 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
         RootFix fix{gpair, scale[0], scale[1], pairs_stay_fp32 ? nullptr : gq, sums_dev, uniform_h,
                     (int32_t)llrint((double)h_value * scale[1]), (int64_t *)(ws + L.jobs), 0};
         st = hist_uniform(ctx, packed, bits, n, F, B, missing_sym, nullptr, n, gq, pool,
-                          (HistJob *)(ws + L.jobs), fix_in_hist ? &fix : nullptr, uniform_h != 0, fix.hq_uniform);
+                          planned ? nullptr : (HistJob *)(ws + L.jobs), fix_in_hist ? &fix : nullptr, uniform_h != 0, fix.hq_uniform);
         if (st != GBT_OK) return st;
         sum_slots = fix_in_hist ? fix.n_slots : 0;
+    }
+    std::vector<LeafSeg> leaves;
+    int32_t n_nodes = 1, n_leaves = 1;
+    // margin_update: one walk of the finished tree over the packed matrix adds eta * leaf weight to every row's
+    // margin, and counts the rows of the nodes whose counting was left to it
+    auto update_margin = [&](int32_t n_tree) -> int32_t {
+        if (!margin_update) return GBT_OK;
+        tree->n_nodes = n_tree;
+        uint32_t *node_rows = deferred_children.empty() ? nullptr : (uint32_t *)(ws + L.node_rows);
+        if (node_rows) GBT_HIP(ctx, gbt_launch_fill_u64(s, (uint64_t *)node_rows, 0, (int64_t)n_tree * kNodeRowsStride / 2));
+        gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * (row_bits / 8.0 + 8.0));
+        const int32_t st2 = predict_impl(ctx, tree, 1, packed, bits, missing_sym, nullptr, n, F, params->eta, margin_update,
+                                         nullptr, ws + L.tree_stage, L.tree_stage_bytes, nullptr, false, node_rows, margin_src);
+        gbt_prof_end(ctx);
+        if (st2 != GBT_OK || !node_rows) return st2;
+        std::vector<uint32_t> counts((size_t)n_tree * kNodeRowsStride);
+        GBT_HIP(ctx, hipMemcpyAsync(counts.data(), node_rows, counts.size() * 4, hipMemcpyDeviceToHost, s));
+        GBT_SYNC(ctx);
+        for (const int32_t id : deferred_children) tree->n_rows[id] = (int64_t)counts[(size_t)id * kNodeRowsStride];
+        return GBT_OK;
+    };
+    // What is left when the tree is complete and the host knows it: the margins, each row's leaf, the row order.
+    auto finish = [&]() -> int32_t {
+        const int32_t n_tree = n_nodes;
+        if (!tracked || path == 1 || path == 2 || lossguide) {
+            tree->n_nodes = n_tree;
+            st = update_margin(n_tree);
+            if (st != GBT_OK) return st;
+            // the rows were not followed: one walk of the finished tree over the matrix names each row's leaf
+            int32_t *leaf_ids = leaf_of_row_out ? leaf_of_row_out : (int32_t *)W[0].id_rw;
+            if (leaf_of_row_out || tracked) {
+                gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * (row_bits / 8.0 + 4.0));
+                st = predict_impl(ctx, tree, 1, packed, bits, missing_sym, nullptr, n, F, 0.0, nullptr, leaf_ids,
+                                  ws + L.tree_stage, L.tree_stage_bytes);
+                gbt_prof_end(ctx);
+                if (st != GBT_OK) return st;
+            }
+            if (tracked) {
+                // ... and the stable partitions' final id list is the rows sorted by their leaf's place in
+                // the tree's left-to-right order, ids ascending inside a leaf
+                std::vector<uint32_t> rank((size_t)n_tree, 0u);
+                std::vector<int32_t> stack{0};
+                uint32_t n_ranks = 0;
+                while (!stack.empty()) {
+                    const int32_t id = stack.back();
+                    stack.pop_back();
+                    if (tree->feature[id] < 0) {
+                        rank[(size_t)id] = n_ranks++;
+                    } else {
+                        stack.push_back(tree->right[id]);
+                        stack.push_back(tree->left[id]);
+                    }
+                }
+                const size_t per_upload = kUploadBytes / 4;
+                for (size_t i0 = 0; i0 < rank.size(); i0 += per_upload) {
+                    st = upload(ctx, rank.data() + i0, std::min(per_upload, rank.size() - i0) * 4, ws + L.rank_tbl + i0 * 4);
+                    if (st != GBT_OK) return st;
+                }
+                uint32_t *key_tmp[2] = {W[1].id_rw, (uint32_t *)(ws + L.wgq[0]) + n};
+                uint32_t *val_tmp[2] = {(uint32_t *)(ws + L.wgq[0]), (uint32_t *)(ws + L.wgq[1])};
+                gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * 12.0);
+                GBT_HIP(ctx, gbt_launch_order_rows(s, leaf_ids, (const uint32_t *)(ws + L.rank_tbl), (uint32_t)n_tree,
+                                                   n_ranks, n, key_tmp, val_tmp, ws + L.order, row_idx_out));
+                gbt_prof_end(ctx);
+            }
+            GBT_SYNC(ctx);
+            return GBT_OK;
+        }
+
+        std::sort(leaves.begin(), leaves.end(),
+                  [](const LeafSeg &a, const LeafSeg &b) {   // an empty segment sorts before the one that starts at the same place
+                      return a.seg_begin != b.seg_begin ? a.seg_begin < b.seg_begin : (a.len != 0) < (b.len != 0);
+                  });
+        st = upload(ctx, leaves.data(), leaves.size() * sizeof(LeafSeg), ws + L.jobs);
+        if (st != GBT_OK) return st;
+        gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * 12.0);
+        GBT_HIP(ctx, gbt_launch_leaf_gather(s, W[0].id, W[1].id, (const LeafSeg *)(ws + L.jobs), (int)leaves.size(), n,
+                                            row_idx_out, leaf_of_row_out));
+        gbt_prof_end(ctx);
+        GBT_SYNC(ctx);
+        tree->n_nodes = n_nodes;
+        return update_margin(n_nodes);
+    };
+    if (planned) {
+        PlannedGrowth g{};
+        const PlanLayout P = plan_layout((int64_t)(2 * L.hist_nodes + 1), L.level_nodes);
+        g.v = plan_view(ctx, ws + L.plan, P, ws + L.tree_stage, cap);
+        g.v.hjobs = (HistJob *)(ws + L.jobs);
+        g.v.cursors = (unsigned long long *)(ws + L.state);
+        g.v.cursors_per_job = path == 1 ? 1 : 0;
+        g.v.pool = pool;
+        g.v.hist_len = hist_len;
+        g.v.cuts = cuts;
+        g.v.F = F;
+        g.v.B = B;
+        g.v.inv_sg = inv_sg;
+        g.v.inv_sh = inv_sh;
+        g.v.lambda = lambda;
+        g.v.min_gain = min_gain;
+        const bool uni_w = uniform_h && bits != 8 && !ctx->hist_runtime_bits;   // the kernels with a row-count form
+        const int32_t hq_w = (int32_t)llrint((double)h_value * scale[1]);
+        g.rule = plan_rule;
+        g.rule.max_rows = gbt_histw_max_rows(uni_w);
+        g.max_depth = max_depth;
+        g.F = F;
+        g.B = B;
+        g.n = n;
+        g.cap_nodes = cap;
+        // (path 1 moves records in one launch, its last level only counts; path 3 partitions ids in three launches throughout)
+        g.tile_rows[0] = path == 1 ? (uint32_t)gbt_partition_fused_tile(W[0]) : (uint32_t)GBT_PART_TILE;
+        g.tile_rows[1] = GBT_PART_TILE;
+        g.n_left[0] = path == 1 ? (const uint32_t *)(ws + L.state) : (const uint32_t *)(ws + L.n_left);
+        g.n_left_stride[0] = path == 1 ? 2 : 1;
+        g.n_left[1] = (const uint32_t *)(ws + L.n_left);
+        g.n_left_stride[1] = 1;
+        g.nb = nb;
+        g.min_child_weight = params->min_child_weight;
+        // The rest of the call can be enqueued behind the levels as well where the tree is walked from LDS at the size it
+        // may have, and a wanted row order has ranks of one byte; otherwise the host waits for the tree first.
+        const bool walk_now = max_depth <= kPlanWalkDepth && gbt_predict_counts_ok(true, bits, F, (int)cap, true) &&
+                              !(tracked && (path == 3 || max_depth > 8));
+        const bool will_walk = margin_update || leaf_of_row_out || (tracked && path == 1);
+        g.defer_last = walk_now ? will_walk : defer_counts;
+        struct PassSpan { int span, depth, kind; };
+        std::vector<PassSpan> pass_spans;
+        std::vector<std::pair<int, int>> eval_spans;
+        uint32_t *n_left32 = (uint32_t *)(ws + L.n_left);
+        auto partition = [&](int d, int64_t splits, int64_t tiles, bool last) -> int32_t {
+            const uint32_t *counts = &g.v.levels[d].n_splits;
+            const GbtRows &cur = d == 0 ? matrix : W[(d - 1) & 1];
+            const GbtRows &dst = W[d & 1];
+            const int span = gbt_prof_begin(ctx, GBT_PROF_PARTITION, 0.0);
+            if (span >= 0) pass_spans.push_back({span, d, path == 3 ? 1 : last ? 2 : 0});
+            if (path == 3) {
+                GBT_HIP(ctx, gbt_launch_partition(s, packed, bits, row_bits, n, (uint32_t)missing_sym, d == 0 ? W[1].id : cur.id,
+                                                  dst.id_rw, g.v.pjobs, (int)splits, (int)tiles, (uint64_t *)(ws + L.masks),
+                                                  (uint32_t *)(ws + L.tile_left), n_left32, counts));
+            } else if (!last) {
+                GBT_HIP(ctx, gbt_launch_partition_fused(s, cur, dst, bits, row_bits, (uint32_t)missing_sym, g.v.pjobs, (int)splits,
+                                                        (int)tiles, g.v.cursors, counts));
+            } else {
+                GBT_HIP(ctx, gbt_launch_partition_records(s, cur, dst, bits, row_bits, n, (uint32_t)missing_sym, GBT_PART_COUNT,
+                                                          g.v.pjobs, (int)splits, (int)tiles, (uint64_t *)(ws + L.masks),
+                                                          (uint32_t *)(ws + L.tile_left), n_left32, counts));
+            }
+            gbt_prof_end(ctx);
+            return GBT_OK;
+        };
+        auto hist = [&](int d, int64_t jobs) -> int32_t {
+            const GbtRows &rows = W[d & 1];
+            const int span = gbt_prof_begin(ctx, GBT_PROF_HIST_NODE, 0.0, 0.0, d + 1, 0.0);
+            if (span >= 0) pass_spans.push_back({span, d, 3});
+            const bool ids = path == 3;   // the rows by id from the caller's matrix, the pairs by id
+            GBT_HIP(ctx, gbt_launch_hist(ctx, ids ? packed : rows.sym, bits, ids ? (int64_t)row_bits : rows.stride_bits,
+                                         ids ? gbt_packed_words(n, F, bits) : rows.n_words, n, B, (uint32_t)missing_sym,
+                                         ids ? rows.id : nullptr, ids ? gq : rows.gq, pool, g.v.hjobs, (int)jobs, pl.ft, uni_w,
+                                         hq_w, &g.v.levels[d + 1].n_hist_jobs));
+            gbt_prof_end(ctx);
+            return GBT_OK;
+        };
+        GBT_HIP(ctx, gbt_launch_plan_root(s, g.v, sums_dev, n, max_depth + 2));
+        int n_levels = 0;
+        st = planned_levels(ctx, g, partition, hist, &eval_spans, &n_levels);
+        if (st != GBT_OK) return st;
+        int32_t *leaf_ids = leaf_of_row_out ? leaf_of_row_out : (int32_t *)W[0].id_rw;
+        const uint32_t *counted = nullptr;
+        if (walk_now && will_walk) {
+            uint32_t *node_rows = (uint32_t *)(ws + L.node_rows);
+            const bool count = g.defer_last && n_levels == max_depth;
+            if (count) {
+                GBT_HIP(ctx, gbt_launch_fill_u64(s, (uint64_t *)node_rows, 0, cap * kNodeRowsStride / 2));
+                counted = node_rows;
+            }
+            const DevTree *dev_tree = (const DevTree *)g.v.tree;
+            if (margin_update) {
+                gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * (row_bits / 8.0 + 8.0));
+                GBT_HIP(ctx, gbt_launch_predict(s, g.v.tree, dev_tree, 1, packed, bits, (uint32_t)missing_sym, nullptr, n, F,
+                                                params->eta, margin_update, nullptr, (int)cap, true, count ? node_rows : nullptr,
+                                                margin_src));
+                gbt_prof_end(ctx);
+            }
+            if (leaf_of_row_out || tracked) {
+                gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * (row_bits / 8.0 + 4.0));
+                GBT_HIP(ctx, gbt_launch_predict(s, g.v.tree, dev_tree, 1, packed, bits, (uint32_t)missing_sym, nullptr, n, F, 0.0,
+                                                nullptr, leaf_ids, (int)cap, true, count && !margin_update ? node_rows : nullptr,
+                                                nullptr));
+                gbt_prof_end(ctx);
+            }
+            if (tracked) {   // (see the end of this function)
+                uint32_t *key_tmp[2] = {W[1].id_rw, (uint32_t *)(ws + L.wgq[0]) + n};
+                uint32_t *val_tmp[2] = {(uint32_t *)(ws + L.wgq[0]), (uint32_t *)(ws + L.wgq[1])};
+                gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * 12.0);
+                GBT_HIP(ctx, gbt_launch_plan_rank(s, g.v, n_levels + 1, (uint32_t *)(ws + L.plan + P.rank_count),
+                                                  (uint32_t *)(ws + L.rank_tbl)));
+                GBT_HIP(ctx, gbt_launch_order_rows(s, leaf_ids, (const uint32_t *)(ws + L.rank_tbl), (uint32_t)cap,
+                                                   1u << max_depth, n, key_tmp, val_tmp, ws + L.order, row_idx_out));
+                gbt_prof_end(ctx);
+            }
+        }
+        GBT_HIP(ctx, gbt_launch_plan_finish(s, g.v, max_depth + 2, max_depth - 1, counted, (PlanLevel *)rb(ctx),
+                                            (PlanNode *)(rb(ctx) + kPlanNodesOff), (uint32_t)cap));
+        GBT_SYNC(ctx);
+        st = read_planned_tree(ctx, g, max_depth + 1, tree);
+        if (st != GBT_OK) return st;
+        n_nodes = tree->n_nodes;
+        const PlanLevel *lv = (const PlanLevel *)rb(ctx);
+        if (ctx->profiling) {   // the passes' bytes, now that the rows are known
+            auto split_rows = [&](int d) {
+                double r = 0;
+                for (uint32_t i = lv[d].first_node; i < lv[d].first_node + lv[d].n_nodes; ++i)
+                    if (tree->feature[i] >= 0) r += (double)tree->n_rows[i];
+                return r;
+            };
+            for (const auto &e : eval_spans)
+                prof_patch_bytes(ctx, e.first, (double)lv[e.second].n_nodes * (double)hist_len * 8.0, -1.0, 0.0);
+            for (const PassSpan &e : pass_spans) {
+                const double sym = bits / 8.0, rec = row_bits / 8.0 + 8.0;
+                if (e.kind == 3) {
+                    const double b = (double)lv[e.depth + 1].built_rows;
+                    prof_patch_bytes(ctx, e.span, b * (rec + (path == 3 ? 4.0 : 0.0)), b * (row_bits / 8.0 + 12.0), b * F);
+                } else {
+                    const double r = split_rows(e.depth);
+                    prof_patch_bytes(ctx, e.span, r * (e.kind == 1 ? 40.0 : e.kind == 2 ? row_bits / 8.0 : 2.0 * rec),
+                                     r * (e.kind == 2 ? sym : 8.0 + sym), 0.0);
+                }
+            }
+        }
+        if (walk_now && (will_walk || !tracked)) return GBT_OK;
+        // the rest on the host's side of the tree
+        if (g.defer_last && n_levels == max_depth)
+            for (uint32_t i = lv[max_depth].first_node; i < lv[max_depth].first_node + lv[max_depth].n_nodes; ++i)
+                deferred_children.push_back((int32_t)i);
+        for (int32_t i = 0, d = 0; i < n_nodes; ++i) {
+            while (d <= max_depth && (uint32_t)i >= lv[d].first_node + lv[d].n_nodes) ++d;
+            if (tree->feature[i] >= 0) continue;
+            const PlanNode &nd = ((const PlanNode *)(rb(ctx) + kPlanNodesOff))[i];
+            leaves.push_back(LeafSeg{nd.begin, (uint32_t)i, d == 0 ? 2u : (uint32_t)((d - 1) & 1), nd.len});
+        }
+        return finish();
     }
     GBT_REQUIRE(ctx, sum_slots <= gbt_hist8_max_jobs() && (size_t)sum_slots * 16 <= kCutsRb, GBT_EHIP, "internal: partial totals");
     GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), sum_slots ? (const void *)(ws + L.jobs) : (const void *)sums_dev,
@@ -1087,14 +1519,12 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
     auto set_node = [&](const HNode &nd) { set_node_at(nd.id, nd); };
 
     std::vector<HNode> level, next;   // the nodes created by the last round: to be evaluated
-    std::vector<LeafSeg> leaves;
     HNode root{0, 0, (uint32_t)n, root_sums[0], root_sums[1], 0, 2};
     set_node(root);
     if (root_may_split)
         level.push_back(root);
     else
         leaves.push_back(LeafSeg{0, 0, 2, (uint32_t)n});
-    int32_t n_nodes = 1, n_leaves = 1;
     // Loss-guided growth.  The tree is defined by a strictly sequential rule (expand the open leaf with
     // the largest gain, then look again), but a step per expansion leaves the chip idle between small
     // launches.  So growth runs in two layers.  PHYSICAL nodes are created in rounds: the leaf whose turn it
@@ -1814,83 +2244,8 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
     }
     // whatever is still waiting when nothing splits any more is a leaf
     for (const HNode &nd : level) leaves.push_back(LeafSeg{nd.begin, (uint32_t)nd.id, (uint32_t)nd.buf, nd.len});
-    const int32_t n_tree = lossguide ? n_logical : n_nodes;   // nodes of the caller's tree
-    // margin_update: one walk of the finished tree over the packed matrix adds eta * leaf weight to every row's
-    // margin, and counts the rows of the nodes whose counting was left to it
-    auto update_margin = [&]() -> int32_t {
-        if (!margin_update) return GBT_OK;
-        tree->n_nodes = n_tree;
-        uint32_t *node_rows = deferred_children.empty() ? nullptr : (uint32_t *)(ws + L.node_rows);
-        if (node_rows) GBT_HIP(ctx, gbt_launch_fill_u64(s, (uint64_t *)node_rows, 0, (int64_t)n_tree * kNodeRowsStride / 2));
-        gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * (row_bits / 8.0 + 8.0));
-        const int32_t st2 = predict_impl(ctx, tree, 1, packed, bits, missing_sym, nullptr, n, F, params->eta, margin_update,
-                                         nullptr, ws + L.tree_stage, L.tree_stage_bytes, nullptr, false, node_rows, margin_src);
-        gbt_prof_end(ctx);
-        if (st2 != GBT_OK || !node_rows) return st2;
-        std::vector<uint32_t> counts((size_t)n_tree * kNodeRowsStride);
-        GBT_HIP(ctx, hipMemcpyAsync(counts.data(), node_rows, counts.size() * 4, hipMemcpyDeviceToHost, s));
-        GBT_SYNC(ctx);
-        for (const int32_t id : deferred_children) tree->n_rows[id] = (int64_t)counts[(size_t)id * kNodeRowsStride];
-        return GBT_OK;
-    };
-    if (!tracked || path == 1 || path == 2 || lossguide) {
-        tree->n_nodes = n_tree;
-        st = update_margin();
-        if (st != GBT_OK) return st;
-        // the rows were not followed: one walk of the finished tree over the matrix names each row's leaf
-        int32_t *leaf_ids = leaf_of_row_out ? leaf_of_row_out : (int32_t *)W[0].id_rw;
-        if (leaf_of_row_out || tracked) {
-            gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * (row_bits / 8.0 + 4.0));
-            st = predict_impl(ctx, tree, 1, packed, bits, missing_sym, nullptr, n, F, 0.0, nullptr, leaf_ids,
-                              ws + L.tree_stage, L.tree_stage_bytes);
-            gbt_prof_end(ctx);
-            if (st != GBT_OK) return st;
-        }
-        if (tracked) {
-            // ... and the stable partitions' final id list is the rows sorted by their leaf's place in
-            // the tree's left-to-right order, ids ascending inside a leaf
-            std::vector<uint32_t> rank((size_t)n_tree, 0u);
-            std::vector<int32_t> stack{0};
-            uint32_t n_ranks = 0;
-            while (!stack.empty()) {
-                const int32_t id = stack.back();
-                stack.pop_back();
-                if (tree->feature[id] < 0) {
-                    rank[(size_t)id] = n_ranks++;
-                } else {
-                    stack.push_back(tree->right[id]);
-                    stack.push_back(tree->left[id]);
-                }
-            }
-            const size_t per_upload = kUploadBytes / 4;
-            for (size_t i0 = 0; i0 < rank.size(); i0 += per_upload) {
-                st = upload(ctx, rank.data() + i0, std::min(per_upload, rank.size() - i0) * 4, ws + L.rank_tbl + i0 * 4);
-                if (st != GBT_OK) return st;
-            }
-            uint32_t *key_tmp[2] = {W[1].id_rw, (uint32_t *)(ws + L.wgq[0]) + n};
-            uint32_t *val_tmp[2] = {(uint32_t *)(ws + L.wgq[0]), (uint32_t *)(ws + L.wgq[1])};
-            gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * 12.0);
-            GBT_HIP(ctx, gbt_launch_order_rows(s, leaf_ids, (const uint32_t *)(ws + L.rank_tbl), (uint32_t)n_tree,
-                                               n_ranks, n, key_tmp, val_tmp, ws + L.order, row_idx_out));
-            gbt_prof_end(ctx);
-        }
-        GBT_SYNC(ctx);
-        return GBT_OK;
-    }
-
-    std::sort(leaves.begin(), leaves.end(),
-              [](const LeafSeg &a, const LeafSeg &b) {   // an empty segment sorts before the one that starts at the same place
-                  return a.seg_begin != b.seg_begin ? a.seg_begin < b.seg_begin : (a.len != 0) < (b.len != 0);
-              });
-    st = upload(ctx, leaves.data(), leaves.size() * sizeof(LeafSeg), ws + L.jobs);
-    if (st != GBT_OK) return st;
-    gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * 12.0);
-    GBT_HIP(ctx, gbt_launch_leaf_gather(s, W[0].id, W[1].id, (const LeafSeg *)(ws + L.jobs), (int)leaves.size(), n,
-                                        row_idx_out, leaf_of_row_out));
-    gbt_prof_end(ctx);
-    GBT_SYNC(ctx);
-    tree->n_nodes = n_nodes;
-    return update_margin();
+    if (lossguide) n_nodes = n_logical;   // nodes of the caller's tree
+    return finish();
 }
 
 extern "C" int32_t gbt_grow_tree(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int64_t n, int32_t F,
@@ -2208,13 +2563,14 @@ int sparse_ent_bytes(int64_t F, int64_t B) { return F * B <= 65536 ? 2 : 4; }
 // Rows per workgroup: every workgroup merges its whole id tile into HBM at the end with 64-bit global
 // atomics (about 10^11 of them per second, all compute units together), so a launch aims at few, long
 // jobs: the rows are cut into about one piece per compute unit, whatever the number of id tiles.
+constexpr int64_t kSparseMinRowsPerJob = 2048, kSparseMaxRowsPerJob = (int64_t)1 << 24;
 uint32_t sparse_rows_per_job(const gbt_ctx *ctx, int64_t total_rows, int64_t bins, int glen) {
     (void)bins;
     (void)glen;
     int64_t per_tile = std::max<int64_t>(1, (int64_t)ctx->num_cu * ctx->sparse_jobs_per_cu);
     int64_t rpj = (total_rows + per_tile - 1) / per_tile;
-    if (rpj < 2048) rpj = 2048;
-    if (rpj > ((int64_t)1 << 24)) rpj = (int64_t)1 << 24;
+    if (rpj < kSparseMinRowsPerJob) rpj = kSparseMinRowsPerJob;
+    if (rpj > kSparseMaxRowsPerJob) rpj = kSparseMaxRowsPerJob;
     return (uint32_t)rpj;
 }
 
@@ -2320,7 +2676,7 @@ extern "C" int32_t gbt_build_hist_sparse(gbt_ctx *ctx, const uint32_t *rowptr, c
 namespace {
 struct SparseGrowLayout {
     size_t gq, rowptr[2], ent[2], wgq[2], state, pool, eval_nodes, jobs, scratch, tree_stage, tree_stage_bytes,
-        order, rank_tbl, total;
+        order, rank_tbl, plan, total;
     int64_t hist_nodes, level_nodes;
 };
 // hist_nodes: nodes that may own a histogram (ids below it); level_nodes: most nodes split in one round
@@ -2345,6 +2701,7 @@ SparseGrowLayout sparse_grow_layout_nodes(int64_t n, int64_t nnz, int F, int B, 
     L.tree_stage = o; o += gbt_align(L.tree_stage_bytes);
     L.order = o;      o += gbt_order_ws(n);
     L.rank_tbl = o;   o += gbt_align(cap_nodes * 4);
+    L.plan = o;       o += plan_layout((int64_t)cap_nodes, L.level_nodes).total;
     L.total = o;
     return L;
 }
@@ -2409,8 +2766,19 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
     void *w_ent[2] = {(void *)(ws + L.ent[0]), (void *)(ws + L.ent[1])};
     int32_t *w_gq[2] = {(int32_t *)(ws + L.wgq[0]), (int32_t *)(ws + L.wgq[1])};
     auto rows_of = [&](int buf) { return buf == 2 ? canon : Rows{w_rowptr[buf], w_ent[buf], w_gq[buf]}; };
-    std::vector<float> hcuts((size_t)F * (B - 1));
-    GBT_HIP(ctx, hipMemcpyAsync(hcuts.data(), cuts, hcuts.size() * sizeof(float), hipMemcpyDeviceToHost, s));
+    const bool root_may_split = max_depth > 0 && (!lossguide || max_leaves > 1);
+    // depth-wise: the levels are planned on the device, as in grow_impl
+    PlanHistRule plan_rule{};   // the rule of sparse_rows_per_job
+    plan_rule.pieces_max = std::max<int64_t>(1, (int64_t)ctx->num_cu * ctx->sparse_jobs_per_cu);
+    plan_rule.min_rows = kSparseMinRowsPerJob;
+    plan_rule.max_rows = kSparseMaxRowsPerJob;
+    plan_rule.tiles = (int)((bins + glen - 1) / glen);
+    plan_rule.ft = glen;
+    plan_rule.width = (int)bins;
+    const bool planned = ctx->plan && !lossguide && root_may_split && cap <= kPlanNodesMax &&
+                         plan_hist_jobs_max(plan_rule, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
+    std::vector<float> hcuts(planned ? 0 : (size_t)F * (B - 1));
+    if (!planned) GBT_HIP(ctx, hipMemcpyAsync(hcuts.data(), cuts, hcuts.size() * sizeof(float), hipMemcpyDeviceToHost, s));
 
     double scale[2];
     int64_t *sums_dev = (int64_t *)(ws + L.scratch + 256);
@@ -2442,13 +2810,131 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
         return GBT_OK;
     };
 
-    const bool root_may_split = max_depth > 0 && (!lossguide || max_leaves > 1);
     if (root_may_split) {
         GBT_HIP(ctx, gbt_launch_fill_u64(s, (uint64_t *)pool, 0, hist_len));
         hjobs.clear();
         add_sparse_hist_jobs(hjobs, 0, 0, (uint32_t)n, bins, glen, sparse_rows_per_job(ctx, n, bins, glen));
         st = launch_hist(canon, GBT_PROF_HIST_ROOT, (double)n * row_bytes);
         if (st != GBT_OK) return st;
+    }
+    // What is left when the tree is complete: each row's leaf, the row order.
+    auto finish = [&](int32_t n_tree) -> int32_t {
+        tree->n_nodes = n_tree;
+
+        // ---- each row's leaf by a walk of the finished tree; the row order by a stable sort on leaf rank
+        int32_t *leaf_ids = leaf_of_row_out ? leaf_of_row_out : (int32_t *)w_rowptr[0];
+        if (leaf_of_row_out || row_idx_out) {
+            const SparseRowsArg sr{rowptr, ent, ent_bytes, B};
+            gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * (row_bytes - 8.0 + 4.0));
+            st = predict_impl(ctx, tree, 1, nullptr, 1, 0, nullptr, n, F, 0.0, nullptr, leaf_ids, ws + L.tree_stage,
+                              L.tree_stage_bytes, &sr);
+            gbt_prof_end(ctx);
+            if (st != GBT_OK) return st;
+        }
+        if (row_idx_out) {
+            std::vector<uint32_t> rank((size_t)n_tree, 0u);
+            std::vector<int32_t> stack{0};
+            uint32_t n_ranks = 0;
+            while (!stack.empty()) {
+                const int32_t id = stack.back();
+                stack.pop_back();
+                if (tree->feature[id] < 0) {
+                    rank[(size_t)id] = n_ranks++;
+                } else {
+                    stack.push_back(tree->right[id]);
+                    stack.push_back(tree->left[id]);
+                }
+            }
+            const size_t per_upload = kUploadBytes / 4;
+            for (size_t i0 = 0; i0 < rank.size(); i0 += per_upload) {
+                st = upload(ctx, rank.data() + i0, std::min(per_upload, rank.size() - i0) * 4, ws + L.rank_tbl + i0 * 4);
+                if (st != GBT_OK) return st;
+            }
+            uint32_t *key_tmp[2] = {w_rowptr[1], (uint32_t *)w_gq[0] + n};
+            uint32_t *val_tmp[2] = {(uint32_t *)w_gq[0], (uint32_t *)w_gq[1]};
+            gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * 12.0);
+            GBT_HIP(ctx, gbt_launch_order_rows(s, leaf_ids, (const uint32_t *)(ws + L.rank_tbl), (uint32_t)n_tree, n_ranks, n,
+                                               key_tmp, val_tmp, ws + L.order, row_idx_out));
+            gbt_prof_end(ctx);
+        }
+        GBT_SYNC(ctx);
+        return GBT_OK;
+    };
+    if (planned) {
+        PlannedGrowth g{};
+        const PlanLayout P = plan_layout((int64_t)(2 * L.hist_nodes + 1), L.level_nodes);
+        g.v = plan_view(ctx, ws + L.plan, P, ws + L.tree_stage, cap);
+        g.v.hjobs = (HistJob *)(ws + L.jobs);
+        g.v.cursors = (unsigned long long *)(ws + L.state);
+        g.v.cursors_per_job = 2;
+        g.v.pool = pool;
+        g.v.hist_len = hist_len;
+        g.v.cuts = cuts;
+        g.v.F = F;
+        g.v.B = B;
+        g.v.inv_sg = inv_sg;
+        g.v.inv_sh = inv_sh;
+        g.v.lambda = lambda;
+        g.v.min_gain = min_gain;
+        g.rule = plan_rule;
+        g.max_depth = max_depth;
+        g.F = F;
+        g.B = B;
+        g.n = n;
+        g.cap_nodes = cap;
+        for (int k = 0; k < 2; ++k) {
+            g.tile_rows[k] = (uint32_t)gbt_sparse_part_tile();
+            g.n_left[k] = (const uint32_t *)(ws + L.state);   // four words per job; the first: left rows
+            g.n_left_stride[k] = 4;
+        }
+        g.nb = nb;
+        g.min_child_weight = params->min_child_weight;
+        struct PassSpan { int span, depth; bool hist; };
+        std::vector<PassSpan> pass_spans;
+        std::vector<std::pair<int, int>> eval_spans;
+        auto partition = [&](int d, int64_t n_splits, int64_t tiles, bool last) -> int32_t {
+            const Rows cur = rows_of(d == 0 ? 2 : (d - 1) & 1);
+            const int to = d & 1;
+            const int span = gbt_prof_begin(ctx, GBT_PROF_PARTITION, 0.0);
+            if (span >= 0) pass_spans.push_back({span, d, false});
+            GBT_HIP(ctx, gbt_launch_sparse_partition(s, cur.rowptr, cur.ent, ent_bytes, cur.gq, w_rowptr[to], w_ent[to], w_gq[to], B,
+                                                     !last, g.v.pjobs, (int)n_splits, (int)tiles, g.v.cursors,
+                                                     &g.v.levels[d].n_splits));
+            gbt_prof_end(ctx);
+            return GBT_OK;
+        };
+        auto hist = [&](int d, int64_t jobs) -> int32_t {
+            const Rows rows = rows_of(d & 1);
+            const int span = gbt_prof_begin(ctx, GBT_PROF_HIST_NODE, 0.0);
+            if (span >= 0) pass_spans.push_back({span, d, true});
+            GBT_HIP(ctx, gbt_launch_sparse_hist(ctx, rows.rowptr, rows.ent, ent_bytes, rows.gq, pool, g.v.hjobs, (int)jobs, glen,
+                                                glen < bins, &g.v.levels[d + 1].n_hist_jobs));
+            gbt_prof_end(ctx);
+            return GBT_OK;
+        };
+        GBT_HIP(ctx, gbt_launch_plan_root(s, g.v, sums_dev, n, max_depth + 2));
+        int n_levels = 0;
+        st = planned_levels(ctx, g, partition, hist, &eval_spans, &n_levels);
+        if (st != GBT_OK) return st;
+        GBT_HIP(ctx, gbt_launch_plan_finish(s, g.v, max_depth + 2, max_depth - 1, nullptr, (PlanLevel *)rb(ctx),
+                                            (PlanNode *)(rb(ctx) + kPlanNodesOff), (uint32_t)cap));
+        GBT_SYNC(ctx);
+        st = read_planned_tree(ctx, g, max_depth + 1, tree);
+        if (st != GBT_OK) return st;
+        if (ctx->profiling) {   // the passes' bytes, now that the rows are known
+            const PlanLevel *lv = (const PlanLevel *)rb(ctx);
+            for (const auto &e : eval_spans)
+                prof_patch_bytes(ctx, e.first, (double)lv[e.second].n_nodes * (double)hist_len * 8.0, -1.0, 0.0);
+            for (const PassSpan &e : pass_spans) {
+                double r = e.hist ? (double)lv[e.depth + 1].built_rows * row_bytes : 0.0;
+                if (!e.hist)
+                    for (uint32_t i = lv[e.depth].first_node; i < lv[e.depth].first_node + lv[e.depth].n_nodes; ++i)
+                        if (tree->feature[i] >= 0)
+                            r += (double)tree->n_rows[i] * (e.depth + 1 < max_depth ? 2.0 * row_bytes : row_bytes - 8.0);
+                prof_patch_bytes(ctx, e.span, r, -1.0, 0.0);
+            }
+        }
+        return finish(tree->n_nodes);
     }
     GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), sums_dev, 16, hipMemcpyDeviceToHost, s));
     GBT_SYNC(ctx);
@@ -2684,47 +3170,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
         }
         level.swap(next);
     }
-    const int32_t n_tree = lossguide ? n_logical : n_nodes;   // nodes of the caller's tree
-    tree->n_nodes = n_tree;
-
-    // ---- each row's leaf by a walk of the finished tree; the row order by a stable sort on leaf rank
-    int32_t *leaf_ids = leaf_of_row_out ? leaf_of_row_out : (int32_t *)w_rowptr[0];
-    if (leaf_of_row_out || row_idx_out) {
-        const SparseRowsArg sr{rowptr, ent, ent_bytes, B};
-        gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * (row_bytes - 8.0 + 4.0));
-        st = predict_impl(ctx, tree, 1, nullptr, 1, 0, nullptr, n, F, 0.0, nullptr, leaf_ids, ws + L.tree_stage,
-                          L.tree_stage_bytes, &sr);
-        gbt_prof_end(ctx);
-        if (st != GBT_OK) return st;
-    }
-    if (row_idx_out) {
-        std::vector<uint32_t> rank((size_t)n_tree, 0u);
-        std::vector<int32_t> stack{0};
-        uint32_t n_ranks = 0;
-        while (!stack.empty()) {
-            const int32_t id = stack.back();
-            stack.pop_back();
-            if (tree->feature[id] < 0) {
-                rank[(size_t)id] = n_ranks++;
-            } else {
-                stack.push_back(tree->right[id]);
-                stack.push_back(tree->left[id]);
-            }
-        }
-        const size_t per_upload = kUploadBytes / 4;
-        for (size_t i0 = 0; i0 < rank.size(); i0 += per_upload) {
-            st = upload(ctx, rank.data() + i0, std::min(per_upload, rank.size() - i0) * 4, ws + L.rank_tbl + i0 * 4);
-            if (st != GBT_OK) return st;
-        }
-        uint32_t *key_tmp[2] = {w_rowptr[1], (uint32_t *)w_gq[0] + n};
-        uint32_t *val_tmp[2] = {(uint32_t *)w_gq[0], (uint32_t *)w_gq[1]};
-        gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * 12.0);
-        GBT_HIP(ctx, gbt_launch_order_rows(s, leaf_ids, (const uint32_t *)(ws + L.rank_tbl), (uint32_t)n_tree, n_ranks, n,
-                                           key_tmp, val_tmp, ws + L.order, row_idx_out));
-        gbt_prof_end(ctx);
-    }
-    GBT_SYNC(ctx);
-    return GBT_OK;
+    return finish(lossguide ? n_logical : n_nodes);   // nodes of the caller's tree
 }
 
 extern "C" int32_t gbt_grow_tree_sparse(gbt_ctx *ctx, const uint32_t *rowptr, const void *ent, int64_t n,

@@ -7,6 +7,7 @@
 #include <stdint.h>
 #include <stdio.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "gbt.h"
@@ -32,6 +33,7 @@ struct gbt_ctx {
     int hist_runtime_bits;  // 1: unpack with run-time shifts even where a compile-time kernel exists
     int part_fused;         // 1: one-launch record partition where it applies
     int lossguide_batch;    // open leaves a round of loss-guided growth expands at once (1: only the one whose turn it is)
+    int plan;               // 1: depth-wise levels are planned on the device where that applies (paths 1 and 3, sparse rows)
     int part_nomove;        // partition + histogram path, depth-wise: 1: the last histogram level is built without moving rows; 2: the last two
     int part_cycle;         // same path: above the last two levels, rows are moved every third level only (keep, keep with two histograms, move three levels)
     int part_ids;           // 1: rows wider than 64 words are not moved: id lists are partitioned and the histogram kernel gathers
@@ -170,10 +172,76 @@ struct LeafSeg {
     uint32_t len;
 };
 
+struct DevTree {   // one tree's arrays inside the predict workspace (offsets in bytes)
+    int32_t n_nodes;
+    int32_t pad;   // the tree's depth (steps of its longest root-to-leaf walk)
+    uint64_t feature, bin, default_left, left, right, threshold, weight;
+};
+
+// ---- growth planned on the device (kernels_plan.hip) -------------------------
+struct PlanLevel {           // one depth of the tree
+    uint32_t n_nodes;        // nodes of this depth; their ids are consecutive, from first_node
+    uint32_t first_node;
+    uint32_t n_splits;       // of them split: jobs of the partition ...
+    uint32_t n_tiles;        // ... and its tiles
+    uint32_t n_hist_jobs;    // jobs that build this depth's histograms
+    uint32_t bad;            // a partition counted more left rows than the node has
+    uint64_t built_rows;     // rows of the nodes whose histogram is built
+};
+struct PlanNode {
+    uint32_t begin, len;
+    int64_t Gq, Hq;
+    double gain;
+    int32_t feature, bin, default_left, left;   // feature -1: a leaf; the right child is left + 1
+    float threshold;
+    uint32_t pad;
+};
+struct PlanJob {             // what the children of partition job k need of its node's split
+    uint32_t node, pad;
+    int64_t GLq, HLq;
+};
+// How the rows of a level's built children are cut into histogram jobs (the rule of pick_rows_per_job)
+struct PlanHistRule {
+    int64_t pieces_max, merge_div, cu_per_tile, min_rows, max_rows;
+    int tiles, ft, width;    // feature (or bin id) tiles: `tiles` tiles of ft of the `width` columns (ids)
+    int exclusive_ok;        // a node of one piece stores its bins
+};
+struct PlanView {            // device addresses unless noted
+    PlanLevel *levels;
+    PlanNode *nodes;
+    const gbt_split *recs;   // the evaluation's records, node-major
+    uint32_t *win;           // scratch: the winning chunk of every node of a level
+    PartJob *pjobs;
+    PlanJob *pinfo;
+    EvalNode *enodes;
+    HistJob *hjobs;
+    unsigned long long *cursors;
+    int cursors_per_job;
+    int64_t *pool;
+    int64_t hist_len;
+    const float *cuts;
+    int F, B;
+    double inv_sg, inv_sh, lambda, min_gain;
+    char *tree;              // the tree as the walks read it: a DevTree, then its arrays at `arrays`' offsets
+    DevTree arrays;
+    uint32_t *hint;          // host memory: splits of each level, written when they are known
+};
+hipError_t gbt_launch_plan_root(hipStream_t s, const PlanView &v, const int64_t *sums, int64_t n, int n_levels);
+hipError_t gbt_launch_plan_split(hipStream_t s, const PlanView &v, int depth, int chunks, uint32_t tile_rows);
+// n_left: left rows of split k at n_left[k * stride] (NULL: not counted yet, the children's row counts come later)
+hipError_t gbt_launch_plan_children(hipStream_t s, const PlanView &v, int depth, int64_t max_splits, const uint32_t *n_left,
+                                    int stride, bool with_hist, const PlanHistRule &rule);
+hipError_t gbt_launch_plan_rank(hipStream_t s, const PlanView &v, int n_levels, uint32_t *count, uint32_t *rank);
+hipError_t gbt_launch_plan_finish(hipStream_t s, const PlanView &v, int n_levels, int last, const uint32_t *counted,
+                                  PlanLevel *levels_out, PlanNode *nodes_out, uint32_t cap);
+
 #define GBT_PART_TILE 2048   // rows per partition workgroup
 #define GBT_PART_BLOCK 256
 
 // ---- kernel launchers (each returns the hipGetLastError of its launches) ---
+// DEVICE COUNTS.  Where a launcher takes n_jobs_dev / n_nodes_dev / counts_dev, the number of jobs (nodes) is not known to
+// the host: the host's number is the most there can be, workgroups past the device's one leave at once.  counts_dev holds
+// two words, the jobs and their tiles; the partition's cursors are then cleared by the caller.
 hipError_t gbt_launch_fill_u64(hipStream_t s, uint64_t *p, uint64_t v, int64_t count);
 hipError_t gbt_launch_iota_u32(hipStream_t s, uint32_t *p, int64_t count);
 hipError_t gbt_launch_stream_read(hipStream_t s, const void *buf, int64_t bytes, uint32_t *sink);
@@ -203,12 +271,13 @@ hipError_t gbt_launch_hist(gbt_ctx *ctx, const uint32_t *packed, int bits, int64
                            // every row's rounded h equals hq_uniform: kernels that have a form for it (symbol widths
                            // other than 8 bits) count rows instead of summing h; jobs then hold at most
                            // gbt_histw_max_rows(true) rows
-                           bool uniform_h = false, int32_t hq_uniform = 0);
+                           bool uniform_h = false, int32_t hq_uniform = 0,
+                           const uint32_t *n_jobs_dev = nullptr);   // see DEVICE COUNTS
 int gbt_histw_max_rows(bool uniform_h);
 hipError_t gbt_launch_histw(gbt_ctx *ctx, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n_words,
                             int64_t n, int B, uint32_t missing, const uint32_t *row_idx, const int32_t *gq,
                             int64_t *hist_pool, const HistJob *jobs, int n_jobs, int max_ft, bool uniform_h,
-                            int32_t hq_uniform);
+                            int32_t hq_uniform, const uint32_t *n_jobs_dev = nullptr);
 // Largest feature tile whose LDS histogram fits, and the per-job row count to aim for.
 int gbt_hist_feature_tile(const gbt_ctx *ctx, int F, int B, int64_t n_rows = 0);   // n_rows: rows of the matrix the tiles are for (0: unknown)
 
@@ -234,12 +303,13 @@ struct EvalTail {
 constexpr int kCursorStride = 16;
 hipError_t gbt_launch_eval(hipStream_t s, int64_t *hist_pool, const EvalNode *nodes, int n_nodes,
                            const int32_t *nb, int F, int B, int n_chunks, double inv_sg, double inv_sh,
-                           double lambda, double mcw, gbt_split *out, EvalTail tail = EvalTail{nullptr, nullptr, 0, 0, -1, 0});
+                           double lambda, double mcw, gbt_split *out, EvalTail tail = EvalTail{nullptr, nullptr, 0, 0, -1, 0},
+                           const uint32_t *n_nodes_dev = nullptr);
 
 hipError_t gbt_launch_partition(hipStream_t s, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n,
                                 uint32_t missing, const uint32_t *src, uint32_t *dst,
                                 const PartJob *jobs, int n_jobs, int total_tiles, uint64_t *masks,
-                                uint32_t *tile_left, uint32_t *n_left_out);
+                                uint32_t *tile_left, uint32_t *n_left_out, const uint32_t *counts_dev = nullptr);
 
 // A set of rows in some order: symbols (row p starts at bit p*stride_bits), fixed-point gradient
 // pairs and original row ids (NULL: the id of position p is p).  The *_rw members are the same
@@ -258,7 +328,7 @@ struct GbtRows {
 hipError_t gbt_launch_partition_records(hipStream_t s, const GbtRows &src, const GbtRows &dst, int bits, int row_bits,
                                         int64_t n, uint32_t missing, int what, const PartJob *jobs,
                                         int n_jobs, int total_tiles, uint64_t *masks, uint32_t *tile_left,
-                                        uint32_t *n_left_out);
+                                        uint32_t *n_left_out, const uint32_t *counts_dev = nullptr);
 // `what` above: move whole records, move only the ids, or only count the left rows of every job
 enum { GBT_PART_RECORDS = 0, GBT_PART_IDS = 1, GBT_PART_COUNT = 2 };
 // The same move of whole records in one launch for a caller that does not need the row order
@@ -270,7 +340,7 @@ bool gbt_partition_fused_ok(const GbtRows &dst);
 int gbt_partition_fused_tile(const GbtRows &dst);
 hipError_t gbt_launch_partition_fused(hipStream_t s, const GbtRows &src, const GbtRows &dst, int bits, int row_bits,
                                       uint32_t missing, const PartJob *jobs, int n_jobs, int total_tiles,
-                                      unsigned long long *cursor);
+                                      unsigned long long *cursor, const uint32_t *counts_dev = nullptr);
 // The root histogram straight from the fp32 gradient pairs (8-bit symbols, one feature tile of at
 // most 16 features, jobs that cover rows [0, n) exactly once: gbt_hist_fix_ok): rounds each pair to
 // fixed point with the given scales, stores it to gq_out and adds the totals into sums_out[2].
@@ -398,7 +468,8 @@ hipError_t gbt_launch_sparse_fill(hipStream_t s, const uint16_t *sym, int64_t n,
 int gbt_sparse_hist_tile(const gbt_ctx *ctx, int64_t bins);
 // HistJob.f0 / ft: the job's range of global bin ids
 hipError_t gbt_launch_sparse_hist(gbt_ctx *ctx, const uint32_t *rowptr, const void *ent, int ent_bytes, const int32_t *gq,
-                                  int64_t *pool, const HistJob *jobs, int n_jobs, int max_glen, bool tiled);
+                                  int64_t *pool, const HistJob *jobs, int n_jobs, int max_glen, bool tiled,
+                                  const uint32_t *n_jobs_dev = nullptr);
 
 // Unordered partition of sparse rows, one launch per level (PartJob as for the dense forms; tiles of
 // gbt_sparse_part_tile() rows).  cursor: two 64-bit words per job, cleared here; afterwards the low
@@ -407,8 +478,7 @@ int gbt_sparse_part_tile();
 hipError_t gbt_launch_sparse_partition(hipStream_t s, const uint32_t *src_rowptr, const void *src_ent, int ent_bytes,
                                        const int32_t *src_gq, uint32_t *dst_rowptr, void *dst_ent,
                                        int32_t *dst_gq, int B, bool move, const PartJob *jobs, int n_jobs,
-                                       int n_tiles, unsigned long long *cursor);
-struct DevTree;
+                                       int n_tiles, unsigned long long *cursor, const uint32_t *counts_dev = nullptr);
 hipError_t gbt_launch_sparse_walk(hipStream_t s, const char *ws, const DevTree *trees, int n_trees,
                                   const uint32_t *rowptr, const void *ent, int ent_bytes, int64_t n, int B, double eta,
                                   float *margin, int32_t *leaf_out, int max_nodes);
@@ -416,11 +486,6 @@ hipError_t gbt_launch_sparse_walk(hipStream_t s, const char *ws, const DevTree *
 hipError_t gbt_launch_compress(hipStream_t s, const uint16_t *sym, int64_t n_elems, int bits,
                                uint32_t *packed, int64_t n_words);
 
-struct DevTree {   // one tree's arrays inside the predict workspace (offsets in bytes)
-    int32_t n_nodes;
-    int32_t pad;   // the tree's depth (steps of its longest root-to-leaf walk)
-    uint64_t feature, bin, default_left, left, right, threshold, weight;
-};
 hipError_t gbt_launch_predict(hipStream_t s, const char *ws, const DevTree *trees, int n_trees,
                               const uint32_t *packed, int bits, uint32_t missing, const float *X,
                               int64_t n, int F, double eta, float *margin, int32_t *leaf_out, int max_nodes,

@@ -37,8 +37,10 @@ template <bool LIST>
 __global__ __launch_bounds__(kHistBlock) void hist_generic_kernel(
     const uint32_t *__restrict__ packed, int64_t n_words, int bits, uint32_t inv_bits, int64_t stride_bits,
     int64_t n, int B, int Bp, uint32_t missing, const uint32_t *__restrict__ row_idx,
-    const int2 *__restrict__ gq, int64_t *__restrict__ pool, const HistJob *__restrict__ jobs) {
+    const int2 *__restrict__ gq, int64_t *__restrict__ pool, const HistJob *__restrict__ jobs,
+    const uint32_t *__restrict__ n_jobs_dev) {
     extern __shared__ unsigned long long lds[];
+    if (n_jobs_dev && blockIdx.x >= *n_jobs_dev) return;
     const HistJob job = jobs[blockIdx.x];
     const int ft = (int)job.ft;
     unsigned long long *main_ = lds;
@@ -135,8 +137,9 @@ template <bool LIST, int NS, bool CHK, bool FIX>
 __global__ __launch_bounds__(kHistBlock) void hist_b8_kernel(
     const uint32_t *__restrict__ packed, int64_t n_words, int64_t stride_bytes, int64_t n, int B, int Bp,
     uint32_t missing, const uint32_t *__restrict__ row_idx, const int2 *__restrict__ gq,
-    int64_t *__restrict__ pool, const HistJob *__restrict__ jobs, FixArgs fix) {
+    int64_t *__restrict__ pool, const HistJob *__restrict__ jobs, FixArgs fix, const uint32_t *__restrict__ n_jobs_dev) {
     extern __shared__ unsigned long long lds[];
+    if (n_jobs_dev && blockIdx.x >= *n_jobs_dev) return;
     const HistJob job = jobs[blockIdx.x];
     const int ft = (int)job.ft;
     const int trash = ft * Bp;                       // first word of the trash row
@@ -1271,6 +1274,7 @@ struct B8Args {
     int64_t *pool;
     const HistJob *jobs;
     FixArgs fix;
+    const uint32_t *n_jobs_dev;
 };
 template <bool LIST, int NS, bool CHK, bool FIX>
 hipError_t launch_b8(const B8Args &a) {
@@ -1282,7 +1286,7 @@ hipError_t launch_b8(const B8Args &a) {
     }
     hist_b8_kernel<LIST, NS, CHK, FIX><<<a.n_jobs, a.block, a.lds, a.s>>>(a.packed, a.n_words, a.stride_bytes, a.n,
                                                                               a.B, a.Bp, a.missing, a.row_idx, a.gq,
-                                                                              a.pool, a.jobs, a.fix);
+                                                                              a.pool, a.jobs, a.fix, a.n_jobs_dev);
     return hipGetLastError();
 }
 template <bool LIST, bool CHK, bool FIX>
@@ -1301,7 +1305,8 @@ hipError_t pick_slots(int max_ft, const B8Args &a) {
 template <bool LIST>
 hipError_t launch_generic(hipStream_t s, int n_jobs, int block, size_t lds, const uint32_t *packed, int64_t n_words, int bits,
                           int64_t stride_bits, int64_t n, int B, int Bp, uint32_t missing,
-                          const uint32_t *row_idx, const int2 *gq, int64_t *pool, const HistJob *jobs) {
+                          const uint32_t *row_idx, const int2 *gq, int64_t *pool, const HistJob *jobs,
+                          const uint32_t *n_jobs_dev) {
     GbtLdsGuard lds_guard(lds);
     if (lds_guard.needed) {
         hipError_t e = hipFuncSetAttribute((const void *)hist_generic_kernel<LIST>,
@@ -1310,7 +1315,7 @@ hipError_t launch_generic(hipStream_t s, int n_jobs, int block, size_t lds, cons
     }
     const uint32_t inv_bits = (uint32_t)((((uint64_t)1 << 32) + (uint32_t)bits - 1) / (uint32_t)bits);
     hist_generic_kernel<LIST><<<n_jobs, block, lds, s>>>(packed, n_words, bits, inv_bits, stride_bits, n, B, Bp,
-                                                               missing, row_idx, gq, pool, jobs);
+                                                               missing, row_idx, gq, pool, jobs, n_jobs_dev);
     return hipGetLastError();
 }
 }  // namespace
@@ -1318,24 +1323,24 @@ hipError_t launch_generic(hipStream_t s, int n_jobs, int block, size_t lds, cons
 hipError_t gbt_launch_hist(gbt_ctx *ctx, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n_words,
                            int64_t n, int B, uint32_t missing, const uint32_t *row_idx, const int32_t *gq,
                            int64_t *hist_pool, const HistJob *jobs, int n_jobs, int max_ft, bool uniform_h,
-                           int32_t hq_uniform) {
+                           int32_t hq_uniform, const uint32_t *n_jobs_dev) {
     if (n_jobs <= 0) return hipSuccess;
     if (!ctx->hist_runtime_bits && bits != 8)
         return gbt_launch_histw(ctx, packed, bits, stride_bits, n_words, n, B, missing, row_idx, gq, hist_pool, jobs,
-                                n_jobs, max_ft, uniform_h, hq_uniform);
+                                n_jobs, max_ft, uniform_h, hq_uniform, n_jobs_dev);
     const int Bp = padded_bins(B);
     const size_t lds = ((size_t)max_ft * Bp + 256) * 12;
     const int2 *g2 = (const int2 *)gq;
     hipStream_t s = ctx->stream;
     if (bits == 8 && (stride_bits & 7) == 0) {
         const bool chk = missing < 256u || B < 256;
-        const B8Args a{s, n_jobs, ctx->hist_block, lds, packed, n_words, stride_bits >> 3, n, B, Bp, missing, row_idx, g2, hist_pool, jobs, FixArgs{}};
+        const B8Args a{s, n_jobs, ctx->hist_block, lds, packed, n_words, stride_bits >> 3, n, B, Bp, missing, row_idx, g2, hist_pool, jobs, FixArgs{}, n_jobs_dev};
         if (row_idx) return chk ? pick_slots<true, true>(max_ft, a) : pick_slots<true, false>(max_ft, a);
         return chk ? pick_slots<false, true>(max_ft, a) : pick_slots<false, false>(max_ft, a);
     }
     if (row_idx)
-        return launch_generic<true>(s, n_jobs, ctx->hist_block, lds, packed, n_words, bits, stride_bits, n, B, Bp, missing, row_idx, g2, hist_pool, jobs);
-    return launch_generic<false>(s, n_jobs, ctx->hist_block, lds, packed, n_words, bits, stride_bits, n, B, Bp, missing, row_idx, g2, hist_pool, jobs);
+        return launch_generic<true>(s, n_jobs, ctx->hist_block, lds, packed, n_words, bits, stride_bits, n, B, Bp, missing, row_idx, g2, hist_pool, jobs, n_jobs_dev);
+    return launch_generic<false>(s, n_jobs, ctx->hist_block, lds, packed, n_words, bits, stride_bits, n, B, Bp, missing, row_idx, g2, hist_pool, jobs, n_jobs_dev);
 }
 
 bool gbt_hist_fix_ok(int bits, int64_t stride_bits, int max_ft, int n_ftiles) {
@@ -1351,7 +1356,7 @@ hipError_t gbt_launch_hist_fix(gbt_ctx *ctx, const uint32_t *packed, int64_t str
     const size_t lds = ((size_t)max_ft * Bp + 256) * 12;
     const B8Args a{ctx->stream, n_jobs, ctx->hist_block, lds, packed, n_words, stride_bits >> 3, n, B, Bp, missing,
                    nullptr, nullptr, hist_pool, jobs,
-                   FixArgs{(const float2 *)gpair, sg, sh, (int2 *)gq_out, sums_out}};
+                   FixArgs{(const float2 *)gpair, sg, sh, (int2 *)gq_out, sums_out}, nullptr};
     const bool chk = missing < 256u || B < 256;
     return chk ? pick_slots_single<false, true, true>(max_ft, a) : pick_slots_single<false, false, true>(max_ft, a);
 }

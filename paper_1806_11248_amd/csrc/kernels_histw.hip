@@ -56,7 +56,9 @@ template <int BITS, bool LIST, bool UNI, bool CHK>
 __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
     const uint32_t *__restrict__ packed, int64_t n_words, int64_t stride_bits, int64_t n, int B, int Bp,
     uint32_t missing, const uint32_t *__restrict__ row_idx, const int2 *__restrict__ gq,
-    int64_t *__restrict__ pool, const HistJob *__restrict__ jobs, int32_t hq_uniform) {
+    int64_t *__restrict__ pool, const HistJob *__restrict__ jobs, int32_t hq_uniform,
+    const uint32_t *__restrict__ n_jobs_dev) {
+    if (n_jobs_dev && blockIdx.x >= *n_jobs_dev) return;
     constexpr int E = (128 / BITS) < 32 ? (128 / BITS) : 32;   // elements per window
     constexpr int G = E < 16 ? E : 16;                         // atomics in flight per lane
     constexpr uint32_t MASK = (1u << BITS) - 1u;
@@ -216,6 +218,7 @@ struct WArgs {
     int64_t *pool;
     const HistJob *jobs;
     int32_t hq_uniform;
+    const uint32_t *n_jobs_dev;
 };
 template <int BITS, bool LIST, bool UNI, bool CHK>
 hipError_t launch_w(const WArgs &a) {
@@ -227,7 +230,7 @@ hipError_t launch_w(const WArgs &a) {
     }
     hist_bits_kernel<BITS, LIST, UNI, CHK><<<a.n_jobs, a.block, a.lds, a.s>>>(a.packed, a.n_words, a.stride_bits, a.n, a.B, a.Bp,
                                                                           a.missing, a.row_idx, a.gq, a.pool, a.jobs,
-                                                                          a.hq_uniform);
+                                                                          a.hq_uniform, a.n_jobs_dev);
     return hipGetLastError();
 }
 template <int BITS, bool CHK>
@@ -248,12 +251,12 @@ int gbt_histw_max_rows(bool uniform_h) { return uniform_h ? (int)kWRowsMask : 1 
 hipError_t gbt_launch_histw(gbt_ctx *ctx, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n_words,
                             int64_t n, int B, uint32_t missing, const uint32_t *row_idx, const int32_t *gq,
                             int64_t *hist_pool, const HistJob *jobs, int n_jobs, int max_ft, bool uniform_h,
-                            int32_t hq_uniform) {
+                            int32_t hq_uniform, const uint32_t *n_jobs_dev) {
     if (n_jobs <= 0) return hipSuccess;
     const int Bp = padded_bins(B);
     const size_t lds = ((size_t)max_ft * Bp + 64) * (uniform_h ? 8 : 12);
     const WArgs a{ctx->stream, n_jobs, ctx->hist_block, lds, packed, n_words, stride_bits, n, B, Bp, missing, row_idx,
-                  (const int2 *)gq, hist_pool, jobs, hq_uniform};
+                  (const int2 *)gq, hist_pool, jobs, hq_uniform, n_jobs_dev};
     switch (bits) {
         case 1: return pick_w<1>(a, uniform_h);
         case 2: return pick_w<2>(a, uniform_h);

@@ -460,40 +460,63 @@ __device__ __forceinline__ uint32_t pick4(const uint32_t (&W)[4], int i) {
 // so every row takes exactly T.pad steps (the tree's depth) and the walks of the kPredRows rows
 // a thread handles at once run side by side instead of one divergent loop after the other.
 constexpr int kPredRows = 4;
+constexpr size_t kWalkLds = 96u * 1024u;   // the most LDS a walk takes
+__device__ __forceinline__ void stage_compact(const char *ws, const DevTree &T, uint2 *cnodes, double *lweight, int max_nodes) {
+    const int n = T.n_nodes < max_nodes ? T.n_nodes : max_nodes;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const int32_t f = ((const int32_t *)(ws + T.feature))[i];
+        uint2 c;
+        if (f < 0) {
+            c.x = (uint32_t)i | 0x80000000u;
+            c.y = 0xfffu;
+        } else {
+            c.x = (uint32_t)((const int32_t *)(ws + T.left))[i] |
+                  (((const int32_t *)(ws + T.default_left))[i] ? 0x80000000u : 0u);
+            c.y = ((uint32_t)f << 12) | (uint32_t)((const int32_t *)(ws + T.bin))[i];
+        }
+        cnodes[i] = c;
+        lweight[i] = ((const double *)(ws + T.weight))[i];
+    }
+}
+// The rows that end in each node, counted per workgroup in LDS and then into node_rows[node * kNodeRowsStride] (one
+// counter per 128-byte line: atomics on one line take turns).
+__device__ __forceinline__ void flush_counts(const uint32_t *lcount, int max_nodes, uint32_t *node_rows) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < max_nodes; i += 256) {
+        const uint32_t c = lcount[i];
+        if (c) atomicAdd(&node_rows[(size_t)i * kNodeRowsStride], c);
+    }
+}
+
+// Q rows of a thread are walked side by side: kPredRows, or one where the matrix has too few rows to fill the chip.
+template <int Q>
 __global__ __launch_bounds__(256) void predict_window_kernel(const char *ws, const DevTree *trees, int n_trees,
                                                              const uint32_t *packed, int64_t n_words, int bits,
                                                              uint32_t missing, int64_t n, int F, double eta,
                                                              float *margin, int rows_per_block, int max_nodes,
-                                                             int32_t *leaf_out) {
+                                                             int32_t *leaf_out, uint32_t *node_rows,
+                                                             const float *margin_src) {
     extern __shared__ uint2 cnodes[];
     double *lweight = (double *)(cnodes + max_nodes);
+    uint32_t *lcount = (uint32_t *)(lweight + max_nodes);   // only there when node_rows is given
+    if (node_rows)
+        for (int i = threadIdx.x; i < max_nodes; i += 256) lcount[i] = 0;
     const uint32_t mask = (1u << bits) - 1u;
-    const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
-    const int64_t r1 = r0 + rows_per_block < n ? r0 + rows_per_block : n;
+    const int64_t n_blocks = (n + rows_per_block - 1) / rows_per_block;
     for (int t = 0; t < n_trees; ++t) {
         const DevTree T = trees[t];
         __syncthreads();
-        for (int i = threadIdx.x; i < T.n_nodes; i += 256) {
-            const int32_t f = ((const int32_t *)(ws + T.feature))[i];
-            uint2 c;
-            if (f < 0) {
-                c.x = (uint32_t)i | 0x80000000u;
-                c.y = 0xfffu;
-            } else {
-                c.x = (uint32_t)((const int32_t *)(ws + T.left))[i] |
-                      (((const int32_t *)(ws + T.default_left))[i] ? 0x80000000u : 0u);
-                c.y = ((uint32_t)f << 12) | (uint32_t)((const int32_t *)(ws + T.bin))[i];
-            }
-            cnodes[i] = c;
-            lweight[i] = ((const double *)(ws + T.weight))[i];
-        }
+        stage_compact(ws, T, cnodes, lweight, max_nodes);
         __syncthreads();
         const int depth = T.pad;
-        for (int64_t rb = r0 + threadIdx.x; rb < r1; rb += 256 * kPredRows) {
-            uint32_t W[kPredRows][4];
-            float m[kPredRows];
+        for (int64_t blk = blockIdx.x; blk < n_blocks; blk += gridDim.x) {
+        const int64_t r0 = blk * rows_per_block;
+        const int64_t r1 = r0 + rows_per_block < n ? r0 + rows_per_block : n;
+        for (int64_t rb = r0 + threadIdx.x; rb < r1; rb += 256 * Q) {
+            uint32_t W[Q][4];
+            float m[Q];
 #pragma unroll
-            for (int q = 0; q < kPredRows; ++q) {
+            for (int q = 0; q < Q; ++q) {
                 // rows past the end repeat the last row (their result is dropped)
                 const int64_t r = rb + 256 * q < r1 ? rb + 256 * q : r1 - 1;
                 const uint64_t rowbit = (uint64_t)r * (uint64_t)F * (uint64_t)bits;
@@ -504,14 +527,14 @@ __global__ __launch_bounds__(256) void predict_window_kernel(const char *ws, con
                 for (int k = 0; k < 5; ++k) w[k] = packed[w0 + k < n_words ? w0 + k : n_words - 1];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) W[q][k] = __builtin_amdgcn_alignbit(w[k + 1], w[k], sh);
-                m[q] = leaf_out ? 0.f : margin[r];
+                m[q] = leaf_out ? 0.f : margin_src[r];
             }
-            uint32_t node[kPredRows];
+            uint32_t node[Q];
 #pragma unroll
-            for (int q = 0; q < kPredRows; ++q) node[q] = 0;
+            for (int q = 0; q < Q; ++q) node[q] = 0;
             for (int step = 0; step < depth; ++step) {
 #pragma unroll
-                for (int q = 0; q < kPredRows; ++q) {
+                for (int q = 0; q < Q; ++q) {
                     const uint2 c = cnodes[node[q]];
                     const int pos = (int)(c.y >> 12) * bits, wd = pos >> 5;
                     const uint32_t lo = pick4(W[q], wd), hi = wd < 3 ? pick4(W[q], wd + 1) : 0u;
@@ -521,15 +544,96 @@ __global__ __launch_bounds__(256) void predict_window_kernel(const char *ws, con
                 }
             }
 #pragma unroll
-            for (int q = 0; q < kPredRows; ++q) {
+            for (int q = 0; q < Q; ++q) {
                 const int64_t r = rb + 256 * q;
                 if (r < r1) {
                     if (leaf_out) leaf_out[r] = (int32_t)node[q];
                     else margin[r] = (float)((double)m[q] + eta * lweight[node[q]]);
+                    if (node_rows) atomicAdd(&lcount[node[q]], 1u);
+                }
+            }
+        }
+        }
+    }
+    if (node_rows) flush_counts(lcount, max_nodes, node_rows);
+}
+
+// Rows of any width: every level's symbol is fetched from the matrix, one dependent access per level (the rows a thread
+// walks side by side keep Q of them in flight).  Nodes as above, with bit 30 of x set on a leaf: it keeps its rows
+// whatever symbol the matrix holds for them.
+// 1M x 28 bytes, depth 6: 37 us with one row at a time and a branch per step, 9 us so.
+template <int Q>
+__global__ __launch_bounds__(256) void predict_gather_kernel(const char *ws, const DevTree *trees, int n_trees,
+                                                             const uint32_t *packed, int bits, uint32_t missing, int64_t n,
+                                                             int F, double eta, float *margin, int rows_per_block,
+                                                             int max_nodes, int32_t *leaf_out, uint32_t *node_rows,
+                                                             const float *margin_src) {
+    extern __shared__ uint2 cnodes[];
+    double *lweight = (double *)(cnodes + max_nodes);
+    uint32_t *lcount = (uint32_t *)(lweight + max_nodes);   // only there when node_rows is given
+    if (node_rows)
+        for (int i = threadIdx.x; i < max_nodes; i += 256) lcount[i] = 0;
+    const uint32_t mask = (1u << bits) - 1u;
+    const uint64_t stride_bits = (uint64_t)F * (uint64_t)bits;
+    const int64_t n_blocks = (n + rows_per_block - 1) / rows_per_block;
+    struct __attribute__((packed, aligned(4))) Pair4 {   // a symbol lies in one word or two; the stream ends in a pad word
+        uint32_t lo, hi;
+    };
+    for (int t = 0; t < n_trees; ++t) {
+        const DevTree T = trees[t];
+        __syncthreads();
+        stage_compact(ws, T, cnodes, lweight, max_nodes);
+        __syncthreads();
+        for (int i = threadIdx.x; i < T.n_nodes && i < max_nodes; i += 256)   // (a thread's own nodes)
+            if (cnodes[i].y == 0xfffu && cnodes[i].x == ((uint32_t)i | 0x80000000u)) cnodes[i].x |= 0x40000000u;
+        __syncthreads();
+        const int depth = T.pad;
+        for (int64_t blk = blockIdx.x; blk < n_blocks; blk += gridDim.x) {
+            const int64_t r0 = blk * rows_per_block;
+            const int64_t r1 = r0 + rows_per_block < n ? r0 + rows_per_block : n;
+            for (int64_t rb = r0 + threadIdx.x; rb < r1; rb += 256 * Q) {
+                uint64_t rowbit[Q];
+                float m[Q];
+                uint32_t node[Q];
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const int64_t r = rb + 256 * q < r1 ? rb + 256 * q : r1 - 1;   // past the end: the last row again
+                    rowbit[q] = (uint64_t)r * stride_bits;
+                    m[q] = leaf_out ? 0.f : margin_src[r];
+                    node[q] = 0;
+                }
+                for (int step = 0; step < depth; ++step) {
+                    uint2 c[Q];
+                    Pair4 w[Q];
+                    uint32_t sh[Q];
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) {
+                        c[q] = cnodes[node[q]];
+                        const uint64_t bp = rowbit[q] + (uint64_t)((c[q].y >> 12) * (uint32_t)bits);
+                        w[q] = *(const Pair4 *)(packed + (bp >> 5));
+                        sh[q] = (uint32_t)(bp & 31);
+                    }
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) {
+                        const uint32_t sy = __builtin_amdgcn_alignbit(w[q].hi, w[q].lo, sh[q]) & mask;
+                        bool stay = (sy == missing) ? (c[q].x >> 31) != 0 : (sy <= (c[q].y & 0xfffu));
+                        stay |= (c[q].x & 0x40000000u) != 0;
+                        node[q] = (c[q].x & 0x3fffffffu) + (stay ? 0u : 1u);
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const int64_t r = rb + 256 * q;
+                    if (r < r1) {
+                        if (leaf_out) leaf_out[r] = (int32_t)node[q];
+                        else margin[r] = (float)((double)m[q] + eta * lweight[node[q]]);
+                        if (node_rows) atomicAdd(&lcount[node[q]], 1u);
+                    }
                 }
             }
         }
     }
+    if (node_rows) flush_counts(lcount, max_nodes, node_rows);
 }
 
 // Rows wider than the register window, up to kStagedRowBits bits: a wave's 64 consecutive rows are one contiguous
@@ -541,34 +645,27 @@ __global__ __launch_bounds__(256) void predict_staged_kernel(const char *ws, con
                                                              const uint32_t *packed, int64_t n_words, int bits,
                                                              uint32_t missing, int64_t n, int F, double eta,
                                                              float *margin, int rows_per_block, int max_nodes,
-                                                             int32_t *leaf_out, int wave_words) {
+                                                             int32_t *leaf_out, int wave_words, uint32_t *node_rows,
+                                                             const float *margin_src) {
     extern __shared__ uint2 cnodes[];
     double *lweight = (double *)(cnodes + max_nodes);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint32_t *st = (uint32_t *)(lweight + max_nodes) + (size_t)wave * wave_words;
+    uint32_t *lcount = (uint32_t *)(lweight + max_nodes) + (size_t)4 * wave_words;   // only there when node_rows is given
+    if (node_rows)
+        for (int i = threadIdx.x; i < max_nodes; i += 256) lcount[i] = 0;
     const uint32_t mask = (1u << bits) - 1u;
     const uint64_t stride_bits = (uint64_t)F * (uint64_t)bits;
-    const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
-    const int64_t r1 = r0 + rows_per_block < n ? r0 + rows_per_block : n;
+    const int64_t n_blocks = (n + rows_per_block - 1) / rows_per_block;
     for (int t = 0; t < n_trees; ++t) {
         const DevTree T = trees[t];
         __syncthreads();
-        for (int i = threadIdx.x; i < T.n_nodes; i += 256) {
-            const int32_t f = ((const int32_t *)(ws + T.feature))[i];
-            uint2 c;
-            if (f < 0) {
-                c.x = (uint32_t)i | 0x80000000u;
-                c.y = 0xfffu;
-            } else {
-                c.x = (uint32_t)((const int32_t *)(ws + T.left))[i] |
-                      (((const int32_t *)(ws + T.default_left))[i] ? 0x80000000u : 0u);
-                c.y = ((uint32_t)f << 12) | (uint32_t)((const int32_t *)(ws + T.bin))[i];
-            }
-            cnodes[i] = c;
-            lweight[i] = ((const double *)(ws + T.weight))[i];
-        }
+        stage_compact(ws, T, cnodes, lweight, max_nodes);
         __syncthreads();
         const int depth = T.pad;
+        for (int64_t blk = blockIdx.x; blk < n_blocks; blk += gridDim.x) {
+        const int64_t r0 = blk * rows_per_block;
+        const int64_t r1 = r0 + rows_per_block < n ? r0 + rows_per_block : n;
         for (int64_t rw = r0 + (int64_t)wave * 64; rw < r1; rw += 256) {   // rw: the wave's first row
             const int64_t rend = rw + 64 < r1 ? rw + 64 : r1;
             const uint64_t bit0 = (uint64_t)rw * stride_bits, bit1 = (uint64_t)rend * stride_bits;
@@ -591,11 +688,14 @@ __global__ __launch_bounds__(256) void predict_staged_kernel(const char *ws, con
                     node = (c.x & 0x7fffffffu) + (go_left ? 0u : 1u);
                 }
                 if (leaf_out) leaf_out[r] = (int32_t)node;
-                else margin[r] = (float)((double)margin[r] + eta * lweight[node]);
+                else margin[r] = (float)((double)margin_src[r] + eta * lweight[node]);
+                if (node_rows) atomicAdd(&lcount[node], 1u);
             }
             __builtin_amdgcn_wave_barrier();   // the window is refilled only after every lane has left it
         }
+        }
     }
+    if (node_rows) flush_counts(lcount, max_nodes, node_rows);
 }
 
 // The same walk for 8-bit symbols (rows of at most 16 bytes, any byte alignment): a node is staged
@@ -609,7 +709,7 @@ __global__ __launch_bounds__(256) void predict_staged_kernel(const char *ws, con
 // node_rows (may be NULL; one tree only): the rows that end in each node are counted, per workgroup in LDS and
 // then into node_rows[node * kNodeRowsStride] (one counter per 128-byte line: atomics on one line take turns).
 // margin_src: where a row's margin is read from (margin itself, or with one tree another array: out = src + step).
-template <bool MISS>
+template <bool MISS, int Q>
 __global__ __launch_bounds__(256) void predict_b8_kernel(const char *ws, const DevTree *trees, int n_trees,
                                                          const uint32_t *packed, int64_t n_words, uint32_t missing,
                                                          int64_t n, int F, double eta, float *margin,
@@ -624,7 +724,7 @@ __global__ __launch_bounds__(256) void predict_b8_kernel(const char *ws, const D
     for (int t = 0; t < n_trees; ++t) {
         const DevTree T = trees[t];
         __syncthreads();
-        for (int i = threadIdx.x; i < T.n_nodes; i += 256) {
+        for (int i = threadIdx.x; i < T.n_nodes && i < max_nodes; i += 256) {
             const int32_t f = ((const int32_t *)(ws + T.feature))[i];
             uint2 c;
             if (f < 0) {
@@ -645,11 +745,11 @@ __global__ __launch_bounds__(256) void predict_b8_kernel(const char *ws, const D
         for (int64_t blk = blockIdx.x; blk < n_blocks; blk += gridDim.x) {
         const int64_t r0 = blk * rows_per_block;
         const int64_t r1 = r0 + rows_per_block < n ? r0 + rows_per_block : n;
-        for (int64_t rb = r0 + threadIdx.x; rb < r1; rb += 256 * kPredRows) {
-            uint32_t W[kPredRows][4];
-            float m[kPredRows];
+        for (int64_t rb = r0 + threadIdx.x; rb < r1; rb += 256 * Q) {
+            uint32_t W[Q][4];
+            float m[Q];
 #pragma unroll
-            for (int q = 0; q < kPredRows; ++q) {
+            for (int q = 0; q < Q; ++q) {
                 const int64_t r = rb + 256 * q < r1 ? rb + 256 * q : r1 - 1;   // past the end: the last row again
                 const uint64_t byte0 = (uint64_t)r * (uint64_t)F;
                 const int64_t w0 = (int64_t)(byte0 >> 2);
@@ -665,12 +765,12 @@ __global__ __launch_bounds__(256) void predict_b8_kernel(const char *ws, const D
                 for (int k = 0; k < 4; ++k) W[q][k] = __builtin_amdgcn_alignbyte(w[k + 1], w[k], a);
                 m[q] = leaf_out ? 0.f : margin_src[r];
             }
-            uint32_t node[kPredRows];
+            uint32_t node[Q];
 #pragma unroll
-            for (int q = 0; q < kPredRows; ++q) node[q] = 0;
+            for (int q = 0; q < Q; ++q) node[q] = 0;
             for (int step = 0; step < depth; ++step) {
 #pragma unroll
-                for (int q = 0; q < kPredRows; ++q) {
+                for (int q = 0; q < Q; ++q) {
                     const uint2 c = cnodes[node[q]];
                     const uint32_t lo = __builtin_amdgcn_perm(W[q][1], W[q][0], c.y);
                     const uint32_t hi = __builtin_amdgcn_perm(W[q][3], W[q][2], c.y);
@@ -681,7 +781,7 @@ __global__ __launch_bounds__(256) void predict_b8_kernel(const char *ws, const D
                 }
             }
 #pragma unroll
-            for (int q = 0; q < kPredRows; ++q) {
+            for (int q = 0; q < Q; ++q) {
                 const int64_t r = rb + 256 * q;
                 if (r < r1) {
                     if (leaf_out) leaf_out[r] = (int32_t)node[q];
@@ -692,13 +792,7 @@ __global__ __launch_bounds__(256) void predict_b8_kernel(const char *ws, const D
         }
         }
     }
-    if (node_rows) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < max_nodes; i += 256) {
-            const uint32_t c = lcount[i];
-            if (c) atomicAdd(&node_rows[(size_t)i * kNodeRowsStride], c);
-        }
-    }
+    if (node_rows) flush_counts(lcount, max_nodes, node_rows);
 }
 
 // Final row order and leaf ids: every position of [0, n) lies in exactly one
@@ -1011,10 +1105,44 @@ hipError_t gbt_launch_predict_raw_batched(hipStream_t s, const gbt_batch_node *n
     }
 }
 
-// Can the walk also count the rows per node, or read the margins from another array?  Only the byte-symbol kernel does.
+// LDS of a walk over packed symbols with compact nodes: 16 bytes per node, a row counter per node if it counts, the rows'
+// windows of the staged form.
+namespace {
+enum { WALK_B8, WALK_WINDOW, WALK_STAGED, WALK_GATHER };
+int staged_wave_words(int bits, int F) { return (int)((64 * (int64_t)F * bits + 31) / 32) + 2; }
+// Rows staged through LDS, a wave's 64 at a time, where a row is wider than 32 bytes: a narrower one lies in one cache
+// line that the gathers of its levels all hit (1M x 28 bytes measured 0.107 ms gathered against 0.121 ms staged; 10M x 57
+// bytes 0.39 against 0.30 ms).
+int walk_form(int bits, int F, int max_nodes, bool counts, size_t *lds) {
+    const int64_t row_bits = (int64_t)F * bits;
+    *lds = (size_t)max_nodes * (16 + (counts ? 4 : 0));
+    if (row_bits <= 128) return bits == 8 && F <= 16 && max_nodes <= (1 << 20) ? WALK_B8 : WALK_WINDOW;   // (node ids of 20 bits)
+    if (row_bits > 256 && row_bits <= kStagedRowBits) {
+        const size_t staged = *lds + (size_t)4 * staged_wave_words(bits, F) * 4;
+        if (staged <= kWalkLds) {
+            *lds = staged;
+            return WALK_STAGED;
+        }
+    }
+    return WALK_GATHER;
+}
+template <typename K, typename... A>
+hipError_t launch_walk(K kernel, int64_t grid, size_t lds, hipStream_t s, A... args) {
+    GbtLdsGuard lds_guard(lds);
+    if (lds_guard.needed) {
+        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    kernel<<<(unsigned)grid, 256, lds, s>>>(args...);
+    return hipGetLastError();
+}
+}  // namespace
+
+// Can the walk also count the rows per node, and read the margins from another array?  The forms that keep the tree in LDS do.
 bool gbt_predict_counts_ok(bool packed, int bits, int F, int max_nodes, bool compact_ok) {
-    return packed && compact_ok && bits == 8 && F <= 16 && max_nodes <= (1 << 20) &&
-           (size_t)max_nodes * (sizeof(LdsNode) + 4) <= 96u * 1024u;
+    (void)bits;
+    (void)F;
+    return packed && compact_ok && (size_t)max_nodes * 20 <= kWalkLds;
 }
 
 hipError_t gbt_launch_predict(hipStream_t s, const char *ws, const DevTree *trees, int n_trees,
@@ -1025,74 +1153,47 @@ hipError_t gbt_launch_predict(hipStream_t s, const char *ws, const DevTree *tree
     if (margin_src == margin) margin_src = nullptr;
     if ((node_rows || margin_src) && !(n_trees == 1 && gbt_predict_counts_ok(packed != nullptr, bits, F, max_nodes, compact_ok)))
         return hipErrorInvalidValue;   // (the caller asks gbt_predict_counts_ok first)
-    const size_t lds = (size_t)max_nodes * (sizeof(LdsNode) + (node_rows ? 4 : 0));
-    static_assert(sizeof(LdsNode) >= 16, "the register-window kernel stages 16 bytes per node");
-    if (lds <= 96u * 1024u) {
-        GbtLdsGuard lds_guard(lds);
-        if (lds_guard.needed) {
-            hipError_t e = hipFuncSetAttribute((const void *)predict_lds_kernel,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-        }
-        const int rows_per_block = 256 * 16;
-        const int64_t grid = (n + rows_per_block - 1) / rows_per_block;
-        if (packed && compact_ok && (int64_t)F * bits <= 128) {
-            GbtLdsGuard lds_guard_w(lds);
-            if (lds_guard_w.needed) {
-                hipError_t e = hipFuncSetAttribute((const void *)predict_window_kernel,
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                if (e != hipSuccess) return e;
+    size_t lds = 0;
+    const int form = walk_form(bits, F, max_nodes, node_rows != nullptr, &lds);
+    if (packed && compact_ok && lds <= kWalkLds) {
+        // A workgroup stages the tree and walks a block of rows.  Where blocks of 4096 rows would leave compute units
+        // without a workgroup they are shorter, down to one row per thread (1M x 28 bytes: 37 us with 245 workgroups, 9 us
+        // with 977 and four rows per thread side by side; 50,000 x 22 bytes 36 -> 7 us).
+        const bool few = n <= (int64_t)256 * 1024;
+        const int rows_per_block = few ? 256 : n < (int64_t)4096 * 1024 ? 1024 : 4096;
+        int64_t grid = (n + rows_per_block - 1) / rows_per_block;
+        // counting: few enough workgroups that their counts meet rarely in HBM, each taking many blocks
+        if (node_rows && grid > 2048) grid = 2048;
+        const int64_t n_words = (n * (int64_t)F * bits + 31) / 32 + 1;
+        const float *src = margin_src ? margin_src : margin;
+        switch (form) {
+            case WALK_B8: {
+                const bool miss = missing < 256u;
+                auto k = miss ? (few ? predict_b8_kernel<true, 1> : predict_b8_kernel<true, kPredRows>)
+                              : (few ? predict_b8_kernel<false, 1> : predict_b8_kernel<false, kPredRows>);
+                return launch_walk(k, grid, lds, s, ws, trees, n_trees, packed, n_words, missing, n, F, eta, margin,
+                                   rows_per_block, max_nodes, leaf_out, node_rows, src);
             }
-            const int64_t n_words = (n * (int64_t)F * bits + 31) / 32 + 1;
-            if (bits == 8 && F <= 16 && max_nodes <= (1 << 20)) {   // node ids fit the 20-bit field
-                GbtLdsGuard lds_guard_b(lds);
-                if (lds_guard_b.needed) {
-                    hipError_t e = hipFuncSetAttribute((const void *)predict_b8_kernel<true>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                    if (e == hipSuccess)
-                        e = hipFuncSetAttribute((const void *)predict_b8_kernel<false>,
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                    if (e != hipSuccess) return e;
-                }
-                // counting: few enough workgroups that their counts meet rarely in HBM, each taking many blocks
-                const int64_t grid_b = node_rows && grid > 2048 ? 2048 : grid;
-                if (missing < 256u)
-                    predict_b8_kernel<true><<<(unsigned)grid_b, 256, lds, s>>>(ws, trees, n_trees, packed, n_words, missing,
-                                                                              n, F, eta, margin, rows_per_block, max_nodes,
-                                                                              leaf_out, node_rows, margin_src ? margin_src : margin);
-                else
-                    predict_b8_kernel<false><<<(unsigned)grid_b, 256, lds, s>>>(ws, trees, n_trees, packed, n_words, missing,
-                                                                               n, F, eta, margin, rows_per_block, max_nodes,
-                                                                               leaf_out, node_rows, margin_src ? margin_src : margin);
-                return hipGetLastError();
+            case WALK_WINDOW: {
+                auto k = few ? predict_window_kernel<1> : predict_window_kernel<kPredRows>;
+                return launch_walk(k, grid, lds, s, ws, trees, n_trees, packed, n_words, bits, missing, n, F, eta, margin,
+                                   rows_per_block, max_nodes, leaf_out, node_rows, src);
             }
-            predict_window_kernel<<<(unsigned)grid, 256, lds, s>>>(ws, trees, n_trees, packed, n_words, bits, missing,
-                                                                   n, F, eta, margin, rows_per_block, max_nodes, leaf_out);
-            return hipGetLastError();
-        }
-        // rows staged through LDS, a wave's 64 at a time (a row of up to 32 bytes lies in one cache line that the
-        // gathers of its levels all hit: 1M x 28 bytes measured 0.107 ms gathered against 0.121 ms staged; 10M x 57
-        // bytes 0.39 against 0.30 ms)
-        if (packed && compact_ok && (int64_t)F * bits > 256 && (int64_t)F * bits <= kStagedRowBits) {
-            const int wave_words = (int)((64 * (int64_t)F * bits + 31) / 32) + 2;
-            const size_t lds_s = lds + (size_t)4 * wave_words * 4;
-            if (lds_s <= 96u * 1024u) {
-                GbtLdsGuard lds_guard_s(lds_s);
-                if (lds_guard_s.needed) {
-                    hipError_t e = hipFuncSetAttribute((const void *)predict_staged_kernel,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_s);
-                    if (e != hipSuccess) return e;
-                }
-                const int64_t n_words = (n * (int64_t)F * bits + 31) / 32 + 1;
-                predict_staged_kernel<<<(unsigned)grid, 256, lds_s, s>>>(ws, trees, n_trees, packed, n_words, bits, missing, n, F,
-                                                                         eta, margin, rows_per_block, max_nodes, leaf_out,
-                                                                         wave_words);
-                return hipGetLastError();
+            case WALK_STAGED:
+                return launch_walk(predict_staged_kernel, grid, lds, s, ws, trees, n_trees, packed, n_words, bits, missing, n, F,
+                                   eta, margin, rows_per_block, max_nodes, leaf_out, staged_wave_words(bits, F), node_rows, src);
+            default: {
+                auto k = few ? predict_gather_kernel<1> : predict_gather_kernel<kPredRows>;
+                return launch_walk(k, grid, lds, s, ws, trees, n_trees, packed, bits, missing, n, F, eta, margin,
+                                   rows_per_block, max_nodes, leaf_out, node_rows, src);
             }
         }
-        predict_lds_kernel<<<(unsigned)grid, 256, lds, s>>>(ws, trees, n_trees, packed, bits, missing, X, n, F, eta,
-                                                            margin, rows_per_block, leaf_out);
-        return hipGetLastError();
+    }
+    const size_t lds_full = (size_t)max_nodes * sizeof(LdsNode);
+    if (lds_full <= kWalkLds) {
+        const int rows_per_block = n <= (int64_t)256 * 1024 ? 256 : n < (int64_t)4096 * 1024 ? 1024 : 4096;   // (as above)
+        return launch_walk(predict_lds_kernel, (n + rows_per_block - 1) / rows_per_block, lds_full, s, ws, trees, n_trees,
+                           packed, bits, missing, X, n, F, eta, margin, rows_per_block, leaf_out);
     }
     predict_kernel<<<grid_for(n, kBlock, 1 << 16), kBlock, 0, s>>>(ws, trees, n_trees, packed, bits,
                                                                     missing, X, n, F, eta, margin, leaf_out);

@@ -53,8 +53,12 @@ __device__ inline uint32_t load_symbol(const uint32_t *packed, uint64_t bp, int 
 __global__ __launch_bounds__(kBlock) void part_flag_kernel(
     const uint32_t *__restrict__ packed, int bits, int64_t stride_bits, int64_t n, uint32_t missing,
     const uint32_t *__restrict__ src, const PartJob *__restrict__ jobs, int n_jobs,
-    uint64_t *__restrict__ masks, uint32_t *__restrict__ tile_left) {
+    uint64_t *__restrict__ masks, uint32_t *__restrict__ tile_left, const uint32_t *__restrict__ counts_dev) {
     const uint32_t tile = blockIdx.x;
+    if (counts_dev) {
+        if (tile >= counts_dev[1]) return;
+        n_jobs = (int)counts_dev[0];
+    }
     const PartJob job = jobs[find_job(jobs, n_jobs, tile)];
     const uint32_t t_in_seg = tile - job.tile_begin;
     const uint32_t base = t_in_seg * kTile;   // first row of the tile inside the segment
@@ -85,7 +89,9 @@ __global__ __launch_bounds__(kBlock) void part_flag_kernel(
 
 __global__ __launch_bounds__(kBlock) void part_scan_kernel(const PartJob *__restrict__ jobs,
                                                            uint32_t *__restrict__ tile_left,
-                                                           uint32_t *__restrict__ n_left_out) {
+                                                           uint32_t *__restrict__ n_left_out,
+                                                           const uint32_t *__restrict__ counts_dev) {
+    if (counts_dev && blockIdx.x >= counts_dev[0]) return;
     const PartJob job = jobs[blockIdx.x];
     __shared__ uint32_t wtot[kBlock / 64];
     __shared__ uint32_t carry_s;
@@ -115,8 +121,12 @@ __global__ __launch_bounds__(kBlock) void part_scan_kernel(const PartJob *__rest
 __global__ __launch_bounds__(kBlock) void part_scatter_kernel(
     const uint32_t *__restrict__ src, uint32_t *__restrict__ dst, const PartJob *__restrict__ jobs,
     int n_jobs, const uint64_t *__restrict__ masks, const uint32_t *__restrict__ tile_left_off,
-    const uint32_t *__restrict__ n_left) {
+    const uint32_t *__restrict__ n_left, const uint32_t *__restrict__ counts_dev) {
     const uint32_t tile = blockIdx.x;
+    if (counts_dev) {
+        if (tile >= counts_dev[1]) return;
+        n_jobs = (int)counts_dev[0];
+    }
     const int ji = find_job(jobs, n_jobs, tile);
     const PartJob job = jobs[ji];
     const uint32_t base = (tile - job.tile_begin) * kTile;
@@ -327,11 +337,15 @@ __global__ __launch_bounds__(kFBlock) void part_fused_kernel(
     const uint32_t *__restrict__ src_sym, int64_t src_stride_bits, int64_t src_words, bool aligned_src,
     uint32_t *__restrict__ dst_sym, int SW, int row_bits, int bits, uint32_t missing,
     const int2 *__restrict__ src_gq, int2 *__restrict__ dst_gq, const PartJob *__restrict__ jobs, int n_jobs,
-    unsigned long long *__restrict__ cursor) {
+    unsigned long long *__restrict__ cursor, const uint32_t *__restrict__ counts_dev) {
     __shared__ uint32_t left_base_s, right_base_s;
     __shared__ uint64_t words[kFWords];
     __shared__ uint32_t lefts_before[kFWords];
     const uint32_t tile = blockIdx.x;
+    if (counts_dev) {
+        if (tile >= counts_dev[1]) return;
+        n_jobs = (int)counts_dev[0];
+    }
     const int ji = find_job(jobs, n_jobs, tile);
     const PartJob job = jobs[ji];
     const uint32_t base = (tile - job.tile_begin) * kFTile;
@@ -442,12 +456,16 @@ __global__ __launch_bounds__(kFBlock) void part_staged_kernel(
     const uint32_t *__restrict__ src_sym, int64_t src_stride_bits, int64_t src_words,
     uint32_t *__restrict__ dst_sym, int SW, int row_bits, int bits, uint32_t missing,
     const int2 *__restrict__ src_gq, int2 *__restrict__ dst_gq, const PartJob *__restrict__ jobs, int n_jobs,
-    int tile_cap, unsigned long long *__restrict__ cursor) {
+    int tile_cap, unsigned long long *__restrict__ cursor, const uint32_t *__restrict__ counts_dev) {
     extern __shared__ uint32_t stage[];                 // the tile's words, then one destination per row
     __shared__ uint32_t left_base_s, right_base_s;
     __shared__ uint64_t words[kFWords];
     __shared__ uint32_t lefts_before[kFWords];
     const uint32_t tile = blockIdx.x;
+    if (counts_dev) {
+        if (tile >= counts_dev[1]) return;
+        n_jobs = (int)counts_dev[0];
+    }
     const int ji = find_job(jobs, n_jobs, tile);
     const PartJob job = jobs[ji];
     const uint32_t base = (tile - job.tile_begin) * (uint32_t)tile_cap;
@@ -539,23 +557,24 @@ __global__ __launch_bounds__(kFBlock) void part_staged_kernel(
 hipError_t gbt_launch_partition(hipStream_t s, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n,
                                 uint32_t missing, const uint32_t *src, uint32_t *dst,
                                 const PartJob *jobs, int n_jobs, int total_tiles, uint64_t *masks,
-                                uint32_t *tile_left, uint32_t *n_left_out) {
+                                uint32_t *tile_left, uint32_t *n_left_out, const uint32_t *counts_dev) {
     if (n_jobs <= 0 || total_tiles <= 0) return hipSuccess;
     part_flag_kernel<<<total_tiles, kBlock, 0, s>>>(packed, bits, stride_bits, n, missing, src, jobs, n_jobs, masks,
-                                                    tile_left);
-    part_scan_kernel<<<n_jobs, kBlock, 0, s>>>(jobs, tile_left, n_left_out);
-    part_scatter_kernel<<<total_tiles, kBlock, 0, s>>>(src, dst, jobs, n_jobs, masks, tile_left, n_left_out);
+                                                    tile_left, counts_dev);
+    part_scan_kernel<<<n_jobs, kBlock, 0, s>>>(jobs, tile_left, n_left_out, counts_dev);
+    part_scatter_kernel<<<total_tiles, kBlock, 0, s>>>(src, dst, jobs, n_jobs, masks, tile_left, n_left_out, counts_dev);
     return hipGetLastError();
 }
 
 hipError_t gbt_launch_partition_records(hipStream_t s, const GbtRows &src, const GbtRows &dst, int bits, int row_bits,
                                         int64_t n, uint32_t missing, int what, const PartJob *jobs,
                                         int n_jobs, int total_tiles, uint64_t *masks, uint32_t *tile_left,
-                                        uint32_t *n_left_out) {
+                                        uint32_t *n_left_out, const uint32_t *counts_dev) {
     if (n_jobs <= 0 || total_tiles <= 0) return hipSuccess;
+    if (counts_dev && what != GBT_PART_COUNT) return hipErrorInvalidValue;   // (only the count is planned on the device)
     part_flag_kernel<<<total_tiles, kBlock, 0, s>>>(src.sym, bits, src.stride_bits, n, missing, nullptr, jobs, n_jobs,
-                                                    masks, tile_left);
-    part_scan_kernel<<<n_jobs, kBlock, 0, s>>>(jobs, tile_left, n_left_out);
+                                                    masks, tile_left, counts_dev);
+    part_scan_kernel<<<n_jobs, kBlock, 0, s>>>(jobs, tile_left, n_left_out, counts_dev);
     if (what == GBT_PART_COUNT) return hipGetLastError();
     if (what == GBT_PART_IDS) {
         part_move_ids_kernel<<<total_tiles, kBlock, 0, s>>>(src.id, dst.id_rw, jobs, n_jobs, masks, tile_left,
@@ -695,9 +714,9 @@ int gbt_partition_fused_tile(const GbtRows &dst) {
 
 hipError_t gbt_launch_partition_fused(hipStream_t s, const GbtRows &src, const GbtRows &dst, int bits, int row_bits,
                                       uint32_t missing, const PartJob *jobs, int n_jobs, int total_tiles,
-                                      unsigned long long *cursor) {
+                                      unsigned long long *cursor, const uint32_t *counts_dev) {
     if (n_jobs <= 0 || total_tiles <= 0) return hipSuccess;
-    hipError_t e = gbt_launch_fill_u64(s, (uint64_t *)cursor, 0, n_jobs);
+    hipError_t e = counts_dev ? hipSuccess : gbt_launch_fill_u64(s, (uint64_t *)cursor, 0, n_jobs);
     if (e != hipSuccess) return e;
     const int SW = (int)(dst.stride_bits >> 5);
     const bool aligned_src = src.stride_bits == 128 && ((uintptr_t)src.sym & 15u) == 0;
@@ -705,7 +724,7 @@ hipError_t gbt_launch_partition_fused(hipStream_t s, const GbtRows &src, const G
         part_fused_kernel<<<total_tiles, kFBlock, 0, s>>>(src.sym, src.stride_bits, src.n_words, aligned_src,
                                                                 dst.sym_rw, SW, row_bits, bits, missing,
                                                                 (const int2 *)src.gq, (int2 *)dst.gq_rw, jobs, n_jobs,
-                                                                cursor);
+                                                                cursor, counts_dev);
     else {
         const int cap = staged_tile_rows(dst.stride_bits);
         const size_t lds = ((((size_t)cap * (size_t)src.stride_bits + 31) >> 5) + 2 + (size_t)cap) * 4;
@@ -717,7 +736,7 @@ hipError_t gbt_launch_partition_fused(hipStream_t s, const GbtRows &src, const G
         }
         part_staged_kernel<<<total_tiles, kFBlock, lds, s>>>(src.sym, src.stride_bits, src.n_words, dst.sym_rw, SW,
                                                              row_bits, bits, missing, (const int2 *)src.gq,
-                                                             (int2 *)dst.gq_rw, jobs, n_jobs, cap, cursor);
+                                                             (int2 *)dst.gq_rw, jobs, n_jobs, cap, cursor, counts_dev);
     }
     return hipGetLastError();
 }

@@ -165,8 +165,10 @@ __global__ __launch_bounds__(BLOCK) void sparse_hist_kernel(const uint32_t *__re
                                                             const uint32_t *__restrict__ ent_words,
                                                             const int2 *__restrict__ gq,
                                                             int64_t *__restrict__ pool,
-                                                            const HistJob *__restrict__ jobs) {
+                                                            const HistJob *__restrict__ jobs,
+                                                            const uint32_t *__restrict__ n_jobs_dev) {
     extern __shared__ unsigned long long lds[];
+    if (n_jobs_dev && blockIdx.x >= *n_jobs_dev) return;
     const HistJob job = jobs[blockIdx.x];
     const uint32_t g0 = job.f0, glen = job.ft;
     int64_t *out = pool + job.hist_off + 2 * (int64_t)g0;
@@ -231,8 +233,10 @@ __global__ __launch_bounds__(BLOCK) void sparse_hist32_kernel(const uint32_t *__
                                                               const uint32_t *__restrict__ ent,
                                                               const int2 *__restrict__ gq,
                                                               int64_t *__restrict__ pool,
-                                                              const HistJob *__restrict__ jobs) {
+                                                              const HistJob *__restrict__ jobs,
+                                                            const uint32_t *__restrict__ n_jobs_dev) {
     extern __shared__ unsigned long long lds[];
+    if (n_jobs_dev && blockIdx.x >= *n_jobs_dev) return;
     const HistJob job = jobs[blockIdx.x];
     const uint32_t g0 = job.f0, glen = job.ft;
     int64_t *out = pool + job.hist_off + 2 * (int64_t)g0;
@@ -341,7 +345,12 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
                                                                E *__restrict__ dst_ent,
                                                                int2 *__restrict__ dst_gq, uint32_t B, int move,
                                                                const PartJob *__restrict__ jobs, int n_jobs,
-                                                               unsigned long long *__restrict__ cursor) {
+                                                               unsigned long long *__restrict__ cursor,
+                                                               const uint32_t *__restrict__ counts_dev) {
+    if (counts_dev) {
+        if (blockIdx.x >= counts_dev[1]) return;
+        n_jobs = (int)counts_dev[0];
+    }
     __shared__ uint32_t stage_w[kSpStage / 2];
     __shared__ uint32_t out_w[kSpStage / 2 + 4];
     __shared__ uint32_t grp_rows[2][kSpGroups];   // [side][group]: rows, then their exclusive offsets
@@ -625,7 +634,8 @@ int gbt_sparse_hist_tile(const gbt_ctx *ctx, int64_t bins) {
 
 // tiled: the jobs cover parts of the id range [0, bins)
 hipError_t gbt_launch_sparse_hist(gbt_ctx *ctx, const uint32_t *rowptr, const void *ent, int ent_bytes, const int32_t *gq,
-                                  int64_t *pool, const HistJob *jobs, int n_jobs, int max_glen, bool tiled) {
+                                  int64_t *pool, const HistJob *jobs, int n_jobs, int max_glen, bool tiled,
+                                  const uint32_t *n_jobs_dev) {
     if (n_jobs <= 0) return hipSuccess;
     const size_t lds = (size_t)max_glen * 8;
     const bool big = lds > 64u * 1024u;   // one workgroup per compute unit: make it a large one
@@ -639,10 +649,10 @@ hipError_t gbt_launch_sparse_hist(gbt_ctx *ctx, const uint32_t *rowptr, const vo
         }
         const uint32_t *e32 = (const uint32_t *)ent;
         const int2 *g2 = (const int2 *)gq;
-        if (big && tiled) sparse_hist32_kernel<1024, true><<<n_jobs, 1024, lds, ctx->stream>>>(rowptr, e32, g2, pool, jobs);
-        else if (big) sparse_hist32_kernel<1024, false><<<n_jobs, 1024, lds, ctx->stream>>>(rowptr, e32, g2, pool, jobs);
-        else if (tiled) sparse_hist32_kernel<512, true><<<n_jobs, 512, lds, ctx->stream>>>(rowptr, e32, g2, pool, jobs);
-        else sparse_hist32_kernel<512, false><<<n_jobs, 512, lds, ctx->stream>>>(rowptr, e32, g2, pool, jobs);
+        if (big && tiled) sparse_hist32_kernel<1024, true><<<n_jobs, 1024, lds, ctx->stream>>>(rowptr, e32, g2, pool, jobs, n_jobs_dev);
+        else if (big) sparse_hist32_kernel<1024, false><<<n_jobs, 1024, lds, ctx->stream>>>(rowptr, e32, g2, pool, jobs, n_jobs_dev);
+        else if (tiled) sparse_hist32_kernel<512, true><<<n_jobs, 512, lds, ctx->stream>>>(rowptr, e32, g2, pool, jobs, n_jobs_dev);
+        else sparse_hist32_kernel<512, false><<<n_jobs, 512, lds, ctx->stream>>>(rowptr, e32, g2, pool, jobs, n_jobs_dev);
         return hipGetLastError();
     }
     const void *fn = big ? (tiled ? (const void *)sparse_hist_kernel<1024, true> : (const void *)sparse_hist_kernel<1024, false>)
@@ -654,10 +664,10 @@ hipError_t gbt_launch_sparse_hist(gbt_ctx *ctx, const uint32_t *rowptr, const vo
     }
     const uint32_t *words = (const uint32_t *)ent;
     const int2 *gq2 = (const int2 *)gq;
-    if (big && tiled) sparse_hist_kernel<1024, true><<<n_jobs, 1024, lds, ctx->stream>>>(rowptr, words, gq2, pool, jobs);
-    else if (big) sparse_hist_kernel<1024, false><<<n_jobs, 1024, lds, ctx->stream>>>(rowptr, words, gq2, pool, jobs);
-    else if (tiled) sparse_hist_kernel<512, true><<<n_jobs, 512, lds, ctx->stream>>>(rowptr, words, gq2, pool, jobs);
-    else sparse_hist_kernel<512, false><<<n_jobs, 512, lds, ctx->stream>>>(rowptr, words, gq2, pool, jobs);
+    if (big && tiled) sparse_hist_kernel<1024, true><<<n_jobs, 1024, lds, ctx->stream>>>(rowptr, words, gq2, pool, jobs, n_jobs_dev);
+    else if (big) sparse_hist_kernel<1024, false><<<n_jobs, 1024, lds, ctx->stream>>>(rowptr, words, gq2, pool, jobs, n_jobs_dev);
+    else if (tiled) sparse_hist_kernel<512, true><<<n_jobs, 512, lds, ctx->stream>>>(rowptr, words, gq2, pool, jobs, n_jobs_dev);
+    else sparse_hist_kernel<512, false><<<n_jobs, 512, lds, ctx->stream>>>(rowptr, words, gq2, pool, jobs, n_jobs_dev);
     return hipGetLastError();
 }
 
@@ -666,18 +676,18 @@ int gbt_sparse_part_tile() { return kSpTile; }
 hipError_t gbt_launch_sparse_partition(hipStream_t s, const uint32_t *src_rowptr, const void *src_ent, int ent_bytes,
                                        const int32_t *src_gq, uint32_t *dst_rowptr, void *dst_ent,
                                        int32_t *dst_gq, int B, bool move, const PartJob *jobs, int n_jobs,
-                                       int n_tiles, unsigned long long *cursor) {
+                                       int n_tiles, unsigned long long *cursor, const uint32_t *counts_dev) {
     if (n_jobs <= 0 || n_tiles <= 0) return hipSuccess;
-    hipError_t e = gbt_launch_fill_u64(s, (uint64_t *)cursor, 0, 2 * (int64_t)n_jobs);
+    hipError_t e = counts_dev ? hipSuccess : gbt_launch_fill_u64(s, (uint64_t *)cursor, 0, 2 * (int64_t)n_jobs);
     if (e != hipSuccess) return e;
     if (ent_bytes == 2)
         sparse_part_kernel<uint16_t><<<n_tiles, kSpBlock, 0, s>>>(src_rowptr, (const uint16_t *)src_ent, (const int2 *)src_gq,
                                                                   dst_rowptr, (uint16_t *)dst_ent, (int2 *)dst_gq, (uint32_t)B,
-                                                                  move ? 1 : 0, jobs, n_jobs, cursor);
+                                                                  move ? 1 : 0, jobs, n_jobs, cursor, counts_dev);
     else
         sparse_part_kernel<uint32_t><<<n_tiles, kSpBlock, 0, s>>>(src_rowptr, (const uint32_t *)src_ent, (const int2 *)src_gq,
                                                                   dst_rowptr, (uint32_t *)dst_ent, (int2 *)dst_gq, (uint32_t)B,
-                                                                  move ? 1 : 0, jobs, n_jobs, cursor);
+                                                                  move ? 1 : 0, jobs, n_jobs, cursor, counts_dev);
     return hipGetLastError();
 }
 

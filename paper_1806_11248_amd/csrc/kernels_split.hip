@@ -50,7 +50,8 @@ __device__ __forceinline__ double gain_term(double G, double denom) { return den
 __global__ __launch_bounds__(kEvalBlock) void eval_kernel(
     int64_t *__restrict__ pool, const EvalNode *__restrict__ nodes, const int32_t *__restrict__ nb,
     int F, int B, int f_per_chunk, double inv_sg, double inv_sh, double lambda, double mcw,
-    gbt_split *__restrict__ out, EvalTail tail) {
+    gbt_split *__restrict__ out, EvalTail tail, const uint32_t *__restrict__ n_nodes_dev) {
+    if (n_nodes_dev && blockIdx.x >= *n_nodes_dev) return;   // (the whole workgroup)
     if (blockIdx.x == 0 && blockIdx.y == 0) {   // the words handed back with the records (see gbt_launch_eval)
         for (int i = threadIdx.x; i < tail.n; i += kEvalBlock) {
             tail.dst[i] = tail.src[(size_t)i * tail.src_stride];
@@ -267,10 +268,10 @@ int gbt_eval_chunks(int F, int n_nodes, size_t record_budget_bytes) {
 
 hipError_t gbt_launch_eval(hipStream_t s, int64_t *hist_pool, const EvalNode *nodes, int n_nodes,
                            const int32_t *nb, int F, int B, int n_chunks, double inv_sg, double inv_sh,
-                           double lambda, double mcw, gbt_split *out, EvalTail tail) {
+                           double lambda, double mcw, gbt_split *out, EvalTail tail, const uint32_t *n_nodes_dev) {
     if (n_nodes <= 0) return hipSuccess;   // (the callers have no tail without nodes)
     const int f_per_chunk = (F + n_chunks - 1) / n_chunks;
     dim3 grid((unsigned)n_nodes, (unsigned)n_chunks);
-    eval_kernel<<<grid, kEvalBlock, 0, s>>>(hist_pool, nodes, nb, F, B, f_per_chunk, inv_sg, inv_sh, lambda, mcw, out, tail);
+    eval_kernel<<<grid, kEvalBlock, 0, s>>>(hist_pool, nodes, nb, F, B, f_per_chunk, inv_sg, inv_sh, lambda, mcw, out, tail, n_nodes_dev);
     return hipGetLastError();
 }

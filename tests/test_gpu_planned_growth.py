@@ -1,0 +1,123 @@
+"""Depth-wise growth planned on the device (one wait per tree) against the same growth planned on the host: every array of
+the tree, the margins, each row's leaf and the row order have to be the same (-m gpu).  The shapes sit where the planned
+form can go wrong: trees that end early or never split, levels past the depth from which the host waits for a level's
+splits, more nodes than one workgroup's prefix sum takes in a step, one row, trees walked from LDS and not."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+TREE_KEYS = ("feature", "bin", "default_left", "left", "right", "n_rows", "threshold", "weight", "gain", "sumG", "sumH")
+
+
+def _context(planned):
+    import paper_1806_11248_amd as g
+    key = "GBT_TUNE_PLAN"
+    old = os.environ.pop(key, None)
+    os.environ[key] = "1" if planned else "0"
+    try:
+        return g.Context(0)
+    finally:
+        del os.environ[key]
+        if old is not None:
+            os.environ[key] = old
+
+
+@pytest.fixture(scope="module")
+def contexts():
+    pair = _context(True), _context(False)
+    yield pair
+    for c in pair:
+        c.close()
+
+
+# rows, columns, bins, missing share, depth, labels
+CASES = [
+    (10_000, 8, 16, 0.0, 3, "noise"),       # rows of one word
+    (1, 19, 256, 0.0, 4, "noise"),          # one row: no split
+    (63, 19, 256, 0.3, 6, "noise"),         # less than a wave
+    (4_097, 20, 200, 0.0, 1, "noise"),      # byte symbols; the root's children are the last level
+    (30_011, 28, 256, 0.0, 6, "noise"),     # byte symbols, rows that are moved
+    (30_011, 28, 256, 0.0, 6, "constant"),  # nothing to gain after the first rounding: the tree ends at once
+    (20_000, 19, 256, 0.2, 9, "step"),      # 9 bits; ends after one level of nine
+    (50_021, 19, 256, 0.1, 10, "noise"),    # the deepest tree walked without a wait
+    (60_000, 20, 64, 0.0, 12, "noise"),     # deeper: levels of more than 1024 nodes
+    (3_001, 50, 256, 0.8, 8, "noise"),      # rows that stay in place, ids partitioned
+    (5_000, 200, 64, 0.1, 5, "noise"),      # the same, wide
+    (20_000, 60, 128, 0.5, 11, "noise"),    # ... and deep
+]
+
+
+def _data(n, F, miss, labels):
+    gen = np.random.default_rng(11 * n + F)
+    X = gen.normal(0, 1, (n, F)).astype(np.float32)
+    if miss > 0:
+        X[gen.random(X.shape) < miss] = np.nan
+    if labels == "constant":
+        y = np.ones(n, np.float32)
+    elif labels == "step":
+        y = np.where(np.nan_to_num(X[:, 3], nan=-1.0) > 0, 3.0, -1.0).astype(np.float32)
+    else:
+        y = (np.nan_to_num(X[:, 0]) * 0.7 + gen.normal(0, 1, n)).astype(np.float32)
+    return torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+
+
+def _same_tree(a, b, what):
+    assert a["n_nodes"] == b["n_nodes"], what
+    for k in TREE_KEYS:
+        assert np.array_equal(a[k][:a["n_nodes"]], b[k][:b["n_nodes"]]), (what, k)
+
+
+@pytest.mark.parametrize("n,F,B,miss,depth,labels", CASES)
+def test_planned_growth_equals_growth_planned_on_the_host(contexts, n, F, B, miss, depth, labels):
+    import paper_1806_11248_amd as g
+    print(f"planned growth n={n} F={F} B={B} missing={miss} depth={depth} labels={labels}", flush=True)
+    X, y = _data(n, F, miss, labels)
+    params = g.make_params(max_depth=depth, max_bins=B, eta=0.3, objective="squared", min_child_weight=1.0)
+    cuts, nb, packed, bits, _, ms = contexts[0].quantise_packed(X, max_bins=B)
+    margin0 = torch.full((n,), 0.25, device="cuda")
+    gp = contexts[0].gradients("squared", margin0, y)
+    gp[:, 1] += torch.rand(n, device="cuda", generator=torch.Generator("cuda").manual_seed(1))   # (pairs of unequal h)
+    seen = []
+    for c in contexts:
+        rounds = []
+        margin = margin0.clone()
+        for _ in range(2):   # the second round's pairs follow from the first's tree
+            gpair = torch.empty((n, 2), device="cuda")
+            rounds.append(c.boost_round(packed, bits, n, F, ms, nb, cuts, y, margin, margin, gpair, params))
+        full = c.grow_tree(packed, bits, n, F, ms, nb, cuts, gp, params)
+        leaf_only = c.grow_tree(packed, bits, n, F, ms, nb, cuts, gp, params, want_rows=False)
+        bare = c.grow_tree(packed, bits, n, F, ms, nb, cuts, gp, params, want_rows=False, want_leaf=False)
+        torch.cuda.synchronize()
+        seen.append((rounds, margin, full, leaf_only, bare))
+    (ra, ma, fa, la, ba), (rb, mb, fb, lb, bb) = seen
+    for k in range(2):
+        _same_tree(ra[k], rb[k], f"round {k}")
+    assert torch.equal(ma, mb)
+    for what, a, b in (("full", fa, fb), ("leaf", la, lb), ("bare", ba, bb)):
+        _same_tree(a[0], b[0], what)
+        for k in (1, 2):
+            assert (a[k] is None) == (b[k] is None) and (a[k] is None or torch.equal(a[k], b[k])), (what, k)
+
+
+@pytest.mark.parametrize("n,F,B,miss,depth,labels", [c for c in CASES if c[3] > 0])
+def test_planned_sparse_growth_equals_growth_planned_on_the_host(contexts, n, F, B, miss, depth, labels):
+    import paper_1806_11248_amd as g
+    print(f"planned sparse growth n={n} F={F} B={B} missing={miss} depth={depth} labels={labels}", flush=True)
+    X, y = _data(n, F, miss, labels)
+    params = g.make_params(max_depth=depth, max_bins=B, eta=0.3, objective="squared")
+    cuts, nb, sym, _, ms = contexts[0].quantise(X, max_bins=B)
+    rowptr, ent, nnz = contexts[0].compress_sparse(sym, B, ms)
+    gp = contexts[0].gradients("squared", torch.zeros(n, device="cuda"), y)
+    seen = []
+    for c in contexts:
+        seen.append((c.grow_tree_sparse(rowptr, ent, n, nnz, F, nb, cuts, gp, params),
+                     c.grow_tree_sparse(rowptr, ent, n, nnz, F, nb, cuts, gp, params, want_leaf=False, want_rows=False)))
+        torch.cuda.synchronize()
+    for a, b in zip(*seen):
+        _same_tree(a[0], b[0], "sparse")
+        for k in (1, 2):
+            assert (a[k] is None) == (b[k] is None) and (a[k] is None or torch.equal(a[k], b[k])), k
