@@ -127,7 +127,7 @@ typedef struct gbt_tree {
  *   GBT_TUNE_HIST_LDS_KB        [64] 8..128: cap on a workgroup's LDS histogram (smaller feature tiles, more workgroups per CU); unset, a shape
  *                                    that needs two to four feature tiles takes twice the cap where that saves a tile
  *   GBT_TUNE_HIST_JOBS          [8] 1..64: histogram workgroups to aim for per compute unit and launch
- *   GBT_TUNE_HIST_MERGE_RATIO   [96] 1..100000: LDS additions a bin should receive per value a job merges into HBM (longer row pieces)
+ *   GBT_TUNE_HIST_MERGE_RATIO   [96] 1..100000: weight of the merges into HBM where a node's rows are cut into jobs (more: longer row pieces)
  *   GBT_TUNE_PLAN               [1] 0: depth-wise levels are planned on the host, with two waits each, also where the device plans them
  *   GBT_TUNE_LOSSGUIDE_BATCH    [16] 1..64: open leaves expanded per round of loss-guided growth
  *   GBT_TUNE_SPARSE_JOBS        [1] 1..64: sparse-row histogram workgroups per compute unit

@@ -88,47 +88,77 @@ bool plan_tiles(const gbt_ctx *ctx, int F, int B, int bits, HistPlan *p, int64_t
     return true;
 }
 
-// Appends the jobs of one node; rows_per_job > 0.
+// The jobs of one or several nodes; rows_per_job > 0.
 // A node covered by ONE row piece has exclusive jobs (HistJob.pad0 = 1: their bins are stored, not added); set
-// may_store = false where the histogram is not 16-byte aligned.
-void add_hist_jobs(std::vector<HistJob> &jobs, uint64_t hist_off, uint32_t begin, uint32_t len, int F,
-                   const HistPlan &pl, uint32_t rows_per_job, bool may_store = true) {
-    const bool exclusive = may_store && len <= rows_per_job;
-    for (uint32_t r0 = 0; r0 < len; r0 += rows_per_job) {
-        uint32_t nr = std::min(rows_per_job, len - r0);
-        for (int t = 0; t < pl.n_ftiles; ++t) {
-            HistJob j;
-            j.hist_off = hist_off;
-            j.row_begin = begin + r0;
-            j.n_rows = nr;
-            j.f0 = (uint32_t)(t * pl.ft);
-            j.ft = (uint32_t)std::min(pl.ft, F - t * pl.ft);
-            j.pad0 = exclusive ? 1u : 0u;
-            j.pad1 = 0;
-            if (j.ft > 0) jobs.push_back(j);
-        }
+// may_store = false where the histograms are not 16-byte aligned.
+struct BuiltNode { uint64_t off; uint32_t begin, len; };
+void make_hist_jobs(std::vector<HistJob> &jobs, const std::vector<BuiltNode> &nodes, int F, const HistPlan &pl,
+                    uint32_t rows_per_job, bool may_store = true) {
+    const uint32_t tiles = (uint32_t)((F + pl.ft - 1) / pl.ft);
+    uint32_t pieces = 0, piece = 0;
+    for (const BuiltNode &b : nodes) pieces += (b.len + rows_per_job - 1) / rows_per_job;
+    jobs.assign((size_t)pieces * tiles, HistJob{});
+    for (const BuiltNode &b : nodes) {
+        const bool exclusive = may_store && b.len <= rows_per_job;
+        for (uint32_t r0 = 0; r0 < b.len; r0 += rows_per_job, ++piece)
+            for (uint32_t t = 0; t < tiles; ++t) {
+                HistJob &j = jobs[gbt_job_place(piece, t, pieces, tiles)];
+                j.hist_off = b.off;
+                j.row_begin = b.begin + r0;
+                j.n_rows = std::min(rows_per_job, b.len - r0);
+                j.f0 = t * (uint32_t)pl.ft;
+                j.ft = std::min((uint32_t)pl.ft, (uint32_t)F - j.f0);
+                j.pad0 = exclusive ? 1u : 0u;
+            }
     }
 }
 
 // max_rows: what a job of the kernel may hold (2^21: its per-bin event counters are 16 bits wide; fewer where
 // it counts rows in a narrow field, gbt_histw_max_rows)
-// Every job of a launch merges the bins of its feature tile into HBM with two 64-bit global atomics per non-zero
-// bin, and the chip retires only ~1e11 of those per second, some forty times fewer than LDS atomics: a row piece
-// is therefore long enough that a bin receives hist_merge_ratio LDS additions on average per value merged
-// (rows >= ratio * 2 * B), unless that would leave fewer than about one workgroup per compute unit.
-constexpr int64_t kMinRowsPerJob = 4096;
-uint32_t pick_rows_per_job(const gbt_ctx *ctx, int64_t total_rows, int64_t max_rows = 1 << 21, int n_tiles = 1,
-                           int B = 0) {
-    int64_t pieces = std::max<int64_t>(1, (int64_t)ctx->num_cu * ctx->hist_jobs_per_cu / std::max(1, n_tiles));
-    if (B > 0) {
-        const int64_t by_merge = std::max<int64_t>(total_rows / ((int64_t)ctx->hist_merge_ratio * 2 * B),
-                                                   ((int64_t)ctx->num_cu + n_tiles - 1) / n_tiles);
-        pieces = std::min(pieces, std::max<int64_t>(1, by_merge));
+constexpr int64_t kMinRowsPerJob = 256;
+PlanHistRule hist_rule(const gbt_ctx *ctx, const HistPlan &pl, int F, int B, int64_t max_rows) {
+    PlanHistRule r;
+    r.pieces_max = std::max<int64_t>(1, (int64_t)ctx->num_cu * ctx->hist_jobs_per_cu / std::max(1, pl.n_ftiles));
+    r.min_rows = kMinRowsPerJob;
+    r.max_rows = max_rows;
+    r.merge = 0.15 * B * ctx->hist_merge_ratio / 96.0;   // (0.1, 0.2 and 0.3: within 3 %, 0.4: 10 % slower on the widest)
+    r.num_cu = ctx->num_cu;
+    r.tiles = (F + pl.ft - 1) / pl.ft;
+    r.ft = pl.ft;
+    r.width = F;
+    r.exclusive_ok = 1;
+    return r;
+}
+uint32_t pick_rows_per_job(const PlanHistRule &r, const std::vector<BuiltNode> &nodes) {
+    int64_t rows = 0, longest = 0;
+    for (const BuiltNode &b : nodes) {
+        rows += b.len;
+        longest = std::max<int64_t>(longest, b.len);
     }
-    int64_t rpj = (total_rows + pieces - 1) / pieces;
-    if (rpj < kMinRowsPerJob) rpj = kMinRowsPerJob;
-    if (rpj > max_rows) rpj = max_rows;
-    return (uint32_t)rpj;
+    int best = 0;
+    double best_cost = 0.0;
+    for (int c = 0; c < kPieceCandidates; ++c) {
+        const int64_t length = gbt_piece_candidate(r, rows, c);
+        int64_t pieces = 0, single = 0;
+        for (const BuiltNode &b : nodes) {
+            const int64_t p = (b.len + length - 1) / length;
+            pieces += p;
+            single += p == 1;
+        }
+        const double cost = gbt_piece_cost(r, rows, length, pieces, r.exclusive_ok ? single : 0, longest);
+        if (c == 0 || cost < best_cost) {
+            best = c;
+            best_cost = cost;
+        }
+    }
+    return (uint32_t)gbt_piece_candidate(r, rows, best);
+}
+// Threads of a histogram workgroup: 1024 where the launch is about one workgroup per compute unit (us per round with 512 and
+// 1024: 1M x 28 bytes 606 and 572, 50,000 x 500 x 6 bits 465 and 444), else the context's 512 (500,000 x 2000 x 6 bits 5390 and 5710).
+int hist_block(const gbt_ctx *ctx, const PlanHistRule &r, int64_t rows) {
+    if (!ctx->hist_block_auto) return ctx->hist_block;
+    const double jobs = (double)rows * r.tiles / (double)gbt_piece_candidate(r, rows, kPieceCandidates / 2);
+    return jobs <= r.num_cu ? 1024 : ctx->hist_block;
 }
 
 // Best of one node's per-chunk split records: largest gain, earliest chunk on ties.
@@ -230,12 +260,13 @@ extern "C" int32_t gbt_create(gbt_ctx **ctx_out, int32_t device, void *stream) {
     if (e == hipSuccess) {
         c->num_cu = prop.multiProcessorCount;
         c->hist_block = 512;
+        c->hist_block_auto = 1;
         c->hist_jobs_per_cu = 8;
         c->hist_merge_ratio = 96;
         c->move_max_words = 8;    // measured: 15-word rows (10M x 50 x 9 bits) grow 18 % faster by id lists than moved; 7-word rows stay moved
         if (const char *e20 = getenv("GBT_TUNE_MOVE_MAX_WORDS")) { int v = atoi(e20); if (v >= 1 && v <= 64) c->move_max_words = v; }
         c->hist_lds_kb = 64;   // two resident workgroups per CU hide the row-fetch latency better than one big tile
-        if (const char *e1 = getenv("GBT_TUNE_HIST_BLOCK")) { int v = atoi(e1); if (v == 256 || v == 512 || v == 1024) c->hist_block = v; }
+        if (const char *e1 = getenv("GBT_TUNE_HIST_BLOCK")) { int v = atoi(e1); if (v == 256 || v == 512 || v == 1024) { c->hist_block = v; c->hist_block_auto = 0; } }
         if (const char *e3 = getenv("GBT_TUNE_HIST_RUNTIME_BITS")) c->hist_runtime_bits = atoi(e3) != 0;
         c->part_fused = 1;
         c->part_hist = 1;
@@ -767,10 +798,10 @@ static int32_t hist_uniform(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, 
         return GBT_OK;
     }
     std::vector<HistJob> jobs;
-    const bool uni_w = uniform_h && bits != 8 && !ctx->hist_runtime_bits;   // the kernels with a row-count form
-    add_hist_jobs(jobs, 0, 0, (uint32_t)n_rows, F, pl,
-                  pick_rows_per_job(ctx, n_rows, gbt_histw_max_rows(uni_w), pl.n_ftiles, B),
-                  ((uintptr_t)hist_out & 15u) == 0);
+    const bool uni_w = uniform_h && !ctx->hist_runtime_bits;   // the kernels with a row-count form
+    const std::vector<BuiltNode> all{BuiltNode{0, 0, (uint32_t)n_rows}};
+    const PlanHistRule rule = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(uni_w));
+    make_hist_jobs(jobs, all, F, pl, pick_rows_per_job(rule, all), ((uintptr_t)hist_out & 15u) == 0);
     // Without a caller workspace the job table is read straight from the pinned
     // staging, which the device can address; it is small (a few KB).
     size_t bytes = jobs.size() * sizeof(HistJob);
@@ -793,7 +824,7 @@ static int32_t hist_uniform(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, 
     else
         GBT_HIP(ctx, gbt_launch_hist(ctx, packed, bits, (int64_t)F * bits, gbt_packed_words(n, F, bits), n, B,
                                      (uint32_t)missing_sym, row_idx, gq, hist_out, dev_jobs, (int)jobs.size(), pl.ft,
-                                     uni_w, hq_uniform));
+                                     uni_w, hq_uniform, hist_block(ctx, rule, n_rows)));
     gbt_prof_end(ctx);
     return GBT_OK;
 }
@@ -973,26 +1004,10 @@ struct PlannedGrowth {
     const int32_t *nb;
     double min_child_weight;
 };
-// the rule by which pick_rows_per_job cuts a level's rows into jobs
-PlanHistRule plan_hist_rule(const gbt_ctx *ctx, const HistPlan &pl, int F, int B, int64_t max_rows) {
-    PlanHistRule r;
-    r.pieces_max = std::max<int64_t>(1, (int64_t)ctx->num_cu * ctx->hist_jobs_per_cu / std::max(1, pl.n_ftiles));
-    r.merge_div = (int64_t)ctx->hist_merge_ratio * 2 * B;
-    r.cu_per_tile = ((int64_t)ctx->num_cu + pl.n_ftiles - 1) / pl.n_ftiles;
-    r.min_rows = kMinRowsPerJob;
-    r.max_rows = max_rows;
-    r.tiles = (F + pl.ft - 1) / pl.ft;
-    r.ft = pl.ft;
-    r.width = F;
-    r.exclusive_ok = 1;
-    return r;
-}
 // the most jobs `splits` built children of a matrix of n rows can be cut into
 int64_t plan_hist_jobs_max(const PlanHistRule &r, int64_t n, int64_t splits) {
     const int64_t built = n / 2 + 1;
-    int64_t pieces = r.pieces_max;
-    if (r.merge_div) pieces = std::min(pieces, std::max<int64_t>({1, built / r.merge_div, r.cu_per_tile}));
-    pieces = std::max(pieces, (built + r.max_rows - 1) / r.max_rows);
+    const int64_t pieces = std::max(r.pieces_max, (built + r.max_rows - 1) / r.max_rows);
     return (pieces + splits) * r.tiles;
 }
 constexpr int kPlanExactDepth = 9;   // from this depth on the host waits for a level's number of splits: see planned_levels
@@ -1193,7 +1208,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
     bool planned = ctx->plan && !lossguide && root_may_split && (path == 1 || path == 3) && !fix_in_hist && cap <= kPlanNodesMax;
     PlanHistRule plan_rule{};
     if (planned) {
-        plan_rule = plan_hist_rule(ctx, pl, F, B, gbt_histw_max_rows(true));   // (the limit that makes the most jobs)
+        plan_rule = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(true));   // (the limit that makes the most jobs)
         planned = plan_hist_jobs_max(plan_rule, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
     }
     // thresholds come from the cut table: it travels through the part of the pinned read-back buffer that
@@ -1346,10 +1361,9 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
         g.v.inv_sh = inv_sh;
         g.v.lambda = lambda;
         g.v.min_gain = min_gain;
-        const bool uni_w = uniform_h && bits != 8 && !ctx->hist_runtime_bits;   // the kernels with a row-count form
+        const bool uni_w = uniform_h && !ctx->hist_runtime_bits;   // the kernels with a row-count form
         const int32_t hq_w = (int32_t)llrint((double)h_value * scale[1]);
-        g.rule = plan_rule;
-        g.rule.max_rows = gbt_histw_max_rows(uni_w);
+        g.rule = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(uni_w));
         g.max_depth = max_depth;
         g.F = F;
         g.B = B;
@@ -1403,7 +1417,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
             GBT_HIP(ctx, gbt_launch_hist(ctx, ids ? packed : rows.sym, bits, ids ? (int64_t)row_bits : rows.stride_bits,
                                          ids ? gbt_packed_words(n, F, bits) : rows.n_words, n, B, (uint32_t)missing_sym,
                                          ids ? rows.id : nullptr, ids ? gq : rows.gq, pool, g.v.hjobs, (int)jobs, pl.ft, uni_w,
-                                         hq_w, &g.v.levels[d + 1].n_hist_jobs));
+                                         hq_w, hist_block(ctx, g.rule, n / 2), &g.v.levels[d + 1].n_hist_jobs));
             gbt_prof_end(ctx);
             return GBT_OK;
         };
@@ -2081,8 +2095,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
         // ---- children, in creation order
         hjobs.clear();
         int64_t built_rows = 0;
-        struct Built { uint64_t off; uint32_t begin, len; };
-        std::vector<Built> built;
+        std::vector<BuiltNode> built;
         const int32_t first_child = n_nodes;
         for (size_t k = 0; k < pjobs.size(); ++k) {
             const HNode &nd = sel_nodes[k];
@@ -2134,7 +2147,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
                 // built, else the one with fewer rows; its sibling comes by subtraction
                 const bool left_small = with_hist ? pjobs[k].pad == 1u : lc.len <= rc.len;
                 const HNode &sm = left_small ? lc : rc;
-                built.push_back(Built{(uint64_t)sm.id * (uint64_t)hist_len, sm.begin, sm.len});
+                built.push_back(BuiltNode{(uint64_t)sm.id * (uint64_t)hist_len, sm.begin, sm.len});
                 built_rows += sm.len;
                 HNode &other = left_small ? rc : lc;   // its histogram: parent - built, made when it is evaluated
                 other.sub_parent = nd.id;
@@ -2167,7 +2180,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
             const uint32_t ktile = (uint32_t)std::min<double>(std::max<double>(std::ceil(want / t), 4.0), (double)((1u << 21) / t)) * t;
             kjobs.clear();
             uint32_t kspans = 0;
-            for (const Built &b : built) {
+            for (const BuiltNode &b : built) {
                 if (b.len == 0) continue;   // its histogram stays zero
                 PartJob j{};
                 j.seg_begin = b.begin;
@@ -2204,22 +2217,23 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
             // ---- BuildPartialHistograms for the smaller children (their rows are now one
             //      contiguous run of the working copy)
             const int32_t n_children = n_nodes - first_child;
-            const bool uni_w = uniform_h && bits != 8 && !ctx->hist_runtime_bits;   // the kernels with a row-count form
+            const bool uni_w = uniform_h && !ctx->hist_runtime_bits;   // the kernels with a row-count form
             const int32_t hq_uniform = (int32_t)llrint((double)h_value * scale[1]);
-            const uint32_t rpj = pick_rows_per_job(ctx, built_rows, gbt_histw_max_rows(uni_w), pl.n_ftiles, B);
+            const PlanHistRule rule = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(uni_w));
+            const uint32_t rpj = pick_rows_per_job(rule, built);
             // Jobs add into a histogram that must start at zero, except where a node is one row piece: its jobs
             // store every bin of their tile.  (The sibling's histogram is stored bin by bin by the evaluation's
             // subtraction.)  Deep levels consist of such nodes only, and there the fill is the larger part of the
             // level: 2 MB per node for 2000 features x 64 bins.
             bool all_stored = true;
-            for (const Built &b : built) all_stored = all_stored && b.len > 0 && b.len <= rpj;
+            for (const BuiltNode &b : built) all_stored = all_stored && b.len > 0 && b.len <= rpj;
             if (!all_stored) {
                 gbt_prof_begin(ctx, GBT_PROF_CLEAR, (double)n_children * (double)hist_len * 8.0);
                 GBT_HIP(ctx, gbt_launch_fill_u64(s, (uint64_t *)(pool + (int64_t)first_child * hist_len), 0,
                                                  (int64_t)n_children * hist_len));
                 gbt_prof_end(ctx);
             }
-            for (const Built &b : built) add_hist_jobs(hjobs, b.off, b.begin, b.len, F, pl, rpj);
+            make_hist_jobs(hjobs, built, F, pl, rpj);
             const size_t per_launch = kUploadBytes / sizeof(HistJob);
             for (size_t j0 = 0; j0 < hjobs.size(); j0 += per_launch) {
                 const size_t nj = std::min(per_launch, hjobs.size() - j0);
@@ -2232,11 +2246,13 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
                 if (path == 3)   // the rows by id from the caller's matrix, the pairs by id
                     GBT_HIP(ctx, gbt_launch_hist(ctx, packed, bits, row_bits, gbt_packed_words(n, F, bits), n, B,
                                                  (uint32_t)missing_sym, W[wnext].id, gq, pool,
-                                                 (const HistJob *)(ws + L.jobs), (int)nj, pl.ft, uni_w, hq_uniform));
+                                                 (const HistJob *)(ws + L.jobs), (int)nj, pl.ft, uni_w, hq_uniform,
+                                                 hist_block(ctx, rule, built_rows)));
                 else
                     GBT_HIP(ctx, gbt_launch_hist(ctx, W[wnext].sym, bits, W[wnext].stride_bits, W[wnext].n_words, n, B,
                                                  (uint32_t)missing_sym, nullptr, W[wnext].gq, pool,
-                                                 (const HistJob *)(ws + L.jobs), (int)nj, pl.ft, uni_w, hq_uniform));
+                                                 (const HistJob *)(ws + L.jobs), (int)nj, pl.ft, uni_w, hq_uniform,
+                                                 hist_block(ctx, rule, built_rows)));
                 gbt_prof_end(ctx);
             }
         }

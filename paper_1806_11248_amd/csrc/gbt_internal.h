@@ -7,6 +7,8 @@
 #include <stdint.h>
 #include <stdio.h>
 
+#include <math.h>
+
 #include <algorithm>
 #include <vector>
 
@@ -30,6 +32,7 @@ struct gbt_ctx {
     char *pinned;           // host staging for job tables and small read-backs
     size_t pinned_bytes;
     int hist_block;         // threads per histogram workgroup
+    int hist_block_auto;    // 1: hist_block is the default, which a launch of few workgroups may double
     int hist_runtime_bits;  // 1: unpack with run-time shifts even where a compile-time kernel exists
     int part_fused;         // 1: one-launch record partition where it applies
     int lossguide_batch;    // open leaves a round of loss-guided growth expands at once (1: only the one whose turn it is)
@@ -44,7 +47,7 @@ struct gbt_ctx {
     int hist_lds_auto;      // 1: hist_lds_kb is the default, which a shape of two to four feature tiles may double to save a tile
     int hist_jobs_per_cu;   // histogram workgroups to aim for per compute unit and launch
     int move_max_words;     // rows of more 32-bit words than this are never moved: only their ids are partitioned
-    int hist_merge_ratio;   // LDS additions a bin should receive, on average, per value a job merges into HBM
+    int hist_merge_ratio;   // weight of the merges into HBM in the cutting of rows into histogram jobs (96: as measured)
     int hist8;              // 1: the root histogram of 8-bit symbols with at most 16 features takes kernels_hist8.hip
     int hist8_stagger;      // its workgroups on one compute unit get unequal shares of rows: spread in 1/256ths
     int sparse_jobs_per_cu; // row pieces per compute unit and launch of the sparse-row histogram kernel
@@ -200,12 +203,52 @@ struct PlanJob {             // what the children of partition job k need of its
     uint32_t node, pad;
     int64_t GLq, HLq;
 };
-// How the rows of a level's built children are cut into histogram jobs (the rule of pick_rows_per_job)
+// How the rows of a level's built nodes are cut into histogram jobs: pieces of at most rows_per_job rows of a node, a job
+// per piece and column tile.  Short pieces spread the rows over the chip, long ones merge fewer histograms into HBM (two
+// 64-bit atomics per bin, some 1.2*10^11 a second over the whole chip).  Both sides in rows a compute unit could have
+// added instead (an element takes one 0.165 ns, whatever the kernel's form):
+//   adding   the busiest compute unit's share: the longest piece, or the average job times the jobs of a compute unit;
+//   merging  jobs * merge, merge = 0.15 * bins (a node of one piece stores its bins: a quarter of that).
+// With equal pieces and fewer jobs than compute units the best length is sqrt(rows * tiles * merge); the candidates are
+// that length times 2^(-1) .. 2^(7/8), because what decides near it is how the number of jobs falls on the compute units
+// (5M x 30 bytes, us per round with a fixed number of jobs per launch: 250 jobs 1790, 300 2012, 500 1987, 560 2184).
 struct PlanHistRule {
-    int64_t pieces_max, merge_div, cu_per_tile, min_rows, max_rows;
+    int64_t pieces_max, min_rows, max_rows;
+    double merge;            // see above, per job; 0: pieces_max alone decides
+    int num_cu;
     int tiles, ft, width;    // feature (or bin id) tiles: `tiles` tiles of ft of the `width` columns (ids)
     int exclusive_ok;        // a node of one piece stores its bins
 };
+constexpr int kPieceCandidates = 16;
+__host__ __device__ inline int64_t gbt_clamp_rows(const PlanHistRule &r, double rows) {
+    const int64_t v = rows > 1e18 ? (int64_t)1e18 : (int64_t)rows;
+    return v < r.min_rows ? r.min_rows : v > r.max_rows ? r.max_rows : v;
+}
+// candidate c for `rows` rows in all
+__host__ __device__ inline int64_t gbt_piece_candidate(const PlanHistRule &r, int64_t rows, int c) {
+    // 2^((c - 8) / 8)
+    constexpr double step[8] = {1.0, 1.0905077326652577, 1.189207115002721, 1.2968395546510096,
+                                1.4142135623730951, 1.5422108254079407, 1.681792830507429, 1.8340080864093424};
+    double v = sqrt((double)rows * r.tiles * r.merge) * step[c & 7] * (c < 8 ? 0.5 : 1.0);
+    const double least = (double)((rows + r.pieces_max - 1) / r.pieces_max);
+    return gbt_clamp_rows(r, v < least ? least : v);
+}
+// what cutting at `length` rows costs: pieces in all, those of nodes of one piece, the longest node
+__host__ __device__ inline double gbt_piece_cost(const PlanHistRule &r, int64_t rows, int64_t length, int64_t pieces, int64_t single,
+                                                 int64_t longest) {
+    const double jobs = (double)pieces * r.tiles, most = (double)(longest < length ? longest : length);
+    const double per_cu = (double)(((int64_t)pieces * r.tiles + r.num_cu - 1) / r.num_cu);
+    const double share = jobs > 0.0 ? per_cu * (double)rows * r.tiles / jobs : 0.0;
+    const double merged = (double)(pieces - single) + 0.25 * (double)single;
+    return (share > most ? share : most) + merged * r.tiles * r.merge;
+}
+// Where the job of column tile `tile` of row piece `piece` stands among a launch's pieces * tiles jobs.  Workgroups are
+// dealt to the eight dies in turn, and each die has an L2 of its own: the tiles of a piece, which read the same rows, pairs
+// and ids, stand eight apart and meet in one L2.
+__host__ __device__ inline uint32_t gbt_job_place(uint32_t piece, uint32_t tile, uint32_t pieces, uint32_t tiles) {
+    const uint32_t group = piece & ~7u, wide = pieces - group < 8u ? pieces - group : 8u;
+    return group * tiles + tile * wide + (piece - group);
+}
 struct PlanView {            // device addresses unless noted
     PlanLevel *levels;
     PlanNode *nodes;
@@ -271,13 +314,13 @@ hipError_t gbt_launch_hist(gbt_ctx *ctx, const uint32_t *packed, int bits, int64
                            // every row's rounded h equals hq_uniform: kernels that have a form for it (symbol widths
                            // other than 8 bits) count rows instead of summing h; jobs then hold at most
                            // gbt_histw_max_rows(true) rows
-                           bool uniform_h = false, int32_t hq_uniform = 0,
+                           bool uniform_h = false, int32_t hq_uniform = 0, int block = 0,   // threads (0: ctx->hist_block)
                            const uint32_t *n_jobs_dev = nullptr);   // see DEVICE COUNTS
 int gbt_histw_max_rows(bool uniform_h);
 hipError_t gbt_launch_histw(gbt_ctx *ctx, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n_words,
                             int64_t n, int B, uint32_t missing, const uint32_t *row_idx, const int32_t *gq,
                             int64_t *hist_pool, const HistJob *jobs, int n_jobs, int max_ft, bool uniform_h,
-                            int32_t hq_uniform, const uint32_t *n_jobs_dev = nullptr);
+                            int32_t hq_uniform, int block, const uint32_t *n_jobs_dev = nullptr);
 // Largest feature tile whose LDS histogram fits, and the per-job row count to aim for.
 int gbt_hist_feature_tile(const gbt_ctx *ctx, int F, int B, int64_t n_rows = 0);   // n_rows: rows of the matrix the tiles are for (0: unknown)
 

@@ -1323,24 +1323,25 @@ hipError_t launch_generic(hipStream_t s, int n_jobs, int block, size_t lds, cons
 hipError_t gbt_launch_hist(gbt_ctx *ctx, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n_words,
                            int64_t n, int B, uint32_t missing, const uint32_t *row_idx, const int32_t *gq,
                            int64_t *hist_pool, const HistJob *jobs, int n_jobs, int max_ft, bool uniform_h,
-                           int32_t hq_uniform, const uint32_t *n_jobs_dev) {
+                           int32_t hq_uniform, int block, const uint32_t *n_jobs_dev) {
     if (n_jobs <= 0) return hipSuccess;
-    if (!ctx->hist_runtime_bits && bits != 8)
+    if (block == 0) block = ctx->hist_block;
+    if (!ctx->hist_runtime_bits && (bits != 8 || uniform_h))
         return gbt_launch_histw(ctx, packed, bits, stride_bits, n_words, n, B, missing, row_idx, gq, hist_pool, jobs,
-                                n_jobs, max_ft, uniform_h, hq_uniform, n_jobs_dev);
+                                n_jobs, max_ft, uniform_h, hq_uniform, block, n_jobs_dev);
     const int Bp = padded_bins(B);
     const size_t lds = ((size_t)max_ft * Bp + 256) * 12;
     const int2 *g2 = (const int2 *)gq;
     hipStream_t s = ctx->stream;
     if (bits == 8 && (stride_bits & 7) == 0) {
         const bool chk = missing < 256u || B < 256;
-        const B8Args a{s, n_jobs, ctx->hist_block, lds, packed, n_words, stride_bits >> 3, n, B, Bp, missing, row_idx, g2, hist_pool, jobs, FixArgs{}, n_jobs_dev};
+        const B8Args a{s, n_jobs, block, lds, packed, n_words, stride_bits >> 3, n, B, Bp, missing, row_idx, g2, hist_pool, jobs, FixArgs{}, n_jobs_dev};
         if (row_idx) return chk ? pick_slots<true, true>(max_ft, a) : pick_slots<true, false>(max_ft, a);
         return chk ? pick_slots<false, true>(max_ft, a) : pick_slots<false, false>(max_ft, a);
     }
     if (row_idx)
-        return launch_generic<true>(s, n_jobs, ctx->hist_block, lds, packed, n_words, bits, stride_bits, n, B, Bp, missing, row_idx, g2, hist_pool, jobs, n_jobs_dev);
-    return launch_generic<false>(s, n_jobs, ctx->hist_block, lds, packed, n_words, bits, stride_bits, n, B, Bp, missing, row_idx, g2, hist_pool, jobs, n_jobs_dev);
+        return launch_generic<true>(s, n_jobs, block, lds, packed, n_words, bits, stride_bits, n, B, Bp, missing, row_idx, g2, hist_pool, jobs, n_jobs_dev);
+    return launch_generic<false>(s, n_jobs, block, lds, packed, n_words, bits, stride_bits, n, B, Bp, missing, row_idx, g2, hist_pool, jobs, n_jobs_dev);
 }
 
 bool gbt_hist_fix_ok(int bits, int64_t stride_bits, int max_ft, int n_ftiles) {

@@ -251,11 +251,11 @@ int gbt_histw_max_rows(bool uniform_h) { return uniform_h ? (int)kWRowsMask : 1 
 hipError_t gbt_launch_histw(gbt_ctx *ctx, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n_words,
                             int64_t n, int B, uint32_t missing, const uint32_t *row_idx, const int32_t *gq,
                             int64_t *hist_pool, const HistJob *jobs, int n_jobs, int max_ft, bool uniform_h,
-                            int32_t hq_uniform, const uint32_t *n_jobs_dev) {
+                            int32_t hq_uniform, int block, const uint32_t *n_jobs_dev) {
     if (n_jobs <= 0) return hipSuccess;
     const int Bp = padded_bins(B);
     const size_t lds = ((size_t)max_ft * Bp + 64) * (uniform_h ? 8 : 12);
-    const WArgs a{ctx->stream, n_jobs, ctx->hist_block, lds, packed, n_words, stride_bits, n, B, Bp, missing, row_idx,
+    const WArgs a{ctx->stream, n_jobs, block, lds, packed, n_words, stride_bits, n, B, Bp, missing, row_idx,
                   (const int2 *)gq, hist_pool, jobs, hq_uniform, n_jobs_dev};
     switch (bits) {
         case 1: return pick_w<1>(a, uniform_h);
@@ -265,6 +265,7 @@ hipError_t gbt_launch_histw(gbt_ctx *ctx, const uint32_t *packed, int bits, int6
         case 5: return pick_w<5>(a, uniform_h);
         case 6: return pick_w<6>(a, uniform_h);
         case 7: return pick_w<7>(a, uniform_h);
+        case 8: return pick_w<8>(a, uniform_h);
         case 9: return pick_w<9>(a, uniform_h);
         case 10: return pick_w<10>(a, uniform_h);
         case 11: return pick_w<11>(a, uniform_h);

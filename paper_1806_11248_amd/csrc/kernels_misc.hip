@@ -561,7 +561,7 @@ __global__ __launch_bounds__(256) void predict_window_kernel(const char *ws, con
 // Rows of any width: every level's symbol is fetched from the matrix, one dependent access per level (the rows a thread
 // walks side by side keep Q of them in flight).  Nodes as above, with bit 30 of x set on a leaf: it keeps its rows
 // whatever symbol the matrix holds for them.
-// 1M x 28 bytes, depth 6: 37 us with one row at a time and a branch per step, 9 us so.
+// 1M x 28 bytes, depth 6: 37 us with one row at a time and a branch per step, 23 us so.
 template <int Q>
 __global__ __launch_bounds__(256) void predict_gather_kernel(const char *ws, const DevTree *trees, int n_trees,
                                                              const uint32_t *packed, int bits, uint32_t missing, int64_t n,
@@ -1157,7 +1157,7 @@ hipError_t gbt_launch_predict(hipStream_t s, const char *ws, const DevTree *tree
     const int form = walk_form(bits, F, max_nodes, node_rows != nullptr, &lds);
     if (packed && compact_ok && lds <= kWalkLds) {
         // A workgroup stages the tree and walks a block of rows.  Where blocks of 4096 rows would leave compute units
-        // without a workgroup they are shorter, down to one row per thread (1M x 28 bytes: 37 us with 245 workgroups, 9 us
+        // without a workgroup they are shorter, down to one row per thread (1M x 28 bytes: 37 us with 245 workgroups, 23 us
         // with 977 and four rows per thread side by side; 50,000 x 22 bytes 36 -> 7 us).
         const bool few = n <= (int64_t)256 * 1024;
         const int rows_per_block = few ? 256 : n < (int64_t)4096 * 1024 ? 1024 : 4096;

@@ -174,10 +174,42 @@ __global__ __launch_bounds__(kSplitBlock) void plan_split_kernel(PlanView v, int
     }
 }
 
+// The cheapest of the candidate piece lengths (gbt_piece_cost); sixteen threads count the pieces of one candidate.  Levels of
+// more than kPieceNodes splits take the middle candidate: their nodes are one piece each nearly everywhere.
+constexpr uint32_t kPieceNodes = 2048;
+__device__ uint32_t pick_piece(const PlanHistRule &rule, int64_t rows, uint32_t ns, const uint32_t *s_small, double *s_cost) {
+    if (rule.merge <= 0.0) return (uint32_t)gbt_clamp_rows(rule, (double)((rows + rule.pieces_max - 1) / rule.pieces_max));
+    if (ns > kPieceNodes) return (uint32_t)gbt_piece_candidate(rule, rows, kPieceCandidates / 2);
+    static_assert(kChildBlock == 16 * kPieceCandidates, "sixteen threads per candidate");
+    const int c = threadIdx.x >> 4;
+    const uint32_t length = (uint32_t)gbt_piece_candidate(rule, rows, c);
+    uint32_t pieces = 0, single = 0, longest = 0;
+    for (uint32_t k = threadIdx.x & 15; k < ns; k += 16) {
+        const uint32_t s = s_small[k], p = (s + length - 1) / length;
+        pieces += p;
+        single += p == 1 ? 1u : 0u;
+        longest = longest > s ? longest : s;
+    }
+    for (int o = 8; o > 0; o >>= 1) {
+        pieces += (uint32_t)__shfl_xor((int)pieces, o);
+        single += (uint32_t)__shfl_xor((int)single, o);
+        const uint32_t l = (uint32_t)__shfl_xor((int)longest, o);
+        longest = longest > l ? longest : l;
+    }
+    if ((threadIdx.x & 15) == 0) s_cost[c] = gbt_piece_cost(rule, rows, length, pieces, rule.exclusive_ok ? single : 0, longest);
+    __syncthreads();
+    int best = 0;
+    for (int k = 1; k < kPieceCandidates; ++k)
+        if (s_cost[k] < s_cost[best]) best = k;
+    return (uint32_t)gbt_piece_candidate(rule, rows, best);
+}
+
 __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, int d, const uint32_t *__restrict__ n_left,
                                                                     int stride, int with_hist, PlanHistRule rule) {
     __shared__ int64_t tmp[kChildBlock / 64];
-    __shared__ uint32_t s_off[kChildBlock], s_begin[kChildBlock], s_len[kChildBlock], s_slot[kChildBlock], s_jobs[kChildBlock];
+    __shared__ uint32_t s_small[kPieceNodes];
+    __shared__ double s_cost[kPieceCandidates];
+    __shared__ uint32_t s_off[kChildBlock], s_begin[kChildBlock], s_len[kChildBlock], s_slot[kChildBlock], s_pieces[kChildBlock];
     const uint32_t ns = v.levels[d].n_splits;
     const uint32_t first_child = v.levels[d].first_node + v.levels[d].n_nodes;
     const bool lead = blockIdx.x == 0;
@@ -186,31 +218,28 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
         return l < len ? l : len;
     };
     uint32_t rpj = 1;
-    int64_t built = 0;
+    int64_t built = 0, pieces = 0;
     if (with_hist) {
         int64_t mine = 0;
         for (uint32_t k = threadIdx.x; k < ns; k += kChildBlock) {
+            const uint32_t len = v.pjobs[k].seg_len, l = left_rows(k, len), small = l <= len - l ? l : len - l;
+            mine += small;
+            if (k < kPieceNodes) s_small[k] = small;
+        }
+        (void)block_scan<kChildBlock>(mine, tmp, &built);   // (its barriers also complete s_small)
+        rpj = pick_piece(rule, built, ns, s_small, s_cost);
+        mine = 0;
+        for (uint32_t k = threadIdx.x; k < ns; k += kChildBlock) {
             const uint32_t len = v.pjobs[k].seg_len, l = left_rows(k, len);
-            mine += l <= len - l ? l : len - l;
+            mine += ((l <= len - l ? l : len - l) + rpj - 1) / rpj;
         }
-        (void)block_scan<kChildBlock>(mine, tmp, &built);
-        int64_t pieces = rule.pieces_max;
-        if (rule.merge_div) {
-            int64_t by = built / rule.merge_div;
-            if (by < rule.cu_per_tile) by = rule.cu_per_tile;
-            if (by < 1) by = 1;
-            if (pieces > by) pieces = by;
-        }
-        int64_t r = (built + pieces - 1) / pieces;
-        if (r < rule.min_rows) r = rule.min_rows;
-        if (r > rule.max_rows) r = rule.max_rows;
-        rpj = (uint32_t)r;
+        (void)block_scan<kChildBlock>(mine, tmp, &pieces);
     }
     int64_t carry = 0;
     uint32_t bad = 0;
     for (uint32_t k0 = 0; k0 < ns; k0 += kChildBlock) {
         const uint32_t k = k0 + threadIdx.x;
-        uint32_t jobs = 0;
+        uint32_t mine = 0;   // pieces of this thread's node
         if (k < ns) {
             const PartJob j = v.pjobs[k];
             const PlanJob info = v.pinfo[k];
@@ -221,11 +250,11 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
             const bool left_small = l <= r;
             const uint32_t small = left_small ? l : r;
             if (with_hist) {
-                jobs = (small + rpj - 1) / rpj * (uint32_t)rule.tiles;
+                mine = (small + rpj - 1) / rpj;
                 s_begin[threadIdx.x] = left_small ? j.seg_begin : j.seg_begin + l;
                 s_len[threadIdx.x] = small;
                 s_slot[threadIdx.x] = left_small ? lid : rid;
-                s_jobs[threadIdx.x] = jobs;
+                s_pieces[threadIdx.x] = mine;
             }
             if (lead) {
                 const int64_t GR = nd.Gq - info.GLq, HR = nd.Hq - info.HLq;
@@ -256,8 +285,8 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
         }
         if (!with_hist) continue;
         int64_t all;
-        const int64_t incl = block_scan<kChildBlock>((int64_t)jobs, tmp, &all);
-        s_off[threadIdx.x] = (uint32_t)(carry + incl) - jobs;
+        const int64_t incl = block_scan<kChildBlock>((int64_t)mine, tmp, &all);
+        s_off[threadIdx.x] = (uint32_t)(carry + incl) - mine;
         __syncthreads();
         const uint32_t here = ns - k0 < (uint32_t)kChildBlock ? ns - k0 : (uint32_t)kChildBlock;
         for (uint32_t q = 0; q < here; ++q) {
@@ -270,7 +299,7 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
                     z[i] = make_ulonglong2(0ull, 0ull);
             }
             if ((k0 + q) % gridDim.x != blockIdx.x) continue;
-            for (uint32_t t = threadIdx.x; t < s_jobs[q]; t += kChildBlock) {
+            for (uint32_t t = threadIdx.x; t < s_pieces[q] * (uint32_t)rule.tiles; t += kChildBlock) {
                 const uint32_t piece = t / (uint32_t)rule.tiles, tile = t - piece * (uint32_t)rule.tiles;
                 HistJob h;
                 h.hist_off = (uint64_t)s_slot[q] * (uint64_t)v.hist_len;
@@ -280,7 +309,7 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
                 h.ft = (uint32_t)rule.width - h.f0 < (uint32_t)rule.ft ? (uint32_t)rule.width - h.f0 : (uint32_t)rule.ft;
                 h.pad0 = exclusive ? 1u : 0u;
                 h.pad1 = 0;
-                v.hjobs[s_off[q] + t] = h;
+                v.hjobs[gbt_job_place(s_off[q] + piece, tile, (uint32_t)pieces, (uint32_t)rule.tiles)] = h;
             }
         }
         carry += all;
@@ -291,7 +320,7 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
         PlanLevel &nx = v.levels[d + 1];
         nx.first_node = first_child;
         nx.n_nodes = 2u * ns;
-        nx.n_hist_jobs = (uint32_t)carry;
+        nx.n_hist_jobs = (uint32_t)(pieces * rule.tiles);
         nx.built_rows = (uint64_t)built;
     }
 }
