@@ -776,7 +776,9 @@ static int32_t hist_uniform(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, 
                 "max_bins = %d: one feature's bins (%d bytes) exceed the LDS budget", B, B * 16);
     GBT_HIP(ctx, gbt_launch_fill_u64(ctx->stream, (uint64_t *)hist_out, 0, (int64_t)F * B * 2));
     if (n_rows == 0) return GBT_OK;
-    if (ctx->hist8 && !row_idx && n_rows == n && gbt_hist8_ok(bits, F, pl.n_ftiles, n, gbt_packed_words(n, F, bits))) {
+    // (fewer rows than give kernels_hist8.hip a column of 2048 for every compute unit are cut by gbt_rows_per_job's rule instead)
+    if (ctx->hist8 && !row_idx && n_rows == n && (fix || n >= (int64_t)2048 * ctx->num_cu) &&
+        gbt_hist8_ok(bits, F, pl.n_ftiles, n, gbt_packed_words(n, F, bits))) {
         Hist8Pairs p{};
         if (fix) {
             p.gpair = fix->gpair;
@@ -789,6 +791,8 @@ static int32_t hist_uniform(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, 
             p.sums = fix->slot_sums;
         } else {
             p.gq = gq;
+            p.uniform_h = uniform_h;
+            p.hq_uniform = hq_uniform;
         }
         int n_jobs8 = 0;
         gbt_prof_begin(ctx, GBT_PROF_HIST_ROOT, (double)n_rows * ((double)F * bits / 8.0 + 8.0), -1.0, 0, (double)n_rows * F);
@@ -1007,9 +1011,16 @@ struct PlannedGrowth {
 // the most jobs `splits` built children of a matrix of n rows can be cut into
 int64_t plan_hist_jobs_max(const PlanHistRule &r, int64_t n, int64_t splits) {
     const int64_t built = n / 2 + 1;
-    const int64_t pieces = std::max(r.pieces_max, (built + r.max_rows - 1) / r.max_rows);
+    // (by the shortest candidate length: its square grows with the rows, so the pieces do as well)
+    int64_t pieces = r.pieces_max;
+    if (r.merge > 0.0) pieces = std::min(pieces, built / std::max<int64_t>(1, gbt_piece_candidate(r, built, 0)) + 1);
+    pieces = std::max(pieces, (built + r.max_rows - 1) / r.max_rows);
     return (pieces + splits) * r.tiles;
 }
+// Byte symbols of at most 16 features take path 2 (whose levels the host plans, with a wait and some copies each) from this
+// many rows on, below it path 1.  us per round by path 2 and by path 1, 13 columns, depth 6: 20,000 rows 354 and 249, 300,000
+// 468 and 317, 1M 531 and 412, 3M 687 and 643, 4M 727 and 731, 7M 876 and 1018; 5M x 5 665 and 656, 5M x 16 892 and 844.
+constexpr int64_t kPath2Rows = 4 << 20;
 constexpr int kPlanExactDepth = 9;   // from this depth on the host waits for a level's number of splits: see planned_levels
 constexpr int kPlanWalkDepth = 10;   // a tree of at most this depth is walked from LDS at its largest size (41 KB)
 
@@ -1173,7 +1184,8 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
     // The rows in their current order.  Level 0 reads the caller's packed matrix; every
     // partition then moves whole records (symbols, gradient pair, id) into the other of two
     // word-aligned working copies, so that each node's rows stay contiguous.
-    const int path = grow_path(ctx, F, bits, B, tracked, pl.n_ftiles);
+    int path = grow_path(ctx, F, bits, B, tracked, pl.n_ftiles);
+    if (path == 2 && ctx->plan && !lossguide && n < kPath2Rows) path = 1;
     GbtRows W[2];
     for (int k = 0; k < 2; ++k) {
         W[k].sym_rw = (uint32_t *)(ws + L.wsym[k]);
@@ -1201,16 +1213,16 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
     matrix.id_rw = nullptr;
 
     const bool root_may_split = max_depth > 0 && (!lossguide || max_leaves > 1);
-    const bool fix_in_hist = ctx->hist_fix && root_may_split && gbt_hist_fix_ok(bits, row_bits, pl.ft, pl.n_ftiles);
     // Paths 1 and 3, depth-wise: the levels are planned on the device and enqueued without a wait.  (Path 2 and the
     // loss-guided policy plan on the host; so does a tree too deep for the tables: its job table would not fit the
     // workspace's, or its nodes the read-back buffer.)
-    bool planned = ctx->plan && !lossguide && root_may_split && (path == 1 || path == 3) && !fix_in_hist && cap <= kPlanNodesMax;
+    bool planned = ctx->plan && !lossguide && root_may_split && (path == 1 || path == 3) && cap <= kPlanNodesMax;
     PlanHistRule plan_rule{};
     if (planned) {
         plan_rule = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(true));   // (the limit that makes the most jobs)
         planned = plan_hist_jobs_max(plan_rule, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
     }
+    const bool fix_in_hist = ctx->hist_fix && root_may_split && !planned && gbt_hist_fix_ok(bits, row_bits, pl.ft, pl.n_ftiles);
     // thresholds come from the cut table: it travels through the part of the pinned read-back buffer that
     // the split records use later, and is picked up behind the first wait below (a copy into pageable
     // memory would be a wait of its own); a table too large for that is copied directly
@@ -1370,7 +1382,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
         g.n = n;
         g.cap_nodes = cap;
         // (path 1 moves records in one launch, its last level only counts; path 3 partitions ids in three launches throughout)
-        g.tile_rows[0] = path == 1 ? (uint32_t)gbt_partition_fused_tile(W[0]) : (uint32_t)GBT_PART_TILE;
+        g.tile_rows[0] = path == 1 ? (uint32_t)gbt_partition_fused_tile(W[0], n) : (uint32_t)GBT_PART_TILE;
         g.tile_rows[1] = GBT_PART_TILE;
         g.n_left[0] = path == 1 ? (const uint32_t *)(ws + L.state) : (const uint32_t *)(ws + L.n_left);
         g.n_left_stride[0] = path == 1 ? 2 : 1;
@@ -1399,7 +1411,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
                                                   dst.id_rw, g.v.pjobs, (int)splits, (int)tiles, (uint64_t *)(ws + L.masks),
                                                   (uint32_t *)(ws + L.tile_left), n_left32, counts));
             } else if (!last) {
-                GBT_HIP(ctx, gbt_launch_partition_fused(s, cur, dst, bits, row_bits, (uint32_t)missing_sym, g.v.pjobs, (int)splits,
+                GBT_HIP(ctx, gbt_launch_partition_fused(s, cur, dst, bits, row_bits, n, (uint32_t)missing_sym, g.v.pjobs, (int)splits,
                                                         (int)tiles, g.v.cursors, counts));
             } else {
                 GBT_HIP(ctx, gbt_launch_partition_records(s, cur, dst, bits, row_bits, n, (uint32_t)missing_sym, GBT_PART_COUNT,
@@ -1752,7 +1764,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
         for (const HNode &nd : sel_nodes) part_rows += nd.len;
         // rows per partition workgroup: a tile, or (with the histogram) a span of tiles long enough
         // to be worth merging an LDS histogram into HBM for
-        uint32_t part_tile = fused ? (uint32_t)gbt_partition_fused_tile(W[wnext]) : (uint32_t)GBT_PART_TILE;
+        uint32_t part_tile = fused ? (uint32_t)gbt_partition_fused_tile(W[wnext], n) : (uint32_t)GBT_PART_TILE;
         if (with_hist) {
             // Every span merges a whole histogram (two in the two-histogram pass, which has one workgroup per CU) into
             // HBM at its end, 64-bit global atomics that the chip retires slowly: a pass that moves nothing has little
@@ -2061,7 +2073,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
                 pool_zero_end = zero_end;
                 pre_eval = true;
             } else if (fused) {
-                GBT_HIP(ctx, gbt_launch_partition_fused(s, cur, W[wnext], bits, row_bits, (uint32_t)missing_sym,
+                GBT_HIP(ctx, gbt_launch_partition_fused(s, cur, W[wnext], bits, row_bits, n, (uint32_t)missing_sym,
                                                         (const PartJob *)(ws + L.jobs), (int)pjobs.size(),
                                                         (int)tile_cursor, (unsigned long long *)(ws + L.state)));
                 cursors_zero = false;

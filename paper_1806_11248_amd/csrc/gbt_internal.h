@@ -375,14 +375,14 @@ hipError_t gbt_launch_partition_records(hipStream_t s, const GbtRows &src, const
 // `what` above: move whole records, move only the ids, or only count the left rows of every job
 enum { GBT_PART_RECORDS = 0, GBT_PART_IDS = 1, GBT_PART_COUNT = 2 };
 // The same move of whole records in one launch for a caller that does not need the row order
-// (and no ids): rows narrow enough (gbt_partition_fused_ok), tiles of gbt_partition_fused_tile(dst)
+// (and no ids): rows narrow enough (gbt_partition_fused_ok), tiles of gbt_partition_fused_tile(dst, n)
 // rows (PartJob.tile_begin / n_tiles count those).  cursor: one word per job, cleared by the
 // launcher; after the launch its low half is the job's n_left.  Inside a child the rows of one
 // tile keep their order, the tiles' order is arbitrary.
 bool gbt_partition_fused_ok(const GbtRows &dst);
-int gbt_partition_fused_tile(const GbtRows &dst);
+int gbt_partition_fused_tile(const GbtRows &dst, int64_t n);   // n: rows of the matrix
 hipError_t gbt_launch_partition_fused(hipStream_t s, const GbtRows &src, const GbtRows &dst, int bits, int row_bits,
-                                      uint32_t missing, const PartJob *jobs, int n_jobs, int total_tiles,
+                                      int64_t n, uint32_t missing, const PartJob *jobs, int n_jobs, int total_tiles,
                                       unsigned long long *cursor, const uint32_t *counts_dev = nullptr);
 // The root histogram straight from the fp32 gradient pairs (8-bit symbols, one feature tile of at
 // most 16 features, jobs that cover rows [0, n) exactly once: gbt_hist_fix_ok): rounds each pair to

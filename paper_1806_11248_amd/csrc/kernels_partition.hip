@@ -444,13 +444,20 @@ __global__ __launch_bounds__(kFBlock) void part_fused_kernel(
 // contiguous piece of the source bit stream, which is read linearly into LDS (every lane busy, whole
 // lines, each byte fetched once); the split symbols are then cut out of LDS, and every row is copied
 // from LDS to its new place by a group of lanes, one word per lane.  The tile holds as many rows as
-// fit kStageBytes (at most kFTile).
+// fit kStageBytes (at most kFTile).  What it waits for is latency, so everything is asked for in groups: the
+// pairs first, four 16-byte pieces of the rows per thread, four rows per lane on the way out (1M x 28 bytes: 38 us
+// per level with one word and one row at a time, 25 so).
 constexpr int kStageBytes = 48 * 1024;
-__host__ __device__ inline int staged_tile_rows(int64_t dst_stride_bits) {
+constexpr int64_t kFusedRows = 1 << 20;   // (1M x 13 bytes: either form takes the same time within 5 %)
+// Rows of a tile: no more than give a matrix of n rows a tile per compute unit (50,000 x 24 bytes: 18 us per level with
+// tiles of 2048 rows, 7 with 256).
+inline int staged_tile_rows(int64_t dst_stride_bits, int64_t n) {
     int64_t r = (int64_t)kStageBytes * 8 / dst_stride_bits;   // the source stride is never larger
-    r = r / 64 * 64;
-    return (int)(r > kFTile ? kFTile : (r < 64 ? 64 : r));
+    r = std::min<int64_t>({r / 64 * 64, kFTile, (n / 256 + 63) / 64 * 64});
+    return (int)std::max<int64_t>(r, 64);
 }
+// Rows of four words take part_fused_kernel's tiles of 4096 rows where those fill the chip.
+inline bool fused_form(int64_t dst_stride_bits, int64_t n) { return (dst_stride_bits >> 5) == 4 && n >= kFusedRows; }
 
 __global__ __launch_bounds__(kFBlock) void part_staged_kernel(
     const uint32_t *__restrict__ src_sym, int64_t src_stride_bits, int64_t src_words,
@@ -476,14 +483,42 @@ __global__ __launch_bounds__(kFBlock) void part_staged_kernel(
     const int64_t w_lo = (int64_t)(bit0 >> 5);
     const uint32_t sh0 = (uint32_t)(bit0 & 31);
     const uint32_t n_stage = (uint32_t)((sh0 + (uint64_t)tile_rows * (uint64_t)src_stride_bits + 31) >> 5) + 1u;
-    uint32_t *dstpos = stage + (((uint64_t)tile_cap * (uint64_t)src_stride_bits + 31) >> 5) + 2;
-    for (uint32_t i = threadIdx.x; i < n_stage; i += kFBlock)
-        stage[i] = src_sym[w_lo + i < src_words ? w_lo + i : src_words - 1];
+    // (the tile's words are stored four at a time)
+    uint32_t *dstpos = stage + (((((uint64_t)tile_cap * (uint64_t)src_stride_bits + 31) >> 5) + 2 + 3) & ~(uint64_t)3);
+    const int n_words_tile = (tile_cap + 63) / 64;             // ballot words in use, <= kFWords
+    int2 pair[kRowsPerThread];   // the pairs are asked for first and needed last
+#pragma unroll
+    for (int j = 0; j < kRowsPerThread; ++j) {
+        const uint32_t in_tile = (uint32_t)(j * (kFBlock / 64) + wave) * 64u + (uint32_t)lane;
+        pair[j] = in_tile < tile_rows ? src_gq[p0 + in_tile] : make_int2(0, 0);
+    }
+    // four 16-byte loads in flight per thread (words past the end of the buffer hold no bit of the tile)
+    for (uint32_t i0 = 4u * threadIdx.x; i0 < n_stage; i0 += 16u * kFBlock) {
+        gbt_u32x4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t i = i0 + 4u * kFBlock * k;
+            v[k] = gbt_u32x4{0u, 0u, 0u, 0u};
+            if (i < n_stage) {
+                if (w_lo + i + 3 < src_words) {
+                    v[k] = *(const gbt_u32x4 *)(src_sym + w_lo + i);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (w_lo + i + c < src_words) v[k][c] = src_sym[w_lo + i + c];
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t i = i0 + 4u * kFBlock * k;
+            if (i < n_stage) *(uint4 *)(stage + i) = make_uint4(v[k][0], v[k][1], v[k][2], v[k][3]);
+        }
+    }
     __syncthreads();
 
     const uint32_t sym_mask = (1u << bits) - 1u;
     const uint32_t fbit = job.feature * (uint32_t)bits;
-    const int n_words_tile = (tile_cap + 63) / 64;             // ballot words in use, <= kFWords
     for (int w = wave; w < n_words_tile; w += kFBlock / 64) {
         const uint32_t in_tile = (uint32_t)w * 64u + (uint32_t)lane;
         bool left = false;
@@ -515,7 +550,9 @@ __global__ __launch_bounds__(kFBlock) void part_staged_kernel(
     __syncthreads();
     const uint32_t left_base = left_base_s, right_base = right_base_s;
     const uint32_t seg_last = job.seg_begin + job.seg_len - 1u;
-    for (int w = wave; w < n_words_tile; w += kFBlock / 64) {
+#pragma unroll
+    for (int j = 0; j < kRowsPerThread; ++j) {
+        const int w = j * (kFBlock / 64) + wave;
         const uint32_t in_tile = (uint32_t)w * 64u + (uint32_t)lane;
         if (in_tile < tile_rows) {
             const uint64_t m = words[w];
@@ -528,7 +565,7 @@ __global__ __launch_bounds__(kFBlock) void part_staged_kernel(
                 q = seg_last - (right_base + rights_before_word + ((uint32_t)lane - below));
             }
             dstpos[in_tile] = q;
-            dst_gq[q] = src_gq[p0 + in_tile];
+            dst_gq[q] = pair[j];
         }
     }
     __syncthreads();
@@ -537,17 +574,25 @@ __global__ __launch_bounds__(kFBlock) void part_staged_kernel(
     int lpr = 1;   // lanes per row: the next power of two >= SW, at most 64
     while (lpr < SW && lpr < 64) lpr <<= 1;
     const int rows_per_wave = 64 / lpr;
-    const int sub = lane / lpr, k0 = lane % lpr;
-    for (uint32_t row0 = (uint32_t)wave * rows_per_wave; row0 < tile_rows; row0 += (kFBlock / 64) * rows_per_wave) {
-        const uint32_t in_tile = row0 + (uint32_t)sub;
-        if (in_tile >= tile_rows) continue;
-        const uint64_t b = sh0 + (uint64_t)in_tile * (uint64_t)src_stride_bits;
-        const uint32_t s0 = (uint32_t)(b >> 5), sh = (uint32_t)(b & 31);
-        uint32_t *d = dst_sym + (uint64_t)dstpos[in_tile] * (uint64_t)SW;
-        for (int k = k0; k < SW; k += lpr) {
-            uint32_t v = __builtin_amdgcn_alignbit(stage[s0 + k + 1], stage[s0 + k], sh);   // s0 + k + 1 < n_stage
-            if (k == SW - 1) v &= tail_mask;
-            d[k] = v;
+    const int sub = lane / lpr, k0 = lane % lpr;   // (SW <= 64: a lane copies one word of a row)
+    const uint32_t step = (uint32_t)(kFBlock / 64) * rows_per_wave;
+    for (uint32_t row0 = (uint32_t)wave * rows_per_wave + (uint32_t)sub; row0 < tile_rows; row0 += 4u * step) {
+        uint32_t at[4], lo[4], hi[4], sh[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {   // four rows' LDS reads in flight (past the end: the last row again)
+            const uint32_t in_tile = row0 + u * step < tile_rows ? row0 + u * step : tile_rows - 1u;
+            const uint64_t b = sh0 + (uint64_t)in_tile * (uint64_t)src_stride_bits;
+            const uint32_t s0 = (uint32_t)(b >> 5) + (uint32_t)(k0 < SW ? k0 : SW - 1);
+            sh[u] = (uint32_t)(b & 31);
+            at[u] = dstpos[in_tile];
+            lo[u] = stage[s0];
+            hi[u] = stage[s0 + 1];   // s0 + 1 < n_stage
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            uint32_t v = __builtin_amdgcn_alignbit(hi[u], lo[u], sh[u]);
+            if (k0 == SW - 1) v &= tail_mask;
+            if (k0 < SW && row0 + u * step < tile_rows) dst_sym[(uint64_t)at[u] * (uint64_t)SW + k0] = v;
         }
     }
 }
@@ -708,26 +753,26 @@ hipError_t gbt_launch_count2(hipStream_t s, const uint8_t *rows, int64_t stride_
 }
 
 bool gbt_partition_fused_ok(const GbtRows &dst) { return (dst.stride_bits >> 5) <= 64; }
-int gbt_partition_fused_tile(const GbtRows &dst) {
-    return (dst.stride_bits >> 5) == 4 ? kFTile : staged_tile_rows(dst.stride_bits);
+int gbt_partition_fused_tile(const GbtRows &dst, int64_t n) {
+    return fused_form(dst.stride_bits, n) ? kFTile : staged_tile_rows(dst.stride_bits, n);
 }
 
 hipError_t gbt_launch_partition_fused(hipStream_t s, const GbtRows &src, const GbtRows &dst, int bits, int row_bits,
-                                      uint32_t missing, const PartJob *jobs, int n_jobs, int total_tiles,
+                                      int64_t n, uint32_t missing, const PartJob *jobs, int n_jobs, int total_tiles,
                                       unsigned long long *cursor, const uint32_t *counts_dev) {
     if (n_jobs <= 0 || total_tiles <= 0) return hipSuccess;
     hipError_t e = counts_dev ? hipSuccess : gbt_launch_fill_u64(s, (uint64_t *)cursor, 0, n_jobs);
     if (e != hipSuccess) return e;
     const int SW = (int)(dst.stride_bits >> 5);
     const bool aligned_src = src.stride_bits == 128 && ((uintptr_t)src.sym & 15u) == 0;
-    if (SW == 4 && src.stride_bits <= 128)
+    if (fused_form(dst.stride_bits, n) && src.stride_bits <= 128)
         part_fused_kernel<<<total_tiles, kFBlock, 0, s>>>(src.sym, src.stride_bits, src.n_words, aligned_src,
                                                                 dst.sym_rw, SW, row_bits, bits, missing,
                                                                 (const int2 *)src.gq, (int2 *)dst.gq_rw, jobs, n_jobs,
                                                                 cursor, counts_dev);
     else {
-        const int cap = staged_tile_rows(dst.stride_bits);
-        const size_t lds = ((((size_t)cap * (size_t)src.stride_bits + 31) >> 5) + 2 + (size_t)cap) * 4;
+        const int cap = gbt_partition_fused_tile(dst, n);
+        const size_t lds = (((((size_t)cap * (size_t)src.stride_bits + 31) >> 5) + 2 + 3) / 4 * 4 + (size_t)cap) * 4;
         GbtLdsGuard lds_guard(lds);
         if (lds_guard.needed) {
             e = hipFuncSetAttribute((const void *)part_staged_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -13,22 +13,23 @@ pytestmark = pytest.mark.gpu
 TREE_KEYS = ("feature", "bin", "default_left", "left", "right", "n_rows", "threshold", "weight", "gain", "sumG", "sumH")
 
 
-def _context(planned):
+def _context(**env):
     import paper_1806_11248_amd as g
-    key = "GBT_TUNE_PLAN"
-    old = os.environ.pop(key, None)
-    os.environ[key] = "1" if planned else "0"
+    old = {k: os.environ.get(k) for k in env}
+    os.environ.update(env)
     try:
         return g.Context(0)
     finally:
-        del os.environ[key]
-        if old is not None:
-            os.environ[key] = old
+        for k, v in old.items():
+            if v is None:
+                del os.environ[k]
+            else:
+                os.environ[k] = v
 
 
 @pytest.fixture(scope="module")
 def contexts():
-    pair = _context(True), _context(False)
+    pair = _context(GBT_TUNE_PLAN="1"), _context(GBT_TUNE_PLAN="0")
     yield pair
     for c in pair:
         c.close()
@@ -121,3 +122,47 @@ def test_planned_sparse_growth_equals_growth_planned_on_the_host(contexts, n, F,
         _same_tree(a[0], b[0], "sparse")
         for k in (1, 2):
             assert (a[k] is None) == (b[k] is None) and (a[k] is None or torch.equal(a[k], b[k])), k
+
+
+# Byte symbols of at most 16 features: few rows are planned on the device and moved (path 1), many take the passes that
+# partition and build histograms at once, which the host plans (path 2, here for every size with GBT_TUNE_PLAN=0).
+FEW = [
+    (50, 13, 256, 0.0, 4, "noise"),
+    (4_095, 4, 256, 0.0, 6, "noise"),
+    (20_011, 13, 256, 0.0, 8, "noise"),
+    (70_001, 16, 255, 0.1, 7, "noise"),
+    (150_001, 13, 256, 0.0, 9, "noise"),
+    (9_000, 5, 250, 0.0, 11, "noise"),
+]
+
+
+@pytest.mark.parametrize("env", [{}, {"GBT_TUNE_PART_NOMOVE": "0"}, {"GBT_TUNE_PART_NOMOVE": "1"}, {"GBT_TUNE_PART_CYCLE": "0"},
+                                 {"GBT_TUNE_HIST8": "0"}])
+def test_few_rows_of_bytes_equal_the_fused_passes(contexts, env):
+    import paper_1806_11248_amd as g
+    other = _context(GBT_TUNE_PLAN="0", **env)
+    try:
+        for n, F, B, miss, depth, labels in FEW:
+            print(f"few rows of bytes n={n} F={F} B={B} missing={miss} depth={depth} {env}", flush=True)
+            X, y = _data(n, F, miss, labels)
+            params = g.make_params(max_depth=depth, max_bins=B, eta=0.3, objective="logistic")
+            y = (y > 0).float()
+            cuts, nb, packed, bits, _, ms = other.quantise_packed(X, max_bins=B)
+            if n > 1000:
+                assert bits == 8
+            seen = []
+            for c in (contexts[0], other):
+                margin, trees = torch.zeros(n, device="cuda"), []
+                for _ in range(2):
+                    gpair = torch.empty((n, 2), device="cuda")
+                    trees.append(c.boost_round(packed, bits, n, F, ms, nb, cuts, y, margin, margin, gpair, params))
+                full = c.grow_tree(packed, bits, n, F, ms, nb, cuts, gpair, params)
+                torch.cuda.synchronize()
+                seen.append((trees, margin, full))
+            (ta, ma, fa), (tb, mb, fb) = seen
+            for k in range(2):
+                _same_tree(ta[k], tb[k], k)
+            _same_tree(fa[0], fb[0], "full")
+            assert torch.equal(ma, mb) and torch.equal(fa[1], fb[1]) and torch.equal(fa[2], fb[2])
+    finally:
+        other.close()
