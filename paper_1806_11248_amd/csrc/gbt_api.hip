@@ -487,17 +487,24 @@ extern "C" int32_t gbt_gradients(gbt_ctx *ctx, int32_t objective, const float *m
 // ------------------------------------------------------- fixed-point gpair --
 // The scales alone (one pass for the largest |g| and h; synchronises).
 // uniform_h (may be NULL): receives 1 and the common value when every row has the same |h| (n >= 1), else 0.
-// bounds_dev (may be NULL): the four words gbt_launch_absmax would find, already on the device (left there by
-// gbt_launch_gradients when the same call made the pairs)
-static int32_t gpair_scale_impl(gbt_ctx *ctx, const float *gpair, int64_t n, double *scale, void *ws,
-                                int *uniform_h = nullptr, float *h_value = nullptr, const uint32_t *bounds_dev = nullptr) {
-    if (!bounds_dev) GBT_HIP(ctx, gbt_launch_absmax(ctx->stream, gpair, n, (uint32_t *)ws));
-    const int stride = bounds_dev ? kBoundsStride : 1;   // (gbt_launch_gradients keeps its four words on lines of their own)
-    GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), bounds_dev ? (const void *)bounds_dev : (const void *)ws, (3 * stride + 1) * 4,
-                                hipMemcpyDeviceToHost, ctx->stream));
+// bounds (may be NULL): the bounds of the pairs are on their way into the read-back buffer already (gbt_launch_gradients, when
+// the same call made the pairs), so many slots of them; they are never read from anywhere else.
+static int32_t gpair_scale_impl(gbt_ctx *ctx, const float *gpair, int64_t n, double *scale,
+                                int *uniform_h = nullptr, float *h_value = nullptr, const int *bounds = nullptr) {
+    int n_slots = 0;
+    if (bounds)
+        n_slots = *bounds;
+    else
+        GBT_HIP(ctx, gbt_launch_absmax(ctx->stream, gpair, n, rb(ctx), &n_slots));
     GBT_SYNC(ctx);
-    uint32_t bits2[4];
-    for (int k = 0; k < 4; ++k) memcpy(&bits2[k], rb(ctx) + (size_t)k * stride * 4, 4);
+    uint32_t bits2[4] = {0, 0, 0, 0xffffffffu};
+    const uint32_t *slot = (const uint32_t *)rb(ctx);
+    for (int k = 0; k < n_slots; ++k, slot += 4) {
+        bits2[0] = std::max(bits2[0], slot[0]);
+        bits2[1] = std::max(bits2[1], slot[1]);
+        bits2[2] |= slot[2];
+        bits2[3] = std::min(bits2[3], slot[3]);
+    }
     GBT_REQUIRE(ctx, bits2[0] < 0x7f800000u && bits2[1] < 0x7f800000u, GBT_EINVAL,
                 "gradient pairs contain a non-finite value");
     GBT_REQUIRE(ctx, bits2[2] == 0, GBT_EINVAL, "gradient pairs contain a negative hessian");
@@ -507,18 +514,20 @@ static int32_t gpair_scale_impl(gbt_ctx *ctx, const float *gpair, int64_t n, dou
     scale[0] = fixed_scale(mg, kGBits);
     scale[1] = fixed_scale(mh, kHBits);
     if (uniform_h) {
-        *uniform_h = n >= 1 && ~bits2[3] == bits2[1];   // smallest |h| == largest |h| (and none is negative)
+        *uniform_h = n >= 1 && bits2[3] == bits2[1];   // smallest |h| == largest |h| (and none is negative)
         if (h_value) *h_value = mh;
     }
     return GBT_OK;
 }
 
-static int32_t gpair_fixed_impl(gbt_ctx *ctx, const float *gpair, int64_t n, int32_t *gq, double *scale,
-                                void *ws, int64_t *sums_dev /* may be NULL */) {
-    int32_t st = gpair_scale_impl(ctx, gpair, n, scale, ws);
-    if (st != GBT_OK) return st;
-    GBT_HIP(ctx, gbt_launch_to_fixed(ctx->stream, gpair, n, scale[0], scale[1], gq, sums_dev));
-    return GBT_OK;
+// the totals of partial sums the stream has left in the read-back buffer (waited for)
+static void add_sum_slots(const char *slots, int n_slots, int64_t out[2]) {
+    const int64_t *p = (const int64_t *)slots;
+    out[0] = out[1] = 0;
+    for (int k = 0; k < n_slots; ++k) {
+        out[0] += p[2 * k];
+        out[1] += p[2 * k + 1];
+    }
 }
 
 extern "C" int32_t gbt_gpair_fixed(gbt_ctx *ctx, const float *gpair, int64_t n, int32_t *gq_out,
@@ -527,8 +536,9 @@ extern "C" int32_t gbt_gpair_fixed(gbt_ctx *ctx, const float *gpair, int64_t n, 
     GBT_REQUIRE(ctx, gpair && gq_out && scale_out && workspace, GBT_EINVAL, "NULL argument");
     GBT_REQUIRE(ctx, n >= 0, GBT_EINVAL, "n < 0");
     GBT_REQUIRE(ctx, workspace_bytes >= 4096, GBT_ENOMEM, "workspace < 4096 bytes");
-    int32_t st = gpair_fixed_impl(ctx, gpair, n, gq_out, scale_out, workspace, nullptr);
+    int32_t st = gpair_scale_impl(ctx, gpair, n, scale_out);
     if (st != GBT_OK) return st;
+    GBT_HIP(ctx, gbt_launch_to_fixed(ctx->stream, gpair, n, scale_out[0], scale_out[1], gq_out, nullptr, nullptr));
     GBT_SYNC(ctx);
     return GBT_OK;
 }
@@ -539,10 +549,10 @@ extern "C" int32_t gbt_sum_gpair(gbt_ctx *ctx, const int32_t *gq, const uint32_t
     GBT_REQUIRE(ctx, gq && sums_out && workspace, GBT_EINVAL, "NULL argument");
     GBT_REQUIRE(ctx, n_rows >= 0, GBT_EINVAL, "n_rows < 0");
     GBT_REQUIRE(ctx, workspace_bytes >= 4096, GBT_ENOMEM, "workspace < 4096 bytes");
-    GBT_HIP(ctx, gbt_launch_sum_gq(ctx->stream, gq, row_idx, n_rows, (int64_t *)workspace));
-    GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), workspace, 16, hipMemcpyDeviceToHost, ctx->stream));
+    int n_slots = 0;
+    GBT_HIP(ctx, gbt_launch_sum_gq(ctx->stream, gq, row_idx, n_rows, rb(ctx), &n_slots));
     GBT_SYNC(ctx);
-    memcpy(sums_out, rb(ctx), 16);
+    add_sum_slots(rb(ctx), n_slots, sums_out);
     return GBT_OK;
 }
 
@@ -616,14 +626,13 @@ extern "C" int32_t gbt_eval_split(gbt_ctx *ctx, const int64_t *hist, const int32
     nd.Gq = Gq;
     nd.Hq = Hq;
     nd.parent_off = nd.built_off = GBT_NO_HIST;
-    char *ws = (char *)workspace;
-    st = upload(ctx, &nd, sizeof nd, ws);
+    // one node and a few records: read and written where the host has them
+    char *node;
+    st = stage(ctx, &nd, sizeof nd, &node);
     if (st != GBT_OK) return st;
-    gbt_split *dsplit = (gbt_split *)(ws + 256);
-    const int chunks = gbt_eval_chunks(F, 1, workspace_bytes - 256);
-    GBT_HIP(ctx, gbt_launch_eval(ctx->stream, const_cast<int64_t *>(hist), (const EvalNode *)ws, 1, nb, F, B, chunks, 1.0 / scale[0],
-                                 1.0 / scale[1], params->lambda, params->min_child_weight, dsplit));
-    GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), dsplit, chunks * sizeof(gbt_split), hipMemcpyDeviceToHost, ctx->stream));
+    const int chunks = gbt_eval_chunks(F, 1, GBT_STAGING_BYTES - kReadbackOff);
+    GBT_HIP(ctx, gbt_launch_eval(ctx->stream, const_cast<int64_t *>(hist), (const EvalNode *)node, 1, nb, F, B, chunks, 1.0 / scale[0],
+                                 1.0 / scale[1], params->lambda, params->min_child_weight, (gbt_split *)rb(ctx)));
     GBT_SYNC(ctx);
     *split_out = merge_chunks((const gbt_split *)rb(ctx), chunks);
     return GBT_OK;
@@ -664,15 +673,15 @@ int32_t partition_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int64
     job.tile_begin = 0;
     job.n_tiles = (uint32_t)((len + GBT_PART_TILE - 1) / GBT_PART_TILE);
     job.pad = 0;
-    int32_t st = upload(ctx, &job, sizeof job, ws + L.jobs);
+    char *job_at;   // (one job: the kernels read it where the host has it)
+    int32_t st = stage(ctx, &job, sizeof job, &job_at);
     if (st != GBT_OK) return st;
     uint32_t *seg = row_idx + begin;
-    GBT_HIP(ctx, gbt_launch_partition(ctx->stream, packed, bits, (int64_t)F * bits, n, (uint32_t)missing_sym, seg,
-                                      (uint32_t *)(ws + L.dst), (const PartJob *)(ws + L.jobs), 1,
-                                      (int)job.n_tiles, (uint64_t *)(ws + L.masks),
-                                      (uint32_t *)(ws + L.tile_left), (uint32_t *)(ws + L.n_left)));
-    GBT_HIP(ctx, hipMemcpyAsync(seg, ws + L.dst, (size_t)len * 4, hipMemcpyDeviceToDevice, ctx->stream));
-    GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), ws + L.n_left, 4, hipMemcpyDeviceToHost, ctx->stream));
+    memset(rb(ctx), 0, 4);   // (an empty segment launches nothing)
+    GBT_HIP(ctx, gbt_launch_partition(ctx->stream, packed, bits, (int64_t)F * bits, n, (uint32_t)missing_sym, seg, seg,
+                                      (const PartJob *)job_at, 1, (int)job.n_tiles, (uint64_t *)(ws + L.masks),
+                                      (uint32_t *)(ws + L.tile_left), (uint32_t *)(ws + L.n_left), nullptr,
+                                      (uint32_t *)(ws + L.dst), (uint32_t *)rb(ctx)));
     GBT_SYNC(ctx);
     uint32_t nl;
     memcpy(&nl, rb(ctx), 4);
@@ -895,7 +904,7 @@ GrowLayout grow_layout_nodes(int64_t n, int F, int bits, int B, int64_t hist_nod
     L.pool = o;       o += gbt_align((size_t)L.hist_nodes * F * B * 16);
     L.eval_nodes = o; o += gbt_align((size_t)L.level_nodes * 2 * sizeof(EvalNode));
     L.jobs = o;       o += gbt_align(kUploadBytes);
-    L.scratch = o;    o += 4096;
+    L.scratch = o;    o += gbt_align((size_t)gbt_red_slots_max() * 16);
     // room to stage the finished tree for a walk (as gbt_predict_workspace_bytes counts it); a tree has
     // at most 2 * hist_nodes + 1 nodes under either policy
     const size_t cap_nodes = (size_t)(2 * hist_nodes + 1);
@@ -1141,10 +1150,10 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
                          const gbt_params *params, int policy, int32_t max_leaves, gbt_tree *tree,
                          uint32_t *row_idx_out, int32_t *leaf_of_row_out, void *workspace, size_t workspace_bytes,
                          float *margin_update = nullptr, const float *margin_src = nullptr,
-                         const uint32_t *bounds_dev = nullptr) {
+                         const int *bounds = nullptr) {
     // margin_update (may be NULL): margin_update[r] = margin_src[r] + eta * (weight of r's leaf), by a walk of the
     // finished tree (margin_src NULL: margin_update itself)
-    // bounds_dev (may be NULL): see gpair_scale_impl
+    // bounds (may be NULL): see gpair_scale_impl
     if (!ctx) return GBT_EINVAL;
     int32_t st = check_matrix(ctx, packed, bits, n, F);
     if (st != GBT_OK) return st;
@@ -1235,7 +1244,8 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
     // Fixed-point gradient pairs and the root's totals: the scales need one pass over the pairs;
     // the conversion is a pass of its own, or part of the root histogram kernel where that can do it.
     double scale[2];
-    int64_t *sums_dev = (int64_t *)(ws + L.scratch + 256);
+    int64_t *sums_dev = (int64_t *)(ws + L.scratch);   // partial totals of the pairs (gbt_launch_to_fixed)
+    int n_sums = 1;
     // With a margin to update the finished tree is walked over all rows anyway; that walk can count the rows of
     // every node, so the children of the last level (leaves, of which only the row counts are wanted) need no
     // counting pass of their own.
@@ -1245,9 +1255,9 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
     int uniform_h = 0;
     float h_value = 0.0f;
     gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * (fix_in_hist ? 8.0 : 24.0));
-    st = gpair_scale_impl(ctx, gpair, n, scale, ws + L.scratch, &uniform_h, &h_value, bounds_dev);
+    st = gpair_scale_impl(ctx, gpair, n, scale, &uniform_h, &h_value, bounds);
     if (st == GBT_OK && !fix_in_hist) {
-        hipError_t e = gbt_launch_to_fixed(s, gpair, n, scale[0], scale[1], gq, sums_dev);
+        hipError_t e = gbt_launch_to_fixed(s, gpair, n, scale[0], scale[1], gq, sums_dev, &n_sums);
         if (e != hipSuccess) st = gbt_fail(ctx, GBT_EHIP, "gbt_launch_to_fixed: %s", hipGetErrorString(e));
     }
     gbt_prof_end(ctx);
@@ -1433,7 +1443,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
             gbt_prof_end(ctx);
             return GBT_OK;
         };
-        GBT_HIP(ctx, gbt_launch_plan_root(s, g.v, sums_dev, n, max_depth + 2));
+        GBT_HIP(ctx, gbt_launch_plan_root(s, g.v, sums_dev, n_sums, n, max_depth + 2));
         int n_levels = 0;
         st = planned_levels(ctx, g, partition, hist, &eval_spans, &n_levels);
         if (st != GBT_OK) return st;
@@ -1514,19 +1524,12 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
         return finish();
     }
     GBT_REQUIRE(ctx, sum_slots <= gbt_hist8_max_jobs() && (size_t)sum_slots * 16 <= kCutsRb, GBT_EHIP, "internal: partial totals");
-    GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), sum_slots ? (const void *)(ws + L.jobs) : (const void *)sums_dev,
-                                sum_slots ? (size_t)sum_slots * 16 : 16, hipMemcpyDeviceToHost, s));
+    const int n_slots = sum_slots ? sum_slots : n_sums;
+    GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), sum_slots ? (const void *)(ws + L.jobs) : (const void *)sums_dev, (size_t)n_slots * 16,
+                                hipMemcpyDeviceToHost, s));
     GBT_SYNC(ctx);
-    int64_t root_sums[2] = {0, 0};
-    if (sum_slots) {
-        const int64_t *ps = (const int64_t *)rb(ctx);
-        for (int j = 0; j < sum_slots; ++j) {
-            root_sums[0] += ps[2 * j];
-            root_sums[1] += ps[2 * j + 1];
-        }
-    } else {
-        memcpy(root_sums, rb(ctx), 16);
-    }
+    int64_t root_sums[2];
+    add_sum_slots(rb(ctx), n_slots, root_sums);
     if (cuts_via_pinned) memcpy(hcuts.data(), rb(ctx) + kCutsRb, hcuts.size() * sizeof(float));
 
     auto set_node_at = [&](int32_t at, const HNode &nd) {
@@ -2299,12 +2302,12 @@ extern "C" int32_t gbt_boost_round(gbt_ctx *ctx, const uint32_t *packed, int32_t
                          params->max_depth >= 0 && params->max_depth <= kMaxDepth, GBT_EINVAL, "bad shape");
     const GrowLayout L = grow_layout(n, F, bits, params->max_bins, params->max_depth);
     GBT_REQUIRE(ctx, workspace_bytes >= L.total, GBT_ENOMEM, "workspace %zu < %zu bytes", workspace_bytes, L.total);
-    uint32_t *bounds = (uint32_t *)((char *)workspace + L.scratch + 1024);
+    int bounds = 0;
     gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * 16.0);
-    GBT_HIP(ctx, gbt_launch_gradients(ctx->stream, params->objective, margin_in, label, n, gpair, bounds));
+    GBT_HIP(ctx, gbt_launch_gradients(ctx->stream, params->objective, margin_in, label, n, gpair, rb(ctx), &bounds));
     gbt_prof_end(ctx);
     return grow_impl(ctx, packed, bits, n, F, missing_sym, nb, cuts, gpair, params, GBT_POLICY_DEPTHWISE, 0, tree,
-                     nullptr, nullptr, workspace, workspace_bytes, margin_out, margin_in, bounds);
+                     nullptr, nullptr, workspace, workspace_bytes, margin_out, margin_in, &bounds);
 }
 
 extern "C" size_t gbt_grow_tree_lossguide_workspace_bytes(int64_t n, int32_t F, int32_t bits, int32_t max_bins,
@@ -2723,7 +2726,7 @@ SparseGrowLayout sparse_grow_layout_nodes(int64_t n, int64_t nnz, int F, int B, 
     L.pool = o;       o += gbt_align((size_t)L.hist_nodes * F * B * 16);
     L.eval_nodes = o; o += gbt_align((size_t)L.level_nodes * 2 * sizeof(EvalNode));
     L.jobs = o;       o += gbt_align(kUploadBytes);
-    L.scratch = o;    o += 4096;
+    L.scratch = o;    o += gbt_align((size_t)gbt_red_slots_max() * 16);
     const size_t cap_nodes = (size_t)(2 * L.hist_nodes + 1);
     L.tree_stage_bytes = gbt_align(64) + gbt_align(cap_nodes * 4) * 6 + gbt_align(cap_nodes * 8) + 256;
     L.tree_stage = o; o += gbt_align(L.tree_stage_bytes);
@@ -2809,11 +2812,12 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
     if (!planned) GBT_HIP(ctx, hipMemcpyAsync(hcuts.data(), cuts, hcuts.size() * sizeof(float), hipMemcpyDeviceToHost, s));
 
     double scale[2];
-    int64_t *sums_dev = (int64_t *)(ws + L.scratch + 256);
+    int64_t *sums_dev = (int64_t *)(ws + L.scratch);   // partial totals of the pairs
+    int n_sums = 1;
     gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * 24.0);
-    st = gpair_scale_impl(ctx, gpair, n, scale, ws + L.scratch);
+    st = gpair_scale_impl(ctx, gpair, n, scale);
     if (st == GBT_OK) {
-        hipError_t e = gbt_launch_to_fixed(s, gpair, n, scale[0], scale[1], gq, sums_dev);
+        hipError_t e = gbt_launch_to_fixed(s, gpair, n, scale[0], scale[1], gq, sums_dev, &n_sums);
         if (e != hipSuccess) st = gbt_fail(ctx, GBT_EHIP, "gbt_launch_to_fixed: %s", hipGetErrorString(e));
     }
     gbt_prof_end(ctx);
@@ -2940,7 +2944,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
             gbt_prof_end(ctx);
             return GBT_OK;
         };
-        GBT_HIP(ctx, gbt_launch_plan_root(s, g.v, sums_dev, n, max_depth + 2));
+        GBT_HIP(ctx, gbt_launch_plan_root(s, g.v, sums_dev, n_sums, n, max_depth + 2));
         int n_levels = 0;
         st = planned_levels(ctx, g, partition, hist, &eval_spans, &n_levels);
         if (st != GBT_OK) return st;
@@ -2964,10 +2968,10 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
         }
         return finish(tree->n_nodes);
     }
-    GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), sums_dev, 16, hipMemcpyDeviceToHost, s));
+    GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), sums_dev, (size_t)n_sums * 16, hipMemcpyDeviceToHost, s));
     GBT_SYNC(ctx);
     int64_t root_sums[2];
-    memcpy(root_sums, rb(ctx), 16);
+    add_sum_slots(rb(ctx), n_sums, root_sums);
 
     auto set_node_at = [&](int32_t at, const HNode &nd) {
         const double G = (double)nd.Gq * inv_sg, H = (double)nd.Hq * inv_sh;

@@ -269,7 +269,8 @@ struct PlanView {            // device addresses unless noted
     DevTree arrays;
     uint32_t *hint;          // host memory: splits of each level, written when they are known
 };
-hipError_t gbt_launch_plan_root(hipStream_t s, const PlanView &v, const int64_t *sums, int64_t n, int n_levels);
+// sums: n_sums partial totals of the pairs (int64[2] each)
+hipError_t gbt_launch_plan_root(hipStream_t s, const PlanView &v, const int64_t *sums, int n_sums, int64_t n, int n_levels);
 hipError_t gbt_launch_plan_split(hipStream_t s, const PlanView &v, int depth, int chunks, uint32_t tile_rows);
 // n_left: left rows of split k at n_left[k * stride] (NULL: not counted yet, the children's row counts come later)
 hipError_t gbt_launch_plan_children(hipStream_t s, const PlanView &v, int depth, int64_t max_splits, const uint32_t *n_left,
@@ -288,18 +289,19 @@ hipError_t gbt_launch_plan_finish(hipStream_t s, const PlanView &v, int n_levels
 hipError_t gbt_launch_fill_u64(hipStream_t s, uint64_t *p, uint64_t v, int64_t count);
 hipError_t gbt_launch_iota_u32(hipStream_t s, uint32_t *p, int64_t count);
 hipError_t gbt_launch_stream_read(hipStream_t s, const void *buf, int64_t bytes, uint32_t *sink);
-// out2 [dev] uint32[4]: bits of the largest |g|, of the largest |h|, 1 if some h < 0, ~(bits of the smallest |h|)
-hipError_t gbt_launch_absmax(hipStream_t s, const float *gpair, int64_t n, uint32_t *out2);
-// sums_out (may be NULL): int64[2] [dev] receiving the exact totals of gq (zeroed by the launcher).
+// Reductions over rows store one partial result of 16 bytes per workgroup into `slots` (device memory, or host memory that
+// the device can address: room for gbt_red_slots_max() of them); *n_slots receives their number.
+//   bounds  uint32[4]: bits of the largest |g|, of the largest |h|, 1 if some h < 0, bits of the smallest |h|
+//   sums    int64[2]
+int gbt_red_slots_max();
+hipError_t gbt_launch_absmax(hipStream_t s, const float *gpair, int64_t n, void *slots, int *n_slots);
+// slots (may be NULL): the sums of gq
 hipError_t gbt_launch_to_fixed(hipStream_t s, const float *gpair, int64_t n, double sg, double sh,
-                               int32_t *gq, int64_t *sums_out);
-hipError_t gbt_launch_sum_gq(hipStream_t s, const int32_t *gq, const uint32_t *row_idx, int64_t n_rows,
-                             int64_t *out2 /* zeroed by the launcher */);
-// bounds (may be NULL): 4 * kBoundsStride words, cleared here; word k * kBoundsStride receives what word k of
-// gbt_launch_absmax's output holds for these pairs
-constexpr int kBoundsStride = 32;
+                               int32_t *gq, void *slots, int *n_slots);
+hipError_t gbt_launch_sum_gq(hipStream_t s, const int32_t *gq, const uint32_t *row_idx, int64_t n_rows, void *slots, int *n_slots);
+// bounds (may be NULL): slots for the bounds of these pairs
 hipError_t gbt_launch_gradients(hipStream_t s, int objective, const float *margin, const float *label,
-                                int64_t n, float *gpair, uint32_t *bounds = nullptr);
+                                int64_t n, float *gpair, void *bounds = nullptr, int *n_slots = nullptr);
 hipError_t gbt_launch_subtract_one(hipStream_t s, const int64_t *parent, const int64_t *child,
                                    int64_t *out, int64_t count);
 hipError_t gbt_launch_export(hipStream_t s, const int64_t *hist, int64_t count, double inv_sg,
@@ -352,7 +354,10 @@ hipError_t gbt_launch_eval(hipStream_t s, int64_t *hist_pool, const EvalNode *no
 hipError_t gbt_launch_partition(hipStream_t s, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n,
                                 uint32_t missing, const uint32_t *src, uint32_t *dst,
                                 const PartJob *jobs, int n_jobs, int total_tiles, uint64_t *masks,
-                                uint32_t *tile_left, uint32_t *n_left_out, const uint32_t *counts_dev = nullptr);
+                                uint32_t *tile_left, uint32_t *n_left_out, const uint32_t *counts_dev = nullptr,
+                                // one job only: dst == src, the ids are copied to `ids` by the first pass and come back
+                                // from there; n_left_host also receives n_left
+                                uint32_t *ids = nullptr, uint32_t *n_left_host = nullptr);
 
 // A set of rows in some order: symbols (row p starts at bit p*stride_bits), fixed-point gradient
 // pairs and original row ids (NULL: the id of position p is p).  The *_rw members are the same

@@ -27,16 +27,45 @@ __global__ void iota_u32_kernel(uint32_t *p, int64_t count) {
         p[i] = (uint32_t)i;
 }
 
+// Reductions over all rows leave one partial result of 16 bytes per workgroup (at most kRedGroups of kRedBlock threads: as
+// many waves as are resident); whoever reads them (the host, from its own memory; plan_root_kernel) puts them together.
+// One atomic per workgroup on one address, some 12 ns each whatever the kernel does meanwhile, was what these launches
+// waited for: 10M pairs, absmax 78 us, to_fixed 61; 1M rows, gradients with bounds 15.6 us.
+constexpr int kRedBlock = 1024, kRedGroups = 512;
+inline int red_grid(int64_t count, int per_thread) { return grid_for(count, kRedBlock * per_thread, kRedGroups); }
+
 // max |g| and max |h| as raw float bits (non-negative floats order like their
 // bit patterns; NaN sorts above +inf, so a non-finite input is detected).
-// out2[2] becomes non-zero if any h is negative.
+// Word 2 becomes non-zero if any h is negative, word 3 is the smallest |h| as bits.
 // A thread takes kStreamBatch 16-byte loads (two pairs each) that are all issued before the
 // first is used, so that enough bytes are in flight to cover the HBM latency.
 constexpr int kStreamBatch = 4;
 // The pointers must be 16-byte aligned; `head` pairs (0 or 1) in front of them are taken singly,
 // which is how a caller's pointer that is only 8-byte aligned is served.
-// out2[3] receives ~(smallest |h| as bits), so that a zero-filled word is the neutral start of an atomicMax
-__global__ __launch_bounds__(kBlock) void absmax_kernel(const float2 *gp, int64_t n, int head, uint32_t *out2) {
+// The workgroup's (largest |g|, largest |h|, is some h negative, smallest |h|) to out[blockIdx.x]; every thread must call.
+__device__ __forceinline__ void store_bounds(uint32_t mg, uint32_t mh, uint32_t neg, uint32_t lh, uint4 *out) {
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint32_t a = __shfl_xor(mg, o), b = __shfl_xor(mh, o), c = __shfl_xor(lh, o);
+        mg = a > mg ? a : mg;
+        mh = b > mh ? b : mh;
+        lh = c < lh ? c : lh;
+        neg |= __shfl_xor(neg, o);
+    }
+    __shared__ uint4 red[kRedBlock / 64];
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = make_uint4(mg, mh, neg, lh);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) {
+            mg = max(mg, red[w].x);
+            mh = max(mh, red[w].y);
+            neg |= red[w].z;
+            lh = min(lh, red[w].w);
+        }
+        out[blockIdx.x] = make_uint4(mg, mh, neg, lh);
+    }
+}
+
+__global__ __launch_bounds__(kRedBlock) void absmax_kernel(const float2 *gp, int64_t n, int head, uint4 *out) {
     uint32_t mg = 0, mh = 0, neg = 0, lh = 0xffffffffu;
     if (head && blockIdx.x == 0 && threadIdx.x == 1) {
         const float2 v = gp[-1];
@@ -56,15 +85,15 @@ __global__ __launch_bounds__(kBlock) void absmax_kernel(const float2 *gp, int64_
         neg |= (v.y < 0.0f || v.w < 0.0f) ? 1u : 0u;
     };
     // a workgroup takes contiguous chunks of kStreamBatch * kBlock pieces; whole chunks need no conditional load
-    const int64_t chunk = (int64_t)kStreamBatch * kBlock, n_whole = n4 / chunk;
+    const int64_t chunk = (int64_t)kStreamBatch * kRedBlock, n_whole = n4 / chunk;
     for (int64_t c = blockIdx.x; c < n_whole; c += gridDim.x) {
         float4 v[kStreamBatch];
 #pragma unroll
-        for (int k = 0; k < kStreamBatch; ++k) v[k] = gp4[c * chunk + k * kBlock + threadIdx.x];
+        for (int k = 0; k < kStreamBatch; ++k) v[k] = gp4[c * chunk + k * kRedBlock + threadIdx.x];
 #pragma unroll
         for (int k = 0; k < kStreamBatch; ++k) take(v[k]);
     }
-    for (int64_t i = n_whole * chunk + (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n4; i += (int64_t)gridDim.x * kBlock)
+    for (int64_t i = n_whole * chunk + (int64_t)blockIdx.x * kRedBlock + threadIdx.x; i < n4; i += (int64_t)gridDim.x * kRedBlock)
         take(gp4[i]);
     if ((n & 1) && blockIdx.x == 0 && threadIdx.x == 0) {   // the odd last pair
         const float2 v = gp[n - 1];
@@ -73,38 +102,8 @@ __global__ __launch_bounds__(kBlock) void absmax_kernel(const float2 *gp, int64_
         lh = min(lh, __float_as_uint(v.y) & 0x7fffffffu);
         neg |= v.y < 0.0f ? 1u : 0u;
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        uint32_t a = __shfl_xor(mg, o), b = __shfl_xor(mh, o), c = __shfl_xor(lh, o);
-        mg = a > mg ? a : mg;
-        mh = b > mh ? b : mh;
-        lh = c < lh ? c : lh;
-        neg |= __shfl_xor(neg, o);
-    }
-    // one set of atomics per workgroup: atomics on one address run one after the other
-    __shared__ uint32_t red[4][kBlock / 64];
-    if ((threadIdx.x & 63) == 0) {
-        red[0][threadIdx.x >> 6] = mg;
-        red[1][threadIdx.x >> 6] = mh;
-        red[2][threadIdx.x >> 6] = neg;
-        red[3][threadIdx.x >> 6] = lh;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kBlock / 64; ++w) {
-            mg = max(mg, red[0][w]);
-            mh = max(mh, red[1][w]);
-            neg |= red[2][w];
-            lh = min(lh, red[3][w]);
-        }
-        atomicMax(&out2[0], mg);
-        atomicMax(&out2[1], mh);
-        if (neg) atomicOr(&out2[2], 1u);
-        atomicMax(&out2[3], ~lh);
-    }
+    store_bounds(mg, mh, neg, lh, out);
 }
-
-// Adds the workgroup's (g, h) to sums[0..1] with one pair of atomics (every thread must call).
-__device__ inline void block_add_i64x2(int64_t g, int64_t h, int64_t *sums);
 
 __device__ inline int64_t wave_sum_i64(int64_t v) {
     for (int o = 32; o > 0; o >>= 1) {
@@ -115,9 +114,9 @@ __device__ inline int64_t wave_sum_i64(int64_t v) {
     return v;
 }
 
-// gp and gq must be 16-byte aligned; `head` pairs (0 or 1) in front of BOTH are taken singly.
-__device__ inline void block_add_i64x2(int64_t g, int64_t h, int64_t *sums) {
-    __shared__ int64_t red[2][kBlock / 64];
+// The workgroup's (g, h) to sums[blockIdx.x]; every thread must call.
+__device__ inline void store_sums(int64_t g, int64_t h, longlong2 *sums) {
+    __shared__ int64_t red[2][kRedBlock / 64];
     g = wave_sum_i64(g);
     h = wave_sum_i64(h);
     if ((threadIdx.x & 63) == 0) {
@@ -130,13 +129,13 @@ __device__ inline void block_add_i64x2(int64_t g, int64_t h, int64_t *sums) {
             g += red[0][w];
             h += red[1][w];
         }
-        atomicAdd((unsigned long long *)&sums[0], (unsigned long long)g);
-        atomicAdd((unsigned long long *)&sums[1], (unsigned long long)h);
+        sums[blockIdx.x] = make_longlong2(g, h);
     }
 }
 
-__global__ __launch_bounds__(kBlock) void to_fixed_kernel(const float2 *gp, int64_t n, int head, double sg, double sh,
-                                                          int2 *gq, int64_t *sums) {
+// gp and gq must be 16-byte aligned; `head` pairs (0 or 1) in front of BOTH are taken singly.
+__global__ __launch_bounds__(kRedBlock) void to_fixed_kernel(const float2 *gp, int64_t n, int head, double sg, double sh,
+                                                             int2 *gq, longlong2 *sums) {
     int64_t g = 0, h = 0;
     if (head && blockIdx.x == 0 && threadIdx.x == 1) {
         const float2 v = gp[-1];
@@ -160,15 +159,15 @@ __global__ __launch_bounds__(kBlock) void to_fixed_kernel(const float2 *gp, int6
         g += (int64_t)q.x + q.z;
         h += (int64_t)q.y + q.w;
     };
-    const int64_t chunk = (int64_t)kStreamBatch * kBlock, n_whole = n4 / chunk;
+    const int64_t chunk = (int64_t)kStreamBatch * kRedBlock, n_whole = n4 / chunk;
     for (int64_t c = blockIdx.x; c < n_whole; c += gridDim.x) {
         float4 v[kStreamBatch];
 #pragma unroll
-        for (int k = 0; k < kStreamBatch; ++k) v[k] = gp4[c * chunk + k * kBlock + threadIdx.x];
+        for (int k = 0; k < kStreamBatch; ++k) v[k] = gp4[c * chunk + k * kRedBlock + threadIdx.x];
 #pragma unroll
-        for (int k = 0; k < kStreamBatch; ++k) take(c * chunk + k * kBlock + threadIdx.x, v[k]);
+        for (int k = 0; k < kStreamBatch; ++k) take(c * chunk + k * kRedBlock + threadIdx.x, v[k]);
     }
-    for (int64_t i = n_whole * chunk + (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n4; i += (int64_t)gridDim.x * kBlock)
+    for (int64_t i = n_whole * chunk + (int64_t)blockIdx.x * kRedBlock + threadIdx.x; i < n4; i += (int64_t)gridDim.x * kRedBlock)
         take(i, gp4[i]);
     if ((n & 1) && blockIdx.x == 0 && threadIdx.x == 0) {   // the odd last pair
         const float2 v = gp[n - 1];
@@ -179,14 +178,12 @@ __global__ __launch_bounds__(kBlock) void to_fixed_kernel(const float2 *gp, int6
         g += q.x;
         h += q.y;
     }
-    if (sums) {
-        block_add_i64x2(g, h, sums);
-    }
+    if (sums) store_sums(g, h, sums);
 }
 
 // One pair per load: for a source and a destination whose 16-byte alignments differ.
-__global__ __launch_bounds__(kBlock) void to_fixed_pairs_kernel(const float2 *gp, int64_t n, double sg, double sh,
-                                                                int2 *gq, int64_t *sums) {
+__global__ __launch_bounds__(kRedBlock) void to_fixed_pairs_kernel(const float2 *gp, int64_t n, double sg, double sh,
+                                                                   int2 *gq, longlong2 *sums) {
     int64_t g = 0, h = 0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const float2 v = gp[i];
@@ -197,12 +194,10 @@ __global__ __launch_bounds__(kBlock) void to_fixed_pairs_kernel(const float2 *gp
         g += q.x;
         h += q.y;
     }
-    if (sums) {
-        block_add_i64x2(g, h, sums);
-    }
+    if (sums) store_sums(g, h, sums);
 }
 
-__global__ __launch_bounds__(kBlock) void sum_gq_kernel(const int2 *gq, const uint32_t *row_idx, int64_t n_rows, int64_t *out2) {
+__global__ __launch_bounds__(kRedBlock) void sum_gq_kernel(const int2 *gq, const uint32_t *row_idx, int64_t n_rows, longlong2 *sums) {
     int64_t g = 0, h = 0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_rows;
          i += (int64_t)gridDim.x * blockDim.x) {
@@ -211,7 +206,7 @@ __global__ __launch_bounds__(kBlock) void sum_gq_kernel(const int2 *gq, const ui
         g += q.x;
         h += q.y;
     }
-    block_add_i64x2(g, h, out2);
+    store_sums(g, h, sums);
 }
 
 // Eq. 1 and Eq. 2 (logistic) and the squared-error pair, one instance per
@@ -231,11 +226,11 @@ __device__ __forceinline__ float2 gradient_pair(int objective, float margin, flo
 }
 // A thread takes four consecutive instances at a time (16-byte loads, two 16-byte stores) where the three
 // arrays are 16-byte aligned; the launcher says so.  The last n mod 4 instances are taken singly.
-// bounds (may be NULL): the four words absmax_kernel leaves for these pairs (largest |g| and |h| as bits, a flag for a
-// negative h, ~smallest |h|), reduced on the way so that the pairs need not be read again for them.
-__global__ __launch_bounds__(kBlock) void gradients_kernel(int objective, const float *__restrict__ margin,
+// bounds (may be NULL): what absmax_kernel leaves for these pairs, reduced on the way so that the pairs need not be read
+// again for them.
+__global__ __launch_bounds__(kRedBlock) void gradients_kernel(int objective, const float *__restrict__ margin,
                                                            const float *__restrict__ label, int64_t n,
-                                                           float2 *__restrict__ gp, int vec, uint32_t *bounds, int nt) {
+                                                           float2 *__restrict__ gp, int vec, uint4 *bounds, int nt) {
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, nthreads = (int64_t)gridDim.x * blockDim.x;
     uint32_t mg = 0, mh = 0, neg = 0, lh = 0xffffffffu;
     auto note = [&](const float2 &v) {
@@ -279,37 +274,8 @@ __global__ __launch_bounds__(kBlock) void gradients_kernel(int objective, const 
         gp[i] = v;
         note(v);
     }
-    if (!bounds) return;
-    for (int o = 32; o > 0; o >>= 1) {
-        uint32_t a = __shfl_xor(mg, o), b = __shfl_xor(mh, o), c = __shfl_xor(lh, o);
-        mg = a > mg ? a : mg;
-        mh = b > mh ? b : mh;
-        lh = c < lh ? c : lh;
-        neg |= __shfl_xor(neg, o);
-    }
-    __shared__ uint32_t red[4][kBlock / 64];   // one set of atomics per workgroup
-    if ((threadIdx.x & 63) == 0) {
-        red[0][threadIdx.x >> 6] = mg;
-        red[1][threadIdx.x >> 6] = mh;
-        red[2][threadIdx.x >> 6] = neg;
-        red[3][threadIdx.x >> 6] = lh;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kBlock / 64; ++w) {
-            mg = max(mg, red[0][w]);
-            mh = max(mh, red[1][w]);
-            neg |= red[2][w];
-            lh = min(lh, red[3][w]);
-        }
-        // (a word per 128-byte line: atomics on words of one line take turns like atomics on one address)
-        atomicMax(&bounds[0 * kBoundsStride], mg);
-        atomicMax(&bounds[1 * kBoundsStride], mh);
-        if (neg) atomicOr(&bounds[2 * kBoundsStride], 1u);
-        atomicMax(&bounds[3 * kBoundsStride], ~lh);
-    }
+    if (bounds) store_bounds(mg, mh, neg, lh, bounds);
 }
-
 
 __global__ void subtract_one_kernel(const int64_t *p, const int64_t *c, int64_t *o, int64_t count) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
@@ -866,51 +832,47 @@ hipError_t gbt_launch_stream_read(hipStream_t s, const void *buf, int64_t bytes,
     return hipGetLastError();
 }
 
-hipError_t gbt_launch_absmax(hipStream_t s, const float *gpair, int64_t n, uint32_t *out2) {
-    hipError_t e = gbt_launch_fill_u64(s, (uint64_t *)out2, 0, 2);
-    if (e != hipSuccess || n <= 0) return e;
+int gbt_red_slots_max() { return kRedGroups; }
+hipError_t gbt_launch_absmax(hipStream_t s, const float *gpair, int64_t n, void *slots, int *n_slots) {
+    *n_slots = 0;
+    if (n <= 0) return hipSuccess;
     const int head = (int)(((uintptr_t)gpair >> 3) & 1u);   // pairs before the first 16-byte boundary
-    absmax_kernel<<<grid_for(n, kBlock * 2 * kStreamBatch, 2048), kBlock, 0, s>>>((const float2 *)gpair + head,
-                                                                                  n - head, head, out2);
+    *n_slots = red_grid(n, 2 * kStreamBatch);
+    absmax_kernel<<<*n_slots, kRedBlock, 0, s>>>((const float2 *)gpair + head, n - head, head, (uint4 *)slots);
     return hipGetLastError();
 }
 hipError_t gbt_launch_to_fixed(hipStream_t s, const float *gpair, int64_t n, double sg, double sh,
-                               int32_t *gq, int64_t *sums_out) {
-    if (sums_out) {
-        hipError_t e = gbt_launch_fill_u64(s, (uint64_t *)sums_out, 0, 2);
-        if (e != hipSuccess) return e;
-    }
+                               int32_t *gq, void *slots, int *n_slots) {
+    if (n_slots) *n_slots = 0;
     if (n <= 0) return hipSuccess;
     const int head = (int)(((uintptr_t)gpair >> 3) & 1u);
-    if (head != (int)(((uintptr_t)gq >> 3) & 1u)) {
-        to_fixed_pairs_kernel<<<grid_for(n, kBlock * 4, 2048), kBlock, 0, s>>>((const float2 *)gpair, n, sg, sh,
-                                                                               (int2 *)gq, sums_out);
-        return hipGetLastError();
-    }
-    to_fixed_kernel<<<grid_for(n, kBlock * 2 * kStreamBatch, 2048), kBlock, 0, s>>>(
-        (const float2 *)gpair + head, n - head, head, sg, sh, (int2 *)gq + head, sums_out);
+    const bool pairs = head != (int)(((uintptr_t)gq >> 3) & 1u);
+    const int grid = red_grid(n, pairs ? 4 : 2 * kStreamBatch);
+    if (n_slots) *n_slots = grid;
+    if (pairs)
+        to_fixed_pairs_kernel<<<grid, kRedBlock, 0, s>>>((const float2 *)gpair, n, sg, sh, (int2 *)gq, (longlong2 *)slots);
+    else
+        to_fixed_kernel<<<grid, kRedBlock, 0, s>>>((const float2 *)gpair + head, n - head, head, sg, sh, (int2 *)gq + head,
+                                                   (longlong2 *)slots);
     return hipGetLastError();
 }
-hipError_t gbt_launch_sum_gq(hipStream_t s, const int32_t *gq, const uint32_t *row_idx, int64_t n_rows,
-                             int64_t *out2) {
-    hipError_t e = gbt_launch_fill_u64(s, (uint64_t *)out2, 0, 2);
-    if (e != hipSuccess || n_rows <= 0) return e;
-    sum_gq_kernel<<<grid_for(n_rows, kBlock * 8, 2048), kBlock, 0, s>>>((const int2 *)gq, row_idx, n_rows,
-                                                                        out2);
+hipError_t gbt_launch_sum_gq(hipStream_t s, const int32_t *gq, const uint32_t *row_idx, int64_t n_rows, void *slots, int *n_slots) {
+    *n_slots = 0;
+    if (n_rows <= 0) return hipSuccess;
+    *n_slots = red_grid(n_rows, 4);
+    sum_gq_kernel<<<*n_slots, kRedBlock, 0, s>>>((const int2 *)gq, row_idx, n_rows, (longlong2 *)slots);
     return hipGetLastError();
 }
 hipError_t gbt_launch_gradients(hipStream_t s, int objective, const float *margin, const float *label,
-                                int64_t n, float *gpair, uint32_t *bounds) {
-    if (bounds) {
-        hipError_t e = gbt_launch_fill_u64(s, (uint64_t *)bounds, 0, 2 * kBoundsStride);
-        if (e != hipSuccess) return e;
-    }
+                                int64_t n, float *gpair, void *bounds, int *n_slots) {
+    if (n_slots) *n_slots = 0;
     if (n <= 0) return hipSuccess;
     const int vec = ((((uintptr_t)margin | (uintptr_t)label | (uintptr_t)gpair) & 15u) == 0) ? 1 : 0;
-    // with bounds: no more workgroups than are resident at once, each ends with one set of atomics
-    gradients_kernel<<<grid_for(n, kBlock * 4, bounds ? 2048 : 8192), kBlock, 0, s>>>(objective, margin, label, n,
-                                                                      (float2 *)gpair, vec, bounds,
-                                                                      (size_t)n * sizeof(float2) > ((size_t)192 << 20) ? 1 : 0);
+    const int grid = bounds ? red_grid(n, 4) : grid_for(n, kBlock * 4, 8192);
+    if (bounds) *n_slots = grid;
+    gradients_kernel<<<grid, bounds ? kRedBlock : kBlock, 0, s>>>(objective, margin, label, n, (float2 *)gpair, vec,
+                                                                 (uint4 *)bounds,
+                                                                 (size_t)n * sizeof(float2) > ((size_t)192 << 20) ? 1 : 0);
     return hipGetLastError();
 }
 hipError_t gbt_launch_subtract_one(hipStream_t s, const int64_t *parent, const int64_t *child,

@@ -53,7 +53,8 @@ __device__ inline uint32_t load_symbol(const uint32_t *packed, uint64_t bp, int 
 __global__ __launch_bounds__(kBlock) void part_flag_kernel(
     const uint32_t *__restrict__ packed, int bits, int64_t stride_bits, int64_t n, uint32_t missing,
     const uint32_t *__restrict__ src, const PartJob *__restrict__ jobs, int n_jobs,
-    uint64_t *__restrict__ masks, uint32_t *__restrict__ tile_left, const uint32_t *__restrict__ counts_dev) {
+    uint64_t *__restrict__ masks, uint32_t *__restrict__ tile_left, const uint32_t *__restrict__ counts_dev,
+    uint32_t *__restrict__ ids_out) {   // (may be NULL) receives the segment's ids, for a scatter that writes into src
     const uint32_t tile = blockIdx.x;
     if (counts_dev) {
         if (tile >= counts_dev[1]) return;
@@ -72,6 +73,7 @@ __global__ __launch_bounds__(kBlock) void part_flag_kernel(
         if (off < job.seg_len) {
             const uint64_t p = (uint64_t)job.seg_begin + off;
             const uint64_t r = src ? (uint64_t)src[p] : p;
+            if (ids_out) ids_out[p] = (uint32_t)r;
             if (r < (uint64_t)n) {
                 const uint32_t s = load_symbol(packed, r * (uint64_t)stride_bits + (uint64_t)job.feature * bits, bits, mask);
                 left = (s == missing) ? (job.default_left != 0) : (s <= job.bin);
@@ -90,7 +92,7 @@ __global__ __launch_bounds__(kBlock) void part_flag_kernel(
 __global__ __launch_bounds__(kBlock) void part_scan_kernel(const PartJob *__restrict__ jobs,
                                                            uint32_t *__restrict__ tile_left,
                                                            uint32_t *__restrict__ n_left_out,
-                                                           const uint32_t *__restrict__ counts_dev) {
+                                                           const uint32_t *__restrict__ counts_dev, uint32_t *n_left_host) {
     if (counts_dev && blockIdx.x >= counts_dev[0]) return;
     const PartJob job = jobs[blockIdx.x];
     __shared__ uint32_t wtot[kBlock / 64];
@@ -115,7 +117,10 @@ __global__ __launch_bounds__(kBlock) void part_scan_kernel(const PartJob *__rest
         if (threadIdx.x == 0) carry_s += wtot[0] + wtot[1] + wtot[2] + wtot[3];
         __syncthreads();
     }
-    if (threadIdx.x == 0) n_left_out[blockIdx.x] = carry_s;
+    if (threadIdx.x == 0) {
+        n_left_out[blockIdx.x] = carry_s;
+        if (n_left_host) n_left_host[blockIdx.x] = carry_s;
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void part_scatter_kernel(
@@ -602,12 +607,13 @@ __global__ __launch_bounds__(kFBlock) void part_staged_kernel(
 hipError_t gbt_launch_partition(hipStream_t s, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n,
                                 uint32_t missing, const uint32_t *src, uint32_t *dst,
                                 const PartJob *jobs, int n_jobs, int total_tiles, uint64_t *masks,
-                                uint32_t *tile_left, uint32_t *n_left_out, const uint32_t *counts_dev) {
+                                uint32_t *tile_left, uint32_t *n_left_out, const uint32_t *counts_dev, uint32_t *ids,
+                                uint32_t *n_left_host) {
     if (n_jobs <= 0 || total_tiles <= 0) return hipSuccess;
     part_flag_kernel<<<total_tiles, kBlock, 0, s>>>(packed, bits, stride_bits, n, missing, src, jobs, n_jobs, masks,
-                                                    tile_left, counts_dev);
-    part_scan_kernel<<<n_jobs, kBlock, 0, s>>>(jobs, tile_left, n_left_out, counts_dev);
-    part_scatter_kernel<<<total_tiles, kBlock, 0, s>>>(src, dst, jobs, n_jobs, masks, tile_left, n_left_out, counts_dev);
+                                                    tile_left, counts_dev, ids);
+    part_scan_kernel<<<n_jobs, kBlock, 0, s>>>(jobs, tile_left, n_left_out, counts_dev, n_left_host);
+    part_scatter_kernel<<<total_tiles, kBlock, 0, s>>>(ids ? ids : src, dst, jobs, n_jobs, masks, tile_left, n_left_out, counts_dev);
     return hipGetLastError();
 }
 
@@ -618,8 +624,8 @@ hipError_t gbt_launch_partition_records(hipStream_t s, const GbtRows &src, const
     if (n_jobs <= 0 || total_tiles <= 0) return hipSuccess;
     if (counts_dev && what != GBT_PART_COUNT) return hipErrorInvalidValue;   // (only the count is planned on the device)
     part_flag_kernel<<<total_tiles, kBlock, 0, s>>>(src.sym, bits, src.stride_bits, n, missing, nullptr, jobs, n_jobs,
-                                                    masks, tile_left, counts_dev);
-    part_scan_kernel<<<n_jobs, kBlock, 0, s>>>(jobs, tile_left, n_left_out, counts_dev);
+                                                    masks, tile_left, counts_dev, nullptr);
+    part_scan_kernel<<<n_jobs, kBlock, 0, s>>>(jobs, tile_left, n_left_out, counts_dev, nullptr);
     if (what == GBT_PART_COUNT) return hipGetLastError();
     if (what == GBT_PART_IDS) {
         part_move_ids_kernel<<<total_tiles, kBlock, 0, s>>>(src.id, dst.id_rw, jobs, n_jobs, masks, tile_left,

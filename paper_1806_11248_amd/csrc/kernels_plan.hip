@@ -52,7 +52,15 @@ __device__ __forceinline__ void set_leaf(const PlanView &v, uint32_t id, int64_t
     ((double *)(t + T.weight))[id] = H + v.lambda > 0.0 ? -G / (H + v.lambda) : 0.0;
 }
 
-__global__ __launch_bounds__(64) void plan_root_kernel(PlanView v, const int64_t *__restrict__ sums, uint32_t n_rows, int n_levels) {
+__global__ __launch_bounds__(64) void plan_root_kernel(PlanView v, const int64_t *__restrict__ sums, int n_sums, uint32_t n_rows,
+                                                       int n_levels) {
+    int64_t G = 0, H = 0;
+    for (int i = threadIdx.x; i < n_sums; i += 64) {
+        G += sums[2 * i];
+        H += sums[2 * i + 1];
+    }
+    G = last_lane_i64(wave_scan_i64(G));
+    H = last_lane_i64(wave_scan_i64(H));
     for (int d = threadIdx.x; d < n_levels; d += 64) {
         PlanLevel l{};
         if (d == 0) l.n_nodes = 1;
@@ -61,8 +69,8 @@ __global__ __launch_bounds__(64) void plan_root_kernel(PlanView v, const int64_t
     if (threadIdx.x == 0) {
         PlanNode nd{};
         nd.len = n_rows;
-        nd.Gq = sums[0];
-        nd.Hq = sums[1];
+        nd.Gq = G;
+        nd.Hq = H;
         nd.feature = -1;
         nd.left = -1;
         v.nodes[0] = nd;
@@ -369,8 +377,8 @@ __global__ __launch_bounds__(256) void plan_finish_kernel(PlanView v, int n_leve
 
 }  // namespace
 
-hipError_t gbt_launch_plan_root(hipStream_t s, const PlanView &v, const int64_t *sums, int64_t n, int n_levels) {
-    plan_root_kernel<<<1, 64, 0, s>>>(v, sums, (uint32_t)n, n_levels);
+hipError_t gbt_launch_plan_root(hipStream_t s, const PlanView &v, const int64_t *sums, int n_sums, int64_t n, int n_levels) {
+    plan_root_kernel<<<1, 64, 0, s>>>(v, sums, n_sums, (uint32_t)n, n_levels);
     return hipGetLastError();
 }
 hipError_t gbt_launch_plan_split(hipStream_t s, const PlanView &v, int depth, int chunks, uint32_t tile_rows) {
