@@ -2345,6 +2345,7 @@ struct BatchLayout {
 BatchLayout batch_layout(size_t base, int64_t total_nodes, int32_t n_trees) {
     BatchLayout L;
     size_t o = base;
+    total_nodes += n_trees;   // (a tree may start one place further on)
     L.nodes = o;      o += gbt_align((size_t)total_nodes * 8);
     L.wts = o;        o += gbt_align((size_t)total_nodes * 8);
     L.tree_off = o;   o += gbt_align((size_t)(n_trees + 1) * 4);
@@ -2444,11 +2445,11 @@ static int32_t predict_impl(gbt_ctx *ctx, const gbt_tree *trees, int32_t n_trees
     }
     // Several trees on raw floats: one pass over the rows with the trees taken through LDS in groups
     // (needs right == left + 1 and children after parents, which grown trees have).
-    if (may_batch && compact_ok && ordered && F < 65536 && max_nodes <= 32767) {
+    if (may_batch && compact_ok && ordered && F <= kBatchColsMax && max_nodes < kBatchNodesMax) {
         // (1536 nodes beside the rows leave a compute unit three workgroups of a 28-feature tile: 0.267 ms for 1M rows and
         // 100 trees; 700 nodes 0.33, 1024 0.28, 2560 0.28)
         const size_t tile = gbt_predict_batch_tile_bytes(F);
-        const int cap_nodes = std::max(tile + (size_t)1536 * 8 <= ctx->lds_per_block ? 1536 : 1, max_nodes);
+        const int cap_nodes = std::max(tile + (size_t)1536 * 8 <= ctx->lds_per_block ? 1536 : 2, (max_nodes + 2) & ~1);
         const size_t lds = tile + (size_t)cap_nodes * 8;
         int64_t steps = n_trees;
         for (int t = 0; t < n_trees; ++t) steps += depths[(size_t)t];
@@ -2468,32 +2469,58 @@ static int32_t predict_impl(gbt_ctx *ctx, const gbt_tree *trees, int32_t n_trees
             gbt_batch_node *bn = (gbt_batch_node *)(img + BL.nodes);
             double *bw = (double *)(img + BL.wts);
             int32_t *off = (int32_t *)(img + BL.tree_off), *grp = (int32_t *)(img + BL.group_end);
+            std::vector<int32_t> place;
             int64_t run = 0;
             int in_group = 0, n_groups = 0;
             for (int t = 0; t < n_trees; ++t) {
                 const gbt_tree &T = trees[t];
-                if (in_group + T.n_nodes > cap_nodes) {   // the group is full: it ends before this tree
+                if ((in_group | 1) + T.n_nodes > cap_nodes) {   // the group is full: it ends before this tree
                     grp[n_groups++] = t;
                     in_group = 0;
                 }
+                // A tree's nodes stand in their own order from an odd place of the group on: pairs of children are allocated
+                // behind the root, so a left child's id is odd and its place even.  (A tree with other ids is numbered anew.)
+                if ((in_group & 1) == 0) {
+                    ++in_group;
+                    bn[run] = gbt_batch_node{INT32_MAX, 1u};
+                    bw[run++] = 0.0;
+                }
+                const uint32_t base = (uint32_t)in_group;   // of this tree's nodes inside the group
+                bool odd = true;
+                for (int i = 0; i < T.n_nodes; ++i) odd = odd && (T.feature[i] < 0 || (T.left[i] & 1));
+                place.clear();
+                if (!odd) {
+                    place.assign((size_t)T.n_nodes, -1);
+                    place[0] = 0;
+                    int next = 1;
+                    for (int i = 0; i < T.n_nodes; ++i)
+                        if (T.feature[i] >= 0 && place[(size_t)i] >= 0) {
+                            place[(size_t)T.left[i]] = next;
+                            place[(size_t)T.right[i]] = next + 1;
+                            next += 2;
+                        }
+                }
+                auto at = [&](int i) { return odd ? i : place[(size_t)i]; };
                 in_group += T.n_nodes;
                 off[t] = (int32_t)run;
                 for (int i = 0; i < T.n_nodes; ++i) {
+                    const int to = at(i);
+                    if (to < 0) continue;   // (no walk reaches it; in a tree numbered anew)
                     gbt_batch_node q;
                     if (T.feature[i] < 0) {
                         q.thr = INT32_MAX;
-                        q.meta = (uint32_t)i | (1u << 15);
+                        q.meta = 1u | ((base + (uint32_t)to) << 3);
                     } else {
                         const uint32_t a = T.default_left[i] ? 1u : 0u;
                         q.thr = batch_threshold(T.threshold[i], a);
-                        q.meta = (uint32_t)T.left[i] | (a << 15) | ((uint32_t)T.feature[i] << 16);
+                        q.meta = a | ((base + (uint32_t)at(T.left[i])) << 3) | ((uint32_t)T.feature[i] << 18);
                     }
-                    bn[run + i] = q;
-                    bw[run + i] = eta * T.weight[i];
+                    bn[run + to] = q;
+                    bw[run + to] = eta * T.weight[i];
                 }
                 run += T.n_nodes;
             }
-            off[n_trees] = (int32_t)run;
+            off[n_trees] = (int32_t)run + 1;   // (as if another group followed)
             grp[n_groups++] = n_trees;
             memcpy(img + BL.tree_depth, depths.data(), depths.size() * 4);
             char *wsb = (char *)workspace;

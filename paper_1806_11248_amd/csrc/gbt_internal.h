@@ -547,14 +547,16 @@ bool gbt_predict_counts_ok(bool packed, int bits, int F, int max_nodes, bool com
 
 // Many trees on raw floats in one pass over the rows (kernels_misc.hip).  A node is 8 bytes: values are compared as
 // integers in the floats' order (NaN the largest), "right" iff value + a >= thr with a = the node's default_left, and
-// meta = left child's id inside its tree (15 bits) | a << 15 | feature << 16; a leaf leads to itself (thr = the
-// largest integer, a = 1, left = its own id).  wts: eta * weight of every node.  tree_off[t] = first node of
-// tree t in nodes / wts (tree_off[n_trees] = total); group_end[g] = one past the last tree of group g; no group has
+// meta = a | the left child's byte offset from the group's first node (bits 4..17: a left child stands at an even place,
+// so that the right one is 8 | that) | feature << 18; a leaf leads to itself (thr = the largest integer, a = 1, bit 3 as
+// its own place has it).  wts: eta * weight of every node.  tree_off[t] = first node of
+// tree t in nodes / wts, an odd place of its group (tree_off[n_trees] = all places + 1); group_end[g] = one past the last tree of group g; no group has
 // more than cap_nodes nodes; gbt_predict_batch_tile_bytes(F) + 8 * cap_nodes bytes of LDS per workgroup.
 struct gbt_batch_node {
     int32_t thr;
     uint32_t meta;
 };
+constexpr int kBatchNodesMax = 1 << 15, kBatchColsMax = 1 << 14;   // what the fields of meta hold
 int gbt_predict_batch_rows(int F);
 size_t gbt_predict_batch_tile_bytes(int F);
 hipError_t gbt_launch_predict_raw_batched(hipStream_t s, const gbt_batch_node *nodes, const double *wts,

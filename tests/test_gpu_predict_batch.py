@@ -142,3 +142,51 @@ def test_few_trees_on_wide_rows_cost_no_more_than_one_by_one(ctx):
     print("wide rows, two trees", flush=True)
     together, single = fastest([trees]), fastest([[t] for t in trees])
     assert together < 2 * single, (together, single)
+
+
+def _made_tree(rng, F, n_splits, numbering):
+    """A tree of n_splits splits made by hand.  numbering: where the pairs of children stand, "dense" (odd left ids, as
+    grown trees have them), "gap" (an unused node behind the root: even left ids) or "mixed" (unused nodes in between)."""
+    import paper_1806_11248_amd as g
+    cap = 2 * n_splits + 1 + (0 if numbering == "dense" else n_splits + 1)
+    t = {k: np.zeros(cap, v.dtype) for k, v in g.new_tree(0).items() if isinstance(v, np.ndarray)}
+    t["feature"][:] = -1
+    t["left"][:] = t["right"][:] = -1
+    t["threshold"][:] = np.inf
+    t["weight"][:] = rng.normal(0, 1, cap)
+    open_, at = [0], 1 if numbering == "dense" else 2
+    for _ in range(n_splits):
+        i = open_.pop(rng.integers(0, len(open_)))
+        if numbering == "mixed":
+            at += int(rng.integers(0, 2))
+        t["feature"][i], t["left"][i], t["right"][i] = rng.integers(0, F), at, at + 1
+        t["threshold"][i] = np.float32(rng.choice([rng.normal(), 0.0, -0.0, 1e30]))
+        t["default_left"][i] = rng.integers(0, 2)
+        open_ += [at, at + 1]
+        at += 2
+    # children have to come after their parents for the one-pass form: they do, pairs are handed out in order
+    t["n_nodes"], t["capacity"] = at, cap
+    return t
+
+
+@pytest.mark.parametrize("numbering", ["dense", "gap", "mixed"])
+@pytest.mark.parametrize("sizes", [[3, 1, 0, 2], [766, 767, 768], [700, 60, 6, 1], [100] * 16, [2500, 5, 2500]])
+@pytest.mark.parametrize("miss", [0.0, 0.1])
+def test_groups_of_trees_and_their_numbering(ctx, oracle, numbering, sizes, miss):
+    """Groups that end at, before and behind the 1536 places they have, trees of one node, ids with gaps; tiles of rows with
+    and without a missing value."""
+    rng = np.random.default_rng(sum(sizes) + len(numbering))
+    F, n = 9, 700
+    trees = [_made_tree(rng, F, k, numbering) for k in sizes]
+    print(f"groups sizes={sizes} {numbering} missing={miss}", flush=True)
+    Z = rng.standard_normal((n, F)).astype(np.float32)
+    Z[rng.random(Z.shape) < 0.02] = np.inf
+    Z[rng.random(Z.shape) < 0.05] = 0.0
+    if miss:
+        Z[:300][rng.random((300, F)) < miss] = np.nan   # (the rows behind are tiles without a missing value)
+    start = rng.standard_normal(n).astype(np.float32)
+    ref = start.copy()
+    for t in trees:
+        ref = oracle.predict_raw(t, Z, 0.3, ref)
+    got = ctx.predict(trees, dev(start), 0.3, X=dev(Z)).cpu().numpy()
+    assert np.array_equal(got, ref)
