@@ -1395,7 +1395,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
         g.tile_rows[0] = path == 1 ? (uint32_t)gbt_partition_fused_tile(W[0], n) : (uint32_t)GBT_PART_TILE;
         g.tile_rows[1] = GBT_PART_TILE;
         g.n_left[0] = path == 1 ? (const uint32_t *)(ws + L.state) : (const uint32_t *)(ws + L.n_left);
-        g.n_left_stride[0] = path == 1 ? 2 : 1;
+        g.n_left_stride[0] = path == 1 ? 2 * kCursorStride : 1;
         g.n_left[1] = (const uint32_t *)(ws + L.n_left);
         g.n_left_stride[1] = 1;
         g.nb = nb;
@@ -1422,7 +1422,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
                                                   (uint32_t *)(ws + L.tile_left), n_left32, counts));
             } else if (!last) {
                 GBT_HIP(ctx, gbt_launch_partition_fused(s, cur, dst, bits, row_bits, n, (uint32_t)missing_sym, g.v.pjobs, (int)splits,
-                                                        (int)tiles, g.v.cursors, counts));
+                                                        (int)tiles, g.v.cursors, kCursorStride, counts));
             } else {
                 GBT_HIP(ctx, gbt_launch_partition_records(s, cur, dst, bits, row_bits, n, (uint32_t)missing_sym, GBT_PART_COUNT,
                                                           g.v.pjobs, (int)splits, (int)tiles, (uint64_t *)(ws + L.masks),
@@ -1729,6 +1729,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
             child_depth < max_depth && (!lossguide || n_leaves + 1 < max_leaves);
         const bool unordered = path == 1 || path == 2;
         const bool fused = children_need_hist && unordered;
+        const int fused_stride = sel_nodes.size() <= 1024 ? kCursorStride : 1;   // (the read-back buffer holds so many lines)
         const bool in_place = sel_nodes[0].virt >= 0;   // this level's nodes were not moved when they were made
         // Rows that have stayed in place for two levels (their nodes are grandchildren of the segment they lie in) are
         // put in order again by a pass of its own, without a histogram: one child of each is then built from its
@@ -2078,9 +2079,9 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
             } else if (fused) {
                 GBT_HIP(ctx, gbt_launch_partition_fused(s, cur, W[wnext], bits, row_bits, n, (uint32_t)missing_sym,
                                                         (const PartJob *)(ws + L.jobs), (int)pjobs.size(),
-                                                        (int)tile_cursor, (unsigned long long *)(ws + L.state)));
+                                                        (int)tile_cursor, (unsigned long long *)(ws + L.state), fused_stride));
                 cursors_zero = false;
-                GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), ws + L.state, pjobs.size() * 8, hipMemcpyDeviceToHost, s));
+                GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), ws + L.state, pjobs.size() * 8 * fused_stride, hipMemcpyDeviceToHost, s));
                 gbt_prof_end(ctx);
             } else if (path == 3) {
                 // stable partition of the nodes' id lists; the symbols are gathered from the caller's matrix
@@ -2100,7 +2101,8 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
                 gbt_prof_end(ctx);
             }
             GBT_SYNC(ctx);
-            const int nl_stride = fused ? 2 : 1;   // the one-launch form returns 64-bit cursors, n_left in the low half
+            // (the one-launch form returns 64-bit cursors, n_left in the low half)
+            const size_t nl_stride = with_hist ? 2 : fused ? 2 * (size_t)fused_stride : 1;
             const uint32_t *n_left = (const uint32_t *)rb(ctx);
             for (size_t k = 0; k < pjobs.size(); ++k)   // (two-histogram pass: cursor 2 * job + child, 64 bits each)
                 nl_of[k] = nomove2 ? n_left[2 * (2 * job_of[k] + (sel_nodes[k].vpos - 1))] : n_left[k * nl_stride];
@@ -2749,7 +2751,7 @@ SparseGrowLayout sparse_grow_layout_nodes(int64_t n, int64_t nnz, int F, int B, 
         L.ent[k] = o;    o += gbt_align((size_t)gbt_sparse_capacity(nnz) * sparse_ent_bytes(F, B));
         L.wgq[k] = o;    o += gbt_align((size_t)n * 8);
     }
-    L.state = o;      o += gbt_align((size_t)L.level_nodes * 16);
+    L.state = o;      o += gbt_align((size_t)L.level_nodes * 16 * kCursorStride);
     L.pool = o;       o += gbt_align((size_t)L.hist_nodes * F * B * 16);
     L.eval_nodes = o; o += gbt_align((size_t)L.level_nodes * 2 * sizeof(EvalNode));
     L.jobs = o;       o += gbt_align(kUploadBytes);
@@ -2943,8 +2945,8 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
         g.cap_nodes = cap;
         for (int k = 0; k < 2; ++k) {
             g.tile_rows[k] = (uint32_t)gbt_sparse_part_tile();
-            g.n_left[k] = (const uint32_t *)(ws + L.state);   // four words per job; the first: left rows
-            g.n_left_stride[k] = 4;
+            g.n_left[k] = (const uint32_t *)(ws + L.state);   // two cursors per job; the first one's low word: left rows
+            g.n_left_stride[k] = 4 * kCursorStride;
         }
         g.nb = nb;
         g.min_child_weight = params->min_child_weight;
@@ -2957,7 +2959,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
             const int span = gbt_prof_begin(ctx, GBT_PROF_PARTITION, 0.0);
             if (span >= 0) pass_spans.push_back({span, d, false});
             GBT_HIP(ctx, gbt_launch_sparse_partition(s, cur.rowptr, cur.ent, ent_bytes, cur.gq, w_rowptr[to], w_ent[to], w_gq[to], B,
-                                                     !last, g.v.pjobs, (int)n_splits, (int)tiles, g.v.cursors,
+                                                     !last, g.v.pjobs, (int)n_splits, (int)tiles, g.v.cursors, kCursorStride,
                                                      &g.v.levels[d].n_splits));
             gbt_prof_end(ctx);
             return GBT_OK;
@@ -3158,6 +3160,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
             part_rows += j.seg_len;
             pjobs.push_back(j);
         }
+        const int stride = pjobs.size() <= 1024 ? kCursorStride : 1;   // (the read-back buffer holds so many lines)
         GBT_REQUIRE(ctx, pjobs.size() * sizeof(PartJob) <= kUploadBytes && pjobs.size() * 16 <= kSplitRb, GBT_EUNSUPPORTED,
                     "level too wide");
         st = upload(ctx, pjobs.data(), pjobs.size() * sizeof(PartJob), ws + L.jobs);
@@ -3165,11 +3168,11 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
         gbt_prof_begin(ctx, GBT_PROF_PARTITION, part_rows * (children_need_hist ? 2.0 * row_bytes : row_bytes - 8.0));
         GBT_HIP(ctx, gbt_launch_sparse_partition(s, cur.rowptr, cur.ent, ent_bytes, cur.gq, w_rowptr[wnext], w_ent[wnext], w_gq[wnext],
                                                  B, children_need_hist, (const PartJob *)(ws + L.jobs), (int)pjobs.size(),
-                                                 (int)tile_cursor, (unsigned long long *)(ws + L.state)));
-        GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), ws + L.state, pjobs.size() * 16, hipMemcpyDeviceToHost, s));
+                                                 (int)tile_cursor, (unsigned long long *)(ws + L.state), stride));
+        GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), ws + L.state, pjobs.size() * 16 * stride, hipMemcpyDeviceToHost, s));
         gbt_prof_end(ctx);
         GBT_SYNC(ctx);
-        const uint32_t *cur_words = (const uint32_t *)rb(ctx);   // four words per job; the first: left rows
+        const uint32_t *cur_words = (const uint32_t *)rb(ctx);   // two cursors per job; the first one's low word: left rows
 
         // ---- children, in creation order; the child with fewer rows is built from rows
         hjobs.clear();
@@ -3182,7 +3185,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
         for (size_t k = 0; k < pjobs.size(); ++k) {
             const HNode &nd = sel_nodes[k];
             const gbt_split &sp = sel_splits[k];
-            const uint32_t nl = cur_words[4 * k];
+            const uint32_t nl = cur_words[4 * k * (size_t)stride];
             GBT_REQUIRE(ctx, nl <= nd.len, GBT_EHIP, "internal: n_left %u > %u", nl, nd.len);
             HNode lc{n_nodes, nd.begin, nl, sp.GLq, sp.HLq, nd.depth + 1, child_buf};
             HNode rc{n_nodes + 1, nd.begin + nl, nd.len - nl, nd.Gq - sp.GLq, nd.Hq - sp.HLq, nd.depth + 1, child_buf};

@@ -343,8 +343,9 @@ struct EvalTail {
     int skip_store = 0;   // 1: a histogram made by subtraction is evaluated but not stored (nothing below these nodes
                           // will subtract from it: their children are leaves)
 };
-// The cursors of the passes that partition and build histograms in one launch lie one per 128-byte line
-// (index * kCursorStride): atomics on words of one line take turns as if they were one address.
+// The cursors of the passes that partition in one launch lie one per 128-byte line (index * kCursorStride): atomics on
+// words of one line take turns as if they were one address, 12 ns each.  (10M sparse rows, 9766 tiles with two cursors of
+// a node side by side: 240 us per level of atomics alone, whatever the tiles did meanwhile.)
 constexpr int kCursorStride = 16;
 hipError_t gbt_launch_eval(hipStream_t s, int64_t *hist_pool, const EvalNode *nodes, int n_nodes,
                            const int32_t *nb, int F, int B, int n_chunks, double inv_sg, double inv_sh,
@@ -388,7 +389,7 @@ bool gbt_partition_fused_ok(const GbtRows &dst);
 int gbt_partition_fused_tile(const GbtRows &dst, int64_t n);   // n: rows of the matrix
 hipError_t gbt_launch_partition_fused(hipStream_t s, const GbtRows &src, const GbtRows &dst, int bits, int row_bits,
                                       int64_t n, uint32_t missing, const PartJob *jobs, int n_jobs, int total_tiles,
-                                      unsigned long long *cursor, const uint32_t *counts_dev = nullptr);
+                                      unsigned long long *cursor, int cursor_stride, const uint32_t *counts_dev = nullptr);
 // The root histogram straight from the fp32 gradient pairs (8-bit symbols, one feature tile of at
 // most 16 features, jobs that cover rows [0, n) exactly once: gbt_hist_fix_ok): rounds each pair to
 // fixed point with the given scales, stores it to gq_out and adds the totals into sums_out[2].
@@ -526,7 +527,8 @@ int gbt_sparse_part_tile();
 hipError_t gbt_launch_sparse_partition(hipStream_t s, const uint32_t *src_rowptr, const void *src_ent, int ent_bytes,
                                        const int32_t *src_gq, uint32_t *dst_rowptr, void *dst_ent,
                                        int32_t *dst_gq, int B, bool move, const PartJob *jobs, int n_jobs,
-                                       int n_tiles, unsigned long long *cursor, const uint32_t *counts_dev = nullptr);
+                                       int n_tiles, unsigned long long *cursor, int cursor_stride,
+                                       const uint32_t *counts_dev = nullptr);
 hipError_t gbt_launch_sparse_walk(hipStream_t s, const char *ws, const DevTree *trees, int n_trees,
                                   const uint32_t *rowptr, const void *ent, int ent_bytes, int64_t n, int B, double eta,
                                   float *margin, int32_t *leaf_out, int max_nodes);
@@ -580,6 +582,22 @@ __device__ __forceinline__ void load_words(uint32_t (&x)[N], const uint32_t *p) 
 #pragma unroll
         for (int k = 0; k < N; ++k) x[k] = p[k];
     }
+}
+// The job whose tile range contains `tile` (jobs are sorted by tile_begin, the first begins at or before it).  A wave looks
+// at 64 of them at once, so that up to 64 jobs cost one load and up to 4096 two; a bisection of 128 jobs is seven loads one
+// behind the other, two or three microseconds in front of everything a workgroup does.  Every lane of the wave must call.
+template <typename Job>
+__device__ __forceinline__ int gbt_find_job(const Job *jobs, int n_jobs, uint32_t tile) {
+    const int lane = (int)(threadIdx.x & 63u);
+    int lo = 0, n = n_jobs;   // the job is one of [lo, lo + n)
+    while (n > 1) {
+        const int step = (n + 63) >> 6, at = lane * step;
+        const bool before = at < n && jobs[lo + at].tile_begin <= tile;
+        const int k = __popcll(__ballot(before)) - 1;   // the last of the 64 that begins at or before the tile
+        lo += (k < 0 ? 0 : k) * step;
+        n = n - (k < 0 ? 0 : k) * step < step ? n - (k < 0 ? 0 : k) * step : step;
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
 }
 constexpr int kHShift = 30;                        // width of the h field
 constexpr uint32_t kHMask = (1u << kHShift) - 1u;

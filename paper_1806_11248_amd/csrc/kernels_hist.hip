@@ -310,15 +310,6 @@ constexpr int kPHGroup = 7;                      // atomics of a row in flight t
 constexpr int record_words(int ns) { return (ns + 7 + 3) / 4; }
 constexpr int slots_for(int ft) { return ft <= 4 ? 4 : ft <= 8 ? 8 : ft <= 12 ? 12 : ft == 13 ? 13 : 16; }
 
-__device__ inline int find_span_job(const PartJob *jobs, int n_jobs, uint32_t span) {
-    int lo = 0, hi = n_jobs;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (jobs[mid].tile_begin <= span) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
 // Adds one record's pair to the LDS histogram at the bins of its NS symbol slots (slot j of a lane
 // is feature (j + lane) mod ft; pre[] / selA / selB are the lane's slot tables).  The atomics go out
 // in groups; a group's returned words are tested together for an event (a carry out of the h field,
@@ -442,7 +433,7 @@ __global__ __launch_bounds__(kPHBlock, 4) void part_hist_first_kernel(
     __shared__ uint64_t words[2][kPHWords];
     __shared__ uint32_t lefts_before[2][kPHWords];
     __shared__ uint32_t base_s[2][2];
-    const int ji = find_span_job(jobs, n_jobs, blockIdx.x);
+    const int ji = gbt_find_job(jobs, n_jobs, blockIdx.x);
     const PartJob job = jobs[ji];
     const uint32_t span_begin = (blockIdx.x - job.tile_begin) * rows_per_span;
     const uint32_t span_rows = job.seg_len - span_begin < rows_per_span ? job.seg_len - span_begin : rows_per_span;
@@ -624,7 +615,7 @@ __global__ __launch_bounds__(kPHBlock, 4) void part_hist_kernel(
     __shared__ uint64_t words[2][NW];
     __shared__ uint32_t lefts_before[2][NW];
     __shared__ uint32_t base_s[2][2];
-    const int ji = find_span_job(jobs, n_jobs, blockIdx.x);
+    const int ji = gbt_find_job(jobs, n_jobs, blockIdx.x);
     const PartJob job = jobs[ji];
     const uint32_t span_begin = (blockIdx.x - job.tile_begin) * rows_per_span;
     const uint32_t span_rows = job.seg_len - span_begin < rows_per_span ? job.seg_len - span_begin : rows_per_span;
@@ -822,7 +813,7 @@ __global__ __launch_bounds__(kKeepBlock, 2) void hist_keep_kernel(
     constexpr int RW = record_words(NS);
     constexpr int BLK = kKeepBlock, ROWS = kPFRows, TILE = BLK * ROWS, WAVES = BLK / 64;
     extern __shared__ unsigned long long lds[];
-    const int ji = find_span_job(jobs, n_jobs, blockIdx.x);
+    const int ji = gbt_find_job(jobs, n_jobs, blockIdx.x);
     const PartJob job = jobs[ji];
     const uint32_t span_begin = (blockIdx.x - job.tile_begin) * rows_per_span;
     const uint32_t span_rows = job.seg_len - span_begin < rows_per_span ? job.seg_len - span_begin : rows_per_span;
@@ -946,11 +937,7 @@ __global__ __launch_bounds__(kH2Block) void hist2_kernel(
     constexpr int RW = record_words(NS);
     constexpr int ROWS = kPFRows, TILE = kH2Block * ROWS, WAVES = kH2Block / 64;
     extern __shared__ unsigned long long lds[];
-    int lo = 0, hi = n_jobs;   // last job with tile_begin <= this span
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (jobs[mid].tile_begin <= blockIdx.x) lo = mid; else hi = mid;
-    }
+    const int lo = gbt_find_job(jobs, n_jobs, blockIdx.x);
     const int ji = lo;
     const Hist2Job job = jobs[ji];
     const uint32_t span_begin = (blockIdx.x - job.tile_begin) * rows_per_span;
@@ -1103,11 +1090,7 @@ __global__ __launch_bounds__(kM3Block, 2) void move_levels_kernel(
     __shared__ Move3Job sjob;
     __shared__ uint32_t cnt[2][NW][NC];
     __shared__ uint32_t base_s[2][NC];
-    int lo = 0, hi = n_jobs;   // last job with tile_begin <= this span
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (jobs[mid].tile_begin <= blockIdx.x) lo = mid; else hi = mid;
-    }
+    const int lo = gbt_find_job(jobs, n_jobs, blockIdx.x);
     const int ji = lo;
     if (threadIdx.x < (int)(sizeof(Move3Job) / 4)) ((uint32_t *)&sjob)[threadIdx.x] = ((const uint32_t *)&jobs[ji])[threadIdx.x];
     __syncthreads();

@@ -148,12 +148,7 @@ __global__ __launch_bounds__(BLOCK, MINWG) void hist8_kernel(const Hist8Args a) 
     uint32_t job_rows;
     int64_t *__restrict__ out = a.out;
     if (REC) {
-        int lo = 0, hi = a.n_jobs;   // last job whose first span is <= this one
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (a.jobs[mid].tile_begin <= blockIdx.x) lo = mid; else hi = mid;
-        }
-        const PartJob job = a.jobs[lo];
+        const PartJob job = a.jobs[gbt_find_job(a.jobs, a.n_jobs, blockIdx.x)];
         const uint32_t span_begin = (blockIdx.x - job.tile_begin) * a.rows_per_span;
         job_rows = job.seg_len - span_begin < a.rows_per_span ? job.seg_len - span_begin : a.rows_per_span;
         job_row0 = (uint64_t)job.seg_begin + span_begin;

@@ -31,16 +31,6 @@ constexpr int kWordsPerTile = kTile / 64;       // 32 ballot words
 constexpr int kRowsPerThread = kTile / kBlock;  // 8
 static_assert(kBlock == 256 && kTile == 2048, "index arithmetic below assumes 4 waves x 8 steps");
 
-// the job whose tile range contains `tile` (jobs are sorted by tile_begin)
-__device__ inline int find_job(const PartJob *jobs, int n_jobs, uint32_t tile) {
-    int lo = 0, hi = n_jobs;
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (jobs[mid].tile_begin <= tile) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
 __device__ inline uint32_t load_symbol(const uint32_t *packed, uint64_t bp, int bits, uint32_t mask) {
     const uint32_t *w = packed + (bp >> 5);
     const uint32_t sh = (uint32_t)(bp & 31);
@@ -60,7 +50,7 @@ __global__ __launch_bounds__(kBlock) void part_flag_kernel(
         if (tile >= counts_dev[1]) return;
         n_jobs = (int)counts_dev[0];
     }
-    const PartJob job = jobs[find_job(jobs, n_jobs, tile)];
+    const PartJob job = jobs[gbt_find_job(jobs, n_jobs, tile)];
     const uint32_t t_in_seg = tile - job.tile_begin;
     const uint32_t base = t_in_seg * kTile;   // first row of the tile inside the segment
     const uint32_t mask = (1u << bits) - 1u;
@@ -132,7 +122,7 @@ __global__ __launch_bounds__(kBlock) void part_scatter_kernel(
         if (tile >= counts_dev[1]) return;
         n_jobs = (int)counts_dev[0];
     }
-    const int ji = find_job(jobs, n_jobs, tile);
+    const int ji = gbt_find_job(jobs, n_jobs, tile);
     const PartJob job = jobs[ji];
     const uint32_t base = (tile - job.tile_begin) * kTile;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -185,7 +175,7 @@ __global__ __launch_bounds__(kBlock) void part_move_kernel(
     const uint32_t *__restrict__ tile_left_off, const uint32_t *__restrict__ n_left, int slice_words,
     bool vec_rows) {
     const uint32_t tile = blockIdx.x;
-    const int ji = find_job(jobs, n_jobs, tile);
+    const int ji = gbt_find_job(jobs, n_jobs, tile);
     const PartJob job = jobs[ji];
     const uint32_t base = (tile - job.tile_begin) * kTile;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -276,7 +266,7 @@ __global__ __launch_bounds__(kBlock) void part_move_ids_kernel(
     int n_jobs, const uint64_t *__restrict__ masks, const uint32_t *__restrict__ tile_left_off,
     const uint32_t *__restrict__ n_left) {
     const uint32_t tile = blockIdx.x;
-    const int ji = find_job(jobs, n_jobs, tile);
+    const int ji = gbt_find_job(jobs, n_jobs, tile);
     const PartJob job = jobs[ji];
     const uint32_t base = (tile - job.tile_begin) * kTile;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -342,7 +332,7 @@ __global__ __launch_bounds__(kFBlock) void part_fused_kernel(
     const uint32_t *__restrict__ src_sym, int64_t src_stride_bits, int64_t src_words, bool aligned_src,
     uint32_t *__restrict__ dst_sym, int SW, int row_bits, int bits, uint32_t missing,
     const int2 *__restrict__ src_gq, int2 *__restrict__ dst_gq, const PartJob *__restrict__ jobs, int n_jobs,
-    unsigned long long *__restrict__ cursor, const uint32_t *__restrict__ counts_dev) {
+    unsigned long long *__restrict__ cursor, int cursor_stride, const uint32_t *__restrict__ counts_dev) {
     __shared__ uint32_t left_base_s, right_base_s;
     __shared__ uint64_t words[kFWords];
     __shared__ uint32_t lefts_before[kFWords];
@@ -351,7 +341,7 @@ __global__ __launch_bounds__(kFBlock) void part_fused_kernel(
         if (tile >= counts_dev[1]) return;
         n_jobs = (int)counts_dev[0];
     }
-    const int ji = find_job(jobs, n_jobs, tile);
+    const int ji = gbt_find_job(jobs, n_jobs, tile);
     const PartJob job = jobs[ji];
     const uint32_t base = (tile - job.tile_begin) * kFTile;
     const uint32_t tile_rows = job.seg_len - base < (uint32_t)kFTile ? job.seg_len - base : (uint32_t)kFTile;
@@ -414,7 +404,7 @@ __global__ __launch_bounds__(kFBlock) void part_fused_kernel(
         if (lane == 63) {
             const uint32_t cnt = x;
             const unsigned long long old =
-                atomicAdd(&cursor[ji], (unsigned long long)cnt | ((unsigned long long)(tile_rows - cnt) << 32));
+                atomicAdd(&cursor[(size_t)ji * cursor_stride], (unsigned long long)cnt | ((unsigned long long)(tile_rows - cnt) << 32));
             left_base_s = (uint32_t)(old & 0xffffffffull);
             right_base_s = (uint32_t)(old >> 32);
         }
@@ -468,7 +458,7 @@ __global__ __launch_bounds__(kFBlock) void part_staged_kernel(
     const uint32_t *__restrict__ src_sym, int64_t src_stride_bits, int64_t src_words,
     uint32_t *__restrict__ dst_sym, int SW, int row_bits, int bits, uint32_t missing,
     const int2 *__restrict__ src_gq, int2 *__restrict__ dst_gq, const PartJob *__restrict__ jobs, int n_jobs,
-    int tile_cap, unsigned long long *__restrict__ cursor, const uint32_t *__restrict__ counts_dev) {
+    int tile_cap, unsigned long long *__restrict__ cursor, int cursor_stride, const uint32_t *__restrict__ counts_dev) {
     extern __shared__ uint32_t stage[];                 // the tile's words, then one destination per row
     __shared__ uint32_t left_base_s, right_base_s;
     __shared__ uint64_t words[kFWords];
@@ -478,7 +468,7 @@ __global__ __launch_bounds__(kFBlock) void part_staged_kernel(
         if (tile >= counts_dev[1]) return;
         n_jobs = (int)counts_dev[0];
     }
-    const int ji = find_job(jobs, n_jobs, tile);
+    const int ji = gbt_find_job(jobs, n_jobs, tile);
     const PartJob job = jobs[ji];
     const uint32_t base = (tile - job.tile_begin) * (uint32_t)tile_cap;
     const uint32_t tile_rows = job.seg_len - base < (uint32_t)tile_cap ? job.seg_len - base : (uint32_t)tile_cap;
@@ -547,7 +537,7 @@ __global__ __launch_bounds__(kFBlock) void part_staged_kernel(
         if (lane < n_words_tile) lefts_before[lane] = x - c;
         if (lane == 63) {
             const unsigned long long old =
-                atomicAdd(&cursor[ji], (unsigned long long)x | ((unsigned long long)(tile_rows - x) << 32));
+                atomicAdd(&cursor[(size_t)ji * cursor_stride], (unsigned long long)x | ((unsigned long long)(tile_rows - x) << 32));
             left_base_s = (uint32_t)(old & 0xffffffffull);
             right_base_s = (uint32_t)(old >> 32);
         }
@@ -664,11 +654,7 @@ __global__ __launch_bounds__(kC2Block) void count2_kernel(const uint8_t *__restr
     constexpr int FIRST_T = NT - 1;          // heap position of the first target
     __shared__ uint32_t acc[NT];
     __shared__ CountJob sjob;
-    int lo = 0, hi = n_jobs;   // last job with tile_begin <= this tile
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (jobs[mid].tile_begin <= blockIdx.x) lo = mid; else hi = mid;
-    }
+    const int lo = gbt_find_job(jobs, n_jobs, blockIdx.x);
     if (threadIdx.x < (int)(sizeof(CountJob) / 4)) ((uint32_t *)&sjob)[threadIdx.x] = ((const uint32_t *)&jobs[lo])[threadIdx.x];
     if (threadIdx.x < NT) acc[threadIdx.x] = 0;
     __syncthreads();
@@ -765,9 +751,9 @@ int gbt_partition_fused_tile(const GbtRows &dst, int64_t n) {
 
 hipError_t gbt_launch_partition_fused(hipStream_t s, const GbtRows &src, const GbtRows &dst, int bits, int row_bits,
                                       int64_t n, uint32_t missing, const PartJob *jobs, int n_jobs, int total_tiles,
-                                      unsigned long long *cursor, const uint32_t *counts_dev) {
+                                      unsigned long long *cursor, int cursor_stride, const uint32_t *counts_dev) {
     if (n_jobs <= 0 || total_tiles <= 0) return hipSuccess;
-    hipError_t e = counts_dev ? hipSuccess : gbt_launch_fill_u64(s, (uint64_t *)cursor, 0, n_jobs);
+    hipError_t e = counts_dev ? hipSuccess : gbt_launch_fill_u64(s, (uint64_t *)cursor, 0, (int64_t)n_jobs * cursor_stride);
     if (e != hipSuccess) return e;
     const int SW = (int)(dst.stride_bits >> 5);
     const bool aligned_src = src.stride_bits == 128 && ((uintptr_t)src.sym & 15u) == 0;
@@ -775,7 +761,7 @@ hipError_t gbt_launch_partition_fused(hipStream_t s, const GbtRows &src, const G
         part_fused_kernel<<<total_tiles, kFBlock, 0, s>>>(src.sym, src.stride_bits, src.n_words, aligned_src,
                                                                 dst.sym_rw, SW, row_bits, bits, missing,
                                                                 (const int2 *)src.gq, (int2 *)dst.gq_rw, jobs, n_jobs,
-                                                                cursor, counts_dev);
+                                                                cursor, cursor_stride, counts_dev);
     else {
         const int cap = gbt_partition_fused_tile(dst, n);
         const size_t lds = (((((size_t)cap * (size_t)src.stride_bits + 31) >> 5) + 2 + 3) / 4 * 4 + (size_t)cap) * 4;
@@ -787,7 +773,7 @@ hipError_t gbt_launch_partition_fused(hipStream_t s, const GbtRows &src, const G
         }
         part_staged_kernel<<<total_tiles, kFBlock, lds, s>>>(src.sym, src.stride_bits, src.n_words, dst.sym_rw, SW,
                                                              row_bits, bits, missing, (const int2 *)src.gq,
-                                                             (int2 *)dst.gq_rw, jobs, n_jobs, cap, cursor, counts_dev);
+                                                             (int2 *)dst.gq_rw, jobs, n_jobs, cap, cursor, cursor_stride, counts_dev);
     }
     return hipGetLastError();
 }

@@ -153,7 +153,7 @@ __global__ __launch_bounds__(kSplitBlock) void plan_split_kernel(PlanView v, int
             j.hist_off = 0;
             v.pjobs[k] = j;
             v.pinfo[k] = PlanJob{id, 0, r.GLq, r.HLq};
-            for (int c = 0; c < v.cursors_per_job; ++c) v.cursors[(size_t)k * v.cursors_per_job + c] = 0ull;
+            for (int c = 0; c < v.cursors_per_job; ++c) v.cursors[((size_t)k * v.cursors_per_job + c) * kCursorStride] = 0ull;
             PlanNode &nd = v.nodes[id];
             nd.gain = r.gain;
             nd.feature = r.feature;

@@ -305,15 +305,6 @@ constexpr int kSpTile = 1024;
 constexpr int kSpRowsPerThread = kSpTile / kSpBlock;   // 2
 constexpr int kSpGroups = kSpRowsPerThread * (kSpBlock / 64);   // (k, wave) groups of 64 rows: 16
 
-__device__ inline int find_part_job(const PartJob *jobs, int n_jobs, uint32_t tile) {
-    int lo = 0, hi = n_jobs;   // last job with tile_begin <= tile
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (jobs[mid].tile_begin <= tile) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
 // the entry with an id in [lo, lo + B) among the ascending ids ent[s .. e), or 0xffffffff
 template <typename P>
 __device__ __forceinline__ uint32_t find_feature_entry(P ent, uint32_t s, uint32_t e, uint32_t lo, uint32_t B) {
@@ -345,13 +336,13 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
                                                                E *__restrict__ dst_ent,
                                                                int2 *__restrict__ dst_gq, uint32_t B, int move,
                                                                const PartJob *__restrict__ jobs, int n_jobs,
-                                                               unsigned long long *__restrict__ cursor,
+                                                               unsigned long long *__restrict__ cursor, int cursor_stride,
                                                                const uint32_t *__restrict__ counts_dev) {
     if (counts_dev) {
         if (blockIdx.x >= counts_dev[1]) return;
         n_jobs = (int)counts_dev[0];
     }
-    __shared__ uint32_t stage_w[kSpStage / 2];
+    __shared__ __align__(16) uint32_t stage_w[kSpStage / 2];
     __shared__ uint32_t out_w[kSpStage / 2 + 4];
     __shared__ uint32_t grp_rows[2][kSpGroups];   // [side][group]: rows, then their exclusive offsets
     __shared__ uint32_t grp_ent[2][kSpGroups];
@@ -359,7 +350,7 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
     __shared__ uint32_t tot[4];                   // rows L, rows R, entries L, entries R of the tile
     constexpr uint32_t EPW = 4 / sizeof(E), SH = EPW == 2 ? 1 : 0;   // entries per word, and its log2
     const E *stage = (const E *)stage_w;
-    const int j = find_part_job(jobs, n_jobs, blockIdx.x);
+    const int j = gbt_find_job(jobs, n_jobs, blockIdx.x);
     const PartJob job = jobs[j];
     const uint32_t t_local = blockIdx.x - job.tile_begin;
     const uint32_t seg_end = job.seg_begin + job.seg_len;
@@ -370,11 +361,25 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
 
     // the tile's piece of the stream, from the word that holds its first entry
     const uint32_t e0 = src_rowptr[r0], e1 = src_rowptr[r1];
+    const uint32_t ent_begin = src_rowptr[job.seg_begin], ent_end = src_rowptr[seg_end];
     const uint32_t w0 = e0 >> SH, n_words = ((e1 + EPW - 1) >> SH) - w0;
     const bool staged = n_words <= (uint32_t)(kSpStage / 2);
     if (staged) {
+        // four words per load, all of a thread's loads in flight together; the stream ends in slack that such loads may touch
         const uint32_t *src_w = (const uint32_t *)src_ent + w0;
-        for (uint32_t w = threadIdx.x; w < n_words; w += kSpBlock) stage_w[w] = src_w[w];
+        constexpr int kLoads = kSpStage / 2 / (4 * kSpBlock);
+        static_assert(kLoads * 4 * kSpBlock == kSpStage / 2, "whole turns");
+        Words4 v[kLoads];
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k) {
+            const uint32_t w = 4u * (k * kSpBlock + threadIdx.x);
+            if (w < n_words) v[k] = *(const Words4 *)(src_w + w);
+        }
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k) {
+            const uint32_t w = 4u * (k * kSpBlock + threadIdx.x);
+            if (w < n_words) *(uint4 *)(stage_w + w) = make_uint4(v[k].x, v[k].y, v[k].z, v[k].w);
+        }
     }
     const uint32_t sbase = w0 << SH;   // stream index of stage[0]
 
@@ -440,13 +445,11 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        base[0] = atomicAdd(&cursor[2 * j], ((unsigned long long)tot[2] << 32) | tot[0]);
-        if (move) base[1] = atomicAdd(&cursor[2 * j + 1], ((unsigned long long)tot[3] << 32) | tot[1]);
-    }
+    // (a wave per side: neither waits for the other's answer)
+    if (threadIdx.x == 0) base[0] = atomicAdd(&cursor[(size_t)(2 * j) * cursor_stride], ((unsigned long long)tot[2] << 32) | tot[0]);
+    if (move && threadIdx.x == 64) base[1] = atomicAdd(&cursor[(size_t)(2 * j + 1) * cursor_stride], ((unsigned long long)tot[3] << 32) | tot[1]);
     if (!move) return;
     __syncthreads();
-    const uint32_t ent_begin = src_rowptr[job.seg_begin], ent_end = src_rowptr[seg_end];
     const uint32_t row_l = job.seg_begin + (uint32_t)base[0], ent_l = ent_begin + (uint32_t)(base[0] >> 32);
     const uint32_t row_r = seg_end - (uint32_t)base[1] - tot[1], ent_r = ent_end - (uint32_t)(base[1] >> 32) - tot[3];
     if (t_local == 0 && threadIdx.x == 0) dst_rowptr[seg_end] = ent_end;   // the segment's closing row pointer
@@ -467,7 +470,14 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
             if (staged) {
                 const E *from = stage + (rs[k] - sbase);
                 E *to = outE + (left[k] ? lds_l : lds_r) + in_piece;
-                for (uint32_t q = 0; q < rlen[k]; ++q) to[q] = from[q];
+                for (uint32_t q = 0; q < rlen[k]; q += 4) {   // four reads in flight (past the row's end: its last entry again)
+                    E v[4];
+#pragma unroll
+                    for (uint32_t u = 0; u < 4; ++u) v[u] = from[q + u < rlen[k] ? q + u : rlen[k] - 1u];
+#pragma unroll
+                    for (uint32_t u = 0; u < 4; ++u)
+                        if (q + u < rlen[k]) to[q + u] = v[u];
+                }
             }
         }
         if (!staged) {   // the wave copies its rows one after the other, 64 entries at a time (rlen is 0 off the tile)
@@ -676,18 +686,18 @@ int gbt_sparse_part_tile() { return kSpTile; }
 hipError_t gbt_launch_sparse_partition(hipStream_t s, const uint32_t *src_rowptr, const void *src_ent, int ent_bytes,
                                        const int32_t *src_gq, uint32_t *dst_rowptr, void *dst_ent,
                                        int32_t *dst_gq, int B, bool move, const PartJob *jobs, int n_jobs,
-                                       int n_tiles, unsigned long long *cursor, const uint32_t *counts_dev) {
+                                       int n_tiles, unsigned long long *cursor, int cursor_stride, const uint32_t *counts_dev) {
     if (n_jobs <= 0 || n_tiles <= 0) return hipSuccess;
-    hipError_t e = counts_dev ? hipSuccess : gbt_launch_fill_u64(s, (uint64_t *)cursor, 0, 2 * (int64_t)n_jobs);
+    hipError_t e = counts_dev ? hipSuccess : gbt_launch_fill_u64(s, (uint64_t *)cursor, 0, 2 * (int64_t)n_jobs * cursor_stride);
     if (e != hipSuccess) return e;
     if (ent_bytes == 2)
         sparse_part_kernel<uint16_t><<<n_tiles, kSpBlock, 0, s>>>(src_rowptr, (const uint16_t *)src_ent, (const int2 *)src_gq,
                                                                   dst_rowptr, (uint16_t *)dst_ent, (int2 *)dst_gq, (uint32_t)B,
-                                                                  move ? 1 : 0, jobs, n_jobs, cursor, counts_dev);
+                                                                  move ? 1 : 0, jobs, n_jobs, cursor, cursor_stride, counts_dev);
     else
         sparse_part_kernel<uint32_t><<<n_tiles, kSpBlock, 0, s>>>(src_rowptr, (const uint32_t *)src_ent, (const int2 *)src_gq,
                                                                   dst_rowptr, (uint32_t *)dst_ent, (int2 *)dst_gq, (uint32_t)B,
-                                                                  move ? 1 : 0, jobs, n_jobs, cursor, counts_dev);
+                                                                  move ? 1 : 0, jobs, n_jobs, cursor, cursor_stride, counts_dev);
     return hipGetLastError();
 }
 
