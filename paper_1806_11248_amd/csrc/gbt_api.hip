@@ -2728,7 +2728,7 @@ extern "C" int32_t gbt_build_hist_sparse(gbt_ctx *ctx, const uint32_t *rowptr, c
     if (st != GBT_OK) return st;
     gbt_prof_begin(ctx, row_begin == 0 && n_node_rows == n ? GBT_PROF_HIST_ROOT : GBT_PROF_HIST_NODE, 0.0);
     GBT_HIP(ctx, gbt_launch_sparse_hist(ctx, rowptr, ent, sparse_ent_bytes(F, B), gq, hist_out, (const HistJob *)slot,
-                                        (int)jobs.size(), glen, glen < bins));
+                                        (int)jobs.size(), glen, glen < bins, -1));
     gbt_prof_end(ctx);
     return GBT_OK;
 }
@@ -2828,13 +2828,21 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
     auto rows_of = [&](int buf) { return buf == 2 ? canon : Rows{w_rowptr[buf], w_ent[buf], w_gq[buf]}; };
     const bool root_may_split = max_depth > 0 && (!lossguide || max_leaves > 1);
     // depth-wise: the levels are planned on the device, as in grow_impl
-    PlanHistRule plan_rule{};   // the rule of sparse_rows_per_job
-    plan_rule.pieces_max = std::max<int64_t>(1, (int64_t)ctx->num_cu * ctx->sparse_jobs_per_cu);
-    plan_rule.min_rows = kSparseMinRowsPerJob;
-    plan_rule.max_rows = kSparseMaxRowsPerJob;
+    PlanHistRule plan_rule{};
+    plan_rule.pieces_max = (int64_t)ctx->num_cu * 16 * ctx->sparse_jobs_per_cu;
+    plan_rule.min_rows = kMinRowsPerJob;
+    plan_rule.max_rows = gbt_sparse_hist_max_rows();   // (the limit that makes the most jobs; see below)
     plan_rule.tiles = (int)((bins + glen - 1) / glen);
     plan_rule.ft = glen;
     plan_rule.width = (int)bins;
+    plan_rule.num_cu = ctx->num_cu;
+    // A job merges its whole id tile, two atomics per id, against rows that cost as much as their entries in the tile and
+    // about eight more; with two or more workgroups on a compute unit (tiles of at most 64 KB) short jobs hide more latency
+    // than their merges cost, the more so the fewer entries a row has in a tile.  us per round with pieces of a 256th of the
+    // rows and so: 10M x 50 x 256 with 10 entries a row 3140 and 2777, 1M x 40 x 256 with 4 629 and 590, 1M x 200 x 256 with
+    // 60 (seven tiles) 3112 and 2657, 300,000 x 200 x 512 with 60 1976 and 1700, 1M x 200 x 128 with 10 (four tiles) 798 and 825.
+    const double in_tile = (double)nnz / (double)n / plan_rule.tiles, thin = std::min(1.0, in_tile * in_tile / 64.0);
+    plan_rule.merge = ((size_t)glen * 8 > 64u * 1024u ? 0.25 : 0.08) * glen / (in_tile + 8.0) * (plan_rule.tiles > 1 ? thin : 1.0) + 1e-3;
     const bool planned = ctx->plan && !lossguide && root_may_split && cap <= kPlanNodesMax &&
                          plan_hist_jobs_max(plan_rule, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
     std::vector<float> hcuts(planned ? 0 : (size_t)F * (B - 1));
@@ -2844,7 +2852,9 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
     int64_t *sums_dev = (int64_t *)(ws + L.scratch);   // partial totals of the pairs
     int n_sums = 1;
     gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * 24.0);
-    st = gpair_scale_impl(ctx, gpair, n, scale);
+    int uniform_h = 0;
+    float h_value = 0.0f;
+    st = gpair_scale_impl(ctx, gpair, n, scale, &uniform_h, &h_value);
     if (st == GBT_OK) {
         hipError_t e = gbt_launch_to_fixed(s, gpair, n, scale[0], scale[1], gq, sums_dev, &n_sums);
         if (e != hipSuccess) st = gbt_fail(ctx, GBT_EHIP, "gbt_launch_to_fixed: %s", hipGetErrorString(e));
@@ -2854,6 +2864,10 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
     const double inv_sg = 1.0 / scale[0], inv_sh = 1.0 / scale[1];
     const double lambda = params->lambda;
     const double min_gain = std::max(params->gamma, (double)GBT_GAIN_FLOOR);
+    // every row has the same hessian: 16-bit entries count rows instead of adding it (>= 0: that hessian in fixed point)
+    const int hq_uni = uniform_h && ent_bytes == 2 ? (int)llrint((double)h_value * scale[1]) : -1;
+    plan_rule.max_rows = hq_uni >= 0 ? gbt_sparse_hist_max_rows() : kSparseMaxRowsPerJob;
+    plan_rule.exclusive_ok = hq_uni >= 0 ? 1 : 0;
     const double row_bytes = 12.0 + (double)ent_bytes * (double)nnz / (double)n;   // row pointer, pair, the average row's entries
 
     std::vector<HistJob> hjobs;
@@ -2865,7 +2879,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
             if (st2 != GBT_OK) return st2;
             gbt_prof_begin(ctx, cls, j0 == 0 ? bytes : 0.0);
             GBT_HIP(ctx, gbt_launch_sparse_hist(ctx, R.rowptr, R.ent, ent_bytes, R.gq, pool, (const HistJob *)(ws + L.jobs), (int)nj,
-                                                glen, glen < bins));
+                                                glen, glen < bins, hq_uni));
             gbt_prof_end(ctx);
         }
         return GBT_OK;
@@ -2874,7 +2888,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
     if (root_may_split) {
         GBT_HIP(ctx, gbt_launch_fill_u64(s, (uint64_t *)pool, 0, hist_len));
         hjobs.clear();
-        add_sparse_hist_jobs(hjobs, 0, 0, (uint32_t)n, bins, glen, sparse_rows_per_job(ctx, n, bins, glen));
+        add_sparse_hist_jobs(hjobs, 0, 0, (uint32_t)n, bins, glen, std::min<uint32_t>(sparse_rows_per_job(ctx, n, bins, glen), (uint32_t)plan_rule.max_rows));
         st = launch_hist(canon, GBT_PROF_HIST_ROOT, (double)n * row_bytes);
         if (st != GBT_OK) return st;
     }
@@ -2969,7 +2983,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
             const int span = gbt_prof_begin(ctx, GBT_PROF_HIST_NODE, 0.0);
             if (span >= 0) pass_spans.push_back({span, d, true});
             GBT_HIP(ctx, gbt_launch_sparse_hist(ctx, rows.rowptr, rows.ent, ent_bytes, rows.gq, pool, g.v.hjobs, (int)jobs, glen,
-                                                glen < bins, &g.v.levels[d + 1].n_hist_jobs));
+                                                glen < bins, hq_uni, &g.v.levels[d + 1].n_hist_jobs));
             gbt_prof_end(ctx);
             return GBT_OK;
         };
@@ -3225,7 +3239,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
             GBT_HIP(ctx, gbt_launch_fill_u64(s, (uint64_t *)(pool + (int64_t)first_child * hist_len), 0,
                                              (int64_t)n_children * hist_len));
             gbt_prof_end(ctx);
-            const uint32_t rpj = sparse_rows_per_job(ctx, built_rows, bins, glen);
+            const uint32_t rpj = std::min<uint32_t>(sparse_rows_per_job(ctx, built_rows, bins, glen), (uint32_t)plan_rule.max_rows);
             for (const Built &b : built) add_sparse_hist_jobs(hjobs, b.off, b.begin, b.len, bins, glen, rpj);
             st = launch_hist(rows_of(wnext), GBT_PROF_HIST_NODE, (double)built_rows * row_bytes);
             if (st != GBT_OK) return st;

@@ -518,7 +518,10 @@ int gbt_sparse_hist_tile(const gbt_ctx *ctx, int64_t bins);
 // HistJob.f0 / ft: the job's range of global bin ids
 hipError_t gbt_launch_sparse_hist(gbt_ctx *ctx, const uint32_t *rowptr, const void *ent, int ent_bytes, const int32_t *gq,
                                   int64_t *pool, const HistJob *jobs, int n_jobs, int max_glen, bool tiled,
-                                  const uint32_t *n_jobs_dev = nullptr);
+                                  // >= 0 (16-bit entries only): every row has this hessian; jobs of at most
+                                  // gbt_sparse_hist_max_rows() rows, and HistJob.pad0 as for the dense kernels
+                                  int hq_uniform, const uint32_t *n_jobs_dev = nullptr);
+int gbt_sparse_hist_max_rows();
 
 // Unordered partition of sparse rows, one launch per level (PartJob as for the dense forms; tiles of
 // gbt_sparse_part_tile() rows).  cursor: two 64-bit words per job, cleared here; afterwards the low

@@ -160,13 +160,19 @@ struct __attribute__((packed, aligned(4))) Words4 {   // four words at a 4-byte 
 
 // BLOCK: 512, or 1024 for an id range whose LDS histogram leaves room for one workgroup per compute
 // unit only.  TILED: the job covers part of the ids, entries outside it are skipped.
-template <int BLOCK, bool TILED>
+// UNI: every row has the same hessian: a word is [ g : 46 | rows : 18 ], added to with an atomic that returns nothing, and
+// nothing is tested (at most kSpUniRows rows per job; a job that is the only one of its node and id range stores its bins).
+// Bound: latency, with one workgroup per compute unit: a row's pointers lead to its entries.  So the pointers and the pair
+// are asked for two rows ahead of the row that is added, its first 16 entries one row ahead.
+constexpr int kSpUniShift = 18;
+constexpr uint32_t kSpUniRows = (1u << kSpUniShift) - 1u;
+template <int BLOCK, bool TILED, bool UNI>
 __global__ __launch_bounds__(BLOCK) void sparse_hist_kernel(const uint32_t *__restrict__ rowptr,
                                                             const uint32_t *__restrict__ ent_words,
                                                             const int2 *__restrict__ gq,
                                                             int64_t *__restrict__ pool,
                                                             const HistJob *__restrict__ jobs,
-                                                            const uint32_t *__restrict__ n_jobs_dev) {
+                                                            const uint32_t *__restrict__ n_jobs_dev, int32_t hq_uniform) {
     extern __shared__ unsigned long long lds[];
     if (n_jobs_dev && blockIdx.x >= *n_jobs_dev) return;
     const HistJob job = jobs[blockIdx.x];
@@ -174,25 +180,44 @@ __global__ __launch_bounds__(BLOCK) void sparse_hist_kernel(const uint32_t *__re
     int64_t *out = pool + job.hist_off + 2 * (int64_t)g0;
     for (uint32_t i = threadIdx.x; i < glen; i += BLOCK) lds[i] = 0;
     __syncthreads();
+    struct Row { uint32_t s, len; int2 q; };
+    auto row_at = [&](uint32_t i) __attribute__((always_inline)) -> Row {
+        Row x{0, 0, make_int2(0, 0)};
+        if (i < job.n_rows) {
+            const uint64_t r = (uint64_t)job.row_begin + i;
+            x.s = rowptr[r];
+            x.len = rowptr[r + 1];   // (its end, until the row's turn comes)
+            x.q = gq[r];
+        }
+        return x;
+    };
+    // nine words hold a step's 16 entries whatever the row's alignment; shifted so that entry k0 + k sits at halfword k
+    auto words_at = [&](uint32_t s, uint32_t k0, uint32_t (&w)[9]) __attribute__((always_inline)) {
+        const uint32_t *wp = ent_words + (s >> 1) + (k0 >> 1);
+        const Words4 lo = *(const Words4 *)wp;
+        const Words4 hi = *(const Words4 *)(wp + 4);
+        w[0] = lo.x; w[1] = lo.y; w[2] = lo.z; w[3] = lo.w;
+        w[4] = hi.x; w[5] = hi.y; w[6] = hi.z; w[7] = hi.w;
+        w[8] = wp[8];
+    };
+    Row cur = row_at(threadIdx.x), nxt = row_at(threadIdx.x + BLOCK);
+    cur.len -= cur.s;
+    uint32_t w[9], wn[9];
+    if (cur.len) words_at(cur.s, 0, w);
     for (uint32_t i = threadIdx.x; i < job.n_rows; i += BLOCK) {
-        const uint64_t r = (uint64_t)job.row_begin + i;
-        const uint32_t s = rowptr[r], len = rowptr[r + 1] - s;
-        const int2 q = gq[r];
-        const unsigned long long addv = sp_pack_pair(q);
-        const uint32_t hq = (uint32_t)q.y;
-        const uint32_t sh = (s & 1u) * 16u;               // the row starts in the upper half of its first word
-        const uint32_t *wp = ent_words + (s >> 1);
-        for (uint32_t k0 = 0; k0 < len; k0 += 16) {
-            // nine words hold the step's 16 entries whatever the row's alignment; shifted so that
-            // entry k0 + k sits at halfword k
-            const Words4 lo = *(const Words4 *)(wp + (k0 >> 1));
-            const Words4 hi = *(const Words4 *)(wp + (k0 >> 1) + 4);
-            const uint32_t w8 = wp[(k0 >> 1) + 8];
-            const uint32_t w[9] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w, w8};
+        const Row far = row_at(i + 2 * BLOCK);
+        nxt.len -= nxt.s;
+        if (nxt.len) words_at(nxt.s, 0, wn);
+        const unsigned long long addv =
+            UNI ? ((unsigned long long)(long long)cur.q.x << kSpUniShift) + 1ull : sp_pack_pair(cur.q);
+        const uint32_t hq = (uint32_t)cur.q.y;
+        const uint32_t sh = (cur.s & 1u) * 16u;               // the row starts in the upper half of its first word
+        for (uint32_t k0 = 0; k0 < cur.len; k0 += 16) {
+            if (k0) words_at(cur.s, k0, w);
             uint32_t W[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) W[k] = __builtin_amdgcn_alignbit(w[k + 1], w[k], sh);
-            const uint32_t rem = len - k0;
+            const uint32_t rem = cur.len - k0;
             uint32_t rel[16];
             unsigned long long old[16];
             uint32_t live = 0;
@@ -204,23 +229,45 @@ __global__ __launch_bounds__(BLOCK) void sparse_hist_kernel(const uint32_t *__re
                 bool in = (uint32_t)k < rem;
                 if (TILED) in = in && rel[k] < glen;
                 if (in) {
-                    live |= 1u << k;
-                    old[k] = atomicAdd(&lds[rel[k]], addv);
+                    if (UNI) {
+                        (void)__hip_atomic_fetch_add(&lds[rel[k]], addv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    } else {
+                        live |= 1u << k;
+                        old[k] = atomicAdd(&lds[rel[k]], addv);
+                    }
                 }
             }
+            if (!UNI) {
 #pragma unroll
-            for (int k = 0; k < 16; ++k)
-                if (live & (1u << k)) sp_check(out, rel[k], old[k], addv, hq);
+                for (int k = 0; k < 16; ++k)
+                    if (live & (1u << k)) sp_check(out, rel[k], old[k], addv, hq);
+            }
         }
+        cur = nxt;
+        nxt = far;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) w[k] = wn[k];
     }
     __syncthreads();
+    const bool exclusive = UNI && job.pad0 == 1u;
     for (uint32_t i = threadIdx.x; i < glen; i += BLOCK) {
-        const unsigned long long w = lds[i];
-        if (w == 0) continue;
-        const int64_t g = (int64_t)w >> kHShift;
-        const int64_t h = (int64_t)(w & kHMask);
-        if (g != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i), (unsigned long long)g);
-        if (h != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i + 1), (unsigned long long)h);
+        const unsigned long long v = lds[i];
+        if (!exclusive && v == 0) continue;
+        int64_t g, h;
+        if (UNI) {
+            const int64_t rows = (int64_t)(v & kSpUniRows);
+            g = ((int64_t)v - rows) >> kSpUniShift;
+            h = rows * hq_uniform;
+        } else {
+            g = (int64_t)v >> kHShift;
+            h = (int64_t)(v & kHMask);
+        }
+        if (exclusive) {
+            *(longlong2 *)(out + 2 * (int64_t)i) = make_longlong2(g, h);
+        } else {
+            if (g != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i), (unsigned long long)g);
+            if (h != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i + 1), (unsigned long long)h);
+        }
     }
 }
 
@@ -645,7 +692,7 @@ int gbt_sparse_hist_tile(const gbt_ctx *ctx, int64_t bins) {
 // tiled: the jobs cover parts of the id range [0, bins)
 hipError_t gbt_launch_sparse_hist(gbt_ctx *ctx, const uint32_t *rowptr, const void *ent, int ent_bytes, const int32_t *gq,
                                   int64_t *pool, const HistJob *jobs, int n_jobs, int max_glen, bool tiled,
-                                  const uint32_t *n_jobs_dev) {
+                                  int hq_uniform, const uint32_t *n_jobs_dev) {
     if (n_jobs <= 0) return hipSuccess;
     const size_t lds = (size_t)max_glen * 8;
     const bool big = lds > 64u * 1024u;   // one workgroup per compute unit: make it a large one
@@ -665,22 +712,22 @@ hipError_t gbt_launch_sparse_hist(gbt_ctx *ctx, const uint32_t *rowptr, const vo
         else sparse_hist32_kernel<512, false><<<n_jobs, 512, lds, ctx->stream>>>(rowptr, e32, g2, pool, jobs, n_jobs_dev);
         return hipGetLastError();
     }
-    const void *fn = big ? (tiled ? (const void *)sparse_hist_kernel<1024, true> : (const void *)sparse_hist_kernel<1024, false>)
-                         : (tiled ? (const void *)sparse_hist_kernel<512, true> : (const void *)sparse_hist_kernel<512, false>);
+    using K = void (*)(const uint32_t *, const uint32_t *, const int2 *, int64_t *, const HistJob *, const uint32_t *, int32_t);
+    const bool uni = hq_uniform >= 0;
+    const K fn = uni ? (big ? (tiled ? sparse_hist_kernel<1024, true, true> : sparse_hist_kernel<1024, false, true>)
+                            : (tiled ? sparse_hist_kernel<512, true, true> : sparse_hist_kernel<512, false, true>))
+                     : (big ? (tiled ? sparse_hist_kernel<1024, true, false> : sparse_hist_kernel<1024, false, false>)
+                            : (tiled ? sparse_hist_kernel<512, true, false> : sparse_hist_kernel<512, false, false>));
     GbtLdsGuard lds_guard(lds);
     if (lds_guard.needed) {
-        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    const uint32_t *words = (const uint32_t *)ent;
-    const int2 *gq2 = (const int2 *)gq;
-    if (big && tiled) sparse_hist_kernel<1024, true><<<n_jobs, 1024, lds, ctx->stream>>>(rowptr, words, gq2, pool, jobs, n_jobs_dev);
-    else if (big) sparse_hist_kernel<1024, false><<<n_jobs, 1024, lds, ctx->stream>>>(rowptr, words, gq2, pool, jobs, n_jobs_dev);
-    else if (tiled) sparse_hist_kernel<512, true><<<n_jobs, 512, lds, ctx->stream>>>(rowptr, words, gq2, pool, jobs, n_jobs_dev);
-    else sparse_hist_kernel<512, false><<<n_jobs, 512, lds, ctx->stream>>>(rowptr, words, gq2, pool, jobs, n_jobs_dev);
+    fn<<<n_jobs, big ? 1024 : 512, lds, ctx->stream>>>(rowptr, (const uint32_t *)ent, (const int2 *)gq, pool, jobs, n_jobs_dev, hq_uniform);
     return hipGetLastError();
 }
 
+int gbt_sparse_hist_max_rows() { return (int)kSpUniRows; }
 int gbt_sparse_part_tile() { return kSpTile; }
 
 hipError_t gbt_launch_sparse_partition(hipStream_t s, const uint32_t *src_rowptr, const void *src_ent, int ent_bytes,
