@@ -1020,9 +1020,14 @@ struct PlannedGrowth {
 // the most jobs `splits` built children of a matrix of n rows can be cut into
 int64_t plan_hist_jobs_max(const PlanHistRule &r, int64_t n, int64_t splits) {
     const int64_t built = n / 2 + 1;
-    // (by the shortest candidate length: its square grows with the rows, so the pieces do as well)
+    // By the shortest candidate length: b / (length(b) - 1) grows with the b rows built (length is the square root, rounded
+    // down, and at least min_rows), so that of the most rows bounds them all; without the 1, fewer rows whose length rounds
+    // down by more can make a few pieces more.
     int64_t pieces = r.pieces_max;
-    if (r.merge > 0.0) pieces = std::min(pieces, built / std::max<int64_t>(1, gbt_piece_candidate(r, built, 0)) + 1);
+    if (r.merge > 0.0) {
+        const int64_t shortest = std::max<int64_t>({1, r.min_rows, gbt_piece_candidate(r, built, 0) - 1});
+        pieces = std::min(pieces, built / shortest + 2);
+    }
     pieces = std::max(pieces, (built + r.max_rows - 1) / r.max_rows);
     return (pieces + splits) * r.tiles;
 }
@@ -1194,7 +1199,17 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
     // partition then moves whole records (symbols, gradient pair, id) into the other of two
     // word-aligned working copies, so that each node's rows stay contiguous.
     int path = grow_path(ctx, F, bits, B, tracked, pl.n_ftiles);
-    if (path == 2 && ctx->plan && !lossguide && n < kPath2Rows) path = 1;
+    const bool root_may_split = max_depth > 0 && (!lossguide || max_leaves > 1);
+    // Paths 1 and 3, depth-wise: the levels are planned on the device and enqueued without a wait.  (Path 2 and the
+    // loss-guided policy plan on the host; so does a tree too deep for the tables: its job table would not fit the
+    // workspace's, or its nodes the read-back buffer.)
+    bool planned = ctx->plan && !lossguide && root_may_split && cap <= kPlanNodesMax &&
+                   (path == 1 || path == 3 || (path == 2 && n < kPath2Rows));
+    if (planned) {
+        const PlanHistRule most = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(true));   // (the limit that makes the most jobs)
+        planned = plan_hist_jobs_max(most, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
+    }
+    if (planned && path == 2) path = 1;
     GbtRows W[2];
     for (int k = 0; k < 2; ++k) {
         W[k].sym_rw = (uint32_t *)(ws + L.wsym[k]);
@@ -1221,16 +1236,6 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
     matrix.gq_rw = nullptr;
     matrix.id_rw = nullptr;
 
-    const bool root_may_split = max_depth > 0 && (!lossguide || max_leaves > 1);
-    // Paths 1 and 3, depth-wise: the levels are planned on the device and enqueued without a wait.  (Path 2 and the
-    // loss-guided policy plan on the host; so does a tree too deep for the tables: its job table would not fit the
-    // workspace's, or its nodes the read-back buffer.)
-    bool planned = ctx->plan && !lossguide && root_may_split && (path == 1 || path == 3) && cap <= kPlanNodesMax;
-    PlanHistRule plan_rule{};
-    if (planned) {
-        plan_rule = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(true));   // (the limit that makes the most jobs)
-        planned = plan_hist_jobs_max(plan_rule, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
-    }
     const bool fix_in_hist = ctx->hist_fix && root_may_split && !planned && gbt_hist_fix_ok(bits, row_bits, pl.ft, pl.n_ftiles);
     // thresholds come from the cut table: it travels through the part of the pinned read-back buffer that
     // the split records use later, and is picked up behind the first wait below (a copy into pageable

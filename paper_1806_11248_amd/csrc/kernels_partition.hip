@@ -459,7 +459,7 @@ __global__ __launch_bounds__(kFBlock) void part_staged_kernel(
     uint32_t *__restrict__ dst_sym, int SW, int row_bits, int bits, uint32_t missing,
     const int2 *__restrict__ src_gq, int2 *__restrict__ dst_gq, const PartJob *__restrict__ jobs, int n_jobs,
     int tile_cap, unsigned long long *__restrict__ cursor, int cursor_stride, const uint32_t *__restrict__ counts_dev) {
-    extern __shared__ uint32_t stage[];                 // the tile's words, then one destination per row
+    extern __shared__ __align__(16) uint32_t stage[];   // the tile's words, then one destination per row
     __shared__ uint32_t left_base_s, right_base_s;
     __shared__ uint64_t words[kFWords];
     __shared__ uint32_t lefts_before[kFWords];
