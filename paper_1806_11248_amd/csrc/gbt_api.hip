@@ -2591,7 +2591,8 @@ static int32_t predict_impl(gbt_ctx *ctx, const gbt_tree *trees, int32_t n_trees
     if (sparse) {
         if (own_span) gbt_prof_begin(ctx, GBT_PROF_OTHER, 0.0);
         GBT_HIP(ctx, gbt_launch_sparse_walk(ctx->stream, (const char *)workspace, (const DevTree *)workspace, n_trees,
-                                            sparse->rowptr, sparse->ent, sparse->ent_bytes, n, sparse->B, eta, margin, leaf_out, max_nodes));
+                                            sparse->rowptr, sparse->ent, sparse->ent_bytes, n, F, sparse->B, eta, margin, leaf_out, max_nodes,
+                                            compact_ok));
         if (own_span) gbt_prof_end(ctx);
         return GBT_OK;
     }

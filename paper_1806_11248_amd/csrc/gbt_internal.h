@@ -533,8 +533,9 @@ hipError_t gbt_launch_sparse_partition(hipStream_t s, const uint32_t *src_rowptr
                                        int n_tiles, unsigned long long *cursor, int cursor_stride,
                                        const uint32_t *counts_dev = nullptr);
 hipError_t gbt_launch_sparse_walk(hipStream_t s, const char *ws, const DevTree *trees, int n_trees,
-                                  const uint32_t *rowptr, const void *ent, int ent_bytes, int64_t n, int B, double eta,
-                                  float *margin, int32_t *leaf_out, int max_nodes);
+                                  const uint32_t *rowptr, const void *ent, int ent_bytes, int64_t n, int F, int B, double eta,
+                                  float *margin, int32_t *leaf_out, int max_nodes,
+                                  bool compact_ok);
 
 hipError_t gbt_launch_compress(hipStream_t s, const uint16_t *sym, int64_t n_elems, int bits,
                                uint32_t *packed, int64_t n_words);

@@ -10,6 +10,8 @@
 //
 // The entry stream is read as aligned 32-bit words, up to nine words per row and step, so the buffer
 // must extend 32 entries past the last one (gbt_sparse_capacity).
+#include <type_traits>
+
 #include "gbt_internal.h"
 #include "wave_scan.h"
 
@@ -641,6 +643,125 @@ __global__ __launch_bounds__(256) void sparse_walk_kernel(const char *ws, const 
     }
 }
 
+// The same walk for 16-bit entries and trees whose right child follows the left one and whose nodes fit LDS.
+// Bound: instructions and the latency of each step (the bytes take a fifth to a half of the time), so a row's entries are
+// read once, into registers, two to a word, and a step needs no search: with d = entry - feature * B, modulo 2^16, the entry
+// of the node's feature is the one with d < B (ids below the feature wrap to at least 2^16 - feature * B >= B), so the
+// smallest d decides, a packed subtract and a packed minimum per two entries.  Halfwords of the neighbouring rows are
+// replaced by the row's first entry.  A wave takes as many words as its longest row needs, at most MAXW; a longer row is
+// bisected in the stream.  Nodes are 8 bytes, a leaf leads to itself, so that every row takes depth steps.
+// MAXW is 32, 64 or 128, the least that holds a row of all F columns: the widest form decides how many waves are resident.
+// us per call, sparse_walk_kernel and so (depth 8): 10M x 50 with 10 entries a row 291 and 145, 1M rows of 30 114 and 54,
+// of 100 282 and 104.
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 as_u16x2(uint32_t v) {
+    u16x2 r;
+    __builtin_memcpy(&r, &v, 4);
+    return r;
+}
+// node: { feature * B | bin << 16, left child | default-left << 31 }; a leaf has bin 0xffff and itself as the left child
+__device__ __forceinline__ uint32_t walk_step(const uint2 c, uint32_t d, uint32_t B) {
+    const bool left = d >= B ? (c.y >> 31) != 0 : d <= (c.x >> 16);
+    return (c.y & 0x7fffffffu) + (left ? 0u : 1u);
+}
+template <int NW, int MAXW>
+__device__ __forceinline__ uint32_t walk_row(const uint2 *nodes, int depth, uint32_t B, const uint16_t *ent, uint32_t s, uint32_t e) {
+    const uint32_t odd = s & 1u, have = e - s + odd;   // halfwords from the row's first word to its end
+    const bool none = e == s, far = have > 2u * MAXW;
+    const uint32_t *wp = (const uint32_t *)ent + (s >> 1);
+    uint32_t w[NW];
+#pragma unroll
+    for (int k = 0; k < NW; k += 4) {
+        Words4 v{0u, 0u, 0u, 0u};
+        if (!none && !far && 2u * k < have) v = *(const Words4 *)(wp + k);   // (at most 6 entries past the row: the stream's slack)
+        w[k] = v.x; w[k + 1] = v.y; w[k + 2] = v.z; w[k + 3] = v.w;
+    }
+    const uint32_t first = odd ? w[0] >> 16 : w[0] & 0xffffu, both = first | first << 16;
+    if (odd) w[0] = both;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+        if (2u * k + 1u == have) w[k] = (w[k] & 0xffffu) | (both & 0xffff0000u);
+        if (2u * k >= have) w[k] = both;
+    }
+    uint32_t node = 0;
+    for (int step = 0; step < depth; ++step) {
+        const uint2 c = nodes[node];
+        const uint32_t lo = c.x & 0xffffu;
+        uint32_t d;
+        if (far) {
+            const uint32_t g = find_feature_entry(ent, s, e, lo, B);
+            d = g == 0xffffffffu ? 0xffffu : g - lo;
+        } else {
+            const u16x2 lo2 = as_u16x2(lo | lo << 16);
+            u16x2 m = as_u16x2(w[0]) - lo2;
+#pragma unroll
+            for (int k = 1; k < NW; ++k) m = __builtin_elementwise_min(m, (u16x2)(as_u16x2(w[k]) - lo2));
+            d = m.x < m.y ? m.x : m.y;
+            d = none ? 0xffffu : d;
+        }
+        node = walk_step(c, d, B);
+    }
+    return node;
+}
+template <int MAXW>
+__global__ __launch_bounds__(256) void sparse_walk_regs_kernel(const char *ws, const DevTree *trees, int n_trees,
+                                                               const uint32_t *__restrict__ rowptr,
+                                                               const uint16_t *__restrict__ ent, int64_t n, uint32_t B,
+                                                               double eta, float *margin, int32_t *leaf_out,
+                                                               int rows_per_block, int max_nodes) {
+    extern __shared__ uint2 walk_nodes[];
+    double *weight = (double *)(walk_nodes + max_nodes);
+    const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
+    const int64_t r1 = r0 + rows_per_block < n ? r0 + rows_per_block : n;
+    for (int t = 0; t < n_trees; ++t) {
+        const DevTree T = trees[t];
+        __syncthreads();
+        for (int i = threadIdx.x; i < T.n_nodes && i < max_nodes; i += 256) {
+            const int32_t f = ((const int32_t *)(ws + T.feature))[i];
+            uint2 c;
+            if (f < 0) {
+                c = make_uint2(0xffff0000u, (uint32_t)i | 0x80000000u);
+            } else {
+                c.x = (uint32_t)f * B | (uint32_t)((const int32_t *)(ws + T.bin))[i] << 16;
+                c.y = (uint32_t)((const int32_t *)(ws + T.left))[i] | (((const int32_t *)(ws + T.default_left))[i] ? 0x80000000u : 0u);
+            }
+            walk_nodes[i] = c;
+            weight[i] = ((const double *)(ws + T.weight))[i];
+        }
+        __syncthreads();
+        const int depth = T.pad;
+        for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) {
+            const uint32_t s = rowptr[r], e = rowptr[r + 1];
+            const float m = leaf_out ? 0.f : margin[r];
+            uint32_t have = e - s + (s & 1u);
+            have = have < 2u * MAXW ? have : 2u * MAXW;
+            uint32_t node = 0;
+            bool done = false;
+            auto walk = [&](auto words) __attribute__((always_inline)) {   // (the test is the same in all lanes)
+                constexpr int NW = decltype(words)::value;
+                if constexpr (NW <= MAXW) {
+                    if (!done && (NW == MAXW || !__ballot(have > 2u * NW))) {
+                        node = walk_row<NW, MAXW>(walk_nodes, depth, B, ent, s, e);
+                        done = true;
+                    }
+                }
+            };
+            walk(std::integral_constant<int, 4>{});
+            walk(std::integral_constant<int, 8>{});
+            walk(std::integral_constant<int, 12>{});
+            walk(std::integral_constant<int, 16>{});
+            walk(std::integral_constant<int, 24>{});
+            walk(std::integral_constant<int, 32>{});
+            walk(std::integral_constant<int, 48>{});
+            walk(std::integral_constant<int, 64>{});
+            walk(std::integral_constant<int, 96>{});
+            walk(std::integral_constant<int, 128>{});
+            if (leaf_out) leaf_out[r] = (int32_t)node;
+            else margin[r] = (float)((double)m + eta * weight[node]);
+        }
+    }
+}
+
 int grid_rows(int64_t n) {
     int64_t g = (n + 255) / 256;
     if (g < 1) g = 1;
@@ -750,9 +871,25 @@ hipError_t gbt_launch_sparse_partition(hipStream_t s, const uint32_t *src_rowptr
 
 // the trees staged as for gbt_launch_predict; a tree's nodes go through LDS (32 bytes each) when they fit
 hipError_t gbt_launch_sparse_walk(hipStream_t s, const char *ws, const DevTree *trees, int n_trees,
-                                  const uint32_t *rowptr, const void *ent, int ent_bytes, int64_t n, int B, double eta,
-                                  float *margin, int32_t *leaf_out, int max_nodes) {
+                                  const uint32_t *rowptr, const void *ent, int ent_bytes, int64_t n, int F, int B, double eta,
+                                  float *margin, int32_t *leaf_out, int max_nodes, bool compact_ok) {
     if (n <= 0 || n_trees <= 0) return hipSuccess;
+    if (ent_bytes == 2 && compact_ok && (size_t)max_nodes * 16 <= 96u * 1024u) {
+        const size_t lds = (size_t)max_nodes * 16;
+        using K = void (*)(const char *, const DevTree *, int, const uint32_t *, const uint16_t *, int64_t, uint32_t, double, float *,
+                           int32_t *, int, int);
+        const K fn = F < 64 ? sparse_walk_regs_kernel<32> : F < 128 ? sparse_walk_regs_kernel<64> : sparse_walk_regs_kernel<128>;
+        GbtLdsGuard lds_guard(lds);
+        if (lds_guard.needed) {
+            hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+        }
+        // blocks short enough that few rows fill the chip
+        const int rows = n <= (int64_t)256 * 1024 ? 256 : n < (int64_t)4096 * 1024 ? 1024 : 2048;
+        fn<<<(unsigned)((n + rows - 1) / rows), 256, lds, s>>>(ws, trees, n_trees, rowptr, (const uint16_t *)ent, n, (uint32_t)B, eta,
+                                                               margin, leaf_out, rows, max_nodes);
+        return hipGetLastError();
+    }
     if ((size_t)max_nodes * sizeof(SpNode) + 4 * kWalkWords * 4 > 120u * 1024u) max_nodes = 0;   // nodes stay in HBM / L2
     const size_t lds = (size_t)max_nodes * sizeof(SpNode) + 4 * kWalkWords * 4;
     const void *fn = ent_bytes == 2 ? (const void *)sparse_walk_kernel<uint16_t> : (const void *)sparse_walk_kernel<uint32_t>;
