@@ -354,7 +354,9 @@ GBT_API size_t gbt_grow_tree_workspace_bytes(int64_t n, int32_t F, int32_t bits,
  *      then leave the rows where they are (a pass reads them in place and
  *      adds up the rows of the children to be built, for up to two levels in
  *      a row) and every third level moves them over three levels of splits
- *      at once; see GBT_TUNE_PART_NOMOVE and GBT_TUNE_PART_CYCLE
+ *      at once; see GBT_TUNE_PART_NOMOVE and GBT_TUNE_PART_CYCLE.  Below
+ *      4M rows depth-wise growth takes form 1 for these shapes, planned on
+ *      the device (GBT_TUNE_PLAN)
  *   3  rows wider than 64 words are never moved: the nodes' row-id lists are
  *      partitioned (stable, three launches) and the histogram kernel gathers
  *      the rows by id from the packed matrix

@@ -651,8 +651,8 @@ __global__ __launch_bounds__(256) void sparse_walk_kernel(const char *ws, const 
 // replaced by the row's first entry.  A wave takes as many words as its longest row needs, at most MAXW; a longer row is
 // bisected in the stream.  Nodes are 8 bytes, a leaf leads to itself, so that every row takes depth steps.
 // MAXW is 32, 64 or 128, the least that holds a row of all F columns: the widest form decides how many waves are resident.
-// us per call, sparse_walk_kernel and so (depth 8): 10M x 50 with 10 entries a row 291 and 145, 1M rows of 30 114 and 54,
-// of 100 282 and 104.
+// us per call, sparse_walk_kernel and so (depth 8): 10M x 50 with 10 entries a row 291 and 136, 1M rows of 30 114 and 54,
+// of 100 282 and 106, of 150 321 and 188; 500,000 of 300, past the registers, 229 and 243.
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u16x2 as_u16x2(uint32_t v) {
     u16x2 r;
