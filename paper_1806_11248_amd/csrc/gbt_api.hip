@@ -1,5 +1,6 @@
 // The C ABI of libgbt (see include/gbt.h) and the host side of Alg. 1.
 #include "gbt_internal.h"
+#include "tree_shape.h"
 
 #include <math.h>
 #include <stdarg.h>
@@ -2437,35 +2438,22 @@ static int32_t predict_impl(gbt_ctx *ctx, const gbt_tree *trees, int32_t n_trees
                                                    : predict_plain_bytes(trees, n_trees)),
                 GBT_ENOMEM, "workspace too small");
     bool compact_ok = true;   // the 8-byte node form of the register-window kernel applies
-    bool ordered = true;      // every child comes after its parent, in every tree
-    std::vector<int> depths((size_t)n_trees, 0), depth_of;
+    bool proper = true;       // every tree is one (no node of two parents), and its children come after their parents
+    std::vector<int> depths((size_t)n_trees, 0), scratch;
     int max_nodes = 1;
     for (int t = 0; t < n_trees; ++t) {
         const gbt_tree &T = trees[t];
         GBT_REQUIRE(ctx, T.n_nodes >= 1 && T.n_nodes <= T.capacity, GBT_EINVAL, "tree %d: bad n_nodes", t);
+        const TreeShape shape = tree_shape(T, F, scratch);
+        GBT_REQUIRE(ctx, shape.bad_node < 0, GBT_EINVAL, "tree %d node %d: bad feature or child id", t, shape.bad_node);
         max_nodes = std::max(max_nodes, T.n_nodes);
-        depth_of.assign((size_t)T.n_nodes, 0);   // the tree's depth (steps of its longest walk), if every child comes after its parent
-        int tree_depth = 0;
-        bool in_order = true;
-        for (int i = 0; i < T.n_nodes; ++i) {
-            if (T.feature[i] < 0) continue;
-            if (T.right[i] != T.left[i] + 1 || T.feature[i] >= (1 << 20) || T.bin[i] < 0 || T.bin[i] >= 4096)
-                compact_ok = false;
-            GBT_REQUIRE(ctx, T.feature[i] < F && T.left[i] >= 0 && T.left[i] < T.n_nodes && T.right[i] >= 0 &&
-                                 T.right[i] < T.n_nodes,
-                        GBT_EINVAL, "tree %d node %d: bad feature or child id", t, i);
-            in_order = in_order && T.left[i] > i && T.right[i] > i;
-            if (in_order) {
-                depth_of[T.left[i]] = depth_of[T.right[i]] = depth_of[i] + 1;
-                tree_depth = std::max(tree_depth, depth_of[i] + 1);
-            }
-        }
-        if (!in_order) compact_ok = ordered = false;
-        depths[(size_t)t] = tree_depth;
+        compact_ok = compact_ok && shape.compact;
+        proper = proper && shape.proper;
+        depths[(size_t)t] = shape.depth;
     }
     // Several trees on raw floats: one pass over the rows with the trees taken through LDS in groups
-    // (needs right == left + 1 and children after parents, which grown trees have).
-    if (may_batch && compact_ok && ordered && F <= kBatchColsMax && max_nodes < kBatchNodesMax) {
+    // (needs right == left + 1, children after parents and no shared ones, which grown trees have).
+    if (may_batch && compact_ok && proper && F <= kBatchColsMax && max_nodes < kBatchNodesMax) {
         // (1536 nodes beside the rows leave a compute unit three workgroups of a 28-feature tile: 0.267 ms for 1M rows and
         // 100 trees; 700 nodes 0.33, 1024 0.28, 2560 0.28)
         const size_t tile = gbt_predict_batch_tile_bytes(F);
@@ -2506,20 +2494,7 @@ static int32_t predict_impl(gbt_ctx *ctx, const gbt_tree *trees, int32_t n_trees
                     bw[run++] = 0.0;
                 }
                 const uint32_t base = (uint32_t)in_group;   // of this tree's nodes inside the group
-                bool odd = true;
-                for (int i = 0; i < T.n_nodes; ++i) odd = odd && (T.feature[i] < 0 || (T.left[i] & 1));
-                place.clear();
-                if (!odd) {
-                    place.assign((size_t)T.n_nodes, -1);
-                    place[0] = 0;
-                    int next = 1;
-                    for (int i = 0; i < T.n_nodes; ++i)
-                        if (T.feature[i] >= 0 && place[(size_t)i] >= 0) {
-                            place[(size_t)T.left[i]] = next;
-                            place[(size_t)T.right[i]] = next + 1;
-                            next += 2;
-                        }
-                }
+                const bool odd = tree_places(T, place);
                 auto at = [&](int i) { return odd ? i : place[(size_t)i]; };
                 in_group += T.n_nodes;
                 off[t] = (int32_t)run;

@@ -1,0 +1,69 @@
+// What the walks ask of a caller's tree, found on the host before anything is staged.
+#ifndef GBT_TREE_SHAPE_H
+#define GBT_TREE_SHAPE_H
+#include <stdint.h>
+
+#include <algorithm>
+#include <vector>
+
+#include "gbt.h"
+
+namespace {
+
+struct TreeShape {
+    int bad_node = -1;      // the first split whose feature or children do not exist: the tree is refused, nothing else is set
+    bool compact = true;    // every split has right == left + 1, feature < 2^20 and bin < 4096, and the tree is in order
+    bool in_order = true;   // children come after their parents
+    bool proper = true;     // in order, and no node is the child of two splits
+    int depth = 0;          // in order: steps of the longest walk from the root
+};
+// scratch: any vector, reused from tree to tree.
+// A node of two parents is legal (two splits may lead to the same subtree); its depth is that of the longer way to it.
+inline TreeShape tree_shape(const gbt_tree &T, int32_t F, std::vector<int> &scratch) {
+    TreeShape s;
+    std::vector<int> &depth_of = scratch;
+    depth_of.assign((size_t)T.n_nodes, 0);   // (a child's is at least 1)
+    for (int i = 0; i < T.n_nodes; ++i) {
+        if (T.feature[i] < 0) continue;
+        const int32_t l = T.left[i], r = T.right[i];
+        if (r != l + 1 || T.feature[i] >= (1 << 20) || T.bin[i] < 0 || T.bin[i] >= 4096) s.compact = false;
+        if (!(T.feature[i] < F && l >= 0 && l < T.n_nodes && r >= 0 && r < T.n_nodes)) {
+            s.bad_node = i;
+            return s;
+        }
+        s.in_order = s.in_order && l > i && r > i;
+        if (!s.in_order) continue;
+        s.proper = s.proper && l != r && depth_of[(size_t)l] == 0 && depth_of[(size_t)r] == 0;
+        const int d = depth_of[(size_t)i] + 1;
+        depth_of[(size_t)l] = std::max(depth_of[(size_t)l], d);
+        depth_of[(size_t)r] = std::max(depth_of[(size_t)r], d);
+        s.depth = std::max(s.depth, d);
+    }
+    s.compact = s.compact && s.in_order;
+    s.proper = s.proper && s.in_order;
+    return s;
+}
+
+// Places for the many-trees kernel, where every left child stands at an odd place of its tree and the right one behind it.
+// Returns true where the tree's own ids have that form (grown trees have them: pairs of children are allocated behind the
+// root); else place[i] is node i's place, -1 for one that no walk reaches.  The tree is compact and proper: a reachable
+// split then takes two places that nothing else takes, so that places stay below n_nodes.
+inline bool tree_places(const gbt_tree &T, std::vector<int32_t> &place) {
+    bool odd = true;
+    for (int i = 0; i < T.n_nodes; ++i) odd = odd && (T.feature[i] < 0 || (T.left[i] & 1));
+    place.clear();
+    if (odd) return true;
+    place.assign((size_t)T.n_nodes, -1);
+    place[0] = 0;
+    int next = 1;
+    for (int i = 0; i < T.n_nodes; ++i)
+        if (T.feature[i] >= 0 && place[(size_t)i] >= 0) {
+            place[(size_t)T.left[i]] = next;
+            place[(size_t)T.right[i]] = next + 1;
+            next += 2;
+        }
+    return false;
+}
+
+}  // namespace
+#endif

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from gpu_util import dev
+from test_host_rules import SHARED
 
 pytestmark = pytest.mark.gpu
 
@@ -190,3 +191,37 @@ def test_groups_of_trees_and_their_numbering(ctx, oracle, numbering, sizes, miss
         ref = oracle.predict_raw(t, Z, 0.3, ref)
     got = ctx.predict(trees, dev(start), 0.3, X=dev(Z)).cpu().numpy()
     assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("F,bits", [(3, 5), (9, 8), (28, 8), (57, 8)])
+@pytest.mark.parametrize("name", SHARED)
+def test_splits_that_share_children(ctx, oracle, name, F, bits):
+    """Two splits may lead to the same node: many trees and one, on raw floats, packed symbols and sparse rows."""
+    import paper_1806_11248_amd as g
+    splits, n_nodes = SHARED[name]
+    rng = np.random.default_rng(len(name) + F)
+    t = {k: np.zeros(n_nodes, v.dtype) for k, v in g.new_tree(0).items() if isinstance(v, np.ndarray)}
+    t["feature"][:], t["left"][:], t["right"][:] = -1, -1, -1
+    t["weight"][:] = rng.normal(0, 1, n_nodes)
+    for i, (f, l, r) in splits.items():
+        t["feature"][i], t["left"][i], t["right"][i], t["bin"][i] = f, l, r, rng.integers(5, 25)
+        t["threshold"][i], t["default_left"][i] = t["bin"][i] + 1, rng.integers(0, 2)   # (the values below are symbols)
+    t["n_nodes"] = t["capacity"] = n_nodes
+    n, missing = 3_001, 30
+    sym = rng.integers(0, 31, (n, F)).astype(np.uint16)
+    Z = np.where(sym == missing, np.nan, sym).astype(np.float32)
+    start = rng.standard_normal(n).astype(np.float32)
+    print(f"shared children {name} F={F} bits={bits}", flush=True)
+    trees = [t, _made_tree(rng, F, 5, "gap"), t]
+    ref = start
+    for q in trees:
+        ref = oracle.predict_raw(q, Z, 0.3, ref)
+    assert np.array_equal(ctx.predict(trees, dev(start), 0.3, X=dev(Z)).cpu().numpy(), ref)
+    ref = oracle.predict_raw(t, Z, 0.3, start)
+    assert np.array_equal(ref, oracle.predict_sym(t, sym, missing, 0.3, start))
+    assert np.array_equal(ctx.predict([t], dev(start), 0.3, X=dev(Z)).cpu().numpy(), ref)
+    packed = dev(oracle.pack(sym, bits).view(np.int32))
+    got = ctx.predict([t], dev(start), 0.3, packed=packed, bits=bits, missing_sym=missing, n=n, F=F).cpu().numpy()
+    assert np.array_equal(got, ref)
+    rowptr, ent, _ = ctx.compress_sparse(dev(sym), 32, missing)
+    assert np.array_equal(ctx.predict_sparse([t], dev(start), 0.3, rowptr, ent, n, F, 32).cpu().numpy(), ref)

@@ -1,0 +1,114 @@
+"""Rules the library's host side decides by, compiled apart from it and checked without a GPU: what a walk may assume of a
+caller's tree (csrc/tree_shape.h)."""
+import ctypes as C
+import subprocess
+
+import numpy as np
+import pytest
+
+SOURCE = r"""
+#include "tree_shape.h"
+
+// out: bad_node, compact, in_order, proper, depth, odd; place: n_nodes places (where the tree is compact, proper and not odd)
+extern "C" __attribute__((visibility("default"))) void shape_of(int n_nodes, int F, int *feature, int *bin, int *left, int *right,
+                                                                int *out, int *place) {
+    gbt_tree T{};
+    T.capacity = T.n_nodes = n_nodes;
+    T.feature = feature;
+    T.bin = bin;
+    T.left = left;
+    T.right = right;
+    std::vector<int> scratch(3, 7);
+    const TreeShape s = tree_shape(T, F, scratch);
+    out[0] = s.bad_node;
+    out[1] = s.compact;
+    out[2] = s.in_order;
+    out[3] = s.proper;
+    out[4] = s.depth;
+    out[5] = -1;
+    if (s.bad_node >= 0 || !s.compact || !s.proper) return;
+    std::vector<int32_t> p(5, 3);
+    out[5] = tree_places(T, p);
+    for (size_t i = 0; i < p.size(); ++i) place[i] = p[i];
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    from paper_1806_11248_amd import build
+    d = tmp_path_factory.mktemp("rules")
+    src, lib = d / "rules.hip", d / "librules.so"
+    src.write_text(SOURCE)
+    r = subprocess.run([build._hipcc(), *build.FLAGS, "-shared", "-o", str(lib), str(src)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return C.CDLL(str(lib))
+
+
+def _shape(rules, F, splits, n_nodes):
+    """splits: {node: (feature, left, right)}"""
+    feature, left, right = (np.full(n_nodes, -1, np.int32) for _ in range(3))
+    for i, (f, l, r) in splits.items():
+        feature[i], left[i], right[i] = f, l, r
+    out, place = np.zeros(6, np.int32), np.full(n_nodes, -9, np.int32)
+    p = [a.ctypes.data_as(C.c_void_p) for a in (feature, np.zeros(n_nodes, np.int32), left, right, out, place)]
+    rules.shape_of(n_nodes, F, *p)
+    return dict(zip(("bad_node", "compact", "in_order", "proper", "depth", "odd"), out.tolist())), place
+
+
+def _longest(splits, i=0):
+    return 1 + max(_longest(splits, c) for c in splits[i][1:]) if i in splits else 0
+
+
+# splits that lead to the same pair of children, or to pairs that overlap
+SHARED = {
+    "even ids": ({0: (0, 2, 3), 2: (1, 4, 5), 3: (2, 4, 5)}, 6),
+    "odd ids": ({0: (0, 1, 2), 1: (1, 3, 4), 2: (2, 3, 4)}, 5),
+    "overlapping pairs": ({0: (0, 1, 2), 1: (1, 3, 4), 2: (2, 4, 5)}, 6),
+    # 13 and 14 are four and three steps below the root; only the longer way counts
+    "two depths": ({0: (0, 1, 2), 1: (1, 3, 4), 2: (2, 11, 12), 3: (0, 5, 6), 5: (1, 13, 14), 11: (2, 13, 14),
+                    13: (0, 15, 16)}, 17),
+    # many parents of one pair: places handed out per parent would run far past the tree
+    "many parents": ({0: (0, 2, 3), 2: (1, 4, 5), 3: (1, 6, 7), 4: (0, 8, 9), 5: (0, 8, 9), 6: (0, 8, 9), 7: (0, 8, 9)}, 10),
+}
+
+
+@pytest.mark.parametrize("name", SHARED)
+def test_shared_children_are_no_proper_tree(rules, name):
+    splits, n_nodes = SHARED[name]
+    s, _ = _shape(rules, 3, splits, n_nodes)
+    assert s["bad_node"] == -1 and s["compact"] and s["in_order"] and not s["proper"]
+    assert s["depth"] == _longest(splits)
+
+
+def test_trees_that_are_refused_or_out_of_order(rules):
+    assert _shape(rules, 3, {0: (3, 1, 2)}, 3)[0]["bad_node"] == 0                   # no such feature
+    assert _shape(rules, 3, {0: (0, 1, 2), 2: (0, 3, 4)}, 4)[0]["bad_node"] == 2     # no such child
+    s, _ = _shape(rules, 3, {0: (0, 3, 4), 3: (1, 1, 2)}, 5)                         # a child before its parent
+    assert s["bad_node"] == -1 and not s["in_order"] and not s["proper"] and not s["compact"]
+    s, _ = _shape(rules, 3, {0: (0, 1, 1)}, 2)                                       # both children the same node
+    assert s["bad_node"] == -1 and not s["proper"] and not s["compact"]
+
+
+@pytest.mark.parametrize("gaps", [0.0, 0.3])
+def test_places_of_proper_trees(rules, gaps):
+    """Whatever the ids: every reachable node has a place of its own below n_nodes, a left child an odd one with its sibling
+    behind it, the root the first."""
+    rng = np.random.default_rng(5)
+    for n_splits in (0, 1, 2, 7, 40, 300):
+        splits, open_, at = {}, [0], 1
+        for _ in range(n_splits):
+            i = open_.pop(int(rng.integers(0, len(open_))))
+            at += int(rng.random() < gaps)
+            splits[i] = (0, at, at + 1)
+            open_ += [at, at + 1]
+            at += 2
+        s, place = _shape(rules, 1, splits, at)
+        assert s["compact"] and s["proper"] and s["depth"] == _longest(splits)
+        assert s["odd"] == all(l % 2 for _, l, _ in splits.values())
+        if s["odd"]:
+            continue
+        reached = {0} | {c for v in splits.values() for c in v[1:]}
+        assert place[0] == 0 and sorted(place[list(reached)]) == list(range(len(reached)))
+        assert all(place[i] == -1 for i in range(at) if i not in reached)
+        assert all(place[l] % 2 == 1 and place[r] == place[l] + 1 for _, l, r in splits.values())
