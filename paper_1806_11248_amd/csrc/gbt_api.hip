@@ -1018,20 +1018,6 @@ struct PlannedGrowth {
     const int32_t *nb;
     double min_child_weight;
 };
-// the most jobs `splits` built children of a matrix of n rows can be cut into
-int64_t plan_hist_jobs_max(const PlanHistRule &r, int64_t n, int64_t splits) {
-    const int64_t built = n / 2 + 1;
-    // By the shortest candidate length: b / (length(b) - 1) grows with the b rows built (length is the square root, rounded
-    // down, and at least min_rows), so that of the most rows bounds them all; without the 1, fewer rows whose length rounds
-    // down by more can make a few pieces more.
-    int64_t pieces = r.pieces_max;
-    if (r.merge > 0.0) {
-        const int64_t shortest = std::max<int64_t>({1, r.min_rows, gbt_piece_candidate(r, built, 0) - 1});
-        pieces = std::min(pieces, built / shortest + 2);
-    }
-    pieces = std::max(pieces, (built + r.max_rows - 1) / r.max_rows);
-    return (pieces + splits) * r.tiles;
-}
 // Byte symbols of at most 16 features take path 2 (whose levels the host plans, with a wait and some copies each) from this
 // many rows on, below it path 1.  us per round by path 2 and by path 1, 13 columns, depth 6: 20,000 rows 354 and 249, 300,000
 // 468 and 317, 1M 531 and 412, 3M 687 and 643, 4M 727 and 731, 7M 876 and 1018; 5M x 5 665 and 656, 5M x 16 892 and 844.
@@ -1077,10 +1063,12 @@ int32_t planned_levels(gbt_ctx *ctx, const PlannedGrowth &g, Partition partition
             const int32_t st = partition(d, nodes, g.n / g.tile_rows[last] + nodes, last);
             if (st != GBT_OK) return st;
         }
+        const int64_t jobs_max = gbt_plan_jobs_max(g.rule, g.n, nodes);
+        GBT_REQUIRE(ctx, last || jobs_max * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes, GBT_EHIP, "internal: job table");
         GBT_HIP(ctx, gbt_launch_plan_children(s, g.v, d, nodes, deferred ? nullptr : g.n_left[last],
-                                              g.n_left_stride[last], !last, g.rule));
+                                              g.n_left_stride[last], !last, g.rule, (uint32_t)jobs_max));
         if (!last) {
-            const int32_t st = hist(d, plan_hist_jobs_max(g.rule, g.n, nodes));
+            const int32_t st = hist(d, jobs_max);
             if (st != GBT_OK) return st;
         }
         *levels = d + 1;
@@ -1096,7 +1084,8 @@ int32_t read_planned_tree(gbt_ctx *ctx, const PlannedGrowth &g, int n_levels, gb
     int64_t n_nodes = 1;
     for (int d = 0; d <= n_levels; ++d) {
         n_nodes = std::max<int64_t>(n_nodes, (int64_t)lv[d].first_node + lv[d].n_nodes);
-        GBT_REQUIRE(ctx, !lv[d].bad, GBT_EHIP, "internal: a node of depth %d has fewer rows than went left", d - 1);
+        GBT_REQUIRE(ctx, !(lv[d].bad & PLAN_BAD_ROWS), GBT_EHIP, "internal: a node of depth %d has fewer rows than went left", d - 1);
+        GBT_REQUIRE(ctx, !(lv[d].bad & PLAN_BAD_JOBS), GBT_EHIP, "internal: depth %d has more histogram jobs than its launch", d);
     }
     GBT_REQUIRE(ctx, n_nodes <= g.cap_nodes && n_nodes <= tree->capacity, GBT_EHIP, "internal: %lld nodes", (long long)n_nodes);
     for (int64_t i = 0; i < n_nodes; ++i) {
@@ -1208,7 +1197,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
                    (path == 1 || path == 3 || (path == 2 && n < kPath2Rows));
     if (planned) {
         const PlanHistRule most = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(true));   // (the limit that makes the most jobs)
-        planned = plan_hist_jobs_max(most, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
+        planned = gbt_plan_jobs_max(most, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
     }
     if (planned && path == 2) path = 1;
     GbtRows W[2];
@@ -2838,7 +2827,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
     const double in_tile = (double)nnz / (double)n / plan_rule.tiles, thin = std::min(1.0, in_tile * in_tile / 64.0);
     plan_rule.merge = ((size_t)glen * 8 > 64u * 1024u ? 0.25 : 0.08) * glen / (in_tile + 8.0) * (plan_rule.tiles > 1 ? thin : 1.0) + 1e-3;
     const bool planned = ctx->plan && !lossguide && root_may_split && cap <= kPlanNodesMax &&
-                         plan_hist_jobs_max(plan_rule, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
+                         gbt_plan_jobs_max(plan_rule, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
     std::vector<float> hcuts(planned ? 0 : (size_t)F * (B - 1));
     if (!planned) GBT_HIP(ctx, hipMemcpyAsync(hcuts.data(), cuts, hcuts.size() * sizeof(float), hipMemcpyDeviceToHost, s));
 

@@ -182,13 +182,14 @@ struct DevTree {   // one tree's arrays inside the predict workspace (offsets in
 };
 
 // ---- growth planned on the device (kernels_plan.hip) -------------------------
+enum { PLAN_BAD_ROWS = 1, PLAN_BAD_JOBS = 2 };
 struct PlanLevel {           // one depth of the tree
     uint32_t n_nodes;        // nodes of this depth; their ids are consecutive, from first_node
     uint32_t first_node;
     uint32_t n_splits;       // of them split: jobs of the partition ...
     uint32_t n_tiles;        // ... and its tiles
     uint32_t n_hist_jobs;    // jobs that build this depth's histograms
-    uint32_t bad;            // a partition counted more left rows than the node has
+    uint32_t bad;            // PLAN_BAD_*: a partition counted more left rows than the node has, more jobs than the launch has
     uint64_t built_rows;     // rows of the nodes whose histogram is built
 };
 struct PlanNode {
@@ -242,6 +243,21 @@ __host__ __device__ inline double gbt_piece_cost(const PlanHistRule &r, int64_t 
     const double merged = (double)(pieces - single) + 0.25 * (double)single;
     return (share > most ? share : most) + merged * r.tiles * r.merge;
 }
+// The most jobs `splits` built children of a matrix of n rows can be cut into: the size of the launch that takes them, which
+// plan_children_kernel holds its own count against.
+inline int64_t gbt_plan_jobs_max(const PlanHistRule &r, int64_t n, int64_t splits) {
+    const int64_t built = n / 2 + 1;
+    // By the shortest candidate length: b / (length(b) - 1) grows with the b rows built (length is the square root, rounded
+    // down, and at least min_rows), so that of the most rows bounds them all; without the 1, fewer rows whose length rounds
+    // down by more can make a few pieces more.
+    int64_t pieces = r.pieces_max;
+    if (r.merge > 0.0) {
+        const int64_t shortest = std::max<int64_t>({1, r.min_rows, gbt_piece_candidate(r, built, 0) - 1});
+        pieces = std::min(pieces, built / shortest + 2);
+    }
+    pieces = std::max(pieces, (built + r.max_rows - 1) / r.max_rows);
+    return (pieces + splits) * r.tiles;
+}
 // Where the job of column tile `tile` of row piece `piece` stands among a launch's pieces * tiles jobs.  Workgroups are
 // dealt to the eight dies in turn, and each die has an L2 of its own: the tiles of a piece, which read the same rows, pairs
 // and ids, stand eight apart and meet in one L2.
@@ -272,9 +288,10 @@ struct PlanView {            // device addresses unless noted
 // sums: n_sums partial totals of the pairs (int64[2] each)
 hipError_t gbt_launch_plan_root(hipStream_t s, const PlanView &v, const int64_t *sums, int n_sums, int64_t n, int n_levels);
 hipError_t gbt_launch_plan_split(hipStream_t s, const PlanView &v, int depth, int chunks, uint32_t tile_rows);
-// n_left: left rows of split k at n_left[k * stride] (NULL: not counted yet, the children's row counts come later)
+// n_left: left rows of split k at n_left[k * stride] (NULL: not counted yet, the children's row counts come later).
+// jobs_max: what the job table and the launch behind it hold; a level that needs more gets no jobs and PLAN_BAD_JOBS
 hipError_t gbt_launch_plan_children(hipStream_t s, const PlanView &v, int depth, int64_t max_splits, const uint32_t *n_left,
-                                    int stride, bool with_hist, const PlanHistRule &rule);
+                                    int stride, bool with_hist, const PlanHistRule &rule, uint32_t jobs_max);
 hipError_t gbt_launch_plan_rank(hipStream_t s, const PlanView &v, int n_levels, uint32_t *count, uint32_t *rank);
 hipError_t gbt_launch_plan_finish(hipStream_t s, const PlanView &v, int n_levels, int last, const uint32_t *counted,
                                   PlanLevel *levels_out, PlanNode *nodes_out, uint32_t cap);

@@ -213,7 +213,7 @@ __device__ uint32_t pick_piece(const PlanHistRule &rule, int64_t rows, uint32_t 
 }
 
 __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, int d, const uint32_t *__restrict__ n_left,
-                                                                    int stride, int with_hist, PlanHistRule rule) {
+                                                                    int stride, int with_hist, PlanHistRule rule, uint32_t jobs_max) {
     __shared__ int64_t tmp[kChildBlock / 64];
     __shared__ uint32_t s_small[kPieceNodes];
     __shared__ double s_cost[kPieceCandidates];
@@ -243,8 +243,10 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
         }
         (void)block_scan<kChildBlock>(mine, tmp, &pieces);
     }
+    // (the host's bound holds for every rule and number of rows; were it short, nothing is written past the table)
+    const bool fits = pieces * rule.tiles <= (int64_t)jobs_max;
     int64_t carry = 0;
-    uint32_t bad = 0;
+    uint32_t bad = fits ? 0u : (uint32_t)PLAN_BAD_JOBS;
     for (uint32_t k0 = 0; k0 < ns; k0 += kChildBlock) {
         const uint32_t k = k0 + threadIdx.x;
         uint32_t mine = 0;   // pieces of this thread's node
@@ -253,7 +255,7 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
             const PlanJob info = v.pinfo[k];
             const PlanNode nd = v.nodes[info.node];
             const uint32_t l = left_rows(k, j.seg_len), r = j.seg_len - l;
-            if (n_left && n_left[(size_t)k * stride] > j.seg_len) bad = 1;
+            if (n_left && n_left[(size_t)k * stride] > j.seg_len) bad |= (uint32_t)PLAN_BAD_ROWS;
             const uint32_t lid = first_child + 2u * k, rid = lid + 1u;
             const bool left_small = l <= r;
             const uint32_t small = left_small ? l : r;
@@ -306,7 +308,7 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
                      i += (int64_t)gridDim.x * kChildBlock)
                     z[i] = make_ulonglong2(0ull, 0ull);
             }
-            if ((k0 + q) % gridDim.x != blockIdx.x) continue;
+            if (!fits || (k0 + q) % gridDim.x != blockIdx.x) continue;
             for (uint32_t t = threadIdx.x; t < s_pieces[q] * (uint32_t)rule.tiles; t += kChildBlock) {
                 const uint32_t piece = t / (uint32_t)rule.tiles, tile = t - piece * (uint32_t)rule.tiles;
                 HistJob h;
@@ -323,12 +325,12 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
         carry += all;
         __syncthreads();   // (the tables are rewritten)
     }
-    if (lead && bad) v.levels[d + 1].bad = 1;
+    if (lead && bad) atomicOr(&v.levels[d + 1].bad, bad);
     if (lead && threadIdx.x == 0) {
         PlanLevel &nx = v.levels[d + 1];
         nx.first_node = first_child;
         nx.n_nodes = 2u * ns;
-        nx.n_hist_jobs = (uint32_t)(pieces * rule.tiles);
+        nx.n_hist_jobs = fits ? (uint32_t)(pieces * rule.tiles) : 0u;
         nx.built_rows = (uint64_t)built;
     }
 }
@@ -386,11 +388,11 @@ hipError_t gbt_launch_plan_split(hipStream_t s, const PlanView &v, int depth, in
     return hipGetLastError();
 }
 hipError_t gbt_launch_plan_children(hipStream_t s, const PlanView &v, int depth, int64_t max_splits, const uint32_t *n_left,
-                                    int stride, bool with_hist, const PlanHistRule &rule) {
+                                    int stride, bool with_hist, const PlanHistRule &rule, uint32_t jobs_max) {
     // workgroups: enough to clear what the level may have to clear at a few kilobytes each
     const int64_t clear = with_hist ? max_splits * v.hist_len : 0;
     const int64_t grid = std::min<int64_t>(256, std::max<int64_t>(1, (clear + 2047) / 2048));
-    plan_children_kernel<<<(unsigned)grid, kChildBlock, 0, s>>>(v, depth, n_left, stride, with_hist ? 1 : 0, rule);
+    plan_children_kernel<<<(unsigned)grid, kChildBlock, 0, s>>>(v, depth, n_left, stride, with_hist ? 1 : 0, rule, jobs_max);
     return hipGetLastError();
 }
 hipError_t gbt_launch_plan_rank(hipStream_t s, const PlanView &v, int n_levels, uint32_t *count, uint32_t *rank) {

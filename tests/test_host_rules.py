@@ -1,5 +1,5 @@
 """Rules the library's host side decides by, compiled apart from it and checked without a GPU: what a walk may assume of a
-caller's tree (csrc/tree_shape.h)."""
+caller's tree (csrc/tree_shape.h), and how many histogram jobs a level planned on the device can have (csrc/gbt_internal.h)."""
 import ctypes as C
 import subprocess
 
@@ -7,11 +7,34 @@ import numpy as np
 import pytest
 
 SOURCE = r"""
+#include "gbt_internal.h"
 #include "tree_shape.h"
 
+#define API extern "C" __attribute__((visibility("default")))
+
+// The most jobs a level can have beyond gbt_plan_jobs_max (<= 0), over `count` numbers of rows its `splits` built children
+// have in all and every candidate length; each child has one row more than whole pieces.
+API long long jobs_over_bound(int num_cu, int per_cu, int tiles, long long max_rows, double merge, long long n, long long splits,
+                              const long long *rows, int count) {
+    PlanHistRule r{};
+    r.pieces_max = std::max<int64_t>(1, (int64_t)num_cu * per_cu / tiles);
+    r.min_rows = 256;
+    r.max_rows = max_rows;
+    r.merge = merge;
+    r.num_cu = num_cu;
+    r.tiles = tiles;
+    const long long bound = gbt_plan_jobs_max(r, n, splits);
+    long long over = -bound;
+    for (int k = 0; k < count; ++k)
+        for (int c = 0; c < kPieceCandidates; ++c) {
+            const long long length = gbt_piece_candidate(r, rows[k], c), with_rows = std::min(splits, rows[k]);
+            over = std::max(over, ((rows[k] - with_rows) / length + with_rows) * tiles - bound);
+        }
+    return over;
+}
+
 // out: bad_node, compact, in_order, proper, depth, odd; place: n_nodes places (where the tree is compact, proper and not odd)
-extern "C" __attribute__((visibility("default"))) void shape_of(int n_nodes, int F, int *feature, int *bin, int *left, int *right,
-                                                                int *out, int *place) {
+API void shape_of(int n_nodes, int F, int *feature, int *bin, int *left, int *right, int *out, int *place) {
     gbt_tree T{};
     T.capacity = T.n_nodes = n_nodes;
     T.feature = feature;
@@ -112,3 +135,29 @@ def test_places_of_proper_trees(rules, gaps):
         assert place[0] == 0 and sorted(place[list(reached)]) == list(range(len(reached)))
         assert all(place[i] == -1 for i in range(at) if i not in reached)
         assert all(place[l] % 2 == 1 and place[r] == place[l] + 1 for _, l, r in splits.values())
+
+
+@pytest.mark.parametrize("kind", ["dense", "sparse"])
+def test_bound_of_a_levels_histogram_jobs(rules, kind):
+    """No level makes more jobs than its launch and its table hold, for any number of rows the built children can have (half
+    the matrix): near every power of two and square (where the candidate lengths round), near the most, and at random."""
+    rng = np.random.default_rng(3)
+    rules.jobs_over_bound.restype = C.c_longlong
+    rules.jobs_over_bound.argtypes = [C.c_int] * 3 + [C.c_longlong, C.c_double] + [C.c_longlong] * 2 + [C.c_void_p, C.c_int]
+    for _ in range(3000):
+        n = int(np.exp(rng.uniform(0, np.log(4e9))))
+        most = n // 2
+        rows = np.concatenate([2 ** np.arange(32), np.arange(1, 65536, 257) ** 2, most - np.arange(64),
+                               np.exp(rng.uniform(0, np.log(most + 1), 300)).astype(np.int64)])
+        rows = np.unique(np.concatenate([rows - 1, rows, rows + 1]))
+        rows = np.ascontiguousarray(rows[(rows >= 0) & (rows <= most)], np.int64)
+        tiles = int(rng.choice([1, 1, 2, 3, 8, 40, 700]))
+        if kind == "dense":
+            per_cu, max_rows = int(rng.choice([1, 8, 64])), int(rng.choice([2 ** 18 - 1, 2 ** 21]))
+            merge = 0.15 * int(rng.integers(2, 4097)) * float(rng.choice([1, 96, 100_000])) / 96.0
+        else:
+            per_cu, max_rows = 16 * int(rng.choice([1, 64])), int(rng.choice([2 ** 18 - 1, 2 ** 24]))
+            merge = float(rng.choice([0.08, 0.25])) * int(rng.integers(64, 20_000)) / (8 + 300 * rng.random()) * rng.random() + 1e-3
+        splits = int(2 ** rng.integers(0, 16))
+        over = rules.jobs_over_bound(256, per_cu, tiles, max_rows, merge, n, splits, rows.ctypes.data, len(rows))
+        assert over <= 0, (n, tiles, per_cu, max_rows, merge, splits, over)
