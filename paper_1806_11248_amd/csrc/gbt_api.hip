@@ -850,7 +850,6 @@ namespace {
 struct PlanLayout {
     size_t levels, nodes, win, pjobs, pinfo, enodes, recs, rank_count, total;
 };
-constexpr int kPlanEvalRecords = 8192;   // gbt_eval_chunks keeps a level's records below this plus one per node
 PlanLayout plan_layout(int64_t cap_nodes, int64_t level_nodes) {
     PlanLayout P;
     size_t o = 0;
@@ -860,7 +859,7 @@ PlanLayout plan_layout(int64_t cap_nodes, int64_t level_nodes) {
     P.pjobs = o;      o += gbt_align((size_t)level_nodes * sizeof(PartJob));
     P.pinfo = o;      o += gbt_align((size_t)level_nodes * sizeof(PlanJob));
     P.enodes = o;     o += gbt_align((size_t)level_nodes * 2 * sizeof(EvalNode));
-    P.recs = o;       o += gbt_align((size_t)(kPlanEvalRecords + level_nodes) * sizeof(gbt_split));
+    P.recs = o;       o += gbt_align((size_t)gbt_eval_records_max(level_nodes) * sizeof(gbt_split));
     P.rank_count = o; o += gbt_align((size_t)cap_nodes * 4);
     P.total = o;
     return P;
@@ -1008,7 +1007,7 @@ struct PlannedGrowth {
     PlanView v;
     PlanHistRule rule;
     int max_depth, F, B;
-    int64_t n, cap_nodes;
+    int64_t n, cap_nodes, level_nodes;   // cap_nodes, level_nodes: what the tables hold
     // the partition of the last level [1] (whose children are leaves) and of the others [0]: rows of a tile, and where it
     // leaves the left rows of split k: n_left[k * n_left_stride]
     uint32_t tile_rows[2];
@@ -1049,7 +1048,7 @@ int32_t planned_levels(gbt_ctx *ctx, const PlannedGrowth &g, Partition partition
             if (nodes == 0) break;
         }
         const bool last = d + 1 == g.max_depth;
-        const int chunks = gbt_eval_chunks(g.F, (int)nodes, (size_t)-1);
+        const int chunks = gbt_eval_chunks(g.F, (int)nodes, (size_t)gbt_eval_records_max(g.level_nodes) * sizeof(gbt_split));
         EvalTail tail{nullptr, nullptr, 0, 0, -1, 0};
         tail.skip_store = last ? 1 : 0;   // (the children are leaves: nothing will subtract from these histograms)
         const int span = gbt_prof_begin(ctx, GBT_PROF_EVAL, 0.0);
@@ -1386,6 +1385,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
         g.B = B;
         g.n = n;
         g.cap_nodes = cap;
+        g.level_nodes = L.level_nodes;
         // (path 1 moves records in one launch, its last level only counts; path 3 partitions ids in three launches throughout)
         g.tile_rows[0] = path == 1 ? (uint32_t)gbt_partition_fused_tile(W[0], n) : (uint32_t)GBT_PART_TILE;
         g.tile_rows[1] = GBT_PART_TILE;
@@ -2940,6 +2940,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
         g.B = B;
         g.n = n;
         g.cap_nodes = cap;
+        g.level_nodes = L.level_nodes;
         for (int k = 0; k < 2; ++k) {
             g.tile_rows[k] = (uint32_t)gbt_sparse_part_tile();
             g.n_left[k] = (const uint32_t *)(ws + L.state);   // two cursors per job; the first one's low word: left rows

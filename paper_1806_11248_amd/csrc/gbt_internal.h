@@ -345,6 +345,9 @@ int gbt_hist_feature_tile(const gbt_ctx *ctx, int F, int B, int64_t n_rows = 0);
 
 // out receives n_nodes * n_chunks records (node-major); gbt_eval_chunks picks n_chunks.
 int gbt_eval_chunks(int F, int n_nodes, size_t record_budget_bytes);
+constexpr int kEvalGroups = 8192;   // workgroups an evaluation of many nodes is cut into, about
+// the most records of any F features and at most n_nodes nodes (fewer than one more chunk per node than fill kEvalGroups)
+inline int64_t gbt_eval_records_max(int64_t n_nodes) { return kEvalGroups + n_nodes; }
 // `out` may be host memory the device can address (the pinned staging): the records are then where the
 // host reads them when the launch has finished, without a copy.  tail: n 64-bit words copied from src to
 // dst (again possibly such host memory) by the same launch, and src cleared behind the copy if `clear`

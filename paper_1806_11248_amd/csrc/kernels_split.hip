@@ -22,7 +22,6 @@ namespace {
 
 constexpr int kEvalBlock = 256;
 constexpr int kEvalWaves = kEvalBlock / 64;
-constexpr int kEvalGroups = 8192;
 
 __device__ inline int64_t shfl_xor_i64(int64_t v, int m) {
     int lo = __shfl_xor((int)(v & 0xffffffff), m);

@@ -1,5 +1,6 @@
 """Rules the library's host side decides by, compiled apart from it and checked without a GPU: what a walk may assume of a
-caller's tree (csrc/tree_shape.h), and how many histogram jobs a level planned on the device can have (csrc/gbt_internal.h)."""
+caller's tree (csrc/tree_shape.h), and how many histogram jobs and
+evaluation records a level planned on the device can have (csrc/gbt_internal.h)."""
 import ctypes as C
 import subprocess
 
@@ -8,6 +9,7 @@ import pytest
 
 SOURCE = r"""
 #include "gbt_internal.h"
+#include "kernels_split.hip"
 #include "tree_shape.h"
 
 #define API extern "C" __attribute__((visibility("default")))
@@ -32,6 +34,10 @@ API long long jobs_over_bound(int num_cu, int per_cu, int tiles, long long max_r
         }
     return over;
 }
+
+API int eval_chunks(int F, int n_nodes, long long budget) { return gbt_eval_chunks(F, n_nodes, (size_t)budget); }
+API long long eval_records_max(long long n_nodes) { return gbt_eval_records_max(n_nodes); }
+API long long split_bytes() { return (long long)sizeof(gbt_split); }
 
 // out: bad_node, compact, in_order, proper, depth, odd; place: n_nodes places (where the tree is compact, proper and not odd)
 API void shape_of(int n_nodes, int F, int *feature, int *bin, int *left, int *right, int *out, int *place) {
@@ -161,3 +167,20 @@ def test_bound_of_a_levels_histogram_jobs(rules, kind):
         splits = int(2 ** rng.integers(0, 16))
         over = rules.jobs_over_bound(256, per_cu, tiles, max_rows, merge, n, splits, rows.ctypes.data, len(rows))
         assert over <= 0, (n, tiles, per_cu, max_rows, merge, splits, over)
+
+
+def test_bound_of_a_levels_evaluation_records(rules):
+    """The table of a planned level's split records holds every number of nodes and chunks; a budget that holds less (one
+    record per node is the least) is kept."""
+    rules.eval_records_max.restype = rules.split_bytes.restype = C.c_longlong
+    rules.eval_records_max.argtypes = [C.c_longlong]
+    rules.eval_chunks.argtypes = [C.c_int, C.c_int, C.c_longlong]
+    size = rules.split_bytes()
+    nodes = sorted({v for k in range(17) for v in (2 ** k - 1, 2 ** k, 2 ** k + 1) if 0 < v <= 65536} | set(range(1, 9000, 97)))
+    for level_nodes in (1, 64, 4096, 65536):
+        room = rules.eval_records_max(level_nodes)
+        for n_nodes in [v for v in nodes if v <= level_nodes]:
+            for F in (1, 4, 5, 13, 253, 2000, 1 << 20):
+                assert n_nodes * rules.eval_chunks(F, n_nodes, 1 << 60) <= room, (level_nodes, n_nodes, F)
+                tight = 3 * n_nodes * size
+                assert n_nodes * rules.eval_chunks(F, n_nodes, tight) * size <= tight
