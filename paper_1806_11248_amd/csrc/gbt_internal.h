@@ -215,7 +215,7 @@ struct PlanJob {             // what the children of partition job k need of its
 // (5M x 30 bytes, us per round with a fixed number of jobs per launch: 250 jobs 1790, 300 2012, 500 1987, 560 2184).
 struct PlanHistRule {
     int64_t pieces_max, min_rows, max_rows;
-    double merge;            // see above, per job; 0: pieces_max alone decides
+    double merge;            // see above, per job; more than 0
     int num_cu;
     int tiles, ft, width;    // feature (or bin id) tiles: `tiles` tiles of ft of the `width` columns (ids)
     int exclusive_ok;        // a node of one piece stores its bins
@@ -250,11 +250,8 @@ inline int64_t gbt_plan_jobs_max(const PlanHistRule &r, int64_t n, int64_t split
     // By the shortest candidate length: b / (length(b) - 1) grows with the b rows built (length is the square root, rounded
     // down, and at least min_rows), so that of the most rows bounds them all; without the 1, fewer rows whose length rounds
     // down by more can make a few pieces more.
-    int64_t pieces = r.pieces_max;
-    if (r.merge > 0.0) {
-        const int64_t shortest = std::max<int64_t>({1, r.min_rows, gbt_piece_candidate(r, built, 0) - 1});
-        pieces = std::min(pieces, built / shortest + 2);
-    }
+    const int64_t shortest = std::max<int64_t>({1, r.min_rows, gbt_piece_candidate(r, built, 0) - 1});
+    int64_t pieces = std::min(r.pieces_max, built / shortest + 2);
     pieces = std::max(pieces, (built + r.max_rows - 1) / r.max_rows);
     return (pieces + splits) * r.tiles;
 }

@@ -186,7 +186,6 @@ __global__ __launch_bounds__(kSplitBlock) void plan_split_kernel(PlanView v, int
 // more than kPieceNodes splits take the middle candidate: their nodes are one piece each nearly everywhere.
 constexpr uint32_t kPieceNodes = 2048;
 __device__ uint32_t pick_piece(const PlanHistRule &rule, int64_t rows, uint32_t ns, const uint32_t *s_small, double *s_cost) {
-    if (rule.merge <= 0.0) return (uint32_t)gbt_clamp_rows(rule, (double)((rows + rule.pieces_max - 1) / rule.pieces_max));
     if (ns > kPieceNodes) return (uint32_t)gbt_piece_candidate(rule, rows, kPieceCandidates / 2);
     static_assert(kChildBlock == 16 * kPieceCandidates, "sixteen threads per candidate");
     const int c = threadIdx.x >> 4;
