@@ -994,6 +994,7 @@ struct SparseRowsArg {   // rows in the sparse form instead of packed / X
     const void *ent;
     int32_t ent_bytes;
     int32_t B;
+    int64_t nnz;   // entries of all rows; -1: not known to the caller
 };
 static int32_t predict_impl(gbt_ctx *ctx, const gbt_tree *trees, int32_t n_trees, const uint32_t *packed,
                             int32_t bits, int32_t missing_sym, const float *X, int64_t n, int32_t F, double eta,
@@ -2554,9 +2555,11 @@ static int32_t predict_impl(gbt_ctx *ctx, const gbt_tree *trees, int32_t n_trees
     if (!big.empty()) GBT_SYNC(ctx);
     if (sparse) {
         if (own_span) gbt_prof_begin(ctx, GBT_PROF_OTHER, 0.0);
+        double steps = 0.0;
+        for (const int d : depths) steps += d;
         GBT_HIP(ctx, gbt_launch_sparse_walk(ctx->stream, (const char *)workspace, (const DevTree *)workspace, n_trees,
-                                            sparse->rowptr, sparse->ent, sparse->ent_bytes, n, F, sparse->B, eta, margin, leaf_out, max_nodes,
-                                            compact_ok));
+                                            sparse->rowptr, sparse->ent, sparse->ent_bytes, n, sparse->nnz, F, sparse->B, eta, margin,
+                                            leaf_out, max_nodes, compact_ok, steps / std::max(1, n_trees)));
         if (own_span) gbt_prof_end(ctx);
         return GBT_OK;
     }
@@ -2882,7 +2885,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
         // ---- each row's leaf by a walk of the finished tree; the row order by a stable sort on leaf rank
         int32_t *leaf_ids = leaf_of_row_out ? leaf_of_row_out : (int32_t *)w_rowptr[0];
         if (leaf_of_row_out || row_idx_out) {
-            const SparseRowsArg sr{rowptr, ent, ent_bytes, B};
+            const SparseRowsArg sr{rowptr, ent, ent_bytes, B, nnz};
             gbt_prof_begin(ctx, GBT_PROF_OTHER, (double)n * (row_bytes - 8.0 + 4.0));
             st = predict_impl(ctx, tree, 1, nullptr, 1, 0, nullptr, n, F, 0.0, nullptr, leaf_ids, ws + L.tree_stage,
                               L.tree_stage_bytes, &sr);
@@ -3265,7 +3268,7 @@ extern "C" int32_t gbt_predict_sparse(gbt_ctx *ctx, const gbt_tree *trees, int32
     GBT_REQUIRE(ctx, rowptr && ent && margin, GBT_EINVAL, "NULL argument");
     int32_t st = check_sparse_shape(ctx, n, F, max_bins);
     if (st != GBT_OK) return st;
-    const SparseRowsArg sr{rowptr, ent, sparse_ent_bytes(F, max_bins), max_bins};
+    const SparseRowsArg sr{rowptr, ent, sparse_ent_bytes(F, max_bins), max_bins, -1};
     st = predict_impl(ctx, trees, n_trees, nullptr, 1, 0, nullptr, n, F, eta, margin, nullptr, workspace, workspace_bytes,
                       &sr, true);
     if (st != GBT_OK) return st;

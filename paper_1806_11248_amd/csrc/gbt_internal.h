@@ -549,10 +549,10 @@ hipError_t gbt_launch_sparse_partition(hipStream_t s, const uint32_t *src_rowptr
                                        int32_t *dst_gq, int B, bool move, const PartJob *jobs, int n_jobs,
                                        int n_tiles, unsigned long long *cursor, int cursor_stride,
                                        const uint32_t *counts_dev = nullptr);
+// nnz: entries of all rows (-1: only the row pointers say); depth: of the trees, on average
 hipError_t gbt_launch_sparse_walk(hipStream_t s, const char *ws, const DevTree *trees, int n_trees,
-                                  const uint32_t *rowptr, const void *ent, int ent_bytes, int64_t n, int F, int B, double eta,
-                                  float *margin, int32_t *leaf_out, int max_nodes,
-                                  bool compact_ok);
+                                  const uint32_t *rowptr, const void *ent, int ent_bytes, int64_t n, int64_t nnz, int F, int B, double eta,
+                                  float *margin, int32_t *leaf_out, int max_nodes, bool compact_ok, double depth);
 
 hipError_t gbt_launch_compress(hipStream_t s, const uint16_t *sym, int64_t n_elems, int bits,
                                uint32_t *packed, int64_t n_words);

@@ -556,6 +556,18 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
 }
 
 // ---- Sec. 2.4 prediction over sparse rows -----------------------------------
+// Which of the two walks below a call takes can depend on how many entries its rows have, which the host may not know.  Both
+// are launched then, and the one that the number of entries does not concern leaves at once.
+struct WalkWhen {
+    uint64_t from, to;   // entries of all rows: `inside` says whether the launch is for more than `from` and at most `to` of
+    int inside;          // them (1), for the others (0), or for any number (-1)
+};
+__device__ __forceinline__ bool walk_leaves(const WalkWhen &w, const uint32_t *rowptr, int64_t n) {
+    if (w.inside < 0) return false;
+    const uint64_t nnz = (uint64_t)(rowptr[n] - rowptr[0]);
+    return (nnz > w.from && nnz <= w.to) != (w.inside != 0);
+}
+
 // One row per thread, trees in order, nodes staged in LDS as in the dense kernels; the row's entry of
 // a node's feature is found by bisection over the row's ascending ids.
 struct SpNode {
@@ -572,7 +584,8 @@ __global__ __launch_bounds__(256) void sparse_walk_kernel(const char *ws, const 
                                                           const uint32_t *__restrict__ rowptr,
                                                           const E *__restrict__ ent, int64_t n, uint32_t B,
                                                           double eta, float *margin, int32_t *leaf_out,
-                                                          int rows_per_block, int max_nodes) {
+                                                          int rows_per_block, int max_nodes, WalkWhen when) {
+    if (walk_leaves(when, rowptr, n)) return;
     // max_nodes == 0: the trees are too large for LDS, their nodes are read from the staged arrays
     const bool lds_nodes = max_nodes > 0;
     extern __shared__ SpNode sp_nodes[];
@@ -652,7 +665,7 @@ __global__ __launch_bounds__(256) void sparse_walk_kernel(const char *ws, const 
 // bisected in the stream.  Nodes are 8 bytes, a leaf leads to itself, so that every row takes depth steps.
 // MAXW is 32, 64 or 128, the least that holds a row of all F columns: the widest form decides how many waves are resident.
 // us per call, sparse_walk_kernel and so (depth 8): 10M x 50 with 10 entries a row 291 and 136, 1M rows of 30 114 and 54,
-// of 100 282 and 106, of 150 321 and 188; 500,000 of 300, past the registers, 229 and 243.
+// of 100 282 and 106, of 150 321 and 188; where the staged walk is the shorter way: staged_walk_range.
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u16x2 as_u16x2(uint32_t v) {
     u16x2 r;
@@ -708,7 +721,8 @@ __global__ __launch_bounds__(256) void sparse_walk_regs_kernel(const char *ws, c
                                                                const uint32_t *__restrict__ rowptr,
                                                                const uint16_t *__restrict__ ent, int64_t n, uint32_t B,
                                                                double eta, float *margin, int32_t *leaf_out,
-                                                               int rows_per_block, int max_nodes) {
+                                                               int rows_per_block, int max_nodes, WalkWhen when) {
+    if (walk_leaves(when, rowptr, n)) return;
     extern __shared__ uint2 walk_nodes[];
     double *weight = (double *)(walk_nodes + max_nodes);
     const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
@@ -869,26 +883,71 @@ hipError_t gbt_launch_sparse_partition(hipStream_t s, const uint32_t *src_rowptr
     return hipGetLastError();
 }
 
+// Numbers of entries for which sparse_walk_kernel is the shorter way (none: to == 0); depth: of the trees, on average.
+// A bisection touches one or two cache lines of a row per level, the registers take all of them whatever the tree: shallow trees
+// on long rows are bisected.  Past 256 entries both bisect, and blocks of 2048 rows, as long as three per compute unit hold them
+// all, keep fewer rows in the caches at once.  us per call, staged and by registers:
+//   rows   entries  depth 1      2            3            4            6            9
+//   270k   125      46    60     60    61     75    62     88    64     114   71     158   89
+//   270k   300      51    57     68    72     85    86     104   101    140   131    202   184
+//   1M     100      71    86     98    88     126   89     156   90     215   95     310   113
+//   1M     200      83    227    128   234    170   234    218   237    307   246    423   261
+//   1M     300      98    150    164   249    207   322    250   381    341   512    477   693
+//   2M     150      183   299    284   303    380   305    470   308    674   320    974   339
+//   2M     300      201   231    348   352    500   474    663   597    965   814    1314  1157
+//   4M     200      412   762    843   762    1280  757    1695  755    2503  766    1878  811
+//   4M     300      467   441    930   632    1406  860    1872  1092   2811  1532   2189  2237
+// Up to 256k rows the registers' blocks of 256 rows fill more of the device (20,000 rows of 300, depth 2: 53 and 30).
+WalkWhen staged_walk_range(int64_t n, double depth) {
+    constexpr int64_t kFewRows = (int64_t)256 * 1024, kHeldRows = (int64_t)2048 * 3 * 256;
+    WalkWhen w{0, 0, 1};
+    if (n <= kFewRows) return w;
+    const double held = (double)n / (double)kHeldRows;
+    double from = 40.0 + 40.0 * depth, to = 1e18;   // entries of a row
+    if (held > 1.0) {
+        from = 40.0 + 35.0 * depth * depth * held;
+        if (held > 2.0) to = 256.0;
+        if (from >= 256.0) return w;
+    } else if (2 * n > 3 * kFewRows) {
+        from = std::min(from, 256.0);
+    }
+    w.from = (uint64_t)(from * (double)n);
+    w.to = (uint64_t)std::min(to * (double)n, 1e18);
+    return w;
+}
+
 // the trees staged as for gbt_launch_predict; a tree's nodes go through LDS (32 bytes each) when they fit
 hipError_t gbt_launch_sparse_walk(hipStream_t s, const char *ws, const DevTree *trees, int n_trees,
-                                  const uint32_t *rowptr, const void *ent, int ent_bytes, int64_t n, int F, int B, double eta,
-                                  float *margin, int32_t *leaf_out, int max_nodes, bool compact_ok) {
+                                  const uint32_t *rowptr, const void *ent, int ent_bytes, int64_t n, int64_t nnz, int F, int B, double eta,
+                                  float *margin, int32_t *leaf_out, int max_nodes, bool compact_ok, double depth) {
     if (n <= 0 || n_trees <= 0) return hipSuccess;
+    WalkWhen when{0, 0, -1};
+    bool staged = true;
     if (ent_bytes == 2 && compact_ok && (size_t)max_nodes * 16 <= 96u * 1024u) {
-        const size_t lds = (size_t)max_nodes * 16;
-        using K = void (*)(const char *, const DevTree *, int, const uint32_t *, const uint16_t *, int64_t, uint32_t, double, float *,
-                           int32_t *, int, int);
-        const K fn = F < 64 ? sparse_walk_regs_kernel<32> : F < 128 ? sparse_walk_regs_kernel<64> : sparse_walk_regs_kernel<128>;
-        GbtLdsGuard lds_guard(lds);
-        if (lds_guard.needed) {
-            hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
+        const WalkWhen range = staged_walk_range(n, depth);
+        const bool may = (uint64_t)n * (uint64_t)F > range.from && range.to > 0;   // (a row has at most F entries)
+        if (nnz >= 0)
+            staged = may && (uint64_t)nnz > range.from && (uint64_t)nnz <= range.to;
+        else if ((staged = may))
+            when = range;
+        if (!staged || when.inside >= 0) {
+            const size_t lds = (size_t)max_nodes * 16;
+            using K = void (*)(const char *, const DevTree *, int, const uint32_t *, const uint16_t *, int64_t, uint32_t, double, float *,
+                               int32_t *, int, int, WalkWhen);
+            const K fn = F < 64 ? sparse_walk_regs_kernel<32> : F < 128 ? sparse_walk_regs_kernel<64> : sparse_walk_regs_kernel<128>;
+            GbtLdsGuard lds_guard(lds);
+            if (lds_guard.needed) {
+                hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                if (e != hipSuccess) return e;
+            }
+            // blocks short enough that few rows fill the chip
+            const int rows = n <= (int64_t)256 * 1024 ? 256 : n < (int64_t)4096 * 1024 ? 1024 : 2048;
+            WalkWhen others = when;
+            if (others.inside >= 0) others.inside = 0;
+            fn<<<(unsigned)((n + rows - 1) / rows), 256, lds, s>>>(ws, trees, n_trees, rowptr, (const uint16_t *)ent, n, (uint32_t)B, eta,
+                                                                   margin, leaf_out, rows, max_nodes, others);
         }
-        // blocks short enough that few rows fill the chip
-        const int rows = n <= (int64_t)256 * 1024 ? 256 : n < (int64_t)4096 * 1024 ? 1024 : 2048;
-        fn<<<(unsigned)((n + rows - 1) / rows), 256, lds, s>>>(ws, trees, n_trees, rowptr, (const uint16_t *)ent, n, (uint32_t)B, eta,
-                                                               margin, leaf_out, rows, max_nodes);
-        return hipGetLastError();
+        if (!staged) return hipGetLastError();
     }
     if ((size_t)max_nodes * sizeof(SpNode) + 4 * kWalkWords * 4 > 120u * 1024u) max_nodes = 0;   // nodes stay in HBM / L2
     const size_t lds = (size_t)max_nodes * sizeof(SpNode) + 4 * kWalkWords * 4;
@@ -902,9 +961,9 @@ hipError_t gbt_launch_sparse_walk(hipStream_t s, const char *ws, const DevTree *
     const int64_t grid = (n + rows_per_block - 1) / rows_per_block;
     if (ent_bytes == 2)
         sparse_walk_kernel<uint16_t><<<(unsigned)grid, 256, lds, s>>>(ws, trees, n_trees, rowptr, (const uint16_t *)ent, n,
-                                                                      (uint32_t)B, eta, margin, leaf_out, rows_per_block, max_nodes);
+                                                                      (uint32_t)B, eta, margin, leaf_out, rows_per_block, max_nodes, when);
     else
         sparse_walk_kernel<uint32_t><<<(unsigned)grid, 256, lds, s>>>(ws, trees, n_trees, rowptr, (const uint32_t *)ent, n,
-                                                                      (uint32_t)B, eta, margin, leaf_out, rows_per_block, max_nodes);
+                                                                      (uint32_t)B, eta, margin, leaf_out, rows_per_block, max_nodes, when);
     return hipGetLastError();
 }

@@ -66,3 +66,52 @@ def test_sparse_walk_equals_packed_walk(n, F, B, lengths, depth):
         assert torch.equal(together, margin)
     finally:
         ctx.close()
+
+
+# rows, columns, bins, share present, depth: both sides of the numbers of rows and of entries at which the walk bisects staged
+# rows instead of keeping them in registers (more than 262,144 rows; 40 + 40 per level entries a row; 1,572,864 rows)
+LONG = [
+    (262_144, 100, 128, 0.95, 1),
+    (262_145, 100, 128, 0.95, 1),
+    (262_145, 100, 128, 0.5, 1),
+    (300_001, 130, 128, 0.95, 2),    # 123 entries, from 120 on
+    (300_001, 130, 128, 0.9, 2),     # 117
+    (280_000, 300, 200, 0.99, 6),    # past the registers
+    (1_572_864, 96, 64, 0.98, 1),
+    (1_572_865, 96, 64, 0.98, 1),
+]
+
+
+@pytest.mark.parametrize("n,F,B,present,depth", LONG)
+def test_walks_of_long_rows(n, F, B, present, depth):
+    import paper_1806_11248_amd as g
+    print(f"long sparse rows n={n} F={F} B={B} present={present} depth={depth}", flush=True)
+    gen = torch.Generator("cuda").manual_seed(n + F)
+    sym = torch.empty((n, F), dtype=torch.uint16, device="cuda")
+    for a in range(0, n, 200_000):
+        m = min(200_000, n - a)
+        s = torch.randint(0, B, (m, F), device="cuda", generator=gen)
+        s[torch.rand((m, F), device="cuda", generator=gen) >= present] = B
+        sym[a:a + m] = s.to(torch.uint16)
+    ctx = g.Context(0)
+    try:
+        packed, bits = ctx.compress(sym, B)
+        rowptr, ent, nnz = ctx.compress_sparse(sym, B, B)
+        assert ent.element_size() == 2
+        cuts = torch.arange(B - 1, device="cuda", dtype=torch.float32).repeat(F, 1).contiguous()
+        nb = torch.full((F,), B, dtype=torch.int32, device="cuda")
+        y = torch.randn(n, device="cuda", generator=gen)
+        margin = torch.randn(n, device="cuda", generator=gen)
+        params = g.make_params(max_depth=depth, max_bins=B)
+        gp = ctx.gradients("squared", margin, y)
+        tree, _, leaf = ctx.grow_tree(packed, bits, n, F, B, nb, cuts, gp, params, want_rows=False)
+        sp_tree, _, sp_leaf = ctx.grow_tree_sparse(rowptr, ent, n, nnz, F, nb, cuts, gp, params, want_rows=False)
+        assert sp_tree["n_nodes"] == tree["n_nodes"] > 1 and torch.equal(leaf, sp_leaf)
+        sparse = margin.clone()
+        for _ in range(2):
+            ctx.predict([tree], margin, 0.3, packed=packed, bits=bits, missing_sym=B, n=n, F=F)
+        ctx.predict_sparse([tree, tree], sparse, 0.3, rowptr, ent, n, F, B)
+        torch.cuda.synchronize()
+        assert torch.equal(sparse, margin)
+    finally:
+        ctx.close()
