@@ -290,7 +290,8 @@ def run_workload(g, a, cfg, rows, steps, warmup, layout="dense", policy="depthwi
         f"({ms_per_step_plain:.3f} ms without event records)")
 
     # which kernels the classes of the library's profile stand for on this shape
-    path = ctx.grow_tree_path(F, bits, p["max_bins"], track_rows=False)
+    path = (ctx.grow_tree_path(F, bits, p["max_bins"], track_rows=False) if lossguide
+            else ctx.grow_tree_form(n, F, bits, p["max_bins"], p["max_depth"], track_rows=False)[0])
     root8 = bits == 8 and F <= 16
     hist_kernel = ("hist8_kernel" if root8 else "hist_b8_kernel") if bits == 8 else "hist_bits_kernel"
     node_hist_kernel = "hist_b8_kernel" if bits == 8 else "hist_bits_kernel"
@@ -302,7 +303,7 @@ def run_workload(g, a, cfg, rows, steps, warmup, layout="dense", policy="depthwi
     part_kernel = ("move_levels_kernel (rows moved over two or three levels of splits at once)"
                    + ("" if one_call else " + count2_kernel (row counts of the leaves)") if path == 2 and not lossguide else
                    "part_flag_kernel + part_scan_kernel (row counts of the last level)" if path == 2 else
-                   ("part_fused_kernel" if (F * bits + 31) // 32 == 4 else "part_staged_kernel") if path == 1 else
+                   ("part_fused_kernel" if (F * bits + 31) // 32 == 4 and n >= 1 << 20 else "part_staged_kernel") if path == 1 else
                    "part_flag_kernel + part_scan_kernel + part_scatter_kernel (row-id lists)" if path == 3 else
                    "part_flag_kernel + part_scan_kernel + part_move_kernel")
     if sparse:

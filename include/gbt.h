@@ -354,9 +354,8 @@ GBT_API size_t gbt_grow_tree_workspace_bytes(int64_t n, int32_t F, int32_t bits,
  *      then leave the rows where they are (a pass reads them in place and
  *      adds up the rows of the children to be built, for up to two levels in
  *      a row) and every third level moves them over three levels of splits
- *      at once; see GBT_TUNE_PART_NOMOVE and GBT_TUNE_PART_CYCLE.  Below
- *      4M rows depth-wise growth takes form 1 for these shapes, planned on
- *      the device (GBT_TUNE_PLAN)
+ *      at once; see GBT_TUNE_PART_NOMOVE and GBT_TUNE_PART_CYCLE.  Of few
+ *      rows depth-wise growth takes form 1 instead (gbt_grow_tree_form)
  *   3  rows wider than 64 words are never moved: the nodes' row-id lists are
  *      partitioned (stable, three launches) and the histogram kernel gathers
  *      the rows by id from the packed matrix
@@ -367,6 +366,17 @@ GBT_API size_t gbt_grow_tree_workspace_bytes(int64_t n, int32_t F, int32_t bits,
  * Negative: a GBT_E* code.
  */
 GBT_API int32_t gbt_grow_tree_path(gbt_ctx *ctx, int32_t F, int32_t bits, int32_t max_bins, int32_t track_rows);
+
+/*
+ * The form that gbt_grow_tree and gbt_boost_round take for n rows and this
+ * depth: one of the above, with GBT_GROW_PLANNED added where the levels are
+ * planned on the device, without a wait between them (forms 1 and 3; see
+ * GBT_TUNE_PLAN).  Byte symbols of at most 16 features below 2^22 rows take
+ * form 1 in place of 2 where that is so.  Negative: a GBT_E* code.
+ */
+#define GBT_GROW_PLANNED 16
+GBT_API int32_t gbt_grow_tree_form(gbt_ctx *ctx, int64_t n, int32_t F, int32_t bits, int32_t max_bins, int32_t max_depth,
+                                   int32_t track_rows);
 
 /*
  * Grows one tree depth-wise (Alg. 1 with the "closest to the root first"

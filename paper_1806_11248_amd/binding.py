@@ -17,6 +17,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libgbt.so")
 
 OK, EINVAL, ENOMEM, EHIP, EUNSUPPORTED = 0, -1, -2, -3, -4
+GROW_PLANNED = 16   # GBT_GROW_PLANNED
 PARTITION_STATIC_MAX_ROWS = 1 << 22   # GBT_PARTITION_STATIC_MAX_ROWS
 OBJECTIVES = {"squared": 0, "logistic": 1}
 
@@ -27,7 +28,7 @@ SYMBOLS = [
     "gbt_gradients", "gbt_gpair_fixed", "gbt_sum_gpair", "gbt_build_hist", "gbt_hist_subtract",
     "gbt_hist_export_f64", "gbt_eval_split", "gbt_partition_workspace_bytes", "gbt_partition",
     "gbt_partition_static",
-    "gbt_grow_tree_workspace_bytes", "gbt_grow_tree_path", "gbt_grow_tree",
+    "gbt_grow_tree_workspace_bytes", "gbt_grow_tree_path", "gbt_grow_tree_form", "gbt_grow_tree",
     "gbt_grow_tree_lossguide_workspace_bytes", "gbt_grow_tree_lossguide", "gbt_boost_round",
     "gbt_predict_workspace_bytes", "gbt_predict",
     "gbt_profile_enable", "gbt_profile_read", "gbt_measure_stream_read",
@@ -107,6 +108,8 @@ def load():
     L.gbt_grow_tree_lossguide_workspace_bytes.restype = C.c_size_t
     L.gbt_grow_tree_path.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32]
     L.gbt_grow_tree_path.restype = C.c_int32
+    L.gbt_grow_tree_form.argtypes = [C.c_void_p, C.c_int64] + [C.c_int32] * 5
+    L.gbt_grow_tree_form.restype = C.c_int32
     L.gbt_predict_workspace_bytes.argtypes = [C.c_void_p, C.c_int32]
     vp, i32, i64, u32, f64, sz = C.c_void_p, C.c_int32, C.c_int64, C.c_uint32, C.c_double, C.c_size_t
     L.gbt_quantise.argtypes = [vp, vp, vp, vp, vp, i64, i32, i32, vp, vp, vp, vp, vp, vp, sz]
@@ -556,6 +559,13 @@ class Context:
         if r < 0:
             self._check(r)
         return r
+
+    def grow_tree_form(self, n, F, bits, max_bins, max_depth, track_rows=True):
+        """(path, planned): what depth-wise growth of n rows takes, and whether its levels are planned on the device."""
+        r = self.lib.gbt_grow_tree_form(self.h, n, F, bits, max_bins, max_depth, 1 if track_rows else 0)
+        if r < 0:
+            self._check(r)
+        return r % GROW_PLANNED, r >= GROW_PLANNED
 
     # -- Sec. 2.4 ------------------------------------------------------------
     def predict_sparse(self, trees, margin, eta: float, rowptr, ent, n, F, max_bins):

@@ -1022,6 +1022,19 @@ struct PlannedGrowth {
 // many rows on, below it path 1.  us per round by path 2 and by path 1, 13 columns, depth 6: 20,000 rows 354 and 249, 300,000
 // 468 and 317, 1M 531 and 412, 3M 687 and 643, 4M 727 and 731, 7M 876 and 1018; 5M x 5 665 and 656, 5M x 16 892 and 844.
 constexpr int64_t kPath2Rows = 4 << 20;
+// How depth-wise growth goes.  Paths 1 and 3: the levels are planned on the device and enqueued without a wait.  (Path 2 and
+// the loss-guided policy plan on the host; so does a tree too deep for the tables: its job table would not fit the workspace's,
+// or its nodes the read-back buffer.)
+struct GrowForm { int path; bool planned; };
+GrowForm depthwise_form(const gbt_ctx *ctx, const HistPlan &pl, int64_t n, int F, int bits, int B, int max_depth, bool tracked) {
+    GrowForm f{grow_path(ctx, F, bits, B, tracked, pl.n_ftiles), false};
+    const int64_t cap = ((int64_t)1 << (max_depth + 1)) - 1;
+    if (!ctx->plan || max_depth < 1 || cap > kPlanNodesMax || f.path == 0 || (f.path == 2 && n >= kPath2Rows)) return f;
+    const PlanHistRule most = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(true));   // (the limit that makes the most jobs)
+    f.planned = gbt_plan_jobs_max(most, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
+    if (f.planned && f.path == 2) f.path = 1;
+    return f;
+}
 constexpr int kPlanExactDepth = 9;   // from this depth on the host waits for a level's number of splits: see planned_levels
 constexpr int kPlanWalkDepth = 10;   // a tree of at most this depth is walked from LDS at its largest size (41 KB)
 
@@ -1137,6 +1150,18 @@ PlanView plan_view(gbt_ctx *ctx, char *plan, const PlanLayout &P, char *tree_sta
 }
 }  // namespace
 
+extern "C" int32_t gbt_grow_tree_form(gbt_ctx *ctx, int64_t n, int32_t F, int32_t bits, int32_t max_bins, int32_t max_depth,
+                                      int32_t track_rows) {
+    if (!ctx) return GBT_EINVAL;
+    GBT_REQUIRE(ctx, n >= 1 && F >= 1 && bits >= 1 && bits <= GBT_MAX_BITS && max_bins >= 2 && max_depth >= 0 && max_depth <= kMaxDepth,
+                GBT_EINVAL, "bad shape");
+    HistPlan pl;
+    GBT_REQUIRE(ctx, plan_tiles(ctx, F, max_bins, bits, &pl, n), GBT_EUNSUPPORTED,
+                "max_bins = %d: one feature's bins exceed the LDS budget", max_bins);
+    const GrowForm f = depthwise_form(ctx, pl, n, F, bits, max_bins, max_depth, track_rows != 0);
+    return f.path + (f.planned ? GBT_GROW_PLANNED : 0);
+}
+
 // Alg. 1 under either policy of Sec. 2.3.  Growth proceeds in rounds: the nodes created by the round
 // before are evaluated; depth-wise then splits every one of them that may split, loss-guided only
 // the open leaf with the largest gain (smaller id on equal gains), however long ago it was created.
@@ -1188,18 +1213,11 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
     // The rows in their current order.  Level 0 reads the caller's packed matrix; every
     // partition then moves whole records (symbols, gradient pair, id) into the other of two
     // word-aligned working copies, so that each node's rows stay contiguous.
-    int path = grow_path(ctx, F, bits, B, tracked, pl.n_ftiles);
+    const GrowForm form = lossguide ? GrowForm{grow_path(ctx, F, bits, B, tracked, pl.n_ftiles), false}
+                                    : depthwise_form(ctx, pl, n, F, bits, B, max_depth, tracked);
+    const int path = form.path;
+    const bool planned = form.planned;
     const bool root_may_split = max_depth > 0 && (!lossguide || max_leaves > 1);
-    // Paths 1 and 3, depth-wise: the levels are planned on the device and enqueued without a wait.  (Path 2 and the
-    // loss-guided policy plan on the host; so does a tree too deep for the tables: its job table would not fit the
-    // workspace's, or its nodes the read-back buffer.)
-    bool planned = ctx->plan && !lossguide && root_may_split && cap <= kPlanNodesMax &&
-                   (path == 1 || path == 3 || (path == 2 && n < kPath2Rows));
-    if (planned) {
-        const PlanHistRule most = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(true));   // (the limit that makes the most jobs)
-        planned = gbt_plan_jobs_max(most, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
-    }
-    if (planned && path == 2) path = 1;
     GbtRows W[2];
     for (int k = 0; k < 2; ++k) {
         W[k].sym_rw = (uint32_t *)(ws + L.wsym[k]);

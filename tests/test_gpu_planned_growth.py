@@ -166,3 +166,42 @@ def test_few_rows_of_bytes_equal_the_fused_passes(contexts, env):
             assert torch.equal(ma, mb) and torch.equal(fa[1], fb[1]) and torch.equal(fa[2], fb[2])
     finally:
         other.close()
+
+
+@pytest.mark.parametrize("n,form", [((1 << 22) - 1, (1, True)), (1 << 22, (2, False))])
+def test_both_sides_of_the_rows_at_which_bytes_take_the_fused_passes(contexts, n, form):
+    import paper_1806_11248_amd as g
+    F, B, depth = 5, 256, 6
+    print(f"fused passes from 2^22 rows on, n={n}", flush=True)
+    planned, host = contexts
+    assert planned.grow_tree_form(n, F, 8, B, depth) == form and host.grow_tree_form(n, F, 8, B, depth) == (2, False)
+    X, y = _data(n, F, 0.0, "noise")
+    params = g.make_params(max_depth=depth, max_bins=B, eta=0.3, objective="squared")
+    cuts, nb, packed, bits, _, ms = planned.quantise_packed(X, max_bins=B)
+    assert bits == 8
+    del X
+    seen = []
+    for c in contexts:
+        margin, gpair = torch.zeros(n, device="cuda"), torch.empty((n, 2), device="cuda")
+        tree = c.boost_round(packed, bits, n, F, ms, nb, cuts, y, margin, margin, gpair, params)
+        full = c.grow_tree(packed, bits, n, F, ms, nb, cuts, gpair, params)
+        torch.cuda.synchronize()
+        seen.append((tree, margin, full))
+    (ta, ma, fa), (tb, mb, fb) = seen
+    _same_tree(ta, tb, "round")
+    _same_tree(fa[0], fb[0], "full")
+    assert torch.equal(ma, mb) and torch.equal(fa[1], fb[1]) and torch.equal(fa[2], fb[2])
+
+
+def test_form_of_a_growth(contexts):
+    """Which form a shape takes, at the edges of the rules."""
+    planned, host = contexts
+    assert planned.grow_tree_form(10_000, 28, 8, 256, 6) == (1, True) and host.grow_tree_form(10_000, 28, 8, 256, 6) == (1, False)
+    assert planned.grow_tree_form(10_000, 50, 9, 256, 6) == (3, True) and host.grow_tree_form(10_000, 50, 9, 256, 6) == (3, False)
+    assert planned.grow_tree_form(10_000, 13, 8, 256, 0) == (2, False)    # a single leaf
+    assert planned.grow_tree_form(10_000, 13, 8, 256, 15) == (1, True)
+    assert planned.grow_tree_form(10_000, 13, 8, 256, 16) == (2, False)   # more nodes than the read-back buffer holds
+    for c in contexts:
+        for bad in (dict(n=0), dict(F=0), dict(bits=17), dict(max_bins=1), dict(max_depth=17), dict(max_depth=-1)):
+            with pytest.raises(Exception):
+                c.grow_tree_form(**{**dict(n=100, F=4, bits=8, max_bins=16, max_depth=3), **bad})
