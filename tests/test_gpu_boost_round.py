@@ -45,8 +45,9 @@ def _workload(cfg, n, F=None, B=None, miss=0.0, depth=None, seed=0):
     return dict(X=X, y=d["y"] if d.get("y") is not None else d["g"], params=p)
 
 
-# (config, rows, features, bins, missing, depth, rounds): byte symbols of at most 16 features take the walk that
-# counts (grow paths 2 and, with the fused pass switched off, 1); other shapes take the plain walks
+# (config, rows, features, bins, missing, depth, rounds); planned on the host, byte symbols of at most 16 features take the
+# passes that partition and build histograms at once, and every shape whose tree fits LDS counts the last level's rows in
+# the walk under either planning
 CASES = [
     (4, 150_001, None, None, 0.0, 8, 3),      # the 115M-row workload's shape: 13 byte symbols
     (4, 70_001, 16, 256, 0.1, 6, 2),          # a missing symbol, 16 features
@@ -55,15 +56,32 @@ CASES = [
     (4, 60_000, 8, 256, 0.05, 11, 1),         # one level more: the leaves are counted by a pass of their own again
     (4, 9_000, 13, 256, 0.0, 1, 2),           # the root's children are the last level
     (4, 9_000, 13, 256, 0.0, 0, 1),           # no split at all
-    (2, 50_000, None, None, 0.0, 6, 3),       # 28 byte symbols: rows of 7 words (path 1, plain walk)
+    (2, 50_000, None, None, 0.0, 6, 3),       # 28 byte symbols: rows of 7 words (path 1)
     (3, 40_000, None, None, 0.0, 5, 2),       # 9-bit symbols, 80% missing, squared error
     (1, 10_000, None, None, 0.0, 3, 1),       # 4-bit symbols
 ]
 
 
-@pytest.mark.parametrize("cfg,n,F,B,miss,depth,rounds", CASES)
-def test_boost_round_equals_the_three_calls(ctx, oracle, cfg, n, F, B, miss, depth, rounds):
+@pytest.fixture(scope="module")
+def ctx_host():
+    """A context whose levels are planned on the host."""
+    import os
+
     import paper_1806_11248_amd as g
+    os.environ["GBT_TUNE_PLAN"] = "0"
+    try:
+        c = g.Context(0)
+    finally:
+        del os.environ["GBT_TUNE_PLAN"]
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("plan", ["device", "host"])
+@pytest.mark.parametrize("cfg,n,F,B,miss,depth,rounds", CASES)
+def test_boost_round_equals_the_three_calls(ctx, ctx_host, oracle, cfg, n, F, B, miss, depth, rounds, plan):
+    import paper_1806_11248_amd as g
+    ctx = ctx if plan == "device" else ctx_host
     d = _workload(cfg, n, F, B, miss, depth)
     p = d["params"]
     n, F = d["X"].shape

@@ -23,19 +23,20 @@ from test_gpu_tree import gpu_prep, grow_and_judge
 
 pytestmark = pytest.mark.gpu
 
-# Contexts are created under one of these settings in turn: every path the growers can take (the default
+# Contexts are created under one of these settings in turn: every path the growers can take (few rows are planned on the
+# device unless GBT_TUNE_PLAN=0, so the settings that choose between the passes planned on the host come with it; the default
 # choices, rows moved at every level or not at the last one or two or only every third level, the three-launch partition, histograms
 # apart from the partition, pairs rounded in a pass of their own, row ids carried along, one loss-guided
 # expansion per round, run-time bit widths, other workgroup shapes and LDS tile sizes, rows of up to 64 words moved instead of listed,
 # the 8-bit root histogram by the general kernel, every histogram job a single merge-free piece or many short ones)
 VARIANTS = [
     {},
-    {"GBT_TUNE_PART_NOMOVE": "0"},
-    {"GBT_TUNE_PART_NOMOVE": "1"},
-    {"GBT_TUNE_PART_CYCLE": "0"},
+    {"GBT_TUNE_PART_NOMOVE": "0", "GBT_TUNE_PLAN": "0"},
+    {"GBT_TUNE_PART_NOMOVE": "1", "GBT_TUNE_PLAN": "0"},
+    {"GBT_TUNE_PART_CYCLE": "0", "GBT_TUNE_PLAN": "0"},
     {"GBT_TUNE_PART_FUSED": "0"},
-    {"GBT_TUNE_PART_HIST": "0"},
-    {"GBT_TUNE_HIST_FIX": "0"},
+    {"GBT_TUNE_PART_HIST": "0", "GBT_TUNE_PLAN": "0"},
+    {"GBT_TUNE_HIST_FIX": "0", "GBT_TUNE_PLAN": "0"},
     {"GBT_TUNE_ORDER_ROWS": "0"},
     {"GBT_TUNE_LOSSGUIDE_BATCH": "1"},
     {"GBT_TUNE_HIST_RUNTIME_BITS": "1"},
@@ -43,7 +44,7 @@ VARIANTS = [
     {"GBT_TUNE_HIST_LDS_KB": "128"},
     {"GBT_TUNE_PART_IDS": "0"},
     {"GBT_TUNE_MOVE_MAX_WORDS": "64"},
-    {"GBT_TUNE_HIST8": "0"},
+    {"GBT_TUNE_HIST8": "0", "GBT_TUNE_PLAN": "0"},
     {"GBT_TUNE_HIST_MERGE_RATIO": "100000"},
     {"GBT_TUNE_HIST_MERGE_RATIO": "1", "GBT_TUNE_HIST_JOBS": "32"},
 ]

@@ -74,15 +74,17 @@ def check_order(tree, row_idx, leaf, n):
     return n_leaves
 
 
-@pytest.mark.parametrize("F,B,n,depth", [(4, 256, 1_500_000, 14),    # 8-bit records: partition + histogram pass
+@pytest.mark.parametrize("plan", [0, 1])
+@pytest.mark.parametrize("F,B,n,depth", [(4, 256, 1_500_000, 14),    # 8-bit records: planned on the host, the partition + histogram pass
                                          (3, 64, 300_000, 16),        # 18-bit rows: staged one-launch partition
                                          (5, 200, 9_000, 0)])         # one leaf
-def test_depthwise_order_beyond_one_pass(ctx_env, F, B, n, depth):
+def test_depthwise_order_beyond_one_pass(ctx_env, F, B, n, depth, plan):
     import paper_1806_11248_amd as g
-    c = ctx_env()
+    c = ctx_env(GBT_TUNE_PLAN=plan)
     packed, bits, nb, cuts, gp = random_symbols(c, n, F, B, 11 + F)
     params = g.make_params(max_depth=depth, max_bins=B, lam=0.0, gamma=0.0, min_child_weight=0.0)
-    _say(f"row order F={F} B={B} n={n} depth={depth} path={c.grow_tree_path(F, bits, B, track_rows=True)}")
+    _say(f"row order F={F} B={B} n={n} depth={depth} form={c.grow_tree_form(n, F, bits, B, depth)}")
+    assert c.grow_tree_form(n, F, bits, B, depth)[1] == (plan == 1 and 0 < depth < 16)
     tree, row_idx, leaf = c.grow_tree(packed, bits, n, F, B, nb, cuts, gp, params)
     n_leaves = check_order(tree, row_idx, leaf, n)
     _say(f"  {tree['n_nodes']} nodes, {n_leaves} leaves")

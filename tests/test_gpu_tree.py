@@ -166,10 +166,13 @@ def test_three_launch_partition_path(ctx_env, oracle, cfg, n, kw):
 @pytest.mark.parametrize("F,B,miss", [(1, 256, 0.0), (3, 256, 0.0), (4, 256, 0.0), (7, 256, 0.0), (8, 200, 0.1),
                                       (11, 256, 0.0), (12, 128, 0.3), (13, 256, 0.0), (14, 255, 0.05),
                                       (16, 256, 0.0)])
-def test_byte_symbols_up_to_16_features(ctx, oracle, F, B, miss):
-    """8-bit rows of one to four words: without row ids the partition pass also builds one child's
-    histogram; the trees must equal the tracked ones (separate kernels) and the oracle's."""
+@pytest.mark.parametrize("plan", [0, 1])
+def test_byte_symbols_up_to_16_features(ctx_env, oracle, F, B, miss, plan):
+    """8-bit rows of one to four words: planned on the host, the partition pass also builds one child's
+    histogram (planned on the device, so few rows are moved and added up by separate kernels); the trees must equal
+    the tracked ones and the oracle's."""
     n = 70_001
+    ctx = ctx_env(GBT_TUNE_PLAN=plan)
     d = synth.make(4, n)
     rng = np.random.default_rng(1000 * F + B)
     X = d["X"][:, rng.integers(0, d["X"].shape[1], F)].copy()
@@ -180,7 +183,7 @@ def test_byte_symbols_up_to_16_features(ctx, oracle, F, B, miss):
     dd = dict(X=X, params=p)
     _say(f"byte symbols F={F} B={B} missing={miss}")
     o, gdev = gpu_prep(ctx, oracle, dd)
-    assert gdev["bits"] == 8
+    assert gdev["bits"] == 8 and ctx.grow_tree_form(n, F, 8, B, 6, track_rows=False) == ((1, True) if plan else (2, False))
     gp = oracle.gradients(p["objective"], np.zeros(n, np.float32), d["y"])
     grow_and_judge(ctx, oracle, o, gdev, gp, p, n, F)
 
@@ -189,12 +192,16 @@ def test_byte_symbols_up_to_16_features(ctx, oracle, F, B, miss):
                                       (9, 70_001, "general"), (12, 70_001, "tiny-uniform"), (13, 2_300_003, "general"),
                                       (13, 70_001, "huge"), (14, 70_001, "general"), (16, 2_300_003, "uniform"),
                                       (16, 40_000, "general"), (13, 200, "general"), (7, 300, "uniform")])
-def test_root_histogram_forms(ctx, oracle, F, n, kind):
+@pytest.mark.parametrize("plan", [0, 1])
+def test_root_histogram_forms(ctx_env, oracle, F, n, kind, plan):
     """The root's histogram kernel for byte symbols: every slot class (1..16 features), pairs with one common
     hessian (count word, no tests) and without (packed word with carry / wrap bookkeeping), fp32 pairs rounded
     in fp32 and, where the scales leave the range in which that is exact, through fp64; inputs short enough
     for one workgroup and long enough for unequal slices per compute unit.  Judged through the tree: the
-    root's totals, its split and the gains reported come from that histogram."""
+    root's totals, its split and the gains reported come from that histogram.  Planned on the device (so few rows are,
+    by default) the pairs are rounded by a pass of their own, so the forms that round run with plan = 0."""
+    ctx = ctx_env(GBT_TUNE_PLAN=plan)
+    assert ctx.grow_tree_form(n, F, 8, 256, 2, track_rows=False) == ((1, True) if plan else (2, False))
     d = synth.make(4, max(n, 400))
     rng = np.random.default_rng(31 * F + n % 1000)
     X = d["X"][:n, rng.integers(0, d["X"].shape[1], F)].copy()
@@ -212,7 +219,7 @@ def test_root_histogram_forms(ctx, oracle, F, n, kind):
 
 
 @pytest.mark.parametrize("F", [13, 16, 5])
-def test_pass_with_carries_and_wraps_everywhere(ctx, ctx_env, oracle, F):
+def test_pass_with_carries_and_wraps_everywhere(ctx_env, oracle, F):
     """Extreme same-sign pairs piled into few bins: in the partition + histogram pass the packed LDS
     words carry and wrap every few hundred adds.  The tree must equal, to the last bit of every sum,
     the one grown through the separate histogram kernels on row lists."""
@@ -233,10 +240,11 @@ def test_pass_with_carries_and_wraps_everywhere(ctx, ctx_env, oracle, F):
     packed = dev(oracle.pack(sym, 8).view(np.int32))
     params = g.make_params(max_depth=4, max_bins=B)
     _say(f"carries and wraps in the pass, F={F}")
-    assert ctx.grow_tree_path(F, 8, B, track_rows=False) == 2
+    ctx = ctx_env(GBT_TUNE_PLAN=0)
+    assert ctx.grow_tree_form(n, F, 8, B, 4, track_rows=False) == (2, False)
     tree, _, leaf = ctx.grow_tree(packed, 8, n, F, B, dev(nb), dev(cuts), dev(gp), params, want_rows=False)
     other = ctx_env(GBT_TUNE_PART_HIST=0, GBT_TUNE_PART_FUSED=0, GBT_TUNE_ORDER_ROWS=0)
-    assert other.grow_tree_path(F, 8, B, track_rows=True) == 0
+    assert other.grow_tree_form(n, F, 8, B, 4, track_rows=True) == (0, False)
     ref, _, leaf_ref = other.grow_tree(packed, 8, n, F, B, dev(nb), dev(cuts), dev(gp), params)
     nn = tree["n_nodes"]
     assert nn > 3 and ref["n_nodes"] == nn
@@ -250,10 +258,11 @@ def test_pass_with_carries_and_wraps_everywhere(ctx, ctx_env, oracle, F):
 
 
 @pytest.mark.parametrize("F,B,miss", [(16, 200, 0.05), (6, 256, 0.0)])
-def test_byte_symbols_many_tiles(ctx, oracle, F, B, miss):
+def test_byte_symbols_many_tiles(ctx_env, oracle, F, B, miss):
     """The partition + histogram pass over millions of rows: spans of several tiles, cursors handed
     out to hundreds of workgroups, the slot classes other than the 13-feature one."""
     n = 2_500_003
+    ctx = ctx_env(GBT_TUNE_PLAN=0)
     d = synth.make(4, n)
     rng = np.random.default_rng(77 + F)
     X = d["X"][:, rng.integers(0, d["X"].shape[1], F)].copy()
@@ -263,7 +272,7 @@ def test_byte_symbols_many_tiles(ctx, oracle, F, B, miss):
     p = dict(d["params"], max_bins=B, max_depth=5)
     _say(f"byte symbols, many tiles: n={n} F={F} B={B} missing={miss}")
     o, gdev = gpu_prep(ctx, oracle, dict(X=X, params=p))
-    assert gdev["bits"] == 8 and ctx.grow_tree_path(F, 8, B, track_rows=False) == 2
+    assert gdev["bits"] == 8 and ctx.grow_tree_form(n, F, 8, B, 5, track_rows=False) == (2, False)
     gp = oracle.gradients(p["objective"], np.zeros(n, np.float32), d["y"])
     grow_and_judge(ctx, oracle, o, gdev, gp, p, n, F, nodes={0, 1, 2, 5, 12, 20, 31, 40})
 
@@ -327,15 +336,17 @@ def test_boosting_rounds_in_lock_step(ctx, oracle):
 @pytest.mark.parametrize("depth,F,miss", [(1, 13, 0.0), (2, 13, 0.0), (3, 13, 0.0), (4, 13, 0.0), (5, 13, 0.0),
                                           (6, 13, 0.0), (8, 13, 0.0), (7, 16, 0.1), (6, 3, 0.0), (9, 8, 0.3),
                                           (10, 13, 0.0), (11, 5, 0.2), (13, 12, 0.0)])
-def test_last_levels_without_moving_rows(ctx, ctx_env, oracle, depth, F, miss):
+def test_last_levels_without_moving_rows(ctx_env, oracle, depth, F, miss):
     """Byte symbols, at most 16 features: the last two levels that need histograms are built without
     moving rows (the second of them with two histograms per workgroup over the first one's segments)
     and the leaves' row counts come from a count over up to three levels of splits (depth 2:
     straight from the packed matrix).  From depth 7 on, levels further up also leave the rows in place two at a
     time and a third pass moves them over three levels of splits at once (depth 10 and 13: twice and three times
-    in a tree).  Same trees as with one such level, as with the rows moved at every level, and as without those
-    cycles."""
+    in a tree).  Same trees as with one such level, as with the rows moved at every level, as without those
+    cycles, and as planned on the device."""
     n = 120_000
+    planned, ctx = ctx_env(GBT_TUNE_PLAN=1), ctx_env(GBT_TUNE_PLAN=0)
+    assert ctx.grow_tree_form(n, F, 8, 256, depth) == (2, False) and planned.grow_tree_form(n, F, 8, 256, depth) == (1, True)
     d = synth.make(4, n)
     rng = np.random.default_rng(100 * depth + F)
     X = d["X"] if F == 13 and miss == 0.0 else d["X"][:, rng.integers(0, d["X"].shape[1], F)].copy()
@@ -353,8 +364,8 @@ def test_last_levels_without_moving_rows(ctx, ctx_env, oracle, depth, F, miss):
                            min_child_weight=p["min_child_weight"])
     nn = tree["n_nodes"]
     # (a variable stays set for the contexts made after it: the cycles need both in-place levels anyway)
-    for env in ({"GBT_TUNE_PART_CYCLE": 0}, {"GBT_TUNE_PART_NOMOVE": 0}, {"GBT_TUNE_PART_NOMOVE": 1}):
-        other, _, _ = ctx_env(**env).grow_tree(gdev["packed"], gdev["bits"], n, F, gdev["missing"], gdev["nb"], gdev["cuts"],
+    for env in (None, {"GBT_TUNE_PART_CYCLE": 0}, {"GBT_TUNE_PART_NOMOVE": 0}, {"GBT_TUNE_PART_NOMOVE": 1}):
+        other, _, _ = (planned if env is None else ctx_env(**env)).grow_tree(gdev["packed"], gdev["bits"], n, F, gdev["missing"], gdev["nb"], gdev["cuts"],
                                                dev(gp), params, want_rows=False, want_leaf=False)
         assert other["n_nodes"] == nn
         for k in ("feature", "bin", "default_left", "left", "right", "n_rows", "weight", "gain", "sumG", "sumH"):
