@@ -2384,21 +2384,23 @@ BatchLayout batch_layout(size_t base, int64_t total_nodes, int32_t n_trees) {
     return L;
 }
 // Many trees on wide rows: one pass that stages whole rows (the many-trees kernel, `lds` bytes a workgroup, `steps` = depth + 1
-// over all trees), or a kernel per tree that gathers the few values a walk asks for.  Up to 95 features the one pass is never
-// the longer way.  Beyond, few waves of it fit a compute unit and every one reads all F values of its rows: in us, per round
-// of resident rows, some 0.1 F for the rows and 0.09 per step (0.35 where a group holds a single tree); a kernel per tree
-// takes its launch and 3 to 12 per step, up to 1M rows by its latency and beyond by its gathers.  1M rows x 300, in us by
-// one pass and by tree: 2 trees of depth 3 1633 and 99, 60 of them 2361 and 2575; 10,000 rows x 300: 46 and 59, 119 and 1158;
-// 1M x 129: 2 trees 371 and 87, 16 trees 442 and 626.  The constants are a fit to 1600 such pairs (96 to 500 features, 200 to
-// 3M rows, 2 to 60 trees of depth 3 to 9): what the rule takes is at most 1.24 times the better one, 1.003 on average.
+// over all trees), or a kernel per tree that gathers the few values a walk asks for.  Up to 95 features the one pass is
+// within 1 % of the shorter way on average (at most 1.34 times it).  Beyond, few waves of it fit a compute unit and every one
+// reads all F values of its rows: in us, per round of resident rows, some 0.11 F for the rows and 0.09 per step (0.38 where a
+// group holds a single tree), and one per tree for the staging; a kernel per tree takes its launch and 0.8 per level by
+// latency, or 17 per level and million rows by its gathers (fewer where rows share a line).  us by one pass and by tree:
+// 100,835 rows x 249, 3 trees of depth 4 136 and 42; 48,147 x 469, 3 of depth 9 193 and 58; 238,596 x 223, 3 of depth 8 236
+// and 123; 1.7M x 194, 23 of depth 9 4404 and 5411.  The constants are a fit to 1000 such pairs (96 to 500 features, 200 to
+// 3M rows, 2 to 60 trees of depth 3 to 9); of 560 others, what the rule takes is on average as long as the better one within
+// the 1 % that runs differ, 1.24 times at most.
 bool batch_pays(const gbt_ctx *ctx, int64_t n, int F, int n_trees, int64_t steps, size_t lds, bool one_tree_groups) {
     if (F < 96) return true;
     const int rows = gbt_predict_batch_rows(F);
     const int waves = std::max(1, std::min(32, (int)(ctx->lds_max / lds) * (rows / 64)));   // of a compute unit
     const double rounds = std::ceil((double)n / ((double)ctx->num_cu * waves * 64.0)), m = (double)n * 1e-6;
-    const double one_pass = rounds * ((0.1 + 0.012 * waves) * F + (one_tree_groups ? 0.35 : 0.09) * (double)steps);
-    const double step = std::max(5.0 * std::min(1.0, (double)n / 5e3) + 3.0 * std::min(1.0, (double)n / 1e5) + 4.5 * m, 11.0 * m);
-    return one_pass < 2.0 * n_trees + step * (double)steps;
+    const double one_pass = 24.0 + 1.1 * n_trees + rounds * ((0.11 + 0.006 * waves) * F + (one_tree_groups ? 0.38 : 0.09) * (double)steps);
+    const double level = std::max(0.8, 17.0 * m * std::min(1.0, F / 120.0));
+    return one_pass < 20.0 + n_trees + level * (double)(steps - n_trees);
 }
 // A threshold in the order of the many-trees kernel's integer values (gbt_batch_node): value + a >= thr sends a row right.
 int32_t batch_threshold(float thr, uint32_t a) {
@@ -2462,8 +2464,8 @@ static int32_t predict_impl(gbt_ctx *ctx, const gbt_tree *trees, int32_t n_trees
     // Several trees on raw floats: one pass over the rows with the trees taken through LDS in groups
     // (needs right == left + 1, children after parents and no shared ones, which grown trees have).
     if (may_batch && compact_ok && proper && F <= kBatchColsMax && max_nodes < kBatchNodesMax) {
-        // (1536 nodes beside the rows leave a compute unit three workgroups of a 28-feature tile: 0.267 ms for 1M rows and
-        // 100 trees; 700 nodes 0.33, 1024 0.28, 2560 0.28)
+        // (1536 nodes beside the rows leave a compute unit four workgroups of a 28-feature tile: 341 us a call for 1M rows and
+        // 100 trees; 512 nodes 382, 700 453, 1024 353, 2048 385, 2560 374)
         const size_t tile = gbt_predict_batch_tile_bytes(F);
         const int cap_nodes = std::max(tile + (size_t)1536 * 8 <= ctx->lds_per_block ? 1536 : 2, (max_nodes + 2) & ~1);
         const size_t lds = tile + (size_t)cap_nodes * 8;
