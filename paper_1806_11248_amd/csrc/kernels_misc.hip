@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kRedBlock) void absmax_kernel(const float2 *gp, int
         lh = min(lh, min(b0, b1));
         neg |= (v.y < 0.0f || v.w < 0.0f) ? 1u : 0u;
     };
-    // a workgroup takes contiguous chunks of kStreamBatch * kBlock pieces; whole chunks need no conditional load
+    // a workgroup takes contiguous chunks of kStreamBatch * kRedBlock pieces; whole chunks need no conditional load
     const int64_t chunk = (int64_t)kStreamBatch * kRedBlock, n_whole = n4 / chunk;
     for (int64_t c = blockIdx.x; c < n_whole; c += gridDim.x) {
         float4 v[kStreamBatch];
@@ -606,7 +606,7 @@ __global__ __launch_bounds__(256) void predict_gather_kernel(const char *ws, con
 // piece of the bit stream, which the wave fetches linearly into an LDS window of its own; every level's symbol is
 // then cut out of LDS instead of being gathered from memory, one dependent access per level.  Nodes as in
 // predict_window_kernel.  wave_words: words of a wave's window (64 rows and one word of slack).
-constexpr int kStagedRowBits = 1024;
+constexpr int kStagedRowBits = 1024, kGatheredRowBits = 320;   // (see walk_form)
 __global__ __launch_bounds__(256) void predict_staged_kernel(const char *ws, const DevTree *trees, int n_trees,
                                                              const uint32_t *packed, int64_t n_words, int bits,
                                                              uint32_t missing, int64_t n, int F, double eta,
@@ -1134,14 +1134,16 @@ hipError_t gbt_launch_predict_raw_batched(hipStream_t s, const gbt_batch_node *n
 namespace {
 enum { WALK_B8, WALK_WINDOW, WALK_STAGED, WALK_GATHER };
 int staged_wave_words(int bits, int F) { return (int)((64 * (int64_t)F * bits + 31) / 32) + 2; }
-// Rows staged through LDS, a wave's 64 at a time, where a row is wider than 32 bytes: a narrower one lies in one cache
-// line that the gathers of its levels all hit (1M x 28 bytes measured 0.107 ms gathered against 0.121 ms staged; 10M x 57
-// bytes 0.39 against 0.30 ms).
+// Rows staged through LDS, a wave's 64 at a time, where a row is wider than 40 bytes: a narrower one lies in a cache line or
+// two that the gathers of its levels all hit.  us per call, gathered and staged, one tree of depth 3, 6 and 9, 10M rows: of 28
+// bytes 99 and 188, 133 and 196, 181 and 219; of 33 116 and 211, 164 and 219, 224 and 243; of 40 138 and 243, 205 and 251, 279
+// and 275; of 57 202 and 317, 355 and 326, 514 and 355; of 112 424 and 554, 826 and 560, 1230 and 979 (below depth 5 the
+// gathers are the shorter way for wider rows as well; 200,000 rows take the same time either way).
 int walk_form(int bits, int F, int max_nodes, bool counts, size_t *lds) {
     const int64_t row_bits = (int64_t)F * bits;
     *lds = (size_t)max_nodes * (16 + (counts ? 4 : 0));
     if (row_bits <= 128) return bits == 8 && F <= 16 && max_nodes <= (1 << 20) ? WALK_B8 : WALK_WINDOW;   // (node ids of 20 bits)
-    if (row_bits > 256 && row_bits <= kStagedRowBits) {
+    if (row_bits > kGatheredRowBits && row_bits <= kStagedRowBits) {
         const size_t staged = *lds + (size_t)4 * staged_wave_words(bits, F) * 4;
         if (staged <= kWalkLds) {
             *lds = staged;
