@@ -441,7 +441,7 @@ __global__ __launch_bounds__(kFBlock) void part_fused_kernel(
 // from LDS to its new place by a group of lanes, one word per lane.  The tile holds as many rows as
 // fit kStageBytes (at most kFTile).  What it waits for is latency, so everything is asked for in groups: the
 // pairs first, four 16-byte pieces of the rows per thread, four rows per lane on the way out (1M x 28 bytes: 38 us
-// per level with one word and one row at a time, 25 so).
+// per level with one word and one row at a time, 22 to 24 so).
 constexpr int kStageBytes = 48 * 1024;
 constexpr int64_t kFusedRows = 1 << 20;   // (1M x 13 bytes: either form takes the same time within 5 %)
 // Rows of a tile: no more than give a matrix of n rows a tile per compute unit (50,000 x 24 bytes: 18 us per level with
