@@ -21,26 +21,48 @@ struct TreeShape {
 // A node of two parents is legal (two splits may lead to the same subtree); its depth is that of the longer way to it.
 inline TreeShape tree_shape(const gbt_tree &T, int32_t F, std::vector<int> &scratch) {
     TreeShape s;
-    std::vector<int> &depth_of = scratch;
-    depth_of.assign((size_t)T.n_nodes, 0);   // (a child's is at least 1)
-    for (int i = 0; i < T.n_nodes; ++i) {
-        if (T.feature[i] < 0) continue;
+    scratch.assign((size_t)T.n_nodes, 0);
+    int *depth_of = scratch.data();   // (a child's is at least 1)
+    const int n = T.n_nodes;
+    int splits = 0, last = 0;
+    bool ascending = true;   // pairs of children in ascending order share none
+    for (int i = 0; i < n; ++i) {
+        const int32_t f = T.feature[i];
+        if (f < 0) continue;
         const int32_t l = T.left[i], r = T.right[i];
-        if (r != l + 1 || T.feature[i] >= (1 << 20) || T.bin[i] < 0 || T.bin[i] >= 4096) s.compact = false;
-        if (!(T.feature[i] < F && l >= 0 && l < T.n_nodes && r >= 0 && r < T.n_nodes)) {
+        if (r != l + 1 || f >= (1 << 20) || T.bin[i] < 0 || T.bin[i] >= 4096) s.compact = false;
+        if (f >= F || l < 0 || l >= n || r < 0 || r >= n) {
             s.bad_node = i;
             return s;
         }
         s.in_order = s.in_order && l > i && r > i;
-        if (!s.in_order) continue;
-        s.proper = s.proper && l != r && depth_of[(size_t)l] == 0 && depth_of[(size_t)r] == 0;
-        const int d = depth_of[(size_t)i] + 1;
-        depth_of[(size_t)l] = std::max(depth_of[(size_t)l], d);
-        depth_of[(size_t)r] = std::max(depth_of[(size_t)r], d);
-        s.depth = std::max(s.depth, d);
+        ascending = ascending && l > last && r > l;
+        last = r;
+        ++splits;
+        if (s.in_order) {
+            const int d = depth_of[i] + 1;
+            depth_of[l] = depth_of[r] = d;
+            if (d > s.depth) s.depth = d;
+        }
     }
-    s.compact = s.compact && s.in_order;
-    s.proper = s.proper && s.in_order;
+    if (!s.in_order) {
+        s.compact = s.proper = false;
+    } else if (!ascending) {
+        int children = 0;
+        for (int i = 0; i < n; ++i) children += depth_of[i] != 0;
+        s.proper = children == 2 * splits;
+        if (!s.proper) {
+            scratch.assign((size_t)n, 0);
+            s.depth = 0;
+            for (int i = 0; i < n; ++i) {
+                if (T.feature[i] < 0) continue;
+                const int32_t l = T.left[i], r = T.right[i], d = depth_of[i] + 1;
+                depth_of[l] = std::max(depth_of[l], d);
+                depth_of[r] = std::max(depth_of[r], d);
+                s.depth = std::max(s.depth, d);
+            }
+        }
+    }
     return s;
 }
 
