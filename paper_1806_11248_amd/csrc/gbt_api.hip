@@ -1265,7 +1265,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
     // every node, so the children of the last level (leaves, of which only the row counts are wanted) need no
     // counting pass of their own.
     const bool defer_counts = margin_update && !tracked && !leaf_of_row_out && !lossguide && path != 0 &&
-                              cap <= 8192 && gbt_predict_counts_ok(true, bits, F, (int)cap, true);
+                              cap <= 8192 && gbt_predict_counts_ok(true, bits, F, n, (int)cap, true);
     std::vector<int32_t> deferred_children;
     int uniform_h = 0;
     float h_value = 0.0f;
@@ -1418,7 +1418,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
         g.min_child_weight = params->min_child_weight;
         // The rest of the call can be enqueued behind the levels as well where the tree is walked from LDS at the size it
         // may have, and a wanted row order has ranks of one byte; otherwise the host waits for the tree first.
-        const bool walk_now = max_depth <= kPlanWalkDepth && gbt_predict_counts_ok(true, bits, F, (int)cap, true) &&
+        const bool walk_now = max_depth <= kPlanWalkDepth && gbt_predict_counts_ok(true, bits, F, n, (int)cap, true) &&
                               !(tracked && (path == 3 || max_depth > 8));
         const bool will_walk = margin_update || leaf_of_row_out || (tracked && path == 1);
         g.defer_last = walk_now ? will_walk : defer_counts;
@@ -2588,7 +2588,7 @@ static int32_t predict_impl(gbt_ctx *ctx, const gbt_tree *trees, int32_t n_trees
     if (margin_src == margin) margin_src = nullptr;
     if (margin_src) {
         GBT_REQUIRE(ctx, n_trees == 1 && margin && !leaf_out && !sparse, GBT_EINVAL, "internal: margin_src");
-        if (!gbt_predict_counts_ok(packed != nullptr, bits, F, max_nodes, compact_ok)) {   // no kernel form reads it: copy first
+        if (!gbt_predict_counts_ok(packed != nullptr, bits, F, n, max_nodes, compact_ok)) {   // no kernel form reads it: copy first
             GBT_HIP(ctx, hipMemcpyAsync(margin, margin_src, (size_t)n * sizeof(float), hipMemcpyDeviceToDevice, ctx->stream));
             margin_src = nullptr;
         }

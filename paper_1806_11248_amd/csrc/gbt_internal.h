@@ -565,7 +565,7 @@ hipError_t gbt_launch_predict(hipStream_t s, const char *ws, const DevTree *tree
 // node_rows, margin_src (one tree, and only where gbt_predict_counts_ok): count the rows that end in every node into
 // node_rows[node * kNodeRowsStride] (zeroed by the caller); margin[r] = margin_src[r] + eta * weight
 constexpr int kNodeRowsStride = 32;   // words between two nodes' row counters (gbt_launch_predict's node_rows)
-bool gbt_predict_counts_ok(bool packed, int bits, int F, int max_nodes, bool compact_ok);
+bool gbt_predict_counts_ok(bool packed, int bits, int F, int64_t n, int max_nodes, bool compact_ok);
 // compact_ok: every split node has right == left + 1, feature < 2^20 and bin < 4096
 
 // Many trees on raw floats in one pass over the rows (kernels_misc.hip).  A node is 8 bytes: values are compared as

@@ -1152,6 +1152,19 @@ int walk_form(int bits, int F, int max_nodes, bool counts, size_t *lds) {
     }
     return WALK_GATHER;
 }
+// Trees that a walk over packed symbols keeps in LDS.  Every workgroup stages the whole tree, and past 80 KB a compute unit
+// holds one workgroup: larger trees are read from the caches, but where rows are many and their own reads few.  us per call,
+// from LDS and from the caches, 3071, 4095 and 4801 nodes: 100,000 rows of 28 bytes 47 and 43, 52 and 44, 57 and 47; 1M of 14 symbols of 9
+// bits 78 and 60, 88 and 61, 96 and 65; 1M of 13 bytes 60 and 61, 67 and 62, 74 and 66; 4M of 13 bytes 106 and 140, 143 and 143, 157 and 151;
+// 10M of 13 bytes 169 and 296, 212 and 297, 234 and 314; of 28 212 and 330, 246 and 332, 270 and 347.
+constexpr int kWalkNodes = 3072;
+constexpr int64_t kWalkManyRows = 6 << 20;
+bool walk_from_lds(int bits, int F, int max_nodes, int64_t n) {
+    if (max_nodes <= kWalkNodes) return true;
+    const int64_t row_bits = (int64_t)F * bits;
+    const bool few_reads = row_bits <= 128 ? bits == 8 && F <= 16 : row_bits <= kGatheredRowBits || row_bits > kStagedRowBits;
+    return n >= kWalkManyRows && few_reads && (size_t)max_nodes * 20 <= kWalkLds;
+}
 template <typename K, typename... A>
 hipError_t launch_walk(K kernel, int64_t grid, size_t lds, hipStream_t s, A... args) {
     GbtLdsGuard lds_guard(lds);
@@ -1165,10 +1178,8 @@ hipError_t launch_walk(K kernel, int64_t grid, size_t lds, hipStream_t s, A... a
 }  // namespace
 
 // Can the walk also count the rows per node, and read the margins from another array?  The forms that keep the tree in LDS do.
-bool gbt_predict_counts_ok(bool packed, int bits, int F, int max_nodes, bool compact_ok) {
-    (void)bits;
-    (void)F;
-    return packed && compact_ok && (size_t)max_nodes * 20 <= kWalkLds;
+bool gbt_predict_counts_ok(bool packed, int bits, int F, int64_t n, int max_nodes, bool compact_ok) {
+    return packed && compact_ok && walk_from_lds(bits, F, max_nodes, n);
 }
 
 hipError_t gbt_launch_predict(hipStream_t s, const char *ws, const DevTree *trees, int n_trees,
@@ -1177,11 +1188,11 @@ hipError_t gbt_launch_predict(hipStream_t s, const char *ws, const DevTree *tree
                               bool compact_ok, uint32_t *node_rows, const float *margin_src) {
     if (n <= 0) return hipSuccess;
     if (margin_src == margin) margin_src = nullptr;
-    if ((node_rows || margin_src) && !(n_trees == 1 && gbt_predict_counts_ok(packed != nullptr, bits, F, max_nodes, compact_ok)))
+    if ((node_rows || margin_src) && !(n_trees == 1 && gbt_predict_counts_ok(packed != nullptr, bits, F, n, max_nodes, compact_ok)))
         return hipErrorInvalidValue;   // (the caller asks gbt_predict_counts_ok first)
     size_t lds = 0;
     const int form = walk_form(bits, F, max_nodes, node_rows != nullptr, &lds);
-    if (packed && compact_ok && lds <= kWalkLds) {
+    if (packed && compact_ok && walk_from_lds(bits, F, max_nodes, n) && lds <= kWalkLds) {
         // A workgroup stages the tree and walks a block of rows.  Where blocks of 4096 rows would leave compute units
         // without a workgroup they are shorter, down to one row per thread (1M x 28 bytes: 37 us with 245 workgroups, 23 us
         // with 977 and four rows per thread side by side; 50,000 x 22 bytes 36 -> 7 us).

@@ -923,7 +923,9 @@ hipError_t gbt_launch_sparse_walk(hipStream_t s, const char *ws, const DevTree *
     if (n <= 0 || n_trees <= 0) return hipSuccess;
     WalkWhen when{0, 0, -1};
     bool staged = true;
-    if (ent_bytes == 2 && compact_ok && (size_t)max_nodes * 16 <= 96u * 1024u) {
+    // (past 80 KB of nodes a compute unit holds one workgroup: 4M rows of 16 entries, us with the tree in LDS and in the caches, 4801
+    // nodes 208 and 253, 6001 nodes 361 and 257)
+    if (ent_bytes == 2 && compact_ok && (size_t)max_nodes * 16 <= 80u * 1024u) {
         const WalkWhen range = staged_walk_range(n, depth);
         const bool may = (uint64_t)n * (uint64_t)F > range.from && range.to > 0;   // (a row has at most F entries)
         if (nnz >= 0)

@@ -225,3 +225,57 @@ def test_splits_that_share_children(ctx, oracle, name, F, bits):
     assert np.array_equal(got, ref)
     rowptr, ent, _ = ctx.compress_sparse(dev(sym), 32, missing)
     assert np.array_equal(ctx.predict_sparse([t], dev(start), 0.3, rowptr, ent, n, F, 32).cpu().numpy(), ref)
+
+
+MANY = 6 << 20   # rows from which on trees past 3072 nodes are walked from LDS where the rows' own reads are few
+
+
+@pytest.mark.parametrize("splits", [1535, 1536, 2457, 2458, 2559, 2560])   # 3071, 3073, 4915, 4917, 5119, 5121 nodes
+@pytest.mark.parametrize("n,F,bits", [(2_001, 13, 8), (2_001, 14, 9), (2_001, 28, 8), (2_001, 57, 8), (MANY - 1, 5, 8), (MANY, 5, 8)])
+def test_trees_around_the_sizes_kept_in_lds(ctx, oracle, n, F, bits, splits):
+    """One tree at the sizes and row counts where a walk keeps its nodes in LDS or leaves them in the caches."""
+    rng = np.random.default_rng(splits + F)
+    t = _made_tree(rng, F, splits, "dense")
+    t["bin"][:] = rng.integers(60, 190, len(t["bin"]))
+    missing = (1 << bits) - 1
+    sym = rng.integers(0, missing + 1, (n, F), dtype=np.uint16)
+    start = rng.standard_normal(n).astype(np.float32)
+    print(f"tree sizes n={n} F={F} bits={bits} nodes={t['n_nodes']}", flush=True)
+    ref = oracle.predict_sym(t, sym, missing, 0.3, start)
+    packed = dev(oracle.pack(sym, bits).view(np.int32))
+    got = ctx.predict([t], dev(start), 0.3, packed=packed, bits=bits, missing_sym=missing, n=n, F=F).cpu().numpy()
+    assert np.array_equal(got, ref)
+    if n < MANY - 1:
+        rowptr, ent, _ = ctx.compress_sparse(dev(sym), missing, missing)
+        assert np.array_equal(ctx.predict_sparse([t], dev(start), 0.3, rowptr, ent, n, F, missing).cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("n", [MANY - 1, MANY])
+def test_rows_counted_by_the_walk_of_a_large_tree(ctx, n):
+    """A boosting round of depth 11 (4095 nodes at most): its last level's rows are counted in the margin's walk, from 6M rows of
+    bytes on, else by a pass of their own; the growth on its own counts them with the partition."""
+    import paper_1806_11248_amd as g
+    F, B = 6, 255
+    gen = torch.Generator("cuda").manual_seed(2)
+    sym = torch.randint(0, B, (n, F), device="cuda", generator=gen, dtype=torch.int16)
+    y = torch.randn(n, device="cuda", generator=gen) * 0.01
+    for f in range(F):
+        y += (1 + 0.3 * f) * sym[:, f].float() / B   # (smooth: nodes split near the middle, down to the last level)
+    packed, bits = ctx.compress(sym.view(torch.uint16), B)
+    assert bits == 8
+    nb = torch.full((F,), B, dtype=torch.int32, device="cuda")
+    cuts = torch.arange(1, B, device="cuda", dtype=torch.float32).repeat(F, 1)
+    params = g.make_params(max_depth=11, max_bins=B, eta=0.3, objective="squared")
+    print(f"rows counted by the walk n={n}", flush=True)
+    m, out, gp = torch.zeros(n, device="cuda"), torch.empty(n, device="cuda"), torch.empty((n, 2), device="cuda")
+    t = ctx.boost_round(packed, bits, n, F, B, nb, cuts, y, m, out, gp, params)
+    bare, _, leaf = ctx.grow_tree(packed, bits, n, F, B, nb, cuts, gp, params, want_rows=False)
+    nn = t["n_nodes"]
+    assert nn > 3072 and bare["n_nodes"] == nn
+    for k in ("feature", "bin", "left", "n_rows", "weight"):
+        assert np.array_equal(t[k][:nn], bare[k][:nn]), k
+    count = torch.bincount(leaf, minlength=nn).cpu().numpy()
+    leaves = t["feature"][:nn] < 0
+    assert np.array_equal(t["n_rows"][:nn][leaves], count[leaves])
+    w = torch.from_numpy(0.3 * t["weight"][:nn]).cuda()
+    assert torch.equal(out, (m.double() + w[leaf.long()]).float())
