@@ -22,46 +22,43 @@ struct TreeShape {
 inline TreeShape tree_shape(const gbt_tree &T, int32_t F, std::vector<int> &scratch) {
     TreeShape s;
     scratch.assign((size_t)T.n_nodes, 0);
-    int *depth_of = scratch.data();   // (a child's is at least 1)
+    int *__restrict__ depth_of = scratch.data();   // (a child's is at least 1)
+    const int32_t *__restrict__ feature = T.feature, *__restrict__ bin = T.bin, *__restrict__ left = T.left, *__restrict__ right = T.right;
     const int n = T.n_nodes;
-    int splits = 0, last = 0;
-    bool ascending = true;   // pairs of children in ascending order share none
+    int splits = 0, depth = 0;
+    bool compact = true, in_order = true;
     for (int i = 0; i < n; ++i) {
-        const int32_t f = T.feature[i];
+        const int32_t f = feature[i];
         if (f < 0) continue;
-        const int32_t l = T.left[i], r = T.right[i];
-        if (r != l + 1 || f >= (1 << 20) || T.bin[i] < 0 || T.bin[i] >= 4096) s.compact = false;
+        const int32_t l = left[i], r = right[i];
         if (f >= F || l < 0 || l >= n || r < 0 || r >= n) {
             s.bad_node = i;
             return s;
         }
-        s.in_order = s.in_order && l > i && r > i;
-        ascending = ascending && l > last && r > l;
-        last = r;
+        compact &= r == l + 1 && f < (1 << 20) && (uint32_t)bin[i] < 4096u;
+        in_order &= l > i && r > i;
         ++splits;
-        if (s.in_order) {
-            const int d = depth_of[i] + 1;
-            depth_of[l] = depth_of[r] = d;
-            if (d > s.depth) s.depth = d;
-        }
+        const int d = depth_of[i] + 1;
+        depth_of[l] = depth_of[r] = d;
+        depth = std::max(depth, d);
     }
-    if (!s.in_order) {
-        s.compact = s.proper = false;
-    } else if (!ascending) {
-        int children = 0;
-        for (int i = 0; i < n; ++i) children += depth_of[i] != 0;
-        s.proper = children == 2 * splits;
-        if (!s.proper) {
-            scratch.assign((size_t)n, 0);
-            s.depth = 0;
-            for (int i = 0; i < n; ++i) {
-                if (T.feature[i] < 0) continue;
-                const int32_t l = T.left[i], r = T.right[i], d = depth_of[i] + 1;
-                depth_of[l] = std::max(depth_of[l], d);
-                depth_of[r] = std::max(depth_of[r], d);
-                s.depth = std::max(s.depth, d);
-            }
-        }
+    s.in_order = in_order;
+    s.compact = compact && in_order;
+    s.proper = in_order;
+    if (!in_order) return s;
+    s.depth = depth;
+    int children = 0;   // (two to a split where none is shared)
+    for (int i = 0; i < n; ++i) children += depth_of[i] != 0;
+    if (children == 2 * splits) return s;
+    s.proper = false;
+    s.depth = 0;
+    scratch.assign((size_t)n, 0);
+    for (int i = 0; i < n; ++i) {
+        if (feature[i] < 0) continue;
+        const int32_t l = left[i], r = right[i], d = depth_of[i] + 1;
+        depth_of[l] = std::max(depth_of[l], d);
+        depth_of[r] = std::max(depth_of[r], d);
+        s.depth = std::max(s.depth, d);
     }
     return s;
 }
