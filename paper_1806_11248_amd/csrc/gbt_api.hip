@@ -122,7 +122,10 @@ PlanHistRule hist_rule(const gbt_ctx *ctx, const HistPlan &pl, int F, int B, int
     r.pieces_max = std::max<int64_t>(1, (int64_t)ctx->num_cu * ctx->hist_jobs_per_cu / std::max(1, pl.n_ftiles));
     r.min_rows = kMinRowsPerJob;
     r.max_rows = max_rows;
-    r.merge = 0.15 * B * ctx->hist_merge_ratio / 96.0;   // (0.1, 0.2 and 0.3: within 3 %, 0.4: 10 % slower on the widest)
+    // (0.1, 0.2 and 0.3: within 3 %, 0.4: 10 % slower on the widest.)  In a tile of few columns a row costs its words and its pair more
+    // than its elements, and more bins than rows are not all met: us per call with the weight whole and so, 100,000 x 40 x 4096 bins 97
+    // and 65, a quarter of its rows 64 and 40, 1M x 20 x 4096 183 and 172; rounds of depth 7 over them 1175 and 1090, 2038 and 1730.
+    r.merge = 0.15 * B * ctx->hist_merge_ratio / 96.0 * std::min(1.0, pl.ft / 8.0);
     r.num_cu = ctx->num_cu;
     r.tiles = (F + pl.ft - 1) / pl.ft;
     r.ft = pl.ft;
