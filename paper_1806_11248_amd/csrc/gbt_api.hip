@@ -1102,8 +1102,8 @@ int32_t read_planned_tree(gbt_ctx *ctx, const PlannedGrowth &g, int n_levels, gb
     int64_t n_nodes = 1;
     for (int d = 0; d <= n_levels; ++d) {
         n_nodes = std::max<int64_t>(n_nodes, (int64_t)lv[d].first_node + lv[d].n_nodes);
-        GBT_REQUIRE(ctx, !(lv[d].bad & PLAN_BAD_ROWS), GBT_EHIP, "internal: a node of depth %d has fewer rows than went left", d - 1);
-        GBT_REQUIRE(ctx, !(lv[d].bad & PLAN_BAD_JOBS), GBT_EHIP, "internal: depth %d has more histogram jobs than its launch", d);
+        GBT_REQUIRE(ctx, !(lv[d].bad == PLAN_BAD_ROWS), GBT_EHIP, "internal: a node of depth %d has fewer rows than went left", d - 1);
+        GBT_REQUIRE(ctx, !(lv[d].bad == PLAN_BAD_JOBS), GBT_EHIP, "internal: depth %d has more histogram jobs than its launch", d);
     }
     GBT_REQUIRE(ctx, n_nodes <= g.cap_nodes && n_nodes <= tree->capacity, GBT_EHIP, "internal: %lld nodes", (long long)n_nodes);
     for (int64_t i = 0; i < n_nodes; ++i) {

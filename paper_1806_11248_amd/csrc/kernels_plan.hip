@@ -212,7 +212,7 @@ __device__ uint32_t pick_piece(const PlanHistRule &rule, int64_t rows, uint32_t 
 }
 
 __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, int d, const uint32_t *__restrict__ n_left,
-                                                                    int stride, int with_hist, PlanHistRule rule, uint32_t jobs_max) {
+                                                                    int stride, int with_hist, PlanHistRule rule, uint32_t pieces_max) {
     __shared__ int64_t tmp[kChildBlock / 64];
     __shared__ uint32_t s_small[kPieceNodes];
     __shared__ double s_cost[kPieceCandidates];
@@ -243,9 +243,9 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
         (void)block_scan<kChildBlock>(mine, tmp, &pieces);
     }
     // (the host's bound holds for every rule and number of rows; were it short, nothing is written past the table)
-    const bool fits = pieces * rule.tiles <= (int64_t)jobs_max;
+    const bool fits = (uint32_t)pieces <= pieces_max;
     int64_t carry = 0;
-    uint32_t bad = fits ? 0u : (uint32_t)PLAN_BAD_JOBS;
+    uint32_t bad = 0;
     for (uint32_t k0 = 0; k0 < ns; k0 += kChildBlock) {
         const uint32_t k = k0 + threadIdx.x;
         uint32_t mine = 0;   // pieces of this thread's node
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
             const PlanJob info = v.pinfo[k];
             const PlanNode nd = v.nodes[info.node];
             const uint32_t l = left_rows(k, j.seg_len), r = j.seg_len - l;
-            if (n_left && n_left[(size_t)k * stride] > j.seg_len) bad |= (uint32_t)PLAN_BAD_ROWS;
+            if (n_left && n_left[(size_t)k * stride] > j.seg_len) bad = 1;
             const uint32_t lid = first_child + 2u * k, rid = lid + 1u;
             const bool left_small = l <= r;
             const uint32_t small = left_small ? l : r;
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
         const int64_t incl = block_scan<kChildBlock>((int64_t)mine, tmp, &all);
         s_off[threadIdx.x] = (uint32_t)(carry + incl) - mine;
         __syncthreads();
-        const uint32_t here = ns - k0 < (uint32_t)kChildBlock ? ns - k0 : (uint32_t)kChildBlock;
+        const uint32_t here = !fits ? 0u : ns - k0 < (uint32_t)kChildBlock ? ns - k0 : (uint32_t)kChildBlock;
         for (uint32_t q = 0; q < here; ++q) {
             const uint32_t len = s_len[q];
             const bool exclusive = rule.exclusive_ok && len <= rpj && len > 0;
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
                      i += (int64_t)gridDim.x * kChildBlock)
                     z[i] = make_ulonglong2(0ull, 0ull);
             }
-            if (!fits || (k0 + q) % gridDim.x != blockIdx.x) continue;
+            if ((k0 + q) % gridDim.x != blockIdx.x) continue;
             for (uint32_t t = threadIdx.x; t < s_pieces[q] * (uint32_t)rule.tiles; t += kChildBlock) {
                 const uint32_t piece = t / (uint32_t)rule.tiles, tile = t - piece * (uint32_t)rule.tiles;
                 HistJob h;
@@ -324,12 +324,13 @@ __global__ __launch_bounds__(kChildBlock) void plan_children_kernel(PlanView v, 
         carry += all;
         __syncthreads();   // (the tables are rewritten)
     }
-    if (lead && bad) atomicOr(&v.levels[d + 1].bad, bad);
+    if (lead && bad) v.levels[d + 1].bad = PLAN_BAD_ROWS;
     if (lead && threadIdx.x == 0) {
         PlanLevel &nx = v.levels[d + 1];
         nx.first_node = first_child;
         nx.n_nodes = 2u * ns;
         nx.n_hist_jobs = fits ? (uint32_t)(pieces * rule.tiles) : 0u;
+        if (!fits) nx.bad = PLAN_BAD_JOBS;
         nx.built_rows = (uint64_t)built;
     }
 }
@@ -391,7 +392,7 @@ hipError_t gbt_launch_plan_children(hipStream_t s, const PlanView &v, int depth,
     // workgroups: enough to clear what the level may have to clear at a few kilobytes each
     const int64_t clear = with_hist ? max_splits * v.hist_len : 0;
     const int64_t grid = std::min<int64_t>(256, std::max<int64_t>(1, (clear + 2047) / 2048));
-    plan_children_kernel<<<(unsigned)grid, kChildBlock, 0, s>>>(v, depth, n_left, stride, with_hist ? 1 : 0, rule, jobs_max);
+    plan_children_kernel<<<(unsigned)grid, kChildBlock, 0, s>>>(v, depth, n_left, stride, with_hist ? 1 : 0, rule, jobs_max / (uint32_t)rule.tiles);
     return hipGetLastError();
 }
 hipError_t gbt_launch_plan_rank(hipStream_t s, const PlanView &v, int n_levels, uint32_t *count, uint32_t *rank) {
