@@ -1228,7 +1228,12 @@ hipError_t gbt_launch_predict(hipStream_t s, const char *ws, const DevTree *tree
     }
     const size_t lds_full = (size_t)max_nodes * sizeof(LdsNode);
     if (lds_full <= kWalkLds) {
-        const int rows_per_block = n <= (int64_t)256 * 1024 ? 256 : n < (int64_t)4096 * 1024 ? 1024 : 4096;   // (as above)
+        // Blocks as above, but raw floats past 128 MB are read in blocks of 4096 rows from 768k rows on (1536k of 96 and more columns): the more rows a compute unit
+        // walks at once, the more often a row's line is fetched again.  us per call with 1024 and 4096, depth 6: 1M x 28 53 and 57, 2M x
+        // 28 155 and 78, 3.9M x 28 251 and 151, 500,000 x 64 49 and 65, 1M x 64 102 and 72, 1M x 100 112 and 110, 2M x 100 222 and 181,
+        // 500,000 x 200 65 and 96, 2M x 200 235 and 214, two trees of depth 3 over 1M x 216 133 and 152, 3.9M x 4 54 and 65.
+        const bool wide = X && n > (int64_t)(F < 96 ? 768 : 1536) * 1024 && n * (int64_t)F * 4 > (int64_t)128 << 20;
+        const int rows_per_block = n <= (int64_t)256 * 1024 ? 256 : n < (int64_t)4096 * 1024 && !wide ? 1024 : 4096;
         return launch_walk(predict_lds_kernel, (n + rows_per_block - 1) / rows_per_block, lds_full, s, ws, trees, n_trees,
                            packed, bits, missing, X, n, F, eta, margin, rows_per_block, leaf_out);
     }
