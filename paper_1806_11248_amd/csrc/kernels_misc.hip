@@ -939,6 +939,24 @@ __global__ __launch_bounds__(R) void predict_raw_batched_kernel(
     bool nan = false;
     const int64_t r0 = (int64_t)blockIdx.x * R;
     const int rows = n - r0 < R ? (int)(n - r0) : R;
+    // A group's nodes are asked for while the trees of the group before are walked, the first group's while the tile is fetched
+    // (kAhead per thread; of a larger group the rest is fetched when it is needed).
+    constexpr int kAhead = 1536 / R;
+    gbt_batch_node ahead[kAhead];
+    auto fetch = [&](int n0, int n1, int first, gbt_batch_node (&a)[kAhead]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const int i = first + (int)threadIdx.x + k * R;
+            a[k] = nodes_g[n0 + (i < n1 - n0 ? i : n1 - n0 - 1)];
+        }
+    };
+    // (a group's first tree stands at its second place)
+    int t_begin = 0, n0 = tree_off[0] - 1, n1 = tree_off[group_end[0]] - 1;
+    fetch(n0, n1, 0, ahead);
+    // (the vote on missing values goes through the nodes' place: a word of static LDS would cost a compute unit its fourth workgroup)
+    int *vote = (int *)smem;
+    if (threadIdx.x == 0) *vote = 0;
+    __syncthreads();
     {   // the tile is one contiguous piece of X, taken in chunks of four features of a row: chunk tid + R k by thread
         // tid in step k, four chunks in flight per thread; (row, chunk) advance without divisions
         const int C = (F + 3) >> 2, total = rows * C;
@@ -976,9 +994,8 @@ __global__ __launch_bounds__(R) void predict_raw_batched_kernel(
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
                     if (j < nf[k]) {
-                        const int key = float_key(v[k][j]);
-                        nan |= key == 0x7fffffff;
-                        xs[at[k] + j * R] = key;
+                        nan |= v[k][j] != v[k][j];
+                        xs[at[k] + j * R] = float_key(v[k][j]);
                     }
         }
     }
@@ -989,11 +1006,6 @@ __global__ __launch_bounds__(R) void predict_raw_batched_kernel(
     // LDS addresses as numbers: nothing is added to an offset before it is read
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_i32 *)smem;
     const uint32_t xrow = lds0 + (uint32_t)cap_nodes * 8u + 4u * (live ? threadIdx.x : 0u);
-    // (the vote goes through the nodes' place: a word of static LDS would cost a compute unit its fourth workgroup)
-    int *vote = (int *)smem;
-    __syncthreads();
-    if (threadIdx.x == 0) *vote = 0;
-    __syncthreads();
     if (nan) *vote = 1;
     __syncthreads();
     const bool any_nan = *vote != 0;
@@ -1005,17 +1017,6 @@ __global__ __launch_bounds__(R) void predict_raw_batched_kernel(
         for (int k = 0; k < kBatchTrees; ++k)
             if (k < n_w) m = (float)((double)m + w[k]);
     };
-    // A group's nodes are asked for while the trees of the group before are walked (kAhead per thread; of a larger group the
-    // rest is fetched when it is needed).
-    constexpr int kAhead = 1536 / R;
-    gbt_batch_node ahead[kAhead];
-    auto fetch = [&](int n0, int n1, int first, gbt_batch_node (&a)[kAhead]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int k = 0; k < kAhead; ++k) {
-            const int i = first + (int)threadIdx.x + k * R;
-            a[k] = nodes_g[n0 + (i < n1 - n0 ? i : n1 - n0 - 1)];
-        }
-    };
     auto place = [&](int count, int first, const gbt_batch_node (&a)[kAhead]) __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) {
@@ -1026,9 +1027,6 @@ __global__ __launch_bounds__(R) void predict_raw_batched_kernel(
             if (i < count) nd[i] = q;
         }
     };
-    // (a group's first tree stands at its second place)
-    int t_begin = 0, n0 = tree_off[0] - 1, n1 = tree_off[group_end[0]] - 1;
-    fetch(n0, n1, 0, ahead);
     for (int g = 0; g < n_groups; ++g) {
         const int t_end = group_end[g];
         __syncthreads();   // the row tile is complete; the previous group's walks are done
