@@ -1163,6 +1163,30 @@ bool walk_from_lds(int bits, int F, int max_nodes, int64_t n) {
     const bool few_reads = row_bits <= 128 ? bits == 8 && F <= 16 : row_bits <= kGatheredRowBits || row_bits > kStagedRowBits;
     return n >= kWalkManyRows && few_reads && (size_t)max_nodes * 20 <= kWalkLds;
 }
+// Rows that a thread gathers for side by side, and rows of a block.  The more rows a compute unit walks at once, the more often a
+// row's lines leave the caches between two levels: rows past 32 bytes are walked one by one, wide ones in longer blocks from 768k
+// rows on; past 3M rows nothing is kept between levels, and short blocks that follow each other closely share DRAM pages.  us per
+// call, depth 8, (4 rows, blocks of 1024), (1, 1024), (1, 4096) and (2, 256): 1M x 40 bytes 51, 46, 64, 52; 500,000 x 132 92, 52,
+// 67, 63; 1M x 132 147, 77, 70, 83; 1M x 300 166, 129, 115, 128; 2M x 132 262, 228, 104, 124; 2M x 300 301, 281, 191, 217; 5M x 132
+// 611, 479, 353, 261; 5M x 200 682, 591, 528, 395 (of depth 10, 2047 nodes, 785, 560, 694, 648); 5M x 40 121, 107, 95, 114 and 95
+// with (2, 4096); 1M x 28 44, 44, 63, 53.
+// Past 1024 nodes short blocks would mostly stage nodes: there LDS for two workgroups of a compute unit bounds the rows at once
+// (6M x 180, 2047 nodes: 445 so, 603 with (1, 1024), 991 with (4, 4096)).
+void gathered_rows(int64_t row_bits, int64_t n, int max_nodes, int *side_by_side, int *rows_per_block, size_t *lds) {
+    if (row_bits <= 256) return;
+    *side_by_side = 1;
+    if (row_bits <= kStagedRowBits) {
+        if (*rows_per_block == 4096) *side_by_side = 2;
+    } else if (n <= (int64_t)3 << 20) {
+        *rows_per_block = n <= (int64_t)768 * 1024 ? 1024 : 4096;
+    } else if (max_nodes <= 1024) {
+        *side_by_side = 2;
+        *rows_per_block = 256;
+    } else {
+        *rows_per_block = 4096;
+        *lds = std::max(*lds, (size_t)64 * 1024);
+    }
+}
 template <typename K, typename... A>
 hipError_t launch_walk(K kernel, int64_t grid, size_t lds, hipStream_t s, A... args) {
     GbtLdsGuard lds_guard(lds);
@@ -1195,7 +1219,9 @@ hipError_t gbt_launch_predict(hipStream_t s, const char *ws, const DevTree *tree
         // without a workgroup they are shorter, down to one row per thread (1M x 28 bytes: 37 us with 245 workgroups, 23 us
         // with 977 and four rows per thread side by side; 50,000 x 22 bytes 36 -> 7 us).
         const bool few = n <= (int64_t)256 * 1024;
-        const int rows_per_block = few ? 256 : n < (int64_t)4096 * 1024 ? 1024 : 4096;
+        int rows_per_block = few ? 256 : n < (int64_t)4096 * 1024 ? 1024 : 4096;
+        int side_by_side = few ? 1 : kPredRows;   // rows of a thread
+        if (form == WALK_GATHER && !few) gathered_rows((int64_t)F * bits, n, max_nodes, &side_by_side, &rows_per_block, &lds);
         int64_t grid = (n + rows_per_block - 1) / rows_per_block;
         // counting: few enough workgroups that their counts meet rarely in HBM, each taking many blocks
         if (node_rows && grid > 2048) grid = 2048;
@@ -1218,7 +1244,7 @@ hipError_t gbt_launch_predict(hipStream_t s, const char *ws, const DevTree *tree
                 return launch_walk(predict_staged_kernel, grid, lds, s, ws, trees, n_trees, packed, n_words, bits, missing, n, F,
                                    eta, margin, rows_per_block, max_nodes, leaf_out, staged_wave_words(bits, F), node_rows, src);
             default: {
-                auto k = few ? predict_gather_kernel<1> : predict_gather_kernel<kPredRows>;
+                auto k = side_by_side == 1 ? predict_gather_kernel<1> : side_by_side == 2 ? predict_gather_kernel<2> : predict_gather_kernel<kPredRows>;
                 return launch_walk(k, grid, lds, s, ws, trees, n_trees, packed, bits, missing, n, F, eta, margin,
                                    rows_per_block, max_nodes, leaf_out, node_rows, src);
             }

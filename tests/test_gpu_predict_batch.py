@@ -279,3 +279,35 @@ def test_rows_counted_by_the_walk_of_a_large_tree(ctx, n):
     assert np.array_equal(t["n_rows"][:nn][leaves], count[leaves])
     w = torch.from_numpy(0.3 * t["weight"][:nn]).cuda()
     assert torch.equal(out, (m.double() + w[leaf.long()]).float())
+
+
+# rows, bytes a row, splits: both sides of the rows, widths and tree sizes at which gathering walks change their blocks
+GATHERED = [(262_144, 130, 200), (262_145, 130, 200), (768 << 10, 129, 300), ((768 << 10) + 1, 129, 300), (3 << 20, 129, 400),
+            ((3 << 20) + 1, 129, 511), ((3 << 20) + 1, 129, 512), ((3 << 20) + 1, 129, 1023), (400_000, 32, 200), (400_000, 33, 200),
+            (4 << 20, 33, 200), ((4 << 20) - 1, 40, 200), (400_000, 41, 200)]
+
+
+@pytest.mark.parametrize("n,F,splits", GATHERED)
+def test_gathered_rows_of_every_block_form(ctx, n, F, splits):
+    """Byte rows and one tree: margins against the same walk in torch."""
+    rng = np.random.default_rng(n % 1000 + F)
+    t = _made_tree(rng, F, splits, "dense")
+    t["bin"][:] = rng.integers(60, 190, len(t["bin"]))
+    print(f"gathered rows n={n} F={F} nodes={t['n_nodes']}", flush=True)
+    gen = torch.Generator("cuda").manual_seed(F)
+    flat = torch.randint(0, 256, (n * F + 64,), dtype=torch.uint8, device="cuda", generator=gen)
+    packed = flat[:(flat.numel() // 4) * 4].view(torch.int32)
+    sym = flat[:n * F].view(n, F)
+    at = {k: torch.from_numpy(t[k].astype(np.int64)).cuda() for k in ("feature", "bin", "default_left", "left", "right")}
+    node = torch.zeros(n, dtype=torch.int64, device="cuda")
+    while True:
+        f = at["feature"][node]
+        if not bool((f >= 0).any()):
+            break
+        s = sym.gather(1, f.clamp(min=0)[:, None])[:, 0].long()
+        left = torch.where(s == 255, at["default_left"][node] != 0, s <= at["bin"][node])
+        node = torch.where(f < 0, node, torch.where(left, at["left"][node], at["right"][node]))
+    start = torch.randn(n, device="cuda", generator=gen)
+    weight = torch.from_numpy(t["weight"]).cuda()
+    got = ctx.predict([t], start.clone(), 0.3, packed=packed, bits=8, missing_sym=255, n=n, F=F)
+    assert torch.equal(got, (start.double() + 0.3 * weight[node]).float())
