@@ -282,7 +282,7 @@ def test_rows_counted_by_the_walk_of_a_large_tree(ctx, n):
 
 
 # rows, bytes a row, splits: both sides of the rows, widths and tree sizes at which gathering walks change their blocks
-GATHERED = [(262_144, 130, 200), (262_145, 130, 200), (768 << 10, 129, 300), ((768 << 10) + 1, 129, 300), (3 << 20, 129, 400),
+GATHERED = [(262_144, 130, 200), (262_145, 130, 200), (704 << 10, 129, 300), ((704 << 10) + 1, 129, 300), (3 << 20, 129, 400),
             ((3 << 20) + 1, 129, 511), ((3 << 20) + 1, 129, 512), ((3 << 20) + 1, 129, 1023), (400_000, 32, 200), (400_000, 33, 200),
             (4 << 20, 33, 200), ((4 << 20) - 1, 40, 200), (400_000, 41, 200)]
 
