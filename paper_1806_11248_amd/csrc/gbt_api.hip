@@ -72,9 +72,9 @@ struct HistPlan {
 // every slot of a window, used or not.  More tiles than the LDS budget demands cost a pass over the
 // gradient pairs each, so they are taken only when they save at least a fifth of the slots.
 bool plan_tiles(const gbt_ctx *ctx, int F, int B, int bits, HistPlan *p, int64_t n_rows = 0) {
-    p->ft_max = gbt_hist_feature_tile(ctx, F, B, n_rows);
+    const int E = gbt_histw_window(std::max(bits, 1));   // (16 of 8 bits)
+    p->ft_max = std::min(gbt_hist_feature_tile(ctx, F, B, n_rows), GBT_HISTW_WINDOWS * E);
     if (p->ft_max < 1) return false;
-    const int E = bits == 8 ? 16 : std::min(128 / std::max(bits, 1), 32);
     const int nt_min = (F + p->ft_max - 1) / p->ft_max;
     int64_t best_slots = -1;
     for (int nt = nt_min; nt <= nt_min + 8 && nt <= F; ++nt) {

@@ -332,6 +332,13 @@ hipError_t gbt_launch_hist(gbt_ctx *ctx, const uint32_t *packed, int bits, int64
                            // gbt_histw_max_rows(true) rows
                            bool uniform_h = false, int32_t hq_uniform = 0, int block = 0,   // threads (0: ctx->hist_block)
                            const uint32_t *n_jobs_dev = nullptr);   // see DEVICE COUNTS
+// Most whole symbols of `bits` bits in 16 bytes that start at the first one's byte: a register window of kernels_histw.hip.
+#define GBT_HISTW_WINDOWS 4   // of a row that a tile may have
+constexpr int gbt_histw_window(int bits) {
+    const int first = bits % 8 == 0 ? 0 : bits % 4 == 0 ? 4 : bits % 2 == 0 ? 6 : 7;   // the first one's bit, at most
+    const int e = (128 - first) / bits;
+    return e < 32 ? e : 32;
+}
 int gbt_histw_max_rows(bool uniform_h);
 hipError_t gbt_launch_histw(gbt_ctx *ctx, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n_words,
                             int64_t n, int B, uint32_t missing, const uint32_t *row_idx, const int32_t *gq,

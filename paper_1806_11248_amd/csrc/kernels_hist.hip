@@ -1309,7 +1309,7 @@ hipError_t gbt_launch_hist(gbt_ctx *ctx, const uint32_t *packed, int bits, int64
                            int32_t hq_uniform, int block, const uint32_t *n_jobs_dev) {
     if (n_jobs <= 0) return hipSuccess;
     if (block == 0) block = ctx->hist_block;
-    if (!ctx->hist_runtime_bits && (bits != 8 || uniform_h))
+    if (!ctx->hist_runtime_bits && (bits != 8 || uniform_h) && n_words >= 4)   // (it reads 16 bytes at a time)
         return gbt_launch_histw(ctx, packed, bits, stride_bits, n_words, n, B, missing, row_idx, gq, hist_pool, jobs,
                                 n_jobs, max_ft, uniform_h, hq_uniform, block, n_jobs_dev);
     const int Bp = padded_bins(B);

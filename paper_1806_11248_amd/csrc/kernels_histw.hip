@@ -1,14 +1,22 @@
-// BuildPartialHistograms (Alg. 1) for symbol widths other than 8 bits (compile-time width), any feature tile,
-// rows given as a range or as a list of row ids.
+// BuildPartialHistograms (Alg. 1) for symbol widths other than 8 bits (compile-time width; 8 bits in the uniform form), any
+// feature tile, rows given as a range or as a list of row ids.
 //
-// lane = one row.  A row's slice of the bit stream is consumed in register windows of E = min(128 / BITS, 32)
-// whole elements: five words are loaded, funnel-shifted (v_alignbit) so that the window starts at bit 0, and
-// every element is then cut out at a compile-time position.  The lanes of a wave start at different windows of
-// a multi-window row, so that they work on different features.  What keeps the launch off the memory latency:
-// the words of the NEXT window (of this row, or the first of the lane's next row) are requested before the
-// current window is processed, the next row's gradient pair one row ahead, a listed row's id two rows ahead.
-// A slot without a live feature, a missing symbol or a symbol >= B goes to a spare LDS word of the lane's own
-// (conflict-free) instead of being predicated.
+// A row's slice of the bit stream, of up to four register windows of E = gbt_histw_window(BITS) whole symbols, is taken by
+// as many neighbouring lanes, a window each: sixteen bytes from the byte of the first symbol on, in any alignment.  What
+// decides, in the order the counters showed it (500,000 x 2000 x 6 bits, uniform, us of the root launch and of the round):
+//   one row per lane, bins of a column side by side in LDS                           583    4820
+//     (16 LDS clocks an atomic, of them 8 bank conflicts and 4 on one address; 10 vector instructions an element, which the
+//     compiler makes of predicated slots and of an address it forms anew for each)
+//   columns side by side in LDS, lanes that start at different columns, so that an instruction meets the banks of many;
+//   an element is a field, a multiply-add and an atomic with its own offset           491    4400
+//     (7 LDS clocks, 5 vector instructions: the L1 is what is busy, for it takes the dwords of scattered lanes one by one)
+//   a row's windows in neighbouring lanes, whose sixteen bytes the L1 takes as one    333    3606
+// So: word (symbol, column) of the table is symbol * fs + column, fs a multiple of 16 where that leaves two workgroups on a
+// compute unit; a lane begins at column `start` of its window and goes on from the window's first column behind its last (a
+// second load, placed that far back, brings those).  Symbols that are no bin, the missing one among them, have rows of the
+// table that nothing reads: B + 1 rows, or one for each symbol where those are fewer.
+// The words of a lane's next row are requested before the present ones are added, its pair one row ahead, a listed row's id
+// two rows ahead.
 //
 // Two forms of the accumulated LDS word, as in kernels_hist8.hip:
 //   general     [ g : 34 | h : 30 ], returning atomics in groups of up to 16 whose returned words are tested
@@ -17,16 +25,20 @@
 //               8 bytes of LDS per bin instead of 12.
 #include "gbt_internal.h"
 #include "hist_common.h"
+#include "hist_merge.h"
+
+#include <type_traits>
 
 namespace {
 
 typedef unsigned long long __attribute__((address_space(3))) ldsw_u64;
 typedef uint32_t __attribute__((address_space(3))) ldsw_u32;
-__device__ __forceinline__ unsigned long long ldsw_add_rtn(uint32_t addr, unsigned long long v) {
-    return __hip_atomic_fetch_add((ldsw_u64 *)(uintptr_t)addr, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+// the 64-bit word `word` words behind the LDS byte address `addr`
+__device__ __forceinline__ unsigned long long ldsw_add_rtn(uint32_t addr, int word, unsigned long long v) {
+    return __hip_atomic_fetch_add((ldsw_u64 *)(uintptr_t)addr + word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-__device__ __forceinline__ void ldsw_add(uint32_t addr, unsigned long long v) {
-    (void)__hip_atomic_fetch_add((ldsw_u64 *)(uintptr_t)addr, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+__device__ __forceinline__ void ldsw_add(uint32_t addr, int word, unsigned long long v) {
+    (void)__hip_atomic_fetch_add((ldsw_u64 *)(uintptr_t)addr + word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 constexpr int kWRowsShift = 18;
@@ -50,23 +62,23 @@ __device__ __forceinline__ void pkw_check(uint32_t side_addr, unsigned long long
     }
 }
 
-// CHK = false: every value the BITS can hold is a bin (B > 2^BITS - 1 and no missing symbol among them), so a
-// symbol is only tested for lying in a live slot of the window.
-template <int BITS, bool LIST, bool UNI, bool CHK>
+typedef uint32_t w_u32x4 __attribute__((ext_vector_type(4), aligned(1)));
+
+// BITS: of a symbol.  CLAMP: a symbol may be larger than the last row of the LDS table and is counted there.
+template <int BITS, bool LIST, bool UNI, bool CLAMP>
 __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
-    const uint32_t *__restrict__ packed, int64_t n_words, int64_t stride_bits, int64_t n, int B, int Bp,
+    const uint32_t *__restrict__ packed, int64_t n_words, int64_t stride_bits, int64_t n, int B, int rows_lds, int fs,
     uint32_t missing, const uint32_t *__restrict__ row_idx, const int2 *__restrict__ gq,
     int64_t *__restrict__ pool, const HistJob *__restrict__ jobs, int32_t hq_uniform,
     const uint32_t *__restrict__ n_jobs_dev) {
     if (n_jobs_dev && blockIdx.x >= *n_jobs_dev) return;
-    constexpr int E = (128 / BITS) < 32 ? (128 / BITS) : 32;   // elements per window
-    constexpr int G = E < 16 ? E : 16;                         // atomics in flight per lane
+    constexpr int E = gbt_histw_window(BITS);       // most elements of a window
+    constexpr int G = E < 16 ? E : 16;      // atomics in flight per lane
     constexpr uint32_t MASK = (1u << BITS) - 1u;
     extern __shared__ unsigned long long lds[];
     const HistJob job = jobs[blockIdx.x];
     const int ft = (int)job.ft;
-    const int trash = ft * Bp;
-    const int n_acc = trash + 64;   // + one spare word per lane
+    const int n_acc = rows_lds * fs;
     unsigned long long *main_ = lds;
     uint32_t *side = (uint32_t *)(lds + n_acc);
     for (int i = threadIdx.x; i < n_acc; i += (int)blockDim.x) {
@@ -75,108 +87,141 @@ __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
     }
     __syncthreads();
 
-    const int lane = threadIdx.x & 63;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(ldsw_u64 *)main_;
     const uint32_t side_base = lds_base + 8u * (uint32_t)n_acc;
-    const uint32_t my_trash = lds_base + 8u * (uint32_t)(trash + lane);
-    const int nwin = (ft + E - 1) / E;
-    const int c0 = (lane * nwin) >> 6;   // lanes of a wave start at different windows
-    const uint32_t nrows = job.n_rows, step = blockDim.x;
-    const uint64_t f0_bits = (uint64_t)job.f0 * BITS;
+    const uint32_t fs8 = 8u * (uint32_t)fs, top = (uint32_t)rows_lds - 1u;
+    // a row's windows (one, two or four) to neighbouring lanes; each begins at another of its columns than its neighbours'
+    // and goes on from its first one behind its last
+    const int log_win = ft <= E ? 0 : ft <= 2 * E ? 1 : 2, win = (int)threadIdx.x & ((1 << log_win) - 1);
+    const int c0 = (ft * win) >> log_win, cnt = ((ft * (win + 1)) >> log_win) - c0;   // this lane's columns
+    const int most = (ft + (1 << log_win) - 1) >> log_win;                            // of any lane
+    const int start = (int)((threadIdx.x & 63) >> log_win) % cnt, until = cnt - start;   // slots before its first column
+    const int n_step = (int)(blockDim.x >> log_win);
+    const int64_t last_at = n_words * 4 - 16;   // the last byte from which sixteen can be read (the launcher has made sure of one)
+    const char *bytes = (const char *)packed;
+    uint32_t keep[4];   // the bits that come before the first column
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int k = until * BITS - 32 * j;
+        keep[j] = k >= 32 ? 0xffffffffu : k <= 0 ? 0u : (1u << k) - 1u;
+    }
 
     auto row_id = [&](uint32_t i) __attribute__((always_inline)) -> uint64_t {
         const uint64_t pos = (uint64_t)job.row_begin + i;
         return LIST ? (uint64_t)row_idx[pos] : pos;
     };
-    uint32_t wn[5], shn = 0;   // the window on its way
-    auto issue = [&](uint64_t r, int c) __attribute__((always_inline)) {
-        const uint64_t wb = r * (uint64_t)stride_bits + f0_bits + (uint64_t)(c * (E * BITS));
-        const int64_t w0 = (int64_t)(wb >> 5);
-        shn = (uint32_t)(wb & 31);
-        // words past the end of the buffer hold no bit of this row: the last word is read instead
-        const int64_t room = n_words - 1 - w0;
-        const uint32_t room32 = room >= 4 ? 4u : (uint32_t)room;
-        const uint32_t *p = packed + w0;
+    const uint64_t lane_bit = ((uint64_t)job.f0 + (uint32_t)(c0 + start)) * BITS;
+    const int back = cnt * BITS;   // from the first slot's bit to where the window's first column would follow its last
+    // Sixteen bytes from the byte of bit `at` on.  What lies outside the buffer holds no bit that is used: the sixteen bytes
+    // nearest to it are read, and put in their places when they are used.
+    auto byte_in = [&](int64_t at) __attribute__((always_inline)) {
+        const int64_t byte = at >> 3;
+        return byte < 0 ? (int64_t)0 : byte > last_at ? last_at : byte;
+    };
+    auto aligned = [&](const w_u32x4 &v, int64_t at, int off, uint32_t (&W)[4]) __attribute__((always_inline)) {
+        uint32_t x[4] = {v[0], v[1], v[2], v[3]};
+        if (__builtin_expect(off != 0, 0)) {
+            unsigned __int128 y = ((unsigned __int128)(((uint64_t)x[3] << 32) | x[2]) << 64) | (((uint64_t)x[1] << 32) | x[0]);
+            y = off > 15 || off < -15 ? 0 : off > 0 ? y >> (8 * off) : y << (-8 * off);
 #pragma unroll
-        for (int k = 0; k < 5; ++k) wn[k] = p[min((uint32_t)k, room32)];
+            for (int j = 0; j < 4; ++j) x[j] = (uint32_t)(y >> (32 * j));
+        }
+        const uint32_t sh = (uint32_t)at & 7u;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) W[j] = BITS % 8 == 0 ? x[j] : __builtin_amdgcn_alignbit(x[j + 1], x[j], sh);
+        W[3] = BITS % 8 == 0 ? x[3] : x[3] >> sh;
+    };
+    w_u32x4 wa, wb;   // the window on its way: from the lane's start on, and from its first column on (in its place)
+    int64_t at = 0;
+    int offa = 0, offb = 0;
+    auto issue = [&](uint64_t r) __attribute__((always_inline)) {
+        at = (int64_t)(r * (uint64_t)stride_bits + lane_bit);
+        const int64_t a = byte_in(at), b = byte_in(at - back);
+        wa = *(const w_u32x4 *)(bytes + a);
+        wb = *(const w_u32x4 *)(bytes + b);
+        offa = (int)((at >> 3) - a);
+        offb = (int)(((at - back) >> 3) - b);
+    };
+    // (an opaque base: one register and an instruction's own offset, not sums made anew for every slot)
+    uint32_t base = lds_base + 8u * (uint32_t)(c0 + start), base2 = base - 8u * (uint32_t)cnt;
+    asm volatile("" : "+v"(base), "+v"(base2));
+    auto add = [&](const uint32_t (&W)[4], unsigned long long addv, uint32_t hq, auto full) __attribute__((always_inline)) {
+        int n = most;
+        asm volatile("" : "+s"(n));   // (compared where it is needed: a mask per slot, kept, takes all scalar registers)
+#pragma unroll
+        for (int g0 = 0; g0 < E; g0 += G) {
+            if (!full && g0 >= n) break;
+            uint32_t addr[G];
+            unsigned long long old[G];
+#pragma unroll
+            for (int jj = 0; jj < G; ++jj) {
+                const int j = g0 + jj;
+                if (j < E && (full || j < n)) {
+                    const int pos = j * BITS, wd = pos >> 5, off = pos & 31;
+                    uint32_t sv;
+                    if (off + BITS <= 32)
+                        sv = (W[wd] >> off) & MASK;
+                    else
+                        sv = __builtin_amdgcn_alignbit(W[wd < 3 ? wd + 1 : 3], W[wd], (uint32_t)off) & MASK;
+                    if (CLAMP) sv = min(sv, top);
+                    addr[jj] = __umul24(sv, fs8) + (j >= until ? base2 : base);
+                    if (full || j + 1 < n || j < cnt) {   // (the windows differ by one column at most)
+                        if (UNI) ldsw_add(addr[jj], j, addv);
+                        else old[jj] = ldsw_add_rtn(addr[jj], j, addv);
+                    } else if (!UNI) {
+                        old[jj] = 0;
+                    }
+                }
+            }
+            if (!UNI) {
+                // the returned words of the group tested together: the smallest distance of any of them
+                // from an event decides whether the per-word bookkeeping runs at all
+                uint32_t near_carry = 0xffffffffu, near_wrap = 0xffffffffu;
+#pragma unroll
+                for (int jj = 0; jj < G; ++jj)
+                    if (g0 + jj < E && (full || g0 + jj < n)) {
+                        near_carry = min(near_carry, pk_near_carry(old[jj]));
+                        near_wrap = min(near_wrap, pk_near_wrap(old[jj], addv));
+                    }
+                if (near_carry < hq || near_wrap < pk_reach(addv)) {
+#pragma unroll
+                    for (int jj = 0; jj < G; ++jj)
+                        if (g0 + jj < E && (full || g0 + jj < n))
+                            pkw_check(side_base + ((addr[jj] + 8u * (g0 + jj) - lds_base) >> 1), old[jj], addv, hq);
+                }
+            }
+        }
     };
 
-    uint32_t i = threadIdx.x;
+    const uint32_t nrows = job.n_rows, step = (uint32_t)n_step;
+    uint32_t i = threadIdx.x >> log_win;
     if (i < nrows) {
         uint64_t r = row_id(i);
         uint64_t r1 = i + step < nrows ? row_id(i + step) : 0;
-        bool ok_row = r < (uint64_t)n;   // a malformed row id is skipped, never dereferenced
-        int2 q = ok_row ? gq[r] : make_int2(0, 0);
-        if (ok_row) issue(r, c0);
+        bool ok_row = r < (uint64_t)n;   // a malformed row id is skipped, never dereferenced (row 0 is read in its place)
+        int2 q = gq[ok_row ? r : 0];
+        issue(ok_row ? r : 0);
         for (;;) {
             const bool more = i + step < nrows;
             const uint64_t r2 = i + 2 * step < nrows ? row_id(i + 2 * step) : 0;
             const bool ok_next = more && r1 < (uint64_t)n;
-            const int2 q1 = ok_next ? gq[r1] : make_int2(0, 0);
+            const uint64_t next = ok_next ? r1 : 0;
+            const int2 q1 = gq[next];
             const unsigned long long addv =
                 UNI ? ((unsigned long long)(long long)q.x << kWRowsShift) + 1ull : pack_pair(q);
             const uint32_t hq = (uint32_t)q.y;
-            int c = c0;
-            for (int cc = 0; cc < nwin; ++cc) {
-                uint32_t w[5];
+            uint32_t W[4], V[4];
+            aligned(wa, at, offa, W);
+            aligned(wb, at - back, offb, V);
 #pragma unroll
-                for (int k = 0; k < 5; ++k) w[k] = wn[k];
-                const uint32_t sh = shn;
-                const int c_next = c + 1 == nwin ? 0 : c + 1;
-                if (cc + 1 < nwin) {
-                    if (ok_row) issue(r, c_next);
-                } else if (ok_next) {
-                    issue(r1, c0);
-                }
-                if (ok_row) {
-                    uint32_t W[4];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) W[k] = __builtin_amdgcn_alignbit(w[k + 1], w[k], sh);
-                    const int tbase = c * E;
-                    const uint32_t tb8 = lds_base + 8u * (uint32_t)(tbase * Bp);
-#pragma unroll
-                    for (int g0 = 0; g0 < E; g0 += G) {
-                        uint32_t addr[G];
-                        unsigned long long old[G];
-#pragma unroll
-                        for (int jj = 0; jj < G; ++jj) {
-                            const int j = g0 + jj;
-                            if (j < E) {
-                                const int pos = j * BITS, wd = pos >> 5, off = pos & 31;
-                                uint32_t sv;
-                                if (off + BITS <= 32)
-                                    sv = (W[wd] >> off) & MASK;
-                                else
-                                    sv = __builtin_amdgcn_alignbit(W[wd < 3 ? wd + 1 : 3], W[wd], (uint32_t)off) & MASK;
-                                const bool ok = CHK ? (tbase + j < ft) & (sv != missing) & (sv < (uint32_t)B) : (tbase + j < ft);
-                                addr[jj] = ok ? tb8 + 8u * (uint32_t)(j * Bp) + (sv << 3) : my_trash;
-                                if (UNI) ldsw_add(addr[jj], addv);
-                                else old[jj] = ldsw_add_rtn(addr[jj], addv);
-                            }
-                        }
-                        if (!UNI) {
-                            // the returned words of the group tested together: the smallest distance of any of them
-                            // from an event decides whether the per-word bookkeeping runs at all
-                            uint32_t near_carry = 0xffffffffu, near_wrap = 0xffffffffu;
-#pragma unroll
-                            for (int jj = 0; jj < G; ++jj)
-                                if (g0 + jj < E) {
-                                    near_carry = min(near_carry, pk_near_carry(old[jj]));
-                                    near_wrap = min(near_wrap, pk_near_wrap(old[jj], addv));
-                                }
-                            if (near_carry < hq || near_wrap < pk_reach(addv)) {
-#pragma unroll
-                                for (int jj = 0; jj < G; ++jj)
-                                    if (g0 + jj < E) pkw_check(side_base + ((addr[jj] - lds_base) >> 1), old[jj], addv, hq);
-                            }
-                        }
-                    }
-                }
-                c = c_next;
+            for (int j = 0; j < 4; ++j) W[j] = (W[j] & keep[j]) | (V[j] & ~keep[j]);
+            issue(next);
+            if (ok_row) {
+                if (most == E && ft == E << log_win) add(W, addv, hq, std::true_type());
+                else add(W, addv, hq, std::false_type());
             }
             if (!more) break;
             i += step;
-            r = r1;
             r1 = r2;
             q = q1;
             ok_row = ok_next;
@@ -184,25 +229,22 @@ __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
     }
     __syncthreads();
     int64_t *out = pool + job.hist_off + (uint64_t)job.f0 * (uint64_t)B * 2u;
-    const bool exclusive = job.pad0 == 1u;   // the only job of its (node, tile): plain stores, zeros included
-    if (!UNI) {
-        flush_tile(main_, side, ft, B, Bp, out, (int)blockDim.x, exclusive);
-    } else {
-        for (int k = threadIdx.x; k < ft * B; k += (int)blockDim.x) {
-            const int t = k / B, b = k - t * B;
-            const unsigned long long wv = main_[t * Bp + b];
-            if (!exclusive && wv == 0) continue;
+    // (pad0: the only job of its (node, tile))
+    merge_bins(ft, B, out, (int)blockDim.x, job.pad0 == 1u, [&](uint32_t t, uint32_t b, int64_t &g, int64_t &h) __attribute__((always_inline)) {
+        if (b > MASK || b == missing) return;   // (a table of fewer rows than bins: the symbols cannot hold them)
+        const uint32_t idx = b * (uint32_t)fs + t;
+        const unsigned long long wv = main_[idx];
+        if (UNI) {
             const int64_t rows = (int64_t)(wv & kWRowsMask);
-            const int64_t g = ((int64_t)wv - rows) >> kWRowsShift;
-            const int64_t h = rows * hq_uniform;
-            if (exclusive) {
-                *(longlong2 *)(out + 2 * (int64_t)k) = make_longlong2(g, h);
-            } else {
-                if (g != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)k), (unsigned long long)g);
-                if (h != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)k + 1), (unsigned long long)h);
-            }
+            g = ((int64_t)wv - rows) >> kWRowsShift;
+            h = (int64_t)((uint64_t)(uint32_t)rows * (uint32_t)hq_uniform);
+        } else {
+            const uint32_t sc = side[idx];
+            const int64_t carry = (int64_t)(sc & 0xffffu), wr = (int64_t)((int32_t)sc >> 16);
+            g = ((int64_t)wv >> kHShift) + wr * ((int64_t)1 << (64 - kHShift)) - carry;
+            h = (int64_t)(wv & kHMask) + (carry << kHShift);
         }
-    }
+    });
 }
 
 struct WArgs {
@@ -211,7 +253,7 @@ struct WArgs {
     size_t lds;
     const uint32_t *packed;
     int64_t n_words, stride_bits, n;
-    int B, Bp;
+    int B, rows_lds, fs;
     uint32_t missing;
     const uint32_t *row_idx;
     const int2 *gq;
@@ -220,29 +262,27 @@ struct WArgs {
     int32_t hq_uniform;
     const uint32_t *n_jobs_dev;
 };
-template <int BITS, bool LIST, bool UNI, bool CHK>
+template <int BITS, bool LIST, bool UNI, bool CLAMP>
 hipError_t launch_w(const WArgs &a) {
     GbtLdsGuard lds_guard(a.lds);
     if (lds_guard.needed) {
-        hipError_t e = hipFuncSetAttribute((const void *)hist_bits_kernel<BITS, LIST, UNI, CHK>,
+        hipError_t e = hipFuncSetAttribute((const void *)hist_bits_kernel<BITS, LIST, UNI, CLAMP>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds);
         if (e != hipSuccess) return e;
     }
-    hist_bits_kernel<BITS, LIST, UNI, CHK><<<a.n_jobs, a.block, a.lds, a.s>>>(a.packed, a.n_words, a.stride_bits, a.n, a.B, a.Bp,
-                                                                          a.missing, a.row_idx, a.gq, a.pool, a.jobs,
-                                                                          a.hq_uniform, a.n_jobs_dev);
+    hist_bits_kernel<BITS, LIST, UNI, CLAMP><<<a.n_jobs, a.block, a.lds, a.s>>>(a.packed, a.n_words, a.stride_bits, a.n, a.B,
+                                                                                a.rows_lds, a.fs, a.missing, a.row_idx, a.gq, a.pool,
+                                                                                a.jobs, a.hq_uniform, a.n_jobs_dev);
     return hipGetLastError();
 }
-template <int BITS, bool CHK>
+template <int BITS, bool CLAMP>
 hipError_t pick_w2(const WArgs &a, bool uni) {
-    if (a.row_idx) return uni ? launch_w<BITS, true, true, CHK>(a) : launch_w<BITS, true, false, CHK>(a);
-    return uni ? launch_w<BITS, false, true, CHK>(a) : launch_w<BITS, false, false, CHK>(a);
+    if (a.row_idx) return uni ? launch_w<BITS, true, true, CLAMP>(a) : launch_w<BITS, true, false, CLAMP>(a);
+    return uni ? launch_w<BITS, false, true, CLAMP>(a) : launch_w<BITS, false, false, CLAMP>(a);
 }
 template <int BITS>
 hipError_t pick_w(const WArgs &a, bool uni) {
-    constexpr uint32_t MASK = (1u << BITS) - 1u;
-    const bool chk = a.missing <= MASK || (uint32_t)a.B <= MASK;   // some value of the field is not a bin
-    return chk ? pick_w2<BITS, true>(a, uni) : pick_w2<BITS, false>(a, uni);
+    return a.rows_lds < (1 << BITS) ? pick_w2<BITS, true>(a, uni) : pick_w2<BITS, false>(a, uni);
 }
 }  // namespace
 
@@ -253,9 +293,15 @@ hipError_t gbt_launch_histw(gbt_ctx *ctx, const uint32_t *packed, int bits, int6
                             int64_t *hist_pool, const HistJob *jobs, int n_jobs, int max_ft, bool uniform_h,
                             int32_t hq_uniform, int block, const uint32_t *n_jobs_dev) {
     if (n_jobs <= 0) return hipSuccess;
-    const int Bp = padded_bins(B);
-    const size_t lds = ((size_t)max_ft * Bp + 64) * (uniform_h ? 8 : 12);
-    const WArgs a{ctx->stream, n_jobs, block, lds, packed, n_words, stride_bits, n, B, Bp, missing, row_idx,
+    // rows of the LDS table: the symbols, or the bins and one row for what is no bin; a stride that keeps a column in its banks
+    // where that leaves two workgroups on a compute unit
+    const int rows_lds = std::min(1 << bits, B + 1);
+    auto lds_of = [&](int fs) { return (size_t)rows_lds * fs * (uniform_h ? 8 : 12); };
+    int fs = (max_ft + 15) / 16 * 16;
+    if (lds_of(fs) > ctx->lds_per_block / 2) fs = max_ft | 1;
+    if (lds_of(fs) > ctx->lds_per_block) fs = max_ft;
+    const size_t lds = lds_of(fs);
+    const WArgs a{ctx->stream, n_jobs, block, lds, packed, n_words, stride_bits, n, B, rows_lds, fs, missing, row_idx,
                   (const int2 *)gq, hist_pool, jobs, hq_uniform, n_jobs_dev};
     switch (bits) {
         case 1: return pick_w<1>(a, uniform_h);
