@@ -3,6 +3,7 @@
 #ifndef GBT_HIST_COMMON_H
 #define GBT_HIST_COMMON_H
 #include "gbt_internal.h"
+#include "hist_merge.h"
 
 namespace {
 
@@ -22,28 +23,18 @@ __device__ __forceinline__ unsigned long long pack_pair(int2 q) {
     return ((unsigned long long)(long long)q.x << kHShift) + (unsigned long long)(uint32_t)q.y;
 }
 
-// Merge the workgroup's LDS histogram into the node's histogram in HBM: two 64-bit global atomics per non-zero
-// bin -- or, when this job is the only one of its (node, feature tile) (`exclusive`), plain 16-byte stores of
-// every bin, zeros included: no atomics (the chip retires them slowly) and nothing to clear beforehand.
+// Merge the workgroup's LDS histogram into the node's histogram in HBM (hist_merge.h).
 __device__ __forceinline__ void flush_tile(const unsigned long long *main_, const uint32_t *side, int ft, int B,
                                            int Bp, int64_t *out, int block, bool exclusive = false) {
-    for (int i = threadIdx.x; i < ft * B; i += block) {
-        const int t = i / B, b = i - t * B;
-        const int idx = t * Bp + b;
+    merge_bins(ft, B, out, block, exclusive, [&](uint32_t t, uint32_t b, int64_t &g, int64_t &h) __attribute__((always_inline)) {
+        const uint32_t idx = t * (uint32_t)Bp + b;
         const unsigned long long w = main_[idx];
         const uint32_t sc = side[idx];
-        if (!exclusive && w == 0 && sc == 0) continue;
         const int64_t carry = (int64_t)(sc & 0xffffu);
         const int64_t wraps = (int64_t)((int32_t)sc >> 16);
-        const int64_t g = ((int64_t)w >> kHShift) + wraps * ((int64_t)1 << (64 - kHShift)) - carry;
-        const int64_t h = (int64_t)(w & kHMask) + (carry << kHShift);
-        if (exclusive) {
-            *(longlong2 *)(out + 2 * (int64_t)i) = make_longlong2(g, h);
-        } else {
-            if (g != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i), (unsigned long long)g);
-            if (h != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i + 1), (unsigned long long)h);
-        }
-    }
+        g = ((int64_t)w >> kHShift) + wraps * ((int64_t)1 << (64 - kHShift)) - carry;
+        h = (int64_t)(w & kHMask) + (carry << kHShift);
+    });
 }
 
 // The two quick tests on a returned word, as tight as the row's own pair allows (events are not

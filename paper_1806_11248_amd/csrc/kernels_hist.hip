@@ -372,15 +372,12 @@ __device__ __forceinline__ void ph_add_row(const uint32_t (&row)[RW], unsigned l
 // The merge of a histogram kept in the uniform-hessian form (see ph_add_row) into the node's histogram in HBM.
 __device__ __forceinline__ void flush_tile_uniform(const unsigned long long *main_, int ft, int B, int Bp, int64_t *out,
                                                    int block, int64_t hq_uniform) {
-    for (int i = threadIdx.x; i < ft * B; i += block) {
-        const int t = i / B, b = i - t * B;
-        const unsigned long long w = main_[t * Bp + b];
-        if (w == 0) continue;
+    merge_bins(ft, B, out, block, false, [&](uint32_t t, uint32_t b, int64_t &g, int64_t &h) __attribute__((always_inline)) {
+        const unsigned long long w = main_[t * (uint32_t)Bp + b];
         const int64_t rows = (int64_t)(w & kUniRowsMax);
-        const int64_t g = ((int64_t)w - rows) >> kUniRowsShift, h = rows * hq_uniform;
-        if (g != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i), (unsigned long long)g);
-        if (h != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i + 1), (unsigned long long)h);
-    }
+        g = ((int64_t)w - rows) >> kUniRowsShift;
+        h = (int64_t)((uint64_t)(uint32_t)rows * (uint32_t)hq_uniform);
+    });
 }
 
 // Where rows stay in place only some lanes of a wave hold a row whose pair is added, and a wave's LDS atomic

@@ -28,6 +28,7 @@
 //    point itself -- in fp32 arithmetic where that is exact (power-of-two scales of moderate size), else
 //    through fp64 --, stores them only if asked to, and adds up the totals of all rows.
 #include "gbt_internal.h"
+#include "hist_merge.h"
 
 #include <math.h>
 
@@ -279,27 +280,21 @@ __global__ __launch_bounds__(BLOCK, MINWG) void hist8_kernel(const Hist8Args a) 
     __syncthreads();
     // merge the bins into the node's histogram
     const int B = a.B;
-    for (int i = threadIdx.x; i < ft * B; i += BLOCK) {
-        const int t = i / B, b = i - t * B;
-        if (b > 255 || (uint32_t)b == a.missing) continue;
-        const int idx = b * 16 + t;
+    merge_bins(ft, B, out, BLOCK, false, [&](uint32_t t, uint32_t b, int64_t &g, int64_t &h) __attribute__((always_inline)) {
+        if (b > 255u || b == a.missing) return;
+        const uint32_t idx = b * 16u + t;
         const unsigned long long wv = main_[idx];
-        int64_t g, h;
         if (!UNI) {
             const uint32_t sc = side[idx];
-            if (wv == 0 && sc == 0) continue;
             const int64_t carry = (int64_t)(sc & 0xffffu), wraps = (int64_t)((int32_t)sc >> 16);
             g = ((int64_t)wv >> kHShift) + wraps * ((int64_t)1 << (64 - kHShift)) - carry;
             h = (int64_t)(wv & kHMask) + (carry << kHShift);
         } else {
-            if (wv == 0) continue;
             const int64_t rows = (int64_t)(wv & kUniformMaxRows);
             g = ((int64_t)wv - rows) >> kRowsShift;
-            h = rows * a.hq_uniform;
+            h = (int64_t)((uint64_t)(uint32_t)rows * (uint32_t)a.hq_uniform);
         }
-        if (g != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i), (unsigned long long)g);
-        if (h != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i + 1), (unsigned long long)h);
-    }
+    });
     if (!REC && a.sums) {   // totals of this workgroup's rows into its own slot: same-address global atomics take turns
         long long G = sum_g, H = sum_h;
         if (UNI) {

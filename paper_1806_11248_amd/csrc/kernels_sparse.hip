@@ -13,6 +13,7 @@
 #include <type_traits>
 
 #include "gbt_internal.h"
+#include "hist_merge.h"
 #include "wave_scan.h"
 
 namespace {
@@ -252,25 +253,17 @@ __global__ __launch_bounds__(BLOCK) void sparse_hist_kernel(const uint32_t *__re
     }
     __syncthreads();
     const bool exclusive = UNI && job.pad0 == 1u;
-    for (uint32_t i = threadIdx.x; i < glen; i += BLOCK) {
+    merge_bins(1, (int)glen, out, BLOCK, exclusive, [&](uint32_t, uint32_t i, int64_t &g, int64_t &h) __attribute__((always_inline)) {
         const unsigned long long v = lds[i];
-        if (!exclusive && v == 0) continue;
-        int64_t g, h;
         if (UNI) {
             const int64_t rows = (int64_t)(v & kSpUniRows);
             g = ((int64_t)v - rows) >> kSpUniShift;
-            h = rows * hq_uniform;
+            h = (int64_t)((uint64_t)(uint32_t)rows * (uint32_t)hq_uniform);
         } else {
             g = (int64_t)v >> kHShift;
             h = (int64_t)(v & kHMask);
         }
-        if (exclusive) {
-            *(longlong2 *)(out + 2 * (int64_t)i) = make_longlong2(g, h);
-        } else {
-            if (g != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i), (unsigned long long)g);
-            if (h != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i + 1), (unsigned long long)h);
-        }
-    }
+    });
 }
 
 // The same over 32-bit ids (a matrix of more than 65536 global bin ids, whose histogram never fits one LDS tile):
@@ -331,14 +324,11 @@ __global__ __launch_bounds__(BLOCK) void sparse_hist32_kernel(const uint32_t *__
         }
     }
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < glen; i += BLOCK) {
+    merge_bins(1, (int)glen, out, BLOCK, false, [&](uint32_t, uint32_t i, int64_t &g, int64_t &h) __attribute__((always_inline)) {
         const unsigned long long w = lds[i];
-        if (w == 0) continue;
-        const int64_t g = (int64_t)w >> kHShift;
-        const int64_t h = (int64_t)(w & kHMask);
-        if (g != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i), (unsigned long long)g);
-        if (h != 0) atomicAdd((unsigned long long *)(out + 2 * (int64_t)i + 1), (unsigned long long)h);
-    }
+        g = (int64_t)w >> kHShift;
+        h = (int64_t)(w & kHMask);
+    });
 }
 
 // ---- RepartitionInstances over sparse rows ----------------------------------
