@@ -2881,6 +2881,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
     const int hq_uni = uniform_h && ent_bytes == 2 ? (int)llrint((double)h_value * scale[1]) : -1;
     plan_rule.max_rows = hq_uni >= 0 ? gbt_sparse_hist_max_rows() : kSparseMaxRowsPerJob;
     plan_rule.exclusive_ok = hq_uni >= 0 ? 1 : 0;
+    const int part_tile = gbt_sparse_part_tile(ctx, n, nnz, ent_bytes);
     const double row_bytes = 12.0 + (double)ent_bytes * (double)nnz / (double)n;   // row pointer, pair, the average row's entries
 
     std::vector<HistJob> hjobs;
@@ -2972,7 +2973,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
         g.cap_nodes = cap;
         g.level_nodes = L.level_nodes;
         for (int k = 0; k < 2; ++k) {
-            g.tile_rows[k] = (uint32_t)gbt_sparse_part_tile();
+            g.tile_rows[k] = (uint32_t)part_tile;
             g.n_left[k] = (const uint32_t *)(ws + L.state);   // two cursors per job; the first one's low word: left rows
             g.n_left_stride[k] = 4 * kCursorStride;
         }
@@ -2987,7 +2988,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
             const int span = gbt_prof_begin(ctx, GBT_PROF_PARTITION, 0.0);
             if (span >= 0) pass_spans.push_back({span, d, false});
             GBT_HIP(ctx, gbt_launch_sparse_partition(s, cur.rowptr, cur.ent, ent_bytes, cur.gq, w_rowptr[to], w_ent[to], w_gq[to], B,
-                                                     !last, g.v.pjobs, (int)n_splits, (int)tiles, g.v.cursors, kCursorStride,
+                                                     !last, part_tile, g.v.pjobs, (int)n_splits, (int)tiles, g.v.cursors, kCursorStride,
                                                      &g.v.levels[d].n_splits));
             gbt_prof_end(ctx);
             return GBT_OK;
@@ -3169,7 +3170,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
         const Rows cur = rows_of(wcur);
         const int child_depth = sel_nodes[0].depth + 1;   // loss-guided: of the first node; the others agree on "< max_depth"
         const bool children_need_hist = child_depth < max_depth && (!lossguide || n_leaves + 1 < max_leaves);
-        const uint32_t tile = (uint32_t)gbt_sparse_part_tile();
+        const uint32_t tile = (uint32_t)part_tile;
         pjobs.clear();
         uint32_t tile_cursor = 0;
         double part_rows = 0;
@@ -3195,7 +3196,7 @@ static int32_t sparse_grow_impl(gbt_ctx *ctx, const uint32_t *rowptr, const void
         if (st != GBT_OK) return st;
         gbt_prof_begin(ctx, GBT_PROF_PARTITION, part_rows * (children_need_hist ? 2.0 * row_bytes : row_bytes - 8.0));
         GBT_HIP(ctx, gbt_launch_sparse_partition(s, cur.rowptr, cur.ent, ent_bytes, cur.gq, w_rowptr[wnext], w_ent[wnext], w_gq[wnext],
-                                                 B, children_need_hist, (const PartJob *)(ws + L.jobs), (int)pjobs.size(),
+                                                 B, children_need_hist, part_tile, (const PartJob *)(ws + L.jobs), (int)pjobs.size(),
                                                  (int)tile_cursor, (unsigned long long *)(ws + L.state), stride));
         GBT_HIP(ctx, hipMemcpyAsync(rb(ctx), ws + L.state, pjobs.size() * 16 * stride, hipMemcpyDeviceToHost, s));
         gbt_prof_end(ctx);

@@ -332,7 +332,7 @@ __global__ __launch_bounds__(BLOCK) void sparse_hist32_kernel(const uint32_t *__
 }
 
 // ---- RepartitionInstances over sparse rows ----------------------------------
-// One launch per level, order inside a child not kept.  A tile of kSpTile rows finds each row's
+// One launch per level, order inside a child not kept.  A tile of BLOCK * PER rows finds each row's
 // side (the row's entry of the split feature is looked up among its ascending ids; a row without
 // one is missing and takes the default side), ranks rows and entries per side inside the tile and
 // reserves room in both children with two 64-bit atomics on the node's cursors
@@ -340,10 +340,6 @@ __global__ __launch_bounds__(BLOCK) void sparse_hist32_kernel(const uint32_t *__
 // the node's row range and entry range from the front, right rows from the back, so both children
 // stay contiguous in rows AND in entries, and rowptr[r + 1] - rowptr[r] stays a row's length.
 // move == 0: only the left rows are counted (the last level).
-constexpr int kSpTile = 1024;
-constexpr int kSpRowsPerThread = kSpTile / kSpBlock;   // 2
-constexpr int kSpGroups = kSpRowsPerThread * (kSpBlock / 64);   // (k, wave) groups of 64 rows: 16
-
 // the entry with an id in [lo, lo + B) among the ascending ids ent[s .. e), or 0xffffffff
 template <typename P>
 __device__ __forceinline__ uint32_t find_feature_entry(P ent, uint32_t s, uint32_t e, uint32_t lo, uint32_t B) {
@@ -367,8 +363,8 @@ __device__ __forceinline__ uint32_t find_feature_entry(P ent, uint32_t s, uint32
 // retire about one lane per clock and compute unit, whatever their addresses.
 constexpr int kSpStage = 12288;
 
-template <typename E>
-__global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *__restrict__ src_rowptr,
+template <typename E, int BLOCK, int PER>
+__global__ __launch_bounds__(BLOCK) void sparse_part_kernel(const uint32_t *__restrict__ src_rowptr,
                                                                const E *__restrict__ src_ent,
                                                                const int2 *__restrict__ src_gq,
                                                                uint32_t *__restrict__ dst_rowptr,
@@ -381,10 +377,11 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
         if (blockIdx.x >= counts_dev[1]) return;
         n_jobs = (int)counts_dev[0];
     }
+    constexpr int kRows = BLOCK * PER, kGroups = PER * (BLOCK / 64);   // rows of a tile; (k, wave) groups of 64 of them
     __shared__ __align__(16) uint32_t stage_w[kSpStage / 2];
     __shared__ uint32_t out_w[kSpStage / 2 + 4];
-    __shared__ uint32_t grp_rows[2][kSpGroups];   // [side][group]: rows, then their exclusive offsets
-    __shared__ uint32_t grp_ent[2][kSpGroups];
+    __shared__ uint32_t grp_rows[2][kGroups];   // [side][group]: rows, then their exclusive offsets
+    __shared__ uint32_t grp_ent[2][kGroups];
     __shared__ unsigned long long base[2];        // what the cursors returned
     __shared__ uint32_t tot[4];                   // rows L, rows R, entries L, entries R of the tile
     constexpr uint32_t EPW = 4 / sizeof(E), SH = EPW == 2 ? 1 : 0;   // entries per word, and its log2
@@ -393,8 +390,8 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
     const PartJob job = jobs[j];
     const uint32_t t_local = blockIdx.x - job.tile_begin;
     const uint32_t seg_end = job.seg_begin + job.seg_len;
-    const uint32_t r0 = job.seg_begin + t_local * (uint32_t)kSpTile;
-    const uint32_t r1 = r0 + (uint32_t)kSpTile < seg_end ? r0 + (uint32_t)kSpTile : seg_end;
+    const uint32_t r0 = job.seg_begin + t_local * (uint32_t)kRows;
+    const uint32_t r1 = r0 + (uint32_t)kRows < seg_end ? r0 + (uint32_t)kRows : seg_end;
     const uint32_t lo = job.feature * B, thr = lo + job.bin;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
@@ -406,28 +403,28 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
     if (staged) {
         // four words per load, all of a thread's loads in flight together; the stream ends in slack that such loads may touch
         const uint32_t *src_w = (const uint32_t *)src_ent + w0;
-        constexpr int kLoads = kSpStage / 2 / (4 * kSpBlock);
-        static_assert(kLoads * 4 * kSpBlock == kSpStage / 2, "whole turns");
+        constexpr int kLoads = kSpStage / 2 / (4 * BLOCK);
+        static_assert(kLoads * 4 * BLOCK == kSpStage / 2, "whole turns");
         Words4 v[kLoads];
 #pragma unroll
         for (int k = 0; k < kLoads; ++k) {
-            const uint32_t w = 4u * (k * kSpBlock + threadIdx.x);
+            const uint32_t w = 4u * (k * BLOCK + threadIdx.x);
             if (w < n_words) v[k] = *(const Words4 *)(src_w + w);
         }
 #pragma unroll
         for (int k = 0; k < kLoads; ++k) {
-            const uint32_t w = 4u * (k * kSpBlock + threadIdx.x);
+            const uint32_t w = 4u * (k * BLOCK + threadIdx.x);
             if (w < n_words) *(uint4 *)(stage_w + w) = make_uint4(v[k].x, v[k].y, v[k].z, v[k].w);
         }
     }
     const uint32_t sbase = w0 << SH;   // stream index of stage[0]
 
-    uint32_t rs[kSpRowsPerThread], rlen[kSpRowsPerThread], within_rows[kSpRowsPerThread], within_ent[kSpRowsPerThread];
-    bool live[kSpRowsPerThread], left[kSpRowsPerThread];
-    int2 pair[kSpRowsPerThread];
+    uint32_t rs[PER], rlen[PER], within_rows[PER], within_ent[PER];
+    bool live[PER], left[PER];
+    int2 pair[PER];
 #pragma unroll
-    for (int k = 0; k < kSpRowsPerThread; ++k) {
-        const uint32_t r = r0 + (uint32_t)k * kSpBlock + threadIdx.x;
+    for (int k = 0; k < PER; ++k) {
+        const uint32_t r = r0 + (uint32_t)k * BLOCK + threadIdx.x;
         live[k] = r < r1;
         rs[k] = 0;
         rlen[k] = 0;
@@ -441,7 +438,7 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kSpRowsPerThread; ++k) {
+    for (int k = 0; k < PER; ++k) {
         if (live[k]) {
             const uint32_t g = staged ? find_feature_entry(stage, rs[k] - sbase, rs[k] - sbase + rlen[k], lo, B)
                                       : find_feature_entry(src_ent, rs[k], rs[k] + rlen[k], lo, B);
@@ -450,7 +447,7 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
     }
     // ranks inside each group of 64 rows: rows by ballot, entries by a 64-bit scan holding both sides
 #pragma unroll
-    for (int k = 0; k < kSpRowsPerThread; ++k) {
+    for (int k = 0; k < PER; ++k) {
         const uint64_t bl = __ballot(live[k] && left[k]), br = __ballot(live[k] && !left[k]);
         const uint64_t below = (1ull << lane) - 1ull;
         within_rows[k] = (uint32_t)__popcll((left[k] ? bl : br) & below);
@@ -459,7 +456,7 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
         const unsigned long long excl = incl - x;
         within_ent[k] = left[k] ? (uint32_t)excl : (uint32_t)(excl >> 32);
         if (lane == 63) {
-            const int grp = k * (kSpBlock / 64) + wave;
+            const int grp = k * (BLOCK / 64) + wave;
             grp_rows[0][grp] = (uint32_t)__popcll(bl);
             grp_rows[1][grp] = (uint32_t)__popcll(br);
             grp_ent[0][grp] = (uint32_t)incl;
@@ -467,20 +464,20 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
         }
     }
     __syncthreads();
-    if (wave == 0 && lane < 2 * kSpGroups) {   // exclusive offsets over the groups: first G lanes rows, next G entries
-        static_assert(kSpGroups <= 32 && (kSpGroups & (kSpGroups - 1)) == 0, "two tables inside one wave");
-        const int grp = lane & (kSpGroups - 1);
-        const bool rows_tab = lane < kSpGroups;
+    if (wave == 0 && lane < 2 * kGroups) {   // exclusive offsets over the groups: first G lanes rows, next G entries
+        static_assert(kGroups <= 32 && (kGroups & (kGroups - 1)) == 0, "two tables inside one wave");
+        const int grp = lane & (kGroups - 1);
+        const bool rows_tab = lane < kGroups;
         for (int side = 0; side < 2; ++side) {
             uint32_t *tab = rows_tab ? grp_rows[side] : grp_ent[side];
             const uint32_t v = tab[grp];
             uint32_t incl = v;
-            for (int o = 1; o < kSpGroups; o <<= 1) {
+            for (int o = 1; o < kGroups; o <<= 1) {
                 const uint32_t y = (uint32_t)__shfl_up((int)incl, o);
                 if (grp >= o) incl += y;
             }
             tab[grp] = incl - v;
-            if (grp == kSpGroups - 1) tot[(rows_tab ? 0 : 2) + side] = incl;
+            if (grp == kGroups - 1) tot[(rows_tab ? 0 : 2) + side] = incl;
         }
     }
     __syncthreads();
@@ -497,8 +494,8 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
     const uint32_t lds_r = ((lds_l + tot[2] + EPW - 1u) & ~(EPW - 1u)) + (ent_r & (EPW - 1u));
     E *outE = (E *)out_w;
 #pragma unroll
-    for (int k = 0; k < kSpRowsPerThread; ++k) {
-        const int grp = k * (kSpBlock / 64) + wave;
+    for (int k = 0; k < PER; ++k) {
+        const int grp = k * (BLOCK / 64) + wave;
         const int side = left[k] ? 0 : 1;
         const uint32_t in_piece = grp_ent[side][grp] + within_ent[k];   // the row's place inside its side's piece
         const uint32_t drow = (left[k] ? row_l : row_r) + grp_rows[side][grp] + within_rows[k];
@@ -538,7 +535,7 @@ __global__ __launch_bounds__(kSpBlock) void sparse_part_kernel(const uint32_t *_
         const uint32_t wfirst = (gs + EPW - 1u) >> SH, wend = ge >> SH;            // whole words [wfirst, wend)
         const uint32_t lw = (ls + (gs & (EPW - 1u))) >> SH;                        // window word of stream word wfirst
         uint32_t *dst_words = (uint32_t *)dst_ent;
-        for (uint32_t w = threadIdx.x; wfirst + w < wend; w += kSpBlock) dst_words[wfirst + w] = out_w[lw + w];
+        for (uint32_t w = threadIdx.x; wfirst + w < wend; w += BLOCK) dst_words[wfirst + w] = out_w[lw + w];
         // (16-bit ids: a piece may begin and end in the middle of a word)
         if (threadIdx.x == 0 && (gs & (EPW - 1u))) dst_ent[gs] = outE[ls];
         if (threadIdx.x == 64 && (ge & (EPW - 1u)) && (ge - 1 >= gs)) dst_ent[ge - 1] = outE[ls + (ge - 1 - gs)];
@@ -853,23 +850,41 @@ hipError_t gbt_launch_sparse_hist(gbt_ctx *ctx, const uint32_t *rowptr, const vo
 }
 
 int gbt_sparse_hist_max_rows() { return (int)kSpUniRows; }
-int gbt_sparse_part_tile() { return kSpTile; }
+int gbt_sparse_part_tile(const gbt_ctx *ctx, int64_t n, int64_t nnz, int ent_bytes) {
+    const double words = (double)nnz / (double)(n > 0 ? n : 1) * ent_bytes / 4.0;   // of a row, on average
+    int rows = 1024;
+    while (rows > 128 && rows * words * 1.15 > kSpStage / 2) rows /= 2;
+    if (rows * words * 1.15 > kSpStage / 2) rows = 1024;
+    while (rows > 128 && n < (int64_t)rows * ctx->num_cu) rows /= 2;
+    return rows;
+}
 
 hipError_t gbt_launch_sparse_partition(hipStream_t s, const uint32_t *src_rowptr, const void *src_ent, int ent_bytes,
                                        const int32_t *src_gq, uint32_t *dst_rowptr, void *dst_ent,
-                                       int32_t *dst_gq, int B, bool move, const PartJob *jobs, int n_jobs,
+                                       int32_t *dst_gq, int B, bool move, int tile_rows, const PartJob *jobs, int n_jobs,
                                        int n_tiles, unsigned long long *cursor, int cursor_stride, const uint32_t *counts_dev) {
     if (n_jobs <= 0 || n_tiles <= 0) return hipSuccess;
     hipError_t e = counts_dev ? hipSuccess : gbt_launch_fill_u64(s, (uint64_t *)cursor, 0, 2 * (int64_t)n_jobs * cursor_stride);
     if (e != hipSuccess) return e;
-    if (ent_bytes == 2)
-        sparse_part_kernel<uint16_t><<<n_tiles, kSpBlock, 0, s>>>(src_rowptr, (const uint16_t *)src_ent, (const int2 *)src_gq,
-                                                                  dst_rowptr, (uint16_t *)dst_ent, (int2 *)dst_gq, (uint32_t)B,
-                                                                  move ? 1 : 0, jobs, n_jobs, cursor, cursor_stride, counts_dev);
-    else
-        sparse_part_kernel<uint32_t><<<n_tiles, kSpBlock, 0, s>>>(src_rowptr, (const uint32_t *)src_ent, (const int2 *)src_gq,
-                                                                  dst_rowptr, (uint32_t *)dst_ent, (int2 *)dst_gq, (uint32_t)B,
-                                                                  move ? 1 : 0, jobs, n_jobs, cursor, cursor_stride, counts_dev);
+    auto launch = [&](auto block, auto per) {
+        constexpr int BLOCK = decltype(block)::value, PER = decltype(per)::value;
+        if (ent_bytes == 2)
+            sparse_part_kernel<uint16_t, BLOCK, PER><<<n_tiles, BLOCK, 0, s>>>(
+                src_rowptr, (const uint16_t *)src_ent, (const int2 *)src_gq, dst_rowptr, (uint16_t *)dst_ent, (int2 *)dst_gq, (uint32_t)B,
+                move ? 1 : 0, jobs, n_jobs, cursor, cursor_stride, counts_dev);
+        else
+            sparse_part_kernel<uint32_t, BLOCK, PER><<<n_tiles, BLOCK, 0, s>>>(
+                src_rowptr, (const uint32_t *)src_ent, (const int2 *)src_gq, dst_rowptr, (uint32_t *)dst_ent, (int2 *)dst_gq, (uint32_t)B,
+                move ? 1 : 0, jobs, n_jobs, cursor, cursor_stride, counts_dev);
+    };
+    using std::integral_constant;
+    switch (tile_rows) {
+        case 1024: launch(integral_constant<int, 512>(), integral_constant<int, 2>()); break;
+        case 512: launch(integral_constant<int, 512>(), integral_constant<int, 1>()); break;
+        case 256: launch(integral_constant<int, 256>(), integral_constant<int, 1>()); break;
+        case 128: launch(integral_constant<int, 128>(), integral_constant<int, 1>()); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
