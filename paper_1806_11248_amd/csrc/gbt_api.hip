@@ -1286,7 +1286,8 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
     // every row has the same hessian (squared error always, the first tree of a logistic model): the passes over rows
     // that stay in place then keep a row count per bin instead of a hessian sum (>= 0: that hessian in fixed point)
     const int hq_uni = uniform_h ? (int)llrint((double)h_value * scale[1]) : -1;
-    if (path == 3 && root_may_split)   // the root's id list, read by the first partition
+    const bool ids_unordered = path == 3 && planned && !tracked;   // one launch per partition (part_ids_kernel)
+    if (path == 3 && root_may_split && !ids_unordered)   // the root's id list, read by the first partition
         GBT_HIP(ctx, gbt_launch_iota_u32(s, W[1].id_rw, n));
     // Where the partition + histogram pass follows (path 2) and rounding in fp32 is exact, the fixed-point pairs
     // are never stored: the root histogram and the first pass each round the fp32 pairs themselves, and from
@@ -1391,7 +1392,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
         g.v = plan_view(ctx, ws + L.plan, P, ws + L.tree_stage, cap);
         g.v.hjobs = (HistJob *)(ws + L.jobs);
         g.v.cursors = (unsigned long long *)(ws + L.state);
-        g.v.cursors_per_job = path == 1 ? 1 : 0;
+        g.v.cursors_per_job = path == 1 || ids_unordered ? 1 : 0;
         g.v.pool = pool;
         g.v.hist_len = hist_len;
         g.v.cuts = cuts;
@@ -1410,13 +1411,21 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
         g.n = n;
         g.cap_nodes = cap;
         g.level_nodes = L.level_nodes;
-        // (path 1 moves records in one launch, its last level only counts; path 3 partitions ids in three launches throughout)
+        // (path 1 moves records in one launch, its last level only counts; path 3 partitions ids throughout, in one launch or, where
+        // the caller wants the row order, in three)
         g.tile_rows[0] = path == 1 ? (uint32_t)gbt_partition_fused_tile(W[0], n) : (uint32_t)GBT_PART_TILE;
         g.tile_rows[1] = GBT_PART_TILE;
         g.n_left[0] = path == 1 ? (const uint32_t *)(ws + L.state) : (const uint32_t *)(ws + L.n_left);
         g.n_left_stride[0] = path == 1 ? 2 * kCursorStride : 1;
         g.n_left[1] = (const uint32_t *)(ws + L.n_left);
         g.n_left_stride[1] = 1;
+        const int ids_tile = gbt_partition_ids_tile(ctx, n);
+        if (ids_unordered)
+            for (int k = 0; k < 2; ++k) {
+                g.tile_rows[k] = (uint32_t)ids_tile;
+                g.n_left[k] = (const uint32_t *)(ws + L.state);
+                g.n_left_stride[k] = 2 * kCursorStride;
+            }
         g.nb = nb;
         g.min_child_weight = params->min_child_weight;
         // The rest of the call can be enqueued behind the levels as well where the tree is walked from LDS at the size it
@@ -1435,7 +1444,11 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
             const GbtRows &dst = W[d & 1];
             const int span = gbt_prof_begin(ctx, GBT_PROF_PARTITION, 0.0);
             if (span >= 0) pass_spans.push_back({span, d, path == 3 ? 1 : last ? 2 : 0});
-            if (path == 3) {
+            if (ids_unordered) {
+                GBT_HIP(ctx, gbt_launch_partition_ids(s, packed, bits, row_bits, n, (uint32_t)missing_sym, d == 0 ? nullptr : cur.id,
+                                                      dst.id_rw, ids_tile, g.v.pjobs, (int)splits, (int)tiles, g.v.cursors, kCursorStride,
+                                                      counts));
+            } else if (path == 3) {
                 GBT_HIP(ctx, gbt_launch_partition(s, packed, bits, row_bits, n, (uint32_t)missing_sym, d == 0 ? W[1].id : cur.id,
                                                   dst.id_rw, g.v.pjobs, (int)splits, (int)tiles, (uint64_t *)(ws + L.masks),
                                                   (uint32_t *)(ws + L.tile_left), n_left32, counts));

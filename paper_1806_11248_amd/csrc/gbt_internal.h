@@ -376,6 +376,12 @@ hipError_t gbt_launch_eval(hipStream_t s, int64_t *hist_pool, const EvalNode *no
                            double lambda, double mcw, gbt_split *out, EvalTail tail = EvalTail{nullptr, nullptr, 0, 0, -1, 0},
                            const uint32_t *n_nodes_dev = nullptr);
 
+// Row ids in one launch, order not kept: tiles of tile_rows = gbt_partition_ids_tile() rows, a cursor of 64 bits per job (the caller
+// clears them), [ right rows : left rows ].  src NULL: a segment's ids are its places.
+int gbt_partition_ids_tile(const gbt_ctx *ctx, int64_t n);
+hipError_t gbt_launch_partition_ids(hipStream_t s, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n, uint32_t missing,
+                                    const uint32_t *src, uint32_t *dst, int tile_rows, const PartJob *jobs, int n_jobs, int total_tiles,
+                                    unsigned long long *cursor, int cursor_stride, const uint32_t *counts_dev);
 hipError_t gbt_launch_partition(hipStream_t s, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n,
                                 uint32_t missing, const uint32_t *src, uint32_t *dst,
                                 const PartJob *jobs, int n_jobs, int total_tiles, uint64_t *masks,

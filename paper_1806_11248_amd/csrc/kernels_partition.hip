@@ -79,6 +79,88 @@ __global__ __launch_bounds__(kBlock) void part_flag_kernel(
     if (threadIdx.x == 0) tile_left[tile] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
 }
 
+// Row ids in one launch, order not kept: a tile of kBlock * PER rows decides its rows' sides and reserves its room in both children
+// with one 64-bit atomic on the node's cursor [ right rows : left rows ].  Left rows fill the segment from its start, right rows from
+// its end, a tile's in their order.  src == NULL: as for part_flag_kernel.
+// Bound: the gather, one symbol of every row and with it a line of a wide row.  The flag, scan and scatter launches that it stands
+// in for read every id twice: 10M x 50 x 9 bits, seven levels, 1371 us in 21 launches, 1182 us in 7; 50,000 x 500, where launches
+// count, a round of six levels 25 us less.  They stay where the caller wants the rows of a leaf in order.
+template <int PER>
+__global__ __launch_bounds__(kBlock) void part_ids_kernel(const uint32_t *__restrict__ packed, int bits, int64_t stride_bits, int64_t n,
+                                                          uint32_t missing, const uint32_t *__restrict__ src, uint32_t *__restrict__ dst,
+                                                          const PartJob *__restrict__ jobs, int n_jobs,
+                                                          unsigned long long *__restrict__ cursor, int cursor_stride,
+                                                          const uint32_t *__restrict__ counts_dev) {
+    if (counts_dev) {
+        if (blockIdx.x >= counts_dev[1]) return;
+        n_jobs = (int)counts_dev[0];
+    }
+    constexpr int kWaves = kBlock / 64, kGroups = PER * kWaves;   // (step, wave) groups of 64 rows
+    __shared__ uint32_t lefts[kGroups];          // left rows of a group, then of the groups before it
+    __shared__ uint32_t tot_left;
+    __shared__ unsigned long long base;
+    const int ji = gbt_find_job(jobs, n_jobs, blockIdx.x);
+    const PartJob job = jobs[ji];
+    const uint32_t first = (blockIdx.x - job.tile_begin) * (uint32_t)(kBlock * PER);   // of the segment's rows
+    const uint32_t rows = job.seg_len - first < (uint32_t)(kBlock * PER) ? job.seg_len - first : (uint32_t)(kBlock * PER);
+    const uint32_t mask = (1u << bits) - 1u;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t below = (1ull << lane) - 1ull;
+    uint32_t id[PER];
+    uint64_t ballot[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint32_t off = (uint32_t)j * kBlock + threadIdx.x;
+        const uint64_t p = (uint64_t)job.seg_begin + first + off;
+        id[j] = off < rows ? (src ? src[p] : (uint32_t)p) : 0xffffffffu;
+    }
+    // (every row's two words, asked for together: the stream ends in a word of padding)
+    typedef uint32_t two_words __attribute__((ext_vector_type(2), aligned(4)));
+    two_words v[PER];
+    uint32_t sh[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint64_t r = (uint64_t)id[j] < (uint64_t)n ? id[j] : 0u;
+        const uint64_t bp = r * (uint64_t)stride_bits + (uint64_t)job.feature * bits;
+        v[j] = *(const two_words *)(packed + (bp >> 5));
+        sh[j] = (uint32_t)bp & 31u;
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint32_t s = __builtin_amdgcn_alignbit(v[j][1], v[j][0], sh[j]) & mask;
+        const bool ok = (uint32_t)j * kBlock + threadIdx.x < rows && (uint64_t)id[j] < (uint64_t)n;
+        const bool left = ok && ((s == missing) ? (job.default_left != 0) : (s <= job.bin));
+        ballot[j] = __ballot(left);
+        if (lane == 0) lefts[j * kWaves + wave] = (uint32_t)__popcll(ballot[j]);
+    }
+    __syncthreads();
+    if (wave == 0) {
+        static_assert(kGroups <= 64, "one wave sums the groups");
+        const uint32_t v = lane < kGroups ? lefts[lane] : 0u;
+        uint32_t x = v;
+        for (int o = 1; o < kGroups; o <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)x, o);
+            if (lane >= o) x += y;
+        }
+        if (lane < kGroups) lefts[lane] = x - v;
+        if (lane == kGroups - 1) {
+            tot_left = x;
+            base = atomicAdd(&cursor[(size_t)ji * cursor_stride], ((unsigned long long)(rows - x) << 32) | x);
+        }
+    }
+    __syncthreads();
+    const uint32_t at_left = job.seg_begin + (uint32_t)base;
+    const uint32_t at_right = job.seg_begin + job.seg_len - (uint32_t)(base >> 32) - (rows - tot_left);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint32_t off = (uint32_t)j * kBlock + threadIdx.x;
+        if (off >= rows) continue;
+        const uint32_t before = lefts[j * kWaves + wave] + (uint32_t)__popcll(ballot[j] & below);   // left rows of the tile before this
+        const bool left = (ballot[j] >> lane) & 1u;
+        dst[left ? at_left + before : at_right + (off - before)] = id[j];
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void part_scan_kernel(const PartJob *__restrict__ jobs,
                                                            uint32_t *__restrict__ tile_left,
                                                            uint32_t *__restrict__ n_left_out,
@@ -745,6 +827,29 @@ hipError_t gbt_launch_count2(hipStream_t s, const uint8_t *rows, int64_t stride_
 }
 
 bool gbt_partition_fused_ok(const GbtRows &dst) { return (dst.stride_bits >> 5) <= 64; }
+// Rows of a tile of part_ids_kernel: 2048, or as few as give every compute unit a tile (256 at least).
+int gbt_partition_ids_tile(const gbt_ctx *ctx, int64_t n) {
+    int rows = 8 * kBlock;
+    while (rows > kBlock && n < (int64_t)rows * ctx->num_cu) rows /= 2;
+    return rows;
+}
+hipError_t gbt_launch_partition_ids(hipStream_t s, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n, uint32_t missing,
+                                    const uint32_t *src, uint32_t *dst, int tile_rows, const PartJob *jobs, int n_jobs, int total_tiles,
+                                    unsigned long long *cursor, int cursor_stride, const uint32_t *counts_dev) {
+    if (n_jobs <= 0 || total_tiles <= 0) return hipSuccess;
+    auto launch = [&](auto kernel) {
+        kernel<<<total_tiles, kBlock, 0, s>>>(packed, bits, stride_bits, n, missing, src, dst, jobs, n_jobs, cursor, cursor_stride, counts_dev);
+        return hipGetLastError();
+    };
+    switch (tile_rows / kBlock) {
+        case 8: return launch(part_ids_kernel<8>);
+        case 4: return launch(part_ids_kernel<4>);
+        case 2: return launch(part_ids_kernel<2>);
+        case 1: return launch(part_ids_kernel<1>);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 int gbt_partition_fused_tile(const GbtRows &dst, int64_t n) {
     return fused_form(dst.stride_bits, n) ? kFTile : staged_tile_rows(dst.stride_bits, n);
 }
