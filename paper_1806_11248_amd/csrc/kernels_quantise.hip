@@ -251,7 +251,7 @@ __global__ __launch_bounds__(256) void csr_scatter_direct_kernel(const int32_t *
 
 // seg_off / blk_off / chk_off [f] = exclusive prefix of the segments' lengths, tiles and scan chunks (kScanChunk tiles
 // each), by one workgroup: a piece of features per thread, then a scan over the pieces.  With `mode` only the features to
-// be sorted (kSelSorted) have tiles.  *dear (may be NULL) is cleared for the selection.
+// be sorted (kSelSorted) have tiles.  dear[0..1] (may be NULL) are cleared for the selection.
 __global__ __launch_bounds__(1024) void offsets_kernel(const uint32_t *counts, int F, int64_t fixed_len,
                                                        const uint32_t *__restrict__ mode, uint64_t *seg_off,
                                                        uint32_t *blk_off, uint32_t *chk_off, int scan_chunk,
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(1024) void offsets_kernel(const uint32_t *counts, i
         seg_off[F] = so[1023];
         blk_off[F] = bo[1023];
         chk_off[F] = co[1023];
-        if (dear) *dear = 0;
+        if (dear) dear[0] = dear[1] = 0;   // (and SelArrays::mix behind it)
     }
 }
 

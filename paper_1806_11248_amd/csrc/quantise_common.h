@@ -97,6 +97,7 @@ struct SelArrays {
     uint32_t *flag;      // [1] not zero: some feature's mode is kSelSorted
     uint32_t *cost;      // [F] key reads of the workgroup that would spend most on the feature, by its sample
     unsigned long long *dear;   // [1] keys of the features whose cost is more than sorting them alone
+    uint32_t *mix;              // [2] behind it: kinds of features the count meets (1 numbers, 2 discrete, 4 some dear) and the collection (1 work, 2 none)
     int cap, sample_cap;
 };
 #endif
