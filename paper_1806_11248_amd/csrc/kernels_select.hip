@@ -44,6 +44,7 @@ constexpr int kMidSlot = 8192;         // ... and up to which a workgroup of 256
 constexpr int kMidBits = 12, kBigBits = 14;   // counters of those workgroups (16 and 64 KB of LDS)
 constexpr int kMarkBits = 19;          // bits of the mark table (64 KB of LDS)
 constexpr uint32_t kKindDiscrete = 1, kKindNoCollect = 2;   // bits of SelArrays::kind
+constexpr int kKindHotShift = 8;       // above: 1 + where a discrete feature's frequent key stands in the sample (0: there is none)
 constexpr uint16_t kNoSlot = 0xffff;
 
 // Exclusive prefix sum over the workgroup's threads; *total receives the sum.  tmp: one word per wave.
@@ -85,6 +86,9 @@ __device__ inline void wave_sync() {
 // side.  So the limit follows from `dear`, the keys of all features that would be sorted for their own sake: 8 columns of
 // 10M dates in 64 bins, 1.3 ms, sorted 2.1; 30 columns of 3M narrow normals in 16 bins, 1.6 and 2.3.
 constexpr uint64_t kCachedKeys = 1ull << 25;
+// From here on (eight tiles per workgroup on 256 compute units) frequent keys are looked for and runs are of equal work: 3 and 1 us
+// of the sample kernel, which 0.6M keys (the call 220 us) do not gain back.
+constexpr uint64_t kManyKeys = 1ull << 24;
 __device__ inline uint64_t work_limit(uint64_t tuned, const uint64_t *seg_off, int F, int f, uint64_t dear, bool discrete) {
     const uint64_t len = seg_off[f + 1] - seg_off[f], reads = (1ull << 20) + (len > dear ? len : dear) / 32;
     return tuned ? tuned : discrete || seg_off[F] > kCachedKeys ? reads : reads * 5 / 2;
@@ -127,6 +131,8 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) voi
     __shared__ uint32_t tmp[kSelBlock / 64];
     __shared__ uint32_t n_mixed, sum_other;     // cells of several values, and their sampled keys besides the frequent one
     __shared__ uint32_t max_other, max_order;   // the dearest cell: such keys, and key reads of sel_order_kernel
+    __shared__ uint32_t longest;                // the most frequent key: how often << 12 | where (discrete features)
+    static_assert(kSampleMax <= 1 << 12, "a place in the sample has 12 bits");
     const int f = blockIdx.x, tid = threadIdx.x;
     const uint64_t len = seg_off[f + 1] - seg_off[f];
     const uint32_t *p = keys + seg_off[f];
@@ -202,7 +208,7 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) voi
         per_seg[tid * PER + i] = first | ((uint32_t)(kSegShift - bits[i]) << 24);
         first += 1u << bits[i];
     }
-    if (tid == 0) n_mixed = sum_other = max_other = max_order = 0;
+    if (tid == 0) n_mixed = sum_other = max_other = max_order = longest = 0;
     __syncthreads();
     uint32_t *rep = A.rep + (uint64_t)f * kDiscreteCells;
     if (discrete)
@@ -214,6 +220,13 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) voi
         if ((tid & 63) == 0) heads[j >> 6] = m;
     }
     __syncthreads();   // (and `rep` is clear)
+    if (discrete && seg_off[gridDim.x] >= kManyKeys)
+        for (int j = tid; j < (int)present; j += kSelBlock) {
+            const uint32_t k = v[j];
+            if (j > 0 && v[j - 1] == k) continue;
+            const int end = sample_bound(v, j, (int)present, [&](uint32_t x) { return x <= k; });
+            atomicMax(&longest, (uint32_t)(end - j) << 12 | (uint32_t)j);
+        }
     uint32_t used = (tid & 63) < P / 64 ? (uint32_t)__popcll(heads[tid & 63]) : 0u;   // every wave adds them up
     for (int o = 32; o > 0; o >>= 1) used += (uint32_t)__shfl_xor((int)used, o);
     // What the feature would cost.  In no more cells than bins the distinct values are counted by one workgroup; otherwise a
@@ -263,11 +276,12 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) voi
                 cost = all;
             }
         }
-        A.kind[f] = discrete ? kKindDiscrete : 0u;
+        const uint32_t hot = (longest >> 12) * 8u >= present ? (longest & 4095u) + 1u : 0u;
+        A.kind[f] = discrete ? kKindDiscrete | hot << kKindHotShift : 0u;
         A.cost[f] = cost < 4e9f ? (uint32_t)cost : 4000000000u;
         const bool dear = A.cost[f] > work_limit(work_tuned, seg_off, gridDim.x, f, 0, discrete);
         if (dear) atomicAdd(A.dear, (unsigned long long)len);
-        atomicOr(&A.mix[0], (discrete ? 2u : 1u) | (dear ? 4u : 0u));
+        if (seg_off[gridDim.x] >= kManyKeys) atomicOr(&A.mix[0], (discrete ? 2u : 1u) | (dear ? 4u : 0u));
         A.n_cells[f] = total;
     }
     // what the next kernels read (behind the last barrier: none waits for these stores)
@@ -288,8 +302,8 @@ typedef uint32_t sel_u32x4 __attribute__((ext_vector_type(4), aligned(4)));   //
 // Workgroup b of the grid takes a run of tiles, whatever features they belong to: an equal one, or one of equal work where a
 // feature's tiles weigh what the kernel says (0: nothing to do there).  A table of 115M rows with 8 columns of categories and 5
 // of numbers, equal runs and runs of equal work: count 1.69 and 1.46 ms, collect 1.14 and 0.89, the whole call 7.96 and 7.41.
-// The shares cost 7 us a launch, so not where all features are of one kind (`mix`, a bit per kind) nor where a workgroup has
-// fewer than eight tiles; and up to a feature per thread.
+// The shares cost 7 us a launch, so not where all features are of one kind (`mix`, a bit per kind, left empty where there are
+// fewer than kManyKeys keys); and up to a feature per thread.
 struct TileShares {
     uint32_t tmp[kSelBlock / 64], edge[2];
     int first;
@@ -303,7 +317,7 @@ struct TileRun {
     template <typename Weight>
     __device__ TileRun(const uint32_t *blk_off, int F, uint32_t mix, TileShares *sh, Weight &&weight) {
         const uint32_t nt = blk_off[F];
-        if ((mix & (mix - 1u)) == 0u || F > kSelBlock || nt / 8u < gridDim.x) {
+        if ((mix & (mix - 1u)) == 0u || F > kSelBlock) {
             equal(blk_off, F);
             return;
         }
@@ -377,7 +391,8 @@ __device__ inline void for_each_key(const uint32_t *p, uint64_t k0, uint64_t k1,
             if (i + c < k1) fn(p[i + c]);
 }
 
-__global__ __launch_bounds__(kSelBlock) void sel_count_kernel(const uint32_t *__restrict__ keys,
+// (80 scalar registers: as for sel_sample_kernel.  1M x 28, 34.4 us, with 89 38.4.)
+__global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) void sel_count_kernel(const uint32_t *__restrict__ keys,
                                                               const uint64_t *__restrict__ seg_off,
                                                               const uint32_t *__restrict__ blk_off, int F, SelArrays A,
                                                               uint64_t work_tuned) {
@@ -409,16 +424,27 @@ __global__ __launch_bounds__(kSelBlock) void sel_count_kernel(const uint32_t *__
         uint32_t *mine = counters + (threadIdx.x % copies) * nc;
         if (discrete) {
             uint8_t *mixed = A.mixed + (uint64_t)f * kDiscreteCells;
-            for_each_key(p, k0, k1, [&](uint32_t k) {
-                if (k == kMissingKey) return;
+            auto add = [&](uint32_t k, uint32_t times) __attribute__((always_inline)) {
                 const uint32_t c = cell_of(seg, k);
                 uint32_t r = rep[c];
                 if (r != k) {
                     if (r == kMissingKey) r = atomicCAS(&rep[c], kMissingKey, k);
                     if (r != kMissingKey && r != k) mixed[c] = 1;   // (any thread, any number of times)
                 }
-                atomicAdd(&mine[c], 1u);
+                atomicAdd(&mine[c], times);
+            };
+            // The frequent key (none: kMissingKey) is counted in a register: lanes that hold it would take turns on one counter.  The
+            // table of TileRun, count: 1.46 ms without, 1.32 with it.  An eighth of the sample: below it few lanes of a copy meet.
+            const uint32_t at = A.kind[f] >> kKindHotShift, hot = at ? A.sample[(uint64_t)f * A.sample_cap + at - 1u] : kMissingKey;
+            uint32_t times = 0;
+            for_each_key(p, k0, k1, [&](uint32_t k) {
+                if (k == hot) ++times;
+                else if (k != kMissingKey) add(k, 1u);
             });
+            if (hot != kMissingKey) {
+                for (int o = 32; o > 0; o >>= 1) times += (uint32_t)__shfl_xor((int)times, o);
+                if ((threadIdx.x & 63) == 0 && times) add(hot, times);
+            }
         } else {
             for_each_key(p, k0, k1, [&](uint32_t k) {
                 if (k != kMissingKey) atomicAdd(&mine[cell_of(seg, k)], 1u);
@@ -450,7 +476,7 @@ __global__ __launch_bounds__(kSelBlock) void sel_pick_kernel(const uint64_t *__r
             A.n_slots[f] = 0;
             A.mode[f] = kSelSorted;
             A.flag[0] = 1;
-            atomicOr(&A.mix[1], 2u);
+            if (seg_off[gridDim.x] >= kManyKeys) atomicOr(&A.mix[1], 2u);
         }
         return;
     }
@@ -554,7 +580,7 @@ __global__ __launch_bounds__(kSelBlock) void sel_pick_kernel(const uint64_t *__r
     if (tid == 0) {
         A.kind[f] = (discrete ? kKindDiscrete : 0u) | (collect ? 0u : kKindNoCollect);
         A.n_slots[f] = n_slots;
-        atomicOr(&A.mix[1], n_slots && collect ? 1u : 2u);
+        if (seg_off[gridDim.x] >= kManyKeys) atomicOr(&A.mix[1], n_slots && collect ? 1u : 2u);
         A.mode[f] = order ? kSelOrder : kSelDistinct;
         present[f] = m;
     }

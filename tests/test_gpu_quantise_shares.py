@@ -21,7 +21,8 @@ def ctxs():
     srt.close()
 
 
-# n numbers, c categories (no keys collected), d dates (sorted: no work in either kernel), m missing throughout
+# n numbers, c categories (no keys collected), d dates (sorted: no work in either kernel), m missing throughout; categories with one
+# frequent key, counted by itself: h alone in its cell, x beside its neighbours among the floats, v an eighth of the column
 @pytest.mark.parametrize("n,F,kinds", [
     (600_000, 32, "n"),
     (600_011, 32, "c"),              # nothing to collect
@@ -31,6 +32,8 @@ def ctxs():
     (300_007, 64, "dnd"),
     (120_000, 200, 65 * "c" + "n" + 133 * "d" + "n"),
     (130_000, 128, "mndc"),          # fewer tiles than eight a workgroup on a large device
+    (600_011, 32, "hxvn"),
+    (5_001, 6, "hxv"),
     (40_000, 1024, 1023 * "c" + "n"),
     (40_000, 1025, 1000 * "c" + 25 * "n"),   # more columns than threads
 ])
@@ -44,6 +47,13 @@ def test_shares(ctxs, n, F, kinds):
             X[:, f] = torch.floor(3 * X[:, f].abs())
         elif k == "d":
             X[:, f] = 20_150_000 + torch.floor(400 * X[:, f])
+        elif k == "h":
+            X[:, f] = torch.where(X[:, f] < 1.3, 0.0, torch.floor(30 * X[:, f]))
+        elif k == "x":
+            X[:, f] = 1.0 + torch.floor(3 * X[:, f].abs()) * 2.0 ** -23
+            X[n // 5: n // 4, f] = float("nan")
+        elif k == "v":
+            X[:, f] = torch.floor(8 * torch.rand(n, device="cuda", generator=gen))
         elif k == "m":
             X[:, f] = float("nan")
     a, b = (c.quantise_packed(X, max_bins=64) for c in ctxs)
