@@ -206,7 +206,8 @@ struct PlanJob {             // what the children of partition job k need of its
 };
 // How the rows of a level's built nodes are cut into histogram jobs: pieces of at most rows_per_job rows of a node, a job
 // per piece and column tile.  Short pieces spread the rows over the chip, long ones merge fewer histograms into HBM (two
-// 64-bit atomics per bin, some 1.2*10^11 a second over the whole chip).  Both sides in rows a compute unit could have
+// 64-bit atomics per bin; merge_bins has made them 2.5 times as fast since these weights were fitted, but with the second one
+// halved or quartered 1M x 28 x 256 is slower, not faster).  Both sides in rows a compute unit could have
 // added instead (an element takes one 0.165 ns, whatever the kernel's form):
 //   adding   the busiest compute unit's share: the longest piece, or the average job times the jobs of a compute unit;
 //   merging  jobs * merge, merge = 0.15 * bins (hist_rule; a node of one piece stores its bins: a quarter of that).

@@ -19,7 +19,7 @@
 // two rows ahead.
 //
 // Two forms of the accumulated LDS word, as in kernels_hist8.hip:
-//   general     [ g : 34 | h : 30 ], returning atomics in groups of up to 16 whose returned words are tested
+//   general     [ g : 34 | h : 30 ], returning atomics in groups of four whose returned words are tested
 //               together for a carry out of h or a wrap of g, side counter per bin;
 //   uniform h   [ g : 46 | rows : 18 ], non-returning atomics, nothing tested (at most 2^18 - 1 rows per job),
 //               8 bytes of LDS per bin instead of 12.

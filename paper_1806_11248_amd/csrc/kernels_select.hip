@@ -588,7 +588,9 @@ __global__ __launch_bounds__(kSelBlock) void sel_pick_kernel(const uint64_t *__r
 
 // ---- collect ----------------------------------------------------------------------------------------------------
 constexpr int kCollectPer = 16;   // keys per thread and step
-__global__ __launch_bounds__(kSelBlock) void sel_collect_kernel(const uint32_t *__restrict__ keys,
+// (64 vector and 80 scalar registers at most, so that two workgroups fit a compute unit and one reads while the other waits at a
+// barrier: 115M rows of 5 columns of numbers and 8 of categories 0.885 -> 0.578 ms, 1M x 28 numbers 59 -> 44 us.)
+__global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80), amdgpu_waves_per_eu(8))) void sel_collect_kernel(const uint32_t *__restrict__ keys,
                                                                 const uint64_t *__restrict__ seg_off,
                                                                 const uint32_t *__restrict__ blk_off, int F, int B,
                                                                 SelArrays A, uint32_t *__restrict__ out) {
