@@ -68,25 +68,21 @@ double fixed_scale(float vmax, int top) {
 struct HistPlan {
     int ft_max, n_ftiles, ft;
 };
-// The kernels consume a row slice in register windows of E whole elements and issue an atomic for
-// every slot of a window, used or not.  More tiles than the LDS budget demands cost a pass over the
-// gradient pairs each, so they are taken only when they save at least a fifth of the slots.
-bool plan_tiles(const gbt_ctx *ctx, int F, int B, int bits, HistPlan *p, int64_t n_rows = 0) {
-    const int E = gbt_histw_window(std::max(bits, 1));   // (16 of 8 bits)
-    p->ft_max = std::min(gbt_hist_feature_tile(ctx, F, B, n_rows), GBT_HISTW_WINDOWS * E);
+// Column tiles (gbt_tile_columns), at most four windows wide.  (That limit holds for bytes as well, whose general form has no
+// windows: 5M x 70 x 130 bins, root, one tile 358 us, two 284.)  The windows' kernel takes no tile that leaves a compute unit room for
+// one workgroup only, whatever gbt_hist_feature_tile allows (rounds, one tile and two: 6M x 60 x 7 bits 1924 and 1830 us, general pairs
+// 2455 and 1960; 10M x 50 x 9 bits, tiles of 41 and 9 3858, of 25 3096).  gathered: rows are read by id from a matrix of so many bytes.
+bool plan_tiles(const gbt_ctx *ctx, int F, int B, int bits, HistPlan *p, int64_t n_rows = 0, double gathered = 0.0) {
+    p->ft_max = std::min(gbt_hist_feature_tile(ctx, F, B, n_rows), GBT_HISTW_WINDOWS * gbt_histw_window(std::max(bits, 1)));
     if (p->ft_max < 1) return false;
-    const int nt_min = (F + p->ft_max - 1) / p->ft_max;
-    int64_t best_slots = -1;
-    for (int nt = nt_min; nt <= nt_min + 8 && nt <= F; ++nt) {
-        const int ft = (F + nt - 1) / nt;
-        const int64_t slots = (int64_t)nt * ((ft + E - 1) / E) * E;
-        if (best_slots < 0 || slots * 5 <= best_slots * 4) {
-            best_slots = slots;
-            p->n_ftiles = nt;
-            p->ft = ft;
-        }
-    }
+    if (bits != 8) p->ft_max = std::min(p->ft_max, std::max(1, (80 * 1024 / ((B + 1) * 12) - 1) | 1));   // (an odd stride, 160 KB on a unit)
+    p->ft = gbt_tile_columns(F, bits, p->ft_max, gathered);
+    p->n_ftiles = (F + p->ft - 1) / p->ft;
     return true;
+}
+// The bytes of a matrix that growth gathers rows from (0: it moves them): rows too wide to move are listed by id, see grow_path.
+double gathered_bytes(const gbt_ctx *ctx, int64_t n, int F, int bits) {
+    return ((int64_t)F * bits + 31) / 32 > ctx->move_max_words ? (double)n * F * bits / 8.0 : 0.0;
 }
 
 // The jobs of one or several nodes; rows_per_job > 0.
@@ -787,7 +783,7 @@ static int32_t hist_uniform(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, 
                             const int32_t *gq, int64_t *hist_out, HistJob *dev_jobs, RootFix *fix, bool uniform_h,
                             int32_t hq_uniform) {
     HistPlan pl;
-    GBT_REQUIRE(ctx, plan_tiles(ctx, F, B, bits, &pl, n_rows), GBT_EUNSUPPORTED,
+    GBT_REQUIRE(ctx, plan_tiles(ctx, F, B, bits, &pl, n_rows, row_idx ? (double)n * F * bits / 8.0 : 0.0), GBT_EUNSUPPORTED,
                 "max_bins = %d: one feature's bins (%d bytes) exceed the LDS budget", B, B * 16);
     GBT_HIP(ctx, gbt_launch_fill_u64(ctx->stream, (uint64_t *)hist_out, 0, (int64_t)F * B * 2));
     if (n_rows == 0) return GBT_OK;
@@ -1161,7 +1157,7 @@ extern "C" int32_t gbt_grow_tree_form(gbt_ctx *ctx, int64_t n, int32_t F, int32_
     GBT_REQUIRE(ctx, n >= 1 && F >= 1 && bits >= 1 && bits <= GBT_MAX_BITS && max_bins >= 2 && max_depth >= 0 && max_depth <= kMaxDepth,
                 GBT_EINVAL, "bad shape");
     HistPlan pl;
-    GBT_REQUIRE(ctx, plan_tiles(ctx, F, max_bins, bits, &pl, n), GBT_EUNSUPPORTED,
+    GBT_REQUIRE(ctx, plan_tiles(ctx, F, max_bins, bits, &pl, n, gathered_bytes(ctx, n, F, bits)), GBT_EUNSUPPORTED,
                 "max_bins = %d: one feature's bins exceed the LDS budget", max_bins);
     const GrowForm f = depthwise_form(ctx, pl, n, F, bits, max_bins, max_depth, track_rows != 0);
     return f.path + (f.planned ? GBT_GROW_PLANNED : 0);
@@ -1205,7 +1201,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
                                    : grow_layout(n, F, bits, B, max_depth);
     GBT_REQUIRE(ctx, workspace_bytes >= L.total, GBT_ENOMEM, "workspace %zu < %zu bytes", workspace_bytes, L.total);
     HistPlan pl;
-    GBT_REQUIRE(ctx, plan_tiles(ctx, F, B, bits, &pl, n), GBT_EUNSUPPORTED,
+    GBT_REQUIRE(ctx, plan_tiles(ctx, F, B, bits, &pl, n, gathered_bytes(ctx, n, F, bits)), GBT_EUNSUPPORTED,
                 "max_bins = %d: one feature's bins exceed the LDS budget", B);
 
     char *ws = (char *)workspace;

@@ -340,6 +340,43 @@ constexpr int gbt_histw_window(int bits) {
     const int e = (128 - first) / bits;
     return e < 32 ? e : 32;
 }
+// What a tile of ft of the F columns costs a row, in slots (an element's field, address and atomic).
+//   bytes        every slot of a window of sixteen, used or not (hist_b8_kernel)
+//   other widths a lane takes a window's share of a row, which costs it about ten slots beside its columns; where all windows are
+//                full nothing asks whether a column is there, a third less.  Not less than the line of 128 bytes that a tile
+//                reads of a longer row; and where rows are gathered (gathered: the bytes of their matrix) from past the last
+//                cache, that line comes from HBM for every tile.
+// us of a root, general pairs: 1M x 100 x 6 bits in two tiles of 50 118, four of 25 88, five of 20 (full) 53; 1M x 52 x 9 bits, three of
+// 18 84, four of 13 (full) 53; 500,000 x 1000 x 6 bits, 13 of 77 310, 25 of 40 (full) 242, 50 of 20 (full, a line each) 342.  A round
+// that gathers, equal hessians: 10M x 50 x 9 bits (560 MB), four tiles of 13 3514, two of 25 3096; a third of its rows 1166 and (20) 1208.
+constexpr double kLastCacheBytes = 256e6;
+inline double gbt_tile_cost(int ft, int F, int bits, double gathered) {
+    const int E = gbt_histw_window(bits), windows = ft <= E ? 1 : ft <= 2 * E ? 2 : GBT_HISTW_WINDOWS;
+    if (bits == 8) return (ft + E - 1) / E * E;
+    const double slots = ft == windows * E ? windows * (10 + E) * 2.0 / 3.0 : windows * (10 + (ft + windows - 1) / windows);
+    const double line = 35.0 * std::min(1.0, (double)F * bits / 2048.0);
+    return (slots > line ? slots : line) + (gathered > kLastCacheBytes ? 30.0 : 0.0);
+}
+// Columns of a tile, ft_max at most (the last tile has what is left): of the even splits, and of tiles of one, two or four full
+// windows, those that cost a row least.  Bytes: more tiles than needed cost a pass over the pairs each, and are taken where they
+// save a fifth of the slots (with full windows only, 1M x 50 77 instead of 69 us).
+inline int gbt_tile_columns(int F, int bits, int ft_max, double gathered) {
+    int best = 0;
+    double best_cost = 0.0;
+    auto consider = [&](int ft) {
+        if (ft > ft_max) return;
+        const int rest = F % ft;
+        const double cost = (double)(F / ft) * gbt_tile_cost(ft, F, bits, gathered) +
+                            (rest ? gbt_tile_cost(bits == 8 ? ft : rest, F, bits, gathered) : 0.0);
+        if (best && (bits == 8 ? cost * 5.0 > best_cost * 4.0 : cost >= best_cost)) return;
+        best = ft;
+        best_cost = cost;
+    };
+    const int nt_min = (F + ft_max - 1) / ft_max;
+    for (int nt = nt_min; nt <= nt_min + 8 && nt <= F; ++nt) consider((F + nt - 1) / nt);
+    for (int windows = GBT_HISTW_WINDOWS; bits != 8 && windows >= 1; windows /= 2) consider(windows * gbt_histw_window(bits));
+    return best;
+}
 int gbt_histw_max_rows(bool uniform_h);
 hipError_t gbt_launch_histw(gbt_ctx *ctx, const uint32_t *packed, int bits, int64_t stride_bits, int64_t n_words,
                             int64_t n, int B, uint32_t missing, const uint32_t *row_idx, const int32_t *gq,

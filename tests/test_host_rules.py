@@ -35,6 +35,8 @@ API long long jobs_over_bound(int num_cu, int per_cu, int tiles, long long max_r
     return over;
 }
 
+API int tile_columns(int F, int bits, int ft_max, double gathered) { return gbt_tile_columns(F, bits, ft_max, gathered); }
+API int window(int bits) { return gbt_histw_window(bits); }
 API int eval_chunks(int F, int n_nodes, long long budget) { return gbt_eval_chunks(F, n_nodes, (size_t)budget); }
 API long long eval_records_max(long long n_nodes) { return gbt_eval_records_max(n_nodes); }
 API long long split_bytes() { return (long long)sizeof(gbt_split); }
@@ -184,3 +186,39 @@ def test_bound_of_a_levels_evaluation_records(rules):
                 assert n_nodes * rules.eval_chunks(F, n_nodes, 1 << 60) <= room, (level_nodes, n_nodes, F)
                 tight = 3 * n_nodes * size
                 assert n_nodes * rules.eval_chunks(F, n_nodes, tight) * size <= tight
+
+
+@pytest.mark.parametrize("bits", [b for b in range(1, 17) if b != 8])
+def test_column_tiles_by_the_slots_the_kernel_issues(rules, bits):
+    """A tile costs the slots of its lanes, one, two or four, a third less where all are full, and ten per lane; a long row's
+    tile at least its line, and one more where the rows come from HBM.  No even split up to eight tiles past the fewest, nor full
+    windows, cost less than the tiles taken."""
+    rules.tile_columns.argtypes = [C.c_int] * 3 + [C.c_double]
+    E = rules.window(bits)
+
+    def cost(F, ft, far):
+        def tile(t):
+            lanes = 1 if t <= E else 2 if t <= 2 * E else 4
+            each = -(-t // lanes)
+            slots = lanes * (10 + each) * (2 / 3 if t == lanes * E else 1)
+            return max(slots, 35 * min(1, F * bits / 2048)) + 30 * far
+        return F // ft * tile(ft) + (tile(F % ft) if F % ft else 0)
+
+    for F in [*range(1, 420), 700, 1000, 2000, 5001, 1 << 20]:
+        for ft_max in {min(F, m) for m in (1, 2, 5, E - 1, E, E + 7, 2 * E, 4 * E)} - {0}:
+            least = -(-F // ft_max)
+            others = [-(-F // nt) for nt in range(least, min(least + 8, F) + 1)] + [w * E for w in (1, 2, 4) if w * E <= ft_max]
+            for far in (False, True):
+                ft = rules.tile_columns(F, bits, ft_max, 1e9 * far)
+                assert 1 <= ft <= ft_max <= 4 * E
+                assert cost(F, ft, far) <= min(cost(F, o, far) for o in others) * (1 + 1e-12), (F, ft_max, ft)
+
+
+def test_column_tiles_of_known_shapes(rules):
+    rules.tile_columns.argtypes = [C.c_int] * 3 + [C.c_double]
+    # full windows with a ragged last tile: 36 and 52 columns of 9 bits, 100 of 6, a wide matrix
+    assert [rules.tile_columns(*a, 0.0) for a in ((36, 9, 20), (52, 9, 20), (100, 6, 78), (2000, 6, 78))] == [13, 13, 20, 40]
+    # gathered from past the caches: half as many tiles
+    assert [rules.tile_columns(50, 9, 25, b) for b in (0.0, 168e6, 560e6)] == [13, 13, 25]
+    # bytes: more tiles than needed only where they save a fifth of the slots
+    assert [rules.tile_columns(*a, 0.0) for a in ((33, 8, 19), (50, 8, 19), (70, 8, 64), (400, 8, 38))] == [11, 13, 35, 31]
