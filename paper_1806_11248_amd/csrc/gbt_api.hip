@@ -153,12 +153,24 @@ uint32_t pick_rows_per_job(const PlanHistRule &r, const std::vector<BuiltNode> &
     }
     return (uint32_t)gbt_piece_candidate(r, rows, best);
 }
-// Threads of a histogram workgroup: 1024 where the launch is about one workgroup per compute unit (us per round with 512 and
+// Threads of a histogram workgroup: 1024 where the launch is at most one workgroup per compute unit (us per round with 512 and
 // 1024: 1M x 28 bytes 606 and 572, 50,000 x 500 x 6 bits 465 and 444), else the context's 512 (500,000 x 2000 x 6 bits 5390 and 5710).
-int hist_block(const gbt_ctx *ctx, const PlanHistRule &r, int64_t rows) {
-    if (!ctx->hist_block_auto) return ctx->hist_block;
-    const double jobs = (double)rows * r.tiles / (double)gbt_piece_candidate(r, rows, kPieceCandidates / 2);
-    return jobs <= r.num_cu ? 1024 : ctx->hist_block;
+// The jobs as they are cut, not as a middling length would cut them: root of 666,666 x 150 bytes 97 and 74, 250,000 x 400 x 7 bits 103, 83.
+int hist_block(const gbt_ctx *ctx, int64_t jobs) { return ctx->hist_block_auto && jobs <= ctx->num_cu ? 1024 : ctx->hist_block; }
+// The jobs of `count` nodes of `rows` rows in all, as equal as they can be: what a level planned on the device is taken to have.
+int64_t equal_jobs(const PlanHistRule &r, int64_t rows, int64_t count) {
+    const int64_t len = (rows + count - 1) / count;
+    int64_t best = 0;
+    double best_cost = 0.0;
+    for (int c = 0; c < kPieceCandidates; ++c) {
+        const int64_t length = gbt_piece_candidate(r, rows, c), pieces = (len + length - 1) / length * count;
+        const double cost = gbt_piece_cost(r, rows, length, pieces, r.exclusive_ok && len <= length ? count : 0, len);
+        if (c == 0 || cost < best_cost) {
+            best = pieces * r.tiles;
+            best_cost = cost;
+        }
+    }
+    return best;
 }
 
 // Best of one node's per-chunk split records: largest gain, earliest chunk on ties.
@@ -839,7 +851,7 @@ static int32_t hist_uniform(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, 
     else
         GBT_HIP(ctx, gbt_launch_hist(ctx, packed, bits, (int64_t)F * bits, gbt_packed_words(n, F, bits), n, B,
                                      (uint32_t)missing_sym, row_idx, gq, hist_out, dev_jobs, (int)jobs.size(), pl.ft,
-                                     uni_w, hq_uniform, hist_block(ctx, rule, n_rows)));
+                                     uni_w, hq_uniform, hist_block(ctx, (int64_t)jobs.size())));
     gbt_prof_end(ctx);
     return GBT_OK;
 }
@@ -1467,7 +1479,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
             GBT_HIP(ctx, gbt_launch_hist(ctx, ids ? packed : rows.sym, bits, ids ? (int64_t)row_bits : rows.stride_bits,
                                          ids ? gbt_packed_words(n, F, bits) : rows.n_words, n, B, (uint32_t)missing_sym,
                                          ids ? rows.id : nullptr, ids ? gq : rows.gq, pool, g.v.hjobs, (int)jobs, pl.ft, uni_w,
-                                         hq_w, hist_block(ctx, g.rule, n / 2), &g.v.levels[d + 1].n_hist_jobs));
+                                         hq_w, hist_block(ctx, equal_jobs(g.rule, n / 2, (int64_t)1 << d)), &g.v.levels[d + 1].n_hist_jobs));
             gbt_prof_end(ctx);
             return GBT_OK;
         };
@@ -2305,12 +2317,12 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
                     GBT_HIP(ctx, gbt_launch_hist(ctx, packed, bits, row_bits, gbt_packed_words(n, F, bits), n, B,
                                                  (uint32_t)missing_sym, W[wnext].id, gq, pool,
                                                  (const HistJob *)(ws + L.jobs), (int)nj, pl.ft, uni_w, hq_uniform,
-                                                 hist_block(ctx, rule, built_rows)));
+                                                 hist_block(ctx, (int64_t)hjobs.size())));
                 else
                     GBT_HIP(ctx, gbt_launch_hist(ctx, W[wnext].sym, bits, W[wnext].stride_bits, W[wnext].n_words, n, B,
                                                  (uint32_t)missing_sym, nullptr, W[wnext].gq, pool,
                                                  (const HistJob *)(ws + L.jobs), (int)nj, pl.ft, uni_w, hq_uniform,
-                                                 hist_block(ctx, rule, built_rows)));
+                                                 hist_block(ctx, (int64_t)hjobs.size())));
                 gbt_prof_end(ctx);
             }
         }
