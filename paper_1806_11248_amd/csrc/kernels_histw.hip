@@ -63,9 +63,15 @@ __device__ __forceinline__ void pkw_check(uint32_t side_addr, unsigned long long
 }
 
 typedef uint32_t w_u32x4 __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t w_u32x2 __attribute__((ext_vector_type(2), aligned(1)));
 
 // BITS: of a symbol.  CLAMP: a symbol may be larger than the last row of the LDS table and is counted there.
-template <int BITS, bool LIST, bool UNI, bool CLAMP>
+// SHORT: a row's columns are at most kShortBits bits, one window, which one load of eight bytes holds wherever it begins; it is turned to
+// the lane's column in registers.  Wide symbols have such tiles, for their bins fill the LDS, and read little else than what the L1
+// has to look up for them: with two loads of sixteen bytes and with this, root of 1M x 150 columns of 4096 bins 1661 and 948 us (a tile
+// per column), of 462,962 x 324 of 2048 976 and 677, of 1M x 20 of 4096 122 and 88.  (Narrower symbols have tiles of more than 57 bits.)
+constexpr int kShortBits = 57, kShortFrom = 10;
+template <int BITS, bool LIST, bool UNI, bool CLAMP, bool SHORT>
 __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
     const uint32_t *__restrict__ packed, int64_t n_words, int64_t stride_bits, int64_t n, int B, int rows_lds, int fs,
     uint32_t missing, const uint32_t *__restrict__ row_idx, const int2 *__restrict__ gq,
@@ -99,7 +105,8 @@ __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
     const int most = (ft + (1 << log_win) - 1) >> log_win;                            // of any lane
     const int start = (int)((threadIdx.x & 63) >> log_win) % cnt, until = cnt - start;   // slots before its first column
     const int n_step = (int)(blockDim.x >> log_win);
-    const int64_t last_at = n_words * 4 - 16;   // the last byte from which sixteen can be read (the launcher has made sure of one)
+    using Words = std::conditional_t<SHORT, w_u32x2, w_u32x4>;
+    const int64_t last_at = n_words * 4 - (int64_t)sizeof(Words);   // the last byte from which they can be read (the launcher has made sure of one)
     const char *bytes = (const char *)packed;
     uint32_t keep[4];   // the bits that come before the first column
 #pragma unroll
@@ -112,7 +119,7 @@ __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
         const uint64_t pos = (uint64_t)job.row_begin + i;
         return LIST ? (uint64_t)row_idx[pos] : pos;
     };
-    const uint64_t lane_bit = ((uint64_t)job.f0 + (uint32_t)(c0 + start)) * BITS;
+    const uint64_t lane_bit = ((uint64_t)job.f0 + (uint32_t)(SHORT ? c0 : c0 + start)) * BITS;
     const int back = cnt * BITS;   // from the first slot's bit to where the window's first column would follow its last
     // Sixteen bytes from the byte of bit `at` on.  What lies outside the buffer holds no bit that is used: the sixteen bytes
     // nearest to it are read, and put in their places when they are used.
@@ -133,16 +140,27 @@ __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
         for (int j = 0; j < 3; ++j) W[j] = BITS % 8 == 0 ? x[j] : __builtin_amdgcn_alignbit(x[j + 1], x[j], sh);
         W[3] = BITS % 8 == 0 ? x[3] : x[3] >> sh;
     };
-    w_u32x4 wa, wb;   // the window on its way: from the lane's start on, and from its first column on (in its place)
+    auto turned = [&](const w_u32x2 &v, int64_t at, int off, uint32_t (&W)[4]) __attribute__((always_inline)) {
+        uint64_t y = (((uint64_t)v[1] << 32) | v[0]) >> (8 * off + (int)(at & 7));
+        y &= (1ull << back) - 1ull;
+        y = (y >> (start * BITS)) | (y << (until * BITS));
+        W[0] = (uint32_t)y;
+        W[1] = (uint32_t)(y >> 32);
+        W[2] = W[3] = 0;
+    };
+    Words wa, wb;   // the window on its way: from the lane's start on, and from its first column on (in its place); SHORT: the one
     int64_t at = 0;
     int offa = 0, offb = 0;
     auto issue = [&](uint64_t r) __attribute__((always_inline)) {
         at = (int64_t)(r * (uint64_t)stride_bits + lane_bit);
-        const int64_t a = byte_in(at), b = byte_in(at - back);
-        wa = *(const w_u32x4 *)(bytes + a);
-        wb = *(const w_u32x4 *)(bytes + b);
+        const int64_t a = byte_in(at);
+        wa = *(const Words *)(bytes + a);
         offa = (int)((at >> 3) - a);
-        offb = (int)(((at - back) >> 3) - b);
+        if constexpr (!SHORT) {
+            const int64_t b = byte_in(at - back);
+            wb = *(const Words *)(bytes + b);
+            offb = (int)(((at - back) >> 3) - b);
+        }
     };
     // (an opaque base: one register and an instruction's own offset, not sums made anew for every slot)
     uint32_t base = lds_base + 8u * (uint32_t)(c0 + start), base2 = base - 8u * (uint32_t)cnt;
@@ -212,14 +230,19 @@ __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
             const unsigned long long addv =
                 UNI ? ((unsigned long long)(long long)q.x << kWRowsShift) + 1ull : pack_pair(q);
             const uint32_t hq = (uint32_t)q.y;
-            uint32_t W[4], V[4];
-            aligned(wa, at, offa, W);
-            aligned(wb, at - back, offb, V);
+            uint32_t W[4];
+            if constexpr (SHORT) {
+                turned(wa, at, offa, W);
+            } else {
+                uint32_t V[4];
+                aligned(wa, at, offa, W);
+                aligned(wb, at - back, offb, V);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) W[j] = (W[j] & keep[j]) | (V[j] & ~keep[j]);
+                for (int j = 0; j < 4; ++j) W[j] = (W[j] & keep[j]) | (V[j] & ~keep[j]);
+            }
             issue(next);
             if (ok_row) {
-                if (most == E && ft == E << log_win) add(W, addv, hq, std::true_type());
+                if (!SHORT && most == E && ft == E << log_win) add(W, addv, hq, std::integral_constant<bool, !SHORT>());
                 else add(W, addv, hq, std::false_type());
             }
             if (!more) break;
@@ -251,7 +274,7 @@ __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
 
 struct WArgs {
     hipStream_t s;
-    int n_jobs, block;
+    int n_jobs, block, max_ft;
     size_t lds;
     const uint32_t *packed;
     int64_t n_words, stride_bits, n;
@@ -264,27 +287,33 @@ struct WArgs {
     int32_t hq_uniform;
     const uint32_t *n_jobs_dev;
 };
-template <int BITS, bool LIST, bool UNI, bool CLAMP>
+template <int BITS, bool LIST, bool UNI, bool CLAMP, bool SHORT>
 hipError_t launch_w(const WArgs &a) {
+    auto *const kernel = hist_bits_kernel<BITS, LIST, UNI, CLAMP, SHORT>;
     GbtLdsGuard lds_guard(a.lds);
     if (lds_guard.needed) {
-        hipError_t e = hipFuncSetAttribute((const void *)hist_bits_kernel<BITS, LIST, UNI, CLAMP>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds);
+        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds);
         if (e != hipSuccess) return e;
     }
-    hist_bits_kernel<BITS, LIST, UNI, CLAMP><<<a.n_jobs, a.block, a.lds, a.s>>>(a.packed, a.n_words, a.stride_bits, a.n, a.B,
-                                                                                a.rows_lds, a.fs, a.missing, a.row_idx, a.gq, a.pool,
-                                                                                a.jobs, a.hq_uniform, a.n_jobs_dev);
+    kernel<<<a.n_jobs, a.block, a.lds, a.s>>>(a.packed, a.n_words, a.stride_bits, a.n, a.B, a.rows_lds, a.fs, a.missing, a.row_idx, a.gq,
+                                              a.pool, a.jobs, a.hq_uniform, a.n_jobs_dev);
     return hipGetLastError();
 }
-template <int BITS, bool CLAMP>
+template <int BITS, bool CLAMP, bool SHORT>
 hipError_t pick_w2(const WArgs &a, bool uni) {
-    if (a.row_idx) return uni ? launch_w<BITS, true, true, CLAMP>(a) : launch_w<BITS, true, false, CLAMP>(a);
-    return uni ? launch_w<BITS, false, true, CLAMP>(a) : launch_w<BITS, false, false, CLAMP>(a);
+    if (a.row_idx) return uni ? launch_w<BITS, true, true, CLAMP, SHORT>(a) : launch_w<BITS, true, false, CLAMP, SHORT>(a);
+    return uni ? launch_w<BITS, false, true, CLAMP, SHORT>(a) : launch_w<BITS, false, false, CLAMP, SHORT>(a);
+}
+template <int BITS, bool CLAMP>
+hipError_t pick_w1(const WArgs &a, bool uni) {
+    if constexpr (BITS >= kShortFrom) {
+        if (a.max_ft * BITS <= kShortBits) return pick_w2<BITS, CLAMP, true>(a, uni);
+    }
+    return pick_w2<BITS, CLAMP, false>(a, uni);
 }
 template <int BITS>
 hipError_t pick_w(const WArgs &a, bool uni) {
-    return a.rows_lds < (1 << BITS) ? pick_w2<BITS, true>(a, uni) : pick_w2<BITS, false>(a, uni);
+    return a.rows_lds < (1 << BITS) ? pick_w1<BITS, true>(a, uni) : pick_w1<BITS, false>(a, uni);
 }
 }  // namespace
 
@@ -303,7 +332,7 @@ hipError_t gbt_launch_histw(gbt_ctx *ctx, const uint32_t *packed, int bits, int6
     if (lds_of(fs) > ctx->lds_per_block / 2) fs = max_ft | 1;
     if (lds_of(fs) > ctx->lds_per_block) fs = max_ft;
     const size_t lds = lds_of(fs);
-    const WArgs a{ctx->stream, n_jobs, block, lds, packed, n_words, stride_bits, n, B, rows_lds, fs, missing, row_idx,
+    const WArgs a{ctx->stream, n_jobs, block, max_ft, lds, packed, n_words, stride_bits, n, B, rows_lds, fs, missing, row_idx,
                   (const int2 *)gq, hist_pool, jobs, hq_uniform, n_jobs_dev};
     switch (bits) {
         case 1: return pick_w<1>(a, uniform_h);
