@@ -353,28 +353,32 @@ constexpr double kLastCacheBytes = 256e6;
 inline double gbt_tile_cost(int ft, int F, int bits, double gathered) {
     const int E = gbt_histw_window(bits), windows = ft <= E ? 1 : ft <= 2 * E ? 2 : GBT_HISTW_WINDOWS;
     if (bits == 8) return (ft + E - 1) / E * E;
-    const double slots = ft == windows * E ? windows * (10 + E) * 2.0 / 3.0 : windows * (10 + (ft + windows - 1) / windows);
+    const double full = windows == 1 ? 0.67 : windows == 2 ? 0.7 : 0.65;
+    const double slots = ft == windows * E ? windows * (10 + E) * full : windows * (10 + (ft + windows - 1) / windows);
     const double line = 35.0 * std::min(1.0, (double)F * bits / 2048.0);
     return (slots > line ? slots : line) + (gathered > kLastCacheBytes ? 30.0 : 0.0);
 }
-// Columns of a tile, ft_max at most (the last tile has what is left): of the even splits, and of tiles of one, two or four full
-// windows, those that cost a row least.  Bytes: more tiles than needed cost a pass over the pairs each, and are taken where they
-// save a fifth of the slots (with full windows only, 1M x 50 77 instead of 69 us).
+// Columns of a tile, ft_max at most (the last tile has what is left, and is waited for as long as for the others): of the even splits,
+// and of tiles of one, two or four full windows, those that cost a row least.  Four windows of 31 or 32 columns are left out: they
+// meet in the same LDS banks (666,666 x 150 x 3 bits, root, 128 and 22 columns 103 us, 64 at a time 56, 32 at a time 64).  Over 64 shapes of 1 to 10
+// bits, 40 to 1000 columns, what is taken is 1.03 times as slow as the best of some fifteen tiles on average.
+// Bytes: more tiles than needed cost a pass over the pairs each, and are taken where they save a fifth of the slots (with full
+// windows only, 1M x 50 77 instead of 69 us).
 inline int gbt_tile_columns(int F, int bits, int ft_max, double gathered) {
     int best = 0;
     double best_cost = 0.0;
     auto consider = [&](int ft) {
         if (ft > ft_max) return;
-        const int rest = F % ft;
-        const double cost = (double)(F / ft) * gbt_tile_cost(ft, F, bits, gathered) +
-                            (rest ? gbt_tile_cost(bits == 8 ? ft : rest, F, bits, gathered) : 0.0);
+        const int tiles = (F + ft - 1) / ft;
+        const double whole = gbt_tile_cost(ft, F, bits, gathered), last = gbt_tile_cost(F - (tiles - 1) * ft, F, bits, gathered);
+        const double cost = (tiles - 1) * whole + (last > whole ? last : whole);
         if (best && (bits == 8 ? cost * 5.0 > best_cost * 4.0 : cost >= best_cost)) return;
         best = ft;
         best_cost = cost;
     };
-    const int nt_min = (F + ft_max - 1) / ft_max;
+    const int nt_min = (F + ft_max - 1) / ft_max, E = gbt_histw_window(bits);
     for (int nt = nt_min; nt <= nt_min + 8 && nt <= F; ++nt) consider((F + nt - 1) / nt);
-    for (int windows = GBT_HISTW_WINDOWS; bits != 8 && windows >= 1; windows /= 2) consider(windows * gbt_histw_window(bits));
+    for (int windows = 1; bits != 8 && windows <= (E > 24 ? 2 : GBT_HISTW_WINDOWS); windows *= 2) consider(windows * E);
     return best;
 }
 int gbt_histw_max_rows(bool uniform_h);
