@@ -113,15 +113,21 @@ void make_hist_jobs(std::vector<HistJob> &jobs, const std::vector<BuiltNode> &no
 // max_rows: what a job of the kernel may hold (2^21: its per-bin event counters are 16 bits wide; fewer where
 // it counts rows in a narrow field, gbt_histw_max_rows)
 constexpr int64_t kMinRowsPerJob = 256;
-PlanHistRule hist_rule(const gbt_ctx *ctx, const HistPlan &pl, int F, int B, int64_t max_rows) {
+PlanHistRule hist_rule(const gbt_ctx *ctx, const HistPlan &pl, int F, int B, int bits, int64_t max_rows) {
     PlanHistRule r;
     r.pieces_max = std::max<int64_t>(1, (int64_t)ctx->num_cu * ctx->hist_jobs_per_cu / std::max(1, pl.n_ftiles));
     r.min_rows = kMinRowsPerJob;
     r.max_rows = max_rows;
-    // (0.1, 0.2 and 0.3: within 3 %, 0.4: 10 % slower on the widest.)  In a tile of few columns a row costs its words and its pair more
-    // than its elements, and more bins than rows are not all met: us per call with the weight whole and so, 100,000 x 40 x 4096 bins 97
-    // and 65, a quarter of its rows 64 and 40, 1M x 20 x 4096 183 and 172; rounds of depth 7 over them 1175 and 1090, 2038 and 1730.
-    r.merge = 0.15 * B * ctx->hist_merge_ratio / 96.0 * std::min(1.0, pl.ft / 8.0);
+    // What a job's merge weighs against its rows.  In a tile of few columns a row costs its words and its pair more than its
+    // elements, so the bins' share shrinks with them.
+    //   bytes        0.15 of a row for a bin (0.1, 0.2 and 0.3: within 3 %, 0.4: 10 % slower on the widest; a quarter or half of it is
+    //                better on 150 columns and more, up to a fifth, and 10 % worse on 24).
+    //   other widths seven rows for the job and a 24th for a bin.  Roots, listed rows and trees of both forms over 136 shapes (1 to 12 bits,
+    //                5 to 2000 columns, 2 to 4096 bins) with k * (9 + bins / 20), geometric mean over the best of all: k = 1/6 1.086,
+    //                1/3 1.049, 1/2 1.033, 2/3 1.038, 1 1.030, 4/3 1.033, 8/3 1.070; the bytes' weight 1.058 (462,962 x 324 x 1024
+    //                bins, root, 441 us, with 7/9 of that family 223).
+    const double narrow = std::min(1.0, pl.ft / 8.0);
+    r.merge = (bits == 8 ? 0.15 * B * narrow : 7.0 + B * std::max(narrow, 0.25) / 24.0) * ctx->hist_merge_ratio / 96.0;
     r.num_cu = ctx->num_cu;
     r.tiles = (F + pl.ft - 1) / pl.ft;
     r.ft = pl.ft;
@@ -827,7 +833,7 @@ static int32_t hist_uniform(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, 
     std::vector<HistJob> jobs;
     const bool uni_w = uniform_h && !ctx->hist_runtime_bits;   // the kernels with a row-count form
     const std::vector<BuiltNode> all{BuiltNode{0, 0, (uint32_t)n_rows}};
-    const PlanHistRule rule = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(uni_w));
+    const PlanHistRule rule = hist_rule(ctx, pl, F, B, bits, gbt_histw_max_rows(uni_w));
     make_hist_jobs(jobs, all, F, pl, pick_rows_per_job(rule, all), ((uintptr_t)hist_out & 15u) == 0);
     // Without a caller workspace the job table is read straight from the pinned
     // staging, which the device can address; it is small (a few KB).
@@ -1043,7 +1049,7 @@ GrowForm depthwise_form(const gbt_ctx *ctx, const HistPlan &pl, int64_t n, int F
     GrowForm f{grow_path(ctx, F, bits, B, tracked, pl.n_ftiles), false};
     const int64_t cap = ((int64_t)1 << (max_depth + 1)) - 1;
     if (!ctx->plan || max_depth < 1 || cap > kPlanNodesMax || f.path == 0 || (f.path == 2 && n >= kPath2Rows)) return f;
-    const PlanHistRule most = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(true));   // (the limit that makes the most jobs)
+    const PlanHistRule most = hist_rule(ctx, pl, F, B, bits, gbt_histw_max_rows(true));   // (the limit that makes the most jobs)
     f.planned = gbt_plan_jobs_max(most, n, (int64_t)1 << (max_depth - 1)) * (int64_t)sizeof(HistJob) <= (int64_t)kUploadBytes;
     if (f.planned && f.path == 2) f.path = 1;
     return f;
@@ -1412,7 +1418,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
         g.v.min_gain = min_gain;
         const bool uni_w = uniform_h && !ctx->hist_runtime_bits;   // the kernels with a row-count form
         const int32_t hq_w = (int32_t)llrint((double)h_value * scale[1]);
-        g.rule = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(uni_w));
+        g.rule = hist_rule(ctx, pl, F, B, bits, gbt_histw_max_rows(uni_w));
         g.max_depth = max_depth;
         g.F = F;
         g.B = B;
@@ -2289,7 +2295,7 @@ static int32_t grow_impl(gbt_ctx *ctx, const uint32_t *packed, int32_t bits, int
             const int32_t n_children = n_nodes - first_child;
             const bool uni_w = uniform_h && !ctx->hist_runtime_bits;   // the kernels with a row-count form
             const int32_t hq_uniform = (int32_t)llrint((double)h_value * scale[1]);
-            const PlanHistRule rule = hist_rule(ctx, pl, F, B, gbt_histw_max_rows(uni_w));
+            const PlanHistRule rule = hist_rule(ctx, pl, F, B, bits, gbt_histw_max_rows(uni_w));
             const uint32_t rpj = pick_rows_per_job(rule, built);
             // Jobs add into a histogram that must start at zero, except where a node is one row piece: its jobs
             // store every bin of their tile.  (The sibling's histogram is stored bin by bin by the evaluation's

@@ -206,11 +206,9 @@ struct PlanJob {             // what the children of partition job k need of its
 };
 // How the rows of a level's built nodes are cut into histogram jobs: pieces of at most rows_per_job rows of a node, a job
 // per piece and column tile.  Short pieces spread the rows over the chip, long ones merge fewer histograms into HBM (two
-// 64-bit atomics per bin; merge_bins has made them 2.5 times as fast since these weights were fitted, but with the second one
-// halved or quartered 1M x 28 x 256 is slower, not faster).  Both sides in rows a compute unit could have
-// added instead (an element takes one 0.165 ns, whatever the kernel's form):
+// 64-bit atomics per bin).  Both sides in rows a compute unit could have added instead:
 //   adding   the busiest compute unit's share: the longest piece, or the average job times the jobs of a compute unit;
-//   merging  jobs * merge, merge = 0.15 * bins (hist_rule; a node of one piece stores its bins: a quarter of that).
+//   merging  jobs * merge (hist_rule; a node of one piece stores its bins: a quarter of that).
 // With equal pieces and fewer jobs than compute units the best length is sqrt(rows * tiles * merge); the candidates are
 // that length times 2^(-1) .. 2^(7/8), because what decides near it is how the number of jobs falls on the compute units
 // (5M x 30 bytes, us per round with a fixed number of jobs per launch: 250 jobs 1790, 300 2012, 500 1987, 560 2184).
