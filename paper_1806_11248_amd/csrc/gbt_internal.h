@@ -341,9 +341,10 @@ constexpr int gbt_histw_window(int bits) {
 // What a tile of ft of the F columns costs a row, in slots (an element's field, address and atomic).
 //   bytes        every slot of a window of sixteen, used or not (hist_b8_kernel)
 //   other widths a lane takes a window's share of a row, which costs it about ten slots beside its columns; where all windows are
-//                full nothing asks whether a column is there, a third less.  Not less than the line of 128 bytes that a tile
-//                reads of a longer row; and where rows are gathered (gathered: the bytes of their matrix) from past the last
-//                cache, that line comes from HBM for every tile.
+//                full nothing asks whether a column is there, a third less.  (Of four full windows the lanes meet more often in
+//                a bank, those of 31 or 32 columns the most.)  Not less than the line of 128 bytes that a tile reads of a longer
+//                row, dearer the further the rows are apart; and where rows are gathered (gathered: the bytes of their matrix) from
+//                past the last cache, that line comes from HBM for every tile.
 // us of a root, general pairs: 1M x 100 x 6 bits in two tiles of 50 118, four of 25 88, five of 20 (full) 53; 1M x 52 x 9 bits, three of
 // 18 84, four of 13 (full) 53; 500,000 x 1000 x 6 bits, 13 of 77 310, 25 of 40 (full) 242, 50 of 20 (full, a line each) 342.  A round
 // that gathers, equal hessians: 10M x 50 x 9 bits (560 MB), four tiles of 13 3514, two of 25 3096; a third of its rows 1166 and (20) 1208.
@@ -351,15 +352,15 @@ constexpr double kLastCacheBytes = 256e6;
 inline double gbt_tile_cost(int ft, int F, int bits, double gathered) {
     const int E = gbt_histw_window(bits), windows = ft <= E ? 1 : ft <= 2 * E ? 2 : GBT_HISTW_WINDOWS;
     if (bits == 8) return (ft + E - 1) / E * E;
-    const double full = windows == 1 ? 0.67 : windows == 2 ? 0.7 : 0.65;
+    const double full = windows == 1 ? 0.67 : windows == 2 ? 0.69 : E > 24 ? 0.85 : 0.74, row_bytes = (double)F * bits / 8.0;
     const double slots = ft == windows * E ? windows * (10 + E) * full : windows * (10 + (ft + windows - 1) / windows);
-    const double line = 35.0 * std::min(1.0, (double)F * bits / 2048.0);
+    const double line = 35.0 * std::min(1.0, row_bytes / 256.0) + 10.0 * std::min(1.0, row_bytes / 1500.0);
     return (slots > line ? slots : line) + (gathered > kLastCacheBytes ? 30.0 : 0.0);
 }
 // Columns of a tile, ft_max at most (the last tile has what is left, and is waited for as long as for the others): of the even splits,
-// and of tiles of one, two or four full windows, those that cost a row least.  Four windows of 31 or 32 columns are left out: they
-// meet in the same LDS banks (666,666 x 150 x 3 bits, root, 128 and 22 columns 103 us, 64 at a time 56, 32 at a time 64).  Over 64 shapes of 1 to 10
-// bits, 40 to 1000 columns, what is taken is 1.03 times as slow as the best of some fifteen tiles on average.
+// and of tiles of one, two or four full windows, those that cost a row least.  us of a root, 666,666 x 150 x 3 bits: tiles of 128 and 22
+// columns 103, of 64 56, of 32 64.  Over 104 shapes of 1 to 10 bits, 40 to 2000 columns, what is taken is 1.03 times as slow as
+// the best of some fifteen tiles on average, 1.13 at most.
 // Bytes: more tiles than needed cost a pass over the pairs each, and are taken where they save a fifth of the slots (with full
 // windows only, 1M x 50 77 instead of 69 us).
 inline int gbt_tile_columns(int F, int bits, int ft_max, double gathered) {
@@ -376,7 +377,7 @@ inline int gbt_tile_columns(int F, int bits, int ft_max, double gathered) {
     };
     const int nt_min = (F + ft_max - 1) / ft_max, E = gbt_histw_window(bits);
     for (int nt = nt_min; nt <= nt_min + 8 && nt <= F; ++nt) consider((F + nt - 1) / nt);
-    for (int windows = 1; bits != 8 && windows <= (E > 24 ? 2 : GBT_HISTW_WINDOWS); windows *= 2) consider(windows * E);
+    for (int windows = 1; bits != 8 && windows <= GBT_HISTW_WINDOWS; windows *= 2) consider(windows * E);
     return best;
 }
 int gbt_histw_max_rows(bool uniform_h);

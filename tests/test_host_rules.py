@@ -190,25 +190,25 @@ def test_bound_of_a_levels_evaluation_records(rules):
 
 @pytest.mark.parametrize("bits", [b for b in range(1, 17) if b != 8])
 def test_column_tiles_by_the_slots_the_kernel_issues(rules, bits):
-    """A tile costs the slots of its lanes, one, two or four, a third less where all are full, and ten per lane; a long row's
-    tile at least its line, and one more where the rows come from HBM; the last tile no less than the others.  No even split up to
-    eight tiles past the fewest, nor full windows, cost less than the tiles taken."""
+    """A tile costs the slots of its lanes, one, two or four, less where all are full, and ten per lane; at least its line of a long
+    row, and one more where the rows come from HBM; the last tile no less than the others.  No even split up to eight tiles past
+    the fewest, nor full windows, cost less than the tiles taken."""
     rules.tile_columns.argtypes = [C.c_int] * 3 + [C.c_double]
     E = rules.window(bits)
-    full = {1: 0.67, 2: 0.7, 4: 0.65}
-    windows = [w for w in full if w < 4 or E < 31]
+    full = {1: 0.67, 2: 0.69, 4: 0.74 if E <= 24 else 0.85}
 
     def cost(F, ft, far):
         def tile(t):
             lanes = 1 if t <= E else 2 if t <= 2 * E else 4
             slots = lanes * (10 + -(-t // lanes)) * (full[lanes] if t == lanes * E else 1)
-            return max(slots, 35 * min(1, F * bits / 2048)) + 30 * far
+            row = F * bits / 8
+            return max(slots, 35 * min(1, row / 256) + 10 * min(1, row / 1500)) + 30 * far
         return (-(-F // ft) - 1) * tile(ft) + max(tile(ft), tile((F - 1) % ft + 1))
 
     for F in [*range(1, 420), 700, 1000, 2000, 5001, 1 << 20]:
         for ft_max in {min(F, m) for m in (1, 2, 5, E - 1, E, E + 7, 2 * E, 4 * E)} - {0}:
             least = -(-F // ft_max)
-            others = [-(-F // nt) for nt in range(least, min(least + 8, F) + 1)] + [w * E for w in windows if w * E <= ft_max]
+            others = [-(-F // nt) for nt in range(least, min(least + 8, F) + 1)] + [w * E for w in full if w * E <= ft_max]
             for far in (False, True):
                 ft = rules.tile_columns(F, bits, ft_max, 1e9 * far)
                 assert 1 <= ft <= ft_max <= 4 * E
@@ -218,9 +218,10 @@ def test_column_tiles_by_the_slots_the_kernel_issues(rules, bits):
 def test_column_tiles_of_known_shapes(rules):
     rules.tile_columns.argtypes = [C.c_int] * 3 + [C.c_double]
     # full windows with a ragged last tile: 36 and 52 columns of 9 bits, 100 of 6, a wide matrix
-    assert [rules.tile_columns(*a, 0.0) for a in ((36, 9, 20), (52, 9, 20), (100, 6, 78), (1000, 6, 78))] == [13, 13, 20, 40]
+    assert [rules.tile_columns(*a, 0.0) for a in ((36, 9, 20), (52, 9, 20), (100, 6, 78), (40, 6, 40), (1000, 6, 78), (2000, 6, 80))] == \
+        [13, 13, 20, 20, 40, 80]
     # ... that has no more to wait for than the others: 150 columns of 4 and 1 bits, not in tiles of 124 or 128 and what is left
-    assert [rules.tile_columns(*a, 0.0) for a in ((150, 4, 124), (150, 1, 128), (1000, 4, 124))] == [31, 32, 62]
+    assert [rules.tile_columns(*a, 0.0) for a in ((150, 4, 124), (150, 1, 128), (124, 4, 124), (1000, 4, 124))] == [31, 32, 31, 62]
     # gathered from past the caches: half as many tiles
     assert [rules.tile_columns(50, 9, 25, b) for b in (0.0, 168e6, 560e6)] == [13, 13, 25]
     # bytes: more tiles than needed only where they save a fifth of the slots
