@@ -7,6 +7,8 @@ import subprocess
 import numpy as np
 import pytest
 
+import hist_tiles
+
 SOURCE = r"""
 #include "gbt_internal.h"
 #include "kernels_split.hip"
@@ -226,3 +228,12 @@ def test_column_tiles_of_known_shapes(rules):
     assert [rules.tile_columns(50, 9, 25, b) for b in (0.0, 168e6, 560e6)] == [13, 13, 25]
     # bytes: more tiles than needed only where they save a fifth of the slots
     assert [rules.tile_columns(*a, 0.0) for a in ((33, 8, 19), (50, 8, 19), (70, 8, 64), (400, 8, 38))] == [11, 13, 35, 31]
+
+
+def test_column_tiles_the_kernel_tests_count_on(rules):
+    rules.tile_columns.argtypes = [C.c_int] * 3 + [C.c_double]
+    for table, windows, gathered in ((hist_tiles.TWO, 2, 0), (hist_tiles.FOUR, 4, 0), (hist_tiles.FOUR_GATHERED, 4, hist_tiles.GATHERED_BYTES)):
+        for bits, F in table.items():
+            E = rules.window(bits)
+            ft = rules.tile_columns(F, bits, min(F, 4 * E), gathered)
+            assert ft == windows * E and windows * E > F % ft > windows // 2 * E, (bits, F, ft)
