@@ -86,9 +86,10 @@ __device__ inline void wave_sync() {
 // side.  So the limit follows from `dear`, the keys of all features that would be sorted for their own sake: 8 columns of
 // 10M dates in 64 bins, 1.3 ms, sorted 2.1; 30 columns of 3M narrow normals in 16 bins, 1.6 and 2.3.
 constexpr uint64_t kCachedKeys = 1ull << 25;
-// From here on (eight tiles per workgroup on 256 compute units) frequent keys are looked for and runs are of equal work: 3 and 1 us
-// of the sample kernel, which 0.6M keys (the call 220 us) do not gain back.
-constexpr uint64_t kManyKeys = 1ull << 24;
+// Tiles per workgroup of the count from which on (`many`) frequent keys are looked for and runs are of equal work: 3 and 1 us of the
+// sample kernel, which 0.6M keys (the call 220 us) do not gain back.  The host says so: kernels that look up the number of keys wait
+// for it (20,000 x 13, categories and numbers, collect 8.7 us and so 8.4).
+constexpr int64_t kManyTiles = 8;
 __device__ inline uint64_t work_limit(uint64_t tuned, const uint64_t *seg_off, int F, int f, uint64_t dear, bool discrete) {
     const uint64_t len = seg_off[f + 1] - seg_off[f], reads = (1ull << 20) + (len > dear ? len : dear) / 32;
     return tuned ? tuned : discrete || seg_off[F] > kCachedKeys ? reads : reads * 5 / 2;
@@ -124,7 +125,7 @@ __device__ inline int sample_bound(const uint32_t *v, int lo, int hi, Less &&les
 
 // (With 80 scalar registers or fewer two workgroups fit a compute unit: 512 columns of 30,000 in 72 us, with 88 in 96.)
 __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) void sel_sample_kernel(
-    const uint32_t *__restrict__ keys, const uint64_t *__restrict__ seg_off, int B, SelArrays A, uint64_t work_tuned) {
+    const uint32_t *__restrict__ keys, const uint64_t *__restrict__ seg_off, int B, SelArrays A, uint64_t work_tuned, bool many) {
     __shared__ uint32_t v[kSampleMax];
     __shared__ uint32_t per_seg[kSegs];   // sampled keys of an interval, then its first cell and shift
     __shared__ uint64_t heads[kSampleMax / 64];   // bits: a cell's first sampled key
@@ -220,7 +221,7 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) voi
         if ((tid & 63) == 0) heads[j >> 6] = m;
     }
     __syncthreads();   // (and `rep` is clear)
-    if (discrete && seg_off[gridDim.x] >= kManyKeys)
+    if (discrete && many)
         for (int j = tid; j < (int)present; j += kSelBlock) {
             const uint32_t k = v[j];
             if (j > 0 && v[j - 1] == k) continue;
@@ -281,7 +282,7 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) voi
         A.cost[f] = cost < 4e9f ? (uint32_t)cost : 4000000000u;
         const bool dear = A.cost[f] > work_limit(work_tuned, seg_off, gridDim.x, f, 0, discrete);
         if (dear) atomicAdd(A.dear, (unsigned long long)len);
-        if (seg_off[gridDim.x] >= kManyKeys) atomicOr(&A.mix[0], (discrete ? 2u : 1u) | (dear ? 4u : 0u));
+        if (many) atomicOr(&A.mix[0], (discrete ? 2u : 1u) | (dear ? 4u : 0u));
         A.n_cells[f] = total;
     }
     // what the next kernels read (behind the last barrier: none waits for these stores)
@@ -303,7 +304,7 @@ typedef uint32_t sel_u32x4 __attribute__((ext_vector_type(4), aligned(4)));   //
 // feature's tiles weigh what the kernel says (0: nothing to do there).  A table of 115M rows with 8 columns of categories and 5
 // of numbers, equal runs and runs of equal work: count 1.69 and 1.46 ms, collect 1.14 and 0.89, the whole call 7.96 and 7.41.
 // The shares cost 7 us a launch, so not where all features are of one kind (`mix`, a bit per kind, left empty where there are
-// fewer than kManyKeys keys); and up to a feature per thread.
+// fewer than kManyTiles); and up to a feature per thread.
 struct TileShares {
     uint32_t tmp[kSelBlock / 64], edge[2];
     int first;
@@ -395,21 +396,21 @@ __device__ inline void for_each_key(const uint32_t *p, uint64_t k0, uint64_t k1,
 __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) void sel_count_kernel(const uint32_t *__restrict__ keys,
                                                               const uint64_t *__restrict__ seg_off,
                                                               const uint32_t *__restrict__ blk_off, int F, SelArrays A,
-                                                              uint64_t work_tuned) {
+                                                              uint64_t work_tuned, bool many) {
     extern __shared__ uint32_t cnt[];   // cap words: the counters, as many copies as fit (a lane adds to one of them);
                                         // a discrete feature's keys and marks in front of them
     __shared__ uint32_t seg[kSegs];
     __shared__ TileShares shares;
     // (a discrete feature's key: one more read, and lanes that meet on few counters)
-    TileRun run(blk_off, F, A.mix[0], &shares, [&](int f) __attribute__((always_inline)) -> uint32_t {
+    TileRun run(blk_off, F, many ? A.mix[0] : 0u, &shares, [&](int f) __attribute__((always_inline)) -> uint32_t {
         const bool discrete = A.kind[f] & kKindDiscrete;
         return A.cost[f] > work_limit(work_tuned, seg_off, F, f, *A.dear, discrete) ? 0u : discrete ? 3u : 2u;
     });
     uint64_t k0, k1;
     while (run.next(blk_off, seg_off, &k0, &k1)) {
         const int f = run.f;
-        const uint32_t nc = A.n_cells[f];
-        const bool discrete = A.kind[f] & kKindDiscrete;
+        const uint32_t nc = A.n_cells[f], kind = A.kind[f];
+        const bool discrete = kind & kKindDiscrete;
         if (A.cost[f] > work_limit(work_tuned, seg_off, F, f, *A.dear, discrete)) continue;
         uint32_t *rep = cnt, *counters = discrete ? cnt + nc : cnt;   // rep: key of a cell
         uint32_t copies = ((uint32_t)A.cap - (discrete ? nc : 0u)) / nc;
@@ -435,7 +436,7 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) voi
             };
             // The frequent key (none: kMissingKey) is counted in a register: lanes that hold it would take turns on one counter.  The
             // table of TileRun, count: 1.46 ms without, 1.32 with it.  An eighth of the sample: below it few lanes of a copy meet.
-            const uint32_t at = A.kind[f] >> kKindHotShift, hot = at ? A.sample[(uint64_t)f * A.sample_cap + at - 1u] : kMissingKey;
+            const uint32_t at = kind >> kKindHotShift, hot = at ? A.sample[(uint64_t)f * A.sample_cap + at - 1u] : kMissingKey;
             uint32_t times = 0;
             for_each_key(p, k0, k1, [&](uint32_t k) {
                 if (k == hot) ++times;
@@ -466,7 +467,7 @@ __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80))) voi
 
 // ---- pick -------------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kSelBlock) void sel_pick_kernel(const uint64_t *__restrict__ seg_off, SelArrays A, int B,
-                                                             uint32_t *__restrict__ present, uint64_t work_tuned) {
+                                                             uint32_t *__restrict__ present, uint64_t work_tuned, bool many) {
     __shared__ uint32_t seg[kSegs];
     __shared__ uint32_t cell[kSelBinsMax];   // of a slot
     __shared__ uint32_t tmp[kSelBlock / 64];
@@ -476,7 +477,7 @@ __global__ __launch_bounds__(kSelBlock) void sel_pick_kernel(const uint64_t *__r
             A.n_slots[f] = 0;
             A.mode[f] = kSelSorted;
             A.flag[0] = 1;
-            if (seg_off[gridDim.x] >= kManyKeys) atomicOr(&A.mix[1], 2u);
+            if (many) atomicOr(&A.mix[1], 2u);
         }
         return;
     }
@@ -580,7 +581,7 @@ __global__ __launch_bounds__(kSelBlock) void sel_pick_kernel(const uint64_t *__r
     if (tid == 0) {
         A.kind[f] = (discrete ? kKindDiscrete : 0u) | (collect ? 0u : kKindNoCollect);
         A.n_slots[f] = n_slots;
-        if (seg_off[gridDim.x] >= kManyKeys) atomicOr(&A.mix[1], n_slots && collect ? 1u : 2u);
+        if (many) atomicOr(&A.mix[1], n_slots && collect ? 1u : 2u);
         A.mode[f] = order ? kSelOrder : kSelDistinct;
         present[f] = m;
     }
@@ -593,13 +594,13 @@ constexpr int kCollectPer = 16;   // keys per thread and step
 __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_num_sgpr(80), amdgpu_waves_per_eu(8))) void sel_collect_kernel(const uint32_t *__restrict__ keys,
                                                                 const uint64_t *__restrict__ seg_off,
                                                                 const uint32_t *__restrict__ blk_off, int F, int B,
-                                                                SelArrays A, uint32_t *__restrict__ out) {
+                                                                SelArrays A, uint32_t *__restrict__ out, bool many) {
     extern __shared__ uint32_t dyn[];
     __shared__ uint32_t seg[kSegs];
     uint32_t *heavy = dyn, *cnt = dyn + B, *base = dyn + 2 * B;
     uint16_t *slot_of = (uint16_t *)(dyn + 3 * B);   // cap
     __shared__ TileShares shares;
-    TileRun run(blk_off, F, A.mix[1], &shares, [&](int f) __attribute__((always_inline)) -> uint32_t {
+    TileRun run(blk_off, F, many ? A.mix[1] : 0u, &shares, [&](int f) __attribute__((always_inline)) -> uint32_t {
         return A.n_slots[f] == 0 || (A.kind[f] & kKindNoCollect) ? 0u : 1u;
     });
     uint64_t k0, k1;
@@ -1215,10 +1216,11 @@ hipError_t gbt_launch_select(gbt_ctx *ctx, const uint32_t *keys, uint32_t *colle
     // two workgroups of 1024 threads per compute unit, and no more than there are tiles to share out
     const int64_t tiles = n_values / kSortTile + F;
     const int grid = (int)(tiles < 2 * ctx->num_cu ? (tiles > 0 ? tiles : 1) : 2 * ctx->num_cu);
-    sel_sample_kernel<<<F, kSelBlock, 0, s>>>(keys, seg_off, B, A, by_sample);
-    sel_count_kernel<<<grid, kSelBlock, lds_count, s>>>(keys, seg_off, blk_off, F, A, by_sample);
-    sel_pick_kernel<<<F, kSelBlock, 0, s>>>(seg_off, A, B, present, by_sample);
-    sel_collect_kernel<<<grid, kSelBlock, lds_collect, s>>>(keys, seg_off, blk_off, F, B, A, collected);
+    const bool many = n_values >= kManyTiles * kSortTile * 2 * ctx->num_cu;
+    sel_sample_kernel<<<F, kSelBlock, 0, s>>>(keys, seg_off, B, A, by_sample, many);
+    sel_count_kernel<<<grid, kSelBlock, lds_count, s>>>(keys, seg_off, blk_off, F, A, by_sample, many);
+    sel_pick_kernel<<<F, kSelBlock, 0, s>>>(seg_off, A, B, present, by_sample, many);
+    sel_collect_kernel<<<grid, kSelBlock, lds_collect, s>>>(keys, seg_off, blk_off, F, B, A, collected, many);
     sel_distinct_kernel<<<F, kSelBlock, lds_distinct, s>>>(seg_off, B, A, collected, cuts, nb, work);
     const uint64_t all = (uint64_t)F * B;
     auto at_most = [&](uint64_t n, int per_cu) { return (unsigned)(n < (uint64_t)per_cu * ctx->num_cu ? n : (uint64_t)per_cu * ctx->num_cu); };
