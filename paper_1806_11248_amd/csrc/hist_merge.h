@@ -6,13 +6,13 @@
 
 namespace {
 
-// i / d where i * d < 2^32 (a workgroup's bins in units of eight: under 2^13, tiles of under 2^15 columns): a multiplication
-// with ceil(2^32 / d), which is off by less than i * d / 2^32.  (A division by a number that is not known takes some twenty
-// instructions, for every word of a merge.)
+// i / d for i < 2^21, d < 2^16: (i + 1/2) / d is at least 1 / 2d from a whole number, and v_rcp_f32 (1 ulp) with one rounding is off by
+// less than i / d * 2^-22.  (A division of whole numbers takes some twenty-five instructions, and a workgroup of 1024 threads issues
+// one of its own sixteen times before a short job has begun: see merge_bins.)
 struct SmallDiv {
-    uint32_t d, inv;
-    __device__ explicit SmallDiv(uint32_t by) : d(by), inv(by > 1u ? 0xffffffffu / by + 1u : 0u) {}
-    __device__ uint32_t operator()(uint32_t i) const { return d > 1u ? __umulhi(i, inv) : i; }
+    float inv;
+    __device__ explicit SmallDiv(uint32_t d) : inv(__builtin_amdgcn_rcpf((float)d)) {}
+    __device__ uint32_t operator()(uint32_t i) const { return (uint32_t)__builtin_fmaf((float)i, inv, 0.5f * inv); }
 };
 
 // A tile of ft columns of B bins, out[(t * B + b) * 2] its g and the next word its h: adds what bin(t, b, g, h) yields, or,
@@ -24,35 +24,40 @@ struct SmallDiv {
 // bytes of 256 bins, 230 workgroups (1.65M atomics): 24 us a lane per bin, 12.5 with (1), 9.5 with both.  With lines counted from the
 // column's first bin, which is a line's first only where B is a multiple of eight, 255 bins took 39 us a call, and so
 // 36 (256 bins 33).
-// (3) The four lines of an instruction belong to four columns (of tiles that have them):
-// where the bins of a column lie in one LDS bank, eight of them meet there and not 32.
+// (3) The four lines of an instruction belong to four columns (of tiles that have them): where the bins of a column lie in one LDS
+// bank, eight of them meet there and not 32.
+// Small tables: a launch of few short jobs takes what one workgroup has to issue, so groups of lanes are counted in scalar registers
+// and nothing is divided: 5,000 x 19 x 6 bits, us a launch, 5.4 with two divisions here and one in the windows' kernel, 4.8 without
+// (4.6 a lane per bin); 5,000 x 4 bytes 4.95 and 4.75; rounds of 5,000 to 120,000 rows x 4 to 60 columns 1.02 times as fast.
 template <typename Bin>
 __device__ __forceinline__ void merge_bins(int ft, int B, int64_t *out, int block, bool exclusive, Bin &&bin) {
     const uint32_t lead = (uint32_t)((uintptr_t)out >> 4) & 7u;   // bins of a line before the tile's first
-    const uint32_t per_col = lead | ((uint32_t)B & 7u) ? ((uint32_t)B + 14u) >> 3 : (uint32_t)B >> 3, units = (uint32_t)ft * per_col;   // lines a column can touch, in all
+    const uint32_t per_col = lead | ((uint32_t)B & 7u) ? ((uint32_t)B + 14u) >> 3 : (uint32_t)B >> 3;   // lines a column can touch
+    const uint32_t units = (uint32_t)ft * per_col;
     const SmallDiv by_cols((uint32_t)ft);
+    const uint32_t lane = threadIdx.x & 63u, waves = (uint32_t)block >> 6;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (!exclusive) {
-        const uint32_t groups = (units + 3u) >> 2, first = (blockIdx.x * 2654435761u >> 8) % groups;
-        for (uint32_t k = threadIdx.x; k < 64u * groups; k += (uint32_t)block) {
-            uint32_t group = (k >> 6) + first;
-            group = group >= groups ? group - groups : group;
-            const uint32_t unit = 4u * group + ((k >> 4) & 3u), c = by_cols(unit), t = unit - c * (uint32_t)ft;
-            const uint32_t b = 8u * c + ((k >> 1) & 7u) - ((lead + t * (uint32_t)B) & 7u);
+        const uint32_t groups = (units + 3u) >> 2, first = __umulhi(blockIdx.x * 2654435761u, groups);
+        for (uint32_t q = wave; q < groups; q += waves) {
+            const uint32_t group = q + first < groups ? q + first : q + first - groups;
+            const uint32_t unit = 4u * group + (lane >> 4), c = by_cols(unit), t = unit - __umul24(c, (uint32_t)ft);
+            const uint32_t b = 8u * c + ((lane >> 1) & 7u) - ((lead + __umul24(t, (uint32_t)B)) & 7u);
             if (unit >= units || b >= (uint32_t)B) continue;
             int64_t g = 0, h = 0;
             bin(t, b, g, h);
-            const int64_t v = (k & 1u) ? h : g;
-            if (v != 0) atomicAdd((unsigned long long *)(out + 2u * (t * (uint32_t)B + b) + (k & 1u)), (unsigned long long)v);
+            const int64_t v = (lane & 1u) ? h : g;
+            if (v != 0) atomicAdd((unsigned long long *)(out + 2u * (__umul24(t, (uint32_t)B) + b) + (lane & 1u)), (unsigned long long)v);
         }
         return;
     }
-    for (uint32_t k = threadIdx.x; k < 8u * units; k += (uint32_t)block) {
-        const uint32_t unit = k >> 3, c = by_cols(unit), t = unit - c * (uint32_t)ft;
-        const uint32_t b = 8u * c + (k & 7u) - ((lead + t * (uint32_t)B) & 7u);
-        if (b >= (uint32_t)B) continue;
+    for (uint32_t q = wave; 8u * q < units; q += waves) {
+        const uint32_t unit = 8u * q + (lane >> 3), c = by_cols(unit), t = unit - __umul24(c, (uint32_t)ft);
+        const uint32_t b = 8u * c + (lane & 7u) - ((lead + __umul24(t, (uint32_t)B)) & 7u);
+        if (unit >= units || b >= (uint32_t)B) continue;
         int64_t g = 0, h = 0;
         bin(t, b, g, h);
-        *(longlong2 *)(out + 2u * (t * (uint32_t)B + b)) = make_longlong2(g, h);
+        *(longlong2 *)(out + 2u * (__umul24(t, (uint32_t)B) + b)) = make_longlong2(g, h);
     }
 }
 

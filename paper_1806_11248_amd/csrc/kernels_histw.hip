@@ -101,9 +101,10 @@ __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
     // a row's windows (one, two or four) to neighbouring lanes; each begins at another of its columns than its neighbours'
     // and goes on from its first one behind its last
     const int log_win = ft <= E ? 0 : ft <= 2 * E ? 1 : 2, win = (int)threadIdx.x & ((1 << log_win) - 1);
-    const int c0 = (ft * win) >> log_win, cnt = ((ft * (win + 1)) >> log_win) - c0;   // this lane's columns
+    const int c0 = __umul24(ft, win) >> log_win, cnt = ((int)(__umul24(ft, win) + ft) >> log_win) - c0;   // this lane's columns
     const int most = (ft + (1 << log_win) - 1) >> log_win;                            // of any lane
-    const int start = (int)((threadIdx.x & 63) >> log_win) % cnt, until = cnt - start;   // slots before its first column
+    const int turn = (int)((threadIdx.x & 63) >> log_win), start = turn - (int)__umul24(SmallDiv((uint32_t)cnt)((uint32_t)turn), cnt);
+    const int until = cnt - start;   // slots before its first column
     const int n_step = (int)(blockDim.x >> log_win);
     using Words = std::conditional_t<SHORT, w_u32x2, w_u32x4>;
     const int64_t last_at = n_words * 4 - (int64_t)sizeof(Words);   // the last byte from which they can be read (the launcher has made sure of one)
@@ -111,8 +112,8 @@ __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
     uint32_t keep[4];   // the bits that come before the first column
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const int k = until * BITS - 32 * j;
-        keep[j] = k >= 32 ? 0xffffffffu : k <= 0 ? 0u : (1u << k) - 1u;
+        const int k = (int)__umul24(until, BITS) - 32 * j;
+        keep[j] = (uint32_t)((0xffffffffull << std::min(std::max(k, 0), 32)) >> 32);
     }
 
     auto row_id = [&](uint32_t i) __attribute__((always_inline)) -> uint64_t {
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
         return LIST ? (uint64_t)row_idx[pos] : pos;
     };
     const uint64_t lane_bit = ((uint64_t)job.f0 + (uint32_t)(SHORT ? c0 : c0 + start)) * BITS;
-    const int back = cnt * BITS;   // from the first slot's bit to where the window's first column would follow its last
+    const int back = (int)__umul24(cnt, BITS);   // from the first slot's bit to where the window's first column would follow its last
     // Sixteen bytes from the byte of bit `at` on.  What lies outside the buffer holds no bit that is used: the sixteen bytes
     // nearest to it are read, and put in their places when they are used.
     auto byte_in = [&](int64_t at) __attribute__((always_inline)) {
