@@ -598,10 +598,13 @@ int gbt_sparse_hist_max_rows();
 // tile_rows = gbt_sparse_part_tile() rows).  cursor: two 64-bit words per job, cleared here; afterwards the low
 // word of cursor[2 * j] is job j's number of left rows.  move == false: only that count.
 // Rows of a tile, 128 to 1024: as many as leave the average tile's entries an eighth of room in the staging window, for a tile that
-// does not fit reads and copies its rows in place; and no more than give every compute unit a tile.  (Rows that do not fit 128 at a
-// time are read in place anyway.)  us per tree with tiles of 1024 rows and so: 5M x 50 with 17.5 entries a row, depth 6 2684 and 1267;
-// 1M x 200 with 40, depth 7 1801 and 1188, with 80, depth 6 2859 and 1757; 2M x 40 with 14, depth 8 1551 and 799; 400,000 x 300 with 15
-// (32-bit ids), depth 6 902 and 646; 100,000 x 50 with 10, depth 6 326 and 309.
+// does not fit reads and copies its rows in place (rows that do not fit 128 at a time are read in place anyway); and 512 or 256 on
+// few rows, where they are short of tiles.  Not fewer: a node's tiles take turns on its cursors, 12 ns for an atomic.
+// us per tree with tiles of 1024 rows and as few as fit: 5M x 50 with 17.5 entries a row, depth 6 2684 and 1267; 1M x 200 with 40,
+// depth 7 1801 and 1188, with 80, depth 6 2859 and 1757; 2M x 40 with 14, depth 8 1551 and 799; 400,000 x 300 with 15 (32-bit ids),
+// depth 6 902 and 646.  With 128, 256, 512 and 1024 rows, depth 6, two entries a row: 5,000 rows 211, 209, 211, 220; 25,000 225, 220,
+// 218, 228; 50,000 239, 228, 221, 228; 100,000 281, 244, 229, 234; 200,000 335, 284, 248, 243; ten entries: 100,000 277, 246, 240, 249;
+// 200,000 332, 288, 261, 264.
 int gbt_sparse_part_tile(const gbt_ctx *ctx, int64_t n, int64_t nnz, int ent_bytes);
 hipError_t gbt_launch_sparse_partition(hipStream_t s, const uint32_t *src_rowptr, const void *src_ent, int ent_bytes,
                                        const int32_t *src_gq, uint32_t *dst_rowptr, void *dst_ent,

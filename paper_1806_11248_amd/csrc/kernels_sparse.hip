@@ -855,7 +855,8 @@ int gbt_sparse_part_tile(const gbt_ctx *ctx, int64_t n, int64_t nnz, int ent_byt
     int rows = 1024;
     while (rows > 128 && rows * words * 1.15 > kSpStage / 2) rows /= 2;
     if (rows * words * 1.15 > kSpStage / 2) rows = 1024;
-    while (rows > 128 && n < (int64_t)rows * ctx->num_cu) rows /= 2;
+    if (rows > 512 && n < (int64_t)512 * ctx->num_cu) rows = 512;
+    if (rows > 256 && n < (int64_t)64 * ctx->num_cu) rows = 256;
     return rows;
 }
 
