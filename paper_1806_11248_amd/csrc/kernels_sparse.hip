@@ -253,7 +253,7 @@ __global__ __launch_bounds__(BLOCK) void sparse_hist_kernel(const uint32_t *__re
     }
     __syncthreads();
     const bool exclusive = UNI && job.pad0 == 1u;
-    merge_bins(1, (int)glen, out, BLOCK, exclusive, [&](uint32_t, uint32_t i, int64_t &g, int64_t &h) __attribute__((always_inline)) {
+    merge_ids(glen, out, BLOCK, exclusive, [&](uint32_t i, int64_t &g, int64_t &h) __attribute__((always_inline)) {
         const unsigned long long v = lds[i];
         if (UNI) {
             const int64_t rows = (int64_t)(v & kSpUniRows);
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(BLOCK) void sparse_hist32_kernel(const uint32_t *__
         }
     }
     __syncthreads();
-    merge_bins(1, (int)glen, out, BLOCK, false, [&](uint32_t, uint32_t i, int64_t &g, int64_t &h) __attribute__((always_inline)) {
+    merge_ids(glen, out, BLOCK, false, [&](uint32_t i, int64_t &g, int64_t &h) __attribute__((always_inline)) {
         const unsigned long long w = lds[i];
         g = (int64_t)w >> kHShift;
         h = (int64_t)(w & kHMask);
