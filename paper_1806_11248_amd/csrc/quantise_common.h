@@ -85,7 +85,8 @@ struct SelArrays {
     uint32_t *counts;    // [F][cap] keys per cell
     uint32_t *rep;       // [F][kDiscreteCells] a discrete feature's cells: a key of the cell (kMissingKey: none seen yet) ...
     uint8_t *mixed;      // [F][kDiscreteCells] ... and whether the cell holds another one as well
-    uint32_t *kind;      // [F] bit 0: discrete (few distinct keys in the sample), bit 1: nothing of it has to be collected
+    uint32_t *kind;      // [F] bit 0: discrete (few distinct keys in the sample), bit 1: nothing of it has to be collected;
+                         // until the pick, bits 8 up: 1 + the place of its frequent key in the sample
     uint16_t *slot_of;   // [F][cap] the slot of a cell that is looked into, 0xffff: none
     SelSlot *slots;      // [F][B]
     uint32_t *n_slots;   // [F]
