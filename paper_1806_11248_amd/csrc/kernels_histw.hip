@@ -167,8 +167,12 @@ __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
     uint32_t base = lds_base + 8u * (uint32_t)(c0 + start), base2 = base - 8u * (uint32_t)cnt;
     asm volatile("" : "+v"(base), "+v"(base2));
     auto add = [&](const uint32_t (&W)[4], unsigned long long addv, uint32_t hq, auto full) __attribute__((always_inline)) {
-        int n = most;
-        asm volatile("" : "+s"(n));   // (compared where it is needed: a mask per slot, kept, takes all scalar registers)
+        // (Compared where it is needed: a mask per slot, kept, takes all scalar registers.  A lane's own columns by one comparison, the
+        // most of any lane by the group: with both asked for each slot it took eleven instructions and not six, 666,666 x 260 x 9 bits,
+        // root, 222 and 194 us, 2M x 124 x 2 bits 143 and 118.  SHORT has few columns of many slots, and is 4 % slower so.)
+        int n = most, mine = cnt;
+        asm volatile("" : "+s"(n));
+        if constexpr (!SHORT) asm volatile("" : "+v"(mine));
 #pragma unroll
         for (int g0 = 0; g0 < E; g0 += G) {
             if (!full && g0 >= n) break;
@@ -177,7 +181,7 @@ __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
 #pragma unroll
             for (int jj = 0; jj < G; ++jj) {
                 const int j = g0 + jj;
-                if (j < E && (full || j < n)) {
+                if (j < E && (!SHORT || j < n)) {
                     const int pos = j * BITS, wd = pos >> 5, off = pos & 31;
                     uint32_t sv;
                     if (off + BITS <= 32)
@@ -186,7 +190,7 @@ __global__ __launch_bounds__(kHistBlock) void hist_bits_kernel(
                         sv = __builtin_amdgcn_alignbit(W[wd < 3 ? wd + 1 : 3], W[wd], (uint32_t)off) & MASK;
                     if (CLAMP) sv = min(sv, top);
                     addr[jj] = __umul24(sv, fs8) + (j >= until ? base2 : base);
-                    if (full || j + 1 < n || j < cnt) {   // (the windows differ by one column at most)
+                    if (full || (SHORT ? j + 1 < n || j < cnt : __builtin_expect(j < mine, 1))) {
                         if (UNI) ldsw_add(addr[jj], j, addv);
                         else old[jj] = ldsw_add_rtn(addr[jj], j, addv);
                     } else if (!UNI) {
